@@ -1,9 +1,10 @@
-"""ctypes binding over libmate.so (the C ABI of include/mate.h).  Argument marshalling only.
+"""Binding over libmate.so (the C ABI of include/mate.h).  Argument marshalling only.
 
-The raw entry points are exposed under their C names (`mate_build_segments`, ...) taking
-integer addresses; the snake-case helpers below take torch tensors, allocate outputs with
+The raw entry points are exposed under their C names (`mate_build_segments`, ...) through ctypes,
+taking integer addresses; the snake-case helpers below take torch tensors, allocate outputs with
 torch (device memory + current stream are all torch is used for) and raise on any non-zero
-status.  There is no fallback: if the library is missing this module raises on import.
+status.  Their marshalling is native (csrc/bind.cpp): on short sequences the host path is as long
+as the kernels.  There is no fallback: if a library is missing this module raises on import.
 """
 from __future__ import annotations
 
@@ -38,9 +39,13 @@ MATE_KERNEL_OUT_PROJECT_DGRAD, MATE_KERNEL_OUT_PROJECT_WGRAD = 12, 13
 MATE_DENSE_MAX_N = 1024
 MATE_DENSE_PREFERRED_MAX_N = 256
 
-if not os.path.exists(LIB_PATH):
-    raise ImportError(f"{LIB_PATH} is not built; run `python -m paper_2109_04312_amd.build` "
-                      "(there is no CPU fallback)")
+_NATIVE_PATH = os.path.join(_HERE, "_native.so")
+for _path in (LIB_PATH, _NATIVE_PATH):
+    if not os.path.exists(_path):
+        raise ImportError(f"{_path} is not built; run `python -m paper_2109_04312_amd.build` "
+                          "(there is no CPU fallback)")
+from . import _native  # noqa: E402
+
 _lib = C.CDLL(LIB_PATH)
 
 _p, _i, _sz, _f = C.c_void_p, C.c_int, C.c_size_t, C.c_float
@@ -138,20 +143,6 @@ def _stream() -> int:
     return torch.cuda.current_stream().cuda_stream
 
 
-def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return MATE_F32
-    if t.dtype == torch.bfloat16:
-        return MATE_BF16
-    raise TypeError(f"unsupported dtype {t.dtype}")
-
-
-def _dev(t: torch.Tensor, name: str) -> int:
-    if not (t.is_cuda and t.is_contiguous()):
-        raise ValueError(f"{name} must be a contiguous device tensor")
-    return t.data_ptr()
-
-
 @dataclass
 class Segments:
     """Device buffer holding the tables of mate_build_segments for (B, N)."""
@@ -160,40 +151,28 @@ class Segments:
     N: int
 
 
+def _head_kind_host(head_kind, H: int):
+    hk = np.ascontiguousarray(np.asarray(head_kind, dtype=np.uint8))
+    assert hk.shape == (H,)
+    return hk
+
+
+_native.bind({n: C.cast(getattr(_lib, n), C.c_void_p).value for n in EXPORTS}, MateError, _head_kind_host)
+
+
 def build_segments(row_ids: torch.Tensor, col_ids: torch.Tensor, flags: torch.Tensor,
                    out: Segments | None = None, bucketed=None) -> Segments:
     """bucketed = (global_length, radius) builds the tables of the bucketed mode."""
-    B, N = flags.shape
-    assert row_ids.dtype == torch.int32 and col_ids.dtype == torch.int32 and flags.dtype == torch.uint8
-    assert row_ids.shape == (B, N) and col_ids.shape == (B, N)
-    nbytes = mate_segments_bytes(B, N)
-    if nbytes == 0:
-        raise MateError(MATE_ERR_SHAPE, "mate_segments_bytes")
     if out is None:
-        out = Segments(torch.empty(nbytes, dtype=torch.uint8, device=flags.device), B, N)
-    if bucketed is None:
-        _check(mate_build_segments(_dev(row_ids, "row_ids"), _dev(col_ids, "col_ids"),
-                                   _dev(flags, "flags"), B, N, out.buf.data_ptr(), _stream()),
-               "mate_build_segments")
-    else:
-        _check(mate_build_segments_bucketed(_dev(row_ids, "row_ids"), _dev(col_ids, "col_ids"),
-                                            _dev(flags, "flags"), B, N, int(bucketed[0]),
-                                            int(bucketed[1]), out.buf.data_ptr(), _stream()),
-               "mate_build_segments_bucketed")
+        out = Segments(_native.segments_buffer(flags), *flags.shape)
+    G, R = (None, None) if bucketed is None else (int(bucketed[0]), int(bucketed[1]))
+    _native.build_segments(row_ids, col_ids, flags, out.buf, G, R)
     return out
 
 
 def cell_positions(row_ids: torch.Tensor, col_ids: torch.Tensor, flags: torch.Tensor,
                    out: torch.Tensor | None = None) -> torch.Tensor:
-    B, N = flags.shape
-    assert row_ids.dtype == torch.int32 and col_ids.dtype == torch.int32 and flags.dtype == torch.uint8
-    assert row_ids.shape == (B, N) and col_ids.shape == (B, N)
-    if out is None:
-        out = torch.empty((B, N), dtype=torch.int32, device=flags.device)
-    assert out.dtype == torch.int32 and out.shape == (B, N)
-    _check(mate_cell_positions(_dev(row_ids, "row_ids"), _dev(col_ids, "col_ids"), _dev(flags, "flags"),
-                               B, N, _dev(out, "positions"), _stream()), "mate_cell_positions")
-    return out
+    return _native.cell_positions(row_ids, col_ids, flags, out)
 
 
 def segments_export(seg: Segments, view: int) -> dict:
@@ -214,127 +193,38 @@ def segments_export(seg: Segments, view: int) -> dict:
                 counts=counts, window=window)
 
 
-def _head_kind_host(head_kind, H: int):
-    hk = np.ascontiguousarray(np.asarray(head_kind, dtype=np.uint8))
-    assert hk.shape == (H,)
-    return hk
-
-
 def workspace(B, H, N, D, dtype_code, for_bwd, device) -> torch.Tensor:
     n = mate_workspace_bytes(B, H, N, D, dtype_code, int(for_bwd))
     return torch.empty(max(n, 16), dtype=torch.uint8, device=device)
 
 
-def _check_tables(seg: Segments, B: int, N: int):
-    if (seg.B, seg.N) != (B, N) or seg.buf.numel() < mate_segments_bytes(B, N):
-        raise MateError(MATE_ERR_SHAPE, f"segment tables are for (B, N) = ({seg.B}, {seg.N}), tensors for ({B}, {N})")
-
-
 def attn_fwd(q, k, v, seg: Segments, head_kind, scale: float, out=None, lse=None, ws=None):
-    B, H, N, D = q.shape
-    _check_tables(seg, B, N)
-    hk = _head_kind_host(head_kind, H)
-    code = _dtype_code(q)
-    if out is None:
-        out = torch.empty_like(q)
-    if lse is None:
-        lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
-    if ws is None:
-        ws = workspace(B, H, N, D, code, False, q.device)
-    _check(mate_attn_fwd(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), seg.buf.data_ptr(),
-                         hk.ctypes.data, B, H, N, D, code, float(scale), _dev(out, "out"),
-                         _dev(lse, "lse"), ws.data_ptr(), ws.numel(), _stream()),
-           "mate_attn_fwd")
-    return out, lse
+    return _native.attn_fwd(q, k, v, seg, head_kind, scale, out, lse, ws)
 
 
 def attn_bwd(q, k, v, out, lse, dout, seg: Segments, head_kind, scale: float,
              dq=None, dk=None, dv=None, ws=None):
-    B, H, N, D = q.shape
-    _check_tables(seg, B, N)
-    hk = _head_kind_host(head_kind, H)
-    code = _dtype_code(q)
-    dq = torch.empty_like(q) if dq is None else dq
-    dk = torch.empty_like(q) if dk is None else dk
-    dv = torch.empty_like(q) if dv is None else dv
-    if ws is None:
-        ws = workspace(B, H, N, D, code, True, q.device)
-    _check(mate_attn_bwd(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _dev(out, "out"),
-                         _dev(lse, "lse"), _dev(dout, "dout"), seg.buf.data_ptr(),
-                         hk.ctypes.data, B, H, N, D, code, float(scale), _dev(dq, "dq"),
-                         _dev(dk, "dk"), _dev(dv, "dv"), ws.data_ptr(), ws.numel(), _stream()),
-           "mate_attn_bwd")
-    return dq, dk, dv
+    return _native.attn_bwd(q, k, v, out, lse, dout, seg, head_kind, scale, dq, dk, dv, ws)
 
 
 def attn_fwd_dense(q, k, v, row_ids, col_ids, flags, head_kind, scale: float, out=None, lse=None):
     """Dense-mask variant (no segment tables); bf16, N <= MATE_DENSE_MAX_N."""
-    B, H, N, D = q.shape
-    hk = _head_kind_host(head_kind, H)
-    code = _dtype_code(q)
-    if out is None:
-        out = torch.empty_like(q)
-    if lse is None:
-        lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
-    _check(mate_attn_fwd_dense(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _dev(row_ids, "row_ids"),
-                               _dev(col_ids, "col_ids"), _dev(flags, "flags"), hk.ctypes.data,
-                               B, H, N, D, code, float(scale), _dev(out, "out"), _dev(lse, "lse"),
-                               _stream()), "mate_attn_fwd_dense")
-    return out, lse
+    return _native.attn_fwd_dense(q, k, v, row_ids, col_ids, flags, head_kind, scale, out, lse)
 
 
 def attn_bwd_dense(q, k, v, out, lse, dout, row_ids, col_ids, flags, head_kind, scale: float,
                    dq=None, dk=None, dv=None, ws=None):
-    B, H, N, D = q.shape
-    hk = _head_kind_host(head_kind, H)
-    code = _dtype_code(q)
-    dq = torch.empty_like(q) if dq is None else dq
-    dk = torch.empty_like(q) if dk is None else dk
-    dv = torch.empty_like(q) if dv is None else dv
-    if ws is None:
-        ws = torch.empty(max(mate_dense_workspace_bytes(B, H, N), 16), dtype=torch.uint8, device=q.device)
-    _check(mate_attn_bwd_dense(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _dev(out, "out"),
-                               _dev(lse, "lse"), _dev(dout, "dout"), _dev(row_ids, "row_ids"),
-                               _dev(col_ids, "col_ids"), _dev(flags, "flags"), hk.ctypes.data,
-                               B, H, N, D, code, float(scale), _dev(dq, "dq"), _dev(dk, "dk"),
-                               _dev(dv, "dv"), ws.data_ptr(), ws.numel(), _stream()),
-           "mate_attn_bwd_dense")
-    return dq, dk, dv
+    return _native.attn_bwd_dense(q, k, v, out, lse, dout, row_ids, col_ids, flags, head_kind, scale, dq, dk, dv, ws)
 
 
 def qkv_project(x, w_qkv, bias, flags, H: int, q=None, k=None, v=None):
     """x [B,N,E] bf16, w_qkv [3*H*64, E] bf16, bias [3*H*64] float32 or None -> q, k, v [B,H,N,64]."""
-    B, N, E = x.shape
-    assert x.dtype == torch.bfloat16 and w_qkv.dtype == torch.bfloat16 and w_qkv.shape == (3 * H * 64, E)
-    assert flags.dtype == torch.uint8 and flags.shape == (B, N)
-    assert bias is None or (bias.dtype == torch.float32 and bias.shape == (3 * H * 64,))
-    outs = [t if t is not None else torch.empty((B, H, N, 64), dtype=x.dtype, device=x.device) for t in (q, k, v)]
-    for t in outs:
-        assert t.dtype == x.dtype and t.shape == (B, H, N, 64)
-    _check(mate_qkv_project(_dev(x, "x"), _dev(w_qkv, "w_qkv"), _dev(bias, "bias") if bias is not None else None,
-                            _dev(flags, "flags"), B, N, H, E, MATE_BF16, *(_dev(t, "out") for t in outs),
-                            _stream()), "mate_qkv_project")
-    return tuple(outs)
+    return _native.qkv_project(x, w_qkv, bias, flags, H, q, k, v)
 
 
 def out_project(o, w_o, bias, flags, y=None):
     """o [B,H,N,64] bf16, w_o [E, H*64] bf16, bias [E] float32 or None -> y [B,N,E]."""
-    B, H, N, D = o.shape
-    E = w_o.shape[0]
-    assert o.dtype == torch.bfloat16 and w_o.dtype == torch.bfloat16 and w_o.shape == (E, H * 64) and D == 64
-    assert flags.dtype == torch.uint8 and flags.shape == (B, N)
-    assert bias is None or (bias.dtype == torch.float32 and bias.shape == (E,))
-    if y is None:
-        y = torch.empty((B, N, E), dtype=o.dtype, device=o.device)
-    assert y.dtype == o.dtype and y.shape == (B, N, E)
-    _check(mate_out_project(_dev(o, "o"), _dev(w_o, "w_o"), _dev(bias, "bias") if bias is not None else None,
-                            _dev(flags, "flags"), B, N, H, E, MATE_BF16, _dev(y, "y"), _stream()),
-           "mate_out_project")
-    return y
-
-
-def _opt(t, name):
-    return _dev(t, name) if t is not None else None
+    return _native.out_project(o, w_o, bias, flags, y)
 
 
 def project_bwd_workspace(B, N, H, E, device) -> torch.Tensor:
@@ -347,34 +237,12 @@ def project_bwd_workspace(B, N, H, E, device) -> torch.Tensor:
 def qkv_project_bwd(x, w_qkv, flags, dq, dk, dv, want_dx=True, want_dw=True, want_dbias=True, ws=None):
     """Gradients of qkv_project: dx [B,N,E] bf16, dw_qkv [3*H*64,E] float32, dbias [3*H*64] float32
     (None for the ones not wanted)."""
-    B, N, E = x.shape
-    H = dq.shape[1]
-    assert x.dtype == torch.bfloat16 and w_qkv.shape == (3 * H * 64, E) and dq.shape == (B, H, N, 64)
-    assert dk.shape == dq.shape and dv.shape == dq.shape and flags.shape == (B, N)
-    dx = torch.empty_like(x) if want_dx else None
-    dw = torch.empty((3 * H * 64, E), dtype=torch.float32, device=x.device) if want_dw else None
-    db = torch.empty(3 * H * 64, dtype=torch.float32, device=x.device) if want_dbias else None
-    ws = project_bwd_workspace(B, N, H, E, x.device) if ws is None else ws
-    _check(mate_qkv_project_bwd(_dev(x, "x"), _dev(w_qkv, "w_qkv"), _dev(flags, "flags"), _dev(dq, "dq"),
-                                _dev(dk, "dk"), _dev(dv, "dv"), B, N, H, E, MATE_BF16, _opt(dx, "dx"),
-                                _opt(dw, "dw"), _opt(db, "dbias"), ws.data_ptr(), ws.numel(), _stream()),
-           "mate_qkv_project_bwd")
-    return dx, dw, db
+    return _native.qkv_project_bwd(x, w_qkv, flags, dq, dk, dv, want_dx, want_dw, want_dbias, ws)
 
 
 def out_project_bwd(o, w_o, flags, dy, want_do=True, want_dw=True, want_dbias=True, ws=None):
     """Gradients of out_project: d_o [B,H,N,64] bf16, dw_o [E,H*64] float32, dbias [E] float32."""
-    B, H, N, D = o.shape
-    E = w_o.shape[0]
-    assert o.dtype == torch.bfloat16 and w_o.shape == (E, H * 64) and dy.shape == (B, N, E) and D == 64
-    d_o = torch.empty_like(o) if want_do else None
-    dw = torch.empty((E, H * 64), dtype=torch.float32, device=o.device) if want_dw else None
-    db = torch.empty(E, dtype=torch.float32, device=o.device) if want_dbias else None
-    ws = project_bwd_workspace(B, N, H, E, o.device) if ws is None else ws
-    _check(mate_out_project_bwd(_dev(o, "o"), _dev(w_o, "w_o"), _dev(flags, "flags"), _dev(dy, "dy"),
-                                B, N, H, E, MATE_BF16, _opt(d_o, "d_o"), _opt(dw, "dw"), _opt(db, "dbias"),
-                                ws.data_ptr(), ws.numel(), _stream()), "mate_out_project_bwd")
-    return d_o, dw, db
+    return _native.out_project_bwd(o, w_o, flags, dy, want_do, want_dw, want_dbias, ws)
 
 
 def prefer_dense(B: int, H: int, N: int, dtype: torch.dtype = torch.bfloat16) -> bool:
