@@ -18,7 +18,7 @@
  * Conventions for every entry point
  *   - Pointers are DEVICE pointers unless the comment says HOST.  The caller owns every
  *     buffer (inputs, outputs, segment tables, workspace); the library allocates nothing
- *     and keeps no state between calls.
+ *     and keeps no results between calls.
  *   - Tensors are contiguous, row-major.  Q, K, V, O, dO, dQ, dK, dV are [B, H, N, D];
  *     LSE is [B, H, N] float; row_ids / col_ids are [B, N] int32; flags is [B, N] uint8.
  *   - D must be 64.  1 <= N <= MATE_MAX_N.  1 <= H <= MATE_MAX_HEADS.  B >= 1.

@@ -1,10 +1,11 @@
 // C ABI entry points: argument validation on the host, then kernel launches on the caller's
-// stream.  No allocation, no global state.
+// stream.  No allocation; the only global state is the counter behind next_ticket().
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <atomic>
 #include <cstring>
+#include <random>
 
 #include "../../include/mate.h"
 #include "launch.h"
@@ -32,7 +33,27 @@ size_t align16(size_t n) { return (n + 15) & ~size_t(15); }
 size_t delta_bytes(int B, int H, int N) { return align16((size_t)B * H * N * sizeof(float)); }
 // partial results of chunked question-token owners (bf16 MFMA path only)
 size_t part_bytes(int B, int H, int N) { return (size_t)B * H * part_words_per_bh(N) * sizeof(float); }
+// one arrival word per partial slot (see stream_plan.h)
+size_t word_bytes(int B, int H, int N) { return (size_t)B * H * owner_slots(N) * sizeof(unsigned long long); }
 size_t stat_bytes(int B, int H, int N) { return (size_t)B * H * stat_words_per_bh(N) * sizeof(float); }
+
+// The value a call's chunks announce themselves with: never zero, and a 64-bit number that no earlier
+// call of this process has used (the mix below is a bijection) and that uninitialised memory does
+// not hold by accident.
+unsigned long long next_ticket() {
+  static std::atomic<unsigned long long> count{[] {
+    std::random_device r;
+    return ((unsigned long long)r() << 32) | r();
+  }()};
+  unsigned long long z = 0;
+  while (z == 0) {
+    z = count.fetch_add(0x9e3779b97f4a7c15ull, std::memory_order_relaxed);
+    z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
+    z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
+    z ^= z >> 31;
+  }
+  return z;
+}
 
 mate_status fill_args(AttnArgs& a, const void* segments, const uint8_t* head_kind, int B, int H,
                       int N, int D, mate_dtype t, float scale) {
@@ -72,8 +93,8 @@ size_t mate_workspace_bytes(int B, int H, int N, int D, mate_dtype t, int for_bw
   if (!shape_ok(B, N) || H < 1 || H > MATE_MAX_HEADS || D != MATE_HEAD_DIM) return 0;
   if (t == MATE_F32) return for_bwd ? delta_bytes(B, H, N) : 0;
   if (t != MATE_BF16) return 0;
-  return for_bwd ? 2 * delta_bytes(B, H, N) + 3 * part_bytes(B, H, N)
-                 : part_bytes(B, H, N) + stat_bytes(B, H, N);
+  return for_bwd ? 2 * delta_bytes(B, H, N) + 3 * part_bytes(B, H, N) + word_bytes(B, H, N)
+                 : part_bytes(B, H, N) + stat_bytes(B, H, N) + word_bytes(B, H, N);
 }
 
 mate_status mate_build_segments(const int32_t* row_ids, const int32_t* col_ids,
@@ -287,6 +308,8 @@ mate_status mate_attn_fwd(const void* q, const void* k, const void* v, const voi
     char* p = static_cast<char*>(workspace);
     a.part[0] = reinterpret_cast<float*>(p);
     a.part_ml = reinterpret_cast<float*>(p + part_bytes(B, H, N));
+    a.arrived = reinterpret_cast<unsigned long long*>(p + part_bytes(B, H, N) + stat_bytes(B, H, N));
+    a.ticket = next_ticket();
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = (t == MATE_BF16) ? launch_fwd_mfma(a, s) : launch_fwd_scalar(a, false, s);
@@ -312,6 +335,7 @@ mate_status mate_attn_bwd(const void* q, const void* k, const void* v, const voi
     a.nlse = reinterpret_cast<float*>(static_cast<char*>(workspace) + delta_bytes(B, H, N));
     char* p = static_cast<char*>(workspace) + 2 * delta_bytes(B, H, N);
     for (int i = 0; i < 3; ++i) a.part[i] = reinterpret_cast<float*>(p + i * part_bytes(B, H, N));
+    a.arrived = reinterpret_cast<unsigned long long*>(p + 3 * part_bytes(B, H, N));
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = (t == MATE_BF16) ? launch_bwd_mfma(a, s) : launch_bwd_scalar(a, false, s);

@@ -11,9 +11,9 @@
 //                 question tokens plus the table tokens of the keys' own segments (every
 //                 non-pad token when the keys are question tokens):
 //                 dV += P^T dO, dK += dS^T Q.
-//   finalize   -- question-token owners stream the whole sequence, so their stream is cut into
-//                 chunks run by separate workgroups; this kernel adds the fp32 partials in
-//                 chunk order.
+// Question-token owners stream the whole sequence, so their stream is cut into chunks run by
+// separate workgroups, which leave fp32 partials that are added in chunk order: dQ's by the first
+// workgroups of the dkv kernel, dK's and dV's by the chunk that arrives last.
 // Pairs (table query, table key) are therefore recomputed once in each of the first two.
 #include <hip/hip_runtime.h>
 
@@ -26,6 +26,37 @@
 
 namespace mate {
 namespace {
+
+// Adds the chunk partials of one owner tile of question tokens in chunk order and stores its rows of
+// kTensors gradients; part[x] = the tile's first partial slot.  Items (32 rows x 32 dims of one tensor)
+// are dealt to the four wavefronts.
+template <int kTensors, bool kShared>
+__device__ __forceinline__ void merge_chunks(const float* const (&part)[kTensors], unsigned short* const (&out)[kTensors],
+                                             int rows, int n_chunks, char* stage, const int* row_tok, int wave, int lane) {
+  const int items = 2 * ((min(rows, BM) + 31) / 32);
+  for (int i = wave; i < items * kTensors; i += kThreads / 64) {
+    const int x = i / items, item = i - x * items;
+    const float* src = x == 0 ? part[0] : part[kTensors - 1];
+    f32x16 acc = zero16();
+    for (int c0 = 0; c0 < n_chunks; c0 += kBatch) {
+      float2 v[kBatch][8];
+      load_items<kShared>(v, src, item, c0, n_chunks, lane);
+#pragma unroll
+      for (int e = 0; e < kBatch; ++e) {
+        const float w = c0 + e < n_chunks ? 1.f : 0.f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          acc[2 * k] += w * v[e][k].x;
+          acc[2 * k + 1] += w * v[e][k].y;
+        }
+      }
+    }
+    stage_rows(acc, 1.f, stage + x * (BM * 128), (item >> 1) * 32 + (lane & 31), item & 1, lane >> 5);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < kTensors; ++x) flush_rows(out[x], stage + x * (BM * 128), row_tok, wave, lane);
+}
 
 // ======================================================================================
 // dQ (and delta)
@@ -69,6 +100,8 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
   const OwnedRow me = owned_row(u, a, b, view, wave, m);
   asm volatile("" ::"v"(me.pos), "v"(me.lo), "v"(me.hi), "v"(me.stage_tok));  // the owned rows are known from here on
   if (tid < BM) q_tok[tid] = me.stage_tok;
+  // the dkv kernel counts the chunks of an owner tile in the word of its first one
+  if (tid == 0 && u.part >= 0) a.arrived[(size_t)w.bh * owner_slots(N) + u.part] = 0;
   stream.prime();
 
   // this lane's query row and dO row as B operands (column m, k = dims), and delta
@@ -119,7 +152,7 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
   __syncthreads();  // all wavefronts are done reading the stages; reuse them for the epilogue
   if (u.part >= 0) {
     const size_t slot = (size_t)w.bh * owner_slots(N) + u.part;
-    store_partial(dq_acc, a.scale, a.part[0] + slot * BM * kD, wave, lane);
+    if (me.wave_active) store_partial<false>(dq_acc, a.scale, a.part[0] + slot * BM * kD, wave, lane);
     return;
   }
   const f32x16 (*accs[1])[2] = {&dq_acc};
@@ -132,17 +165,16 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
 // fit at once and the stragglers double the kernel's critical path)
 __global__ __launch_bounds__(kThreads, 4) void bwd_dq_mfma_kernel(AttnArgs a) {
   Work w;
-  if (!take_unit<true>(a, w)) return;
+  if (!take_unit<true>(a, blockIdx.x, w)) return;
   bwd_dq_unit(a, w);
 }
 
 // ======================================================================================
 // dK, dV
 // ======================================================================================
-__device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w) {
-  __shared__ __attribute__((aligned(1024))) char lds[kDkvNS * kDkvStage];
+__device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, char* lds, int* k_tok) {
   __shared__ int idx_ring[kIdxSlots][BN];
-  __shared__ int k_tok[BM];
+  __shared__ int group_done;
 
   const int b = w.bh / a.H;
   const int N = a.N, tid = threadIdx.x, lane = tid & 63;
@@ -212,8 +244,21 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w) {
   __syncthreads();  // all wavefronts are done reading the stages; reuse them for the epilogue
   if (u.part >= 0) {
     const size_t slot = (size_t)w.bh * owner_slots(N) + u.part;
-    store_partial(dk_acc, a.scale, a.part[1] + slot * BM * kD, wave, lane);
-    store_partial(dv_acc, 1.f, a.part[2] + slot * BM * kD, wave, lane);
+    const size_t slot0 = slot - u.part % u.n_chunks;
+    if (me.wave_active) {
+      store_partial<true>(dk_acc, a.scale, a.part[1] + slot * BM * kD, wave, lane);
+      store_partial<true>(dv_acc, 1.f, a.part[2] + slot * BM * kD, wave, lane);
+    }
+    publish_partials();
+    if (tid == 0)
+      group_done = __hip_atomic_fetch_add(a.arrived + slot0, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                   (unsigned long long)(u.n_chunks - 1);
+    __syncthreads();
+    if (group_done) {
+      const float* const parts[2] = {a.part[1] + slot0 * BM * kD, a.part[2] + slot0 * BM * kD};
+      unsigned short* const grads[2] = {dK, dV};
+      merge_chunks<2, true>(parts, grads, u.own_count - u.t0, u.n_chunks, lds, k_tok, wave, lane);
+    }
     return;
   }
   const f32x16 (*accs[2])[2] = {&dk_acc, &dv_acc};
@@ -222,61 +267,40 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w) {
   store_owned_rows<2>(accs, muls, outs, lds, k_tok, wave, lane);
 }
 
-__global__ __launch_bounds__(kThreads) void bwd_dkv_mfma_kernel(AttnArgs a) {
-  Work w;
-  if (!take_unit<true>(a, w)) return;
-  bwd_dkv_unit(a, w);
-}
-
-// Adds the chunk partials of question-token rows in chunk order and stores dQ, dK, dV rows.
-// blockIdx.z selects the tensor; 8 threads per row, 32 rows per workgroup.
-__global__ __launch_bounds__(kThreads) void bwd_finalize_kernel(AttnArgs a) {
-  const int bh_i = blockIdx.y, b = bh_i / a.H, N = a.N, which = blockIdx.z;
+// dQ rows of the question tokens of one (sequence, head) from the dq kernel's chunk partials.
+__device__ __forceinline__ void merge_dq(const AttnArgs& a, int bh_i, char* stage, int* row_tok) {
+  const int b = bh_i / a.H, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // header and counts in one scalar round trip (both lie inside the table buffer whatever it holds)
   const int* cnt = a.seg.counts + (size_t)b * kCountWords;
   const int h_magic = a.seg.hdr[0], h_B = a.seg.hdr[1], h_N = a.seg.hdr[2];
   const int G = cnt[C_G], L = cnt[C_L];
   if (h_magic != kMagic || h_B != a.B || h_N != a.N) return;
-  const GlobalSplit s = global_split(G, L, N);
+  const GlobalSplit s = global_split(G, L, a.N);
   if (s.n_chunks <= 1) return;
-  const int piece = threadIdx.x & 7;
-  for (int x = blockIdx.x * 32 + (threadIdx.x >> 3); x < G; x += gridDim.x * 32) {
-  const int gt = x / BM, r = x % BM;
-  const size_t slot0 = (size_t)bh_i * owner_slots(N) + (size_t)gt * s.n_chunks;
-  // chunks are read eight at a time, all loads issued before the first addition (the pin below:
-  // left alone, the compiler keeps only a few in flight and the kernel becomes a chain of memory
-  // round trips); the order of the additions is fixed, so the result is deterministic
-  const int tok = a.seg.global_idx[(size_t)b * N + x];
-  constexpr int kBatch = 8;
-  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int c0 = 0; c0 < s.n_chunks; c0 += kBatch) {
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
-    f32x4 p0[kBatch], p1[kBatch];
-#pragma unroll
-    for (int e = 0; e < kBatch; ++e) {
-      const int c = min(c0 + e, s.n_chunks - 1);
-      const float* p = a.part[which] + ((slot0 + c) * BM + r) * kD + piece * 8;
-      p0[e] = *reinterpret_cast<const f32x4*>(p);
-      p1[e] = *reinterpret_cast<const f32x4*>(p + 4);
-    }
-    asm volatile("" ::"v"(p0[0]), "v"(p0[1]), "v"(p0[2]), "v"(p0[3]), "v"(p0[4]), "v"(p0[5]), "v"(p0[6]), "v"(p0[7]),
-                 "v"(p1[0]), "v"(p1[1]), "v"(p1[2]), "v"(p1[3]), "v"(p1[4]), "v"(p1[5]), "v"(p1[6]), "v"(p1[7]));
-#pragma unroll
-    for (int e = 0; e < kBatch; ++e) {
-      const float w = c0 + e < s.n_chunks ? 1.f : 0.f;
-      acc[0] += w * p0[e].x; acc[1] += w * p0[e].y; acc[2] += w * p0[e].z; acc[3] += w * p0[e].w;
-      acc[4] += w * p1[e].x; acc[5] += w * p1[e].y; acc[6] += w * p1[e].z; acc[7] += w * p1[e].w;
-    }
+  unsigned short* const out[1] = {static_cast<unsigned short*>(a.dq) + (size_t)bh_i * a.N * kD};
+  for (int gt = 0; gt < s.n_gt; ++gt) {
+    const int row = gt * BM + tid;
+    if (tid < BM) row_tok[tid] = row < G ? a.seg.global_idx[(size_t)b * a.N + row] : -1;
+    const size_t slot0 = (size_t)bh_i * owner_slots(a.N) + (size_t)gt * s.n_chunks;
+    const float* const part[1] = {a.part[0] + slot0 * BM * kD};
+    merge_chunks<1, false>(part, out, G - gt * BM, s.n_chunks, stage, row_tok, wave, lane);
+    __syncthreads();
   }
-  void* dst = which == 0 ? a.dq : which == 1 ? a.dk : a.dv;
-  uint4 w;
-  w.x = f32_to_bf16_bits(acc[0]) | ((unsigned)f32_to_bf16_bits(acc[1]) << 16);
-  w.y = f32_to_bf16_bits(acc[2]) | ((unsigned)f32_to_bf16_bits(acc[3]) << 16);
-  w.z = f32_to_bf16_bits(acc[4]) | ((unsigned)f32_to_bf16_bits(acc[5]) << 16);
-  w.w = f32_to_bf16_bits(acc[6]) | ((unsigned)f32_to_bf16_bits(acc[7]) << 16);
-  *reinterpret_cast<uint4*>(static_cast<unsigned short*>(dst) + ((size_t)bh_i * N + tok) * kD +
-                            piece * 8) = w;
+}
+
+// The first `n_merge` workgroups (a multiple of eight, so that the unit queues keep their XCDs) merge
+// dQ partials: a few microseconds each, out of the way before the kernel's own tail.
+__global__ __launch_bounds__(kThreads) void bwd_dkv_mfma_kernel(AttnArgs a, int n_merge) {
+  __shared__ __attribute__((aligned(1024))) char lds[kDkvNS * kDkvStage];
+  __shared__ int row_tok[BM];
+  if ((int)blockIdx.x < n_merge) {
+    if ((int)blockIdx.x < a.B * a.H) merge_dq(a, blockIdx.x, lds, row_tok);
+    return;
   }
+  Work w;
+  if (!take_unit<true>(a, blockIdx.x - n_merge, w)) return;
+  bwd_dkv_unit(a, w, lds, row_tok);
 }
 
 }  // namespace
@@ -290,14 +314,9 @@ hipError_t launch_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  {
-    ProfileScope prof(4, stream);
-    hipLaunchKernelGGL(bwd_dkv_mfma_kernel, grid, block, 0, stream, a);
-  }
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (owner_slots(a.N) >= 2)  // partials exist only while question tokens fill <= half the owner slots
-    hipLaunchKernelGGL(bwd_finalize_kernel, dim3(kFinalizeBlocks, a.B * a.H, 3), block, 0, stream, a);
+  ProfileScope prof(4, stream);
+  const int n_merge = may_chunk(a.N) ? 8 * ((a.B * a.H + 7) / 8) : 0;
+  hipLaunchKernelGGL(bwd_dkv_mfma_kernel, dim3(grid.x + n_merge), block, 0, stream, a, n_merge);
   return hipGetLastError();
 }
 

@@ -11,8 +11,8 @@
 // used by all four wavefronts; scores are masked per element by "key slot inside this query's
 // segment range", and one online softmax runs across
 // the question-key and segment-key tiles, which is the single softmax over the union that the
-// definition asks for.  Chunked owners leave (unnormalised O, max, sum) partials that the
-// finalize kernel merges with the usual log-sum-exp rule.
+// definition asks for.  Chunked owners leave (unnormalised O, max, sum) partials that the chunk
+// arriving last merges with the usual log-sum-exp rule.
 #include <hip/hip_runtime.h>
 
 #include "d2l.h"
@@ -29,10 +29,76 @@ constexpr int kStageBytes = 2 * kTileBytes;   // K tile, V tile
 constexpr float kLazyBits = 8.f;
 constexpr int NS = 2;  // LDS stages: small enough for four workgroups per CU
 
+// Who merges.  The workspace is uninitialised, so there is no counter to add to: every chunk has a
+// word of its own and sets it to the call's ticket, a 64-bit number no earlier call has used; a
+// workgroup that then finds every word of its group set is the one (or one of several, which write
+// the same values: each sets its word before it reads the others', so at least one sees all).
+// The words are cleared again afterwards, so that a captured launch, which is replayed with its
+// old ticket, finds none of its own.
+__device__ __forceinline__ bool completes_group(unsigned long long* words, int mine, int n_chunks,
+                                                unsigned long long ticket, int* flag) {
+  publish_partials();
+  if (threadIdx.x < 64) {
+    if (threadIdx.x == 0) __hip_atomic_store(words + mine, ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    bool all = true;
+    for (int j = threadIdx.x; j < n_chunks; j += 64)
+      all &= __hip_atomic_load(words + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == ticket;
+    const bool every = __all(all);
+    if (threadIdx.x == 0) *flag = every;
+  }
+  __syncthreads();
+  return *flag != 0;
+}
+
+// O = sum_c 2^(m_c - m) O_c / sum_c 2^(m_c - m) l_c over the chunks of one owner tile of question
+// tokens; slot0 = the tile's first partial slot.  Items are dealt to the four wavefronts.
+__device__ __forceinline__ void merge_chunks(const AttnArgs& a, const UnitPlan& u, size_t slot0, unsigned short* O,
+                                             float* LSE, char* stage, const int* row_tok, int wave, int lane) {
+  const int m = lane & 31, hl = lane >> 5;
+  const float* part = a.part[0] + slot0 * BM * kD;
+  const float* stat = a.part_ml + slot0 * BM * 2;
+  for (int item = wave; item < 2 * BM / 32; item += kThreads / 64) {
+    const int row = (item >> 1) * 32 + m;
+    if (u.t0 + (item >> 1) * 32 >= u.own_count) break;  // no question token in this block
+    f32x16 acc = zero16();
+    float mx = -INFINITY, l = 0.f;
+    for (int c0 = 0; c0 < u.n_chunks; c0 += kBatch) {
+      float2 ml[kBatch], v[kBatch][8];
+#pragma unroll
+      for (int e = 0; e < kBatch; ++e) ml[e] = get_pair<true>(stat + ((size_t)min(c0 + e, u.n_chunks - 1) * BM + row) * 2);
+      load_items<true>(v, part, item, c0, u.n_chunks, lane);
+      float m_new = mx;
+#pragma unroll
+      for (int e = 0; e < kBatch; ++e) m_new = fmaxf(m_new, ml[e].x);  // (repeats of the last chunk change nothing)
+      const float alpha = __builtin_amdgcn_exp2f(mx - m_new);          // every chunk has a key: m_new is finite
+      mx = m_new;
+      l *= alpha;
+#pragma unroll
+      for (int c = 0; c < 16; ++c) acc[c] *= alpha;
+#pragma unroll
+      for (int e = 0; e < kBatch; ++e) {
+        const float w = c0 + e < u.n_chunks ? __builtin_amdgcn_exp2f(ml[e].x - mx) : 0.f;
+        l += w * ml[e].y;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          acc[2 * i] += w * v[e][i].x;
+          acc[2 * i + 1] += w * v[e][i].y;
+        }
+      }
+    }
+    stage_rows(acc, 1.f / l, stage, row, item & 1, hl);
+    if ((item & 1) == 0 && hl == 0 && row_tok[row] >= 0) LSE[row_tok[row]] = (mx + __builtin_amdgcn_logf(l)) * kLn2;
+  }
+  __syncthreads();
+  flush_rows(O, stage, row_tok, wave, lane);
+}
+
 __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
   __shared__ __attribute__((aligned(1024))) char lds[NS * kStageBytes];
   __shared__ int idx_ring[kIdxSlots][BN];  // [tile & 7][row] token positions
   __shared__ int q_tok[BM];
+  __shared__ int group_done;
 
   const int b = w.bh / a.H;
   const int N = a.N, tid = threadIdx.x, lane = tid & 63;
@@ -111,12 +177,19 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
 
   const float l_tot = half_sum(l_run);
   if (u.part >= 0) {
-    // chunk of a question-token owner: leave (unnormalised O, max, sum) for the finalize kernel
+    // chunk of a question-token owner: leave (unnormalised O, max, sum); the last one merges
     const size_t slot = (size_t)w.bh * owner_slots(N) + u.part;
-    store_partial(o_acc, 1.f, a.part[0] + slot * BM * kD, wave, lane);
-    if (hl == 0)
-      *reinterpret_cast<float2*>(a.part_ml + (slot * BM + wave * 32 + m) * 2) =
-          make_float2(m_run == -INFINITY ? m_run : m_run * sc, l_tot);
+    const int mine = u.part % u.n_chunks;
+    if (me.wave_active) {
+      store_partial<true>(o_acc, 1.f, a.part[0] + slot * BM * kD, wave, lane);
+      if (hl == 0)
+        put_pair<true>(a.part_ml + (slot * BM + wave * 32 + m) * 2, m_run == -INFINITY ? m_run : m_run * sc, l_tot);
+    }
+    unsigned long long* words = a.arrived + (slot - mine);
+    if (completes_group(words, mine, u.n_chunks, a.ticket, &group_done)) {
+      merge_chunks(a, u, slot - mine, O, LSE, lds, q_tok, wave, lane);
+      if (tid < u.n_chunks) __hip_atomic_store(words + tid, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     return;
   }
   if (hl == 0 && me.valid) LSE[me.pos] = (m_run * sc + __builtin_amdgcn_logf(l_tot)) * kLn2;
@@ -128,98 +201,15 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
 
 __global__ __launch_bounds__(kThreads, 4) void fwd_mfma_kernel(AttnArgs a) {
   Work w;
-  if (!take_unit<false>(a, w)) return;
+  if (!take_unit<false>(a, blockIdx.x, w)) return;
   fwd_unit(a, w);
-}
-
-// Merges the chunk partials of question-token queries: O = sum_c 2^(m_c - m) O_c / sum_c 2^(m_c - m) l_c.
-// 8 threads per query row (8 dims each), 32 rows per workgroup.
-__global__ __launch_bounds__(kThreads) void fwd_finalize_kernel(AttnArgs a) {
-  const int bh_i = blockIdx.y, b = bh_i / a.H, N = a.N;
-  // header and counts in one scalar round trip (both lie inside the table buffer whatever it holds)
-  const int* cnt = a.seg.counts + (size_t)b * kCountWords;
-  const int h_magic = a.seg.hdr[0], h_B = a.seg.hdr[1], h_N = a.seg.hdr[2];
-  const int G = cnt[C_G], L = cnt[C_L];
-  if (h_magic != kMagic || h_B != a.B || h_N != a.N) return;
-  const GlobalSplit s = global_split(G, L, N);
-  if (s.n_chunks <= 1) return;
-  const int piece = threadIdx.x & 7;
-  for (int x = blockIdx.x * 32 + (threadIdx.x >> 3); x < G; x += gridDim.x * 32) {
-  const int gt = x / BM, r = x % BM;
-  const int tok = a.seg.global_idx[(size_t)b * N + x];
-  const size_t slot0 = (size_t)bh_i * owner_slots(N) + (size_t)gt * s.n_chunks;
-  // Chunks are read kBatch at a time with all loads of a batch issued before the first use (the
-  // pin at the end of load_batch: left alone, the compiler keeps only a few in flight and the
-  // kernel becomes a chain of memory round trips).  The chunk count is only known on the device;
-  // the combination order is fixed, so the result is deterministic.  A first batch usually
-  // covers every chunk: then each partial is read exactly once.
-  constexpr int kBatch = 8;
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
-  typedef float f32x2 __attribute__((ext_vector_type(2)));
-  float m = -INFINITY;
-  f32x2 ml[kBatch];
-  f32x4 p0[kBatch], p1[kBatch];
-  auto load_batch = [&](int c0) {
-#pragma unroll
-    for (int e = 0; e < kBatch; ++e) {
-      const int c = min(c0 + e, s.n_chunks - 1);
-      ml[e] = *reinterpret_cast<const f32x2*>(a.part_ml + ((slot0 + c) * BM + r) * 2);
-      const float* p = a.part[0] + ((slot0 + c) * BM + r) * kD + piece * 8;
-      p0[e] = *reinterpret_cast<const f32x4*>(p);
-      p1[e] = *reinterpret_cast<const f32x4*>(p + 4);
-    }
-    asm volatile("" ::"v"(p0[0]), "v"(p0[1]), "v"(p0[2]), "v"(p0[3]), "v"(p0[4]), "v"(p0[5]), "v"(p0[6]), "v"(p0[7]),
-                 "v"(p1[0]), "v"(p1[1]), "v"(p1[2]), "v"(p1[3]), "v"(p1[4]), "v"(p1[5]), "v"(p1[6]), "v"(p1[7]),
-                 "v"(ml[0]), "v"(ml[1]), "v"(ml[2]), "v"(ml[3]), "v"(ml[4]), "v"(ml[5]), "v"(ml[6]), "v"(ml[7]));
-  };
-  load_batch(0);
-#pragma unroll
-  for (int e = 0; e < kBatch; ++e) m = fmaxf(m, e < s.n_chunks ? ml[e].x : -INFINITY);
-  for (int c0 = kBatch; c0 < s.n_chunks; c0 += 8) {  // more chunks than one batch: finish the maximum first
-    float mv[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-      mv[e] = c0 + e < s.n_chunks ? a.part_ml[((slot0 + c0 + e) * BM + r) * 2] : -INFINITY;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) m = fmaxf(m, mv[e]);
-  }
-  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0}, l = 0.f;
-  for (int c0 = 0; c0 < s.n_chunks; c0 += kBatch) {
-    if (c0) load_batch(c0);
-#pragma unroll
-    for (int e = 0; e < kBatch; ++e) {
-      const float w = c0 + e < s.n_chunks ? __builtin_amdgcn_exp2f(ml[e].x - m) : 0.f;
-      l += w * ml[e].y;
-      acc[0] += w * p0[e].x; acc[1] += w * p0[e].y; acc[2] += w * p0[e].z; acc[3] += w * p0[e].w;
-      acc[4] += w * p1[e].x; acc[5] += w * p1[e].y; acc[6] += w * p1[e].z; acc[7] += w * p1[e].w;
-    }
-  }
-  const float inv = 1.f / l;
-  const size_t bh = (size_t)bh_i * N;
-  uint4 w;
-  w.x = f32_to_bf16_bits(acc[0] * inv) | ((unsigned)f32_to_bf16_bits(acc[1] * inv) << 16);
-  w.y = f32_to_bf16_bits(acc[2] * inv) | ((unsigned)f32_to_bf16_bits(acc[3] * inv) << 16);
-  w.z = f32_to_bf16_bits(acc[4] * inv) | ((unsigned)f32_to_bf16_bits(acc[5] * inv) << 16);
-  w.w = f32_to_bf16_bits(acc[6] * inv) | ((unsigned)f32_to_bf16_bits(acc[7] * inv) << 16);
-  *reinterpret_cast<uint4*>(static_cast<unsigned short*>(a.out) + (bh + tok) * kD + piece * 8) = w;
-  if (piece == 0) a.lse[bh + tok] = (m + __builtin_amdgcn_logf(l)) * kLn2;
-  }
 }
 
 }  // namespace
 
 hipError_t launch_fwd_mfma(const AttnArgs& a, hipStream_t stream) {
-  {
-    ProfileScope prof(2, stream);
-    hipLaunchKernelGGL(fwd_mfma_kernel, dim3(unit_grid(a.B, a.H, a.N, a.n_col)), dim3(kThreads), 0, stream, a);
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  // partials exist only while question tokens fill at most half the owner slots; a few
-  // workgroups per (b,h) stride over however many question tokens there are
-  if (owner_slots(a.N) >= 2)
-    hipLaunchKernelGGL(fwd_finalize_kernel, dim3(kFinalizeBlocks, a.B * a.H), dim3(kThreads), 0,
-                       stream, a);
+  ProfileScope prof(2, stream);
+  hipLaunchKernelGGL(fwd_mfma_kernel, dim3(unit_grid(a.B, a.H, a.N, a.n_col)), dim3(kThreads), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -17,6 +17,8 @@ struct AttnArgs {
   float* part[3];           // partial results of chunked question-token owners, per (b,h):
                             //   forward: [0] unnormalised O;  backward: dQ, dK, dV
   float* part_ml;           // forward: running max (log2 domain) and sum per partial row
+  unsigned long long* arrived;     // one word per partial slot: which chunks have left their partials
+  unsigned long long ticket;       // forward: what a chunk sets its word to, new for every call
   SegTables seg;
   unsigned char head_kind[256];
   alignas(4) unsigned char head_order[256];  // heads sorted column heads first (stable);

@@ -21,7 +21,8 @@
 // and streams 64-row tiles of the other side.  Record (8 words):
 //   kind (0 none, 1 question-token owner, 2 table-token owner, 3 pad owner), first owned slot,
 //   streamed sorted-slot window [lo, hi), first and one-past-last streamed tile, partial-result
-//   slot or -1, one past the last owned slot (table-token owners)
+//   slot or -1, one past the last owned slot (table-token owners) or number of chunks of this owner
+//   tile (question-token owners)
 // For a table-token owner [lo, hi) is the union of the windows of its slots.  Its slots are a
 // 128-slot piece of a "run": a segment of at least kBigSegment slots is a run of its own, the
 // shorter segments between two such segments form one run.  So no unit straddles the boundary
@@ -29,7 +30,7 @@
 // on each, and be the longest unit of the launch).  If that needs more records than there
 // are, the sorted order is cut every 128 slots regardless of segments.
 // The streamed side of question-token owners is the whole sequence; it is cut into chunks of at
-// least kMinChunkTiles tiles, one unit each, that leave partial results.
+// least kMinChunkTiles tiles, one unit each, that leave partial results for the last one to merge.
 #pragma once
 #include <stddef.h>
 #include <stdint.h>
@@ -72,6 +73,10 @@ __host__ __device__ inline GlobalSplit global_split(int G, int L, int N) {
   s.n_chunks = s.per ? (s.n_st + s.per - 1) / s.per : 1;  // drop empty trailing chunks
   return s;
 }
+
+// Can any sequence of N positions have more than one chunk?  (Host-side bound: at most N tokens in two
+// lists of 64-row tiles, so never more than (N - 2) / 64 + 2 tiles.)
+inline bool may_chunk(int N) { return (N - 2) / BN + 2 > kMinChunkTiles; }
 
 __host__ __device__ inline size_t align4(size_t w) { return (w + 3) & ~size_t(3); }
 

@@ -457,6 +457,7 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
         q1.x = c * gs.per;
         q1.y = min(gs.n_st, q1.x + gs.per);
         if (gs.n_chunks > 1) q1.z = tid;
+        q1.w = gs.n_chunks;
       }
       gunit[2 * tid] = q0;
       gunit[2 * tid + 1] = q1;
@@ -715,6 +716,7 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
       r1.x = c * gs.per;
       r1.y = min(gs.n_st, r1.x + gs.per);
       if (gs.n_chunks > 1) r1.z = tid;
+      r1.w = gs.n_chunks;
     }
     gunit[2 * tid] = r0;
     gunit[2 * tid + 1] = r1;

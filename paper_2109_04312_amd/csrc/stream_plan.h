@@ -10,8 +10,8 @@
 //           that never straddle the boundary of a long segment; listed longest stream first
 //   pad     ceil(P / 1024) pad owners (zero fill)
 //   global  question-token owners.  Their streamed side is the whole sequence, so it is cut into
-//           chunks that run as separate units and leave partial results, merged by a finalize
-//           kernel.
+//           chunks that run as separate units and leave partial results; the chunk that arrives
+//           last merges them (the dQ kernel's chunks are merged by the next kernel).
 // Workgroup -> unit is arithmetic on the workgroup index plus one record read: no counters, no
 // atomics, no dependent loads.  Workgroup i serves queue i mod 8 (consecutive workgroups go to
 // consecutive XCDs, so a queue stays on one XCD and the units of one (sequence, head) pair
@@ -39,7 +39,6 @@
 namespace mate {
 
 constexpr int kThreads = 256;
-constexpr int kFinalizeBlocks = 4; // workgroups per (b,h) in the finalize kernels (32 rows each, strided)
 
 struct UnitPlan {
   int kind;
@@ -51,6 +50,7 @@ struct UnitPlan {
   int n_t0;              // streamed question-token tiles; table tiles follow
   int t_begin, t_end;    // streamed tiles of this unit
   int part;              // partial-result slot (unit index) or -1: results are final
+  int n_chunks;          // question-token owners: chunks of this owner tile
   int G, L, P;
 };
 
@@ -76,9 +76,9 @@ __device__ inline int head_at(const AttnArgs& a, int i) {
 // Returns false if this workgroup has nothing to do.  Everything here is wave-uniform and
 // stays in scalar registers.
 template <bool kChunksFirst>
-__device__ inline bool take_unit(const AttnArgs& a, Work& w) {
+__device__ inline bool take_unit(const AttnArgs& a, int block, Work& w) {
   const int T = a.seg.tiles, U = a.seg.units, N = a.N, n_col = a.n_col, n_row = a.H - n_col;
-  const int q = blockIdx.x & 7;
+  const int q = block & 7;
   // row-head pairs are dealt to the queues starting where the column-head pairs stopped, so that
   // a handful of pairs still spreads over as many XCDs as possible
   const int qr = (q - a.B * n_col) & 7;
@@ -90,7 +90,7 @@ __device__ inline bool take_unit(const AttnArgs& a, Work& w) {
   // filled to the last position, resp. has more than 128 question tokens) comes first for all
   // three kinds of unit, the remainders after them.
   const int E = min(U, T), T1 = min(T, (T >> 3) + 2);
-  int t = blockIdx.x >> 3;
+  int t = block >> 3;
   // region -> (first pair, pairs, first record, records per pair)
   const int n_all = nc + nr;
   // the first two regions: column heads then question-token owners (early parts), or the reverse
@@ -150,6 +150,7 @@ __device__ inline bool take_unit(const AttnArgs& a, Work& w) {
   u.t_begin = r1.x;
   u.t_end = r1.y;
   u.part = r1.z;
+  u.n_chunks = r1.w;
   u.G = cnt[C_G];
   u.L = cnt[C_L];
   u.P = cnt[C_P];
@@ -211,49 +212,95 @@ __device__ inline OwnedRow owned_row(const UnitPlan& u, const AttnArgs& a, int b
 // tensor: 128 rows of 128 bytes whose 16-byte chunks are XOR-swizzled with the row number so
 // that both the column-wise writes and the row-wise reads spread over all banks.  One barrier;
 // the staging area must not be reused by the caller afterwards without another one.
+// (stage_rows: one wavefront-slot's 32 rows x 32 dims; flush_rows: after a barrier, every wavefront its 32 rows)
+__device__ __forceinline__ void stage_rows(const f32x16& a, float mul, char* stage, int wrow, int db, int hl) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    uint2 w;
+    w.x = f32_to_bf16_bits(a[4 * g] * mul) | ((unsigned)f32_to_bf16_bits(a[4 * g + 1] * mul) << 16);
+    w.y = f32_to_bf16_bits(a[4 * g + 2] * mul) | ((unsigned)f32_to_bf16_bits(a[4 * g + 3] * mul) << 16);
+    *reinterpret_cast<uint2*>(stage + wrow * 128 + (((4 * db + g) ^ (wrow & 7)) << 4) + 8 * hl) = w;
+  }
+}
+__device__ __forceinline__ void flush_rows(unsigned short* out, const char* stage, const int* row_tok, int wave, int lane) {
+#pragma unroll
+  for (int it = 0; it < 4; ++it) {
+    const int row = wave * 32 + it * 8 + (lane >> 3), piece = lane & 7;
+    const int tok = row_tok[row];
+    if (tok >= 0)
+      *reinterpret_cast<uint4*>(out + (size_t)tok * kD + piece * 8) =
+          *reinterpret_cast<const uint4*>(stage + row * 128 + ((piece ^ (row & 7)) << 4));
+  }
+}
 template <int kTensors>
 __device__ inline void store_owned_rows(const f32x16 (*acc[kTensors])[2], const float (&mul)[kTensors],
                                         unsigned short* const (&out)[kTensors], char* stage,
                                         const int* row_tok, int wave, int lane) {
-  const int m = lane & 31, hl = lane >> 5;
-  const int wrow = wave * 32 + m;
 #pragma unroll
   for (int x = 0; x < kTensors; ++x)
 #pragma unroll
     for (int db = 0; db < 2; ++db)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x16& a = (*acc[x])[db];
-        uint2 w;
-        w.x = f32_to_bf16_bits(a[4 * g] * mul[x]) | ((unsigned)f32_to_bf16_bits(a[4 * g + 1] * mul[x]) << 16);
-        w.y = f32_to_bf16_bits(a[4 * g + 2] * mul[x]) | ((unsigned)f32_to_bf16_bits(a[4 * g + 3] * mul[x]) << 16);
-        *reinterpret_cast<uint2*>(stage + x * (BM * 128) + wrow * 128 + (((4 * db + g) ^ (wrow & 7)) << 4) + 8 * hl) = w;
-      }
+      stage_rows((*acc[x])[db], mul[x], stage + x * (BM * 128), wave * 32 + (lane & 31), db, lane >> 5);
   __syncthreads();
 #pragma unroll
-  for (int x = 0; x < kTensors; ++x)
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const int row = wave * 32 + it * 8 + (lane >> 3), piece = lane & 7;
-      const int tok = row_tok[row];
-      if (tok >= 0)
-        *reinterpret_cast<uint4*>(out[x] + (size_t)tok * kD + piece * 8) =
-            *reinterpret_cast<const uint4*>(stage + x * (BM * 128) + row * 128 + ((piece ^ (row & 7)) << 4));
-    }
+  for (int x = 0; x < kTensors; ++x) flush_rows(out[x], stage + x * (BM * 128), row_tok, wave, lane);
 }
 
-// Partial results of a chunked question-token owner: fp32 [128][64], row = owned row.
-__device__ inline void store_partial(const f32x16 acc[2], float mul, float* __restrict__ part,
-                                     int wave, int lane) {
-  const int m = lane & 31, hl = lane >> 5;
-  float* row = part + (size_t)(wave * 32 + m) * kD;
+// ---- partial results of chunked question-token owners ------------------------------------------
+// A chunk leaves its fp32 accumulators in the workspace in register order, [item][8][64 lanes] pairs
+// with item = 2 wavefront + dim block, so every access is 512 contiguous bytes and the merge works on
+// the same registers as the chunks did.  Merging adds the chunks in order, so the result does not
+// depend on who merges, or when.
+//
+// Forward and dK/dV: the chunk of an owner tile that arrives last merges inside the same launch
+// (a finalize kernel of its own cost 4.8 us in the forward and 6.4 us in the backward at B = 2,
+// N = 8192, H = 16, nearly all of it the launch).  Chunks of one tile may run on different XCDs, whose
+// L2s are not coherent, so partials and arrival words are accessed with relaxed device-scope
+// atomics (which bypass the L2), and "partials before arrival" comes from waiting for the stores'
+// acknowledgement.  dQ: merged by the first workgroups of the dK/dV kernel, behind the kernel boundary.
+template <bool kShared>
+__device__ __forceinline__ void put_pair(float* p, float x, float y) {
+  const unsigned long long v = (unsigned long long)__float_as_uint(x) | ((unsigned long long)__float_as_uint(y) << 32);
+  if (kShared) __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *reinterpret_cast<unsigned long long*>(p) = v;
+}
+template <bool kShared>
+__device__ __forceinline__ float2 get_pair(const float* p) {
+  const unsigned long long* q = reinterpret_cast<const unsigned long long*>(p);
+  const unsigned long long v = kShared ? __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *q;
+  return make_float2(__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32)));
+}
+constexpr int kItemFloats = 16 * 64;  // one wavefront's accumulator of one dim block
+template <bool kShared>
+__device__ __forceinline__ void store_partial(const f32x16 acc[2], float mul, float* __restrict__ part, int wave, int lane) {
+  asm volatile("" : "+v"(lane));  // keeps the address arithmetic out of the tile loop's registers
 #pragma unroll
   for (int db = 0; db < 2; ++db)
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
-      *reinterpret_cast<float4*>(row + db * 32 + 8 * g + 4 * hl) =
-          make_float4(acc[db][4 * g] * mul, acc[db][4 * g + 1] * mul, acc[db][4 * g + 2] * mul,
-                      acc[db][4 * g + 3] * mul);
+    for (int i = 0; i < 8; ++i)
+      put_pair<kShared>(part + (2 * wave + db) * kItemFloats + (i * 64 + lane) * 2, acc[db][2 * i] * mul, acc[db][2 * i + 1] * mul);
+}
+// kBatch chunks of one item with all loads issued before the first use (the pin: left alone, the
+// compiler keeps only a few in flight and the merge becomes a chain of memory round trips).
+constexpr int kBatch = 4;
+template <bool kShared>
+__device__ __forceinline__ void load_items(float2 (&v)[kBatch][8], const float* part0, int item, int c0, int n_chunks, int lane) {
+#pragma unroll
+  for (int e = 0; e < kBatch; ++e)
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      v[e][i] = get_pair<kShared>(part0 + (size_t)min(c0 + e, n_chunks - 1) * (BM * kD) + item * kItemFloats + (i * 64 + lane) * 2);
+#pragma unroll
+  for (int e = 0; e < kBatch; ++e)
+#pragma unroll
+    for (int i = 0; i < 8; i += 4)
+      asm volatile("" ::"v"(v[e][i].x), "v"(v[e][i].y), "v"(v[e][i + 1].x), "v"(v[e][i + 1].y), "v"(v[e][i + 2].x),
+                   "v"(v[e][i + 2].y), "v"(v[e][i + 3].x), "v"(v[e][i + 3].y));
+}
+// All of the workgroup's partials and words are where every XCD sees them from here on.
+__device__ __forceinline__ void publish_partials() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
 }
 
 // Zero fill of the rows of a pad unit in kTensors tensors.  The positions of all the rows a
