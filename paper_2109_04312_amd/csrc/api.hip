@@ -65,7 +65,6 @@ mate_status fill_args(AttnArgs& a, const void* segments, const uint8_t* head_kin
   int n_sorted = 0;
   for (int h = 0; h < H; ++h) {
     if (head_kind[h] > MATE_HEAD_COL) return MATE_ERR_UNSUPPORTED;
-    a.head_kind[h] = head_kind[h];
   }
   for (int kind = MATE_HEAD_COL; kind >= MATE_HEAD_ROW; --kind)
     for (int h = 0; h < H; ++h)
@@ -312,7 +311,7 @@ mate_status mate_attn_fwd(const void* q, const void* k, const void* v, const voi
     a.ticket = next_ticket();
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = (t == MATE_BF16) ? launch_fwd_mfma(a, s) : launch_fwd_scalar(a, false, s);
+  hipError_t e = (t == MATE_BF16) ? launch_fwd_mfma(a, s) : launch_fwd_f32(a, s);
   return e == hipSuccess ? MATE_OK : MATE_ERR_HIP;
 }
 
@@ -338,7 +337,7 @@ mate_status mate_attn_bwd(const void* q, const void* k, const void* v, const voi
     a.arrived = reinterpret_cast<unsigned long long*>(p + 3 * part_bytes(B, H, N));
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = (t == MATE_BF16) ? launch_bwd_mfma(a, s) : launch_bwd_scalar(a, false, s);
+  hipError_t e = (t == MATE_BF16) ? launch_bwd_mfma(a, s) : launch_bwd_f32(a, s);
   return e == hipSuccess ? MATE_OK : MATE_ERR_HIP;
 }
 

@@ -20,7 +20,6 @@ struct AttnArgs {
   unsigned long long* arrived;     // one word per partial slot: which chunks have left their partials
   unsigned long long ticket;       // forward: what a chunk sets its word to, new for every call
   SegTables seg;
-  unsigned char head_kind[256];
   alignas(4) unsigned char head_order[256];  // heads sorted column heads first (stable);
                                              // read as 32-bit words by the kernels
   int n_col;                      // number of column heads
@@ -101,10 +100,9 @@ hipError_t launch_out_project_bwd(const void* o, const void* w_o, const unsigned
 hipError_t launch_mfma_probe(float* sink, int workgroups, int iters, hipStream_t stream);
 double mfma_probe_flop(int workgroups, int iters);
 
-// Scalar (non-MFMA) kernels: fp32 arithmetic throughout, one wavefront per query / key.
-// They serve dtype f32 and are the fallback-free reference-quality path for it.
-hipError_t launch_fwd_scalar(const AttnArgs& a, bool bf16, hipStream_t stream);
-hipError_t launch_bwd_scalar(const AttnArgs& a, bool bf16, hipStream_t stream);
+// fp32 matrix-core kernels: the path for dtype f32.
+hipError_t launch_fwd_f32(const AttnArgs& a, hipStream_t stream);
+hipError_t launch_bwd_f32(const AttnArgs& a, hipStream_t stream);
 
 // bf16 MFMA kernels.
 hipError_t launch_fwd_mfma(const AttnArgs& a, hipStream_t stream);

@@ -341,3 +341,13 @@ def test_step_replays_identically_from_a_captured_graph():
         torch.cuda.synchronize()
         for name in ("out", "lse", "dq", "dk", "dv"):
             assert torch.equal(graphed[name], eager[name]), (replay, name)
+
+
+@pytest.mark.parametrize("n_global,rows,cols,cell,N", [(31, 3, 1, 32, 127), (32, 2, 2, 32, 161), (33, 1, 3, 33, 132),
+                                                       (1, 1, 1, 1, 2), (65, 31, 2, 3, 260), (40, 90, 5, 4, 2100)])
+def test_f32_tile_edges(n_global, rows, cols, cell, N):
+    """Lists and segments at and beside multiples of the 32-row tiles; the last one is long enough for
+    question-token owners that the tables cut into chunks."""
+    st = synth._stack([synth.flatten_table(N, n_global, rows, cols, np.full(rows * cols, cell))])
+    q, k, v, do = synth.draw_tensors(np.random.default_rng(N), 1, 2, N, 64, "f32", 4)
+    check_workload(synth.Workload(f"f32 edges {N}", "f32", st, np.array([ROW, COL], np.uint8), q, k, v, do, 0.125), True)
