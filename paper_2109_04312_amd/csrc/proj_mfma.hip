@@ -329,6 +329,7 @@ struct WgradArgs {
 // halves the operand reads per contraction and is used when its tiles still fill the chip without
 // cutting the tokens into many ranges (each range leaves an fp32 partial matrix behind).
 constexpr int kWgRows = 256, kWgThreads = 512;
+constexpr int kMaxRange = 1024;  // token blocks of one range
 template <int KX>
 struct WgShape {
   static constexpr int kCols = 64 * KX, kTiles = 4 + KX, kStageBytesW = kTiles * kTileBytes;
@@ -396,11 +397,31 @@ __global__ __launch_bounds__(kWgThreads, 1) void proj_wgrad_kernel(WgradArgs a) 
       load_to_lds_16(bp, (unsigned)r1 * row_stride[j] + (ll.chunk0 ^ 2) * 16, st + lds_off[j] + 8 * 128);
     }
   };
-  // next block at or after s that has a non-pad row (all of this is scalar)
-  auto next_live = [&](int s) {
-    while (s < s_end && a.pad[s] == ~0ull) ++s;
-    return s;
-  };
+  // The range's blocks with a non-pad row, in order, and their pad masks: listed in LDS before the loop
+  // (looked up one by one inside it, every step of the loop waited for two dependent scalar loads:
+  // 3 us a step where the contractions need 0.9).
+  __shared__ unsigned long long live_mask[kMaxRange];
+  __shared__ unsigned short live_at[kMaxRange];
+  __shared__ int wave_live[kWgThreads / 64];
+  int n_live = 0;
+  for (int s0 = s_begin; s0 < s_end; s0 += kWgThreads) {
+    const unsigned long long mask = s0 + tid < s_end ? a.pad[s0 + tid] : ~0ull;
+    const unsigned long long ballot = __ballot(mask != ~0ull);
+    if (lane == 0) wave_live[wave] = __popcll(ballot);
+    __syncthreads();
+    int at = n_live + __popcll(ballot & ((1ull << lane) - 1));
+#pragma unroll
+    for (int w = 0; w < kWgThreads / 64; ++w) {
+      if (w < wave) at += wave_live[w];
+      n_live += wave_live[w];
+    }
+    if (mask != ~0ull) {
+      live_mask[at] = mask;
+      live_at[at] = (unsigned short)(s0 + tid - s_begin);
+    }
+    __syncthreads();
+  }
+  n_live = __builtin_amdgcn_readfirstlane(n_live);
 
   f32x16 acc[2][S::kXF];
 #pragma unroll
@@ -417,26 +438,20 @@ __global__ __launch_bounds__(kWgThreads, 1) void proj_wgrad_kernel(WgradArgs a) 
     toff[db][1] = tr_off(lane, db, 1);
   }
 
-  // blocks in flight: `cur` (being waited for, then consumed) and the kStagesW - 1 after it
-  int nx[S::kStagesW];  // nx[0] = cur
-  nx[0] = next_live(s_begin);
-#pragma unroll
-  for (int k = 1; k < S::kStagesW; ++k) nx[k] = next_live(nx[k - 1] + 1);
+  auto block_at = [&](int i) { return s_begin + __builtin_amdgcn_readfirstlane((int)live_at[i]); };
 #pragma unroll
   for (int k = 0; k + 1 < S::kStagesW; ++k)
-    if (nx[k] < s_end) issue_stage(nx[k], k);
-  int it = 0;
-  while (nx[0] < s_end) {
-    const unsigned long long padmask = a.pad[nx[0]];
-    // block nx[0] has landed: everything but the loads of the blocks after it that were issued
-    int younger = 0;
-#pragma unroll
-    for (int k = 1; k + 1 < S::kStagesW; ++k) younger += nx[k] < s_end;
-    wait_vmcnt_le<S::kLoadsW * (S::kStagesW - 2)>(younger * S::kLoadsW);
+    if (k < n_live) issue_stage(block_at(k), k);
+  for (int it = 0; it < n_live; ++it) {
+    const unsigned long long padmask = live_mask[it];
+    const int ahead = it + S::kStagesW - 1;
+    const int next = block_at(min(ahead, n_live - 1));
+    // block `it` has landed: everything but the loads of the blocks after it that were issued
+    wait_vmcnt_le<S::kLoadsW * (S::kStagesW - 2)>(min(S::kStagesW - 2, n_live - 1 - it) * S::kLoadsW);
     barrier_no_fence();          // ... for everyone; and everyone is done with the block before it
-    if (nx[S::kStagesW - 1] < s_end) issue_stage(nx[S::kStagesW - 1], (it + S::kStagesW - 1) % S::kStagesW);
+    if (ahead < n_live) issue_stage(next, ahead % S::kStagesW);
     char* st = lds + (it % S::kStagesW) * S::kStageBytesW;
-    if (padmask) {               // uniform: clear the pad rows of all tiles (0 x anything = 0 then)
+    if (padmask) {               // the same for every lane: clear the pad rows of all tiles (0 x anything = 0 then)
       const int row = tid & 63, which = tid >> 6;
       if (which < S::kTiles && ((padmask >> row) & 1ull)) {
         uint4* p = reinterpret_cast<uint4*>(st + which * kTileBytes + row * 128);
@@ -469,10 +484,6 @@ __global__ __launch_bounds__(kWgThreads, 1) void proj_wgrad_kernel(WgradArgs a) 
         bias_acc[1] = sum8(gf[k16 & 1][1], bias_acc[1]);
       }
     }
-#pragma unroll
-    for (int k = 0; k + 1 < S::kStagesW; ++k) nx[k] = nx[k + 1];
-    nx[S::kStagesW - 1] = next_live(nx[S::kStagesW - 2] + 1);
-    ++it;
   }
 
   // C tile: lane (m, hl) holds column m, register 4 g + r holds row 8 g + 4 hl + r
@@ -593,7 +604,7 @@ BwdPlan plan_bwd(int B, int N, int F, int E, size_t wt_elems) {
   // tile is taken when it fills the chip with at most sixteen ranges.
   auto ranges = [&](int kx) {
     const int tiles = ((F + kWgRows - 1) / kWgRows) * (E / (64 * kx));
-    return std::max(1, std::min(std::max(1, 256 / tiles), total_blocks / 8));
+    return std::max({1, std::min(std::max(1, 256 / tiles), total_blocks / 8), (total_blocks + kMaxRange - 1) / kMaxRange});
   };
   p.kx = (E % 256 == 0 && ((F + kWgRows - 1) / kWgRows) * (E / 256) * ranges(4) >= 192 && ranges(4) <= 16) ? 4 : 2;
   const int want = ranges(p.kx);
