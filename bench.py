@@ -312,7 +312,7 @@ def projections(cfg, steps, warmup):
                                "frac_of_bf16_mfma_peak": flop[n] / t / 1e12 / PEAK_BF16_TFLOPS} for n, t in res.items()},
            "workload": w.name, "B": B, "N": N, "H": H, "E": E, "non_pad_tokens": nonpad, "dtype": "bf16",
            "us_forward_wall": both * 1e6, "us_backward_wall": both_bwd * 1e6, "steps": steps,
-           "backward_wall_includes": "weight transposes and pad masks (preparation kernel), partial-sum finalize kernels",
+           "backward_wall_includes": "the sum of the weight gradients' partial matrices, which rides on the input gradients' kernels",
            "flop_convention": "2 * non-pad tokens * K * F per product (pad rows are not algorithmic work)",
            "timing": "median of HIP event brackets recorded by the library around each launch, minus the median "
                      "of event pairs with nothing between their records"}

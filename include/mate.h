@@ -318,8 +318,8 @@ mate_status mate_out_project(const void* o, const void* w_o, const float* bias,
  *     dbias      = sum over non-pad tokens of G        [E] float
  *
  *   dx / d_o, dw_*, dbias   any of them may be NULL (not computed); dbias needs dw_*
- *   workspace   mate_project_bwd_workspace_bytes(B, N, H, E) bytes (a transposed copy of the
- *               weights, one 64-bit pad mask per 64 tokens, partial sums of the weight gradient)
+ *   workspace   mate_project_bwd_workspace_bytes(B, N, H, E) bytes (partial sums of the weight
+ *               gradient)
  *   t, H, E     as for the forward calls
  * Asynchronous on `stream`; deterministic (partial sums are added in a fixed order, no atomics).
  */

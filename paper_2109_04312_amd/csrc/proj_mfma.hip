@@ -1,26 +1,30 @@
-// The projections either side of the attention, bf16 MFMA (gfx950):
+// The projections either side of the attention and their gradients, bf16 MFMA (gfx950):
 //   QKV:  q[b,i,k,:] = W_Q^i x[b,k,:], likewise K and V -- the W^i X_k of the head equation of
 //         Section 3 for all heads at once, written straight into the [B, H, N, 64] layout the
 //         attention kernels read (the head split costs nothing);
 //   out:  y[b,k,:] = W_O concat_i o[b,i,k,:], reading the attention output head by head in the
-//         layout it was written in (no concatenation pass).
+//         layout it was written in (no concatenation pass);
+//   dX, d_o: the same products with the weight matrix transposed, read through transposing LDS
+//         reads from the matrix as it is;
+//   dW:   contracts over tokens, dW[f, e] = sum_tok G[tok, f] X[tok, e].
 // Pad tokens are not computed when a whole token tile is padding, and are stored as zeros.
 //
-// Both are one kernel template: C^T[f, tok] = sum_k W[f, k] T[tok, k] with W rows (features) as
-// the MFMA A operand and token rows as the B operand, so a lane owns a token column and its
-// registers run over features -- the layout of the attention kernels' accumulators, and the same
-// transposing epilogue through LDS to whole 128-byte rows.  Both operands are K-contiguous and
-// are streamed in 64-row x 64-k tiles of 128-byte rows straight from global memory into LDS
-// (global_load_lds_dwordx4), XOR-swizzled for conflict-free 16-byte operand reads, through a
-// ring of stages with explicit vmcnt waits.
+// All are one main loop over two operands: C[b, a] = sum_k B[b, k] A[a, k], a contiguous in the
+// output (features, or columns of dW), so that the MFMA accumulator layout (rows = a: a lane holds
+// four consecutive a of one b) turns into 16-byte stores without a detour through LDS.  Operands are
+// streamed in tiles of 64 rows x 128 bytes straight from global memory into LDS (global_load_lds_dwordx4),
+// XOR-swizzled so that plain 16-byte operand reads and transposing 8-byte ones are both free of bank
+// conflicts, through a ring of stages with explicit vmcnt waits.  A tile is either "plain" (rows =
+// operand rows, 64 of k per stage) or "transposed" (rows = 64 of k, columns = operand rows: whatever
+// contracts over tokens, and the weights of dX and d_o).
 //
-// Workgroup tile: kTokTiles x 64 tokens by kFeatTiles x 64 features; a wavefront owns 32 kBT
-// tokens by 64 features (one head of Q, K or V).  Workgroup i runs on XCD i mod 8; every XCD
-// takes a contiguous range of token tiles and walks the feature tiles fastest, so the token
-// rows it streams stay in its L2 while the (small) weight matrix cycles.
+// v_mfma_f32_16x16x32_bf16 rather than 32x32x16: at these sizes the chip is limited by power, and the
+// smaller instruction moves half as many accumulator bytes per operation (16384 x 3072 x 1024: 97 us
+// against 104 us, everything else equal).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 
 #include "d2l.h"
 #include "launch.h"
@@ -29,272 +33,365 @@
 namespace mate {
 namespace {
 
-template <int kTokTiles_, int kFeatTiles_, int kWavesTok_, int kStages_>
-struct ProjShape {
-  static constexpr int kTokTiles = kTokTiles_, kFeatTiles = kFeatTiles_;
-  static constexpr int kWavesTok = kWavesTok_, kWavesFeat = kFeatTiles_;  // 64 features per wavefront
-  static constexpr int kWaves = kWavesTok * kWavesFeat;
-  static constexpr int kThreadsP = 64 * kWaves;
-  static constexpr int kBT = kTokTiles * 2 / kWavesTok;       // 32-token blocks per wavefront
-  static constexpr int kStages = kStages_;
-  static constexpr int kStageBytesP = (kTokTiles + kFeatTiles) * kTileBytes;
-  static constexpr int kQuarters = 4 * (kTokTiles + kFeatTiles) / kWaves;  // 16-row loads per wavefront and stage
-  static_assert(4 * (kTokTiles + kFeatTiles) % kWaves == 0, "loads must divide evenly");
-  static_assert(kTokTiles * 2 % kWavesTok == 0, "token blocks must divide evenly");
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+// A pointer the compiler can keep in scalar registers (the value is the same in every lane).
+__device__ inline const char* uniform_ptr(const void* p) {
+  const unsigned long long v = reinterpret_cast<unsigned long long>(p);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+  return reinterpret_cast<const char*>(((unsigned long long)hi << 32) | lo);
+}
+
+// Workgroup shape: kA x 64 rows of operand A by kB x 64 rows of operand B, kWA x kWB wavefronts.
+template <int kA_, int kB_, int kWA_, int kWB_, int kStages_, int kPerCU_>
+struct Shape {
+  static constexpr int kA = kA_, kB = kB_, kWA = kWA_, kWB = kWB_, kStages = kStages_, kPerCU = kPerCU_;
+  static constexpr int kWaves = kWA * kWB, kThreads = 64 * kWaves;
+  static constexpr int kRowsA = 64 * kA, kRowsB = 64 * kB;
+  static constexpr int kFA = 4 * kA / kWA, kFB = 4 * kB / kWB;  // 16-row blocks of a wavefront
+  static constexpr int kStageBytes = (kA + kB) * kTileBytes, kLds = kStages * kStageBytes;
+  static constexpr int kLoadsA = 8 * kA / kWaves, kLoadsB = 8 * kB / kWaves, kLoads = kLoadsA + kLoadsB;
+  static_assert(8 * kA % kWaves == 0 && 8 * kB % kWaves == 0, "loads must divide evenly");
+  static_assert(4 * kA % kWA == 0 && 4 * kB % kWB == 0 && kFA % 2 == 0, "blocks must divide evenly");
 };
 
+// Load instruction i of a wavefront brings eight rows of one tile: which tile, which row this lane's
+// 16 bytes belong to, and which 16-byte chunk of it.
+struct LoadUnit {
+  int tile, row, chunk;
+};
+template <int kWaves>
+__device__ __forceinline__ LoadUnit load_unit(int wave, int lane, int i) {
+  const int u = wave + kWaves * i;
+  LoadUnit l;
+  l.tile = u >> 3;
+  l.row = (u & 7) * 8 + (lane >> 3);
+  l.chunk = (lane & 7) ^ swz(l.row & 15);
+  return l;
+}
+template <int kWaves>
+__device__ __forceinline__ int load_dst(int wave, int i) {
+  const int u = wave + kWaves * i;
+  return (u >> 3) * kTileBytes + (u & 7) * 8 * 128;
+}
+
+// Operand fragment of 16 rows and 32 of k.  Lane l = 16 q + r: row r, k = 8 q .. 8 q + 7.
+struct FragOffsets {
+  int plain[2];      // per 32-wide k slice
+  int trans[2][4];   // [first / second four of k][16-column block of a tile]; a k slice is 32 rows further
+};
+template <bool kTransposed>
+__device__ __forceinline__ void frag_offsets(FragOffsets& f, int lane) {
+  const int r = lane & 15, q = lane >> 4;
+  if (!kTransposed) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) f.plain[k] = r * 128 + (((4 * k + q) ^ swz(r)) << 4);
+  } else {
+    // 16 lanes read 4 rows x 16 columns: lane i addresses row i / 4, columns 4 (i % 4) .., and receives
+    // column i of the four rows
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int row = 8 * q + 4 * h + (r >> 2);
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        f.trans[h][c] = row * 128 + (((2 * c + ((r & 3) >> 1)) ^ swz(row & 15)) << 4) + ((r & 1) << 3);
+    }
+  }
+}
+template <bool kTransposed>
+__device__ __forceinline__ bf16x8 read_frag(const char* tiles, const FragOffsets& f, int block, int k) {
+  if (!kTransposed) return read_plain(tiles + block * 16 * 128, f.plain[k]);
+  const char* t = tiles + (block >> 2) * kTileBytes + k * 32 * 128;
+  return read_transposed(t, f.trans[0][block & 3], f.trans[1][block & 3]);
+}
+
+// One stage (64 of k): two slices of 32.
+template <class S, bool kTA, bool kTB, class PerSlice>
+__device__ __forceinline__ void contract_stage(const char* stage, const FragOffsets& fa, const FragOffsets& fb, int wa,
+                                               int wb, f32x4 (&acc)[S::kFA][S::kFB], PerSlice&& per_slice) {
+  const char* ta = stage + (kTA ? 0 : wa * S::kFA * 16 * 128);
+  const char* tb = stage + S::kA * kTileBytes + (kTB ? 0 : wb * S::kFB * 16 * 128);
+  bf16x8 a[2][S::kFA], b[2][S::kFB];
+  auto read_slice = [&](int k) {
+#pragma unroll
+    for (int i = 0; i < S::kFA; ++i) a[k][i] = read_frag<kTA>(ta, fa, (kTA ? wa * S::kFA : 0) + i, k);
+#pragma unroll
+    for (int j = 0; j < S::kFB; ++j) b[k][j] = read_frag<kTB>(tb, fb, (kTB ? wb * S::kFB : 0) + j, k);
+  };
+  read_slice(0);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    if (k == 0) read_slice(1);  // the second slice travels while the first is contracted
+#pragma unroll
+    for (int i = 0; i < S::kFA; ++i)
+#pragma unroll
+      for (int j = 0; j < S::kFB; ++j) acc[i][j] = mfma16(a[k][i], b[k][j], acc[i][j]);
+    per_slice(b[k]);
+  }
+}
+
+// Partial sums of a weight gradient (one fp32 matrix per token range, see below), added in range order
+// by the workgroups behind the tiles of the product that follows: a launch of its own took 11 to 14 us
+// on the benchmark layer, 5 of them the launch, while the product leaves compute units idle at its end.
+struct RangeSums {
+  const float* part;       // [splits][n] partial sums, n a multiple of 4
+  const float* part_bias;  // [splits][n_bias]
+  float *out, *out_bias;   // out_bias may be null
+  size_t n;
+  int n_bias, splits, blocks;  // blocks: workgroups that share the work (0: nothing to add)
+};
+__device__ __forceinline__ void add_ranges(const RangeSums& s, int block, int threads) {
+  const size_t stride = (size_t)s.blocks * threads, first = (size_t)block * threads + threadIdx.x;
+  const f32x4* part = reinterpret_cast<const f32x4*>(s.part);
+  for (size_t i = first; i < s.n / 4; i += stride) {
+    f32x4 v = part[i];
+    for (int k0 = 1; k0 < s.splits; k0 += 4) {  // four at a time, all loaded before the first is added
+      f32x4 x[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = part[(size_t)min(k0 + e, s.splits - 1) * (s.n / 4) + i];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (k0 + e < s.splits) v += x[e];
+    }
+    reinterpret_cast<f32x4*>(s.out)[i] = v;
+  }
+  if (s.out_bias)
+    for (size_t i = first; i < (size_t)s.n_bias; i += stride) {
+      float v = s.part_bias[i];
+      for (int k = 1; k < s.splits; ++k) v += s.part_bias[(size_t)k * s.n_bias + i];
+      s.out_bias[i] = v;
+    }
+}
+
+// ======================================================================================
+// Products with the weights: forward, dX, d_o
+// ======================================================================================
 struct ProjArgs {
-  const unsigned short* w;       // [F][K] row-major
-  const unsigned short* tok;     // kOut false: [B*N][K] row-major (x, or dy in the backward)
-  const unsigned short* tok3[3]; // kOut true: [B][H][N][64] tensors whose heads are the k steps, one
+  const unsigned short* w;       // plain: [F][K] row-major; transposed: [K][F]
+  const unsigned short* tok;     // flat tokens: [B*N][K] row-major (x, or dy in the backward)
+  const unsigned short* tok3[3]; // head tokens: [B][H][N][64] tensors whose heads are the k steps, one
                                  // after the other (o; or dq, dk, dv in the backward)
   const float* bias;             // [F] or null
   const unsigned char* flags;    // [B][N]
-  unsigned short* out[3];        // QKV: q, k, v [B][H][N][64];  out: y [B][N][E] in out[0]
-  int B, N, H, E;
+  unsigned short* out[3];        // head layout: q, k, v (or d_o) [B][H][N][64];  flat: [B][N][F] in out[0]
+  int B, N, H;
   int F, K;                      // features, contraction length
   int tok_tiles_per_seq;         // ceil(N / tile tokens)
-  int feat_tiles;                // F / tile features
-  int total;                     // workgroups with work
+  int feat_tiles;                // ceil(F / tile features)
+  int tile_blocks;               // workgroups of the product; those behind them add `ranges`
+  RangeSums ranges;
 };
 
-// One stage: kTokTiles token tiles then kFeatTiles weight tiles of 64 rows x 128 bytes.
-template <class S, bool kOut>
-__global__ __launch_bounds__(S::kThreadsP, S::kWaves == 4 ? 2 : 1) void proj_kernel(ProjArgs a) {
+// kHeadTok: the token operand comes from head-layout tensors and the output is flat; else the reverse.
+// kTransposedW: the weight operand is read transposed.
+template <class S, bool kHeadTok, bool kTransposedW>
+__global__ __launch_bounds__(S::kThreads, S::kWaves / 4 * S::kPerCU) void proj_kernel(ProjArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  constexpr int kTokRows = S::kTokTiles * 64, kFeatRows = S::kFeatTiles * 64;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int m = lane & 31, hl = lane >> 5;
+  const int wa = wave / S::kWB, wb = wave - wa * S::kWB;
+  const int r = lane & 15, quarter = lane >> 4;
 
-  // workgroup -> (token tile, feature tile): XCD q owns a contiguous range of the linear order
-  const int q = blockIdx.x & 7, j = blockIdx.x >> 3;
-  const int per = (a.total + 7) >> 3;
-  const int idx = q * per + j;
-  if (j >= per || idx >= a.total) return;
-  const int tt = idx / a.feat_tiles, ft = idx - tt * a.feat_tiles;
-  const int b = tt / a.tok_tiles_per_seq, n0 = (tt - b * a.tok_tiles_per_seq) * kTokRows;
-  const int f0 = ft * kFeatRows;
-  const int rows_valid = min(kTokRows, a.N - n0);
-
-  const int wt = wave / S::kWavesFeat, wf = wave - wt * S::kWavesFeat;
-  // where this wavefront's 64 features go: QKV -> tensor and head; out -> a 128-byte piece of y
-  unsigned short* dst;
-  size_t dst_stride;  // elements between consecutive tokens
-  if (kOut) {
-    dst = a.out[0] + ((size_t)b * a.N + n0) * a.E + f0 + 64 * wf;
-    dst_stride = a.E;
-  } else {
-    const int head_slot = f0 / 64 + wf, t = head_slot / a.H, h = head_slot - t * a.H;
-    dst = a.out[t] + (((size_t)b * a.H + h) * a.N + n0) * kD;
-    dst_stride = kD;
+  if ((int)blockIdx.x >= a.tile_blocks) {  // behind the tiles: partial sums of a weight gradient
+    add_ranges(a.ranges, blockIdx.x - a.tile_blocks, S::kThreads);
+    return;
   }
-  const unsigned char* fl = a.flags + (size_t)b * a.N + n0;
+  // Workgroup -> (token tile, feature tile).  XCD q walks the feature tiles fastest, so the token rows it
+  // streams stay in its L2 while the weights cycle, and takes one of every eight consecutive token
+  // tiles, another one each time, so that the padding at the end of the sequences is spread over all XCDs.
+  const int q = blockIdx.x & 7, jx = blockIdx.x >> 3;
+  const int tj = jx / a.feat_tiles, f0 = (jx - tj * a.feat_tiles) * S::kRowsA;
+  const int tt = 8 * tj + ((q + 3 * tj) & 7), b = tt / a.tok_tiles_per_seq, tile = tt - b * a.tok_tiles_per_seq;
+  if (b >= a.B) return;
+  const int n0 = tile * S::kRowsB;
+  const int rows = min(S::kRowsB, a.N - n0), feats = min(S::kRowsA, a.F - f0);
 
-  // a tile of padding only: zeros, no arithmetic.  The flags stay in LDS for the epilogue (read
-  // from global memory there, every store would wait for a flag load and for the store before it).
-  __shared__ unsigned char tok_flag[kTokRows];
-  int any = 0;
-  for (int r = tid; r < rows_valid; r += S::kThreadsP) {
-    const unsigned char f = fl[r];
-    tok_flag[r] = f;
-    any |= f != 2;
-  }
-  any = __syncthreads_or(any);
-
-  // ---- operand streams ------------------------------------------------------------------
-  // token operand: row r of the tile at tok_base + r * tok_stride bytes, advancing tok_step
-  // bytes per 64-wide k step; weights likewise
-  const char* tok_base;
-  unsigned tok_stride, tok_step;
-  if (kOut) {  // k step = one head of one of the head-layout tensors
-    tok_base = reinterpret_cast<const char*>((((size_t)b * a.H) * a.N + n0) * kD * 2);  // offset only
-    tok_stride = kD * 2;
-    tok_step = (unsigned)a.N * kD * 2;
-  } else {
-    tok_base = reinterpret_cast<const char*>(a.tok + ((size_t)b * a.N + n0) * a.E);
-    tok_stride = (unsigned)a.E * 2;
-    tok_step = 128;
-  }
-  const char* w_base = reinterpret_cast<const char*>(a.w + (size_t)f0 * a.K);
-  const unsigned w_stride = (unsigned)a.K * 2;
-
-  // this wavefront's share of a stage: kQuarters loads of 16 rows (two instructions of 8 rows)
-  const LoadLane ll = make_load_lane(0, lane);  // row inside a 16-row group, swizzled chunk
-  unsigned goff[S::kQuarters][2];
-  int loff[S::kQuarters];
-  bool is_w[S::kQuarters];
+  // ---- operand streams: per load a wave-uniform base and a 32-bit lane offset -----------------------
+  unsigned off[S::kLoads];
 #pragma unroll
-  for (int i = 0; i < S::kQuarters; ++i) {
-    const int qi = wave + S::kWaves * i;          // quarter index in the stage
-    const int tile = qi >> 2, r0 = (qi & 3) * 16 + ll.row0;
-    loff[i] = tile * kTileBytes + (qi & 3) * 16 * 128;
-    is_w[i] = tile >= S::kTokTiles;
-    if (is_w[i]) {
-      const int row = (tile - S::kTokTiles) * 64 + r0;
-      goff[i][0] = (unsigned)row * w_stride + ll.chunk0 * 16;
-      goff[i][1] = (unsigned)(row + 8) * w_stride + (ll.chunk0 ^ 2) * 16;
-    } else {
-      const int row = tile * 64 + r0;  // rows past the end of the sequence repeat the last one
-      goff[i][0] = (unsigned)min(row, rows_valid - 1) * tok_stride + ll.chunk0 * 16;
-      goff[i][1] = (unsigned)min(row + 8, rows_valid - 1) * tok_stride + (ll.chunk0 ^ 2) * 16;
-    }
+  for (int i = 0; i < S::kLoadsA; ++i) {
+    const LoadUnit l = load_unit<S::kWaves>(wave, lane, i);
+    // (features past F repeat the last 64-column block or the last row, and are not stored)
+    off[i] = kTransposedW ? (unsigned)l.row * (unsigned)a.F * 2 + (unsigned)min(64 * l.tile, feats - 64) * 2 + l.chunk * 16
+                          : (unsigned)min(64 * l.tile + l.row, feats - 1) * (unsigned)a.K * 2 + l.chunk * 16;
   }
-  auto issue_stage = [&](int ks) {
-    char* st = lds + (ks % S::kStages) * S::kStageBytesP;
-    const char* tb;
-    if (kOut) {
-      const int t = ks / a.H, h = ks - t * a.H;
-      const unsigned short* tensor = t == 0 ? a.tok3[0] : t == 1 ? a.tok3[1] : a.tok3[2];
-      tb = reinterpret_cast<const char*>(tensor) + (size_t)tok_base + (size_t)h * tok_step;
-    } else {
-      tb = tok_base + (size_t)ks * tok_step;
-    }
-    const char* wb = w_base + (size_t)ks * 128;
 #pragma unroll
-    for (int i = 0; i < S::kQuarters; ++i) {
-      const char* base = is_w[i] ? wb : tb;
-      load_to_lds_16(base, goff[i][0], st + loff[i]);
-      load_to_lds_16(base, goff[i][1], st + loff[i] + 8 * 128);
+  for (int i = 0; i < S::kLoadsB; ++i) {  // (tokens past the end repeat the last one)
+    const LoadUnit l = load_unit<S::kWaves>(wave, lane, i);
+    off[S::kLoadsA + i] = (unsigned)min(64 * l.tile + l.row, rows - 1) * (kHeadTok ? kD * 2u : (unsigned)a.K * 2) + l.chunk * 16;
+  }
+  const char* w_ptr = reinterpret_cast<const char*>(kTransposedW ? a.w + f0 : a.w + (size_t)f0 * a.K);  // of the next stage
+  const size_t w_step = kTransposedW ? (size_t)64 * a.F * 2 : 128;
+  const size_t head0 = (((size_t)b * a.H) * a.N + n0) * kD * 2, t_step = kHeadTok ? (size_t)a.N * kD * 2 : 128;
+  const char* t_ptr = kHeadTok ? reinterpret_cast<const char*>(a.tok3[0]) + head0
+                               : reinterpret_cast<const char*>(a.tok + ((size_t)b * a.N + n0) * a.K);
+  int head = 0, tensor = 0;
+  auto issue_stage = [&](int g) {
+    char* st = lds + (g % S::kStages) * S::kStageBytes;
+    const char *w_base = uniform_ptr(w_ptr), *t_base = uniform_ptr(t_ptr);
+#pragma unroll
+    for (int i = 0; i < S::kLoadsA; ++i) load_to_lds_16(w_base, off[i], st + load_dst<S::kWaves>(wave, i));
+#pragma unroll
+    for (int i = 0; i < S::kLoadsB; ++i)
+      load_to_lds_16(t_base, off[S::kLoadsA + i], st + S::kA * kTileBytes + load_dst<S::kWaves>(wave, i));
+    w_ptr += w_step;
+    t_ptr += t_step;
+    if (kHeadTok && ++head == a.H) {  // the next tensor's heads
+      head = 0;
+      ++tensor;
+      t_ptr = reinterpret_cast<const char*>(tensor == 1 ? a.tok3[1] : a.tok3[2]) + head0;
     }
   };
+  const int nk = a.K / 64;
+#pragma unroll
+  for (int s = 0; s < S::kStages - 1; ++s)
+    if (s < nk) issue_stage(s);
 
-  f32x16 acc[2][S::kBT];
+  // While the first stages travel: is any token of the tile not padding (every wavefront looks at all of
+  // them), which of this lane's are, and the bias of this lane's features.
+  const unsigned char* fl = a.flags + (size_t)b * a.N + n0;
+  bool any = false;
 #pragma unroll
-  for (int bf = 0; bf < 2; ++bf)
+  for (int i = 0; i < S::kB; ++i) any |= fl[min(64 * i + lane, rows - 1)] < 2;
+  int row[S::kFB];
+  unsigned pad_bits = 0;
 #pragma unroll
-    for (int bt = 0; bt < S::kBT; ++bt) acc[bf][bt] = zero16();
+  for (int j = 0; j < S::kFB; ++j) {
+    row[j] = min((wb * S::kFB + j) * 16 + r, rows - 1);
+    pad_bits |= (unsigned)(fl[row[j]] >= 2) << j;
+  }
+  f32x4 bias[S::kFA];
+#pragma unroll
+  for (int i = 0; i < S::kFA; ++i) {
+    bias[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (a.bias) bias[i] = *reinterpret_cast<const f32x4*>(a.bias + f0 + min((wa * S::kFA + i) * 16, feats - 16) + 4 * quarter);
+  }
 
-  if (any) {
-    const int nk = a.K / 64;
-    int poff[4];
+  f32x4 acc[S::kFA][S::kFB];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) poff[ks] = plain_off(m, hl, ks);
+  for (int i = 0; i < S::kFA; ++i)
 #pragma unroll
-    for (int s = 0; s < S::kStages - 1; ++s)
-      if (s < nk) issue_stage(s);
-    constexpr int kLoadsPerStage = 2 * S::kQuarters;
+    for (int j = 0; j < S::kFB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (__any(any)) {  // (a tile of padding only is stored as zeros without arithmetic)
+    FragOffsets fa, fb;
+    frag_offsets<kTransposedW>(fa, lane);
+    frag_offsets<false>(fb, lane);
     for (int ks = 0; ks < nk; ++ks) {
       // stage ks has landed: everything but the younger stages' loads (fewer near the end)
-      const int younger = min(S::kStages - 2, nk - 1 - ks);
-      wait_vmcnt_le<kLoadsPerStage * (S::kStages - 2)>(younger * kLoadsPerStage);
+      wait_vmcnt_le<S::kLoads * (S::kStages - 2)>(min(S::kStages - 2, nk - 1 - ks) * S::kLoads);
       barrier_no_fence();  // ... for every wavefront, and everyone is done with stage ks - 1
       if (ks + S::kStages - 1 < nk) issue_stage(ks + S::kStages - 1);
-      const char* st = lds + (ks % S::kStages) * S::kStageBytesP;
-      const char* tok_t = st + wt * S::kBT * 32 * 128;
-      const char* w_t = st + S::kTokTiles * kTileBytes + wf * 64 * 128;
-      // operand fragments are read one 16-wide k slice ahead of the contractions that use them
-      bf16x8 wfrag[2][2], tfrag[2][S::kBT];
-      auto read_slice = [&](int buf, int k16) {
-#pragma unroll
-        for (int bf = 0; bf < 2; ++bf) wfrag[buf][bf] = read_plain(w_t + bf * 32 * 128, poff[k16]);
-#pragma unroll
-        for (int bt = 0; bt < S::kBT; ++bt) tfrag[buf][bt] = read_plain(tok_t + bt * 32 * 128, poff[k16]);
-      };
-      read_slice(0, 0);
-#pragma unroll
-      for (int k16 = 0; k16 < 4; ++k16) {
-        if (k16 + 1 < 4) read_slice((k16 + 1) & 1, k16 + 1);
-#pragma unroll
-        for (int bf = 0; bf < 2; ++bf)
-#pragma unroll
-          for (int bt = 0; bt < S::kBT; ++bt)
-            acc[bf][bt] = mfma(wfrag[k16 & 1][bf], tfrag[k16 & 1][bt], acc[bf][bt]);
-      }
+      contract_stage<S, kTransposedW, false>(lds + (ks % S::kStages) * S::kStageBytes, fa, fb, wa, wb, acc,
+                                             [](const bf16x8 (&)[S::kFB]) {});
     }
   }
-  __syncthreads();  // the stages are free: reuse them for the epilogue
 
-  // ---- epilogue: + bias, round to bf16, transpose through this wavefront's own 4 KB of LDS,
-  // store whole 128-byte pieces per token ------------------------------------------------------
-  float4 bias4[2][4];
+  // ---- epilogue: + bias, round to bf16.  A lane holds features 16 i + 4 quarter .. + 3 of token 16 j + r;
+  // after exchanging quarters between neighbouring blocks it holds eight consecutive ones and stores
+  // 16 bytes, 64 of a token's bytes per instruction. ------------------------------------------------
 #pragma unroll
-  for (int bf = 0; bf < 2; ++bf)
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-      bias4[bf][g] = a.bias && any ? *reinterpret_cast<const float4*>(a.bias + f0 + 64 * wf + 32 * bf + 8 * g + 4 * hl)
-                                   : make_float4(0.f, 0.f, 0.f, 0.f);
-  char* stage = lds + wave * (32 * 128);
-#pragma unroll
-  for (int bt = 0; bt < S::kBT; ++bt) {
-#pragma unroll
-    for (int bf = 0; bf < 2; ++bf)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x16& c = acc[bf][bt];
-        const float4 bb = bias4[bf][g];
-        uint2 v;
-        v.x = f32_to_bf16_bits(c[4 * g] + bb.x) | ((unsigned)f32_to_bf16_bits(c[4 * g + 1] + bb.y) << 16);
-        v.y = f32_to_bf16_bits(c[4 * g + 2] + bb.z) | ((unsigned)f32_to_bf16_bits(c[4 * g + 3] + bb.w) << 16);
-        *reinterpret_cast<uint2*>(stage + m * 128 + (((4 * bf + g) ^ (m & 7)) << 4) + 8 * hl) = v;
-      }
-    // same wavefront writes and reads: LDS executes a wavefront's accesses in order
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const int row = it * 8 + (lane >> 3), piece = lane & 7;
-      const int r = (wt * S::kBT + bt) * 32 + row;  // token row inside the workgroup tile
-      if (r < rows_valid) {
-        uint4 v = *reinterpret_cast<const uint4*>(stage + row * 128 + ((piece ^ (row & 7)) << 4));
-        if (tok_flag[r] == 2) v = make_uint4(0, 0, 0, 0);
-        *reinterpret_cast<uint4*>(dst + (size_t)r * dst_stride + piece * 8) = v;
-      }
+  for (int i = 0; i < S::kFA; i += 2) {
+    const int fw = (wa * S::kFA + i) * 16;       // first feature of the block pair in the tile
+    if (fw >= feats) break;                      // (F is a multiple of 64: a pair is inside or outside)
+    unsigned short* dst;
+    size_t dst_stride;  // elements between consecutive tokens
+    if (kHeadTok) {
+      dst = a.out[0] + ((size_t)b * a.N + n0) * a.F + f0 + fw;
+      dst_stride = a.F;
+    } else {
+      const int head_slot = (f0 + fw) >> 6, x = head_slot / a.H, h = head_slot - x * a.H;
+      unsigned short* out = x == 0 ? a.out[0] : x == 1 ? a.out[1] : a.out[2];
+      dst = out + (((size_t)b * a.H + h) * a.N + n0) * kD + (fw & 63);
+      dst_stride = kD;
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    dst += (quarter & 1) * 16 + (quarter >> 1) * 8;
+#pragma unroll
+    for (int j = 0; j < S::kFB; ++j) {
+      unsigned u[2][2];
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const f32x4 c = acc[i + p][j] + bias[i + p];
+        u[p][0] = f32_to_bf16_bits(c[0]) | ((unsigned)f32_to_bf16_bits(c[1]) << 16);
+        u[p][1] = f32_to_bf16_bits(c[2]) | ((unsigned)f32_to_bf16_bits(c[3]) << 16);
+      }
+      const auto lo = __builtin_amdgcn_permlane16_swap(u[0][0], u[1][0], false, false);
+      const auto hi = __builtin_amdgcn_permlane16_swap(u[0][1], u[1][1], false, false);
+      uint4 v = make_uint4(lo[0], hi[0], lo[1], hi[1]);
+      if ((pad_bits >> j) & 1u) v = make_uint4(0, 0, 0, 0);
+      if ((wb * S::kFB + j) * 16 + r < rows) *reinterpret_cast<uint4*>(dst + (size_t)row[j] * dst_stride) = v;
+    }
   }
 }
 
-template <class S, bool kOut>
+// More than 64 KB of dynamic LDS has to be allowed explicitly, once per kernel and device (a host-side
+// setting; the call costs a microsecond).
+template <auto kKernel>
+hipError_t allow_lds(int bytes) {
+  static std::atomic<unsigned long long> done{0};  // bit = device
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const unsigned long long bit = dev < 64 ? 1ull << dev : 0;
+  if (bit && (done.load(std::memory_order_acquire) & bit)) return hipSuccess;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(kKernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+  return e;
+}
+
+template <class S, bool kHeadTok, bool kTransposedW>
 hipError_t launch_proj(ProjArgs a, int kernel_id, hipStream_t stream) {
-  constexpr int kTokRows = S::kTokTiles * 64, kFeatRows = S::kFeatTiles * 64;
-  a.tok_tiles_per_seq = (a.N + kTokRows - 1) / kTokRows;
-  a.feat_tiles = a.F / kFeatRows;
-  a.total = a.B * a.tok_tiles_per_seq * a.feat_tiles;
-  const int grid = 8 * ((a.total + 7) / 8);
-  const size_t lds_bytes = (size_t)S::kStages * S::kStageBytesP;
-  // more than 64 KB of dynamic LDS has to be allowed explicitly (a host-side setting, no state here)
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&proj_kernel<S, kOut>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+  a.tok_tiles_per_seq = (a.N + S::kRowsB - 1) / S::kRowsB;
+  a.feat_tiles = (a.F + S::kRowsA - 1) / S::kRowsA;
+  a.tile_blocks = 8 * ((a.B * a.tok_tiles_per_seq + 7) / 8) * a.feat_tiles;
+  if (a.ranges.splits) a.ranges.blocks = (int)std::max<size_t>(1, std::min<size_t>(1024 * 256 / S::kThreads, a.ranges.n / 4 / S::kThreads));
+  const hipError_t e = allow_lds<&proj_kernel<S, kHeadTok, kTransposedW>>(S::kLds);
   if (e != hipSuccess) return e;
   ProfileScope prof(kernel_id, stream);
-  hipLaunchKernelGGL((proj_kernel<S, kOut>), dim3(grid), dim3(S::kThreadsP), lds_bytes, stream, a);
+  hipLaunchKernelGGL((proj_kernel<S, kHeadTok, kTransposedW>), dim3(a.tile_blocks + a.ranges.blocks), dim3(S::kThreads),
+                     S::kLds, stream, a);
   return hipGetLastError();
 }
 
-// Two shapes.  Large: 256 tokens x 256 features, eight wavefronts of 128 x 64, two stages of
-// 64 KB (one workgroup per CU): half the operand traffic per flop of the small shape and the
-// faster of the two once its tiles fill the chip (measured on the 16384 x 3072 x 1024 product:
-// 106 us against 122 us).  Small: 128 x 128, four wavefronts of 64 x 64, two workgroups per CU:
-// for feature counts that are not a multiple of 256 and for products with few tiles.
-using LargeShape = ProjShape<4, 4, 2, 2>;
-using SmallShape = ProjShape<2, 2, 2, 2>;
-
-template <bool kOut>
-hipError_t launch_proj_any(const ProjArgs& a, int kernel_id, hipStream_t stream) {
-  const long large_tiles = (long)a.B * ((a.N + 255) / 256) * (a.F / 256);
-  if (a.F % 256 == 0 && large_tiles >= 256) return launch_proj<LargeShape, kOut>(a, kernel_id, stream);
-  return launch_proj<SmallShape, kOut>(a, kernel_id, stream);
+// Which shape.  A compute unit that gets n tiles of a shape needs about n (c k / 64 + e) us, with c and e
+// as measured below (256 CUs, 257 to 12288 tokens, widths 768 and 1024, one tile per CU as well as many),
+// so the shape with the smallest product of ceil(tiles / 256) and that wins: large tiles once they fill
+// the chip, smaller ones where they fit its 256 units better.  Measured, us, at 8 x 512 tokens and
+// 768 -> 2304 / 768 -> 768 features: 256 x 256 26 / 24, 192 x 128 21 / 15, 128 x 128 25 / 14, 128 x 64
+// 26 / 11; at 2 x 8192 (12860 not padding) and 1024 -> 3072: 92, 94, 109, 143.
+//                        features x tokens, wavefronts, stages, workgroups per CU
+using Proj256 = Shape<4, 4, 2, 4, 2, 1>;   // 256 x 256
+using Proj192 = Shape<3, 2, 2, 2, 2, 2>;   // 192 x 128  (plain weights; its wavefronts' 96 features are not whole tiles)
+using Proj128 = Shape<2, 2, 2, 2, 2, 2>;   // 128 x 128
+using Proj64 = Shape<2, 1, 2, 2, 3, 2>;    // 128 x  64
+template <class S>
+double proj_cost(const ProjArgs& a, double c, double e) {
+  const long tiles = (long)a.B * ((a.N + S::kRowsB - 1) / S::kRowsB) * ((a.F + S::kRowsA - 1) / S::kRowsA);
+  return (double)((tiles + 255) / 256) * (c * (a.K / 64) + e);
 }
 
+template <bool kHeadTok, bool kTransposedW>
+hipError_t launch_proj_any(const ProjArgs& a, int kernel_id, hipStream_t stream) {
+  const double c256 = proj_cost<Proj256>(a, 1.6, 3.0), c128 = proj_cost<Proj128>(a, 0.52, 1.0), c64 = proj_cost<Proj64>(a, 0.33, 0.6);
+  const double best = std::min({c256, c128, c64});
+  if constexpr (!kTransposedW)
+    if (a.F % Proj192::kRowsA == 0 && proj_cost<Proj192>(a, 0.75, 1.3) < best)
+      return launch_proj<Proj192, kHeadTok, kTransposedW>(a, kernel_id, stream);
+  if (c256 == best) return launch_proj<Proj256, kHeadTok, kTransposedW>(a, kernel_id, stream);
+  if (c128 == best) return launch_proj<Proj128, kHeadTok, kTransposedW>(a, kernel_id, stream);
+  return launch_proj<Proj64, kHeadTok, kTransposedW>(a, kernel_id, stream);
+}
 
 // ======================================================================================
-// Backward of the projections
+// Gradient with respect to the weights
 // ======================================================================================
-// Gradient with respect to the input of a projection (dx from dq, dk, dv; d_o from dy) is the
-// same product as the forward with the weight matrix transposed, so it runs the kernel above
-// on a transposed copy of the weights that a small preparation kernel leaves in the workspace
-// (the weights are a few MB; the copy costs microseconds).  Gradient with respect to the
-// weights contracts over TOKENS: dW[f, e] = sum_tok G[tok, f] X[tok, e].  Both operands are
-// token-major, so their 64-token x 64-column tiles go into LDS as they are and both MFMA
-// operands come from transposing reads (which permute the 16 tokens of a slice the same way
-// on both sides).  A workgroup owns 256 x 128 or 256 x 256 of dW and a range of the token blocks; partial
-// sums of the ranges are added in a fixed order by a finalize kernel (no atomics: the result is
-// bit-reproducible).  The bias gradient (column sums of G) rides along in the workgroups of
-// the first column tile.  Rows of pad tokens are cleared in LDS after a block has landed, and
-// blocks of padding only are skipped; which rows are pad comes from one 64-bit mask per block,
-// written by the preparation kernel and read through the scalar cache.
+// Both operands are token-major, so their 64-token x 64-column tiles go into LDS as they are and both
+// are read transposed.  A workgroup owns a tile of dW and a range of the token blocks; partial sums of
+// the ranges are added in a fixed order afterwards (no atomics: the result is bit-reproducible).  The bias gradient (column sums of G) rides along in the workgroups of the first
+// column tile.  Rows of pad tokens are cleared in LDS after a block has landed, and blocks of padding
+// only are skipped.
 
 // Token-major matrix whose 64-column blocks are either columns of a flat [B*N][ld] matrix or
 // heads of up to three [B][H][N][64] tensors (column block c <-> tensor c / H, head c % H).
@@ -303,16 +400,9 @@ struct TokMat {
   int heads;          // 1: head layout, 0: flat
   int ld;             // flat: elements per row
 };
-// A pointer the compiler can keep in scalar registers (the value is the same in every lane).
-__device__ inline const char* uniform_ptr(const char* p) {
-  const unsigned long long v = reinterpret_cast<unsigned long long>(p);
-  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
-  return reinterpret_cast<const char*>(((unsigned long long)hi << 32) | lo);
-}
-
 struct WgradArgs {
   TokMat g, x;                    // G [tok][F-side], X [tok][E-side]
-  const unsigned long long* pad;  // [B * blocks_per_seq]: bit r set = row r of the block is pad / past N
+  const unsigned char* flags;     // [B][N]
   float* out;                     // [F][E] (final when splits == 1)
   float* out_bias;                // [F] or null
   float* part;                    // [splits][F][E] partial sums (splits > 1)
@@ -323,29 +413,37 @@ struct WgradArgs {
   int splits, per_split;          // token-block ranges
   int want_bias;
 };
+constexpr int kMaxRange = 1024;   // token blocks of one range
 
-// Workgroup: 8 wavefronts, 256 rows x (64 KX) columns of dW, KX = 2 or 4; a wavefront owns 64 rows x
-// 32 KX columns; one block of 64 tokens per stage (four G tiles, KX X tiles).  The wide shape
-// halves the operand reads per contraction and is used when its tiles still fill the chip without
-// cutting the tokens into many ranges (each range leaves an fp32 partial matrix behind).
-constexpr int kWgRows = 256, kWgThreads = 512;
-constexpr int kMaxRange = 1024;  // token blocks of one range
-template <int KX>
-struct WgShape {
-  static constexpr int kCols = 64 * KX, kTiles = 4 + KX, kStageBytesW = kTiles * kTileBytes;
-  static constexpr int kStagesW = KX == 2 ? 3 : 2;
-  static constexpr int kQuartersW = 4 * kTiles / 8;          // 16-row loads per wavefront and stage
-  static constexpr int kLoadsW = 2 * kQuartersW;
-  static constexpr int kXF = KX;                              // 32-column X fragments per wavefront
-};
-template <int KX>
-__global__ __launch_bounds__(kWgThreads, 1) void proj_wgrad_kernel(WgradArgs a) {
-  using S = WgShape<KX>;
+// Which of the 64 tokens from position n0 of the sequence at flags[seq] on are padding (or past its end):
+// one bit each.  `total` = bytes of the flags array, which is read 64 bytes at a time.
+__device__ __forceinline__ unsigned long long pad_mask(const unsigned char* flags, size_t total, size_t seq, int n0, int N) {
+  const int n = min(64, N - n0);
+  const size_t first = seq + n0;
+  unsigned long long bits = 0;
+  if (total >= 64) {
+    const size_t at = first < total - 64 ? first : total - 64;  // the 64 bytes must lie inside the array
+    unsigned w[16];
+    __builtin_memcpy(w, flags + at, 64);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const unsigned two = w[i] & 0xfefefefeu;  // a byte of 2 or more leaves a bit here: collect it in bit 7
+      const unsigned pad = (((two & 0x7f7f7f7fu) + 0x7f7f7f7fu) | two) & 0x80808080u;
+      bits |= (unsigned long long)(((pad >> 7) * 0x10204080u) >> 28) << (4 * i);
+    }
+    bits >>= (int)(first - at);
+  } else {
+    for (int i = 0; i < n; ++i) bits |= (unsigned long long)(flags[first + i] >= 2) << i;
+  }
+  return n < 64 ? bits | ~0ull << n : bits;
+}
+
+template <class S>
+__global__ __launch_bounds__(S::kThreads, S::kWaves / 4 * S::kPerCU) void proj_wgrad_kernel(WgradArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int m = lane & 31, hl = lane >> 5;
-  const int e_tiles = a.E / S::kCols, tiles = ((a.F + kWgRows - 1) / kWgRows) * e_tiles;
+  const int e_tiles = (a.E + S::kRowsA - 1) / S::kRowsA, tiles = ((a.F + S::kRowsB - 1) / S::kRowsB) * e_tiles;
   // Workgroup -> (token range, tile): XCD q = blockIdx % 8 takes a contiguous piece of the list
   // ordered by token range first, so the workgroups that stream the same tokens share an L2
   // (dealt round-robin, every XCD would fetch all of G from memory: 8 x the traffic).
@@ -354,200 +452,216 @@ __global__ __launch_bounds__(kWgThreads, 1) void proj_wgrad_kernel(WgradArgs a) 
   if (jx >= per_xcd || idx >= total) return;
   const int split = idx / tiles, tile = idx - split * tiles;
   const int ft = tile / e_tiles, et = tile - ft * e_tiles;
-  const int f0 = ft * kWgRows, e0 = et * S::kCols;
-  const int wf = wave >> 1, we = wave & 1;           // this wavefront: rows 64 wf .., columns 32 KX we ..
+  const int f0 = ft * S::kRowsB, e0 = et * S::kRowsA;
+  const int wa = wave / S::kWB, wb = wave - wa * S::kWB;
   const int total_blocks = a.B * a.blocks_per_seq;
-  const int s_begin = split * a.per_split, s_end = min(total_blocks, s_begin + a.per_split);
+  // Up to kMaxRange token blocks: every workgroup lists all of them and takes its share of the live ones
+  // (with ranges of equal length the padding at the end of the sequences left some ranges half empty:
+  // 52 live blocks in the longest of five where 41 would do).  More: ranges of equal length.
+  const bool share = total_blocks <= kMaxRange;
+  const int s_begin = share ? 0 : split * a.per_split, s_end = share ? total_blocks : min(total_blocks, s_begin + a.per_split);
 
-  // tile i of a stage: 0..3 = G column blocks f0 / 64 + i;  4.. = X column blocks e0 / 64 + i - 4.
-  // Wavefront w loads quarter w + 8 j of the stage: 16 rows of tile (w + 8 j) / 4.
-  const LoadLane ll = make_load_lane(0, lane);
-  const char* base[S::kQuartersW];
-  unsigned row_stride[S::kQuartersW];
-  size_t seq_stride[S::kQuartersW];
-  int row16[S::kQuartersW], lds_off[S::kQuartersW];
-#pragma unroll
-  for (int j = 0; j < S::kQuartersW; ++j) {
-    const int qi = wave + 8 * j, i = qi >> 2;
-    const bool is_g = i < 4;
-    // (F is a multiple of 128, not of 256: the last row tile repeats its last column block of G
-    // and does not store the rows past F)
-    const int c = is_g ? min(f0 / 64 + i, a.F / 64 - 1) : e0 / 64 + i - 4;
-    const bool heads = is_g ? a.g.heads != 0 : a.x.heads != 0;
-    const int ld = is_g ? a.g.ld : a.x.ld;
-    const int t = c / a.H, h = c - t * a.H;
-    const unsigned short* p0 = is_g ? a.g.p[0] : a.x.p[0];
-    const unsigned short* p1 = is_g ? a.g.p[1] : a.x.p[1];
-    const unsigned short* p2 = is_g ? a.g.p[2] : a.x.p[2];
-    const unsigned short* tensor = !heads || t == 0 ? p0 : t == 1 ? p1 : p2;
-    base[j] = uniform_ptr(reinterpret_cast<const char*>(tensor + (heads ? (size_t)h * a.N * kD : (size_t)c * 64)));
-    row_stride[j] = heads ? kD * 2 : (unsigned)ld * 2;
-    seq_stride[j] = heads ? (size_t)a.H * a.N * kD * 2 : (size_t)a.N * ld * 2;
-    row16[j] = 16 * (qi & 3);
-    lds_off[j] = i * kTileBytes + row16[j] * 128;
-  }
-  auto issue_stage = [&](int s, int slot) {
-    const int b = s / a.blocks_per_seq, n0 = (s - b * a.blocks_per_seq) * 64;
-    char* st = lds + slot * S::kStageBytesW;
-#pragma unroll
-    for (int j = 0; j < S::kQuartersW; ++j) {
-      const int r0 = min(n0 + row16[j] + ll.row0, a.N - 1), r1 = min(n0 + row16[j] + ll.row0 + 8, a.N - 1);
-      const char* bp = uniform_ptr(base[j] + (size_t)b * seq_stride[j]);
-      load_to_lds_16(bp, (unsigned)r0 * row_stride[j] + ll.chunk0 * 16, st + lds_off[j]);
-      load_to_lds_16(bp, (unsigned)r1 * row_stride[j] + (ll.chunk0 ^ 2) * 16, st + lds_off[j] + 8 * 128);
-    }
-  };
-  // The range's blocks with a non-pad row, in order, and their pad masks: listed in LDS before the loop
-  // (looked up one by one inside it, every step of the loop waited for two dependent scalar loads:
-  // 3 us a step where the contractions need 0.9).
+  // ---- the blocks with a non-pad row, in order, and their pad masks, listed in LDS before the
+  // loop (looked up one by one inside it, every step waited for dependent loads: 3 us a step where the
+  // contractions need 0.9) ----
   __shared__ unsigned long long live_mask[kMaxRange];
   __shared__ unsigned short live_at[kMaxRange];
-  __shared__ int wave_live[kWgThreads / 64];
+  __shared__ int wave_live[S::kWaves];
   int n_live = 0;
-  for (int s0 = s_begin; s0 < s_end; s0 += kWgThreads) {
-    const unsigned long long mask = s0 + tid < s_end ? a.pad[s0 + tid] : ~0ull;
+  for (int s0 = s_begin; s0 < s_end; s0 += S::kThreads) {  // one block per thread, its 64 flags at once
+    const int s = s0 + tid, b = s / a.blocks_per_seq;
+    const unsigned long long mask = s < s_end ? pad_mask(a.flags, (size_t)a.B * a.N, (size_t)b * a.N, (s - b * a.blocks_per_seq) * 64, a.N) : ~0ull;
     const unsigned long long ballot = __ballot(mask != ~0ull);
     if (lane == 0) wave_live[wave] = __popcll(ballot);
     __syncthreads();
     int at = n_live + __popcll(ballot & ((1ull << lane) - 1));
 #pragma unroll
-    for (int w = 0; w < kWgThreads / 64; ++w) {
+    for (int w = 0; w < S::kWaves; ++w) {
       if (w < wave) at += wave_live[w];
       n_live += wave_live[w];
     }
     if (mask != ~0ull) {
       live_mask[at] = mask;
-      live_at[at] = (unsigned short)(s0 + tid - s_begin);
+      live_at[at] = (unsigned short)(s - s_begin);
     }
     __syncthreads();
   }
   n_live = __builtin_amdgcn_readfirstlane(n_live);
+  const int i_begin = share ? n_live * split / a.splits : 0, i_end = share ? n_live * (split + 1) / a.splits : n_live;
 
-  f32x16 acc[2][S::kXF];
+  // ---- operand streams: X tiles (columns e0 ..) then G tiles (columns f0 ..) ------------------------
+  // The bases are wave-uniform and move with the block; the lane offsets are those of a whole block, and
+  // only a sequence's last, shorter one needs others (its missing rows repeat the last).
+  const unsigned x_stride = a.x.heads ? kD * 2 : (unsigned)a.x.ld * 2, g_stride = a.g.heads ? kD * 2 : (unsigned)a.g.ld * 2;
+  const size_t x_seq = a.x.heads ? (size_t)a.H * a.N * kD * 2 : (size_t)a.N * x_stride;
+  const size_t g_seq = a.g.heads ? (size_t)a.H * a.N * kD * 2 : (size_t)a.N * g_stride;
+  const char* base[S::kLoads];
+  unsigned off[S::kLoads];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < S::kXF; ++j) acc[i][j] = zero16();
-  float bias_acc[2] = {0.f, 0.f};
-  const bool do_bias = a.want_bias && et == 0 && we == 0;
-
-  int toff[2][2];
-#pragma unroll
-  for (int db = 0; db < 2; ++db) {
-    toff[db][0] = tr_off(lane, db, 0);
-    toff[db][1] = tr_off(lane, db, 1);
+  for (int i = 0; i < S::kLoads; ++i) {
+    const bool is_x = i < S::kLoadsA;
+    const LoadUnit l = load_unit<S::kWaves>(wave, lane, is_x ? i : i - S::kLoadsA);
+    const TokMat& mat = is_x ? a.x : a.g;
+    // (column blocks past the last one repeat it and are not stored)
+    const int c = is_x ? min(e0 / 64 + l.tile, a.E / 64 - 1) : min(f0 / 64 + l.tile, a.F / 64 - 1);
+    const int t = c / a.H, h = c - t * a.H;
+    const unsigned short* tensor = !mat.heads || t == 0 ? mat.p[0] : t == 1 ? mat.p[1] : mat.p[2];
+    base[i] = uniform_ptr(tensor + (mat.heads ? (size_t)h * a.N * kD : (size_t)c * 64));
+    off[i] = (unsigned)l.row * (is_x ? x_stride : g_stride) + l.chunk * 16;
   }
+  auto issue_stage = [&](int s, int slot) {
+    const int b = s / a.blocks_per_seq, n0 = (s - b * a.blocks_per_seq) * 64;
+    char* st = lds + slot * S::kStageBytes;
+    const size_t x_at = (size_t)b * x_seq + (size_t)n0 * x_stride, g_at = (size_t)b * g_seq + (size_t)n0 * g_stride;
+    const int missing = max(0, n0 + 64 - a.N);
+#pragma unroll
+    for (int i = 0; i < S::kLoads; ++i) {
+      const bool is_x = i < S::kLoadsA;
+      unsigned o = off[i];
+      if (missing) {
+        const int row = load_unit<S::kWaves>(wave, lane, is_x ? i : i - S::kLoadsA).row;
+        o -= (unsigned)max(0, row - (63 - missing)) * (is_x ? x_stride : g_stride);
+      }
+      load_to_lds_16(uniform_ptr(base[i] + (is_x ? x_at : g_at)), o,
+                     st + (is_x ? load_dst<S::kWaves>(wave, i) : S::kA * kTileBytes + load_dst<S::kWaves>(wave, i - S::kLoadsA)));
+    }
+  };
+
+  f32x4 acc[S::kFA][S::kFB];
+#pragma unroll
+  for (int i = 0; i < S::kFA; ++i)
+#pragma unroll
+    for (int j = 0; j < S::kFB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float bias_acc[S::kFB];
+#pragma unroll
+  for (int j = 0; j < S::kFB; ++j) bias_acc[j] = 0.f;
+  const bool do_bias = a.want_bias && et == 0 && wa == 0;
+  FragOffsets fo;
+  frag_offsets<true>(fo, lane);
 
   auto block_at = [&](int i) { return s_begin + __builtin_amdgcn_readfirstlane((int)live_at[i]); };
 #pragma unroll
-  for (int k = 0; k + 1 < S::kStagesW; ++k)
-    if (k < n_live) issue_stage(block_at(k), k);
-  for (int it = 0; it < n_live; ++it) {
-    const unsigned long long padmask = live_mask[it];
-    const int ahead = it + S::kStagesW - 1;
-    const int next = block_at(min(ahead, n_live - 1));
-    // block `it` has landed: everything but the loads of the blocks after it that were issued
-    wait_vmcnt_le<S::kLoadsW * (S::kStagesW - 2)>(min(S::kStagesW - 2, n_live - 1 - it) * S::kLoadsW);
+  for (int k = 0; k + 1 < S::kStages; ++k)
+    if (i_begin + k < i_end) issue_stage(block_at(i_begin + k), k);
+  for (int i = i_begin, it = 0; i < i_end; ++i, ++it) {
+    const unsigned long long padmask = live_mask[i];
+    const int next = block_at(min(i + S::kStages - 1, i_end - 1));
+    // block i has landed: everything but the loads of the blocks after it that were issued
+    wait_vmcnt_le<S::kLoads * (S::kStages - 2)>(min(S::kStages - 2, i_end - 1 - i) * S::kLoads);
     barrier_no_fence();          // ... for everyone; and everyone is done with the block before it
-    if (ahead < n_live) issue_stage(next, ahead % S::kStagesW);
-    char* st = lds + (it % S::kStagesW) * S::kStageBytesW;
+    if (i + S::kStages - 1 < i_end) issue_stage(next, (it + S::kStages - 1) % S::kStages);
+    char* st = lds + (it % S::kStages) * S::kStageBytes;
     if (padmask) {               // the same for every lane: clear the pad rows of all tiles (0 x anything = 0 then)
-      const int row = tid & 63, which = tid >> 6;
-      if (which < S::kTiles && ((padmask >> row) & 1ull)) {
-        uint4* p = reinterpret_cast<uint4*>(st + which * kTileBytes + row * 128);
+      for (int i = tid; i < 64 * (S::kA + S::kB); i += S::kThreads)
+        if ((padmask >> (i & 63)) & 1ull) {
+          uint4* p = reinterpret_cast<uint4*>(st + (i >> 6) * kTileBytes + (i & 63) * 128);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) p[c] = make_uint4(0, 0, 0, 0);
-      }
+          for (int c = 0; c < 8; ++c) p[c] = make_uint4(0, 0, 0, 0);
+        }
       __syncthreads();
     }
-    const char* g_t = st + wf * kTileBytes;
-    const char* x_t = st + (4 + we * (KX / 2)) * kTileBytes;
-    // operand fragments are read one 16-token slice ahead of the contractions that use them
-    bf16x8 gf[2][2], xf[2][S::kXF];
-    auto read_slice = [&](int buf, int k16) {
-#pragma unroll
-      for (int db = 0; db < 2; ++db) gf[buf][db] = read_transposed(g_t + 16 * k16 * 128, toff[db][0], toff[db][1]);
-#pragma unroll
-      for (int j = 0; j < S::kXF; ++j)
-        xf[buf][j] = read_transposed(x_t + (j >> 1) * kTileBytes + 16 * k16 * 128, toff[j & 1][0], toff[j & 1][1]);
-    };
-    read_slice(0, 0);
-#pragma unroll
-    for (int k16 = 0; k16 < 4; ++k16) {
-      if (k16 + 1 < 4) read_slice((k16 + 1) & 1, k16 + 1);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < S::kXF; ++j) acc[i][j] = mfma(gf[k16 & 1][i], xf[k16 & 1][j], acc[i][j]);
+    contract_stage<S, true, true>(st, fo, fo, wa, wb, acc, [&](const bf16x8 (&g)[S::kFB]) {
       if (do_bias) {
-        bias_acc[0] = sum8(gf[k16 & 1][0], bias_acc[0]);
-        bias_acc[1] = sum8(gf[k16 & 1][1], bias_acc[1]);
+#pragma unroll
+        for (int j = 0; j < S::kFB; ++j) bias_acc[j] = sum8(g[j], bias_acc[j]);
       }
-    }
+    });
   }
 
-  // C tile: lane (m, hl) holds column m, register 4 g + r holds row 8 g + 4 hl + r
+  // a lane holds columns 16 i + 4 quarter .. + 3 of row 16 j + r
+  const int r = lane & 15, quarter = lane >> 4;
   float* dst = (a.splits > 1 ? a.part + (size_t)split * a.F * a.E : a.out);
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int j = 0; j < S::kFB; ++j) {
+    const int f = f0 + (wb * S::kFB + j) * 16 + r;
 #pragma unroll
-    for (int j = 0; j < S::kXF; ++j)
-#pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        const int row = f0 + 64 * wf + 32 * i + 8 * (c >> 2) + 4 * hl + (c & 3);
-        if (row < a.F) dst[(size_t)row * a.E + e0 + 32 * KX * we + 32 * j + m] = acc[i][j][c];
-      }
+    for (int i = 0; i < S::kFA; ++i) {
+      const int e = e0 + (wa * S::kFA + i) * 16 + 4 * quarter;
+      if (f < a.F && e < a.E) *reinterpret_cast<f32x4*>(dst + (size_t)f * a.E + e) = acc[i][j];
+    }
+  }
   if (do_bias) {
     float* bd = a.splits > 1 ? a.part_bias + (size_t)split * a.F : a.out_bias;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const float v = half_sum(bias_acc[i]);
-      if (hl == 0 && f0 + 64 * wf + 32 * i + m < a.F) bd[f0 + 64 * wf + 32 * i + m] = v;
+    for (int j = 0; j < S::kFB; ++j) {
+      float v = bias_acc[j];
+      v += __shfl_xor(v, 16, 64);
+      v += __shfl_xor(v, 32, 64);
+      const int f = f0 + (wb * S::kFB + j) * 16 + r;
+      if (quarter == 0 && f < a.F) bd[f] = v;
     }
   }
 }
 
-// Adds the partial sums of the token-block ranges in range order.
-__global__ __launch_bounds__(256) void proj_wgrad_finalize_kernel(WgradArgs a) {
-  const size_t n4 = (size_t)a.F * a.E / 4;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 256) {
-    float4 s = reinterpret_cast<const float4*>(a.part)[i];
-    for (int k = 1; k < a.splits; ++k) {
-      const float4 v = reinterpret_cast<const float4*>(a.part + (size_t)k * a.F * a.E)[i];
-      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+// For a weight gradient that no product follows.
+__global__ __launch_bounds__(256) void add_ranges_kernel(RangeSums s) { add_ranges(s, blockIdx.x, 256); }
+
+//                         columns x rows of dW
+using Wgrad256 = Shape<4, 4, 2, 4, 2, 1>;   // 256 x 256
+using Wgrad128 = Shape<2, 2, 2, 2, 2, 2>;   // 128 x 128
+
+size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
+struct WgradPlan {
+  int blocks_per_seq, splits, per_split, tile;
+  size_t bias_off, total;
+};
+// F x E = shape of the weight gradient.
+WgradPlan plan_wgrad(int B, int N, int F, int E) {
+  WgradPlan p;
+  p.blocks_per_seq = (N + 63) / 64;
+  const int total_blocks = B * p.blocks_per_seq;
+  // Large tiles read half as much per contraction, small ones need fewer token ranges to fill the chip, and
+  // every range leaves an fp32 partial matrix that is written and read again.  In us, as measured on 768
+  // and 1024 wide layers of 257 to 16384 tokens: 1.9 a token block for 256 x 256 (one workgroup per CU),
+  // 1.2 for 128 x 128 (two), 1 per 5.2 MB of partial sums.  (3072 x 1024 at 4096 tokens: 52 against 54,
+  // at 12288 90 against 125, at 1024 39 against 31.)
+  double best = 0;
+  for (int tile : {256, 128}) {
+    const int slots = tile == 256 ? 256 : 512, tiles = ((F + tile - 1) / tile) * ((E + tile - 1) / tile);
+    // enough workgroups for the chip, but ranges of at least eight token blocks
+    const int want = std::max({1, std::min(std::max(1, slots / tiles), total_blocks / 8), (total_blocks + kMaxRange - 1) / kMaxRange});
+    const int per = (total_blocks + want - 1) / want, splits = (total_blocks + per - 1) / per;
+    const double rounds = (double)((tiles * splits + slots - 1) / slots);
+    const double cost = rounds * per * (tile == 256 ? 1.9 : 1.2) + (splits > 1 ? splits * 8.0 * F * E / 5.2e6 : 0.0);
+    if (tile == 256 || cost < best) {
+      best = cost;
+      p.tile = tile;
+      p.per_split = per;
+      p.splits = splits;
     }
-    reinterpret_cast<float4*>(a.out)[i] = s;
   }
-  if (a.want_bias)
-    for (int f = blockIdx.x * 256 + threadIdx.x; f < a.F; f += gridDim.x * 256) {
-      float s = a.part_bias[f];
-      for (int k = 1; k < a.splits; ++k) s += a.part_bias[(size_t)k * a.F + f];
-      a.out_bias[f] = s;
-    }
+  p.bias_off = p.splits > 1 ? align256((size_t)p.splits * F * E * 4) : 0;
+  p.total = p.bias_off + (p.splits > 1 ? align256((size_t)p.splits * F * 4) : 0) + 256;
+  return p;
 }
 
-// Preparation: blocks [0, R / 64 * C / 64) transpose the bf16 matrix w [R][C] into wt [C][R]
-// (skipped when wt is null); the blocks after them write the pad masks of the token blocks.
-__global__ __launch_bounds__(256) void proj_bwd_prep_kernel(const unsigned short* __restrict__ w,
-                                                            unsigned short* __restrict__ wt, int R, int C,
-                                                            const unsigned char* __restrict__ flags, int B,
-                                                            int N, unsigned long long* __restrict__ pad) {
-  __shared__ unsigned short t[64][66];
-  const int n_tr = wt ? (R / 64) * (C / 64) : 0;
-  if ((int)blockIdx.x < n_tr) {
-    const int r0 = (blockIdx.x / (C / 64)) * 64, c0 = (blockIdx.x % (C / 64)) * 64;
-    for (int i = threadIdx.x; i < 64 * 64; i += 256) t[i >> 6][i & 63] = w[(size_t)(r0 + (i >> 6)) * C + c0 + (i & 63)];
-    __syncthreads();
-    for (int i = threadIdx.x; i < 64 * 64; i += 256) wt[(size_t)(c0 + (i >> 6)) * R + r0 + (i & 63)] = t[i & 63][i >> 6];
-    return;
-  }
-  const int bps = (N + 63) / 64, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int s = ((int)blockIdx.x - n_tr) * 4 + wave; s < B * bps; s += ((int)gridDim.x - n_tr) * 4) {
-    const int b = s / bps, n = (s - b * bps) * 64 + lane;
-    const bool is_pad = n >= N || flags[(size_t)b * N + n] >= 2;
-    const unsigned long long mask = __ballot(is_pad);
-    if (lane == 0) pad[s] = mask;
-  }
+template <class S>
+hipError_t launch_wgrad(const WgradArgs& a, int kernel_id, hipStream_t stream) {
+  const int tiles = ((a.F + S::kRowsB - 1) / S::kRowsB) * ((a.E + S::kRowsA - 1) / S::kRowsA);
+  const hipError_t e = allow_lds<&proj_wgrad_kernel<S>>(S::kLds);
+  if (e != hipSuccess) return e;
+  ProfileScope prof(kernel_id, stream);
+  hipLaunchKernelGGL(proj_wgrad_kernel<S>, dim3(8 * ((tiles * a.splits + 7) / 8)), dim3(S::kThreads), S::kLds, stream, a);
+  return hipGetLastError();
+}
+
+// Leaves in `sums` what is still to be added up.
+hipError_t run_wgrad(WgradArgs a, char* ws, int kernel_id, RangeSums& sums, hipStream_t stream) {
+  const WgradPlan p = plan_wgrad(a.B, a.N, a.F, a.E);
+  a.blocks_per_seq = p.blocks_per_seq;
+  a.splits = p.splits;
+  a.per_split = p.per_split;
+  a.part = reinterpret_cast<float*>(ws);
+  a.part_bias = reinterpret_cast<float*>(ws + p.bias_off);
+  sums = {};
+  if (p.splits > 1) sums = {a.part, a.part_bias, a.out, a.out_bias, (size_t)a.F * a.E, a.F, p.splits, 0};
+  return p.tile == 256 ? launch_wgrad<Wgrad256>(a, kernel_id, stream) : launch_wgrad<Wgrad128>(a, kernel_id, stream);
+}
+hipError_t add_ranges_alone(RangeSums s, hipStream_t stream) {
+  if (!s.splits) return hipSuccess;
+  s.blocks = (int)std::max<size_t>(1, std::min<size_t>(1024, s.n / 4 / 256));
+  hipLaunchKernelGGL(add_ranges_kernel, dim3(s.blocks), dim3(256), 0, stream, s);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -563,10 +677,10 @@ hipError_t launch_qkv_project(const void* x, const void* w_qkv, const float* bia
   a.out[0] = static_cast<unsigned short*>(q);
   a.out[1] = static_cast<unsigned short*>(k);
   a.out[2] = static_cast<unsigned short*>(v);
-  a.B = B; a.N = N; a.H = H; a.E = E;
+  a.B = B; a.N = N; a.H = H;
   a.F = 3 * H * kD;
   a.K = E;
-  return launch_proj_any<false>(a, 8, stream);
+  return launch_proj_any<false, false>(a, 8, stream);
 }
 
 hipError_t launch_out_project(const void* o, const void* w_o, const float* bias,
@@ -578,110 +692,21 @@ hipError_t launch_out_project(const void* o, const void* w_o, const float* bias,
   a.bias = bias;
   a.flags = flags;
   a.out[0] = static_cast<unsigned short*>(y);
-  a.B = B; a.N = N; a.H = H; a.E = E;
+  a.B = B; a.N = N; a.H = H;
   a.F = E;
   a.K = H * kD;
-  return launch_proj_any<true>(a, 9, stream);
+  return launch_proj_any<true, false>(a, 9, stream);
 }
 
-}  // namespace mate
-
-namespace mate {
-
-namespace {
-size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
-struct BwdPlan {
-  int blocks_per_seq, splits, per_split, kx;
-  size_t wt_off, pad_off, part_off, bias_off, total;
-};
-// F x E = shape of the weight gradient; `wt_elems` = elements of the transposed weight copy.
-BwdPlan plan_bwd(int B, int N, int F, int E, size_t wt_elems) {
-  BwdPlan p;
-  p.blocks_per_seq = (N + 63) / 64;
-  const int total_blocks = B * p.blocks_per_seq;
-  // Token ranges: enough workgroups for the chip (one per CU), but ranges of at least eight token
-  // blocks -- every range leaves an fp32 partial matrix that is written and read again.  The wide
-  // tile is taken when it fills the chip with at most sixteen ranges.
-  auto ranges = [&](int kx) {
-    const int tiles = ((F + kWgRows - 1) / kWgRows) * (E / (64 * kx));
-    return std::max({1, std::min(std::max(1, 256 / tiles), total_blocks / 8), (total_blocks + kMaxRange - 1) / kMaxRange});
-  };
-  p.kx = (E % 256 == 0 && ((F + kWgRows - 1) / kWgRows) * (E / 256) * ranges(4) >= 192 && ranges(4) <= 16) ? 4 : 2;
-  const int want = ranges(p.kx);
-  p.per_split = (total_blocks + want - 1) / want;
-  p.splits = (total_blocks + p.per_split - 1) / p.per_split;
-  p.wt_off = 0;
-  p.pad_off = align256(wt_elems * 2);
-  p.part_off = p.pad_off + align256((size_t)total_blocks * 8);
-  p.bias_off = p.part_off + (p.splits > 1 ? align256((size_t)p.splits * F * E * 4) : 0);
-  p.total = p.bias_off + (p.splits > 1 ? align256((size_t)p.splits * F * 4) : 0);
-  return p;
-}
-
-template <int KX>
-hipError_t launch_wgrad(const WgradArgs& a, int splits, int kernel_id, hipStream_t stream) {
-  using S = WgShape<KX>;
-  const int tiles = ((a.F + kWgRows - 1) / kWgRows) * (a.E / S::kCols);
-  const size_t lds_bytes = (size_t)S::kStagesW * S::kStageBytesW;
-  hipError_t e0 = hipFuncSetAttribute(reinterpret_cast<const void*>(&proj_wgrad_kernel<KX>),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-  if (e0 != hipSuccess) return e0;
-  ProfileScope prof(kernel_id, stream);
-  hipLaunchKernelGGL(proj_wgrad_kernel<KX>, dim3(8 * ((tiles * splits + 7) / 8)), dim3(kWgThreads), lds_bytes,
-                     stream, a);
-  return hipGetLastError();
-}
-
-hipError_t run_wgrad(WgradArgs a, const BwdPlan& p, char* ws, int kernel_id, hipStream_t stream) {
-  a.blocks_per_seq = p.blocks_per_seq;
-  a.splits = p.splits;
-  a.per_split = p.per_split;
-  a.pad = reinterpret_cast<const unsigned long long*>(ws + p.pad_off);
-  a.part = reinterpret_cast<float*>(ws + p.part_off);
-  a.part_bias = reinterpret_cast<float*>(ws + p.bias_off);
-  hipError_t e = p.kx == 4 ? launch_wgrad<4>(a, p.splits, kernel_id, stream)
-                           : launch_wgrad<2>(a, p.splits, kernel_id, stream);
-  if (e != hipSuccess || p.splits == 1) return e;
-  hipLaunchKernelGGL(proj_wgrad_finalize_kernel, dim3(1024), dim3(256), 0, stream, a);
-  return hipGetLastError();
-}
-}  // namespace
-
-size_t qkv_project_bwd_workspace(int B, int N, int H, int E) {
-  return plan_bwd(B, N, 3 * H * kD, E, (size_t)3 * H * kD * E).total;
-}
-size_t out_project_bwd_workspace(int B, int N, int H, int E) {
-  return plan_bwd(B, N, E, H * kD, (size_t)E * H * kD).total;
-}
+size_t qkv_project_bwd_workspace(int B, int N, int H, int E) { return plan_wgrad(B, N, 3 * H * kD, E).total; }
+size_t out_project_bwd_workspace(int B, int N, int H, int E) { return plan_wgrad(B, N, E, H * kD).total; }
 
 hipError_t launch_qkv_project_bwd(const void* x, const void* w_qkv, const unsigned char* flags,
                                   const void* dq, const void* dk, const void* dv, int B, int N, int H,
                                   int E, void* dx, float* dw, float* dbias, void* workspace,
                                   hipStream_t stream) {
   const int F = 3 * H * kD;
-  const BwdPlan p = plan_bwd(B, N, F, E, (size_t)F * E);
-  char* ws = static_cast<char*>(workspace);
-  unsigned short* wt = reinterpret_cast<unsigned short*>(ws + p.wt_off);
-  const int n_tr = dx ? (F / 64) * (E / 64) : 0;
-  hipLaunchKernelGGL(proj_bwd_prep_kernel, dim3(n_tr + 64), dim3(256), 0, stream,
-                     static_cast<const unsigned short*>(w_qkv), dx ? wt : nullptr, F, E, flags, B, N,
-                     reinterpret_cast<unsigned long long*>(ws + p.pad_off));
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (dx) {  // dx[tok, :] = sum over the 3 H heads of dq, dk, dv [tok, head] . w_qkv[head rows, :]
-    ProjArgs a = {};
-    a.w = wt;                       // [E][F]
-    a.tok3[0] = static_cast<const unsigned short*>(dq);
-    a.tok3[1] = static_cast<const unsigned short*>(dk);
-    a.tok3[2] = static_cast<const unsigned short*>(dv);
-    a.flags = flags;
-    a.out[0] = static_cast<unsigned short*>(dx);
-    a.B = B; a.N = N; a.H = H; a.E = E;
-    a.F = E;
-    a.K = F;
-    e = launch_proj_any<true>(a, 10, stream);
-    if (e != hipSuccess) return e;
-  }
+  RangeSums sums = {};
   if (dw) {
     WgradArgs g = {};
     g.g.p[0] = static_cast<const unsigned short*>(dq);
@@ -691,40 +716,35 @@ hipError_t launch_qkv_project_bwd(const void* x, const void* w_qkv, const unsign
     g.x.p[0] = static_cast<const unsigned short*>(x);
     g.x.heads = 0;
     g.x.ld = E;
+    g.flags = flags;
     g.out = dw;
     g.out_bias = dbias;
     g.want_bias = dbias != nullptr;
     g.B = B; g.N = N; g.H = H; g.F = F; g.E = E;
-    e = run_wgrad(g, p, ws, 11, stream);
+    const hipError_t e = run_wgrad(g, static_cast<char*>(workspace), 11, sums, stream);
+    if (e != hipSuccess) return e;
   }
-  return e;
+  if (!dx) return add_ranges_alone(sums, stream);
+  // dx[tok, :] = sum over the 3 H heads of dq, dk, dv [tok, head] . w_qkv[head rows, :]
+  ProjArgs a = {};
+  a.w = static_cast<const unsigned short*>(w_qkv);  // [F][E], contracted over its rows
+  a.tok3[0] = static_cast<const unsigned short*>(dq);
+  a.tok3[1] = static_cast<const unsigned short*>(dk);
+  a.tok3[2] = static_cast<const unsigned short*>(dv);
+  a.flags = flags;
+  a.out[0] = static_cast<unsigned short*>(dx);
+  a.B = B; a.N = N; a.H = H;
+  a.F = E;
+  a.K = F;
+  a.ranges = sums;
+  return launch_proj_any<true, true>(a, 10, stream);
 }
 
 hipError_t launch_out_project_bwd(const void* o, const void* w_o, const unsigned char* flags,
                                   const void* dy, int B, int N, int H, int E, void* d_o, float* dw,
                                   float* dbias, void* workspace, hipStream_t stream) {
   const int J = H * kD;
-  const BwdPlan p = plan_bwd(B, N, E, J, (size_t)E * J);
-  char* ws = static_cast<char*>(workspace);
-  unsigned short* wt = reinterpret_cast<unsigned short*>(ws + p.wt_off);
-  const int n_tr = d_o ? (E / 64) * (J / 64) : 0;
-  hipLaunchKernelGGL(proj_bwd_prep_kernel, dim3(n_tr + 64), dim3(256), 0, stream,
-                     static_cast<const unsigned short*>(w_o), d_o ? wt : nullptr, E, J, flags, B, N,
-                     reinterpret_cast<unsigned long long*>(ws + p.pad_off));
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (d_o) {  // d_o[tok, head i] = dy[tok, :] . w_o[:, head i columns], written head by head
-    ProjArgs a = {};
-    a.w = wt;                       // [H*64][E]
-    a.tok = static_cast<const unsigned short*>(dy);
-    a.flags = flags;
-    a.out[0] = static_cast<unsigned short*>(d_o);
-    a.B = B; a.N = N; a.H = H; a.E = E;
-    a.F = J;
-    a.K = E;
-    e = launch_proj_any<false>(a, 12, stream);
-    if (e != hipSuccess) return e;
-  }
+  RangeSums sums = {};
   if (dw) {
     WgradArgs g = {};
     g.g.p[0] = static_cast<const unsigned short*>(dy);
@@ -732,13 +752,26 @@ hipError_t launch_out_project_bwd(const void* o, const void* w_o, const unsigned
     g.g.ld = E;
     g.x.p[0] = static_cast<const unsigned short*>(o);
     g.x.heads = 1;
+    g.flags = flags;
     g.out = dw;
     g.out_bias = dbias;
     g.want_bias = dbias != nullptr;
     g.B = B; g.N = N; g.H = H; g.F = E; g.E = J;
-    e = run_wgrad(g, p, ws, 13, stream);
+    const hipError_t e = run_wgrad(g, static_cast<char*>(workspace), 13, sums, stream);
+    if (e != hipSuccess) return e;
   }
-  return e;
+  if (!d_o) return add_ranges_alone(sums, stream);
+  // d_o[tok, head i] = dy[tok, :] . w_o[:, head i columns], written head by head
+  ProjArgs a = {};
+  a.w = static_cast<const unsigned short*>(w_o);  // [E][H*64], contracted over its rows
+  a.tok = static_cast<const unsigned short*>(dy);
+  a.flags = flags;
+  a.out[0] = static_cast<unsigned short*>(d_o);
+  a.B = B; a.N = N; a.H = H;
+  a.F = J;
+  a.K = E;
+  a.ranges = sums;
+  return launch_proj_any<false, true>(a, 12, stream);
 }
 
 }  // namespace mate

@@ -255,3 +255,12 @@ def test_unsupported_arguments():
     with pytest.raises(mate.MateError) as e:        # width not a multiple of 128
         mate.out_project(dev(o), dev(w_o), None, torch.from_numpy(flags).cuda())
     assert e.value.status == mate.MATE_ERR_UNSUPPORTED
+
+
+# every workgroup shape of the products, with a last feature tile that is not whole (1152 = 4.5 x 256 = 6 x
+# 192) and token counts beside multiples of the token tiles; both tile sizes of the weight gradient; more
+# token blocks than one list of them holds
+@pytest.mark.parametrize("B,N,H,E", [(1, 65, 2, 128), (2, 1025, 6, 384), (1, 12001, 2, 1152), (5, 16384, 2, 128)])
+def test_workgroup_shapes(B, N, H, E):
+    check(N, B, N, H, E, pad_tail=N // 3)
+    check_bwd(N, B, N, H, E, pad_tail=N // 3)
