@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+
 #include "seg_layout.h"
 
 namespace mate {
@@ -62,6 +64,21 @@ struct ProfileScope {
     }
   }
 };
+
+// More than 64 KB of dynamic LDS has to be allowed explicitly, once per kernel and device (a host-side
+// setting; the call costs a microsecond).
+template <auto kKernel>
+hipError_t allow_lds(int bytes) {
+  static std::atomic<unsigned long long> done{0};  // bit = device
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const unsigned long long bit = dev < 64 ? 1ull << dev : 0;
+  if (bit && (done.load(std::memory_order_acquire) & bit)) return hipSuccess;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(kKernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+  return e;
+}
 
 // max_global >= N and radius = 0: the pattern of Section 3; otherwise the bucketed approximation
 // of Section 3.1 (global part of at most max_global tokens, windows of three buckets of radius).

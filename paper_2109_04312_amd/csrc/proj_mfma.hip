@@ -24,7 +24,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 
 #include "d2l.h"
 #include "launch.h"
@@ -324,21 +323,6 @@ __global__ __launch_bounds__(S::kThreads, S::kWaves / 4 * S::kPerCU) void proj_k
       if ((wb * S::kFB + j) * 16 + r < rows) *reinterpret_cast<uint4*>(dst + (size_t)row[j] * dst_stride) = v;
     }
   }
-}
-
-// More than 64 KB of dynamic LDS has to be allowed explicitly, once per kernel and device (a host-side
-// setting; the call costs a microsecond).
-template <auto kKernel>
-hipError_t allow_lds(int bytes) {
-  static std::atomic<unsigned long long> done{0};  // bit = device
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  const unsigned long long bit = dev < 64 ? 1ull << dev : 0;
-  if (bit && (done.load(std::memory_order_acquire) & bit)) return hipSuccess;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(kKernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
-  return e;
 }
 
 template <class S, bool kHeadTok, bool kTransposedW>

@@ -83,3 +83,9 @@ def test_dense_rejects_what_it_does_not_support():
     assert st == mate.MATE_ERR_UNSUPPORTED               # too long for the dense variant
     torch.cuda.synchronize()
     assert bool((out == 7).all()) and bool((lse == 7).all())
+
+
+@pytest.mark.parametrize("N", [1, 2, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 160, 161, 255, 256, 257])
+def test_dense_edges_of_the_one_launch_backward(N):
+    """Lengths at the edges of its 32-row blocks, its workgroup sizes (64, 128, 256) and its range."""
+    check_dense(small_workload(N, "bf16", N=N, max_rows=9, max_cols=5, max_global=9, scatter=N % 2 == 1))
