@@ -3,8 +3,7 @@
 // plus run boundaries.  Integer work only.  1024-thread workgroups; all sorting lives in LDS.
 //
 // Two ways, chosen on the device from the ids themselves:
-//   * sequences of more than 1024 positions whose ids are all below 512 (every row and column
-//     number of a real table): the order is a counting
+//   * ids all below 512 (every row and column number of a real table): the order is a counting
 //     sort, slot(p) = first slot of id_p + number of earlier table tokens with the same id, and
 //     everything else (segments, windows, work units) follows from the histogram of ids.  Up to
 //     eight workgroups share a (sequence, view): each reads the whole sequence (a few KB),
@@ -12,8 +11,7 @@
 //     ranks and writes only its chunk; one more workgroup has no chunk and lists the work units
 //     instead (the longest single piece of work after the histogram).  Nothing is exchanged
 //     between workgroups.
-//   * otherwise (short sequences, where one workgroup is as fast; large ids): workgroup 0 of the
-//     (sequence, view) sorts alone, as described next.
+//   * otherwise workgroup 0 of the (sequence, view) sorts alone, as described next.
 //
 // Sort: table-token positions are first compacted in ascending order, then reordered by a
 // least-significant-digit radix sort on their id, 9 bits per pass.  Each pass is stable (every
@@ -26,6 +24,13 @@
 // segment, listed longest streamed side first) with the window of sorted slots their segments
 // span, then the pad tiles, and per sequence the chunks of the question-token owners.  The
 // attention kernels map a workgroup index to one of these records with arithmetic alone.
+//
+// What bounds it: latency, not traffic -- load, classify, scan, rank, store, with a workgroup barrier
+// between each.  So the counters are cleared while the inputs travel, prefix sums are DPP moves
+// (six dependent shuffles were 2 us of the kernel), ids and segments are counted in one scan, and the
+// classification, which the instruction issue bounds, takes four elements per lane.  Measured before and
+// after, one launch: 512 positions 10.1 -> 6.8 us, one sequence of 1999 9.3 -> 6.3 us, 128 positions
+// 8.6 -> 5.6 us, 8192 15.7 -> 12.0 us.
 //
 // Bucketed mode (the approximation of Section 3.1: a global part of at most G tokens, the rest
 // of the head's order in buckets of R, a bucket meeting itself and its two neighbours): the
@@ -53,28 +58,47 @@ __device__ inline void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// Inclusive prefix sums with DPP moves (a shuffle is a round trip through the LDS unit): over each row of
+// sixteen lanes, and over the wavefront.
+__device__ inline int row_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111 /* row_shr:1 */, 0xf, 0xf, false);  // lanes without a source add 0
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  return v;
+}
+__device__ inline int wave_scan(int v) {
+  v = row_scan(v);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142 /* row_bcast:15 */, 0xa, 0xf, false);  // into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143 /* row_bcast:31 */, 0xc, 0xf, false);  // into rows 2 and 3
+  return v;
+}
+// Bitwise or over the wavefront, in every lane.
+__device__ inline int wave_or(int v) {
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return __builtin_amdgcn_readlane(v, 63);
+}
+// Sum of table[0 .. kSegWaves) before this wavefront's entry, and of all of it: one LDS read.
+__device__ inline int waves_before(const int* table, int wave, int& total) {
+  static_assert(kSegWaves == 16, "one DPP row holds the table");
+  const int inc = row_scan(table[threadIdx.x & (kSegWaves - 1)]);
+  total = __builtin_amdgcn_readlane(inc, kSegWaves - 1);
+  return wave ? __builtin_amdgcn_readlane(inc, wave - 1) : 0;
+}
+
 // Exclusive prefix sum of one int per thread across the workgroup; `total` gets the sum.
-// `tmp` is kSegWaves + 1 ints of LDS.  Ends with a barrier so `tmp` can be reused at once.
+// `tmp` is kSegWaves ints of LDS that no wavefront still reads; it may be written again after the next barrier.
 __device__ inline int block_exclusive_scan(int v, int* tmp, int& total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int inc = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    int up = __shfl_up(inc, d, 64);
-    if (lane >= d) inc += up;
-  }
-  if (lane == 63) tmp[wave] = inc;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int inc = wave_scan(v);
+  if ((threadIdx.x & 63) == 63) tmp[wave] = inc;
   lds_barrier();
-  int base = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < kSegWaves; ++w) {
-    int s = tmp[w];
-    if (w < wave) base += s;
-    tot += s;
-  }
-  lds_barrier();
-  total = tot;
-  return base + inc - v;
+  return waves_before(tmp, wave, total) + inc - v;
 }
 
 // Number of set bits of `mask` that belong to lanes before this one (v_mbcnt).
@@ -82,28 +106,13 @@ __device__ inline int lanes_before(unsigned long long mask) {
   return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
 }
 
-// Exclusive prefix count of one flag per thread across the workgroup (ballots instead of a
-// shuffle chain); `total` gets the number of set flags.  Same contract as block_exclusive_scan.
+// Exclusive prefix count of one flag per thread; same contract.
 __device__ inline int block_flag_scan(bool flag, int* tmp, int& total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const unsigned long long m = __ballot(flag);
-  if (lane == 0) tmp[wave] = __popcll(m);
+  if ((threadIdx.x & 63) == 0) tmp[wave] = __popcll(m);
   lds_barrier();
-  int base = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < kSegWaves; ++w) {
-    const int c = tmp[w];
-    if (w < wave) base += c;
-    tot += c;
-  }
-  lds_barrier();
-  total = tot;
-  return base + lanes_before(m);
-}
-
-// The value of the previous lane (lane 0 keeps its own): a DPP move, no LDS round trip.
-__device__ inline int from_previous_lane(int v) {
-  return __builtin_amdgcn_update_dpp(v, v, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
+  return waves_before(tmp, wave, total) + lanes_before(m);
 }
 
 // Lanes of the wavefront that hold the same digit as this lane (valid lanes only).  Only the
@@ -123,10 +132,7 @@ __device__ inline unsigned varying_bits(unsigned digit, bool valid) {
   const unsigned long long vm = __ballot(valid);
   if (vm == 0) return 0u;
   const unsigned first = __builtin_amdgcn_readlane(digit, __ffsll((long long)vm) - 1);
-  unsigned d = valid ? digit ^ first : 0u;
-#pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) d |= __shfl_xor(d, s, 64);
-  return __builtin_amdgcn_readfirstlane(d);
+  return (unsigned)wave_or(valid ? (int)(digit ^ first) : 0);
 }
 
 template <int P2>
@@ -136,30 +142,31 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
     int* __restrict__ seg) {
   constexpr int CHUNK = P2 / kSegWaves;  // consecutive elements owned by one wavefront
   constexpr int NB = CHUNK / 64;         // 64-element batches per wavefront
+  constexpr int VE = NB < 4 ? NB : 4;    // consecutive elements per lane while classifying
+  constexpr int NV = NB / VE;            // batches of 64 VE elements
   static_assert(NB >= 1, "P2 must be at least the workgroup size");
-  __shared__ int ids[P2];                  // id by token position; later: segment starts (ushort)
+  __shared__ __attribute__((aligned(16))) int ids[P2];                  // id by token position; later: segment starts (ushort)
   __shared__ unsigned short buf_a[P2];     // current order of table-token positions
   __shared__ unsigned short buf_b[P2];     // next order; later: segment index by slot
-  __shared__ unsigned short hist[kSegWaves][kBins];  // per-wavefront digit counts -> first output slots
-  __shared__ int scan_tmp[kSegWaves + 1];
-  __shared__ int wave_tot[5][kSegWaves];
+  __shared__ __attribute__((aligned(16))) unsigned short hist[kSegWaves][kBins];  // per-wavefront digit counts -> first output slots
+  __shared__ int scan_tmp[3][kSegWaves];
+  __shared__ int wave_tot[3][kSegWaves];
   __shared__ int s_or, s_bad;
-  // counting-sort path: ids seen anywhere / before this workgroup's chunk (they live in the two
-  // order buffers, which only the general path uses, and later); first slot and segment index
-  // of every id; scratch for the work-unit list
-  int* const full_h = reinterpret_cast<int*>(buf_b);
-  int* const before_h = reinterpret_cast<int*>(buf_a);
-  __shared__ int start_v[kBins + 1];
+  // counting-sort path: how often every id is seen, anywhere and (<< 16) before this workgroup's
+  // chunk (it lives in an order buffer, which only the general path uses, and later); first slot
+  // and segment index of every id; scratch for the work-unit list
+  unsigned* const id_count = reinterpret_cast<unsigned*>(buf_b);
+  __shared__ int start_v[kBins];
   __shared__ int seg_i[kBins];
   __shared__ int seg_tmp[2][kBins + 8];
-  static_assert(P2 * sizeof(unsigned short) >= kBins * sizeof(int), "histograms must fit the order buffers");
+  static_assert(P2 * sizeof(unsigned short) >= kBins * sizeof(int), "the histogram must fit an order buffer");
 
   const int b = blockIdx.x, view = blockIdx.y, tid = threadIdx.x;
   // Several workgroups per (sequence, view): K of them take a chunk of the positions each, one
   // more (k == K, no chunk) lists the work units.
-  const int k = blockIdx.z, K = gridDim.z > 1 ? (int)gridDim.z - 1 : 1;
+  const int k = blockIdx.z, K = (int)gridDim.z - 1;
   const int chunk = (((N + K - 1) / K) + 63) & ~63, c0 = k < K ? k * chunk : 0, c1 = min(N, c0 + chunk);
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const SegLayout lay(B, N);
   int* counts = seg + lay.counts + (size_t)b * kCountWords;
   int* global_idx = seg + lay.global_idx + (size_t)b * N;
@@ -176,110 +183,121 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
 
   if (b == 0 && view == 0 && k == 0 && tid < kHdrWords)
     seg[tid] = tid == 0 ? kMagic : tid == 1 ? B : tid == 2 ? N : tid == 4 ? max_global : tid == 5 ? radius : 0;
-  if (tid == 0) { s_or = 0; s_bad = 0; }
-  if (tid < kBins) { full_h[tid] = 0; before_h[tid] = 0; }
-  lds_barrier();
-
   // Element order everywhere below: a wavefront owns CHUNK consecutive elements and walks them in
   // batches of 64, lane = consecutive element, so that LDS and global accesses are unit-stride
-  // and ranks inside a batch come from ballots.
+  // and ranks inside a batch come from ballots.  Only the classification, which every workgroup
+  // does for the whole sequence and which the instruction issue bounds, takes VE consecutive
+  // elements per lane.
   const int w0 = wave * CHUNK;
 
   // All of this wavefront's inputs first, in one go: the loads travel together instead of one
-  // dependent round trip per batch (the compiler does not move them across the stores below).
-  unsigned char in_flag[NB];
-  int in_id[NB];
+  // dependent round trip per batch.
+  typedef int idv __attribute__((ext_vector_type(VE)));
+  unsigned char in_flag[NV][VE];
+  int in_id[NV][VE];
 #pragma unroll
-  for (int e = 0; e < NB; ++e) {
-    const int i = w0 + e * 64 + lane;
-    in_flag[e] = i < N ? fl[i] : (unsigned char)3;
-    in_id[e] = i < N ? id_src[i] : 0;
+  for (int e = 0; e < NV; ++e) {
+    const int i0 = w0 + (e * 64 + lane) * VE;
+    if (i0 + VE <= N) {   // (any alignment: a sequence of odd length shifts the next one)
+      __builtin_memcpy(in_flag[e], fl + i0, VE);
+      __builtin_memcpy(in_id[e], id_src + i0, VE * sizeof(int));
+    } else {
+#pragma unroll
+      for (int j = 0; j < VE; ++j) {
+        const int i = min(i0 + j, N - 1);
+        in_flag[e][j] = fl[i];
+        in_id[e][j] = id_src[i];
+      }
+    }
   }
 
+  // (while they travel) clear the counters
+  if (tid == 0) { s_or = 0; s_bad = 0; }
+  if (tid < (int)kBins) id_count[tid] = 0;
+  for (int i = tid; i < kSegWaves * (int)kBins / 8; i += kSegThreads)
+    reinterpret_cast<uint4*>(&hist[0][0])[i] = make_uint4(0, 0, 0, 0);
+  lds_barrier();
+
   // ---- bucketed mode: question tokens past the first max_global join the table tokens ----------
-  unsigned demote = 0;  // bit e: my element of batch e is such a token
+  int q_at = 0;   // question tokens before this wavefront's block
   if (max_global < N) {  // uniform; a sequence has at most N question tokens
     int n_q = 0;
 #pragma unroll
-    for (int e = 0; e < NB; ++e) {
-      n_q += __popcll(__ballot(in_flag[e] == 1));
-    }
-    if (lane == 0) wave_tot[1][wave] = n_q;
+    for (int e = 0; e < NV; ++e)
+#pragma unroll
+      for (int j = 0; j < VE; ++j) {
+        const int i = w0 + (e * 64 + lane) * VE + j;
+        n_q += __popcll(__ballot(i < N && in_flag[e][j] == 1));
+      }
+    if (lane == 0) scan_tmp[0][wave] = n_q;
     lds_barrier();
-    int q_at = 0;
-#pragma unroll
-    for (int w = 0; w < kSegWaves; ++w)
-      if (w < wave) q_at += wave_tot[1][w];
-    lds_barrier();  // wave_tot is written again below
-#pragma unroll
-    for (int e = 0; e < NB; ++e) {
-      const bool is_q = in_flag[e] == 1;
-      const unsigned long long mq = __ballot(is_q);
-      if (is_q && q_at + lanes_before(mq) >= max_global) demote |= 1u << e;
-      q_at += __popcll(mq);
-    }
+    int all_q;
+    q_at = waves_before(scan_tmp[0], wave, all_q);
   }
 
   // ---- classify; count the three kinds of position per wavefront ---------------------------
-  unsigned char my_flag[NB];
-  int n_g = 0, n_p = 0, n_l = 0, bad = 0, my_or = 0;
-  int g_bef = 0, p_bef = 0;  // question / pad tokens before this workgroup's chunk (this wavefront's share)
+  int n_lg = 0, lg_bef = 0;   // my table tokens, and question tokens << 16; those before this workgroup's chunk
+  int bad = 0, my_or = 0;
 #pragma unroll
-  for (int e = 0; e < NB; ++e) {
-    const int i = w0 + e * 64 + lane;
-    unsigned char f = 3;
-    int id = 0;
-    if (i < N) {
-      f = in_flag[e];
-      if (f > 2) { bad = 1; f = 2; }
-      if ((demote >> e) & 1u) f = 0;
-      id = in_id[e];
-      if (f == 0) {
-        if (id < 0) bad = 1;
-        my_or |= id;
+  for (int e = 0; e < NV; ++e) {
+    const int i0 = w0 + (e * 64 + lane) * VE;
+    const bool before = i0 < c0;   // (c0 is a multiple of 64)
+    if (max_global < N) {
+      int mine = 0;
+#pragma unroll
+      for (int j = 0; j < VE; ++j) mine += i0 + j < N && in_flag[e][j] == 1;
+      const int upto = wave_scan(mine);
+      int q = q_at + upto - mine;
+#pragma unroll
+      for (int j = 0; j < VE; ++j)
+        if (i0 + j < N && in_flag[e][j] == 1 && q++ >= max_global) in_flag[e][j] = 0;
+      q_at += __builtin_amdgcn_readlane(upto, 63);
+    }
+    idv code;
+    int lg = 0;
+    unsigned run = 0;
+#pragma unroll
+    for (int j = 0; j < VE; ++j) {
+      unsigned f = in_flag[e][j];
+      const int id = in_id[e][j];
+      const bool have = i0 + j < N;
+      const bool table = have && f == 0;
+      bad |= have && (f > 2 || (f == 0 && id < 0));
+      f = min(f, 2u);
+      my_or |= table ? id : 0;
+      lg += table ? 1 : have && f == 1 ? 1 << 16 : 0;
+      code[j] = f == 0 ? id : -(int)f;   // table token: its id; question token -1; pad -2
+      // histogram of the low digit, one LDS add per run of equal ids of this lane (ids of a
+      // flattened table come in runs); only meaningful if every id turns out to be below kBins
+      const int key = table ? id & (int)(kBins - 1u) : -1;
+      const int next = j + 1 < VE && i0 + j + 1 < N && in_flag[e][j + 1] == 0 ? in_id[e][j + 1] & (int)(kBins - 1u) : -1;
+      ++run;
+      if (key != next || j + 1 == VE) {
+        if (key >= 0) atomicAdd(&id_count[key], before ? run * 0x10001u : run);
+        run = 0;
       }
-      ids[i] = f == 0 ? id : -(int)f;   // table token: its id; question token -1; pad -2
     }
-    my_flag[e] = f;
-    const unsigned long long ml = __ballot(f == 0), mg = __ballot(f == 1), mp = __ballot(f == 2);
-    n_l += __popcll(ml);
-    n_g += __popcll(mg);
-    n_p += __popcll(mp);
-    if (w0 + e * 64 < c0) { g_bef += __popcll(mg); p_bef += __popcll(mp); }   // (c0 is a multiple of 64)
-    // histogram of the low digit, one LDS add per run of equal ids inside the batch (ids of a
-    // flattened table come in runs); only meaningful if every id turns out to be below kBins
-    const int key = f == 0 ? (id & (int)(kBins - 1u)) : -1;
-    const int prev = from_previous_lane(key);
-    const bool head = lane == 0 || key != prev;
-    const unsigned long long mh = __ballot(head);
-    if (head && key >= 0) {
-      const unsigned long long later = lane == 63 ? 0ull : mh >> (lane + 1);
-      const int run = later ? __ffsll((long long)later) : 64 - lane;
-      atomicAdd(&full_h[key], run);
-      if (w0 + e * 64 < c0) atomicAdd(&before_h[key], run);
-    }
+    if constexpr (VE == 1) ids[i0] = code[0];
+    else *reinterpret_cast<idv*>(&ids[i0]) = code;
+    n_lg += lg;
+    if (before) lg_bef += lg;
   }
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) my_or |= __shfl_xor(my_or, d, 64);
-  if (lane == 0) {
-    wave_tot[0][wave] = n_l;
-    wave_tot[1][wave] = n_g;
-    wave_tot[2][wave] = n_p;
-    wave_tot[3][wave] = g_bef;
-    wave_tot[4][wave] = p_bef;
+  my_or = wave_or(my_or);
+  n_lg = wave_scan(n_lg);
+  lg_bef = wave_scan(lg_bef);
+  if (lane == 63) {
     if (my_or) atomicOr(&s_or, my_or);
+    wave_tot[0][wave] = n_lg;
+    wave_tot[1][wave] = lg_bef;
   }
   if (bad) s_bad = 1;
   lds_barrier();
-  int L = 0, G = 0, P = 0, l_at = 0, g_at = 0, p_at = 0, g_before = 0, p_before = 0;
-#pragma unroll
-  for (int w = 0; w < kSegWaves; ++w) {
-    const int cl = wave_tot[0][w], cg = wave_tot[1][w], cp = wave_tot[2][w];
-    if (w < wave) { l_at += cl; g_at += cg; p_at += cp; }
-    L += cl; G += cg; P += cp;
-    g_before += wave_tot[3][w];
-    p_before += wave_tot[4][w];
-  }
+  int lg_all, lg_before;
+  const int lg_at = waves_before(wave_tot[0], wave, lg_all);
+  waves_before(wave_tot[1], wave, lg_before);
+  const int L = lg_all & 0xffff, G = lg_all >> 16, P = N - L - G;
+  // kinds before this workgroup's chunk
+  const int g_before = lg_before >> 16, p_before = c0 - (lg_before & 0xffff) - g_before;
   const unsigned all_bits = (unsigned)s_or;
   const float inv_radius = radius > 0 ? 1.0f / (float)radius : 0.f;
   const int n_pt = (P + kPadSlots - 1) / kPadSlots;
@@ -288,33 +306,34 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
   __shared__ unsigned short head_pos[kMaxUnits];
   __shared__ unsigned short unit_len[kMaxUnits];
 
-  if (K > 1 && (all_bits & ~(kBins - 1u)) == 0) {
-    // ============ counting-sort path: every id is below kBins, several workgroups ============
+  if ((all_bits & ~(kBins - 1u)) == 0) {
+    // ============ counting-sort path: every id is below kBins, all workgroups ============
     constexpr int NBC = P2 > 8 * kSegThreads ? 2 : 1;   // 64-position batches of the chunk per wavefront
-    // first slot and segment index of every id
-    const int c_id = tid < (int)kBins ? full_h[tid] : 0;
-    int tot_l, S;
-    const int first_slot = block_exclusive_scan(c_id, scan_tmp, tot_l);
-    const int seg_index = block_flag_scan(c_id > 0, scan_tmp, S);
+    // first slot and segment index of every id, from one scan (segments << 16)
+    const unsigned count = tid < (int)kBins ? id_count[tid] : 0u;
+    const int c_id = (int)(count & 0xffffu);
+    int tot;
+    const int at = block_exclusive_scan(c_id | (c_id > 0 ? 1 << 16 : 0), scan_tmp[1], tot);
+    const int first_slot = at & 0xffff, seg_index = at >> 16, S = tot >> 16;
     if (tid < (int)kBins) {
       start_v[tid] = first_slot;
       seg_i[tid] = seg_index;
       if (c_id > 0) seg_tmp[0][seg_index] = first_slot;   // first slot of every segment, compact
     }
-    if (tid == 0) { start_v[kBins] = L; seg_tmp[0][S] = L; }
-    for (int i = tid; i < kSegWaves * (int)kBins / 2; i += kSegThreads) reinterpret_cast<int*>(&hist[0][0])[i] = 0;
+    if (tid == 0) seg_tmp[0][S] = L;
     lds_barrier();
-    // window of slot s: the slots of its id (binary search over the first slots), in bucketed
-    // mode cut to the neighbouring buckets.  Slots are below 2^14, so the bucket index comes
-    // exactly from one float multiply: (s + 0.5) / radius is at least 0.5 / radius away from an
-    // integer and the rounding error is below 2e-7 s / radius.
+    const int* sstart = seg_tmp[0];
+    // window of slot s: its segment (binary search over the first slots), in bucketed mode cut to
+    // the neighbouring buckets.  Slots are below 2^14, so the bucket index comes exactly from one
+    // float multiply: (s + 0.5) / radius is at least 0.5 / radius away from an integer and the
+    // rounding error is below 2e-7 s / radius.
     auto window = [&](int s) {
-      int lo_i = 0, hi_i = kBins;   // smallest i in (0, kBins] with start_v[i] > s
+      int lo_i = 0, hi_i = S;   // sstart[lo_i] <= s < sstart[hi_i]
       while (hi_i - lo_i > 1) {
         const int mid = (lo_i + hi_i) >> 1;
-        if (start_v[mid] > s) hi_i = mid; else lo_i = mid;
+        if (sstart[mid] > s) hi_i = mid; else lo_i = mid;
       }
-      int lo = start_v[hi_i - 1], hi = start_v[hi_i];
+      int lo = sstart[lo_i], hi = sstart[hi_i];
       if (radius > 0) {
         const int first = (int)(((float)s + 0.5f) * inv_radius) * radius;  // first slot of s's bucket
         lo = max(lo, first - radius);
@@ -348,22 +367,22 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
         g_w += __popcll(mg);
         p_w += __popcll(mp);
       }
-      if (lane == 0) { wave_tot[1][wave] = g_w; wave_tot[2][wave] = p_w; }
+      if (lane == 0) wave_tot[2][wave] = g_w | p_w << 16;
       lds_barrier();
       // (id, wavefront) counts -> tokens with that id before the wavefront's block
       if (tid < (int)kBins) {
-        int running = before_h[tid];
+        int c[kSegWaves], running = (int)(count >> 16);
+#pragma unroll
+        for (int w = 0; w < kSegWaves; ++w) c[w] = hist[w][tid];
 #pragma unroll
         for (int w = 0; w < kSegWaves; ++w) {
-          const int c = hist[w][tid];
           hist[w][tid] = (unsigned short)running;
-          running += c;
+          running += c[w];
         }
       }
-      int g_at_c = g_before, p_at_c = p_before;
-#pragma unroll
-      for (int w = 0; w < kSegWaves; ++w)
-        if (w < wave) { g_at_c += wave_tot[1][w]; p_at_c += wave_tot[2][w]; }
+      int gp_chunk;
+      const int gp = waves_before(wave_tot[2], wave, gp_chunk);
+      const int g_at_c = g_before + (gp & 0xffff), p_at_c = p_before + (gp >> 16);
       lds_barrier();
 #pragma unroll
       for (int j = 0; j < NBC; ++j) {
@@ -397,9 +416,25 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
     }
     if (k != K) return;
     // ---- work units of the attention kernels (the workgroup without a chunk) ---------------------
+    // question-token owners (the same for both views), by wavefronts that list no units
+    static_assert(kMaxTiles <= kSegThreads - (int)kBins, "a thread per record");
+    if (view == 0 && tid >= (int)kBins && tid - (int)kBins < lay.tiles) {
+      const int rec = tid - (int)kBins;
+      const GlobalSplit gs = global_split(G, L, N);
+      int4 q0 = make_int4(UNIT_NONE, 0, 0, 0), q1 = make_int4(0, 0, -1, 0);
+      if (rec < gs.n_gt * gs.n_chunks) {
+        const int gt = rec / gs.n_chunks, c = rec % gs.n_chunks;
+        q0 = make_int4(UNIT_GLOBAL, gt * BM, 0, L);
+        q1.x = c * gs.per;
+        q1.y = min(gs.n_st, q1.x + gs.per);
+        if (gs.n_chunks > 1) q1.z = rec;
+        q1.w = gs.n_chunks;
+      }
+      gunit[2 * rec] = q0;
+      gunit[2 * rec + 1] = q1;
+    }
     // A run is a segment of at least kBigSegment slots, or the shorter segments between two such
     // segments; units are 128-slot pieces of runs (see the general path below for why).
-    const int* sstart = seg_tmp[0];
     int* run_start = seg_tmp[1];
     bool cut = false;
     if (tid < S) {
@@ -407,13 +442,13 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
       cut = tid == 0 || size >= kBigSegment || sstart[tid] - sstart[tid - 1] >= kBigSegment;
     }
     int n_runs;
-    const int run_index = block_flag_scan(cut, scan_tmp, n_runs);
+    const int run_index = block_flag_scan(cut, scan_tmp[2], n_runs);
     if (cut) run_start[run_index] = sstart[tid];
     if (tid == 0) run_start[n_runs] = L;
     lds_barrier();
     const int run_units = tid < n_runs ? (run_start[tid + 1] - run_start[tid] + kTileSlots - 1) / kTileSlots : 0;
     int n_units;
-    const int unit_base = block_exclusive_scan(run_units, scan_tmp, n_units);
+    const int unit_base = block_exclusive_scan(run_units, scan_tmp[1], n_units);
     if (n_units + n_pt <= lay.units) {
       for (int i = 0; i < run_units; ++i) head_pos[unit_base + i] = (unsigned short)(run_start[tid] + i * kTileSlots);
     } else {  // more records than the buffer has: every 128 slots regardless of segments
@@ -448,36 +483,27 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
       unit[2 * place] = r0;
       unit[2 * place + 1] = r1;
     }
-    if (view == 0 && tid < lay.tiles) {  // question-token owners (the same for both views)
-      const GlobalSplit gs = global_split(G, L, N);
-      int4 q0 = make_int4(UNIT_NONE, 0, 0, 0), q1 = make_int4(0, 0, -1, 0);
-      if (tid < gs.n_gt * gs.n_chunks) {
-        const int gt = tid / gs.n_chunks, c = tid % gs.n_chunks;
-        q0 = make_int4(UNIT_GLOBAL, gt * BM, 0, L);
-        q1.x = c * gs.per;
-        q1.y = min(gs.n_st, q1.x + gs.per);
-        if (gs.n_chunks > 1) q1.z = tid;
-        q1.w = gs.n_chunks;
-      }
-      gunit[2 * tid] = q0;
-      gunit[2 * tid + 1] = q1;
-    }
     return;
   }
   if (k != 0) return;   // ids of 512 and more: the first workgroup sorts alone
 
   // ======================= general path: LSD radix sort in this workgroup =======================
   // ---- compact the three kinds in ascending position order ------------------------------------
+  int l_at = lg_at & 0xffff, g_at = lg_at >> 16, p_at = min(w0, N) - l_at - g_at;
 #pragma unroll
   for (int e = 0; e < NB; ++e) {
     const int i = w0 + e * 64 + lane;
-    const unsigned long long ml = __ballot(my_flag[e] == 0), mg = __ballot(my_flag[e] == 1),
-                             mp = __ballot(my_flag[e] == 2);
-    if (my_flag[e] == 0) buf_a[l_at + lanes_before(ml)] = (unsigned short)i;
+    const unsigned char f = i < N ? fl[i] : (unsigned char)0;
+    const unsigned long long mq = __ballot(i < N && f == 1);
+    // (the question tokens kept come first)
+    const bool question = i < N && f == 1 && g_at + lanes_before(mq) < max_global;
+    const bool table = i < N && (f == 0 || (f == 1 && !question)), pad = i < N && f >= 2;
+    const unsigned long long ml = __ballot(table), mg = __ballot(question), mp = __ballot(pad);
+    if (table) buf_a[l_at + lanes_before(ml)] = (unsigned short)i;
     else if (i < N) seg_of_tok[i] = -1;
     if (view == 0) {
-      if (my_flag[e] == 1) global_idx[g_at + lanes_before(mg)] = i;
-      if (my_flag[e] == 2) pad_idx[p_at + lanes_before(mp)] = i;
+      if (question) global_idx[g_at + lanes_before(mg)] = i;
+      if (pad) pad_idx[p_at + lanes_before(mp)] = i;
     }
     l_at += __popcll(ml);
     g_at += __popcll(mg);
@@ -534,7 +560,7 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
       }
     }
     int all;
-    const int digit_base = block_exclusive_scan(tot, scan_tmp, all);
+    const int digit_base = block_exclusive_scan(tot, scan_tmp[0], all);
     if (tid < kBins) {
 #pragma unroll
       for (int w = 0; w < kSegWaves; ++w) hist[w][tid] = (unsigned short)(first[w] + digit_base);
@@ -726,10 +752,10 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
 hipError_t launch_build_segments(const int* row_ids, const int* col_ids,
                                  const unsigned char* flags, int B, int N, int max_global,
                                  int radius, int* seg, hipStream_t stream) {
-  // up to eight workgroups per (sequence, view) with at least 1024 positions each, and with more
-  // than one of them a further one for the work-unit list
+  // up to eight workgroups per (sequence, view) with about 1024 positions each, and a further one
+  // for the work-unit list
   const int chunks = std::min(8, (N + kSegThreads - 1) / kSegThreads);
-  dim3 grid(B, 2, chunks > 1 ? chunks + 1 : 1), block(kSegThreads);
+  dim3 grid(B, 2, chunks + 1), block(kSegThreads);
   ProfileScope prof(1, stream);
 #define MATE_SEG_CASE(P2)                                                                  \
   if (N <= P2) {                                                                            \

@@ -33,6 +33,18 @@ def test_bucketed_tables_scattered(N, mode):
     hp.compare_segments(_build(st, mode), st, bucketed=mode)
 
 
+@pytest.mark.parametrize("mode", [None, (5, 7)])
+@pytest.mark.parametrize("N", [1, 3, 63, 65, 511, 1023, 1025, 2047, 2050, 4095, 4099, 8191, 8193, 16383])
+def test_counting_sort_edges(N, mode):
+    """Ids below 512 (the counting sort) at the edges of the four-element batches, of the chunks
+    and of the kernel's size classes; odd lengths misalign every sequence but the first."""
+    print(f"counting sort N={N} G,R={mode}", flush=True)
+    rng = np.random.default_rng(N)
+    st = synth.random_structure(rng, 3, N, max_rows=max(1, min(500, N // 3)), max_cols=7, max_global=min(N, 90),
+                                max_cell=5, scatter=N % 4 == 3, sparse_ids=False)
+    hp.compare_segments(_build(st, mode), st, bucketed=mode)
+
+
 @pytest.mark.parametrize("idx", [2, 4, 5, 6])
 def test_bucketed_tables_benchmark_configs(idx):
     print(f"bucketed tables config {idx}", flush=True)
