@@ -62,11 +62,11 @@ __device__ __forceinline__ void merge_chunks(const float* const (&part)[kTensors
 // dQ (and delta)
 // ======================================================================================
 constexpr int kDqStage = 2 * kTileBytes;          // K tile, V tile
-constexpr int kDqNS = 2, kDkvNS = 2;              // LDS stages of the two kernels
+constexpr int NS = 2;                             // LDS stages of the two kernels
 constexpr int kDkvStage = 2 * kTileBytes + 512;   // Q tile, dO tile, -lse/scale[64], -delta[64]
 
 __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
-  __shared__ __attribute__((aligned(1024))) char lds[kDqNS * kDqStage];
+  __shared__ __attribute__((aligned(1024))) char lds[NS * kDqStage];
   __shared__ int idx_ring[kIdxSlots][BN];
   __shared__ int q_tok[BM];
 
@@ -95,9 +95,10 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
   // Second: the owned rows (registers) and the first K / V tiles (LDS), all in flight together.
   // K and V tiles stream through the LDS ring; K is read both plain (S^T = K Q^T) and
   // transposed (dQ^T += K^T dS^T), V plain (dP^T = V dO^T).
-  TileStream<kDqStage, kDqNS> stream(u, global_idx, lds, idx_ring, K, V, nullptr, 0, wave, lane);
+  TileStream<kDqStage, NS> stream(u, global_idx, lds, idx_ring, K, V, nullptr, 0, wave, lane);
   stream.begin();
-  const OwnedRow me = owned_row(u, a, b, view, wave, m);
+  const OwnerSplit split(u, wave);
+  const OwnedRow me = owned_row(u, a, b, view, split.block, m);
   asm volatile("" ::"v"(me.pos), "v"(me.lo), "v"(me.hi), "v"(me.stage_tok));  // the owned rows are known from here on
   if (tid < BM) q_tok[tid] = me.stage_tok;
   // the dkv kernel counts the chunks of an owner tile in the word of its first one
@@ -126,12 +127,12 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
   delta = half_sum(delta);
   // every chunk of a question-token owner computes the same delta; the first one stores it
   // (stored negated, with -lse / scale beside it: the dK/dV kernel starts its accumulators there)
-  if (hl == 0 && me.valid && u.t_begin == 0) {
+  if (hl == 0 && me.valid && u.t_begin == 0 && split.writes(wave)) {
     a.delta[bh + me.pos] = -delta;
     a.nlse[bh + me.pos] = -lse / a.scale;
   }
   const float lse2 = lse * kLog2e;
-  const float sc = a.scale * kLog2e;
+  const float sc = uniform(a.scale * kLog2e);
 
   int koff[4], toff[2][2];
   operand_offsets(lane, koff, toff);
@@ -142,23 +143,31 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
     const char* Vst = Kst + kTileBytes;
     const bool part0 = t < u.n_t0;
     const int base = part0 ? t * BN : u.s_lo + (t - u.n_t0) * BN;
-    const bool skip = !me.wave_active || (!part0 && (base >= me.w_hi || base + BN <= me.w_lo));
-    if (!skip) {
-      const bool full = part0 ? (base + BN <= u.G) : (base >= me.a_lo && base + BN <= me.a_hi);
-      dq_tile(Kst, Vst, qf, gf, koff, toff, sc, lse2, delta, WindowMask(full, base, hl, part0 ? 0 : me.lo, part0 ? u.G : me.hi, part0 ? 0 : me.w_lo, part0 ? u.G : me.w_hi), dq_acc);
+    if (me.wave_active) {
+      WindowMask mask(base, hl, part0 ? 0 : me.lo, part0 ? u.G : me.hi, split.first(base, part0 ? 0 : me.w_lo),
+                      split.end(base, part0 ? u.G : me.w_hi), part0 ? 0 : me.a_lo, part0 ? u.G : me.a_hi);
+      dq_tile(Kst, Vst, qf, gf, koff, toff, sc, lse2, delta, mask, dq_acc);
     }
     stream.release();
   }
   __syncthreads();  // all wavefronts are done reading the stages; reuse them for the epilogue
+  int ln = lane;
+  asm volatile("" : "+v"(ln));  // what follows is computed here, not kept in registers through the loop
+  if (split.on) {  // add the other half of the streamed rows
+    char* const mine = lds + BM * 128 + (wave & 1) * (kItemFloats * 2 * 4);  // (rows are staged below that)
+    if (wave >= 2) put_items<2>(mine, dq_acc, ln);
+    __syncthreads();
+    if (wave < 2) add_items<2>(mine, dq_acc, 1.f, 1.f, ln);
+  }
   if (u.part >= 0) {
     const size_t slot = (size_t)w.bh * owner_slots(N) + u.part;
-    if (me.wave_active) store_partial<false>(dq_acc, a.scale, a.part[0] + slot * BM * kD, wave, lane);
+    if (me.wave_active && split.writes(wave)) store_partial<false>(dq_acc, a.scale, a.part[0] + slot * BM * kD, wave, ln);
     return;
   }
   const f32x16 (*accs[1])[2] = {&dq_acc};
   const float muls[1] = {a.scale};
   unsigned short* const outs[1] = {dQ};
-  store_owned_rows<1>(accs, muls, outs, lds, q_tok, wave, lane);
+  store_owned_rows<1>(accs, muls, outs, lds, q_tok, wave, ln);
 }
 
 // (four workgroups per CU: with three, the column-head units of the benchmark shape do not all
@@ -203,11 +212,12 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
   // First round trip: the owned rows' positions and the first tiles' token indices; second:
   // the owned K / V rows (registers) and the first tiles (LDS).
   const float* row_src = wave == 0 ? a.nlse + bh : wave == 1 ? a.delta + bh : nullptr;
-  TileStream<kDkvStage, kDkvNS> stream(u, global_idx, lds, idx_ring, Q, dO, row_src,
+  TileStream<kDkvStage, NS> stream(u, global_idx, lds, idx_ring, Q, dO, row_src,
                                2 * kTileBytes + 256 * wave, wave, lane);
   stream.begin();
   // `me` is this lane's key; its window is the set of query slots that see it
-  const OwnedRow me = owned_row(u, a, b, view, wave, m);
+  const OwnerSplit split(u, wave);
+  const OwnedRow me = owned_row(u, a, b, view, split.block, m);
   asm volatile("" ::"v"(me.pos), "v"(me.lo), "v"(me.hi), "v"(me.stage_tok));  // the owned rows are known from here on
   if (tid < BM) k_tok[tid] = me.stage_tok;
   stream.prime();
@@ -219,7 +229,7 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
     kf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(K + off));
     vf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(V + off));
   }
-  const float sc = a.scale * kLog2e;
+  const float sc = uniform(a.scale * kLog2e);
   asm volatile("" ::"v"(kf[0]), "v"(kf[1]), "v"(kf[2]), "v"(kf[3]), "v"(vf[0]), "v"(vf[1]),
                "v"(vf[2]), "v"(vf[3]));
 
@@ -234,18 +244,31 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
     const float* delta_row = lse_row + BN;
     const bool part0 = t < u.n_t0;
     const int base = part0 ? t * BN : u.s_lo + (t - u.n_t0) * BN;
-    const bool skip = !me.wave_active || (!part0 && (base >= me.w_hi || base + BN <= me.w_lo));
-    if (!skip) {
-      const bool full = part0 ? (base + BN <= u.G) : (base >= me.a_lo && base + BN <= me.a_hi);
-      dkv_tile(Qst, Gst, lse_row, delta_row, kf, vf, poff, toff, sc, hl, WindowMask(full, base, hl, part0 ? 0 : me.lo, part0 ? u.G : me.hi, part0 ? 0 : me.w_lo, part0 ? u.G : me.w_hi), dk_acc, dv_acc);
+    if (me.wave_active) {
+      WindowMask mask(base, hl, part0 ? 0 : me.lo, part0 ? u.G : me.hi, split.first(base, part0 ? 0 : me.w_lo),
+                      split.end(base, part0 ? u.G : me.w_hi), part0 ? 0 : me.a_lo, part0 ? u.G : me.a_hi);
+      dkv_tile(Qst, Gst, lse_row, delta_row, kf, vf, poff, toff, sc, hl, mask, dk_acc, dv_acc);
     }
     stream.release();
   }
   __syncthreads();  // all wavefronts are done reading the stages; reuse them for the epilogue
+  if (split.on) {  // add the other half of the streamed rows
+    char* const mine = lds + (wave & 1) * (kItemFloats * 4 * 4);
+    if (wave >= 2) {
+      put_items<2>(mine, dk_acc, lane);
+      put_items<2>(mine + kItemFloats * 2 * 4, dv_acc, lane);
+    }
+    __syncthreads();
+    if (wave < 2) {
+      add_items<2>(mine, dk_acc, 1.f, 1.f, lane);
+      add_items<2>(mine + kItemFloats * 2 * 4, dv_acc, 1.f, 1.f, lane);
+    }
+    __syncthreads();
+  }
   if (u.part >= 0) {
     const size_t slot = (size_t)w.bh * owner_slots(N) + u.part;
     const size_t slot0 = slot - u.part % u.n_chunks;
-    if (me.wave_active) {
+    if (me.wave_active && split.writes(wave)) {
       store_partial<true>(dk_acc, a.scale, a.part[1] + slot * BM * kD, wave, lane);
       store_partial<true>(dv_acc, 1.f, a.part[2] + slot * BM * kD, wave, lane);
     }
@@ -292,7 +315,7 @@ __device__ __forceinline__ void merge_dq(const AttnArgs& a, int bh_i, char* stag
 // The first `n_merge` workgroups (a multiple of eight, so that the unit queues keep their XCDs) merge
 // dQ partials: a few microseconds each, out of the way before the kernel's own tail.
 __global__ __launch_bounds__(kThreads) void bwd_dkv_mfma_kernel(AttnArgs a, int n_merge) {
-  __shared__ __attribute__((aligned(1024))) char lds[kDkvNS * kDkvStage];
+  __shared__ __attribute__((aligned(1024))) char lds[NS * kDkvStage];
   __shared__ int row_tok[BM];
   if ((int)blockIdx.x < n_merge) {
     if ((int)blockIdx.x < a.B * a.H) merge_dq(a, blockIdx.x, lds, row_tok);

@@ -111,7 +111,6 @@ struct DenseStream {
 // The dense-mask rule as a Mask of tile_bodies.h: the pair is kept iff the two tokens' codes say
 // so.  `codes` points at the tile's 64 codes in LDS, offset by this lane half's 4 hl.
 struct CodeMask {
-  static constexpr bool full = false;
   const int* codes;
   int my_code;
   bool my_global;
@@ -125,8 +124,10 @@ struct CodeMask {
       k[4 * g] = kc.x; k[4 * g + 1] = kc.y; k[4 * g + 2] = kc.z; k[4 * g + 3] = kc.w;
     }
   }
+  __device__ __forceinline__ bool full(int) const { return false; }
   __device__ __forceinline__ bool skip(int) const { return false; }
-  __device__ __forceinline__ bool in(int, int c) const { return allowed(k[c], my_code, my_global); }
+  __device__ __forceinline__ bool in(int c) const { return allowed(k[c], my_code, my_global); }
+  __device__ __forceinline__ float keep(int c, float x, float other) const { return in(c) ? x : other; }
 };
 
 // ======================================================================================
@@ -159,7 +160,7 @@ __global__ __launch_bounds__(kThreads) void fwd_dense_kernel(DenseArgs a) {
     qf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(Q + (size_t)me.pos * kD + ks * 16 + hl * 8));
   asm volatile("" ::"v"(qf[0]), "v"(qf[1]), "v"(qf[2]), "v"(qf[3]));
 
-  const float sc = a.scale * kLog2e;
+  const float sc = uniform(a.scale * kLog2e);
   f32x16 o_acc[2] = {zero16(), zero16()};
   float m_run = -INFINITY, l_run = 0.f;
   int koff[4], voff[2][2];
@@ -171,7 +172,7 @@ __global__ __launch_bounds__(kThreads) void fwd_dense_kernel(DenseArgs a) {
     const char* Kst = stream.acquire(t, n_tiles);
     const char* Vst = Kst + kTileBytes;
     if (!wave_active) continue;
-    fwd_tile(Kst, Vst, qf, koff, voff, sc, 0.f, CodeMask(code + t * BN, hl, me.code, me.global), o_acc, m_run, l_run);
+    fwd_tile(Kst, Vst, qf, koff, voff, sc, CodeMask(code + t * BN, hl, me.code, me.global), o_acc, m_run, l_run);
   }
   __syncthreads();
   const float l_tot = half_sum(l_run);
@@ -297,7 +298,7 @@ __global__ __launch_bounds__(kThreads) void bwd_dkv_dense_kernel(DenseArgs a) {
   }
   asm volatile("" ::"v"(kf[0]), "v"(kf[1]), "v"(kf[2]), "v"(kf[3]), "v"(vf[0]), "v"(vf[1]),
                "v"(vf[2]), "v"(vf[3]));
-  const float sc = a.scale * kLog2e;
+  const float sc = uniform(a.scale * kLog2e);
   int poff[4], toff[2][2];
   operand_offsets(lane, poff, toff);
   const bool wave_active = u.tile * BM + wave * 32 < N;
@@ -408,7 +409,7 @@ __global__ __launch_bounds__(64 * NW, 2) void bwd_dense_small_kernel(DenseArgs a
       code[32 * wave + m] = 32 * wave + m >= N ? -2 : f == 0 ? id : f == 1 ? -1 : -2;
     }
   }
-  const float sc = a.scale * kLog2e;
+  const float sc = uniform(a.scale * kLog2e);
   int poff[4], toff[2][2];
   operand_offsets(lane, poff, toff);
   const int n_blocks = (N + 31) / 32;  // wavefronts that own keys, and query blocks
@@ -447,7 +448,7 @@ __global__ __launch_bounds__(64 * NW, 2) void bwd_dense_small_kernel(DenseArgs a
         mask.load(0);
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
-          const bool in = mask.in(0, c) && my_code > -2;
+          const bool in = mask.in(c) && my_code > -2;
           s[c] = in ? __builtin_amdgcn_exp2f(s[c] * sc) : 0.f;   // P
           dp[c] = in ? s[c] * dp[c] : 0.f;                       // dS
         }

@@ -166,7 +166,7 @@ struct Rows {
   __device__ __forceinline__ WindowMask mask(int t, int hl) const {
     const bool part0 = t < nG;
     const int base = part0 ? kRows * t : s_lo + kRows * (t - nG);
-    return WindowMask(false, base, hl, part0 ? 0 : lo, part0 ? G : hi, 0, 0);
+    return WindowMask(base, hl, part0 ? 0 : lo, part0 ? G : hi, 0, 0, 0, 0);
   }
 };
 

@@ -26,8 +26,6 @@ namespace mate {
 namespace {
 
 constexpr int kStageBytes = 2 * kTileBytes;   // K tile, V tile
-constexpr float kLazyBits = 8.f;
-constexpr int NS = 2;  // LDS stages: small enough for four workgroups per CU
 
 // Who merges.  The workspace is uninitialised, so there is no counter to add to: every chunk has a
 // word of its own and sets it to the call's ticket, a 64-bit number no earlier call has used; a
@@ -94,6 +92,8 @@ __device__ __forceinline__ void merge_chunks(const AttnArgs& a, const UnitPlan& 
   flush_rows(O, stage, row_tok, wave, lane);
 }
 
+constexpr int NS = 2;  // LDS stages: small enough for four workgroups per CU
+
 __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
   __shared__ __attribute__((aligned(1024))) char lds[NS * kStageBytes];
   __shared__ int idx_ring[kIdxSlots][BN];  // [tile & 7][row] token positions
@@ -135,7 +135,8 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
   // together.
   TileStream<kStageBytes, NS> stream(u, global_idx, lds, idx_ring, K, V, nullptr, 0, wave, lane);
   stream.begin();
-  const OwnedRow me = owned_row(u, a, b, view, wave, m);
+  const OwnerSplit split(u, wave);
+  const OwnedRow me = owned_row(u, a, b, view, split.block, m);
   asm volatile("" ::"v"(me.pos), "v"(me.lo), "v"(me.hi), "v"(me.stage_tok));  // the owned rows are known from here on
   if (tid < BM) q_tok[tid] = me.stage_tok;
   stream.prime();
@@ -145,10 +146,9 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
   for (int ks = 0; ks < 4; ++ks)
     qf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(Q + (size_t)me.pos * kD + ks * 16 + hl * 8));
 
-  const float sc = a.scale * kLog2e;  // scores are kept raw; exp2(s * sc - m * sc)
-  const float lazy = kLazyBits / sc;   // in raw-score units
+  const float sc = uniform(a.scale * kLog2e);  // scores are kept raw; exp2(s * sc - m * sc)
   f32x16 o_acc[2] = {zero16(), zero16()};
-  float m_run = -INFINITY, l_run = 0.f;  // running max of raw scores; this lane-half's share of the sum
+  float m_run = -INFINITY, l_run = 0.f;  // reference of raw scores; this lane-half's share of the sum
 
   const int tb = u.t_begin, te = u.t_end;
   // Everything loaded into registers so far is pinned as complete here, so that no load with a
@@ -166,37 +166,61 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
     // visible slot window for this tile: question keys [0,G), else this lane's segment range
     const bool part0 = t < u.n_t0;
     const int base = part0 ? t * BN : u.s_lo + (t - u.n_t0) * BN;
-    const bool skip = !me.wave_active || (!part0 && (base >= me.w_hi || base + BN <= me.w_lo));
-    if (!skip) {
-      const bool full = part0 ? (base + BN <= u.G) : (base >= me.a_lo && base + BN <= me.a_hi);
-      fwd_tile(Kst, Vst, qf, koff, voff, sc, lazy, WindowMask(full, base, hl, part0 ? 0 : me.lo, part0 ? u.G : me.hi, part0 ? 0 : me.w_lo, part0 ? u.G : me.w_hi), o_acc, m_run, l_run);
+    if (me.wave_active) {
+      WindowMask mask(base, hl, part0 ? 0 : me.lo, part0 ? u.G : me.hi, split.first(base, part0 ? 0 : me.w_lo),
+                      split.end(base, part0 ? u.G : me.w_hi), part0 ? 0 : me.a_lo, part0 ? u.G : me.a_hi);
+      fwd_tile(Kst, Vst, qf, koff, voff, sc, mask, o_acc, m_run, l_run);
     }
     stream.release();
   }
   __syncthreads();  // all wavefronts are done reading the stages; reuse them for the epilogue
 
+  int ln = lane;
+  asm volatile("" : "+v"(ln));  // what follows is computed here, not kept in registers through the loop
+  const int row = wave * 32 + (ln & 31);
+  if (split.on) {  // add the other half of the streamed rows: O = sum_h 2^(m_h - m) O_h, l likewise
+    // (beyond the 16 KB the epilogue stages rows in; the statistics where the token indices were)
+    char* const mine = lds + BM * 128 + (wave & 1) * (kItemFloats * 2 * 4);
+    float* const stat = reinterpret_cast<float*>(&idx_ring[2 * (wave & 1)][0]);
+    if (wave >= 2) {
+      put_items<2>(mine, o_acc, ln);
+      stat[ln] = m_run;
+      stat[64 + ln] = l_run;
+    }
+    __syncthreads();
+    if (wave < 2) {
+      const float m2 = stat[ln], m_new = fmaxf(m_run, m2);
+      const float own = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run - m_new) * sc);
+      const float other = m2 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m2 - m_new) * sc);
+      l_run = l_run * own + stat[64 + ln] * other;
+      m_run = m_new;
+      add_items<2>(mine, o_acc, own, other, ln);
+    }
+  }
+  const bool writes = me.wave_active && split.writes(wave);
   const float l_tot = half_sum(l_run);
   if (u.part >= 0) {
     // chunk of a question-token owner: leave (unnormalised O, max, sum); the last one merges
     const size_t slot = (size_t)w.bh * owner_slots(N) + u.part;
     const int mine = u.part % u.n_chunks;
-    if (me.wave_active) {
-      store_partial<true>(o_acc, 1.f, a.part[0] + slot * BM * kD, wave, lane);
-      if (hl == 0)
-        put_pair<true>(a.part_ml + (slot * BM + wave * 32 + m) * 2, m_run == -INFINITY ? m_run : m_run * sc, l_tot);
+    if (writes) {
+      store_partial<true>(o_acc, 1.f, a.part[0] + slot * BM * kD, wave, ln);
+      if (ln < 32)
+        put_pair<true>(a.part_ml + (slot * BM + row) * 2, m_run == -INFINITY ? m_run : m_run * sc, l_tot);
     }
     unsigned long long* words = a.arrived + (slot - mine);
     if (completes_group(words, mine, u.n_chunks, a.ticket, &group_done)) {
-      merge_chunks(a, u, slot - mine, O, LSE, lds, q_tok, wave, lane);
-      if (tid < u.n_chunks) __hip_atomic_store(words + tid, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      merge_chunks(a, u, slot - mine, O, LSE, lds, q_tok, wave, ln);
+      const int c = wave * 64 + ln;
+      if (c < u.n_chunks) __hip_atomic_store(words + c, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     return;
   }
-  if (hl == 0 && me.valid) LSE[me.pos] = (m_run * sc + __builtin_amdgcn_logf(l_tot)) * kLn2;
+  if (ln < 32 && q_tok[row] >= 0) LSE[q_tok[row]] = (m_run * sc + __builtin_amdgcn_logf(l_tot)) * kLn2;
   const f32x16 (*accs[1])[2] = {&o_acc};
   const float muls[1] = {1.f / l_tot};
   unsigned short* const outs[1] = {O};
-  store_owned_rows<1>(accs, muls, outs, lds, q_tok, wave, lane);
+  store_owned_rows<1>(accs, muls, outs, lds, q_tok, wave, ln);
 }
 
 __global__ __launch_bounds__(kThreads, 4) void fwd_mfma_kernel(AttnArgs a) {

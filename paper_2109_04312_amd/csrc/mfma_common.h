@@ -39,6 +39,9 @@ __device__ inline bf16x8 pack8(const f32x16& x, int c0) {
   return r;
 }
 
+// A value that is the same in all lanes, in a scalar register.
+__device__ inline float uniform(float x) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x))); }
+
 // max / sum of a per-row value across the two lane halves that share the row (lanes l, l ^ 32):
 // v_permlane32_swap exchanges the upper half of its first operand with the lower half of the
 // second, so after swapping (x, x) every lane holds both halves' values.
@@ -75,6 +78,12 @@ __device__ inline bf16x8 as_bf16x8(uint4 v) {
 __device__ inline unsigned short f32_to_bf16_bits(float x) {
   __bf16 h = (__bf16)x;
   return __builtin_bit_cast(unsigned short, h);
+}
+
+// Two values rounded to bf16 in one word, x in the low half (one instruction).
+__device__ inline unsigned pack2(float x, float y) {
+  const bf16x2 r = {(__bf16)x, (__bf16)y};
+  return __builtin_bit_cast(unsigned, r);
 }
 
 }  // namespace mate

@@ -170,6 +170,22 @@ __device__ inline void tile_source(const UnitPlan& u, const int* global_idx, int
   else { list = u.str_list; base = u.s_lo + (t - u.n_t0) * BN; last = u.s_hi - 1; }
 }
 
+// A unit of at most 64 rows has work for two wavefronts; the other two take half of it: wavefronts w and
+// w + 2 own the same 32 rows, w meets the first 32 rows of every streamed tile and w + 2 the last 32, and the
+// two results are added (through LDS) before anything is stored.  Most question-token owners are such units,
+// and they are the longest chain of tiles of a small launch.
+struct OwnerSplit {
+  bool on;
+  int block;  // the wavefront's 32-row block of owned rows
+  int half;   // and of streamed rows
+  __device__ inline OwnerSplit(const UnitPlan& u, int wave)
+      : on(u.own_count - u.t0 <= BM / 2), block(on ? wave & 1 : wave), half(wave >> 1) {}
+  __device__ inline bool writes(int wave) const { return !on || wave < 2; }
+  // [first, end): the part of the slots [lo, hi) met in the tile that begins at slot `base`
+  __device__ inline int first(int base, int lo) const { return on ? max(lo, base + 32 * half) : lo; }
+  __device__ inline int end(int base, int hi) const { return on ? min(hi, base + 32 * half + 32) : hi; }
+};
+
 // Per-lane view of the owned row: position, and the streamed-slot window it may meet.
 struct OwnedRow {
   int stage_tok;      // token position of owned row threadIdx.x (-1 past the end or past row 127):
@@ -217,8 +233,8 @@ __device__ __forceinline__ void stage_rows(const f32x16& a, float mul, char* sta
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
     uint2 w;
-    w.x = f32_to_bf16_bits(a[4 * g] * mul) | ((unsigned)f32_to_bf16_bits(a[4 * g + 1] * mul) << 16);
-    w.y = f32_to_bf16_bits(a[4 * g + 2] * mul) | ((unsigned)f32_to_bf16_bits(a[4 * g + 3] * mul) << 16);
+    w.x = pack2(a[4 * g] * mul, a[4 * g + 1] * mul);
+    w.y = pack2(a[4 * g + 2] * mul, a[4 * g + 3] * mul);
     *reinterpret_cast<uint2*>(stage + wrow * 128 + (((4 * db + g) ^ (wrow & 7)) << 4) + 8 * hl) = w;
   }
 }
@@ -279,6 +295,26 @@ __device__ __forceinline__ void store_partial(const f32x16 acc[2], float mul, fl
 #pragma unroll
     for (int i = 0; i < 8; ++i)
       put_pair<kShared>(part + (2 * wave + db) * kItemFloats + (i * 64 + lane) * 2, acc[db][2 * i] * mul, acc[db][2 * i + 1] * mul);
+}
+// The same registers through LDS (kItems blocks of kItemFloats floats at p): acc = own acc + other p.
+template <int kItems>
+__device__ __forceinline__ void put_items(char* p, const f32x16 (&acc)[kItems], int lane) {
+#pragma unroll
+  for (int x = 0; x < kItems; ++x)
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      *reinterpret_cast<float2*>(p + ((x * 8 + i) * 64 + lane) * 8) = make_float2(acc[x][2 * i], acc[x][2 * i + 1]);
+}
+template <int kItems>
+__device__ __forceinline__ void add_items(const char* p, f32x16 (&acc)[kItems], float own, float other, int lane) {
+#pragma unroll
+  for (int x = 0; x < kItems; ++x)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float2 v = *reinterpret_cast<const float2*>(p + ((x * 8 + i) * 64 + lane) * 8);
+      acc[x][2 * i] = fmaf(v.x, other, acc[x][2 * i] * own);
+      acc[x][2 * i + 1] = fmaf(v.y, other, acc[x][2 * i + 1] * own);
+    }
 }
 // kBatch chunks of one item with all loads issued before the first use (the pin: left alone, the
 // compiler keeps only a few in flight and the merge becomes a chain of memory round trips).

@@ -3,11 +3,11 @@
 // one softmax, weighted sum; and its derivative), only the rule that says which (owned row,
 // streamed row) pairs belong to the attention pattern differs.  That rule is the Mask argument:
 //
-//   mask.full          wave-uniform: every pair of this tile belongs to the pattern (no masking)
+//   mask.full(blk)     wave-uniform: every pair of the 32-row block blk belongs to the pattern (no masking)
 //   mask.skip(blk)     wave-uniform: no pair of the 32-row block blk belongs to the pattern
-//   mask.load(blk)     fetch what in() needs for the 32-row block blk of the tile
-//   mask.in(blk, c)    does the pair (this lane's owned row, streamed row c_row(c) of block blk)
-//                      belong to the pattern?  c = accumulator register 0..15
+//   mask.load(blk)     fetch what keep() needs for the 32-row block blk of the tile
+//   mask.keep(c, x, o) x if the pair (this lane's owned row, streamed row c_row(c) of the loaded
+//                      block) belongs to the pattern, else o.  c = accumulator register 0..15
 //
 // Layout everywhere: C tiles have rows = streamed rows, columns = the wavefront's 32 owned rows
 // (lane m = owned row, lane half hl), so per-owned-row quantities are per-lane scalars.
@@ -34,83 +34,170 @@ __device__ __forceinline__ void operand_offsets(int lane, int (&poff)[4], int (&
 
 // Segment path: the owned row meets the streamed sorted slots [lo, hi); the tile's first row is
 // slot `base`.  (For the question-token part of a stream lo = 0, hi = G.)
+//
+// The window of a block is one word of bits per lane, and a pair costs a bit-field extract (0 or -1) and
+// a bitwise select: no compare, whose result would travel through a scalar register pair (with the wait
+// that takes between two vector instructions).  Add, compare and select per pair before: see fwd_tile.
 struct WindowMask {
-  const bool full;
   const int d0;        // base + 4 hl - lo
-  const unsigned len;  // hi - lo
-  const int skip_lo, skip_hi;  // wave-uniform: block blk is outside every row's window iff
-                               // 32 blk >= skip_hi or 32 blk + 32 <= skip_lo
-  // [u_lo, u_hi) = union of the windows of the wavefront's rows, in the same slot numbering as base
-  __device__ __forceinline__ WindowMask(bool full_, int base, int hl, int lo, int hi, int u_lo, int u_hi)
-      : full(full_), d0(base + 4 * hl - lo), len((unsigned)(hi - lo)), skip_lo(u_lo - base),
-        skip_hi(u_hi - base) {}
-  __device__ __forceinline__ bool skip(int blk) const { return 32 * blk >= skip_hi || 32 * blk + 32 <= skip_lo; }
-  __device__ __forceinline__ void load(int) const {}
+  const int len;       // hi - lo
+  const int u_lo, u_hi, a_lo, a_hi;  // wave-uniform, relative to base: union and intersection of the rows' windows
+  int one = 1;         // width of the extract; its value is hidden from the compiler, which would turn extract
+                       // and select into test, compare and conditional move
+  unsigned bits = 0;   // bit 8 (c >> 2) + (c & 3): register c of the loaded block is inside
+  // [u0, u1) = union, [a0, a1) = intersection of the windows of the wavefront's rows, in the same slot
+  // numbering as base
+  __device__ __forceinline__ WindowMask(int base, int hl, int lo, int hi, int u0, int u1, int a0, int a1)
+      : d0(base + 4 * hl - lo), len(hi - lo), u_lo(u0 - base), u_hi(u1 - base), a_lo(a0 - base), a_hi(a1 - base) {
+    asm("" : "+s"(one));
+  }
+  __device__ __forceinline__ bool full(int blk) const { return 32 * blk >= a_lo && 32 * blk + 32 <= a_hi; }
+  __device__ __forceinline__ bool skip(int blk) const { return 32 * blk >= u_hi || 32 * blk + 32 <= u_lo; }
+  __device__ __forceinline__ void load(int blk) {
+    // (31 of 32 bits are enough: the highest one asked for is 27)
+    const int first = min(max(-d0 - 32 * blk, 0), 31), end = min(max(len - d0 - 32 * blk, 0), 31);
+    bits = ((1u << end) - 1u) & ~((1u << first) - 1u);
+  }
+  // (the fp32 kernels, which the matrix pipe bounds and whose registers are full, compare)
   __device__ __forceinline__ bool in(int blk, int c) const {
-    return (unsigned)(d0 + blk * 32 + 8 * (c >> 2) + (c & 3)) < len;
+    return (unsigned)(d0 + blk * 32 + 8 * (c >> 2) + (c & 3)) < (unsigned)len;
+  }
+  __device__ __forceinline__ float keep(int c, float x, float other) const {
+    const unsigned in = (unsigned)__builtin_amdgcn_sbfe((int)bits, 8 * (c >> 2) + (c & 3), one);
+    return __uint_as_float((__float_as_uint(x) & in) | (__float_as_uint(other) & ~in));
   }
 };
 
-// Forward: S^T = K Q^T, mask, online softmax in base 2 (running maximum m_run of the raw scores,
-// this lane half's share l_run of the row sum, rescaled only when some row's maximum has risen
-// by more than `lazy` raw-score units), P rounded to bf16, O^T += V^T P^T.
-template <class Mask>
-__device__ __forceinline__ void fwd_tile(const char* Kst, const char* Vst, const bf16x8 (&qf)[4],
-                                         const int (&koff)[4], const int (&voff)[2][2], float sc,
-                                         float lazy, Mask&& mask, f32x16 (&o_acc)[2], float& m_run,
-                                         float& l_run) {
-  // S^T = K Q^T : rows = keys of the tile, columns = this wave's queries.  (Both 32-key blocks
-  // are always computed here: skipping invisible blocks, as the backward bodies do, made this
-  // one slower -- the two blocks' instruction streams no longer interleave.)
-  f32x16 s[2] = {zero16(), zero16()};
+// Forward: S^T = K Q^T, mask, online softmax in base 2 (reference score m_run of the raw scores, this lane
+// half's share l_run of the row sum), P rounded to bf16, O^T += V^T P^T.
+//
+// Softmax needs a reference near the row's maximum, not the maximum: any other changes neither the
+// relative rounding of P in bf16 nor the accuracy of the fp32 sums, as long as nothing overflows.  So
+// only a tile that finds a row without a reference takes the maximum of its scores (and rescales what
+// was summed so far); the others use the reference as it is and look at the sum of the tile's
+// probabilities afterwards.  If one exceeds 2^13 (one score more than 8 to 13 bits above the reference),
+// or is not finite, the tile starts again and takes the maximum.
+// Vector and matrix instructions of the resident wavefronts mostly take turns here, and under full load the
+// chip lowers its clock (2.4 to 1.95 GHz), so every instruction left out counts: without the 16 three-operand
+// maxima and the rescaling decision per tile, with two instructions per masked pair instead of three and a wait,
+// and with single blocks, B = 2, N = 8192, H = 16 takes 54 instead of 57 us, B = 8, N = 2048 49 instead of 53.
+constexpr float kMaxTileSum = 8192.f;
+// A tile of which only one 32-key block is visible is done with that block alone (kBlocks = 1); branching
+// around the blocks inside one body would cost the interleaving of their instruction streams.
+//
+// S^T = K Q^T of kBlocks 32-key blocks from block blk0 on: rows = keys, columns = this wave's queries; -inf
+// outside the pattern.
+template <int kBlocks, class Mask>
+__device__ __forceinline__ void fwd_scores(int blk0, const char* Kst, const bf16x8 (&qf)[4], const int (&koff)[4],
+                                           Mask& mask, f32x16 (&s)[kBlocks]) {
 #pragma unroll
-  for (int jb = 0; jb < 2; ++jb)
+  for (int jb = 0; jb < kBlocks; ++jb) {
+    s[jb] = zero16();
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-      s[jb] = mfma(read_plain(Kst + jb * 32 * 128, koff[ks]), qf[ks], s[jb]);
-  if (!mask.full) {  // wave-uniform: some (query, key) pairs of this tile are outside the pattern
+    for (int ks = 0; ks < 4; ++ks) s[jb] = mfma(read_plain(Kst + jb * 32 * 128, koff[ks]), qf[ks], s[jb]);
+  }
+  if constexpr (kBlocks == 2) {  // six of the eight operands ahead: all eight do not fit the registers
+    __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
+  }
+  // wave-uniform: some (query, key) pairs are outside the pattern
+  if (!(mask.full(blk0) && mask.full(blk0 + kBlocks - 1))) {
 #pragma unroll
-    for (int jb = 0; jb < 2; ++jb) {
-      mask.load(jb);
+    for (int jb = 0; jb < kBlocks; ++jb) {
+      mask.load(blk0 + jb);
 #pragma unroll
-      for (int c = 0; c < 16; ++c) s[jb][c] = mask.in(jb, c) ? s[jb][c] : -INFINITY;
+      for (int c = 0; c < 16; ++c) s[jb][c] = mask.keep(c, s[jb][c], -INFINITY);
     }
   }
+}
+// P^T = exp2(S^T sc - msc), rounded to bf16; returns the sum of the rounded values
+template <int kBlocks>
+__device__ __forceinline__ float fwd_probs(f32x16 (&s)[kBlocks], float sc, float msc, bf16x8 (&pb)[2][2]) {
+  float l[kBlocks];
+#pragma unroll
+  for (int jb = 0; jb < kBlocks; ++jb) {
+    l[jb] = 0.f;
+#pragma unroll
+    for (int c = 0; c < 16; ++c) s[jb][c] = __builtin_amdgcn_exp2f(fmaf(s[jb][c], sc, -msc));
+#pragma unroll
+    for (int tt = 0; tt < 2; ++tt) {
+      pb[jb][tt] = pack8(s[jb], 8 * tt);
+      l[jb] = sum8(pb[jb][tt], l[jb]);
+    }
+  }
+  return kBlocks == 2 ? l[0] + l[kBlocks - 1] : l[0];
+}
+template <int kBlocks, class Mask>
+__device__ __forceinline__ float fwd_probs_new_max(int blk0, const char* Kst, const bf16x8 (&qf)[4],
+                                                   const int (&koff)[4], Mask& mask, float sc, float& m_run,
+                                                   bf16x8 (&pb)[2][2]) {
+  f32x16 s[kBlocks];
+  fwd_scores<kBlocks>(blk0, Kst, qf, koff, mask, s);
   float mx = s[0][0];
 #pragma unroll
-  for (int c = 1; c < 16; c += 2) mx = fmaxf(fmaxf(mx, s[0][c]), s[0][c + 1 < 16 ? c + 1 : 0]);
+  for (int jb = 0; jb < kBlocks; ++jb)
 #pragma unroll
-  for (int c = 0; c < 16; c += 2) mx = fmaxf(fmaxf(mx, s[1][c]), s[1][c + 1]);
-  mx = half_max(mx);
-  // Rescale only when some row's maximum has moved up by more than `lazy`.  Until then
-  // probabilities may exceed 1 by that factor, which changes neither their relative rounding in
-  // bf16 nor the fp32 sums' accuracy.
-  if (__any(mx > m_run + lazy)) {
-    const float m_new = fmaxf(m_run, mx);
-    const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m_run - m_new) * sc);
+    for (int c = 0; c < 16; c += 2) mx = fmaxf(fmaxf(mx, s[jb][c]), s[jb][c + 1]);
+  m_run = fmaxf(m_run, half_max(mx));
+  return fwd_probs<kBlocks>(s, sc, (m_run == -INFINITY ? 0.f : m_run) * sc, pb);
+}
+template <class Mask>
+__device__ __forceinline__ void fwd_tile(const char* Kst, const char* Vst, const bf16x8 (&qf)[4],
+                                         const int (&koff_)[4], const int (&voff_)[2][2], float sc, Mask&& mask,
+                                         f32x16 (&o_acc)[2], float& m_run, float& l_run) {
+  if (mask.skip(0) && mask.skip(1)) return;
+  const bool both = !mask.skip(0) && !mask.skip(1);
+  const int blk0 = mask.skip(0) ? 1 : 0;
+  Kst += blk0 * 32 * 128;
+  Vst += blk0 * 32 * 128;
+  // (the other offsets are computed from these per tile: kept, they would be spilled)
+  int koff[4] = {koff_[0]}, voff[2][2] = {{voff_[0][0], voff_[0][1]}};
+  asm volatile("" : "+v"(koff[0]), "+v"(voff[0][0]), "+v"(voff[0][1]));
+  voff[1][0] = voff[0][0] ^ 64;
+  voff[1][1] = voff[0][1] ^ 64;
+#pragma unroll
+  for (int ks = 1; ks < 4; ++ks) koff[ks] = koff[0] ^ (ks << 5);
+  bf16x8 pb[2][2];
+  float l_tile;
+  bool take_max = __any(m_run == -INFINITY);
+  if (!take_max) {
+    if (both) {
+      f32x16 s[2];
+      fwd_scores<2>(0, Kst, qf, koff, mask, s);
+      l_tile = fwd_probs<2>(s, sc, m_run * sc, pb);
+    } else {
+      f32x16 s[1];
+      fwd_scores<1>(blk0, Kst, qf, koff, mask, s);
+      l_tile = fwd_probs<1>(s, sc, m_run * sc, pb);
+    }
+    take_max = !__all(l_tile <= kMaxTileSum);
+  }
+  if (take_max) {
+    const float m_old = m_run;
+    l_tile = both ? fwd_probs_new_max<2>(0, Kst, qf, koff, mask, sc, m_run, pb)
+                  : fwd_probs_new_max<1>(blk0, Kst, qf, koff, mask, sc, m_run, pb);
+    const float alpha = m_run == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m_old - m_run) * sc);
     l_run *= alpha;
 #pragma unroll
     for (int db = 0; db < 2; ++db)
 #pragma unroll
       for (int c = 0; c < 16; ++c) o_acc[db][c] *= alpha;
-    m_run = m_new;
   }
-  const float msc = m_run == -INFINITY ? 0.f : m_run * sc;
-  // P^T = exp2(S^T sc - m sc), rounded to bf16;  O^T += V^T P^T;  l += sum of rounded P
-#pragma unroll
-  for (int jb = 0; jb < 2; ++jb) {
-#pragma unroll
-    for (int c = 0; c < 16; ++c) s[jb][c] = __builtin_amdgcn_exp2f(fmaf(s[jb][c], sc, -msc));
+  l_run += l_tile;
+  // O^T += V^T P^T
+  auto add = [&](int jb) {
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {
-      const bf16x8 pb = pack8(s[jb], 8 * tt);
-      l_run = sum8(pb, l_run);
       const char* vt = Vst + (jb * 32 + tt * 16) * 128;
 #pragma unroll
       for (int db = 0; db < 2; ++db)
-        o_acc[db] = mfma(read_transposed(vt, voff[db][0], voff[db][1]), pb, o_acc[db]);
+        o_acc[db] = mfma(read_transposed(vt, voff[db][0], voff[db][1]), pb[jb][tt], o_acc[db]);
     }
-  }
+  };
+  add(0);
+  if (both) add(1);
 }
 
 // dQ: P = exp2(S sc - lse2), dP^T = V dO^T, dS = P (dP - delta), dQ^T += K^T dS^T; one 32-key block
@@ -132,10 +219,10 @@ __device__ __forceinline__ void dq_tile(const char* Kst, const char* Vst, const 
 #pragma unroll
     for (int c = 0; c < 16; ++c)
       s[c] = __builtin_amdgcn_exp2f(fmaf(s[c], sc, -lse2)) * (dp[c] - delta);
-    if (!mask.full) {  // wave-uniform: zero the pairs outside the pattern
+    if (!mask.full(jb)) {  // wave-uniform: zero the pairs outside the pattern
       mask.load(jb);
 #pragma unroll
-      for (int c = 0; c < 16; ++c) s[c] = mask.in(jb, c) ? s[c] : 0.f;
+      for (int c = 0; c < 16; ++c) s[c] = mask.keep(c, s[c], 0.f);
     }
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {
@@ -180,13 +267,12 @@ __device__ __forceinline__ void dkv_tile(const char* Qst, const char* Gst, const
       s[c] = __builtin_amdgcn_exp2f(s[c] * sc);  // P
       dp[c] *= s[c];                             // dS
     }
-    if (!mask.full) {  // wave-uniform: zero the pairs outside the pattern
+    if (!mask.full(ib)) {  // wave-uniform: zero the pairs outside the pattern
       mask.load(ib);
 #pragma unroll
       for (int c = 0; c < 16; ++c) {
-        const bool in = mask.in(ib, c);
-        s[c] = in ? s[c] : 0.f;
-        dp[c] = in ? dp[c] : 0.f;
+        s[c] = mask.keep(c, s[c], 0.f);
+        dp[c] = mask.keep(c, dp[c], 0.f);
       }
     }
 #pragma unroll

@@ -351,3 +351,16 @@ def test_f32_tile_edges(n_global, rows, cols, cell, N):
     st = synth._stack([synth.flatten_table(N, n_global, rows, cols, np.full(rows * cols, cell))])
     q, k, v, do = synth.draw_tensors(np.random.default_rng(N), 1, 2, N, 64, "f32", 4)
     check_workload(synth.Workload(f"f32 edges {N}", "f32", st, np.array([ROW, COL], np.uint8), q, k, v, do, 0.125), True)
+
+
+@pytest.mark.parametrize("rise", [0, 12])
+@pytest.mark.parametrize("n_global,rows,cols,cell,N", [(1, 1, 1, 1, 2), (31, 3, 1, 32, 127), (32, 5, 2, 13, 170),
+                                                       (33, 4, 3, 33, 440), (64, 2, 2, 65, 330), (65, 31, 2, 3, 260),
+                                                       (40, 90, 5, 4, 2100), (96, 3, 2, 200, 1300)])
+def test_bf16_tile_edges(n_global, rows, cols, cell, N, rise):
+    """Lists and segments at and beside multiples of the 32-row blocks, units of more and of at most 64 rows;
+    with `rise` (forward only) the scores grow along the sequence: later tiles need a new softmax reference."""
+    st = synth._stack([synth.flatten_table(N, n_global, rows, cols, np.full(rows * cols, cell))])
+    q, k, v, do = synth.draw_tensors(np.random.default_rng(N), 1, 2, N, 64, "bf16", 4)
+    k = synth.round_to_bf16(k * (1 + rise * np.arange(N, dtype=np.float32)[:, None] / N))
+    check_workload(synth.Workload(f"bf16 edges {N}", "bf16", st, np.array([ROW, COL], np.uint8), q, k, v, do, 0.125), rise == 0)
