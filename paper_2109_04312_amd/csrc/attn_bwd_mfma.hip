@@ -299,7 +299,7 @@ __device__ __forceinline__ void merge_dq(const AttnArgs& a, int bh_i, char* stag
   const int h_magic = a.seg.hdr[0], h_B = a.seg.hdr[1], h_N = a.seg.hdr[2];
   const int G = cnt[C_G], L = cnt[C_L];
   if (h_magic != kMagic || h_B != a.B || h_N != a.N) return;
-  const GlobalSplit s = global_split(G, L, a.N);
+  const GlobalSplit s = global_split(G, L, a.B, a.N);
   if (s.n_chunks <= 1) return;
   unsigned short* const out[1] = {static_cast<unsigned short*>(a.dq) + (size_t)bh_i * a.N * kD};
   for (int gt = 0; gt < s.n_gt; ++gt) {
@@ -338,7 +338,7 @@ hipError_t launch_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   ProfileScope prof(4, stream);
-  const int n_merge = may_chunk(a.N) ? 8 * ((a.B * a.H + 7) / 8) : 0;
+  const int n_merge = may_chunk(a.B, a.N) ? 8 * ((a.B * a.H + 7) / 8) : 0;
   hipLaunchKernelGGL(bwd_dkv_mfma_kernel, dim3(grid.x + n_merge), block, 0, stream, a, n_merge);
   return hipGetLastError();
 }

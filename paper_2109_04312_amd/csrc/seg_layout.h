@@ -29,8 +29,8 @@
 // of a long segment (it would stream both segments' windows with half of its wavefronts idle
 // on each, and be the longest unit of the launch).  If that needs more records than there
 // are, the sorted order is cut every 128 slots regardless of segments.
-// The streamed side of question-token owners is the whole sequence; it is cut into chunks of at
-// least kMinChunkTiles tiles, one unit each, that leave partial results for the last one to merge.
+// The streamed side of question-token owners is the whole sequence; it is cut into chunks (see
+// chunk_tiles), one unit each, that leave partial results for the last one to merge.
 #pragma once
 #include <stddef.h>
 #include <stdint.h>
@@ -48,7 +48,8 @@ constexpr int kUnitWords = 8;
 constexpr int kBigSegment = 128;   // a segment this long starts a unit of its own
 constexpr int BM = kTileSlots;     // owned rows per workgroup (32 per wavefront)
 constexpr int BN = 64;             // streamed rows per tile
-constexpr int kMinChunkTiles = 16; // streamed tiles per chunk of a question-token owner
+constexpr int kChunkTiles = 16;    // streamed tiles per chunk of a question-token owner (see chunk_tiles)
+constexpr int kSmallBatch = 4096;  // B N up to which a launch leaves much of the chip idle
 enum { UNIT_NONE = 0, UNIT_GLOBAL = 1, UNIT_LOCAL = 2, UNIT_PAD = 3 };
 
 __host__ __device__ inline int owner_slots(int N) { return (N + BM - 1) / BM; }  // T
@@ -62,11 +63,22 @@ struct GlobalSplit {
   int n_chunks;  // units per owner tile (>= 1); partial results are used iff n_chunks > 1
   int per;       // streamed tiles per chunk
 };
-__host__ __device__ inline GlobalSplit global_split(int G, int L, int N) {
+// Tiles per chunk of a stream of n_st tiles, about.  In a launch that fills the chip a chunk is as long as the
+// column-head units beside it, and more chunks only mean more partial results.  In a small one the
+// question-token owners are the longest chain of tiles (about 0.75 us each) and shorter chunks shorten it;
+// merging costs 4 us and another microsecond and a half per four chunks, so short streams stay whole and
+// three or four chunks are best.  Measured with 6, 8 and 16, forward and training step of 12 heads: B N =
+// 1024 18.8/44, 20.8/49, 22.2/58 us; 1 x 2048 24.8/58, 23.0/55, 28.3/70; 4 x 1024 23/58, 25/60, 24/66;
+// 1 x 4096 31/85, 31/84, 33/86; 1 x 8192 77/192, 76/189, 70/175; 8 x 2048 51/155, 49/152, 44/144.
+__host__ __device__ inline int chunk_tiles(int n_st, int B, int N) {
+  if ((long)B * N > kSmallBatch) return kChunkTiles;
+  return n_st < 12 ? 12 : n_st <= 24 ? 6 : 8;
+}
+__host__ __device__ inline GlobalSplit global_split(int G, int L, int B, int N) {
   GlobalSplit s;
   s.n_gt = (G + BM - 1) / BM;
   s.n_st = (G + BN - 1) / BN + (L + BN - 1) / BN;
-  const int want = (s.n_st + kMinChunkTiles - 1) / kMinChunkTiles;
+  const int tiles = chunk_tiles(s.n_st, B, N), want = (s.n_st + tiles - 1) / tiles;
   const int cap = s.n_gt ? owner_slots(N) / s.n_gt : 1;
   const int n = want < cap ? (want > 1 ? want : 1) : (cap > 1 ? cap : 1);
   s.per = (s.n_st + n - 1) / n;
@@ -76,7 +88,10 @@ __host__ __device__ inline GlobalSplit global_split(int G, int L, int N) {
 
 // Can any sequence of N positions have more than one chunk?  (Host-side bound: at most N tokens in two
 // lists of 64-row tiles, so never more than (N - 2) / 64 + 2 tiles.)
-inline bool may_chunk(int N) { return (N - 2) / BN + 2 > kMinChunkTiles; }
+inline bool may_chunk(int B, int N) {
+  const int most = (N - 2) / BN + 2;
+  return most > chunk_tiles(most, B, N);
+}
 
 __host__ __device__ inline size_t align4(size_t w) { return (w + 3) & ~size_t(3); }
 

@@ -420,7 +420,7 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
     static_assert(kMaxTiles <= kSegThreads - (int)kBins, "a thread per record");
     if (view == 0 && tid >= (int)kBins && tid - (int)kBins < lay.tiles) {
       const int rec = tid - (int)kBins;
-      const GlobalSplit gs = global_split(G, L, N);
+      const GlobalSplit gs = global_split(G, L, B, N);
       int4 q0 = make_int4(UNIT_NONE, 0, 0, 0), q1 = make_int4(0, 0, -1, 0);
       if (rec < gs.n_gt * gs.n_chunks) {
         const int gt = rec / gs.n_chunks, c = rec % gs.n_chunks;
@@ -734,7 +734,7 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
   }
   // question-token owners (the same for both views; written by the row view's workgroup)
   if (view == 0 && tid < lay.tiles) {
-    const GlobalSplit gs = global_split(G, L, N);
+    const GlobalSplit gs = global_split(G, L, B, N);
     int4 r0 = make_int4(UNIT_NONE, 0, 0, 0), r1 = make_int4(0, 0, -1, 0);
     if (tid < gs.n_gt * gs.n_chunks) {
       const int gt = tid / gs.n_chunks, c = tid % gs.n_chunks;
