@@ -44,17 +44,35 @@ __device__ inline const char* uniform_ptr(const void* p) {
   return reinterpret_cast<const char*>(((unsigned long long)hi << 32) | lo);
 }
 
-// Workgroup shape: kA x 64 rows of operand A by kB x 64 rows of operand B, kWA x kWB wavefronts.
-template <int kA_, int kB_, int kWA_, int kWB_, int kStages_, int kPerCU_>
+// Workgroup shape: kA x 64 rows of operand A by kB x 64 rows of operand B, kWA x kWB wavefronts; kGroups such
+// sets of wavefronts share the contraction (stage k belongs to group k mod kGroups, each group has its own
+// ring of stages) and add their accumulators at the end.
+//
+// Two groups are for products with so few tiles that a CU has one: alone, four wavefronts read LDS and
+// multiply in turns (0.6 us a stage of 128 x 128 where the matrix pipe needs 0.2), and two workgroups on a
+// CU drift apart so that one reads while the other multiplies.  Two groups of one workgroup would read at the
+// same time, because every stage has a barrier; so they are kept half a stage apart (kAlternate): a second
+// barrier between reading and multiplying, and group 1 one barrier behind.  dX at 8 x 512 tokens and 768
+// wide 26.4 -> 21.8 us, its weight gradient 35.3 -> 32.9, that of the output projection 29.2 -> 24.6; in
+// step they gained 0 to 2.  (The 128 x 64 shape with its shorter stages, three of them, is better in step.)
+//
+// Eight wavefronts on one tile (256 x 256) are kept apart in the same way, the upper four half a slice behind
+// the lower four, where the weights' products use them: 1024 -> 3072 features at 2 x 8192 tokens 97.5 -> 93.0
+// us, 3072 -> 1024 81.7 -> 78.5.  In the weight gradient, whose operands are both read through the slower
+// transposing reads, the reads of one half outlast the products of the other: 111 -> 117 us, so not there.
+template <int kA_, int kB_, int kWA_, int kWB_, int kStages_, int kPerCU_, int kGroups_ = 1>
 struct Shape {
-  static constexpr int kA = kA_, kB = kB_, kWA = kWA_, kWB = kWB_, kStages = kStages_, kPerCU = kPerCU_;
-  static constexpr int kWaves = kWA * kWB, kThreads = 64 * kWaves;
+  static constexpr int kA = kA_, kB = kB_, kWA = kWA_, kWB = kWB_, kStages = kStages_, kPerCU = kPerCU_, kGroups = kGroups_;
+  static constexpr int kWaves = kWA * kWB, kAllWaves = kWaves * kGroups, kThreads = 64 * kAllWaves;
   static constexpr int kRowsA = 64 * kA, kRowsB = 64 * kB;
   static constexpr int kFA = 4 * kA / kWA, kFB = 4 * kB / kWB;  // 16-row blocks of a wavefront
-  static constexpr int kStageBytes = (kA + kB) * kTileBytes, kLds = kStages * kStageBytes;
+  static constexpr int kOutB = kFB / kGroups;                   // and those of B that it stores
+  static constexpr bool kAlternate = kGroups == 2 && kStages == 2;
+  static constexpr int kStageBytes = (kA + kB) * kTileBytes, kRingBytes = kStages * kStageBytes, kLds = kGroups * kRingBytes;
   static constexpr int kLoadsA = 8 * kA / kWaves, kLoadsB = 8 * kB / kWaves, kLoads = kLoadsA + kLoadsB;
   static_assert(8 * kA % kWaves == 0 && 8 * kB % kWaves == 0, "loads must divide evenly");
-  static_assert(4 * kA % kWA == 0 && 4 * kB % kWB == 0 && kFA % 2 == 0, "blocks must divide evenly");
+  static_assert(4 * kA % kWA == 0 && 4 * kB % kWB == 0 && kFA % 2 == 0 && kFB % kGroups == 0, "blocks must divide evenly");
+  static_assert(kGroups == 1 || kGroups == 2, "the exchange is between two groups");
 };
 
 // Load instruction i of a wavefront brings eight rows of one tile: which tile, which row this lane's
@@ -108,9 +126,10 @@ __device__ __forceinline__ bf16x8 read_frag(const char* tiles, const FragOffsets
 }
 
 // One stage (64 of k): two slices of 32.
-template <class S, bool kTA, bool kTB, class PerSlice>
+// kHalves: `next_landed` is called where this wavefront's share of the next stage must have landed.
+template <class S, bool kTA, bool kTB, bool kHalves, class PerSlice, class Next>
 __device__ __forceinline__ void contract_stage(const char* stage, const FragOffsets& fa, const FragOffsets& fb, int wa,
-                                               int wb, f32x4 (&acc)[S::kFA][S::kFB], PerSlice&& per_slice) {
+                                               int wb, f32x4 (&acc)[S::kFA][S::kFB], PerSlice&& per_slice, Next&& next_landed) {
   const char* ta = stage + (kTA ? 0 : wa * S::kFA * 16 * 128);
   const char* tb = stage + S::kA * kTileBytes + (kTB ? 0 : wb * S::kFB * 16 * 128);
   bf16x8 a[2][S::kFA], b[2][S::kFB];
@@ -120,15 +139,81 @@ __device__ __forceinline__ void contract_stage(const char* stage, const FragOffs
 #pragma unroll
     for (int j = 0; j < S::kFB; ++j) b[k][j] = read_frag<kTB>(tb, fb, (kTB ? wb * S::kFB : 0) + j, k);
   };
+  if constexpr (kHalves) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      if (k) barrier_no_fence();
+      __builtin_amdgcn_sched_barrier(0);
+      read_slice(k);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (k) next_landed();
+      __builtin_amdgcn_sched_barrier(0);
+      barrier_no_fence();  // from here on the other half reads
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int i = 0; i < S::kFA; ++i)
+#pragma unroll
+        for (int j = 0; j < S::kFB; ++j) acc[i][j] = mfma16(a[k][i], b[k][j], acc[i][j]);
+      per_slice(b[k]);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(0);
+    }
+    return;
+  }
   read_slice(0);
+  if constexpr (S::kAlternate) {
+    read_slice(1);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    barrier_no_fence();  // from here on the other group reads
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+  }
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
-    if (k == 0) read_slice(1);  // the second slice travels while the first is contracted
+    if (k == 0 && !S::kAlternate) read_slice(1);  // the second slice travels while the first is contracted
 #pragma unroll
     for (int i = 0; i < S::kFA; ++i)
 #pragma unroll
       for (int j = 0; j < S::kFB; ++j) acc[i][j] = mfma16(a[k][i], b[k][j], acc[i][j]);
-    per_slice(b[k]);
+    if constexpr (!S::kAlternate) per_slice(b[k]);
+  }
+  if constexpr (S::kAlternate) {
+    per_slice(b[0]);
+    per_slice(b[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(0);
+  }
+}
+// The two groups' accumulators: each wavefront gives half of its blocks of B to its counterpart in the
+// other group, through LDS, and keeps the sum of the other half.  (Group 0 stores blocks 0 .. kOutB - 1.)
+template <class S>
+__device__ __forceinline__ void add_groups(f32x4 (&acc)[S::kFA][S::kFB], f32x4 (&out)[S::kFA][S::kOutB], char* lds, int group,
+                                           int wave, int lane) {
+  if constexpr (S::kGroups == 1) {
+#pragma unroll
+    for (int i = 0; i < S::kFA; ++i)
+#pragma unroll
+      for (int j = 0; j < S::kOutB; ++j) out[i][j] = acc[i][j];
+  } else {
+    constexpr int kBlocks = S::kFA * S::kOutB;
+    static_assert(2 * S::kWaves * kBlocks * 1024 <= S::kLds, "the exchange must fit the stages");
+    f32x4* x = reinterpret_cast<f32x4*>(lds) + lane;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < S::kFA; ++i)
+#pragma unroll
+      for (int j = 0; j < S::kOutB; ++j)
+        x[((group * S::kWaves + wave) * kBlocks + i * S::kOutB + j) * 64] = group ? acc[i][j] : acc[i][j + S::kOutB];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < S::kFA; ++i)
+#pragma unroll
+      for (int j = 0; j < S::kOutB; ++j) {
+        const f32x4 other = x[(((1 - group) * S::kWaves + wave) * kBlocks + i * S::kOutB + j) * 64];
+        out[i][j] = group ? other + acc[i][j + S::kOutB] : acc[i][j] + other;
+      }
   }
 }
 
@@ -187,12 +272,14 @@ struct ProjArgs {
 // kHeadTok: the token operand comes from head-layout tensors and the output is flat; else the reverse.
 // kTransposedW: the weight operand is read transposed.
 template <class S, bool kHeadTok, bool kTransposedW>
-__global__ __launch_bounds__(S::kThreads, S::kWaves / 4 * S::kPerCU) void proj_kernel(ProjArgs a) {
+__global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void proj_kernel(ProjArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int group = wave_id / S::kWaves, wave = wave_id - group * S::kWaves;
   const int wa = wave / S::kWB, wb = wave - wa * S::kWB;
   const int r = lane & 15, quarter = lane >> 4;
+  char* const ring = lds + group * S::kRingBytes;
 
   if ((int)blockIdx.x >= a.tile_blocks) {  // behind the tiles: partial sums of a weight gradient
     add_ranges(a.ranges, blockIdx.x - a.tile_blocks, S::kThreads);
@@ -222,29 +309,31 @@ __global__ __launch_bounds__(S::kThreads, S::kWaves / 4 * S::kPerCU) void proj_k
     const LoadUnit l = load_unit<S::kWaves>(wave, lane, i);
     off[S::kLoadsA + i] = (unsigned)min(64 * l.tile + l.row, rows - 1) * (kHeadTok ? kD * 2u : (unsigned)a.K * 2) + l.chunk * 16;
   }
-  const char* w_ptr = reinterpret_cast<const char*>(kTransposedW ? a.w + f0 : a.w + (size_t)f0 * a.K);  // of the next stage
   const size_t w_step = kTransposedW ? (size_t)64 * a.F * 2 : 128;
+  const char* w_ptr = reinterpret_cast<const char*>(kTransposedW ? a.w + f0 : a.w + (size_t)f0 * a.K) + group * w_step;  // of the next stage
   const size_t head0 = (((size_t)b * a.H) * a.N + n0) * kD * 2, t_step = kHeadTok ? (size_t)a.N * kD * 2 : 128;
   const char* t_ptr = kHeadTok ? reinterpret_cast<const char*>(a.tok3[0]) + head0
                                : reinterpret_cast<const char*>(a.tok + ((size_t)b * a.N + n0) * a.K);
-  int head = 0, tensor = 0;
+  t_ptr += group * t_step;
+  int head = group, tensor = 0;
   auto issue_stage = [&](int g) {
-    char* st = lds + (g % S::kStages) * S::kStageBytes;
+    char* st = ring + (g % S::kStages) * S::kStageBytes;
     const char *w_base = uniform_ptr(w_ptr), *t_base = uniform_ptr(t_ptr);
 #pragma unroll
     for (int i = 0; i < S::kLoadsA; ++i) load_to_lds_16(w_base, off[i], st + load_dst<S::kWaves>(wave, i));
 #pragma unroll
     for (int i = 0; i < S::kLoadsB; ++i)
       load_to_lds_16(t_base, off[S::kLoadsA + i], st + S::kA * kTileBytes + load_dst<S::kWaves>(wave, i));
-    w_ptr += w_step;
-    t_ptr += t_step;
-    if (kHeadTok && ++head == a.H) {  // the next tensor's heads
-      head = 0;
+    w_ptr += S::kGroups * w_step;
+    t_ptr += S::kGroups * t_step;
+    if (kHeadTok && (head += S::kGroups) >= a.H) {  // the next tensor's heads (H is even)
+      head -= a.H;
       ++tensor;
-      t_ptr = reinterpret_cast<const char*>(tensor == 1 ? a.tok3[1] : a.tok3[2]) + head0;
+      t_ptr = reinterpret_cast<const char*>(tensor == 1 ? a.tok3[1] : a.tok3[2]) + head0 + head * t_step;
     }
   };
-  const int nk = a.K / 64;
+  constexpr bool kHalves = S::kGroups == 1 && S::kWaves == 8 && S::kStages == 2;
+  const int nk = a.K / 64 / S::kGroups;  // this group's stages (K is a multiple of 128)
 #pragma unroll
   for (int s = 0; s < S::kStages - 1; ++s)
     if (s < nk) issue_stage(s);
@@ -255,11 +344,12 @@ __global__ __launch_bounds__(S::kThreads, S::kWaves / 4 * S::kPerCU) void proj_k
   bool any = false;
 #pragma unroll
   for (int i = 0; i < S::kB; ++i) any |= fl[min(64 * i + lane, rows - 1)] < 2;
-  int row[S::kFB];
+  const int j0 = wb * S::kFB + group * S::kOutB;  // first block of tokens that this wavefront stores
+  int row[S::kOutB];
   unsigned pad_bits = 0;
 #pragma unroll
-  for (int j = 0; j < S::kFB; ++j) {
-    row[j] = min((wb * S::kFB + j) * 16 + r, rows - 1);
+  for (int j = 0; j < S::kOutB; ++j) {
+    row[j] = min((j0 + j) * 16 + r, rows - 1);
     pad_bits |= (unsigned)(fl[row[j]] >= 2) << j;
   }
   f32x4 bias[S::kFA];
@@ -278,15 +368,22 @@ __global__ __launch_bounds__(S::kThreads, S::kWaves / 4 * S::kPerCU) void proj_k
     FragOffsets fa, fb;
     frag_offsets<kTransposedW>(fa, lane);
     frag_offsets<false>(fb, lane);
+    // the second half, or group, follows one barrier behind
+    const bool apart = kHalves || S::kAlternate, second = kHalves ? wave >= 4 : group == 1;
+    if (kHalves) wait_vmcnt_le<0>(0);
+    if (apart && second) barrier_no_fence();
     for (int ks = 0; ks < nk; ++ks) {
       // stage ks has landed: everything but the younger stages' loads (fewer near the end)
-      wait_vmcnt_le<S::kLoads * (S::kStages - 2)>(min(S::kStages - 2, nk - 1 - ks) * S::kLoads);
+      if (!kHalves) wait_vmcnt_le<S::kLoads * (S::kStages - 2)>(min(S::kStages - 2, nk - 1 - ks) * S::kLoads);
       barrier_no_fence();  // ... for every wavefront, and everyone is done with stage ks - 1
       if (ks + S::kStages - 1 < nk) issue_stage(ks + S::kStages - 1);
-      contract_stage<S, kTransposedW, false>(lds + (ks % S::kStages) * S::kStageBytes, fa, fb, wa, wb, acc,
-                                             [](const bf16x8 (&)[S::kFB]) {});
+      contract_stage<S, kTransposedW, false, kHalves>(ring + (ks % S::kStages) * S::kStageBytes, fa, fb, wa, wb, acc,
+                                                      [](const bf16x8 (&)[S::kFB]) {}, []() { wait_vmcnt_le<0>(0); });
     }
+    if (apart && !second) barrier_no_fence();
   }
+  f32x4 sum[S::kFA][S::kOutB];
+  add_groups<S>(acc, sum, lds, group, wave, lane);
 
   // ---- epilogue: + bias, round to bf16.  A lane holds features 16 i + 4 quarter .. + 3 of token 16 j + r;
   // after exchanging quarters between neighbouring blocks it holds eight consecutive ones and stores
@@ -308,19 +405,19 @@ __global__ __launch_bounds__(S::kThreads, S::kWaves / 4 * S::kPerCU) void proj_k
     }
     dst += (quarter & 1) * 16 + (quarter >> 1) * 8;
 #pragma unroll
-    for (int j = 0; j < S::kFB; ++j) {
+    for (int j = 0; j < S::kOutB; ++j) {
       unsigned u[2][2];
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
-        const f32x4 c = acc[i + p][j] + bias[i + p];
-        u[p][0] = f32_to_bf16_bits(c[0]) | ((unsigned)f32_to_bf16_bits(c[1]) << 16);
-        u[p][1] = f32_to_bf16_bits(c[2]) | ((unsigned)f32_to_bf16_bits(c[3]) << 16);
+        const f32x4 c = sum[i + p][j] + bias[i + p];
+        u[p][0] = pack2(c[0], c[1]);
+        u[p][1] = pack2(c[2], c[3]);
       }
       const auto lo = __builtin_amdgcn_permlane16_swap(u[0][0], u[1][0], false, false);
       const auto hi = __builtin_amdgcn_permlane16_swap(u[0][1], u[1][1], false, false);
       uint4 v = make_uint4(lo[0], hi[0], lo[1], hi[1]);
       if ((pad_bits >> j) & 1u) v = make_uint4(0, 0, 0, 0);
-      if ((wb * S::kFB + j) * 16 + r < rows) *reinterpret_cast<uint4*>(dst + (size_t)row[j] * dst_stride) = v;
+      if ((j0 + j) * 16 + r < rows) *reinterpret_cast<uint4*>(dst + (size_t)row[j] * dst_stride) = v;
     }
   }
 }
@@ -339,33 +436,47 @@ hipError_t launch_proj(ProjArgs a, int kernel_id, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Which shape.  A compute unit that gets n tiles of a shape needs about n (c k / 64 + e) us, with c and e
-// as measured below (256 CUs, 257 to 12288 tokens, widths 768 and 1024, one tile per CU as well as many),
-// so the shape with the smallest product of ceil(tiles / 256) and that wins: large tiles once they fill
-// the chip, smaller ones where they fit its 256 units better.  Measured, us, at 8 x 512 tokens and
-// 768 -> 2304 / 768 -> 768 features: 256 x 256 26 / 24, 192 x 128 21 / 15, 128 x 128 25 / 14, 128 x 64
-// 26 / 11; at 2 x 8192 (12860 not padding) and 1024 -> 3072: 92, 94, 109, 143.
-//                        features x tokens, wavefronts, stages, workgroups per CU
-using Proj256 = Shape<4, 4, 2, 4, 2, 1>;   // 256 x 256
-using Proj192 = Shape<3, 2, 2, 2, 2, 2>;   // 192 x 128  (plain weights; its wavefronts' 96 features are not whole tiles)
-using Proj128 = Shape<2, 2, 2, 2, 2, 2>;   // 128 x 128
-using Proj64 = Shape<2, 1, 2, 2, 3, 2>;    // 128 x  64
+// Which shape.  A compute unit that gets n tiles of a shape needs about (k / 64) (c2 for every two tiles, c1 for
+// an odd last one) + e n us, measured below (256 CUs, 257 to 12288 tokens, widths 768 and 1024, one tile per CU
+// as well as many), so the shape with the smallest such sum for n = ceil(tiles / 256) wins: large tiles once
+// they fill the chip, smaller ones where they fit its 256 units better.  Measured, us, at 8 x 512 tokens and
+// 768 -> 2304, 768 -> 768, 2304 -> 768 (transposed weights) features: 256 x 256 26, 24; 192 x 128 22, 15; 128 x
+// 128 25, 12, 26; with two groups 30, 11, 22; 128 x 64 27, 11, 23, with two groups 36, 15, 32; at 1 x 512 the last
+// four 11.4, 10.6, 24.7; 11.3, 10.3, 20.2; 9.0, 8.4, 18.6; 8.6, 7.8, 16.4; at 2 x 8192 (12860 not padding) and
+// 1024 -> 3072: 92, 94, 109, -, 143.
+//                        features x tokens, wavefronts, stages, workgroups per CU, groups
+using Proj256 = Shape<4, 4, 2, 4, 2, 1>;      // 256 x 256
+using Proj192 = Shape<3, 2, 2, 2, 2, 2>;      // 192 x 128  (plain weights; its wavefronts' 96 features are not whole tiles)
+using Proj128 = Shape<2, 2, 2, 2, 2, 2>;      // 128 x 128
+using Proj128x2 = Shape<2, 2, 2, 2, 2, 1, 2>;
+using Proj64 = Shape<2, 1, 2, 2, 3, 2>;       // 128 x  64
+using Proj64x2 = Shape<2, 1, 2, 2, 3, 1, 2>;
 template <class S>
-double proj_cost(const ProjArgs& a, double c, double e) {
+double proj_cost(const ProjArgs& a, double c1, double c2, double e) {
   const long tiles = (long)a.B * ((a.N + S::kRowsB - 1) / S::kRowsB) * ((a.F + S::kRowsA - 1) / S::kRowsA);
-  return (double)((tiles + 255) / 256) * (c * (a.K / 64) + e);
+  const long n = (tiles + 255) / 256;
+  return (a.K / 64) * ((n / 2) * c2 + (n % 2) * c1) + e * n;
 }
 
 template <bool kHeadTok, bool kTransposedW>
 hipError_t launch_proj_any(const ProjArgs& a, int kernel_id, hipStream_t stream) {
-  const double c256 = proj_cost<Proj256>(a, 1.6, 3.0), c128 = proj_cost<Proj128>(a, 0.52, 1.0), c64 = proj_cost<Proj64>(a, 0.33, 0.6);
-  const double best = std::min({c256, c128, c64});
+  typedef hipError_t (*Launch)(ProjArgs, int, hipStream_t);
+  double best = 1e30;
+  Launch launch = nullptr;
+  auto offer = [&](double cost, Launch l) {
+    if (cost < best) {
+      best = cost;
+      launch = l;
+    }
+  };
+  offer(proj_cost<Proj256>(a, 1.6, 3.2, 3.0), launch_proj<Proj256, kHeadTok, kTransposedW>);
   if constexpr (!kTransposedW)
-    if (a.F % Proj192::kRowsA == 0 && proj_cost<Proj192>(a, 0.75, 1.3) < best)
-      return launch_proj<Proj192, kHeadTok, kTransposedW>(a, kernel_id, stream);
-  if (c256 == best) return launch_proj<Proj256, kHeadTok, kTransposedW>(a, kernel_id, stream);
-  if (c128 == best) return launch_proj<Proj128, kHeadTok, kTransposedW>(a, kernel_id, stream);
-  return launch_proj<Proj64, kHeadTok, kTransposedW>(a, kernel_id, stream);
+    if (a.F % Proj192::kRowsA == 0) offer(proj_cost<Proj192>(a, 1.0, 1.52, 1.3), launch_proj<Proj192, kHeadTok, kTransposedW>);
+  offer(proj_cost<Proj128>(a, 0.6, 1.04, 1.2), launch_proj<Proj128, kHeadTok, kTransposedW>);
+  offer(proj_cost<Proj128x2>(a, 0.44, 1.1, 2.7), launch_proj<Proj128x2, kHeadTok, kTransposedW>);
+  offer(proj_cost<Proj64>(a, 0.44, 0.66, 0.7), launch_proj<Proj64, kHeadTok, kTransposedW>);
+  offer(proj_cost<Proj64x2>(a, 0.39, 0.78, 0.7), launch_proj<Proj64x2, kHeadTok, kTransposedW>);
+  return launch(a, kernel_id, stream);
 }
 
 // ======================================================================================
@@ -423,10 +534,12 @@ __device__ __forceinline__ unsigned long long pad_mask(const unsigned char* flag
 }
 
 template <class S>
-__global__ __launch_bounds__(S::kThreads, S::kWaves / 4 * S::kPerCU) void proj_wgrad_kernel(WgradArgs a) {
+__global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void proj_wgrad_kernel(WgradArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int group = wave_id / S::kWaves, wave = wave_id - group * S::kWaves;
+  char* const ring = lds + group * S::kRingBytes;
   const int e_tiles = (a.E + S::kRowsA - 1) / S::kRowsA, tiles = ((a.F + S::kRowsB - 1) / S::kRowsB) * e_tiles;
   // Workgroup -> (token range, tile): XCD q = blockIdx % 8 takes a contiguous piece of the list
   // ordered by token range first, so the workgroups that stream the same tokens share an L2
@@ -450,18 +563,18 @@ __global__ __launch_bounds__(S::kThreads, S::kWaves / 4 * S::kPerCU) void proj_w
   // contractions need 0.9) ----
   __shared__ unsigned long long live_mask[kMaxRange];
   __shared__ unsigned short live_at[kMaxRange];
-  __shared__ int wave_live[S::kWaves];
+  __shared__ int wave_live[S::kAllWaves];
   int n_live = 0;
   for (int s0 = s_begin; s0 < s_end; s0 += S::kThreads) {  // one block per thread, its 64 flags at once
     const int s = s0 + tid, b = s / a.blocks_per_seq;
     const unsigned long long mask = s < s_end ? pad_mask(a.flags, (size_t)a.B * a.N, (size_t)b * a.N, (s - b * a.blocks_per_seq) * 64, a.N) : ~0ull;
     const unsigned long long ballot = __ballot(mask != ~0ull);
-    if (lane == 0) wave_live[wave] = __popcll(ballot);
+    if (lane == 0) wave_live[wave_id] = __popcll(ballot);
     __syncthreads();
     int at = n_live + __popcll(ballot & ((1ull << lane) - 1));
 #pragma unroll
-    for (int w = 0; w < S::kWaves; ++w) {
-      if (w < wave) at += wave_live[w];
+    for (int w = 0; w < S::kAllWaves; ++w) {
+      if (w < wave_id) at += wave_live[w];
       n_live += wave_live[w];
     }
     if (mask != ~0ull) {
@@ -495,7 +608,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWaves / 4 * S::kPerCU) void proj_w
   }
   auto issue_stage = [&](int s, int slot) {
     const int b = s / a.blocks_per_seq, n0 = (s - b * a.blocks_per_seq) * 64;
-    char* st = lds + slot * S::kStageBytes;
+    char* st = ring + slot * S::kStageBytes;
     const size_t x_at = (size_t)b * x_seq + (size_t)n0 * x_stride, g_at = (size_t)b * g_seq + (size_t)n0 * g_stride;
     const int missing = max(0, n0 + 64 - a.N);
 #pragma unroll
@@ -523,48 +636,73 @@ __global__ __launch_bounds__(S::kThreads, S::kWaves / 4 * S::kPerCU) void proj_w
   FragOffsets fo;
   frag_offsets<true>(fo, lane);
 
+  // this group's blocks: i_begin + group, + kGroups, ...
   auto block_at = [&](int i) { return s_begin + __builtin_amdgcn_readfirstlane((int)live_at[i]); };
 #pragma unroll
   for (int k = 0; k + 1 < S::kStages; ++k)
-    if (i_begin + k < i_end) issue_stage(block_at(i_begin + k), k);
-  for (int i = i_begin, it = 0; i < i_end; ++i, ++it) {
-    const unsigned long long padmask = live_mask[i];
-    const int next = block_at(min(i + S::kStages - 1, i_end - 1));
-    // block i has landed: everything but the loads of the blocks after it that were issued
-    wait_vmcnt_le<S::kLoads * (S::kStages - 2)>(min(S::kStages - 2, i_end - 1 - i) * S::kLoads);
-    barrier_no_fence();          // ... for everyone; and everyone is done with the block before it
-    if (i + S::kStages - 1 < i_end) issue_stage(next, (it + S::kStages - 1) % S::kStages);
-    char* st = lds + (it % S::kStages) * S::kStageBytes;
-    if (padmask) {               // the same for every lane: clear the pad rows of all tiles (0 x anything = 0 then)
-      for (int i = tid; i < 64 * (S::kA + S::kB); i += S::kThreads)
-        if ((padmask >> (i & 63)) & 1ull) {
-          uint4* p = reinterpret_cast<uint4*>(st + (i >> 6) * kTileBytes + (i & 63) * 128);
+    if (i_begin + group + k * S::kGroups < i_end) issue_stage(block_at(i_begin + group + k * S::kGroups), k);
+  // My share of block i has landed: everything but the loads of the blocks after it that were issued.  Its pad
+  // rows are cleared (0 x anything = 0 then).
+  auto land = [&](int i, int it) {
+    wait_vmcnt_le<S::kLoads * (S::kStages - 2)>(max(0, min(S::kStages - 2, (i_end - 1 - i) / S::kGroups)) * S::kLoads);
+    // (an odd last block leaves group 1 a block of padding only)
+    const unsigned long long padmask = S::kGroups == 1 || i < i_end ? live_mask[i] : ~0ull;
+    if (padmask) {
+      char* st = ring + (it % S::kStages) * S::kStageBytes;
 #pragma unroll
-          for (int c = 0; c < 8; ++c) p[c] = make_uint4(0, 0, 0, 0);
-        }
-      __syncthreads();
-    }
-    contract_stage<S, true, true>(st, fo, fo, wa, wb, acc, [&](const bf16x8 (&g)[S::kFB]) {
-      if (do_bias) {
-#pragma unroll
-        for (int j = 0; j < S::kFB; ++j) bias_acc[j] = sum8(g[j], bias_acc[j]);
+      for (int l = 0; l < S::kLoads; ++l) {
+        const int y = l < S::kLoadsA ? l : l - S::kLoadsA;
+        if ((padmask >> load_unit<S::kWaves>(wave, lane, y).row) & 1ull)
+          *reinterpret_cast<uint4*>(st + (l < S::kLoadsA ? 0 : S::kA * kTileBytes) + load_dst<S::kWaves>(wave, y) + lane * 16) =
+              make_uint4(0, 0, 0, 0);
       }
-    });
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+  };
+  if (S::kAlternate && group == 1) barrier_no_fence();  // group 1 follows one barrier behind
+  for (int i0 = i_begin, it = 0; i0 < i_end; i0 += S::kGroups, ++it) {
+    const int i = i0 + group, ahead = i + (S::kStages - 1) * S::kGroups;
+    const int next = block_at(min(ahead, i_end - 1));
+    land(i, it);
+    barrier_no_fence();          // landed for everyone; and everyone is done with the block before it
+    if (ahead < i_end) issue_stage(next, (it + S::kStages - 1) % S::kStages);
+    contract_stage<S, true, true, false>(ring + (it % S::kStages) * S::kStageBytes, fo, fo, wa, wb, acc,
+                                  [&](const bf16x8 (&g)[S::kFB]) {
+                                    if (do_bias) {
+#pragma unroll
+                                      for (int j = 0; j < S::kFB; ++j) bias_acc[j] = sum8(g[j], bias_acc[j]);
+                                    }
+                                  },
+                                  []() {});
   }
+  if (S::kAlternate && group == 0) barrier_no_fence();
+  f32x4 sum[S::kFA][S::kOutB];
+  add_groups<S>(acc, sum, lds, group, wave, lane);
 
   // a lane holds columns 16 i + 4 quarter .. + 3 of row 16 j + r
   const int r = lane & 15, quarter = lane >> 4;
   float* dst = (a.splits > 1 ? a.part + (size_t)split * a.F * a.E : a.out);
 #pragma unroll
-  for (int j = 0; j < S::kFB; ++j) {
-    const int f = f0 + (wb * S::kFB + j) * 16 + r;
+  for (int j = 0; j < S::kOutB; ++j) {
+    const int f = f0 + (wb * S::kFB + group * S::kOutB + j) * 16 + r;
 #pragma unroll
     for (int i = 0; i < S::kFA; ++i) {
       const int e = e0 + (wa * S::kFA + i) * 16 + 4 * quarter;
-      if (f < a.F && e < a.E) *reinterpret_cast<f32x4*>(dst + (size_t)f * a.E + e) = acc[i][j];
+      if (f < a.F && e < a.E) *reinterpret_cast<f32x4*>(dst + (size_t)f * a.E + e) = sum[i][j];
     }
   }
-  if (do_bias) {
+  if (S::kGroups > 1 && a.want_bias && et == 0) {  // the other group's column sums
+    float* x = reinterpret_cast<float*>(lds);
+    __syncthreads();
+    if (do_bias && group)
+#pragma unroll
+      for (int j = 0; j < S::kFB; ++j) x[(wb * S::kFB + j) * 64 + lane] = bias_acc[j];
+    __syncthreads();
+    if (do_bias && !group)
+#pragma unroll
+      for (int j = 0; j < S::kFB; ++j) bias_acc[j] += x[(wb * S::kFB + j) * 64 + lane];
+  }
+  if (do_bias && !group) {
     float* bd = a.splits > 1 ? a.part_bias + (size_t)split * a.F : a.out_bias;
 #pragma unroll
     for (int j = 0; j < S::kFB; ++j) {
@@ -581,8 +719,8 @@ __global__ __launch_bounds__(S::kThreads, S::kWaves / 4 * S::kPerCU) void proj_w
 __global__ __launch_bounds__(256) void add_ranges_kernel(RangeSums s) { add_ranges(s, blockIdx.x, 256); }
 
 //                         columns x rows of dW
-using Wgrad256 = Shape<4, 4, 2, 4, 2, 1>;   // 256 x 256
-using Wgrad128 = Shape<2, 2, 2, 2, 2, 2>;   // 128 x 128
+using Wgrad256 = Shape<4, 4, 2, 4, 2, 1>;      // 256 x 256
+using Wgrad128 = Shape<2, 2, 2, 2, 2, 1, 2>;   // 128 x 128, two groups
 
 size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
 struct WgradPlan {
@@ -596,17 +734,18 @@ WgradPlan plan_wgrad(int B, int N, int F, int E) {
   const int total_blocks = B * p.blocks_per_seq;
   // Large tiles read half as much per contraction, small ones need fewer token ranges to fill the chip, and
   // every range leaves an fp32 partial matrix that is written and read again.  In us, as measured on 768
-  // and 1024 wide layers of 257 to 16384 tokens: 1.9 a token block for 256 x 256 (one workgroup per CU),
-  // 1.2 for 128 x 128 (two), 1 per 5.2 MB of partial sums.  (3072 x 1024 at 4096 tokens: 52 against 54,
-  // at 12288 90 against 125, at 1024 39 against 31.)
+  // and 1024 wide layers of 257 to 16384 tokens, one workgroup per CU: 1.9 a token block for 256 x 256, 0.7 for
+  // 128 x 128 with two groups, 1 per 5.2 MB of partial sums.  (3072 x 1024 at 4096 tokens: 50 against 47,
+  // at 8192 70 against 85, at 1024 37 against 19.)
+  constexpr int kSlots = 256;
   double best = 0;
   for (int tile : {256, 128}) {
-    const int slots = tile == 256 ? 256 : 512, tiles = ((F + tile - 1) / tile) * ((E + tile - 1) / tile);
+    const int tiles = ((F + tile - 1) / tile) * ((E + tile - 1) / tile);
     // enough workgroups for the chip, but ranges of at least eight token blocks
-    const int want = std::max({1, std::min(std::max(1, slots / tiles), total_blocks / 8), (total_blocks + kMaxRange - 1) / kMaxRange});
+    const int want = std::max({1, std::min(std::max(1, kSlots / tiles), total_blocks / 8), (total_blocks + kMaxRange - 1) / kMaxRange});
     const int per = (total_blocks + want - 1) / want, splits = (total_blocks + per - 1) / per;
-    const double rounds = (double)((tiles * splits + slots - 1) / slots);
-    const double cost = rounds * per * (tile == 256 ? 1.9 : 1.2) + (splits > 1 ? splits * 8.0 * F * E / 5.2e6 : 0.0);
+    const double rounds = (double)((tiles * splits + kSlots - 1) / kSlots);
+    const double cost = rounds * per * (tile == 256 ? 1.9 : 0.7) + (splits > 1 ? splits * 8.0 * F * E / 5.2e6 : 0.0);
     if (tile == 256 || cost < best) {
       best = cost;
       p.tile = tile;
