@@ -223,9 +223,10 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
   store_owned_rows<1>(accs, muls, outs, lds, q_tok, wave, ln);
 }
 
+template <bool kChunksFirst>
 __global__ __launch_bounds__(kThreads, 4) void fwd_mfma_kernel(AttnArgs a) {
   Work w;
-  if (!take_unit<false>(a, blockIdx.x, w)) return;
+  if (!take_unit<kChunksFirst>(a, blockIdx.x, w)) return;
   fwd_unit(a, w);
 }
 
@@ -233,7 +234,9 @@ __global__ __launch_bounds__(kThreads, 4) void fwd_mfma_kernel(AttnArgs a) {
 
 hipError_t launch_fwd_mfma(const AttnArgs& a, hipStream_t stream) {
   ProfileScope prof(2, stream);
-  hipLaunchKernelGGL(fwd_mfma_kernel, dim3(unit_grid(a.B, a.H, a.N, a.n_col)), dim3(kThreads), 0, stream, a);
+  const dim3 grid(unit_grid(a.B, a.H, a.N, a.n_col)), block(kThreads);
+  if (fwd_chunks_first(a.B, a.H, a.N)) hipLaunchKernelGGL(fwd_mfma_kernel<true>, grid, block, 0, stream, a);
+  else hipLaunchKernelGGL(fwd_mfma_kernel<false>, grid, block, 0, stream, a);
   return hipGetLastError();
 }
 

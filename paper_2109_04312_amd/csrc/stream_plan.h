@@ -26,9 +26,11 @@
 // The two backward kernels run 2 before 1: there the question-token chunks are as long as the
 // column-head units, and more of both exist than workgroup slots, so whichever kind comes second
 // has members that start late and end last; the chunks first measured 1-6 us better on four of
-// the five benchmark shapes and the same on the fifth.  In the forward the empty records at the
-// end of 2 (a sequence with few chunks) would then sit in front of every column-head unit, which
-// cost more than the order won.
+// the five benchmark shapes and the same on the fifth.  The forward does so when the streams are cut
+// into chunks and the launch is a few rounds of the 1024 workgroup slots, where chunks that start
+// second are the last to end (training steps: 2 x 8192, 16 heads 208.4 -> 204.5 us, bucketed 154.1 -> 148.8,
+// 8 x 2048 201.0 -> 197.1); in longer launches, and where owners stream a few tiles, it is the
+// column-head units that must not wait (16 x 4096 604 -> 613 with the chunks first, 32 x 512 114.5 -> 115.8).
 // Records of kind "none" pad every pair to the same count; their workgroups exit at once.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -64,6 +66,9 @@ inline int unit_grid(int B, int H, int N, int n_col) {
   const int T = owner_slots(N), U = view_units(N), nc = (B * n_col + 7) / 8, nr = (B * (H - n_col) + 7) / 8;
   return 8 * ((nc + nr) * U + (nc + nr) * T);
 }
+
+// Question-token units before column-head units in the forward: see above.
+inline bool fwd_chunks_first(int B, int H, int N) { return may_chunk(B, N) && (long)B * H * owner_slots(N) <= 3 * 1024; }
 
 // Entry i of the head order.  A byte indexed by a run-time value would be fetched with a vector
 // load (a memory round trip at the start of every workgroup); the containing 32-bit word comes
