@@ -7,9 +7,9 @@
 // tables, no sort, no gathers.  A workgroup owns 128 consecutive positions of one
 // (sequence, head) and streams every 64-position tile of the sequence; each (query, key) pair is
 // scored and then kept or dropped by comparing the two tokens' codes
-//     code = row id (row heads) / column id (column heads) for a table token,
-//            -1 for a question token, -2 for padding
-//     allowed(a, b) = a > -2 and b > -2 and (a == b or a == -1 or b == -1)
+//     code = row id + 1 (row heads) / column id + 1 (column heads) for a table token,
+//            0 for a question token, kPadCode for padding
+//     allowed = both are not padding, and they are equal or one is a question token
 // which is the attention pattern A^i_k of Section 3 written per pair.  The arithmetic (base-2
 // online softmax, bf16 P and dS, fp32 accumulation, accumulators of the dK/dV kernel started at
 // -lse / scale and -delta) is that of the segment kernels, so both paths meet the same oracle.
@@ -26,6 +26,8 @@ namespace {
 
 constexpr int kStage = 2 * kTileBytes;        // two tensors' tiles
 constexpr int kDkvStageD = kStage + 512;      // ... plus -lse/scale[64], -delta[64]
+
+constexpr unsigned kPadCode = 0xffffffffu;
 
 struct DenseUnit {
   int b, bh, view, tile;  // tile: which 128 positions are owned
@@ -44,44 +46,45 @@ __device__ inline bool dense_unit(const DenseArgs& a, DenseUnit& u) {
 }
 inline int dense_grid(const DenseArgs& a) { return 8 * ((a.B * a.H + 7) / 8) * owner_slots(a.N); }
 
-// Codes of all positions of the sequence (padded with -2 to a whole number of tiles) into LDS.
-__device__ inline void load_codes(const DenseArgs& a, const DenseUnit& u, int* code) {
+// (ids below 0 are not valid; -1 and less act as question tokens and padding)
+__device__ inline unsigned token_code(bool in_range, int flag, int id) {
+  if (!in_range || flag > 1 || (flag == 0 && id < -1)) return kPadCode;
+  return flag == 1 ? 0u : (unsigned)id + 1u;
+}
+
+// Codes of all positions of the sequence (padded with kPadCode to a whole number of tiles) into LDS.
+__device__ inline void load_codes(const DenseArgs& a, const DenseUnit& u, unsigned* code) {
   const int N = a.N;
   const int* ids = (u.view == 0 ? a.row_ids : a.col_ids) + (size_t)u.b * N;
   const unsigned char* fl = a.flags + (size_t)u.b * N;
   for (int n = threadIdx.x; n < ((N + BN - 1) / BN) * BN; n += kThreads) {
-    int c = -2;
-    if (n < N) {
-      const int f = fl[n];
-      c = f == 0 ? ids[n] : f == 1 ? -1 : -2;
-    }
-    code[n] = c;
+    const int f = fl[min(n, N - 1)], id = ids[min(n, N - 1)];  // (one round trip: both loads are unconditional)
+    code[n] = token_code(n < N, f, id);
   }
 }
+
+// May the owned row (code mc) meet a streamed row with code kc?  min(kc, kc ^ mc) is 0 iff the streamed row is a
+// question token or has the same code, and with mc = 0 it is kc; so one comparison with a limit that depends on
+// the owned row says it: below 1 for a table token, below kPadCode for a question token (code 0), never for
+// padding.  (Four instructions per pair where comparing the three cases took seven: training steps of 32
+// sequences of 128, 12 heads 27.1 -> 25.5 us, of one 18.0 -> 15.5, with the loads below in one round trip.)
+__device__ inline unsigned owner_limit(unsigned mc) { return mc == 0u ? kPadCode : mc == kPadCode ? 0u : 1u; }
+__device__ inline bool allowed(unsigned kc, unsigned mc, unsigned limit) { return min(kc, kc ^ mc) < limit; }
 
 // Owned row of a lane: position, code, and whether anything may be written for it.
 struct DenseRow {
   int pos;     // clamped to N - 1
   bool in_range;
-  int code;
-  bool global;
+  unsigned code, limit;
 };
-__device__ inline DenseRow dense_row(const DenseArgs& a, const DenseUnit& u, const int* code, int wave, int m) {
+__device__ inline DenseRow dense_row(const DenseArgs& a, const DenseUnit& u, const unsigned* code, int wave, int m) {
   DenseRow r;
   const int p = u.tile * BM + wave * 32 + m;
   r.in_range = p < a.N;
   r.pos = min(p, a.N - 1);
   r.code = code[r.pos];
-  r.global = r.code == -1;
+  r.limit = owner_limit(r.code);
   return r;
-}
-
-// May the owned row (code mc, global flag) meet a streamed row with code kc?  (Pad owners get
-// arbitrary answers; their results are replaced by zeros.)
-// Written with bitwise operators on purpose: as a conditional expression it compiled to a
-// divergent branch per element.
-__device__ inline bool allowed(int kc, int mc, bool owner_global) {
-  return ((int)(kc == mc) | (int)(kc == -1) | ((int)owner_global & (int)(kc > -2))) != 0;
 }
 
 // Streams the sequence's 64-position tiles of two tensors through two LDS stages.
@@ -99,11 +102,16 @@ struct DenseStream {
     const float* rs = wave == 0 ? rows0 : wave == 1 ? rows1 : nullptr;
     if (rs) issue_row_words(rs, min(t * BN + lane, N - 1), st + kStage + 256 * wave);
   }
+  // both stages: tiles 0 and 1
+  __device__ void begin(int n_tiles) {
+    issue(0);
+    if (n_tiles > 1) issue(1);
+  }
   // tile t is complete for every wavefront and the other stage is free: start loading tile t + 1
   __device__ const char* acquire(int t, int n_tiles) {
     wait_vmcnt_le(0);
     barrier_no_fence();
-    if (t + 1 < n_tiles) issue(t + 1);
+    if (t > 0 && t + 1 < n_tiles) issue(t + 1);
     return stages + (t & 1) * stage_bytes;
   }
 };
@@ -111,22 +119,21 @@ struct DenseStream {
 // The dense-mask rule as a Mask of tile_bodies.h: the pair is kept iff the two tokens' codes say
 // so.  `codes` points at the tile's 64 codes in LDS, offset by this lane half's 4 hl.
 struct CodeMask {
-  const int* codes;
-  int my_code;
-  bool my_global;
-  int k[16];
-  __device__ __forceinline__ CodeMask(const int* tile_codes, int hl, int code, bool global)
-      : codes(tile_codes + 4 * hl), my_code(code), my_global(global) {}
+  const unsigned* codes;
+  unsigned my_code, limit;
+  unsigned k[16];
+  __device__ __forceinline__ CodeMask(const unsigned* tile_codes, int hl, unsigned code, unsigned limit_)
+      : codes(tile_codes + 4 * hl), my_code(code), limit(limit_) {}
   __device__ __forceinline__ void load(int blk) {
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      const int4 kc = *reinterpret_cast<const int4*>(codes + blk * 32 + 8 * g);
+      const uint4 kc = *reinterpret_cast<const uint4*>(codes + blk * 32 + 8 * g);
       k[4 * g] = kc.x; k[4 * g + 1] = kc.y; k[4 * g + 2] = kc.z; k[4 * g + 3] = kc.w;
     }
   }
   __device__ __forceinline__ bool full(int) const { return false; }
   __device__ __forceinline__ bool skip(int) const { return false; }
-  __device__ __forceinline__ bool in(int c) const { return allowed(k[c], my_code, my_global); }
+  __device__ __forceinline__ bool in(int c) const { return allowed(k[c], my_code, limit); }
   __device__ __forceinline__ float keep(int c, float x, float other) const { return in(c) ? x : other; }
 };
 
@@ -135,7 +142,7 @@ struct CodeMask {
 // ======================================================================================
 __global__ __launch_bounds__(kThreads) void fwd_dense_kernel(DenseArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds[2 * kStage];
-  __shared__ __attribute__((aligned(16))) int code[kDenseMaxN];
+  __shared__ __attribute__((aligned(16))) unsigned code[kDenseMaxN];
   __shared__ int q_tok[BM];
   DenseUnit u;
   if (!dense_unit(a, u)) return;
@@ -149,15 +156,19 @@ __global__ __launch_bounds__(kThreads) void fwd_dense_kernel(DenseArgs a) {
   unsigned short* O = static_cast<unsigned short*>(a.out) + bh * kD;
 
   DenseStream stream{K, V, nullptr, nullptr, lds, kStage, N, wave, lane, make_load_lane(wave, lane)};
-  stream.issue(0);
-  load_codes(a, u, code);
-  if (tid < BM) q_tok[tid] = u.tile * BM + tid < N ? u.tile * BM + tid : -1;
-  __syncthreads();
-  const DenseRow me = dense_row(a, u, code, wave, m);
+  // everything in one round trip: the owned rows, the first two tiles, the codes
+  const int n_tiles = (N + BN - 1) / BN;
+  const int pos = min(u.tile * BM + wave * 32 + m, N - 1);
   bf16x8 qf[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks)
-    qf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(Q + (size_t)me.pos * kD + ks * 16 + hl * 8));
+    qf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(Q + (size_t)pos * kD + ks * 16 + hl * 8));
+  stream.begin(n_tiles);
+  load_codes(a, u, code);
+  if (tid < BM) q_tok[tid] = u.tile * BM + tid < N ? u.tile * BM + tid : -1;
+  __syncthreads();
+  DenseRow me = dense_row(a, u, code, wave, m);
+  if (me.limit == 0) me.limit = kPadCode;  // (padding meets anything: its results are replaced, and every row has a maximum)
   asm volatile("" ::"v"(qf[0]), "v"(qf[1]), "v"(qf[2]), "v"(qf[3]));
 
   const float sc = uniform(a.scale * kLog2e);
@@ -167,16 +178,15 @@ __global__ __launch_bounds__(kThreads) void fwd_dense_kernel(DenseArgs a) {
   operand_offsets(lane, koff, voff);
   const bool wave_active = u.tile * BM + wave * 32 < N;
 
-  const int n_tiles = (N + BN - 1) / BN;
   for (int t = 0; t < n_tiles; ++t) {
     const char* Kst = stream.acquire(t, n_tiles);
     const char* Vst = Kst + kTileBytes;
     if (!wave_active) continue;
-    fwd_tile(Kst, Vst, qf, koff, voff, sc, CodeMask(code + t * BN, hl, me.code, me.global), o_acc, m_run, l_run);
+    fwd_tile(Kst, Vst, qf, koff, voff, sc, CodeMask(code + t * BN, hl, me.code, me.limit), o_acc, m_run, l_run);
   }
   __syncthreads();
   const float l_tot = half_sum(l_run);
-  const bool live = me.in_range && me.code > -2;  // pad positions: O = 0, LSE = 0
+  const bool live = me.in_range && me.code != kPadCode;  // pad positions: O = 0, LSE = 0
   if (hl == 0 && me.in_range)
     a.lse[bh + me.pos] = live ? (m_run * sc + __builtin_amdgcn_logf(l_tot)) * kLn2 : 0.f;
   const float inv = live ? 1.f / l_tot : 0.f;
@@ -193,9 +203,9 @@ __global__ __launch_bounds__(kThreads) void fwd_dense_kernel(DenseArgs a) {
 // ======================================================================================
 // dQ (and -delta, -lse / scale for the dK/dV kernel)
 // ======================================================================================
-__global__ __launch_bounds__(kThreads) void bwd_dq_dense_kernel(DenseArgs a) {
+__global__ __launch_bounds__(kThreads, 4) void bwd_dq_dense_kernel(DenseArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds[2 * kStage];
-  __shared__ __attribute__((aligned(16))) int code[kDenseMaxN];
+  __shared__ __attribute__((aligned(16))) unsigned code[kDenseMaxN];
   __shared__ int q_tok[BM];
   DenseUnit u;
   if (!dense_unit(a, u)) return;
@@ -211,7 +221,8 @@ __global__ __launch_bounds__(kThreads) void bwd_dq_dense_kernel(DenseArgs a) {
   unsigned short* dQ = static_cast<unsigned short*>(a.dq) + bh * kD;
 
   DenseStream stream{K, V, nullptr, nullptr, lds, kStage, N, wave, lane, make_load_lane(wave, lane)};
-  stream.issue(0);
+  const int n_tiles = (N + BN - 1) / BN;
+  stream.begin(n_tiles);
   load_codes(a, u, code);
   if (tid < BM) q_tok[tid] = u.tile * BM + tid < N ? u.tile * BM + tid : -1;
   __syncthreads();
@@ -243,15 +254,14 @@ __global__ __launch_bounds__(kThreads) void bwd_dq_dense_kernel(DenseArgs a) {
   const bool wave_active = u.tile * BM + wave * 32 < N;
 
   f32x16 dq_acc[2] = {zero16(), zero16()};
-  const int n_tiles = (N + BN - 1) / BN;
   for (int t = 0; t < n_tiles; ++t) {
     const char* Kst = stream.acquire(t, n_tiles);
     const char* Vst = Kst + kTileBytes;
     if (!wave_active) continue;
-    dq_tile(Kst, Vst, qf, gf, koff, toff, sc, lse2, delta, CodeMask(code + t * BN, hl, me.code, me.global), dq_acc);
+    dq_tile(Kst, Vst, qf, gf, koff, toff, sc, lse2, delta, CodeMask(code + t * BN, hl, me.code, me.limit), dq_acc);
   }
   __syncthreads();
-  const float mul = me.in_range && me.code > -2 ? a.scale : 0.f;  // pad positions: zeros
+  const float mul = me.in_range && me.code != kPadCode ? a.scale : 0.f;  // pad positions: zeros
 #pragma unroll
   for (int db = 0; db < 2; ++db)
 #pragma unroll
@@ -267,7 +277,7 @@ __global__ __launch_bounds__(kThreads) void bwd_dq_dense_kernel(DenseArgs a) {
 // ======================================================================================
 __global__ __launch_bounds__(kThreads) void bwd_dkv_dense_kernel(DenseArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds[2 * kDkvStageD];
-  __shared__ __attribute__((aligned(16))) int code[kDenseMaxN];
+  __shared__ __attribute__((aligned(16))) unsigned code[kDenseMaxN];
   __shared__ int k_tok[BM];
   DenseUnit u;
   if (!dense_unit(a, u)) return;
@@ -284,7 +294,8 @@ __global__ __launch_bounds__(kThreads) void bwd_dkv_dense_kernel(DenseArgs a) {
 
   DenseStream stream{Q, dO, a.nlse + bh, a.delta + bh, lds, kDkvStageD, N, wave, lane,
                      make_load_lane(wave, lane)};
-  stream.issue(0);
+  const int n_tiles = (N + BN - 1) / BN;
+  stream.begin(n_tiles);
   load_codes(a, u, code);
   if (tid < BM) k_tok[tid] = u.tile * BM + tid < N ? u.tile * BM + tid : -1;
   __syncthreads();
@@ -304,17 +315,16 @@ __global__ __launch_bounds__(kThreads) void bwd_dkv_dense_kernel(DenseArgs a) {
   const bool wave_active = u.tile * BM + wave * 32 < N;
 
   f32x16 dk_acc[2] = {zero16(), zero16()}, dv_acc[2] = {zero16(), zero16()};
-  const int n_tiles = (N + BN - 1) / BN;
   for (int t = 0; t < n_tiles; ++t) {
     const char* Qst = stream.acquire(t, n_tiles);
     const char* Gst = Qst + kTileBytes;
     const float* lse_row = reinterpret_cast<const float*>(Qst + kStage);
     const float* delta_row = lse_row + BN;
     if (!wave_active) continue;
-    dkv_tile(Qst, Gst, lse_row, delta_row, kf, vf, poff, toff, sc, hl, CodeMask(code + t * BN, hl, me.code, me.global), dk_acc, dv_acc);
+    dkv_tile(Qst, Gst, lse_row, delta_row, kf, vf, poff, toff, sc, hl, CodeMask(code + t * BN, hl, me.code, me.limit), dk_acc, dv_acc);
   }
   __syncthreads();
-  const bool live = me.in_range && me.code > -2;  // pad positions: zeros
+  const bool live = me.in_range && me.code != kPadCode;  // pad positions: zeros
 #pragma unroll
   for (int db = 0; db < 2; ++db)
 #pragma unroll
@@ -352,7 +362,7 @@ template <int NW>
 __global__ __launch_bounds__(64 * NW, 2) void bwd_dense_small_kernel(DenseArgs a) {
   using S = SmallShape<NW>;
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  __shared__ __attribute__((aligned(16))) int code[S::kKeys];
+  __shared__ __attribute__((aligned(16))) unsigned code[S::kKeys];
   __shared__ __attribute__((aligned(16))) float nlse[S::kKeys], ndelta[S::kKeys];
   char *const kt = lds, *const qt = lds + S::kKeyBytes, *const gt = qt + S::kQryBytes;
   char *const ds = S::kOverlay ? qt : gt + S::kQryBytes;
@@ -406,7 +416,7 @@ __global__ __launch_bounds__(64 * NW, 2) void bwd_dense_small_kernel(DenseArgs a
     if (hl == 0) {
       nlse[32 * wave + m] = -lse / a.scale;
       ndelta[32 * wave + m] = -delta;
-      code[32 * wave + m] = 32 * wave + m >= N ? -2 : f == 0 ? id : f == 1 ? -1 : -2;
+      code[32 * wave + m] = token_code(32 * wave + m < N, f, id);
     }
   }
   const float sc = uniform(a.scale * kLog2e);
@@ -425,7 +435,7 @@ __global__ __launch_bounds__(64 * NW, 2) void bwd_dense_small_kernel(DenseArgs a
     wait_vmcnt_le<0>(0);
     __syncthreads();
     bf16x8 ds8[S::kBlocks][2];
-    const int my_code = code[32 * wave + m];
+    const unsigned my_code = code[32 * wave + m], my_limit = owner_limit(my_code);
     if (active)
 #pragma unroll
       for (int ib = 0; ib < S::kBlocks; ++ib) {
@@ -444,11 +454,11 @@ __global__ __launch_bounds__(64 * NW, 2) void bwd_dense_small_kernel(DenseArgs a
           s = mfma(read_plain(qt + ib * 32 * 128, poff[ks]), kf[ks], s);     // S  = Q K^T
           dp = mfma(read_plain(gt + ib * 32 * 128, poff[ks]), vf[ks], dp);   // dP = dO V^T
         }
-        CodeMask mask(code + q0, hl, my_code, my_code == -1);
+        CodeMask mask(code + q0, hl, my_code, my_limit);
         mask.load(0);
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
-          const bool in = mask.in(c) && my_code > -2;
+          const bool in = mask.in(c);
           s[c] = in ? __builtin_amdgcn_exp2f(s[c] * sc) : 0.f;   // P
           dp[c] = in ? s[c] * dp[c] : 0.f;                       // dS
         }
@@ -502,7 +512,7 @@ __global__ __launch_bounds__(64 * NW, 2) void bwd_dense_small_kernel(DenseArgs a
     __syncthreads();  // dS^T has been read: its place (or the Q tiles) takes the dQ rows
     if (has_block) {
       const int q = (p * S::kBlocks + qb) * 32 + m;
-      const bool live_q = code[q] > -2;  // pad positions: zeros, whatever their rows held
+      const bool live_q = code[q] != kPadCode;  // pad positions: zeros, whatever their rows held
 #pragma unroll
       for (int i = 0; i < kHalves; ++i) stage_rows(live_q ? dq_acc[i] : zero16(), a.scale, qt, qb * 32 + m, db0 + i, hl);
     }
@@ -518,7 +528,7 @@ __global__ __launch_bounds__(64 * NW, 2) void bwd_dense_small_kernel(DenseArgs a
   // nobody else touches them, and LDS keeps a wavefront's accesses in order
   if (!active) return;
   char* const st = kt + wave * 32 * 128;
-  const bool live = code[32 * wave + m] > -2;
+  const bool live = code[32 * wave + m] != kPadCode;
   const auto flush = [&](unsigned short* out) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
