@@ -77,7 +77,7 @@ def summarize_pmc(fetch_dir, write_dir):
             for row in csv.DictReader(open(path)):
                 if row["Counter_Name"] == counter:
                     name = row["Kernel_Name"].replace("(anonymous namespace)::", "").replace("void ", "")
-                    name = name.split("(")[0].replace("mate::", "")
+                    name = name.split("(")[0].replace("mate::", "").replace("<true>", "").replace("<false>", "")
                     acc.setdefault(name, {}).setdefault(row["Dispatch_Id"], 0.0)
                     acc[name][row["Dispatch_Id"]] += float(row["Counter_Value"])
         return {k: sum(v.values()) / len(v) for k, v in acc.items()}
