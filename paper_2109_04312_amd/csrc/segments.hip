@@ -1,6 +1,6 @@
 // Segment builder: the per-head-kind reordering of Section 3.1 (row-order / column-order
 // traversal of the table tokens), computed as a stable sort of the table-token positions by id
-// plus run boundaries.  Integer work only.  1024-thread workgroups; all sorting lives in LDS.
+// plus run boundaries.  Integer work only; all sorting lives in LDS.
 //
 // Two ways, chosen on the device from the ids themselves:
 //   * ids all below 512 (every row and column number of a real table): the order is a counting
@@ -46,8 +46,7 @@
 
 namespace mate {
 
-constexpr int kSegThreads = 1024;
-constexpr int kSegWaves = kSegThreads / 64;
+constexpr int kSegChunk = 1024;             // positions per workgroup, about
 constexpr int kDigitBits = 9;               // radix digit: ids below 512 sort in one pass
 constexpr unsigned kBins = 1u << kDigitBits;
 
@@ -83,22 +82,24 @@ __device__ inline int wave_or(int v) {
   v |= __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
   return __builtin_amdgcn_readlane(v, 63);
 }
-// Sum of table[0 .. kSegWaves) before this wavefront's entry, and of all of it: one LDS read.
+// Sum of table[0 .. kWaves) before this wavefront's entry, and of all of it: one LDS read.
+template <int kWaves>
 __device__ inline int waves_before(const int* table, int wave, int& total) {
-  static_assert(kSegWaves == 16, "one DPP row holds the table");
-  const int inc = row_scan(table[threadIdx.x & (kSegWaves - 1)]);
-  total = __builtin_amdgcn_readlane(inc, kSegWaves - 1);
+  static_assert(kWaves == 8 || kWaves == 16, "one DPP row holds the table");
+  const int inc = row_scan(table[threadIdx.x & (kWaves - 1)]);
+  total = __builtin_amdgcn_readlane(inc, kWaves - 1);
   return wave ? __builtin_amdgcn_readlane(inc, wave - 1) : 0;
 }
 
 // Exclusive prefix sum of one int per thread across the workgroup; `total` gets the sum.
-// `tmp` is kSegWaves ints of LDS that no wavefront still reads; it may be written again after the next barrier.
+// `tmp` is kWaves ints of LDS that no wavefront still reads; it may be written again after the next barrier.
+template <int kWaves>
 __device__ inline int block_exclusive_scan(int v, int* tmp, int& total) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int inc = wave_scan(v);
   if ((threadIdx.x & 63) == 63) tmp[wave] = inc;
   lds_barrier();
-  return waves_before(tmp, wave, total) + inc - v;
+  return waves_before<kWaves>(tmp, wave, total) + inc - v;
 }
 
 // Number of set bits of `mask` that belong to lanes before this one (v_mbcnt).
@@ -107,12 +108,13 @@ __device__ inline int lanes_before(unsigned long long mask) {
 }
 
 // Exclusive prefix count of one flag per thread; same contract.
+template <int kWaves>
 __device__ inline int block_flag_scan(bool flag, int* tmp, int& total) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const unsigned long long m = __ballot(flag);
   if ((threadIdx.x & 63) == 0) tmp[wave] = __popcll(m);
   lds_barrier();
-  return waves_before(tmp, wave, total) + lanes_before(m);
+  return waves_before<kWaves>(tmp, wave, total) + lanes_before(m);
 }
 
 // Lanes of the wavefront that hold the same digit as this lane (valid lanes only).  Only the
@@ -135,11 +137,14 @@ __device__ inline unsigned varying_bits(unsigned digit, bool valid) {
   return (unsigned)wave_or(valid ? (int)(digit ^ first) : 0);
 }
 
-template <int P2>
-__global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
+// Longest sequence and wavefronts of the workgroup: with 16, every step from the second barrier on is mostly the
+// issue of their instructions, so up to 2048 positions take eight (one sequence of 512: 6.3 -> 5.6 us, of 2048 8.2 -> 7.6).
+template <int P2, int kSegWaves>
+__global__ __launch_bounds__(64 * kSegWaves) void build_segments_kernel(
     const int* __restrict__ row_ids, const int* __restrict__ col_ids,
     const unsigned char* __restrict__ flags, int B, int N, int max_global, int radius,
     int* __restrict__ seg) {
+  constexpr int kSegThreads = 64 * kSegWaves;
   constexpr int CHUNK = P2 / kSegWaves;  // consecutive elements owned by one wavefront
   constexpr int NB = CHUNK / 64;         // 64-element batches per wavefront
   constexpr int VE = NB < 4 ? NB : 4;    // consecutive elements per lane while classifying
@@ -232,7 +237,7 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
     if (lane == 0) scan_tmp[0][wave] = n_q;
     lds_barrier();
     int all_q;
-    q_at = waves_before(scan_tmp[0], wave, all_q);
+    q_at = waves_before<kSegWaves>(scan_tmp[0], wave, all_q);
   }
 
   // ---- classify; count the three kinds of position per wavefront ---------------------------
@@ -293,8 +298,8 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
   if (bad) s_bad = 1;
   lds_barrier();
   int lg_all, lg_before;
-  const int lg_at = waves_before(wave_tot[0], wave, lg_all);
-  waves_before(wave_tot[1], wave, lg_before);
+  const int lg_at = waves_before<kSegWaves>(wave_tot[0], wave, lg_all);
+  waves_before<kSegWaves>(wave_tot[1], wave, lg_before);
   const int L = lg_all & 0xffff, G = lg_all >> 16, P = N - L - G;
   // kinds before this workgroup's chunk
   const int g_before = lg_before >> 16, p_before = c0 - (lg_before & 0xffff) - g_before;
@@ -308,12 +313,12 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
 
   if ((all_bits & ~(kBins - 1u)) == 0) {
     // ============ counting-sort path: every id is below kBins, all workgroups ============
-    constexpr int NBC = P2 > 8 * kSegThreads ? 2 : 1;   // 64-position batches of the chunk per wavefront
+    constexpr int NBC = (P2 > 8 * kSegChunk ? 2 : 1) * kSegChunk / kSegThreads;   // 64-position batches of the chunk per wavefront
     // first slot and segment index of every id, from one scan (segments << 16)
     const unsigned count = tid < (int)kBins ? id_count[tid] : 0u;
     const int c_id = (int)(count & 0xffffu);
     int tot;
-    const int at = block_exclusive_scan(c_id | (c_id > 0 ? 1 << 16 : 0), scan_tmp[1], tot);
+    const int at = block_exclusive_scan<kSegWaves>(c_id | (c_id > 0 ? 1 << 16 : 0), scan_tmp[1], tot);
     const int first_slot = at & 0xffff, seg_index = at >> 16, S = tot >> 16;
     if (tid < (int)kBins) {
       start_v[tid] = first_slot;
@@ -381,7 +386,7 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
         }
       }
       int gp_chunk;
-      const int gp = waves_before(wave_tot[2], wave, gp_chunk);
+      const int gp = waves_before<kSegWaves>(wave_tot[2], wave, gp_chunk);
       const int g_at_c = g_before + (gp & 0xffff), p_at_c = p_before + (gp >> 16);
       lds_barrier();
 #pragma unroll
@@ -416,10 +421,11 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
     }
     if (k != K) return;
     // ---- work units of the attention kernels (the workgroup without a chunk) ---------------------
-    // question-token owners (the same for both views), by wavefronts that list no units
-    static_assert(kMaxTiles <= kSegThreads - (int)kBins, "a thread per record");
-    if (view == 0 && tid >= (int)kBins && tid - (int)kBins < lay.tiles) {
-      const int rec = tid - (int)kBins;
+    // question-token owners (the same for both views), if possible by wavefronts that list no units
+    constexpr int kFirst = kSegThreads > (int)kBins ? (int)kBins : 0;
+    static_assert(kMaxTiles <= kSegThreads - kFirst, "a thread per record");
+    if (view == 0 && tid >= kFirst && tid - kFirst < lay.tiles) {
+      const int rec = tid - kFirst;
       const GlobalSplit gs = global_split(G, L, B, N);
       int4 q0 = make_int4(UNIT_NONE, 0, 0, 0), q1 = make_int4(0, 0, -1, 0);
       if (rec < gs.n_gt * gs.n_chunks) {
@@ -442,13 +448,13 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
       cut = tid == 0 || size >= kBigSegment || sstart[tid] - sstart[tid - 1] >= kBigSegment;
     }
     int n_runs;
-    const int run_index = block_flag_scan(cut, scan_tmp[2], n_runs);
+    const int run_index = block_flag_scan<kSegWaves>(cut, scan_tmp[2], n_runs);
     if (cut) run_start[run_index] = sstart[tid];
     if (tid == 0) run_start[n_runs] = L;
     lds_barrier();
     const int run_units = tid < n_runs ? (run_start[tid + 1] - run_start[tid] + kTileSlots - 1) / kTileSlots : 0;
     int n_units;
-    const int unit_base = block_exclusive_scan(run_units, scan_tmp[1], n_units);
+    const int unit_base = block_exclusive_scan<kSegWaves>(run_units, scan_tmp[1], n_units);
     if (n_units + n_pt <= lay.units) {
       for (int i = 0; i < run_units; ++i) head_pos[unit_base + i] = (unsigned short)(run_start[tid] + i * kTileSlots);
     } else {  // more records than the buffer has: every 128 slots regardless of segments
@@ -560,7 +566,7 @@ __global__ __launch_bounds__(kSegThreads) void build_segments_kernel(
       }
     }
     int all;
-    const int digit_base = block_exclusive_scan(tot, scan_tmp[0], all);
+    const int digit_base = block_exclusive_scan<kSegWaves>(tot, scan_tmp[0], all);
     if (tid < kBins) {
 #pragma unroll
       for (int w = 0; w < kSegWaves; ++w) hist[w][tid] = (unsigned short)(first[w] + digit_base);
@@ -754,19 +760,20 @@ hipError_t launch_build_segments(const int* row_ids, const int* col_ids,
                                  int radius, int* seg, hipStream_t stream) {
   // up to eight workgroups per (sequence, view) with about 1024 positions each, and a further one
   // for the work-unit list
-  const int chunks = std::min(8, (N + kSegThreads - 1) / kSegThreads);
-  dim3 grid(B, 2, chunks + 1), block(kSegThreads);
+  const int chunks = std::min(8, (N + kSegChunk - 1) / kSegChunk);
+  dim3 grid(B, 2, chunks + 1);
   ProfileScope prof(1, stream);
-#define MATE_SEG_CASE(P2)                                                                  \
-  if (N <= P2) {                                                                            \
-    hipLaunchKernelGGL(build_segments_kernel<P2>, grid, block, 0, stream, row_ids, col_ids, \
-                       flags, B, N, max_global, radius, seg);                               \
-    return hipGetLastError();                                                               \
+#define MATE_SEG_CASE(P2, WAVES)                                                                     \
+  if (N <= P2) {                                                                                      \
+    hipLaunchKernelGGL((build_segments_kernel<P2, WAVES>), grid, dim3(64 * WAVES), 0, stream, row_ids, \
+                       col_ids, flags, B, N, max_global, radius, seg);                                \
+    return hipGetLastError();                                                                         \
   }
-  MATE_SEG_CASE(1024)
-  MATE_SEG_CASE(4096)
-  MATE_SEG_CASE(8192)
-  MATE_SEG_CASE(16384)
+  MATE_SEG_CASE(1024, 8)
+  MATE_SEG_CASE(2048, 8)
+  MATE_SEG_CASE(4096, 16)
+  MATE_SEG_CASE(8192, 16)
+  MATE_SEG_CASE(16384, 16)
 #undef MATE_SEG_CASE
   return hipErrorInvalidValue;
 }
