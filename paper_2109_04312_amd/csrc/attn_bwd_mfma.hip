@@ -70,7 +70,7 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
   __shared__ int idx_ring[kIdxSlots][BN];
   __shared__ int q_tok[BM];
 
-  const int b = w.bh / a.H;
+  const int b = w.b;
   const int N = a.N, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction
   const int m = lane & 31, hl = lane >> 5;
@@ -185,7 +185,7 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
   __shared__ int idx_ring[kIdxSlots][BN];
   __shared__ int group_done;
 
-  const int b = w.bh / a.H;
+  const int b = w.b;
   const int N = a.N, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction
   const int m = lane & 31, hl = lane >> 5;

@@ -140,7 +140,7 @@ struct Rows {
   int G, s_lo, s_hi, nG, n;
   __device__ __forceinline__ Rows(const AttnArgs& a, const Quarter& q, int m) {
     const UnitPlan& u = q.w.u;
-    const int b = q.w.bh / a.H, first = u.t0 + kRows * q.sub, slot = min(first + m, u.own_count - 1);
+    const int b = q.w.b, first = u.t0 + kRows * q.sub, slot = min(first + m, u.own_count - 1);
     valid = first + m < u.own_count;
     pos = u.own_list[slot];
     lo = 0;

@@ -100,7 +100,7 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
   __shared__ int q_tok[BM];
   __shared__ int group_done;
 
-  const int b = w.bh / a.H;
+  const int b = w.b;
   const int N = a.N, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction
   const int m = lane & 31, hl = lane >> 5;

@@ -47,10 +47,9 @@ __device__ inline LoadLane make_load_lane(int wave, int lane) {
 // Ordering against the LDS reads is by the explicit waits and barriers of the caller.  The
 // compiler's own vmcnt bookkeeping for ordinary loads stays safe: loads it cannot see only make
 // its waits stricter, since loads retire in issue order.
-__device__ inline unsigned lds_addr(const void* p) {
-  return __builtin_amdgcn_readfirstlane(
-      (unsigned)(size_t)(const __attribute__((address_space(3))) char*)p);
-}
+// (The low half of the generic address of LDS is the LDS offset; a cast to the LDS address space would add
+// a comparison with the null pointer to every load.)
+__device__ inline unsigned lds_addr(const void* p) { return __builtin_amdgcn_readfirstlane((unsigned)(size_t)p); }
 // Address form: 64-bit base in scalar registers (wave-uniform) plus a 32-bit byte offset per
 // lane, so the per-lane address arithmetic is one shift-add.
 __device__ inline void load_to_lds_16(const void* base /* wave-uniform */, unsigned byte_off,

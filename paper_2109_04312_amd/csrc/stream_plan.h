@@ -58,7 +58,7 @@ struct UnitPlan {
 
 // ---- workgroup -> unit ---------------------------------------------------------------------
 struct Work {
-  int bh, view;
+  int b, bh, view;
   UnitPlan u;
 };
 
@@ -76,6 +76,17 @@ inline bool fwd_chunks_first(int B, int H, int N) { return may_chunk(B, N) && (l
 __device__ inline int head_at(const AttnArgs& a, int i) {
   const unsigned word = reinterpret_cast<const unsigned*>(a.head_order)[i >> 2];
   return (word >> (8 * (i & 3))) & 0xffu;
+}
+
+// x / d and the remainder, both wave-uniform and not negative: one float product and its correction, half the
+// instructions of an integer division (scalar instructions wait for each other, and a workgroup's first
+// microsecond is little else).
+__device__ inline int uniform_div(int x, int d, int& rest) {
+  int k = __builtin_amdgcn_readfirstlane((int)((float)x * __builtin_amdgcn_rcpf((float)d)));
+  rest = x - k * d;
+  while (rest < 0) { rest += d; --k; }   // (at most once below 2^22)
+  while (rest >= d) { rest -= d; ++k; }
+  return k;
 }
 
 // Returns false if this workgroup has nothing to do.  Everything here is wave-uniform and
@@ -121,20 +132,15 @@ __device__ inline bool take_unit(const AttnArgs& a, int block, Work& w) {
   // The hardware hands consecutive workgroups of an XCD to its shader engines in rotation and
   // stalls when the engine whose turn it is has no room, so each engine must see the same mix
   // of units: the pair order rotates from sweep to sweep.
-  const int kk = t / pairs, j = first + (t + kk) % pairs, k = k0 + kk;
+  int at, i;
+  const int kk = uniform_div(t, pairs, at), k = k0 + kk;
   if (kk >= per) return false;
-  int b, h;
-  if (j < nc) {
-    const int c = q + 8 * j;
-    b = c / n_col;
-    h = head_at(a, c % n_col);
-    w.view = 1;
-  } else {
-    const int r = qr + 8 * (j - nc);
-    b = r / n_row;
-    h = head_at(a, n_col + r % n_row);
-    w.view = 0;
-  }
+  uniform_div(at + kk, pairs, at);
+  const int j = first + at;
+  w.view = j < nc ? 1 : 0;
+  const int b = w.view ? uniform_div(q + 8 * j, n_col, i) : uniform_div(qr + 8 * (j - nc), n_row, i);
+  const int h = head_at(a, w.view ? i : n_col + i);
+  w.b = b;
   w.bh = b * a.H + h;
   const int4* rec = glob ? a.seg.gunit + ((size_t)b * T + k) * 2
                          : a.seg.unit[w.view] + ((size_t)b * U + k) * 2;

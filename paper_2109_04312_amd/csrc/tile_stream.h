@@ -58,7 +58,7 @@ struct TileStream {
   __device__ void issue_data(int t, int k /* = t - current tile */) {
     const int* r = ring[t & (kIdxSlots - 1)];
     const int x0 = r[ll.row0], x1 = r[ll.row0 + 8];
-    char* st = stages + ((t - u.t_begin) % NS) * kStageBytes;
+    char* st = stages + ((unsigned)(t - u.t_begin) % NS) * kStageBytes;
     issue_tile(X0, x0, x1, ll, st, wave);
     issue_tile(X1, x0, x1, ll, st + kTileBytes, wave);
     note(4);
@@ -94,7 +94,7 @@ struct TileStream {
     barrier_no_fence();       // ... everyone's has, and everyone is done with tile t - 1
     if (t + 2 * NS - 2 < u.t_end) issue_idx(t + 2 * NS - 2);
     if (t + NS - 1 < u.t_end) issue_data(t + NS - 1, NS - 1);
-    return stages + ((t - u.t_begin) % NS) * kStageBytes;
+    return stages + ((unsigned)(t - u.t_begin) % NS) * kStageBytes;
   }
   __device__ void release() {
 #pragma unroll
