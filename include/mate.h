@@ -43,7 +43,9 @@ typedef enum {
   MATE_ERR_NULL = -1,        /* a required pointer is NULL                                */
   MATE_ERR_SHAPE = -2,       /* B, H, N out of range, or tables built for another (B, N)  */
   MATE_ERR_UNSUPPORTED = -3, /* D != 64, unknown dtype or head kind, scale not positive   */
-  MATE_ERR_WORKSPACE = -4,   /* workspace_bytes smaller than mate_workspace_bytes(...)    */
+  MATE_ERR_WORKSPACE = -4,   /* workspace_bytes smaller than mate_workspace_bytes(...), or an
+                                address that the bf16 attention's 64-bit atomics cannot use
+                                (not a multiple of 8)                                      */
   MATE_ERR_BAD_ID = -5,      /* a table token has a negative id, or a flag value > 2      */
   MATE_ERR_HIP = -6          /* a HIP call or kernel launch failed                        */
 } mate_status;

@@ -36,6 +36,12 @@ size_t part_bytes(int B, int H, int N) { return (size_t)B * H * part_words_per_b
 // one arrival word per partial slot (see stream_plan.h)
 size_t word_bytes(int B, int H, int N) { return (size_t)B * H * owner_slots(N) * sizeof(unsigned long long); }
 size_t stat_bytes(int B, int H, int N) { return (size_t)B * H * stat_words_per_bh(N) * sizeof(float); }
+// The bf16 kernels access partial results and arrival words, which lie at multiples of 8 bytes of the
+// workspace, with 64-bit atomics: an address that is not a multiple of 8 is a memory fault there.
+bool workspace_ok(const void* p, size_t bytes, size_t need, mate_dtype t) {
+  if (need == 0) return true;
+  return p && bytes >= need && (t != MATE_BF16 || reinterpret_cast<uintptr_t>(p) % sizeof(unsigned long long) == 0);
+}
 
 // The value a call's chunks announce themselves with: never zero, and a 64-bit number that no earlier
 // call of this process has used (the mix below is a bijection) and that uninitialised memory does
@@ -300,8 +306,7 @@ mate_status mate_attn_fwd(const void* q, const void* k, const void* v, const voi
   AttnArgs a;
   mate_status st = fill_args(a, segments, head_kind, B, H, N, D, t, scale);
   if (st != MATE_OK) return st;
-  const size_t need = mate_workspace_bytes(B, H, N, D, t, 0);
-  if (need && (!workspace || workspace_bytes < need)) return MATE_ERR_WORKSPACE;
+  if (!workspace_ok(workspace, workspace_bytes, mate_workspace_bytes(B, H, N, D, t, 0), t)) return MATE_ERR_WORKSPACE;
   a.q = q; a.k = k; a.v = v; a.out = out; a.lse = lse;
   if (t == MATE_BF16) {
     char* p = static_cast<char*>(workspace);
@@ -324,8 +329,7 @@ mate_status mate_attn_bwd(const void* q, const void* k, const void* v, const voi
   AttnArgs a;
   mate_status st = fill_args(a, segments, head_kind, B, H, N, D, t, scale);
   if (st != MATE_OK) return st;
-  const size_t need = mate_workspace_bytes(B, H, N, D, t, 1);
-  if (need && (!workspace || workspace_bytes < need)) return MATE_ERR_WORKSPACE;
+  if (!workspace_ok(workspace, workspace_bytes, mate_workspace_bytes(B, H, N, D, t, 1), t)) return MATE_ERR_WORKSPACE;
   a.q = q; a.k = k; a.v = v; a.o = out; a.dout = dout;
   a.lse = const_cast<float*>(lse);
   a.dq = dq; a.dk = dk; a.dv = dv;
@@ -467,7 +471,7 @@ const char* mate_status_string(mate_status s) {
     case MATE_ERR_NULL: return "a required pointer is NULL";
     case MATE_ERR_SHAPE: return "shape out of range, or segment tables built for another (B, N)";
     case MATE_ERR_UNSUPPORTED: return "unsupported head size, dtype or head kind";
-    case MATE_ERR_WORKSPACE: return "workspace too small";
+    case MATE_ERR_WORKSPACE: return "workspace too small or not aligned";
     case MATE_ERR_BAD_ID: return "negative id on a table token, or flag value above 2";
     case MATE_ERR_HIP: return "HIP call or kernel launch failed";
   }

@@ -75,6 +75,19 @@ def test_argument_errors_are_caught_on_the_host(mate):
     assert mate.mate_segments_export(fake, 1, 128, 2, None, None, None, None, None, None) == mate.MATE_ERR_SHAPE
 
 
+@pytest.mark.parametrize("offset", [1, 2, 4, 12])
+def test_misaligned_workspace_is_refused_on_the_host(mate, offset):
+    """The bf16 kernels use 64-bit atomics inside the workspace, which fault at other addresses than
+    multiples of 8; nothing is launched with one."""
+    hk = np.zeros(4, np.uint8)
+    fake = 0x1000  # never dereferenced
+    for B, N in ((1, 128), (2, 2100)):   # without and with chunked question-token owners
+        fwd = [fake] * 4 + [hk.ctypes.data, B, 4, N, 64, mate.MATE_BF16, 1.0, fake, fake]
+        bwd = [fake] * 7 + [hk.ctypes.data, B, 4, N, 64, mate.MATE_BF16, 1.0, fake, fake, fake]
+        assert mate.mate_attn_fwd(*fwd, fake + offset, 1 << 40, None) == mate.MATE_ERR_WORKSPACE
+        assert mate.mate_attn_bwd(*bwd, fake + offset, 1 << 40, None) == mate.MATE_ERR_WORKSPACE
+
+
 def test_argument_errors_of_the_later_entry_points(mate):
     fake = 0x1000  # never dereferenced
     bb = mate.mate_build_segments_bucketed
