@@ -113,16 +113,20 @@ Shape4 shape4(const at::Tensor& t) {
 }
 void* stream() { return c10::hip::getCurrentHIPStreamMasqueradingAsCUDA().stream(); }
 
-// Head kinds on the host: an object that exposes H contiguous bytes is read in place, anything
-// else (a list, an integer array, a tensor) goes through mate.py's conversion to one.
+// Head kinds on the host: a one-dimensional contiguous array of H unsigned bytes is read in place, anything
+// else (a list, an array of another type or shape, a tensor) goes through mate.py's conversion, which
+// accepts or refuses it.  (A bytes object is text to that conversion, not an array.)
 struct HeadKinds {
   Py_buffer view;
   HeadKinds(PyObject* o, int H) {
-    if (PyObject_CheckBuffer(o) && PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) == 0) {
-      if (view.itemsize == 1 && view.len == H) return;
-      PyBuffer_Release(&view);
+    if (!PyBytes_Check(o) && PyObject_CheckBuffer(o)) {
+      if (PyObject_GetBuffer(o, &view, PyBUF_ND | PyBUF_FORMAT) == 0) {
+        if (view.ndim == 1 && view.len == H && view.itemsize == 1 && view.format && !std::strcmp(view.format, "B")) return;
+        PyBuffer_Release(&view);
+      } else {
+        PyErr_Clear();
+      }
     }
-    PyErr_Clear();
     PyObject* converted = PyObject_CallFunction(to_head_kinds, "Oi", o, H);
     if (!converted) throw PyFailure();
     const int bad = PyObject_GetBuffer(converted, &view, PyBUF_SIMPLE);  // (the view keeps it alive)

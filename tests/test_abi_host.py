@@ -88,6 +88,34 @@ def test_misaligned_workspace_is_refused_on_the_host(mate, offset):
         assert mate.mate_attn_bwd(*bwd, fake + offset, 1 << 40, None) == mate.MATE_ERR_WORKSPACE
 
 
+@pytest.mark.parametrize("call", ["attn_fwd", "attn_bwd", "attn_fwd_dense", "attn_bwd_dense"])
+def test_head_kinds_must_be_one_per_head(mate, call):
+    """Whatever converts to a uint8 array of shape (H,) is taken, nothing else; host tensors get past this check
+    and are then refused for not being on the device, so no kernel is launched."""
+    import array
+    import torch
+    H, N = 4, 128
+    x = torch.zeros(1, H, N, 64, dtype=torch.bfloat16)
+    lse = torch.zeros(1, H, N)
+    ids = [torch.zeros(1, N, dtype=t) for t in (torch.int32, torch.int32, torch.uint8)]
+    tables = mate.Segments(torch.zeros(mate.mate_segments_bytes(1, N), dtype=torch.uint8), 1, N)
+    where = ids if call.endswith("dense") else [tables]
+    tensors = [x] * 3 if "fwd" in call else [x, x, x, x, lse, x]
+    f = lambda kinds: getattr(mate, call)(*tensors, *where, kinds, 0.125)
+    kinds = np.array([0, 1, 0, 1], np.uint8)
+    for good in (kinds, [0, 1, 0, 1], kinds.astype(np.int64), kinds.astype(bool), torch.from_numpy(kinds),
+                 np.repeat(kinds, 2)[::2], bytearray(kinds), memoryview(kinds), array.array("B", [0, 1, 0, 1])):
+        with pytest.raises(ValueError, match="device tensor"):
+            f(good)
+    for bad in (kinds.reshape(H, 1), kinds.reshape(2, 2), kinds[None], kinds[:3], np.zeros(5, np.uint8), [], 0,
+                kinds[:2].view(np.uint16), [[0, 1, 0, 1]]):
+        with pytest.raises(AssertionError):
+            f(bad)
+    with pytest.raises(ValueError) as e:
+        f(bytes(kinds))
+    assert "device tensor" not in str(e.value)
+
+
 def test_argument_errors_of_the_later_entry_points(mate):
     fake = 0x1000  # never dereferenced
     bb = mate.mate_build_segments_bucketed
