@@ -342,7 +342,11 @@ mate_status mate_out_project_bwd(const void* o, const void* w_o, const uint8_t* 
  * bracketed by hipEventRecord(start_event) and hipEventRecord(stop_event) on the stream of that
  * call; the hook disarms itself once used.  The events are hipEvent_t handles passed as void*,
  * created with timing enabled and owned by the caller.  kernel = MATE_KERNEL_NONE disarms.
- * This is the only state the library keeps (per host thread).
+ * Up to 256 positions the backward of the dense-mask variant is one launch; both of its names mean
+ * that one.  The kernels of MATE_F32 have no name.
+ * The hook is per host thread.  The library keeps no other state that a caller can see: besides it a
+ * counter that numbers the forward calls of the process, the static array of
+ * mate_attn_bwd_dense_static, and launch settings per device.
  */
 enum { MATE_KERNEL_NONE = 0, MATE_KERNEL_BUILD = 1, MATE_KERNEL_FWD = 2, MATE_KERNEL_BWD_DQ = 3,
        MATE_KERNEL_BWD_DKV = 4, MATE_KERNEL_FWD_DENSE = 5, MATE_KERNEL_BWD_DQ_DENSE = 6,

@@ -1,5 +1,6 @@
 // C ABI entry points: argument validation on the host, then kernel launches on the caller's
-// stream.  No allocation; the only global state is the counter behind next_ticket().
+// stream.  No allocation; what outlives a call: the counter behind next_ticket(), the measurement hook (per host
+// thread), and per device the address of `scratch` and which kernels were allowed more than 64 KB of LDS.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -438,9 +439,10 @@ mate_status mate_attn_bwd_dense_static(const void* q, const void* k, const void*
   a.q = q; a.k = k; a.v = v; a.o = out; a.dout = dout;
   a.lse = const_cast<float*>(lse);
   a.dq = dq; a.dk = dk; a.dv = dv;
-  // Nothing has to be cleared: the dQ kernel writes both arrays at every position before the
-  // dK/dV kernel reads them, for this call's (B, H, N); what an earlier call left behind lies
-  // beyond that or is overwritten.
+  // Nothing has to be cleared: where the backward is two launches (above 256 positions; the single launch
+  // below that uses no scratch) the dQ kernel writes both arrays at every position before the dK/dV
+  // kernel reads them, for this call's (B, H, N); what an earlier call left behind lies beyond that or
+  // is overwritten.
   a.delta = static_cast<float*>(ws);
   a.nlse = reinterpret_cast<float*>(static_cast<char*>(ws) + delta_bytes(B, H, N));
   return launch_bwd_dense(a, static_cast<hipStream_t>(stream)) == hipSuccess ? MATE_OK : MATE_ERR_HIP;

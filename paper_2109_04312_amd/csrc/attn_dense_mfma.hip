@@ -554,7 +554,7 @@ hipError_t launch_bwd_small(const DenseArgs& a, hipStream_t stream) {
   using S = SmallShape<NW>;
   const hipError_t e = allow_lds<&bwd_dense_small_kernel<NW>>(S::kLds);
   if (e != hipSuccess) return e;
-  ProfileScope prof(7, stream);
+  ProfileScope prof(7, stream, 6);
   hipLaunchKernelGGL(bwd_dense_small_kernel<NW>, dim3(a.B * a.H), dim3(64 * NW), S::kLds, stream, a);
   return hipGetLastError();
 }

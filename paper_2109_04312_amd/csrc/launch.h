@@ -44,8 +44,8 @@ struct DenseArgs {
   float scale;
 };
 
-// Measurement hook: when `kernel` matches the kernel about to be launched, record `start`
-// before and `stop` after that one launch on its stream, then disarm.
+// Measurement hook: when `kernel` matches the kernel about to be launched (or `also`, for a launch that does the
+// work of two), record `start` before and `stop` after that one launch on its stream, then disarm.
 struct ProfileHook {
   int kernel;
   hipEvent_t start, stop;
@@ -54,7 +54,8 @@ extern thread_local ProfileHook g_profile_hook;
 struct ProfileScope {
   hipStream_t stream;
   bool armed;
-  ProfileScope(int kernel, hipStream_t s) : stream(s), armed(g_profile_hook.kernel == kernel) {
+  ProfileScope(int kernel, hipStream_t s, int also = -1)
+      : stream(s), armed(g_profile_hook.kernel == kernel || g_profile_hook.kernel == also) {
     if (armed) (void)hipEventRecord(g_profile_hook.start, stream);
   }
   ~ProfileScope() {

@@ -89,3 +89,30 @@ def test_dense_rejects_what_it_does_not_support():
 def test_dense_edges_of_the_one_launch_backward(N):
     """Lengths at the edges of its 32-row blocks, its workgroup sizes (64, 128, 256) and its range."""
     check_dense(small_workload(N, "bf16", N=N, max_rows=9, max_cols=5, max_global=9, scatter=N % 2 == 1))
+
+
+@pytest.mark.parametrize("N", [40, 128, 256, 300])
+@pytest.mark.parametrize("kernel", ["MATE_KERNEL_BWD_DQ_DENSE", "MATE_KERNEL_BWD_DKV_DENSE"])
+def test_dense_backward_answers_to_both_profile_names(N, kernel):
+    """One launch (N <= 256) or two: a hook armed with either name records within the call and is then
+    disarmed, so that a later call leaves the events alone."""
+    from paper_2109_04312_amd import mate
+    w = small_workload(N, "bf16", N=N, max_rows=9, max_cols=5, max_global=9)
+    ids = hp.dev_structure(w.structure)
+    q, k, v, do = (hp.to_dev(x, "bf16") for x in (w.q, w.k, w.v, w.do))
+    out, lse = mate.attn_fwd_dense(q, k, v, *ids, w.head_kind, w.scale)
+    step = lambda: mate.attn_bwd_dense(q, k, v, out, lse, do, *ids, w.head_kind, w.scale)
+    start, stop, mark = (torch.cuda.Event(enable_timing=True) for _ in range(3))
+    for e in (start, stop):
+        e.record()                        # creates the handle
+    torch.cuda.synchronize()
+    mark.record()
+    assert mate.mate_profile_kernel(getattr(mate, kernel), start.cuda_event, stop.cuda_event) == mate.MATE_OK
+    step()
+    torch.cuda.synchronize()
+    assert mark.elapsed_time(start) >= 0 and start.elapsed_time(stop) > 0   # both recorded after the mark
+    mark.record()
+    step()
+    torch.cuda.synchronize()
+    assert stop.elapsed_time(mark) >= 0                                     # and not again
+    assert mate.mate_profile_kernel(mate.MATE_KERNEL_NONE, None, None) == mate.MATE_OK
