@@ -190,6 +190,11 @@ mate_status mate_segments_export_windows(const void* segments, int B, int N, int
  *   out         [B, H, N, D] dtype t;  lse [B, H, N] float
  *   workspace   mate_workspace_bytes(..., 0) bytes (may be NULL if that is 0)
  *
+ * Infinities and NaN: with MATE_F32 a row of q, k, v (or dout) reaches exactly the outputs of the tokens that
+ * meet it, forward and backward.  With MATE_BF16, here and in the dense-mask variant, it can also turn
+ * outputs of tokens that share a tile of the sorted order with it into NaN (a masked weight of 0 is
+ * multiplied with it).
+ *
  * Asynchronous on `stream`, so what only the device can see is not in the return value:
  *   - `segments` must point to mate_segments_bytes(B, N) bytes.  If they do not hold tables
  *     built for this (B, N) (never built, or built for another shape) every workgroup leaves

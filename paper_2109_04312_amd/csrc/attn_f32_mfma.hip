@@ -104,6 +104,52 @@ __device__ __forceinline__ void accumulate(f32x16 (&acc)[2], const float* tile, 
   }
 }
 
+// The same for a tile that may hold an infinity or a NaN.  The matrix instruction multiplies every weight with
+// every row, and 0 x Inf is NaN: such a row would reach the owned rows that do not meet it.  So these rows
+// go through the vector ALU, owned rows that meet them only, and are cleared for the matrix instruction.
+// In the main loops this would take 30 to 40 registers that are not there; a wavefront whose results are
+// not all finite when its loop ends does its tiles again this way, without a prefetch.  (Looking for such values
+// in every tile instead of in the results: 88.8 us a training step for 85.6.)
+__device__ __forceinline__ void accumulate_special(f32x16 (&acc)[2], float* tile, int m, int hl, f32x16& p,
+                                                   const WindowMask& mask) {
+  const int lane = 32 * hl + m;
+#pragma unroll 1
+  for (int row = 0; row < kRows; ++row) {
+    float* const x = tile + row * kStride;
+    if (!__any((__float_as_uint(x[lane]) & 0x7fffffffu) >= 0x7f800000u)) continue;
+    const int reg = 4 * (row >> 3) + (row & 3), half = (row >> 2) & 1;  // where the row's weights are: c_row(reg, half)
+    float w = 0.f;
+#pragma unroll
+    for (int c = 0; c < 16; ++c) {
+      w = c == reg ? p[c] : w;
+      p[c] = c == reg && hl == half ? 0.f : p[c];
+    }
+    w = __shfl(w, 32 * half + m, 64);
+    const bool in = mask.meets(row, hl);
+#pragma unroll
+    for (int c = 0; c < 16; c += 4)
+#pragma unroll
+      for (int db = 0; db < 2; ++db) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(x + 32 * db + 2 * c + 4 * hl);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[db][c + e] = in ? fmaf(w, v[e], acc[db][c + e]) : acc[db][c + e];
+      }
+    x[lane] = 0.f;
+  }
+  accumulate(acc, tile, m, hl, p);
+}
+
+// Is any value infinite or NaN?  (v_maximum3 keeps a NaN; assembly, because the build lets the compiler assume that
+// there is none.  The compiler does not know that assembly may read a matrix result too early, so the chain
+// starts with an instruction of its own that waits for both accumulators.)
+__device__ __forceinline__ bool any_special(const f32x16 (&acc)[2]) {
+  float x = __uint_as_float(max(__float_as_uint(acc[0][0]) & 0x7fffffffu, __float_as_uint(acc[1][0]) & 0x7fffffffu));
+#pragma unroll
+  for (int i = 0; i < 32; i += 2)
+    asm("v_maximum3_f32 %0, |%1|, |%2|, %0" : "+v"(x) : "v"(acc[i >> 4][i & 15]), "v"(acc[i >> 4][(i & 15) + 1]));
+  return __any(__float_as_uint(x) >= 0x7f800000u);
+}
+
 // Loads and stores stay on their side of this (the compiler sinks a prefetch to its first use otherwise).
 __device__ __forceinline__ void keep_order() { asm volatile("" ::: "memory"); }
 
@@ -249,16 +295,8 @@ __global__ __launch_bounds__(kThreads, 3) void fwd_f32_kernel(AttnArgs a) {
   const float sc = a.scale * kLog2e;  // scores are kept raw; exp2(s sc - m sc)
   f32x16 o[2] = {zero16(), zero16()};
   float m_run = -INFINITY, l_run = 0.f;
-  for (int t = t0; t < r.n; t += kWaves) {
-    const int tok_after = r.token(t + 2 * kWaves, m);
-    key.put(tile, lane);
-    key.load(K, tok_next, lane);                          // the next tile's keys land during this one
-    keep_order();
-    f32x16 s = contract(tile, own, m, hl, zero16());      // S^T = K Q^T
-    val.put(tile, lane);                                  // (the keys have been read)
-    val.load(V, tok_next, lane);
-    keep_order();
-    const WindowMask mask = r.mask(t, hl);
+  // S^T -> P^T of a tile, O and the row sum rescaled
+  auto probs = [&](f32x16& s, const WindowMask& mask) {
 #pragma unroll
     for (int c = 0; c < 16; ++c) s[c] = mask.in(0, c) ? s[c] : -INFINITY;
     float mx = s[0];
@@ -276,23 +314,52 @@ __global__ __launch_bounds__(kThreads, 3) void fwd_f32_kernel(AttnArgs a) {
       s[c] = __builtin_amdgcn_exp2f(fmaf(s[c], sc, -msc));
       l_run += s[c];
     }
+  };
+  for (int t = t0; t < r.n; t += kWaves) {
+    const int tok_after = r.token(t + 2 * kWaves, m);
+    key.put(tile, lane);
+    key.load(K, tok_next, lane);                          // the next tile's keys land during this one
+    keep_order();
+    f32x16 s = contract(tile, own, m, hl, zero16());      // S^T = K Q^T
+    val.put(tile, lane);                                  // (the keys have been read)
+    val.load(V, tok_next, lane);
+    keep_order();
+    probs(s, r.mask(t, hl));
     accumulate(o, tile, m, hl, s);                        // O^T += V^T P^T
     tok_next = tok_after;
+  }
+  if (__builtin_expect(any_special(o), 0)) {
+    o[0] = o[1] = zero16();
+    m_run = -INFINITY;
+    l_run = 0.f;
+    for (int t = t0; t < r.n; t += kWaves) {
+      tok = r.token(t, m);
+      key.load(K, tok, lane);
+      key.put(tile, lane);
+      f32x16 s = contract(tile, own, m, hl, zero16());
+      val.load(V, tok, lane);
+      val.put(tile, lane);
+      const WindowMask mask = r.mask(t, hl);
+      probs(s, mask);
+      accumulate_special(o, tile, m, hl, s, mask);
+    }
   }
   // the wavefronts' maxima and sums, then their sum of O scaled to the common maximum
   const float l_tot = half_sum(l_run);
   if (hl == 0) stat[wave][m] = make_float2(m_run, l_tot);
   __syncthreads();
+  // (a wavefront without a maximum has a sum of zero, or of NaN if it met scores of NaN only)
+  auto weight = [&](float mx, float m_all) { return mx == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((mx - m_all) * sc); };
   float m_all = -INFINITY, l_all = 0.f;
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) m_all = fmaxf(m_all, stat[w][m].x);
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) {
     const float2 ml = stat[w][m];
-    if (ml.x != -INFINITY) l_all += ml.y * __builtin_amdgcn_exp2f((ml.x - m_all) * sc);
+    l_all += ml.y * weight(ml.x, m_all);
   }
   if (wave == 0 && hl == 0 && r.valid) a.lse[bh + r.pos] = (m_all * sc + __builtin_amdgcn_logf(l_all)) * kLn2;
-  const float mul = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run - m_all) * sc) / l_all;
+  const float mul = weight(m_run, m_all) / l_all;
   store_sum(o, mul, lds, own, O, wave, m, hl);
 }
 
@@ -351,6 +418,11 @@ __global__ __launch_bounds__(kThreads, 3) void bwd_dq_f32_kernel(AttnArgs a) {
   float* tile = lds + wave * kTileFloats;
 
   f32x16 dq[2] = {zero16(), zero16()};
+  auto dscores = [&](f32x16& s, const f32x16& dp, const WindowMask& mask) {  // S^T -> dS^T
+#pragma unroll
+    for (int c = 0; c < 16; ++c)
+      s[c] = mask.in(0, c) ? __builtin_amdgcn_exp2f(fmaf(s[c], sc, -lse2)) * (dp[c] - delta) : 0.f;
+  };
   for (int t = t0; t < r.n; t += kWaves) {
     const int tok_after = r.token(t + 2 * kWaves, m);
     val.put(tile, lane);
@@ -361,12 +433,27 @@ __global__ __launch_bounds__(kThreads, 3) void bwd_dq_f32_kernel(AttnArgs a) {
     key.load(K, tok_next, lane);
     keep_order();
     f32x16 s = contract(tile, own_q, m, hl, zero16());         // S^T  = K Q^T
-    const WindowMask mask = r.mask(t, hl);
-#pragma unroll
-    for (int c = 0; c < 16; ++c)
-      s[c] = mask.in(0, c) ? __builtin_amdgcn_exp2f(fmaf(s[c], sc, -lse2)) * (dp[c] - delta) : 0.f;
+    dscores(s, dp, r.mask(t, hl));
     accumulate(dq, tile, m, hl, s);                            // dQ^T += K^T dS^T
     tok_next = tok_after;
+  }
+  if (__builtin_expect(any_special(dq), 0)) {
+    dq[0] = dq[1] = zero16();
+    for (int t = t0; t < r.n; t += kWaves) {
+      tok = r.token(t, m);
+      val.load(V, tok, lane);
+      val.put(tile, lane);
+      keep_order();
+      const f32x16 dp = contract(tile, own_g, m, hl, zero16());
+      keep_order();
+      key.load(K, tok, lane);
+      key.put(tile, lane);
+      keep_order();
+      f32x16 s = contract(tile, own_q, m, hl, zero16());
+      const WindowMask mask = r.mask(t, hl);
+      dscores(s, dp, mask);
+      accumulate_special(dq, tile, m, hl, s, mask);
+    }
   }
   __syncthreads();
   store_sum(dq, a.scale, lds, own_q, dQ, wave, m, hl);
@@ -416,6 +503,17 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dkv_f32_kernel(AttnArgs a) {
   const float sc = a.scale * kLog2e;
 
   f32x16 dk[2] = {zero16(), zero16()}, dv[2] = {zero16(), zero16()};
+  // S -> P, dP -> dS.  (A pair outside the pattern has P = 0 and so dS = 0, unless a value is not finite: then dS is
+  // masked as well, in the second pass.)
+  auto dscores = [&](f32x16& s, f32x16& dp, const WindowMask& mask, bool mask_ds) {
+#pragma unroll
+    for (int c = 0; c < 16; ++c) {
+      const float l = __shfl(row_lse, c_row(c, hl), 64), d = __shfl(row_delta, c_row(c, hl), 64);
+      s[c] = mask.in(0, c) ? __builtin_amdgcn_exp2f(fmaf(s[c], sc, -l * kLog2e)) : 0.f;
+      dp[c] = s[c] * (dp[c] - d);
+      if (mask_ds) dp[c] = mask.in(0, c) ? dp[c] : 0.f;
+    }
+  };
   for (int t = t0; t < r.n; t += kWaves) {
     const int tok_after = r.token(t + 2 * kWaves, m);
     qry.put(tile_q, lane);
@@ -425,19 +523,31 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dkv_f32_kernel(AttnArgs a) {
     keep_order();
     f32x16 s = contract(tile_q, own_k, m, hl, zero16());   // S  = Q K^T
     f32x16 dp = contract(tile_g, v_own, m, hl, zero16());  // dP = dO V^T
-    const WindowMask mask = r.mask(t, hl);
-#pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      const float l = __shfl(row_lse, c_row(c, hl), 64), d = __shfl(row_delta, c_row(c, hl), 64);
-      s[c] = mask.in(0, c) ? __builtin_amdgcn_exp2f(fmaf(s[c], sc, -l * kLog2e)) : 0.f;  // P
-      dp[c] = s[c] * (dp[c] - d);                                                       // dS
-    }
+    dscores(s, dp, r.mask(t, hl), false);
     row_lse = lse[tok_next];
     row_delta = delta[tok_next];
     keep_order();
     accumulate(dv, tile_g, m, hl, s);                      // dV^T += dO^T P
     accumulate(dk, tile_q, m, hl, dp);                     // dK^T += Q^T dS
     tok_next = tok_after;
+  }
+  if (__builtin_expect(any_special(dk) || any_special(dv), 0)) {
+    dk[0] = dk[1] = dv[0] = dv[1] = zero16();
+    for (int t = t0; t < r.n; t += kWaves) {
+      tok = r.token(t, m);
+      row_lse = lse[tok];
+      row_delta = delta[tok];
+      qry.load(Q, tok, lane);
+      qry.put(tile_q, lane);
+      grad.load(dO, tok, lane);
+      grad.put(tile_g, lane);
+      f32x16 s = contract(tile_q, own_k, m, hl, zero16());
+      f32x16 dp = contract(tile_g, v_own, m, hl, zero16());
+      const WindowMask mask = r.mask(t, hl);
+      dscores(s, dp, mask, true);
+      accumulate_special(dv, tile_g, m, hl, s, mask);
+      accumulate_special(dk, tile_q, m, hl, dp, mask);
+    }
   }
   __syncthreads();
   store_sum(dk, a.scale, lds, own_k, dK, wave, m, hl);

@@ -62,6 +62,8 @@ struct WindowMask {
   __device__ __forceinline__ bool in(int blk, int c) const {
     return (unsigned)(d0 + blk * 32 + 8 * (c >> 2) + (c & 3)) < (unsigned)len;
   }
+  // tile row `row` of block 0, whichever lane half holds its score
+  __device__ __forceinline__ bool meets(int row, int hl) const { return (unsigned)(d0 - 4 * hl + row) < (unsigned)len; }
   __device__ __forceinline__ float keep(int c, float x, float other) const {
     const unsigned in = (unsigned)__builtin_amdgcn_sbfe((int)bits, 8 * (c >> 2) + (c & 3), one);
     return __uint_as_float((__float_as_uint(x) & in) | (__float_as_uint(other) & ~in));

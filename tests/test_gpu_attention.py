@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import mate_oracle as orc
 from paper_2109_04312_amd import synth
 from tests import helpers as hp
 
@@ -364,3 +365,63 @@ def test_bf16_tile_edges(n_global, rows, cols, cell, N, rise):
     q, k, v, do = synth.draw_tensors(np.random.default_rng(N), 1, 2, N, 64, "bf16", 4)
     k = synth.round_to_bf16(k * (1 + rise * np.arange(N, dtype=np.float32)[:, None] / N))
     check_workload(synth.Workload(f"bf16 edges {N}", "bf16", st, np.array([ROW, COL], np.uint8), q, k, v, do, 0.125), rise == 0)
+
+
+def pairwise_reference(w, bad):
+    """Forward and backward in float64 from explicit key and query lists, so that a value of a token reaches exactly
+    the tokens that meet it (a masked matrix product would multiply it with zeros).  {(b, h): dict}, on tensors
+    `bad` = (q, k, v, do)."""
+    st, ref = w.structure, {}
+    for b in range(st.B):
+        for h, kind in enumerate(w.head_kind):
+            meets = orc.attention_mask(st.row_ids[b], st.col_ids[b], st.flags[b], int(kind)).astype(bool)
+            q, k, v, do = (x[b, h].astype(np.float64) for x in bad)
+            d = {n: np.zeros_like(q) for n in ("o", "dq", "dk", "dv")}
+            d["lse"] = np.zeros(len(q))
+            p, ds = np.zeros(meets.shape), np.zeros(meets.shape)
+            for i in np.flatnonzero(meets.any(1)):
+                keys = np.flatnonzero(meets[i])
+                s = w.scale * (k[keys] @ q[i])
+                mx = s.max()
+                e = np.exp(s - mx)
+                d["o"][i] = (e / e.sum()) @ v[keys]
+                d["lse"][i] = mx + np.log(e.sum())
+                p[i, keys] = np.exp(s - d["lse"][i])
+                ds[i, keys] = p[i, keys] * (v[keys] @ do[i] - do[i] @ d["o"][i])
+                d["dq"][i] = w.scale * (ds[i, keys] @ k[keys])
+            for j in np.flatnonzero(meets.any(0)):
+                rows = np.flatnonzero(meets[:, j])
+                d["dk"][j] = w.scale * (ds[rows, j] @ q[rows])
+                d["dv"][j] = p[rows, j] @ do[rows]
+            ref[(b, h)] = d
+    return ref
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("tensor", ["q", "k", "v", "do"])
+@pytest.mark.parametrize("whole_row", [False, True])
+def test_f32_special_values_reach_only_the_tokens_that_meet_them(tensor, value, whole_row):
+    """An Inf or NaN in one row of an input: outputs are non-finite exactly where the definition makes them so, and
+    right everywhere else.  The table token is the last of its row and column (tiles repeat the last one)."""
+    from paper_2109_04312_amd import mate
+    n_global, rows, cols, cell, N = 33, 9, 5, 4, 230
+    st = synth._stack([synth.flatten_table(N, n_global, rows, cols, np.full(rows * cols, cell))])
+    t = dict(zip(("q", "k", "v", "do"), synth.draw_tensors(np.random.default_rng(3), 1, 2, N, 64, "f32", 4)))
+    w = synth.Workload("special", "f32", st, np.array([ROW, COL], np.uint8), *t.values(), 0.125)
+    at = n_global + rows * cols * cell - 1
+    assert st.flags[0, at] == synth.TOK_LOCAL and st.flags[0, at + 1] == synth.TOK_PAD
+    t[tensor][0, :, at, slice(None) if whole_row else 17] = value
+    with np.errstate(all="ignore"):
+        ref = pairwise_reference(w, t.values())
+    ids = hp.dev_structure(st)
+    q, k, v, do = (hp.to_dev(x, "f32") for x in t.values())
+    seg = mate.build_segments(*ids)
+    out, lse = mate.attn_fwd(q, k, v, seg, w.head_kind, w.scale)
+    got = dict(zip(("o", "lse", "dq", "dk", "dv"), (out, lse, *mate.attn_bwd(q, k, v, out, lse, do, seg, w.head_kind, w.scale))))
+    for (b, h), d in ref.items():
+        for name, r in d.items():
+            g = got[name][b, h].double().cpu().numpy()
+            fine = np.isfinite(r)
+            print(tensor, value, h, name, "finite", int(fine.sum()), "of", fine.size, flush=True)
+            assert np.array_equal(np.isfinite(g), fine), (name, h)
+            assert np.abs(g[fine] - r[fine]).max(initial=0.0) <= 1e-4, (name, h)
