@@ -69,6 +69,12 @@ __device__ inline float sum8(bf16x8 p, float acc) {
   return acc;
 }
 
+// The same for two values in a word.
+__device__ inline float sum2(unsigned p, float acc) {
+  const bf16x2 one = {(__bf16)1.0f, (__bf16)1.0f};
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p), one, acc, false);
+}
+
 __device__ inline bf16x8 as_bf16x8(uint4 v) {
   union { uint4 u; bf16x8 b; } x;
   x.u = v;

@@ -367,6 +367,24 @@ def test_bf16_tile_edges(n_global, rows, cols, cell, N, rise):
     check_workload(synth.Workload(f"bf16 edges {N}", "bf16", st, np.array([ROW, COL], np.uint8), q, k, v, do, 0.125), rise == 0)
 
 
+@pytest.mark.parametrize("bits", [12, 14, 50, 95, 110, 140])
+@pytest.mark.parametrize("n_global,rows,cols,cell,N", [(31, 3, 2, 40, 271), (70, 2, 3, 100, 670), (40, 90, 5, 4, 2100)])
+def test_bf16_scores_that_rise_in_steps(n_global, rows, cols, cell, N, bits):
+    """Every fifth of the sequence scores 2^bits more than the one before: below 2^13 per tile the softmax reference
+    stays, up to 2^100 the sums are scaled by a power of two, beyond that the tile is done again."""
+    st = synth._stack([synth.flatten_table(N, n_global, rows, cols, np.full(rows * cols, cell))])
+    rng = np.random.default_rng(bits)
+    q, k, v = synth.draw_tensors(rng, 1, 2, N, 64, "bf16", 3)
+    u = np.full(64, 0.125, np.float32)
+    step = np.arange(N, dtype=np.float32) * 5 // N
+    q = synth.round_to_bf16(0.3 * q + 16.0 * u)
+    k = synth.round_to_bf16(0.3 * k + (step * bits * np.log(2) / (0.125 * 16.0))[:, None] * u)
+    w = synth.Workload(f"steps{bits}_{N}", "bf16", st, np.array([ROW, COL], np.uint8), q, k, v, None, 0.125)
+    check_workload(w, backward=False)
+    if N <= 1024:
+        print(hp.report(hp.compare(hp.run_hip(w, False, dense=True)[0], hp.run_oracle(w, False), w, "dense steps")))
+
+
 def pairwise_reference(w, bad):
     """Forward and backward in float64 from explicit key and query lists, so that a value of a token reaches exactly
     the tokens that meet it (a masked matrix product would multiply it with zeros).  {(b, h): dict}, on tensors
