@@ -172,9 +172,10 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
 
 // (four workgroups per CU: with three, the column-head units of the benchmark shape do not all
 // fit at once and the stragglers double the kernel's critical path)
+template <bool kJoin>
 __global__ __launch_bounds__(kThreads, 4) void bwd_dq_mfma_kernel(AttnArgs a) {
   Work w;
-  if (!take_unit<true>(a, blockIdx.x, w)) return;
+  if (!take_unit<true, kJoin>(a, blockIdx.x, w)) return;
   bwd_dq_unit(a, w);
 }
 
@@ -291,6 +292,7 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
 }
 
 // dQ rows of the question tokens of one (sequence, head) from the dq kernel's chunk partials.
+template <bool kJoin>
 __device__ __forceinline__ void merge_dq(const AttnArgs& a, int bh_i, char* stage, int* row_tok) {
   const int b = bh_i / a.H, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -299,7 +301,8 @@ __device__ __forceinline__ void merge_dq(const AttnArgs& a, int bh_i, char* stag
   const int h_magic = a.seg.hdr[0], h_B = a.seg.hdr[1], h_N = a.seg.hdr[2];
   const int G = cnt[C_G], L = cnt[C_L];
   if (h_magic != kMagic || h_B != a.B || h_N != a.N) return;
-  const GlobalSplit s = global_split(G, L, a.B, a.N);
+  GlobalSplit s = global_split(G, L, a.B, a.N);
+  if (kJoin && s.n_st <= kLongStream) s.n_chunks = joined(s.n_chunks);
   if (s.n_chunks <= 1) return;
   unsigned short* const out[1] = {static_cast<unsigned short*>(a.dq) + (size_t)bh_i * a.N * kD};
   for (int gt = 0; gt < s.n_gt; ++gt) {
@@ -314,33 +317,38 @@ __device__ __forceinline__ void merge_dq(const AttnArgs& a, int bh_i, char* stag
 
 // The first `n_merge` workgroups (a multiple of eight, so that the unit queues keep their XCDs) merge
 // dQ partials: a few microseconds each, out of the way before the kernel's own tail.
+template <bool kJoin>
 __global__ __launch_bounds__(kThreads) void bwd_dkv_mfma_kernel(AttnArgs a, int n_merge) {
   __shared__ __attribute__((aligned(1024))) char lds[NS * kDkvStage];
   __shared__ int row_tok[BM];
   if ((int)blockIdx.x < n_merge) {
-    if ((int)blockIdx.x < a.B * a.H) merge_dq(a, blockIdx.x, lds, row_tok);
+    if ((int)blockIdx.x < a.B * a.H) merge_dq<kJoin>(a, blockIdx.x, lds, row_tok);
     return;
   }
   Work w;
-  if (!take_unit<true>(a, blockIdx.x - n_merge, w)) return;
+  if (!take_unit<true, kJoin>(a, blockIdx.x - n_merge, w)) return;
   bwd_dkv_unit(a, w, lds, row_tok);
 }
 
 }  // namespace
 
-hipError_t launch_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
+template <bool kJoin>
+static hipError_t launch_bwd(const AttnArgs& a, hipStream_t stream) {
   const dim3 grid(unit_grid(a.B, a.H, a.N, a.n_col)), block(kThreads);
   hipError_t e;
   {
     ProfileScope prof(3, stream);
-    hipLaunchKernelGGL(bwd_dq_mfma_kernel, grid, block, 0, stream, a);
+    hipLaunchKernelGGL(bwd_dq_mfma_kernel<kJoin>, grid, block, 0, stream, a);
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   ProfileScope prof(4, stream);
   const int n_merge = may_chunk(a.B, a.N) ? 8 * ((a.B * a.H + 7) / 8) : 0;
-  hipLaunchKernelGGL(bwd_dkv_mfma_kernel, dim3(grid.x + n_merge), block, 0, stream, a, n_merge);
+  hipLaunchKernelGGL(bwd_dkv_mfma_kernel<kJoin>, dim3(grid.x + n_merge), block, 0, stream, a, n_merge);
   return hipGetLastError();
+}
+hipError_t launch_bwd_mfma(const AttnArgs& a, hipStream_t stream) {
+  return joins_chunks(a.B, a.H, a.N) ? launch_bwd<true>(a, stream) : launch_bwd<false>(a, stream);
 }
 
 }  // namespace mate

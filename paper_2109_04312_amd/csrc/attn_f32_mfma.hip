@@ -166,7 +166,7 @@ struct Quarter {
 __device__ inline bool take_quarter(const AttnArgs& a, Quarter& q) {
   q.sub = ((blockIdx.x >> 3) + (blockIdx.x >> 5)) & 3;
   q.turn = blockIdx.x >> 5;
-  if (!take_unit<false>(a, ((blockIdx.x >> 5) << 3) | (blockIdx.x & 7), q.w)) return false;
+  if (!take_unit<false, false>(a, ((blockIdx.x >> 5) << 3) | (blockIdx.x & 7), q.w)) return false;
   const UnitPlan& u = q.w.u;
   if (u.kind == UNIT_PAD) return true;
   // (a chunked question-token owner: its first unit streams everything, there are no partials here)

@@ -223,10 +223,10 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
   store_owned_rows<1>(accs, muls, outs, lds, q_tok, wave, ln);
 }
 
-template <bool kChunksFirst>
+template <bool kChunksFirst, bool kJoin>
 __global__ __launch_bounds__(kThreads, 4) void fwd_mfma_kernel(AttnArgs a) {
   Work w;
-  if (!take_unit<kChunksFirst>(a, blockIdx.x, w)) return;
+  if (!take_unit<kChunksFirst, kJoin>(a, blockIdx.x, w)) return;
   fwd_unit(a, w);
 }
 
@@ -235,8 +235,11 @@ __global__ __launch_bounds__(kThreads, 4) void fwd_mfma_kernel(AttnArgs a) {
 hipError_t launch_fwd_mfma(const AttnArgs& a, hipStream_t stream) {
   ProfileScope prof(2, stream);
   const dim3 grid(unit_grid(a.B, a.H, a.N, a.n_col)), block(kThreads);
-  if (fwd_chunks_first(a.B, a.H, a.N)) hipLaunchKernelGGL(fwd_mfma_kernel<true>, grid, block, 0, stream, a);
-  else hipLaunchKernelGGL(fwd_mfma_kernel<false>, grid, block, 0, stream, a);
+  const bool first = fwd_chunks_first(a.B, a.H, a.N), join = joins_chunks(a.B, a.H, a.N);
+  if (first && join) hipLaunchKernelGGL((fwd_mfma_kernel<true, true>), grid, block, 0, stream, a);
+  else if (join) hipLaunchKernelGGL((fwd_mfma_kernel<false, true>), grid, block, 0, stream, a);
+  else if (first) hipLaunchKernelGGL((fwd_mfma_kernel<true, false>), grid, block, 0, stream, a);
+  else hipLaunchKernelGGL((fwd_mfma_kernel<false, false>), grid, block, 0, stream, a);
   return hipGetLastError();
 }
 

@@ -70,6 +70,14 @@ inline int unit_grid(int B, int H, int N, int n_col) {
 // Question-token units before column-head units in the forward: see above.
 inline bool fwd_chunks_first(int B, int H, int N) { return may_chunk(B, N) && (long)B * H * owner_slots(N) <= 3 * 1024; }
 
+// A launch that is full although B N is small runs the short chunks that its tables list (see chunk_tiles) in pairs:
+// an even chunk takes the odd one after it along, whose workgroup leaves.  (A template argument of the kernels: as a
+// kernel argument it cost the short launches, which have none of it, 0.3 us each.)
+inline bool joins_chunks(int B, int H, int N) {
+  return may_chunk(B, N) && (long)B * N <= kSmallBatch && (long)B * H * owner_slots(N) > kFullLaunch;
+}
+__host__ __device__ inline int joined(int n_chunks) { return (n_chunks + 1) >> 1; }
+
 // Entry i of the head order.  A byte indexed by a run-time value would be fetched with a vector
 // load (a memory round trip at the start of every workgroup); the containing 32-bit word comes
 // through the scalar cache with the other kernel arguments.
@@ -91,7 +99,7 @@ __device__ inline int uniform_div(int x, int d, int& rest) {
 
 // Returns false if this workgroup has nothing to do.  Everything here is wave-uniform and
 // stays in scalar registers.
-template <bool kChunksFirst>
+template <bool kChunksFirst, bool kJoin>
 __device__ inline bool take_unit(const AttnArgs& a, int block, Work& w) {
   const int T = a.seg.tiles, U = a.seg.units, N = a.N, n_col = a.n_col, n_row = a.H - n_col;
   const int q = block & 7;
@@ -171,6 +179,15 @@ __device__ inline bool take_unit(const AttnArgs& a, int block, Work& w) {
   u.own_list = glob ? a.seg.global_idx + (size_t)b * N
                     : u.kind == UNIT_LOCAL ? perm_v : a.seg.pad_idx + (size_t)b * N;
   u.own_count = glob ? u.G : u.kind == UNIT_LOCAL ? r1.w : u.P;
+  if (kJoin && glob && u.part >= 0) {
+    const int n_st = u.n_t0 + (u.L + BN - 1) / BN, gt = u.t0 / BM, c = u.part - gt * u.n_chunks;
+    if (n_st <= kLongStream) {
+      if (c & 1) return false;
+      u.t_end = min(n_st, 2 * u.t_end - u.t_begin);
+      u.n_chunks = joined(u.n_chunks);
+      u.part = u.n_chunks > 1 ? gt * u.n_chunks + (c >> 1) : -1;
+    }
+  }
   return true;
 }
 

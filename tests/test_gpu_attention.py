@@ -385,6 +385,29 @@ def test_bf16_scores_that_rise_in_steps(n_global, rows, cols, cell, N, bits):
         print(hp.report(hp.compare(hp.run_hip(w, False, dense=True)[0], hp.run_oracle(w, False), w, "dense steps")))
 
 
+@pytest.mark.parametrize("n_global,table,N,H", [(60, 700, 768, 120),     # 12 tiles: two chunks, joined a whole stream
+                                                (20, 790, 832, 104),     # 14: three
+                                                (40, 1060, 1100, 80),    # 18: three
+                                                (130, 1370, 1500, 64),   # 25, two owner tiles of question tokens
+                                                (64, 2490, 2560, 36),    # 40: five
+                                                (64, 2500, 2600, 36)])   # 41: as the tables list them
+def test_chunks_in_pairs_where_many_heads_fill_the_chip(n_global, table, N, H):
+    """Small batches with many heads run the short chunks of question-token owners in pairs.  All row heads have the same
+    inputs and so have all column heads; one of each is compared with the oracle, the others with it."""
+    cols, cell = 5, 10
+    cells = table // cell
+    st = synth._stack([synth.flatten_table(N, n_global, cells // cols, cols, np.full(cells // cols * cols, cell))])
+    hk = synth.half_row_half_col(H)
+    pair = synth.draw_tensors(np.random.default_rng(N), 1, 2, N, 64, "bf16", 4)
+    w = synth.Workload(f"pairs {N}", "bf16", st, hk, *(np.ascontiguousarray(x[:, hk]) for x in pair), 0.125)
+    got, _ = hp.run_hip(w, True)
+    first = {int(kind): int(np.argmax(hk == kind)) for kind in (ROW, COL)}
+    print(hp.report(hp.compare(got, hp.run_oracle(w, True, [(0, h) for h in first.values()]), w, w.name)), flush=True)
+    for name, x in got.items():
+        for h in range(H):
+            assert np.array_equal(x[0, h], x[0, first[int(hk[h])]]), (name, h)
+
+
 def pairwise_reference(w, bad):
     """Forward and backward in float64 from explicit key and query lists, so that a value of a token reaches exactly
     the tokens that meet it (a masked matrix product would multiply it with zeros).  {(b, h): dict}, on tensors
