@@ -408,6 +408,91 @@ def test_chunks_in_pairs_where_many_heads_fill_the_chip(n_global, table, N, H):
             assert np.array_equal(x[0, h], x[0, first[int(hk[h])]]), (name, h)
 
 
+def chunked_workload(seed, B, N, H, n_global=80):
+    """Sequences filled to the last position, whose question-token owners' streams are cut into several chunks."""
+    rng = np.random.default_rng(seed)
+    cols, cell = 6, 5
+    rows = -(-N // (cols * cell))
+    st = synth._stack([synth.flatten_table(N, n_global, rows, cols, np.full(rows * cols, cell)) for _ in range(B)])
+    hk = synth.half_row_half_col(H)
+    return synth.Workload(f"chunks{seed}", "bf16", st, hk, *synth.draw_tensors(rng, B, H, N, 64, "bf16", 4), 0.125)
+
+
+def arrival_words(ws, B, H, N):
+    """The arrival words at the end of a workspace: one per question-token unit that a sequence can have."""
+    return ws.view(torch.int64)[-B * H * ((N + 127) // 128):].view(B * H, -1)
+
+
+# chunks of 16 tiles (B N > 4096), short ones, short ones in pairs, and two owner tiles of question tokens
+CHUNKED = [(2, 2100, 4, 80), (1, 2100, 4, 80), (1, 1500, 64, 40), (1, 2000, 2, 200)]
+
+
+@pytest.mark.parametrize("B,N,H,n_global", CHUNKED)
+def test_chunked_owners_are_bit_reproducible_whatever_the_workspace_held(B, N, H, n_global):
+    """Which chunk merges depends on the run; what it computes does not.  The forward's words are cleared when it is
+    done, all of a group's or none; the backward's first word of a group has counted the group's chunks."""
+    from paper_2109_04312_amd import mate
+    w = chunked_workload(N + B, B, N, H, n_global)
+    ids = hp.dev_structure(w.structure)
+    seg = mate.build_segments(*ids)
+    q, k, v, do = (hp.to_dev(x, "bf16") for x in (w.q, w.k, w.v, w.do))
+    ws_f, ws_b = (mate.workspace(B, H, N, 64, mate.MATE_BF16, back, "cuda") for back in (False, True))
+    first = None
+    for garbage in (0, 0x5A, 0xFF, 0, 0x5A, 0xFF):
+        ws_f.fill_(garbage)
+        ws_b.fill_(garbage)
+        out, lse = mate.attn_fwd(q, k, v, seg, w.head_kind, w.scale, ws=ws_f)
+        res = (out, lse, *mate.attn_bwd(q, k, v, out, lse, do, seg, w.head_kind, w.scale, ws=ws_b))
+        first = first or res
+        for name, x, y in zip(("out", "lse", "dq", "dk", "dv"), res, first):
+            assert torch.equal(x, y), (name, garbage)
+        if garbage:
+            cleared = (arrival_words(ws_f, B, H, N) == 0).sum(1)
+            counted = arrival_words(ws_b, B, H, N)
+            counted = torch.where((counted > 0) & (counted < 256), counted, 0).sum(1)
+            print("chunks per (sequence, head):", cleared.unique().tolist(), flush=True)
+            assert bool((cleared > 1).all()) and torch.equal(cleared, counted)
+
+
+@pytest.mark.parametrize("B,N,H,n_global", CHUNKED)
+def test_chunked_owners_replay_identically_from_a_captured_graph(B, N, H, n_global):
+    """A captured forward keeps its ticket: its words must be cleared for the next replay, also when other calls
+    have used the same workspace in between."""
+    from paper_2109_04312_amd import mate
+    w = chunked_workload(N - B, B, N, H, n_global)
+    r, c, f = hp.dev_structure(w.structure)
+    q, k, v, do = (hp.to_dev(x, "bf16") for x in (w.q, w.k, w.v, w.do))
+    seg = mate.Segments(torch.zeros(mate.mate_segments_bytes(B, N), dtype=torch.uint8, device="cuda"), B, N)
+    res = dict(out=torch.empty_like(q), lse=torch.empty((B, H, N), dtype=torch.float32, device="cuda"),
+               dq=torch.empty_like(q), dk=torch.empty_like(q), dv=torch.empty_like(q))
+    ws_f, ws_b = (mate.workspace(B, H, N, 64, mate.MATE_BF16, back, "cuda") for back in (False, True))
+
+    def step():
+        mate.build_segments(r, c, f, out=seg)
+        mate.attn_fwd(q, k, v, seg, w.head_kind, w.scale, out=res["out"], lse=res["lse"], ws=ws_f)
+        mate.attn_bwd(q, k, v, res["out"], res["lse"], do, seg, w.head_kind, w.scale,
+                      dq=res["dq"], dk=res["dk"], dv=res["dv"], ws=ws_b)
+
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        step()
+    torch.cuda.synchronize()
+    want = {n: x.clone() for n, x in res.items()}
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        step()
+    for replay in range(6):
+        if replay % 2:
+            step()                       # an eager call on the same buffers
+            torch.cuda.synchronize()
+        for x in res.values():
+            x.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        for n, x in res.items():
+            assert torch.equal(x, want[n]), (replay, n)
+
+
 def pairwise_reference(w, bad):
     """Forward and backward in float64 from explicit key and query lists, so that a value of a token reaches exactly
     the tokens that meet it (a masked matrix product would multiply it with zeros).  {(b, h): dict}, on tensors
