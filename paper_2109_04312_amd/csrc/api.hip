@@ -45,8 +45,9 @@ bool workspace_ok(const void* p, size_t bytes, size_t need, mate_dtype t) {
 }
 
 // The value a call's chunks announce themselves with: never zero, and a 64-bit number that no earlier
-// call of this process has used (the mix below is a bijection) and that uninitialised memory does
-// not hold by accident.
+// call of this process has used and that uninitialised memory does not hold by accident.  One step of
+// SplitMix64 (Steele, Lea and Flood, OOPSLA 2014; the constants are its published ones) from a random start: a
+// counter and a mix that is a bijection.
 unsigned long long next_ticket() {
   static std::atomic<unsigned long long> count{[] {
     std::random_device r;

@@ -62,11 +62,10 @@ __device__ __forceinline__ void merge_chunks(const float* const (&part)[kTensors
 // dQ (and delta)
 // ======================================================================================
 constexpr int kDqStage = 2 * kTileBytes;          // K tile, V tile
-constexpr int NS = 2;                             // LDS stages of the two kernels
 constexpr int kDkvStage = 2 * kTileBytes + 512;   // Q tile, dO tile, -lse/scale[64], -delta[64]
 
 __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
-  __shared__ __attribute__((aligned(1024))) char lds[NS * kDqStage];
+  __shared__ __attribute__((aligned(1024))) char lds[kStages * kDqStage];
   __shared__ int idx_ring[kIdxSlots][BN];
   __shared__ int q_tok[BM];
 
@@ -95,7 +94,7 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
   // Second: the owned rows (registers) and the first K / V tiles (LDS), all in flight together.
   // K and V tiles stream through the LDS ring; K is read both plain (S^T = K Q^T) and
   // transposed (dQ^T += K^T dS^T), V plain (dP^T = V dO^T).
-  TileStream<kDqStage, NS> stream(u, global_idx, lds, idx_ring, K, V, nullptr, 0, wave, lane);
+  TileStream<kDqStage> stream(u, global_idx, lds, idx_ring, K, V, nullptr, 0, wave, lane);
   stream.begin();
   const OwnerSplit split(u, wave);
   const OwnedRow me = owned_row(u, a, b, view, split.block, m);
@@ -148,7 +147,6 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
                       split.end(base, part0 ? u.G : me.w_hi), part0 ? 0 : me.a_lo, part0 ? u.G : me.a_hi);
       dq_tile(Kst, Vst, qf, gf, koff, toff, sc, lse2, delta, mask, dq_acc);
     }
-    stream.release();
   }
   __syncthreads();  // all wavefronts are done reading the stages; reuse them for the epilogue
   int ln = lane;
@@ -213,7 +211,7 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
   // First round trip: the owned rows' positions and the first tiles' token indices; second:
   // the owned K / V rows (registers) and the first tiles (LDS).
   const float* row_src = wave == 0 ? a.nlse + bh : wave == 1 ? a.delta + bh : nullptr;
-  TileStream<kDkvStage, NS> stream(u, global_idx, lds, idx_ring, Q, dO, row_src,
+  TileStream<kDkvStage> stream(u, global_idx, lds, idx_ring, Q, dO, row_src,
                                2 * kTileBytes + 256 * wave, wave, lane);
   stream.begin();
   // `me` is this lane's key; its window is the set of query slots that see it
@@ -250,7 +248,6 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
                       split.end(base, part0 ? u.G : me.w_hi), part0 ? 0 : me.a_lo, part0 ? u.G : me.a_hi);
       dkv_tile(Qst, Gst, lse_row, delta_row, kf, vf, poff, toff, sc, hl, mask, dk_acc, dv_acc);
     }
-    stream.release();
   }
   __syncthreads();  // all wavefronts are done reading the stages; reuse them for the epilogue
   if (split.on) {  // add the other half of the streamed rows
@@ -319,7 +316,7 @@ __device__ __forceinline__ void merge_dq(const AttnArgs& a, int bh_i, char* stag
 // dQ partials: a few microseconds each, out of the way before the kernel's own tail.
 template <bool kJoin>
 __global__ __launch_bounds__(kThreads) void bwd_dkv_mfma_kernel(AttnArgs a, int n_merge) {
-  __shared__ __attribute__((aligned(1024))) char lds[NS * kDkvStage];
+  __shared__ __attribute__((aligned(1024))) char lds[kStages * kDkvStage];
   __shared__ int row_tok[BM];
   if ((int)blockIdx.x < n_merge) {
     if ((int)blockIdx.x < a.B * a.H) merge_dq<kJoin>(a, blockIdx.x, lds, row_tok);

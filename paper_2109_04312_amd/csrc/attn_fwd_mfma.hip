@@ -92,10 +92,8 @@ __device__ __forceinline__ void merge_chunks(const AttnArgs& a, const UnitPlan& 
   flush_rows(O, stage, row_tok, wave, lane);
 }
 
-constexpr int NS = 2;  // LDS stages: small enough for four workgroups per CU
-
 __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
-  __shared__ __attribute__((aligned(1024))) char lds[NS * kStageBytes];
+  __shared__ __attribute__((aligned(1024))) char lds[kStages * kStageBytes];
   __shared__ int idx_ring[kIdxSlots][BN];  // [tile & 7][row] token positions
   __shared__ int q_tok[BM];
   __shared__ int group_done;
@@ -133,7 +131,7 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
   // First round trip: which rows this workgroup owns, and the token indices of the first tiles.
   // Second: the owned query rows (registers) and the first K / V tiles (LDS), all in flight
   // together.
-  TileStream<kStageBytes, NS> stream(u, global_idx, lds, idx_ring, K, V, nullptr, 0, wave, lane);
+  TileStream<kStageBytes> stream(u, global_idx, lds, idx_ring, K, V, nullptr, 0, wave, lane);
   stream.begin();
   const OwnerSplit split(u, wave);
   const OwnedRow me = owned_row(u, a, b, view, split.block, m);
@@ -171,7 +169,6 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
                       split.end(base, part0 ? u.G : me.w_hi), part0 ? 0 : me.a_lo, part0 ? u.G : me.a_hi);
       fwd_tile(Kst, Vst, qf, koff, voff, sc, mask, o_acc, m_run, l_run);
     }
-    stream.release();
   }
   __syncthreads();  // all wavefronts are done reading the stages; reuse them for the epilogue
 

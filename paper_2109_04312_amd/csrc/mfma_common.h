@@ -81,11 +81,6 @@ __device__ inline bf16x8 as_bf16x8(uint4 v) {
   return x.b;
 }
 
-__device__ inline unsigned short f32_to_bf16_bits(float x) {
-  __bf16 h = (__bf16)x;
-  return __builtin_bit_cast(unsigned short, h);
-}
-
 // Two values rounded to bf16 in one word, x in the low half (one instruction).
 __device__ inline unsigned pack2(float x, float y) {
   const bf16x2 r = {(__bf16)x, (__bf16)y};

@@ -388,10 +388,6 @@ __device__ inline void zero_pad_rows(unsigned short* const (&out)[kTensors], con
         *reinterpret_cast<uint4*>(out[x] + (size_t)tok[i] * kD + piece * 8) = make_uint4(0, 0, 0, 0);
 }
 
-__device__ inline bool tables_match(const AttnArgs& a) {
-  return a.seg.hdr[0] == kMagic && a.seg.hdr[1] == a.B && a.seg.hdr[2] == a.N;
-}
-
 // Workspace carving (float words).  Partial buffers are per (b,h): [UG][BM][64].
 __host__ __device__ inline size_t part_words_per_bh(int N) { return (size_t)owner_slots(N) * BM * kD; }
 __host__ __device__ inline size_t stat_words_per_bh(int N) { return (size_t)owner_slots(N) * BM * 2; }
