@@ -265,6 +265,7 @@ struct ProjArgs {
   int F, K;                      // features, contraction length
   int tok_tiles_per_seq;         // ceil(N / tile tokens)
   int feat_tiles;                // ceil(F / tile features)
+  int by_feature;                // which way tiles are dealt to the XCDs, see proj_kernel
   int tile_blocks;               // workgroups of the product; those behind them add `ranges`
   RangeSums ranges;
 };
@@ -288,9 +289,21 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
   // Workgroup -> (token tile, feature tile).  XCD q walks the feature tiles fastest, so the token rows it
   // streams stay in its L2 while the weights cycle, and takes one of every eight consecutive token
   // tiles, another one each time, so that the padding at the end of the sequences is spread over all XCDs.
+  // With few token tiles that leaves XCDs idle or uneven (one of 64 tokens and 6144 x 2048 weights: 48 tiles on
+  // the 32 CUs of one XCD, 29 us); then the feature tiles are dealt instead, and every weight is read by one XCD.
   const int q = blockIdx.x & 7, jx = blockIdx.x >> 3;
-  const int tj = jx / a.feat_tiles, f0 = (jx - tj * a.feat_tiles) * S::kRowsA;
-  const int tt = 8 * tj + ((q + 3 * tj) & 7), b = tt / a.tok_tiles_per_seq, tile = tt - b * a.tok_tiles_per_seq;
+  int tt, f0;
+  if (a.by_feature) {
+    const int n_tt = a.B * a.tok_tiles_per_seq, fj = jx / n_tt;
+    tt = jx - fj * n_tt;
+    f0 = (8 * fj + q) * S::kRowsA;
+    if (f0 >= a.F) return;
+  } else {
+    const int tj = jx / a.feat_tiles;
+    f0 = (jx - tj * a.feat_tiles) * S::kRowsA;
+    tt = 8 * tj + ((q + 3 * tj) & 7);
+  }
+  const int b = tt / a.tok_tiles_per_seq, tile = tt - b * a.tok_tiles_per_seq;
   if (b >= a.B) return;
   const int n0 = tile * S::kRowsB;
   const int rows = min(S::kRowsB, a.N - n0), feats = min(S::kRowsA, a.F - f0);
@@ -422,11 +435,23 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
   }
 }
 
+// Tiles of the busiest XCD, dealt by token or by feature tile, and how many its 32 CUs take one after the other.
+// (By feature where that is fewer: 1024 -> 3072 at 600 tokens, 10 tiles of 64: 17.6 -> 9.3 us; 2048 -> 6144 at 64:
+// 29.4 -> 13.4.  In equal rounds by token: the weights are then read once per token tile from an L2 that keeps them.)
+template <class S>
+long tiles_per_xcd(const ProjArgs& a, bool by_feature) {
+  const long tok = (long)a.B * ((a.N + S::kRowsB - 1) / S::kRowsB), feat = (a.F + S::kRowsA - 1) / S::kRowsA;
+  return by_feature ? (feat + 7) / 8 * tok : (tok + 7) / 8 * feat;
+}
+long rounds(long tiles) { return (tiles + 31) / 32; }
+
 template <class S, bool kHeadTok, bool kTransposedW>
 hipError_t launch_proj(ProjArgs a, int kernel_id, hipStream_t stream) {
   a.tok_tiles_per_seq = (a.N + S::kRowsB - 1) / S::kRowsB;
   a.feat_tiles = (a.F + S::kRowsA - 1) / S::kRowsA;
-  a.tile_blocks = 8 * ((a.B * a.tok_tiles_per_seq + 7) / 8) * a.feat_tiles;
+  const long by_token = tiles_per_xcd<S>(a, false), by_feature = tiles_per_xcd<S>(a, true);
+  a.by_feature = rounds(by_feature) < rounds(by_token);
+  a.tile_blocks = 8 * (int)(a.by_feature ? by_feature : by_token);
   if (a.ranges.splits) a.ranges.blocks = (int)std::max<size_t>(1, std::min<size_t>(1024 * 256 / S::kThreads, a.ranges.n / 4 / S::kThreads));
   const hipError_t e = allow_lds<&proj_kernel<S, kHeadTok, kTransposedW>>(S::kLds);
   if (e != hipSuccess) return e;
@@ -438,7 +463,7 @@ hipError_t launch_proj(ProjArgs a, int kernel_id, hipStream_t stream) {
 
 // Which shape.  A compute unit that gets n tiles of a shape needs about (k / 64) (c2 for every two tiles, c1 for
 // an odd last one) + e n us, measured below (256 CUs, 257 to 12288 tokens, widths 768 and 1024, one tile per CU
-// as well as many), so the shape with the smallest such sum for n = ceil(tiles / 256) wins: large tiles once
+// as well as many), so the shape with the smallest such sum for n = rounds of the busiest XCD wins: large tiles once
 // they fill the chip, smaller ones where they fit its 256 units better.  Measured, us, at 8 x 512 tokens and
 // 768 -> 2304, 768 -> 768, 2304 -> 768 (transposed weights) features: 256 x 256 26, 24; 192 x 128 22, 15; 128 x
 // 128 25, 12, 26; with two groups 30, 11, 22; 128 x 64 27, 11, 23, with two groups 36, 15, 32; at 1 x 512 the last
@@ -453,8 +478,7 @@ using Proj64 = Shape<2, 1, 2, 2, 3, 2>;       // 128 x  64
 using Proj64x2 = Shape<2, 1, 2, 2, 3, 1, 2>;
 template <class S>
 double proj_cost(const ProjArgs& a, double c1, double c2, double e) {
-  const long tiles = (long)a.B * ((a.N + S::kRowsB - 1) / S::kRowsB) * ((a.F + S::kRowsA - 1) / S::kRowsA);
-  const long n = (tiles + 255) / 256;
+  const long n = std::min(rounds(tiles_per_xcd<S>(a, false)), rounds(tiles_per_xcd<S>(a, true)));
   return (a.K / 64) * ((n / 2) * c2 + (n % 2) * c1) + e * n;
 }
 

@@ -272,3 +272,12 @@ def test_workgroup_shapes(B, N, H, E):
 def test_shared_contractions(B, N, H, E):
     check(N, B, N, H, E, pad_tail=N // 5)
     check_bwd(N, B, N, H, E, pad_tail=N // 5)
+
+
+# few token tiles and many feature tiles, dealt to the XCDs by feature: heads or width large, feature tiles that are
+# no multiple of eight, one token, several sequences
+@pytest.mark.parametrize("B,N,H,E", [(1, 1, 36, 128), (1, 64, 36, 128), (1, 600, 12, 768), (2, 65, 2, 5120),
+                                     (1, 130, 66, 256), (3, 100, 34, 128)])
+def test_tiles_dealt_by_feature(B, N, H, E):
+    check(N, B, N, H, E, pad_tail=N // 4)
+    check_bwd(N, B, N, H, E, pad_tail=N // 4)
