@@ -462,13 +462,13 @@ hipError_t launch_proj(ProjArgs a, int kernel_id, hipStream_t stream) {
 }
 
 // Which shape.  A compute unit that gets n tiles of a shape needs about (k / 64) (c2 for every two tiles, c1 for
-// an odd last one) + e n us, measured below (256 CUs, 257 to 12288 tokens, widths 768 and 1024, one tile per CU
-// as well as many), so the shape with the smallest such sum for n = rounds of the busiest XCD wins: large tiles once
-// they fill the chip, smaller ones where they fit its 256 units better.  Measured, us, at 8 x 512 tokens and
-// 768 -> 2304, 768 -> 768, 2304 -> 768 (transposed weights) features: 256 x 256 26, 24; 192 x 128 22, 15; 128 x
-// 128 25, 12, 26; with two groups 30, 11, 22; 128 x 64 27, 11, 23, with two groups 36, 15, 32; at 1 x 512 the last
-// four 11.4, 10.6, 24.7; 11.3, 10.3, 20.2; 9.0, 8.4, 18.6; 8.6, 7.8, 16.4; at 2 x 8192 (12860 not padding) and
-// 1024 -> 3072: 92, 94, 109, -, 143.
+// an odd last one) + e n us, so the shape with the smallest such sum wins, n being the rounds of the busiest XCD:
+// large tiles once they fill the chip, smaller ones where they fit its units better.  The constants were fitted
+// to the times of all six shapes for 912 products (64 to 40000 tokens, widths 128 to 4096, 2 to 32 heads, no
+// padding): the shape that they choose takes 0.2 % more than the fastest one on average and 22 % at most, against
+// 2.4 % and 74 % with constants measured on widths of 768 and 1024 alone and n = ceil(tiles / 256).  For
+// instance, us, 256 x 256, 192 x 128, 128 x 128, with two groups, 128 x 64, with two groups: 2048 -> 6144 at 900
+// tokens 47, 39, 34, 40, 55, 61, at 8 x 512 98, 116, 111, 132, 216, 225; 1024 -> 3072 at 512 tokens 27, 17, 15, 12, 11, 11.
 //                        features x tokens, wavefronts, stages, workgroups per CU, groups
 using Proj256 = Shape<4, 4, 2, 4, 2, 1>;      // 256 x 256
 using Proj192 = Shape<3, 2, 2, 2, 2, 2>;      // 192 x 128  (plain weights; its wavefronts' 96 features are not whole tiles)
@@ -493,13 +493,14 @@ hipError_t launch_proj_any(const ProjArgs& a, int kernel_id, hipStream_t stream)
       launch = l;
     }
   };
-  offer(proj_cost<Proj256>(a, 1.6, 3.2, 3.0), launch_proj<Proj256, kHeadTok, kTransposedW>);
+  offer(proj_cost<Proj256>(a, 1.37, 3.14, 5.33), launch_proj<Proj256, kHeadTok, kTransposedW>);
   if constexpr (!kTransposedW)
-    if (a.F % Proj192::kRowsA == 0) offer(proj_cost<Proj192>(a, 1.0, 1.52, 1.3), launch_proj<Proj192, kHeadTok, kTransposedW>);
-  offer(proj_cost<Proj128>(a, 0.6, 1.04, 1.2), launch_proj<Proj128, kHeadTok, kTransposedW>);
-  offer(proj_cost<Proj128x2>(a, 0.44, 1.1, 2.7), launch_proj<Proj128x2, kHeadTok, kTransposedW>);
-  offer(proj_cost<Proj64>(a, 0.44, 0.66, 0.7), launch_proj<Proj64, kHeadTok, kTransposedW>);
-  offer(proj_cost<Proj64x2>(a, 0.39, 0.78, 0.7), launch_proj<Proj64x2, kHeadTok, kTransposedW>);
+    // (beyond 4608 features it takes up to 23 % more than its constants say)
+    if (a.F % Proj192::kRowsA == 0 && a.F <= 4608) offer(proj_cost<Proj192>(a, 1.17, 1.52, 0.86), launch_proj<Proj192, kHeadTok, kTransposedW>);
+  offer(proj_cost<Proj128>(a, 0.62, 1.09, 1.1), launch_proj<Proj128, kHeadTok, kTransposedW>);
+  offer(proj_cost<Proj128x2>(a, 0.47, 1.2, 1.86), launch_proj<Proj128x2, kHeadTok, kTransposedW>);
+  offer(proj_cost<Proj64>(a, 0.46, 0.74, 0.53), launch_proj<Proj64, kHeadTok, kTransposedW>);
+  offer(proj_cost<Proj64x2>(a, 0.39, 0.8, 0.71), launch_proj<Proj64x2, kHeadTok, kTransposedW>);
   return launch(a, kernel_id, stream);
 }
 
