@@ -201,13 +201,14 @@ __device__ inline void tile_source(const UnitPlan& u, const int* global_idx, int
 // A unit of at most 64 rows has work for two wavefronts; the other two take half of it: wavefronts w and
 // w + 2 own the same 32 rows, w meets the first 32 rows of every streamed tile and w + 2 the last 32, and the
 // two results are added (through LDS) before anything is stored.  Most question-token owners are such units,
-// and they are the longest chain of tiles of a small launch.
+// and they are the longest chain of tiles of a small launch.  (One or two tiles are not worth the addition: forward /
+// backward of one sequence of 64 with 12 heads 6.2/14.7 us split, 5.6/13.1 whole; from three on split is faster.)
 struct OwnerSplit {
   bool on;
   int block;  // the wavefront's 32-row block of owned rows
   int half;   // and of streamed rows
   __device__ inline OwnerSplit(const UnitPlan& u, int wave)
-      : on(u.own_count - u.t0 <= BM / 2), block(on ? wave & 1 : wave), half(wave >> 1) {}
+      : on(u.own_count - u.t0 <= BM / 2 && u.t_end - u.t_begin >= 3), block(on ? wave & 1 : wave), half(wave >> 1) {}
   __device__ inline bool writes(int wave) const { return !on || wave < 2; }
   // [first, end): the part of the slots [lo, hi) met in the tile that begins at slot `base`
   __device__ inline int first(int base, int lo) const { return on ? max(lo, base + 32 * half) : lo; }
