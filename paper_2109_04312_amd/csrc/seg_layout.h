@@ -50,7 +50,7 @@ constexpr int BM = kTileSlots;     // owned rows per workgroup (32 per wavefront
 constexpr int BN = 64;             // streamed rows per tile
 constexpr int kChunkTiles = 16;    // streamed tiles per chunk of a question-token owner (see chunk_tiles)
 constexpr int kSmallBatch = 4096;  // B N up to which a launch can leave much of the chip idle
-constexpr int kLongStream = 40;    // tiles
+constexpr int kLongStream = 40;    // tiles of a stream whose chunks are not joined any more
 constexpr int kFullLaunch = 700;   // table-token tiles of a launch, B H T, from which on it does not
 enum { UNIT_NONE = 0, UNIT_GLOBAL = 1, UNIT_LOCAL = 2, UNIT_PAD = 3 };
 
@@ -67,20 +67,21 @@ struct GlobalSplit {
 };
 // Tiles per chunk of a stream of n_st tiles, about.  In a launch that fills the chip a chunk is as long as the
 // column-head units beside it, and more chunks only mean more partial results.  In a small one the
-// question-token owners are the longest chain of tiles (about 0.75 us each) and shorter chunks shorten it;
-// merging costs 4 us and another microsecond and a half per four chunks, so short streams stay whole and
-// three to five chunks are best.  Short chunks (6 up to 24 tiles, 8 up to 40) against 16, forward / training step in
-// us: one sequence of 1024, 16 heads 12.3/43 and 14.4/50; of 2048 (24 tiles), 12 heads 13.6/54 and 18.8/68; two of
-// 2048 (33 tiles), 12 heads 17.8/68 and 20.4/75; longer streams, one of 3000 20.0/74 and 19.1/73, of 4096
-// 22.7/87 and 20.9/85.
+// question-token owners are the longest chain of tiles (about 0.75 us each) and shorter chunks shorten it; the
+// merge loads four chunks at a time and takes a microsecond and a half for every further four, so four chunks it
+// is, and short streams stay whole.  Forward / training step in us, chunks of 16, of 6 up to 24 tiles and 8 above,
+// and four: one sequence of 1024 (17 tiles), 16 heads 14.4/50, 12.3/43, the same; of 2048 (24), 12 heads 18.8/68,
+// 13.6/54, the same; of 2500 (39), 12 heads 16.8/58, 17.8/60, 14.3/51; of 3000 (48), 12 heads 19.1/73, 20.0/74,
+// 17.0/67; of 4096, 12 heads 20.9/85, 22.7/87, 20.9/85; two of 2048 (33), 16 heads 17.5/68, 19.7/75, 16.2/69.
 //
-// The tables do not know how many heads there will be.  A launch that is full in spite of a small B N runs the short
-// chunks in pairs (joins_chunks, stream_plan.h): from B H T of 700 on.  Single and in pairs: 1 x 1024, 96 heads 21.3/85
-// and 19.7/81, 256 heads 44/172 and 41/162; 1 x 2048, 48 heads 22.1/91 and 21.6/84; 2 x 2048, 64 heads 50/189 and
-// 46/177; below, 1 x 2048, 40 heads (B H T = 640) 18.5/79 and 20.9/82, 1 x 1024, 64 heads (512) 15.4/65 and 18.5/68.
+// The tables do not know how many heads there will be.  A launch that is full in spite of a small B N runs chunks of
+// streams up to kLongStream in pairs (joins_chunks, stream_plan.h): from B H T of 700 on.  Single and in pairs: 1 x
+// 1024, 96 heads 21.3/85 and 19.7/81, 256 heads 44/172 and 41/162; 1 x 2048, 48 heads 22.1/91 and 21.6/84; 2 x 2048, 64
+// heads 50/189 and 45/177; below, 1 x 2048, 40 heads (B H T = 640) 18.5/79 and 20.9/82, 1 x 1024, 64 heads (512)
+// 15.4/65 and 18.5/68.
 __host__ __device__ inline int chunk_tiles(int n_st, int B, int N) {
-  if ((long)B * N > kSmallBatch || n_st > kLongStream) return kChunkTiles;
-  return n_st < 12 ? 12 : n_st <= 24 ? 6 : 8;
+  if ((long)B * N > kSmallBatch) return kChunkTiles;
+  return n_st < 12 ? 12 : n_st <= 24 ? 6 : (n_st + 3) / 4;
 }
 __host__ __device__ inline GlobalSplit global_split(int G, int L, int B, int N) {
   GlobalSplit s;

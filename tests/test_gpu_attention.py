@@ -389,7 +389,7 @@ def test_bf16_scores_that_rise_in_steps(n_global, rows, cols, cell, N, bits):
                                                 (20, 790, 832, 104),     # 14: three
                                                 (40, 1060, 1100, 80),    # 18: three
                                                 (130, 1370, 1500, 64),   # 25, two owner tiles of question tokens
-                                                (64, 2490, 2560, 36),    # 40: five
+                                                (64, 2490, 2560, 36),    # 40: four
                                                 (64, 2500, 2600, 36)])   # 41: as the tables list them
 def test_chunks_in_pairs_where_many_heads_fill_the_chip(n_global, table, N, H):
     """Small batches with many heads run the short chunks of question-token owners in pairs.  All row heads have the same
