@@ -292,17 +292,9 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
   // With few token tiles that leaves XCDs idle or uneven (one of 64 tokens and 6144 x 2048 weights: 48 tiles on
   // the 32 CUs of one XCD, 29 us); then the feature tiles are dealt instead, and every weight is read by one XCD.
   const int q = blockIdx.x & 7, jx = blockIdx.x >> 3;
-  int tt, f0;
-  if (a.by_feature) {
-    const int n_tt = a.B * a.tok_tiles_per_seq, fj = jx / n_tt;
-    tt = jx - fj * n_tt;
-    f0 = (8 * fj + q) * S::kRowsA;
-    if (f0 >= a.F) return;
-  } else {
-    const int tj = jx / a.feat_tiles;
-    f0 = (jx - tj * a.feat_tiles) * S::kRowsA;
-    tt = 8 * tj + ((q + 3 * tj) & 7);
-  }
+  const int per = a.by_feature ? a.B * a.tok_tiles_per_seq : a.feat_tiles, jk = jx / per, rest = jx - jk * per;
+  const int tt = a.by_feature ? rest : 8 * jk + ((q + 3 * jk) & 7), f0 = (a.by_feature ? 8 * jk + q : rest) * S::kRowsA;
+  if (f0 >= a.F) return;
   const int b = tt / a.tok_tiles_per_seq, tile = tt - b * a.tok_tiles_per_seq;
   if (b >= a.B) return;
   const int n0 = tile * S::kRowsB;
