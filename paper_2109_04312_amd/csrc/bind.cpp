@@ -100,6 +100,11 @@ float real(PyObject* o) {
   if (v == -1.0 && PyErr_Occurred()) throw PyFailure();
   return (float)v;
 }
+bool truth(PyObject* o) {
+  const int v = PyObject_IsTrue(o);
+  if (v < 0) throw PyFailure();
+  return v != 0;
+}
 mate_dtype dtype_code(const at::Tensor& t) {
   if (t.scalar_type() == at::kFloat) return MATE_F32;
   if (t.scalar_type() == at::kBFloat16) return MATE_BF16;
@@ -376,9 +381,9 @@ PyObject* qkv_project_bwd(Args a) {  // x, w_qkv, flags, dq, dk, dv, want_dx, wa
   MATE_ASSERT(x.scalar_type() == at::kBFloat16 && has_shape(w, {3 * H * 64, E}) && has_shape(dq, {B, H, N, 64}));
   MATE_ASSERT(dk.sizes() == dq.sizes() && dv.sizes() == dq.sizes() && has_shape(flags, {B, N}));
   at::Tensor dx, dw, db;
-  if (PyObject_IsTrue(a[6])) dx = at::empty_like(x);
-  if (PyObject_IsTrue(a[7])) dw = new_tensor({3 * H * 64, E}, at::kFloat, x);
-  if (PyObject_IsTrue(a[8])) db = new_tensor({3 * H * 64}, at::kFloat, x);
+  if (truth(a[6])) dx = at::empty_like(x);
+  if (truth(a[7])) dw = new_tensor({3 * H * 64, E}, at::kFloat, x);
+  if (truth(a[8])) db = new_tensor({3 * H * 64}, at::kFloat, x);
   const Workspace ws = project_workspace(a[9], B, N, H, E, x);
   void *px = dev(x, "x"), *pw = dev(w, "w_qkv"), *pf = dev(flags, "flags"), *pq = dev(dq, "dq"), *pk = dev(dk, "dk"),
        *pv = dev(dv, "dv"), *pdx = dx.defined() ? dx.data_ptr() : nullptr, *pdw = dw.defined() ? dw.data_ptr() : nullptr,
@@ -397,9 +402,9 @@ PyObject* out_project_bwd(Args a) {  // o, w_o, flags, dy, want_do, want_dw, wan
   const int E = (int)w.size(0);
   MATE_ASSERT(o.scalar_type() == at::kBFloat16 && has_shape(w, {E, x.H * 64}) && has_shape(dy, {x.B, x.N, E}) && x.D == 64);
   at::Tensor d_o, dw, db;
-  if (PyObject_IsTrue(a[4])) d_o = at::empty_like(o);
-  if (PyObject_IsTrue(a[5])) dw = new_tensor({E, x.H * 64}, at::kFloat, o);
-  if (PyObject_IsTrue(a[6])) db = new_tensor({E}, at::kFloat, o);
+  if (truth(a[4])) d_o = at::empty_like(o);
+  if (truth(a[5])) dw = new_tensor({E, x.H * 64}, at::kFloat, o);
+  if (truth(a[6])) db = new_tensor({E}, at::kFloat, o);
   const Workspace ws = project_workspace(a[7], x.B, x.N, x.H, E, o);
   void *po = dev(o, "o"), *pw = dev(w, "w_o"), *pf = dev(flags, "flags"), *py = dev(dy, "dy"),
        *pdo = d_o.defined() ? d_o.data_ptr() : nullptr, *pdw = dw.defined() ? dw.data_ptr() : nullptr,

@@ -116,6 +116,25 @@ def test_head_kinds_must_be_one_per_head(mate, call):
     assert "device tensor" not in str(e.value)
 
 
+@pytest.mark.parametrize("which", range(3))
+def test_wanted_gradients_whose_truth_raises(mate, which):
+    """want_dx, want_dw, want_dbias are asked for their truth, and what that raises arrives (on host tensors, which
+    are refused afterwards: no kernel is launched)."""
+    import torch
+    B, N, H, E = 1, 64, 2, 128
+    x, flags = torch.zeros(B, N, E, dtype=torch.bfloat16), torch.zeros(B, N, dtype=torch.uint8)
+    w, w_o = torch.zeros(3 * H * 64, E, dtype=torch.bfloat16), torch.zeros(E, H * 64, dtype=torch.bfloat16)
+    head = torch.zeros(B, H, N, 64, dtype=torch.bfloat16)
+    want = [True] * 3
+    with pytest.raises(ValueError, match="device tensor"):
+        mate.qkv_project_bwd(x, w, flags, head, head, head, *want)
+    want[which] = np.zeros(2)
+    with pytest.raises(ValueError, match="ambiguous"):
+        mate.qkv_project_bwd(x, w, flags, head, head, head, *want)
+    with pytest.raises(ValueError, match="ambiguous"):
+        mate.out_project_bwd(head, w_o, flags, x, *want)
+
+
 def test_argument_errors_of_the_later_entry_points(mate):
     fake = 0x1000  # never dereferenced
     bb = mate.mate_build_segments_bucketed
