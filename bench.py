@@ -16,6 +16,7 @@ from __future__ import annotations
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -77,7 +78,7 @@ def summarize_pmc(fetch_dir, write_dir):
             for row in csv.DictReader(open(path)):
                 if row["Counter_Name"] == counter:
                     name = row["Kernel_Name"].replace("(anonymous namespace)::", "").replace("void ", "")
-                    name = name.split("(")[0].replace("mate::", "").replace("<true>", "").replace("<false>", "")
+                    name = re.sub(r"<(true|false)(, *(true|false))*>", "", name.split("(")[0].replace("mate::", ""))
                     acc.setdefault(name, {}).setdefault(row["Dispatch_Id"], 0.0)
                     acc[name][row["Dispatch_Id"]] += float(row["Counter_Value"])
         return {k: sum(v.values()) / len(v) for k, v in acc.items()}

@@ -28,9 +28,9 @@
 // What bounds it: latency, not traffic -- load, classify, scan, rank, store, with a workgroup barrier
 // between each.  So the counters are cleared while the inputs travel, prefix sums are DPP moves
 // (six dependent shuffles were 2 us of the kernel), ids and segments are counted in one scan, and the
-// classification, which the instruction issue bounds, takes four elements per lane.  Measured before and
-// after, one launch: 512 positions 10.1 -> 6.8 us, one sequence of 1999 9.3 -> 6.3 us, 128 positions
-// 8.6 -> 5.6 us, 8192 15.7 -> 12.0 us.
+// classification, which the instruction issue bounds, takes four elements per lane.  us per launch in a row of
+// them, against the version without these: one sequence of 128 positions 8.6 -> 5.0, of 512 9.3 -> 5.6, of 1999
+// 10.3 -> 7.0, two of 8192 14.3 -> 11.0.
 //
 // Bucketed mode (the approximation of Section 3.1: a global part of at most G tokens, the rest
 // of the head's order in buckets of R, a bucket meeting itself and its two neighbours): the
