@@ -174,6 +174,7 @@ __global__ __launch_bounds__(kThreads) void fwd_dense_kernel(DenseArgs a) {
   const float sc = uniform(a.scale * kLog2e);
   f32x16 o_acc[2] = {zero16(), zero16()};
   float m_run = -INFINITY, l_run = 0.f;
+  Reference ref = kMissing;
   int koff[4], voff[2][2];
   operand_offsets(lane, koff, voff);
   const bool wave_active = u.tile * BM + wave * 32 < N;
@@ -182,7 +183,7 @@ __global__ __launch_bounds__(kThreads) void fwd_dense_kernel(DenseArgs a) {
     const char* Kst = stream.acquire(t, n_tiles);
     const char* Vst = Kst + kTileBytes;
     if (!wave_active) continue;
-    fwd_tile(Kst, Vst, qf, koff, voff, sc, CodeMask(code + t * BN, hl, me.code, me.limit), o_acc, m_run, l_run);
+    fwd_tile(Kst, Vst, qf, koff, voff, sc, CodeMask(code + t * BN, hl, me.code, me.limit), o_acc, m_run, l_run, ref);
   }
   __syncthreads();
   const float l_tot = half_sum(l_run);

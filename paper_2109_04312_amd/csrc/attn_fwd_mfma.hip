@@ -147,6 +147,7 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
   const float sc = uniform(a.scale * kLog2e);  // scores are kept raw; exp2(s * sc - m * sc)
   f32x16 o_acc[2] = {zero16(), zero16()};
   float m_run = -INFINITY, l_run = 0.f;  // reference of raw scores; this lane-half's share of the sum
+  Reference ref = kMissing;
 
   const int tb = u.t_begin, te = u.t_end;
   // Everything loaded into registers so far is pinned as complete here, so that no load with a
@@ -167,7 +168,7 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
     if (me.wave_active) {
       WindowMask mask(base, hl, part0 ? 0 : me.lo, part0 ? u.G : me.hi, split.first(base, part0 ? 0 : me.w_lo),
                       split.end(base, part0 ? u.G : me.w_hi), part0 ? 0 : me.a_lo, part0 ? u.G : me.a_hi);
-      fwd_tile(Kst, Vst, qf, koff, voff, sc, mask, o_acc, m_run, l_run);
+      fwd_tile(Kst, Vst, qf, koff, voff, sc, mask, o_acc, m_run, l_run, ref);
     }
   }
   __syncthreads();  // all wavefronts are done reading the stages; reuse them for the epilogue

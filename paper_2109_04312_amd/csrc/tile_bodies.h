@@ -78,26 +78,22 @@ struct WindowMask {
 // only a tile that finds a row without a reference takes the maximum of its scores (and rescales what
 // was summed so far); the others use the reference as it is and look at the sum of the tile's
 // probabilities afterwards.  Where one exceeds 2^13 (one score more than 8 to 13 bits above the reference)
-// the reference rises by the sum's exponent: everything summed so far and this tile's probabilities, which
-// are rounded already, are scaled by that power of two.  Only from 2^100 on, or if a sum is not finite, the
-// tile starts again and takes the maximum.  (Starting again from 2^13 on cost inputs of widely spread
-// scores, standard deviation 60 before the scale, up to a third of the forward: B = 2, N = 8192, H = 16
-// 70.5 us, now 56.8, and 52.4 at standard-normal inputs; dense 8 x 1024, H = 12 61.9, now 46.5, and 44.2.)
+// the tile starts again with the maximum, and from there on this wavefront's reference follows the maximum in
+// every tile, without the trial: rows whose scores have risen once tend to rise again.  (Starting again each
+// time cost inputs of widely spread scores, standard deviation 60 before the scale, up to two fifths of the
+// forward: B = 2, N = 8192, H = 16 67 us, now 57.3, and 51.2 at standard-normal inputs; dense 8 x 1024, H = 12
+// 61, now 48.8, and 43.9.  Scaling sums and rounded probabilities by a power of two instead is as fast, but the
+// largest probability is then a rounded one and not 1, and the mean error of such rows' LSE five times as large.)
 // Vector and matrix instructions of the resident wavefronts mostly take turns here, and under full load the
 // chip lowers its clock (2.4 to 1.95 GHz), so every instruction left out counts: without the 16 three-operand
 // maxima and the rescaling decision per tile, with two instructions per masked pair instead of three and a wait,
 // and with single blocks, B = 2, N = 8192, H = 16 takes 54 instead of 57 us, B = 8, N = 2048 49 instead of 53.
 constexpr float kMaxTileSum = 8192.f;
-constexpr float kMostTileSum = 0x1p100f;
+// A wavefront's reference: missing for one of its rows, as the first tiles left it, or following the maximum.
+enum Reference { kMissing, kFixed, kFollows };
 // P^T of the tile as the second contraction's operands, [32-key block][half of it], two bf16 values in a word.  (Words,
 // because the compiler takes vectors of bf16 that live across a branch apart and converts every value twice.)
 typedef unsigned Probs[2][2][4];
-// Two values that are not negative, times 2^-k: their exponent fields less k.  (What would fall below the
-// smallest normal number becomes zero or less than that number.)
-__device__ __forceinline__ unsigned times_exp2(unsigned w, unsigned k) {
-  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-  return __builtin_bit_cast(unsigned, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, w), (u16x2)(unsigned short)(k << 7)));
-}
 // A tile of which only one 32-key block is visible is done with that block alone (kBlocks = 1); branching
 // around the blocks inside one body would cost the interleaving of their instruction streams.
 //
@@ -163,7 +159,7 @@ __device__ __forceinline__ float fwd_probs_new_max(int blk0, const char* Kst, co
 template <class Mask>
 __device__ __forceinline__ void fwd_tile(const char* Kst, const char* Vst, const bf16x8 (&qf)[4],
                                          const int (&koff_)[4], const int (&voff_)[2][2], float sc, Mask&& mask,
-                                         f32x16 (&o_acc)[2], float& m_run, float& l_run) {
+                                         f32x16 (&o_acc)[2], float& m_run, float& l_run, Reference& ref) {
   if (mask.skip(0) && mask.skip(1)) return;
   const bool both = !mask.skip(0) && !mask.skip(1);
   const int blk0 = mask.skip(0) ? 1 : 0;
@@ -185,8 +181,7 @@ __device__ __forceinline__ void fwd_tile(const char* Kst, const char* Vst, const
       for (int c = 0; c < 16; ++c) o_acc[db][c] *= alpha;
   };
   float l_tile;
-  bool take_max = __any(m_run == -INFINITY);
-  if (!take_max) {
+  if (ref == kFixed) {
     if (both) {
       f32x16 s[2];
       fwd_scores<2>(0, Kst, qf, koff, mask, s);
@@ -196,28 +191,14 @@ __device__ __forceinline__ void fwd_tile(const char* Kst, const char* Vst, const
       fwd_scores<1>(blk0, Kst, qf, koff, mask, s);
       l_tile = fwd_probs<1>(s, sc, m_run * sc, pb);
     }
-    if (__builtin_expect(!__all(l_tile <= kMaxTileSum), 0)) {
-      const float l_row = half_sum(l_tile);
-      take_max = !__all(l_row < kMostTileSum);
-      if (!take_max) {
-        const unsigned k = l_row > kMaxTileSum ? (__float_as_uint(l_row) >> 23) - 127u : 0u;
-        const float alpha = __uint_as_float((127u - k) << 23);  // 2^-k
-        m_run = fmaf((float)k, __builtin_amdgcn_rcpf(sc), m_run);
-        l_tile *= alpha;
-#pragma unroll
-        for (int jb = 0; jb < 2; ++jb)
-          if (jb == 0 || both)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) pb[jb][i >> 2][i & 3] = times_exp2(pb[jb][i >> 2][i & 3], k);
-        rescale(alpha);
-      }
-    }
+    if (__builtin_expect(!__all(l_tile <= kMaxTileSum), 0)) ref = kFollows;
   }
-  if (take_max) {
+  if (ref != kFixed) {
     const float m_old = m_run;
     l_tile = both ? fwd_probs_new_max<2>(0, Kst, qf, koff, mask, sc, m_run, pb)
                   : fwd_probs_new_max<1>(blk0, Kst, qf, koff, mask, sc, m_run, pb);
     rescale(m_run == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m_old - m_run) * sc));
+    if (ref == kMissing && !__any(m_run == -INFINITY)) ref = kFixed;
   }
   l_run += l_tile;
   // O^T += V^T P^T

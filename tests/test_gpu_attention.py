@@ -371,7 +371,7 @@ def test_bf16_tile_edges(n_global, rows, cols, cell, N, rise):
 @pytest.mark.parametrize("n_global,rows,cols,cell,N", [(31, 3, 2, 40, 271), (70, 2, 3, 100, 670), (40, 90, 5, 4, 2100)])
 def test_bf16_scores_that_rise_in_steps(n_global, rows, cols, cell, N, bits):
     """Every fifth of the sequence scores 2^bits more than the one before: below 2^13 per tile the softmax reference
-    stays, up to 2^100 the sums are scaled by a power of two, beyond that the tile is done again."""
+    stays, above it the tile is done again and the reference follows the maximum from there on."""
     st = synth._stack([synth.flatten_table(N, n_global, rows, cols, np.full(rows * cols, cell))])
     rng = np.random.default_rng(bits)
     q, k, v = synth.draw_tensors(rng, 1, 2, N, 64, "bf16", 3)
