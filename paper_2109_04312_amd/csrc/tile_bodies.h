@@ -172,16 +172,24 @@ __device__ __forceinline__ void fwd_tile(const char* Kst, const char* Vst, const
   voff[1][1] = voff[0][1] ^ 64;
 #pragma unroll
   for (int ks = 1; ks < 4; ++ks) koff[ks] = koff[0] ^ (ks << 5);
-  Probs pb;
-  auto rescale = [&](float alpha) {
-    l_run *= alpha;
+  // O^T += V^T P^T
+  auto add = [&](const Probs& pb, float l_tile) {
+    l_run += l_tile;
+    auto block = [&](int jb) {
 #pragma unroll
-    for (int db = 0; db < 2; ++db)
+      for (int tt = 0; tt < 2; ++tt) {
+        const char* vt = Vst + (jb * 32 + tt * 16) * 128;
+        const bf16x8 p = as_bf16x8(make_uint4(pb[jb][tt][0], pb[jb][tt][1], pb[jb][tt][2], pb[jb][tt][3]));
 #pragma unroll
-      for (int c = 0; c < 16; ++c) o_acc[db][c] *= alpha;
+        for (int db = 0; db < 2; ++db) o_acc[db] = mfma(read_transposed(vt, voff[db][0], voff[db][1]), p, o_acc[db]);
+      }
+    };
+    block(0);
+    if (both) block(1);
   };
-  float l_tile;
   if (ref == kFixed) {
+    Probs pb;
+    float l_tile;
     if (both) {
       f32x16 s[2];
       fwd_scores<2>(0, Kst, qf, koff, mask, s);
@@ -191,28 +199,21 @@ __device__ __forceinline__ void fwd_tile(const char* Kst, const char* Vst, const
       fwd_scores<1>(blk0, Kst, qf, koff, mask, s);
       l_tile = fwd_probs<1>(s, sc, m_run * sc, pb);
     }
-    if (__builtin_expect(!__all(l_tile <= kMaxTileSum), 0)) ref = kFollows;
+    if (__all(l_tile <= kMaxTileSum)) return add(pb, l_tile);
+    ref = kFollows;
   }
-  if (ref != kFixed) {
-    const float m_old = m_run;
-    l_tile = both ? fwd_probs_new_max<2>(0, Kst, qf, koff, mask, sc, m_run, pb)
-                  : fwd_probs_new_max<1>(blk0, Kst, qf, koff, mask, sc, m_run, pb);
-    rescale(m_run == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m_old - m_run) * sc));
-    if (ref == kMissing && !__any(m_run == -INFINITY)) ref = kFixed;
-  }
-  l_run += l_tile;
-  // O^T += V^T P^T
-  auto add = [&](int jb) {
+  Probs pb;
+  const float m_old = m_run;
+  const float l_tile = both ? fwd_probs_new_max<2>(0, Kst, qf, koff, mask, sc, m_run, pb)
+                            : fwd_probs_new_max<1>(blk0, Kst, qf, koff, mask, sc, m_run, pb);
+  const float alpha = m_run == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m_old - m_run) * sc);
+  l_run *= alpha;
 #pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
-      const char* vt = Vst + (jb * 32 + tt * 16) * 128;
-      const bf16x8 p = as_bf16x8(make_uint4(pb[jb][tt][0], pb[jb][tt][1], pb[jb][tt][2], pb[jb][tt][3]));
+  for (int db = 0; db < 2; ++db)
 #pragma unroll
-      for (int db = 0; db < 2; ++db) o_acc[db] = mfma(read_transposed(vt, voff[db][0], voff[db][1]), p, o_acc[db]);
-    }
-  };
-  add(0);
-  if (both) add(1);
+    for (int c = 0; c < 16; ++c) o_acc[db][c] *= alpha;
+  if (ref == kMissing && !__any(m_run == -INFINITY)) ref = kFixed;
+  add(pb, l_tile);
 }
 
 // dQ: P = exp2(S sc - lse2), dP^T = V dO^T, dS = P (dP - delta), dQ^T += K^T dS^T; one 32-key block
