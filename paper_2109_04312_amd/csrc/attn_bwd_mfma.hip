@@ -105,25 +105,19 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
   stream.prime();
 
   // this lane's query row and dO row as B operands (column m, k = dims), and delta
-  bf16x8 qf[4], gf[4], of[4];
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    const size_t off = (size_t)me.pos * kD + ks * 16 + hl * 8;
-    qf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(Q + off));
-    gf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(dO + off));
-    of[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(O + off));
-  }
+  OwnedTile q_rows, g_rows, o_rows;
+  g_rows.load(dO, me.pos, lane);
+  o_rows.load(O, me.pos, lane);
+  q_rows.load(Q, me.pos, lane);
   const float lse = a.lse[bh + me.pos];
+  bf16x8 qf[4], gf[4];
+  g_rows.operands(gf, stream.room(), lane);
+  const float delta = row_delta(g_rows, o_rows, stream.room(), lane);
+  q_rows.operands(qf, stream.room(), lane);
   // Everything loaded into registers so far is pinned as complete here, so that no load with a
   // register destination is pending inside the loop.
   asm volatile("" ::"v"(qf[0]), "v"(qf[1]), "v"(qf[2]), "v"(qf[3]), "v"(gf[0]), "v"(gf[1]),
-               "v"(gf[2]), "v"(gf[3]), "v"(of[0]), "v"(of[1]), "v"(of[2]), "v"(of[3]), "v"(lse));
-  float delta = 0.f;
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) delta = fmaf((float)gf[ks][e], (float)of[ks][e], delta);
-  delta = half_sum(delta);
+               "v"(gf[2]), "v"(gf[3]), "v"(delta), "v"(lse));
   // every chunk of a question-token owner computes the same delta; the first one stores it
   // (stored negated, with -lse / scale beside it: the dK/dV kernel starts its accumulators there)
   if (hl == 0 && me.valid && u.t_begin == 0 && split.writes(wave)) {
@@ -221,13 +215,12 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
   if (tid < BM) k_tok[tid] = me.stage_tok;
   stream.prime();
 
+  OwnedTile k_rows, v_rows;
+  k_rows.load(K, me.pos, lane);
+  v_rows.load(V, me.pos, lane);
   bf16x8 kf[4], vf[4];  // this lane's key and value rows as B operands
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    const size_t off = (size_t)me.pos * kD + ks * 16 + hl * 8;
-    kf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(K + off));
-    vf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(V + off));
-  }
+  k_rows.operands(kf, stream.room(), lane);
+  v_rows.operands(vf, stream.room(), lane);
   const float sc = uniform(a.scale * kLog2e);
   asm volatile("" ::"v"(kf[0]), "v"(kf[1]), "v"(kf[2]), "v"(kf[3]), "v"(vf[0]), "v"(vf[1]),
                "v"(vf[2]), "v"(vf[3]));

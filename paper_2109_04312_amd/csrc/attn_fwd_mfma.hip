@@ -139,10 +139,10 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
   if (tid < BM) q_tok[tid] = me.stage_tok;
   stream.prime();
 
+  OwnedTile q_rows;
+  q_rows.load(Q, me.pos, lane);
   bf16x8 qf[4];
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks)
-    qf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(Q + (size_t)me.pos * kD + ks * 16 + hl * 8));
+  q_rows.operands(qf, stream.room(), lane);
 
   const float sc = uniform(a.scale * kLog2e);  // scores are kept raw; exp2(s * sc - m * sc)
   f32x16 o_acc[2] = {zero16(), zero16()};

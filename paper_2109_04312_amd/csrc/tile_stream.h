@@ -40,6 +40,8 @@ struct TileStream {
         lane(lane_), ll(make_load_lane(wave_, lane_)) {}
 
   __device__ char* stage(int t) { return stages + ((unsigned)(t - u.t_begin) % kStages) * kStageBytes; }
+  // 4 KB of the stage that stays empty until the first acquire(), one piece per wavefront
+  __device__ char* room() { return stages + kStageBytes + wave * 4096; }
   __device__ void issue_idx(int t) {
     const int* list; int base, last;
     if (wave != (t & 3)) return;
