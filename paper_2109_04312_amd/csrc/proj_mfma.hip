@@ -24,6 +24,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "d2l.h"
 #include "launch.h"
@@ -579,9 +580,13 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
   // loop (looked up one by one inside it, every step waited for dependent loads: 3 us a step where the
   // contractions need 0.9) ----
   __shared__ unsigned long long live_mask[kMaxRange];
-  __shared__ unsigned short live_at[kMaxRange];
-  __shared__ int wave_live[S::kAllWaves];
+  __shared__ uint2 live_at[kMaxRange];  // where the block begins in X and G, in units of 128 bytes
+  __shared__ int wave_live[S::kAllWaves], tail_at;
   int n_live = 0;
+  const unsigned x_stride = a.x.heads ? kD * 2 : (unsigned)a.x.ld * 2, g_stride = a.g.heads ? kD * 2 : (unsigned)a.g.ld * 2;
+  const unsigned x_seq = (unsigned)((a.x.heads ? (size_t)a.H * a.N * kD * 2 : (size_t)a.N * x_stride) / 128);
+  const unsigned g_seq = (unsigned)((a.g.heads ? (size_t)a.H * a.N * kD * 2 : (size_t)a.N * g_stride) / 128);
+  if (tid == 0) tail_at = -1;
   for (int s0 = s_begin; s0 < s_end; s0 += S::kThreads) {  // one block per thread, its 64 flags at once
     const int s = s0 + tid, b = s / a.blocks_per_seq;
     const unsigned long long mask = s < s_end ? pad_mask(a.flags, (size_t)a.B * a.N, (size_t)b * a.N, (s - b * a.blocks_per_seq) * 64, a.N) : ~0ull;
@@ -595,8 +600,10 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
       n_live += wave_live[w];
     }
     if (mask != ~0ull) {
+      const unsigned n0 = (unsigned)(s - b * a.blocks_per_seq) * 64;
       live_mask[at] = mask;
-      live_at[at] = (unsigned short)(s - s_begin);
+      live_at[at] = make_uint2(b * x_seq + n0 * (x_stride / 128), b * g_seq + n0 * (g_stride / 128));
+      if (s + 1 == total_blocks && a.N % 64) tail_at = at;
     }
     __syncthreads();
   }
@@ -604,41 +611,46 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
   const int i_begin = share ? n_live * split / a.splits : 0, i_end = share ? n_live * (split + 1) / a.splits : n_live;
 
   // ---- operand streams: X tiles (columns e0 ..) then G tiles (columns f0 ..) ------------------------
-  // The bases are wave-uniform and move with the block; the lane offsets are those of a whole block, and
-  // only a sequence's last, shorter one needs others (its missing rows repeat the last).
-  const unsigned x_stride = a.x.heads ? kD * 2 : (unsigned)a.x.ld * 2, g_stride = a.g.heads ? kD * 2 : (unsigned)a.g.ld * 2;
-  const size_t x_seq = a.x.heads ? (size_t)a.H * a.N * kD * 2 : (size_t)a.N * x_stride;
-  const size_t g_seq = a.g.heads ? (size_t)a.H * a.N * kD * 2 : (size_t)a.N * g_stride;
-  const char* base[S::kLoads];
+  // The bases are wave-uniform and move with the block; the lane offsets are those of a whole block.  A sequence's
+  // last, shorter block reads into the rows that follow, which are cleared like pad rows; only the very last one,
+  // behind which memory may end, repeats its last row instead.
+  constexpr int kTilesX = S::kA, kTilesG = S::kB;
+  const char* base[kTilesX + kTilesG];
+#pragma unroll
+  for (int t = 0; t < kTilesX + kTilesG; ++t) {
+    const bool is_x = t < kTilesX;
+    const TokMat& mat = is_x ? a.x : a.g;
+    // (column blocks past the last one repeat it and are not stored)
+    const int c = is_x ? min(e0 / 64 + t, a.E / 64 - 1) : min(f0 / 64 + t - kTilesX, a.F / 64 - 1);
+    const int x = c / a.H, h = c - x * a.H;
+    const unsigned short* tensor = !mat.heads || x == 0 ? mat.p[0] : x == 1 ? mat.p[1] : mat.p[2];
+    base[t] = uniform_ptr(tensor + (mat.heads ? (size_t)h * a.N * kD : (size_t)c * 64));
+  }
   unsigned off[S::kLoads];
 #pragma unroll
   for (int i = 0; i < S::kLoads; ++i) {
-    const bool is_x = i < S::kLoadsA;
-    const LoadUnit l = load_unit<S::kWaves>(wave, lane, is_x ? i : i - S::kLoadsA);
-    const TokMat& mat = is_x ? a.x : a.g;
-    // (column blocks past the last one repeat it and are not stored)
-    const int c = is_x ? min(e0 / 64 + l.tile, a.E / 64 - 1) : min(f0 / 64 + l.tile, a.F / 64 - 1);
-    const int t = c / a.H, h = c - t * a.H;
-    const unsigned short* tensor = !mat.heads || t == 0 ? mat.p[0] : t == 1 ? mat.p[1] : mat.p[2];
-    base[i] = uniform_ptr(tensor + (mat.heads ? (size_t)h * a.N * kD : (size_t)c * 64));
-    off[i] = (unsigned)l.row * (is_x ? x_stride : g_stride) + l.chunk * 16;
+    const LoadUnit l = load_unit<S::kWaves>(wave, lane, i < S::kLoadsA ? i : i - S::kLoadsA);
+    off[i] = (unsigned)l.row * (i < S::kLoadsA ? x_stride : g_stride) + l.chunk * 16;
   }
-  auto issue_stage = [&](int s, int slot) {
-    const int b = s / a.blocks_per_seq, n0 = (s - b * a.blocks_per_seq) * 64;
+  const int tail = __builtin_amdgcn_readfirstlane(tail_at), tail_rows = a.N % 64;
+  auto issue_stage = [&](int i_live, uint2 at, int slot) {
     char* st = ring + slot * S::kStageBytes;
-    const size_t x_at = (size_t)b * x_seq + (size_t)n0 * x_stride, g_at = (size_t)b * g_seq + (size_t)n0 * g_stride;
-    const int missing = max(0, n0 + 64 - a.N);
+    const size_t x_at = (size_t)(unsigned)__builtin_amdgcn_readfirstlane(at.x) * 128;
+    const size_t g_at = (size_t)(unsigned)__builtin_amdgcn_readfirstlane(at.y) * 128;
+    auto issue = [&](auto whole) {
 #pragma unroll
-    for (int i = 0; i < S::kLoads; ++i) {
-      const bool is_x = i < S::kLoadsA;
-      unsigned o = off[i];
-      if (missing) {
-        const int row = load_unit<S::kWaves>(wave, lane, is_x ? i : i - S::kLoadsA).row;
-        o -= (unsigned)max(0, row - (63 - missing)) * (is_x ? x_stride : g_stride);
+      for (int i = 0; i < S::kLoads; ++i) {
+        const bool is_x = i < S::kLoadsA;
+        const int y = is_x ? i : i - S::kLoadsA, tile = S::kWaves * y / 8;
+        unsigned o = off[i];
+        if (!decltype(whole)::value)
+          o -= (unsigned)max(0, load_unit<S::kWaves>(wave, lane, y).row - (tail_rows - 1)) * (is_x ? x_stride : g_stride);
+        load_to_lds_16(base[is_x ? tile : kTilesX + tile] + (is_x ? x_at : g_at), o,
+                       st + (is_x ? 0 : S::kA * kTileBytes) + load_dst<S::kWaves>(wave, y));
       }
-      load_to_lds_16(uniform_ptr(base[i] + (is_x ? x_at : g_at)), o,
-                     st + (is_x ? load_dst<S::kWaves>(wave, i) : S::kA * kTileBytes + load_dst<S::kWaves>(wave, i - S::kLoadsA)));
-    }
+    };
+    if (__builtin_expect(i_live == tail, 0)) issue(std::false_type());
+    else issue(std::true_type());
   };
 
   f32x4 acc[S::kFA][S::kFB];
@@ -654,10 +666,10 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
   frag_offsets<true>(fo, lane);
 
   // this group's blocks: i_begin + group, + kGroups, ...
-  auto block_at = [&](int i) { return s_begin + __builtin_amdgcn_readfirstlane((int)live_at[i]); };
 #pragma unroll
   for (int k = 0; k + 1 < S::kStages; ++k)
-    if (i_begin + group + k * S::kGroups < i_end) issue_stage(block_at(i_begin + group + k * S::kGroups), k);
+    if (i_begin + group + k * S::kGroups < i_end)
+      issue_stage(i_begin + group + k * S::kGroups, live_at[i_begin + group + k * S::kGroups], k);
   // My share of block i has landed: everything but the loads of the blocks after it that were issued.  Its pad
   // rows are cleared (0 x anything = 0 then).
   auto land = [&](int i, int it) {
@@ -679,10 +691,10 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
   if (S::kAlternate && group == 1) barrier_no_fence();  // group 1 follows one barrier behind
   for (int i0 = i_begin, it = 0; i0 < i_end; i0 += S::kGroups, ++it) {
     const int i = i0 + group, ahead = i + (S::kStages - 1) * S::kGroups;
-    const int next = block_at(min(ahead, i_end - 1));
+    const uint2 next = live_at[min(ahead, i_end - 1)];
     land(i, it);
     barrier_no_fence();          // landed for everyone; and everyone is done with the block before it
-    if (ahead < i_end) issue_stage(next, (it + S::kStages - 1) % S::kStages);
+    if (ahead < i_end) issue_stage(ahead, next, (it + S::kStages - 1) % S::kStages);
     contract_stage<S, true, true, false>(ring + (it % S::kStages) * S::kStageBytes, fo, fo, wa, wb, acc,
                                   [&](const bf16x8 (&g)[S::kFB]) {
                                     if (do_bias) {
