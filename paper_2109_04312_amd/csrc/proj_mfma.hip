@@ -581,12 +581,12 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
   // contractions need 0.9) ----
   __shared__ unsigned long long live_mask[kMaxRange];
   __shared__ uint2 live_at[kMaxRange];  // where the block begins in X and G, in units of 128 bytes
-  __shared__ int wave_live[S::kAllWaves], tail_at;
+  __shared__ int wave_live[S::kAllWaves], first_tail;
   int n_live = 0;
   const unsigned x_stride = a.x.heads ? kD * 2 : (unsigned)a.x.ld * 2, g_stride = a.g.heads ? kD * 2 : (unsigned)a.g.ld * 2;
   const unsigned x_seq = (unsigned)((a.x.heads ? (size_t)a.H * a.N * kD * 2 : (size_t)a.N * x_stride) / 128);
   const unsigned g_seq = (unsigned)((a.g.heads ? (size_t)a.H * a.N * kD * 2 : (size_t)a.N * g_stride) / 128);
-  if (tid == 0) tail_at = -1;
+  if (tid == 0) first_tail = kMaxRange;  // (the loop's first barrier comes before anyone else's turn)
   for (int s0 = s_begin; s0 < s_end; s0 += S::kThreads) {  // one block per thread, its 64 flags at once
     const int s = s0 + tid, b = s / a.blocks_per_seq;
     const unsigned long long mask = s < s_end ? pad_mask(a.flags, (size_t)a.B * a.N, (size_t)b * a.N, (s - b * a.blocks_per_seq) * 64, a.N) : ~0ull;
@@ -603,7 +603,7 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
       const unsigned n0 = (unsigned)(s - b * a.blocks_per_seq) * 64;
       live_mask[at] = mask;
       live_at[at] = make_uint2(b * x_seq + n0 * (x_stride / 128), b * g_seq + n0 * (g_stride / 128));
-      if (s + 1 == total_blocks && a.N % 64) tail_at = at;
+      if ((size_t)a.B * a.N - ((size_t)b * a.N + n0) < 64) atomicMin(&first_tail, at);
     }
     __syncthreads();
   }
@@ -612,8 +612,9 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
 
   // ---- operand streams: X tiles (columns e0 ..) then G tiles (columns f0 ..) ------------------------
   // The bases are wave-uniform and move with the block; the lane offsets are those of a whole block.  A sequence's
-  // last, shorter block reads into the rows that follow, which are cleared like pad rows; only the very last one,
-  // behind which memory may end, repeats its last row instead.
+  // last, shorter block reads into the rows that follow, which are cleared like pad rows; only where fewer than 64 rows
+  // are left before memory may end (the end of the last sequence, or of the last few if they are short) does it
+  // repeat its last row instead.
   constexpr int kTilesX = S::kA, kTilesG = S::kB;
   const char* base[kTilesX + kTilesG];
 #pragma unroll
@@ -632,7 +633,7 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
     const LoadUnit l = load_unit<S::kWaves>(wave, lane, i < S::kLoadsA ? i : i - S::kLoadsA);
     off[i] = (unsigned)l.row * (i < S::kLoadsA ? x_stride : g_stride) + l.chunk * 16;
   }
-  const int tail = __builtin_amdgcn_readfirstlane(tail_at), tail_rows = a.N % 64;
+  const int tail = __builtin_amdgcn_readfirstlane(first_tail), tail_rows = a.N % 64;
   auto issue_stage = [&](int i_live, uint2 at, int slot) {
     char* st = ring + slot * S::kStageBytes;
     const size_t x_at = (size_t)(unsigned)__builtin_amdgcn_readfirstlane(at.x) * 128;
@@ -649,7 +650,7 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
                        st + (is_x ? 0 : S::kA * kTileBytes) + load_dst<S::kWaves>(wave, y));
       }
     };
-    if (__builtin_expect(i_live == tail, 0)) issue(std::false_type());
+    if (__builtin_expect(i_live >= tail, 0)) issue(std::false_type());
     else issue(std::true_type());
   };
 

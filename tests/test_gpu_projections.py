@@ -268,7 +268,8 @@ def test_workgroup_shapes(B, N, H, E):
 
 # contractions shared by two groups of wavefronts: one live token block (the other group has none), an odd
 # number of them, tiles with and without a whole last one, and the eight wavefronts of one large tile in halves
-@pytest.mark.parametrize("B,N,H,E", [(1, 63, 2, 128), (3, 129, 4, 256), (7, 577, 12, 768), (1, 4100, 16, 1024)])
+@pytest.mark.parametrize("B,N,H,E", [(1, 63, 2, 128), (3, 129, 4, 256), (7, 577, 12, 768), (1, 4100, 16, 1024),
+                                     (9, 10, 2, 128), (5, 40, 2, 128), (3, 70, 2, 128)])
 def test_shared_contractions(B, N, H, E):
     check(N, B, N, H, E, pad_tail=N // 5)
     check_bwd(N, B, N, H, E, pad_tail=N // 5)
