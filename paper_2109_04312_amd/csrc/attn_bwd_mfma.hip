@@ -127,19 +127,17 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
   const float lse2 = lse * kLog2e;
   const float sc = uniform(a.scale * kLog2e);
 
-  int koff[4], toff[2][2];
-  operand_offsets(lane, koff, toff);
+  const OperandLanes lanes(lane);
 
   f32x16 dq_acc[2] = {zero16(), zero16()};
   for (int t = u.t_begin; t < u.t_end; ++t) {
-    const char* Kst = stream.acquire(t);
-    const char* Vst = Kst + kTileBytes;
+    const unsigned tile = lds_addr(stream.acquire(t));
     const bool part0 = t < u.n_t0;
     const int base = part0 ? t * BN : u.s_lo + (t - u.n_t0) * BN;
     if (me.wave_active) {
-      WindowMask mask(base, hl, part0 ? 0 : me.lo, part0 ? u.G : me.hi, split.first(base, part0 ? 0 : me.w_lo),
+      WindowMask mask(base, hl, part0, u.G, me.lo, me.hi, split.first(base, part0 ? 0 : me.w_lo),
                       split.end(base, part0 ? u.G : me.w_hi), part0 ? 0 : me.a_lo, part0 ? u.G : me.a_hi);
-      dq_tile(Kst, Vst, qf, gf, koff, toff, sc, lse2, delta, mask, dq_acc);
+      dq_tile(tile, qf, gf, lanes, sc, lse2, delta, mask, dq_acc);
     }
   }
   __syncthreads();  // all wavefronts are done reading the stages; reuse them for the epilogue
@@ -225,21 +223,19 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
   asm volatile("" ::"v"(kf[0]), "v"(kf[1]), "v"(kf[2]), "v"(kf[3]), "v"(vf[0]), "v"(vf[1]),
                "v"(vf[2]), "v"(vf[3]));
 
-  int poff[4], toff[2][2];
-  operand_offsets(lane, poff, toff);
+  const OperandLanes lanes(lane);
 
   f32x16 dk_acc[2] = {zero16(), zero16()}, dv_acc[2] = {zero16(), zero16()};
   for (int t = u.t_begin; t < u.t_end; ++t) {
     const char* Qst = stream.acquire(t);
-    const char* Gst = Qst + kTileBytes;
     const float* lse_row = reinterpret_cast<const float*>(Qst + 2 * kTileBytes);
     const float* delta_row = lse_row + BN;
     const bool part0 = t < u.n_t0;
     const int base = part0 ? t * BN : u.s_lo + (t - u.n_t0) * BN;
     if (me.wave_active) {
-      WindowMask mask(base, hl, part0 ? 0 : me.lo, part0 ? u.G : me.hi, split.first(base, part0 ? 0 : me.w_lo),
+      WindowMask mask(base, hl, part0, u.G, me.lo, me.hi, split.first(base, part0 ? 0 : me.w_lo),
                       split.end(base, part0 ? u.G : me.w_hi), part0 ? 0 : me.a_lo, part0 ? u.G : me.a_hi);
-      dkv_tile(Qst, Gst, lse_row, delta_row, kf, vf, poff, toff, sc, hl, mask, dk_acc, dv_acc);
+      dkv_tile(lds_addr(Qst), lse_row, delta_row, kf, vf, lanes, sc, hl, mask, dk_acc, dv_acc);
     }
   }
   __syncthreads();  // all wavefronts are done reading the stages; reuse them for the epilogue

@@ -175,15 +175,13 @@ __global__ __launch_bounds__(kThreads) void fwd_dense_kernel(DenseArgs a) {
   f32x16 o_acc[2] = {zero16(), zero16()};
   float m_run = -INFINITY, l_run = 0.f;
   Reference ref = kMissing;
-  int koff[4], voff[2][2];
-  operand_offsets(lane, koff, voff);
+  const OperandLanes lanes(lane);
   const bool wave_active = u.tile * BM + wave * 32 < N;
 
   for (int t = 0; t < n_tiles; ++t) {
-    const char* Kst = stream.acquire(t, n_tiles);
-    const char* Vst = Kst + kTileBytes;
+    const unsigned tile = lds_addr(stream.acquire(t, n_tiles));
     if (!wave_active) continue;
-    fwd_tile(Kst, Vst, qf, koff, voff, sc, CodeMask(code + t * BN, hl, me.code, me.limit), o_acc, m_run, l_run, ref);
+    fwd_tile(tile, qf, lanes, sc, CodeMask(code + t * BN, hl, me.code, me.limit), o_acc, m_run, l_run, ref);
   }
   __syncthreads();
   const float l_tot = half_sum(l_run);
@@ -250,16 +248,14 @@ __global__ __launch_bounds__(kThreads, 4) void bwd_dq_dense_kernel(DenseArgs a) 
     a.nlse[bh + me.pos] = -lse / a.scale;
   }
   const float lse2 = lse * kLog2e, sc = a.scale * kLog2e;
-  int koff[4], toff[2][2];
-  operand_offsets(lane, koff, toff);
+  const OperandLanes lanes(lane);
   const bool wave_active = u.tile * BM + wave * 32 < N;
 
   f32x16 dq_acc[2] = {zero16(), zero16()};
   for (int t = 0; t < n_tiles; ++t) {
-    const char* Kst = stream.acquire(t, n_tiles);
-    const char* Vst = Kst + kTileBytes;
+    const unsigned tile = lds_addr(stream.acquire(t, n_tiles));
     if (!wave_active) continue;
-    dq_tile(Kst, Vst, qf, gf, koff, toff, sc, lse2, delta, CodeMask(code + t * BN, hl, me.code, me.limit), dq_acc);
+    dq_tile(tile, qf, gf, lanes, sc, lse2, delta, CodeMask(code + t * BN, hl, me.code, me.limit), dq_acc);
   }
   __syncthreads();
   const float mul = me.in_range && me.code != kPadCode ? a.scale : 0.f;  // pad positions: zeros
@@ -311,18 +307,16 @@ __global__ __launch_bounds__(kThreads) void bwd_dkv_dense_kernel(DenseArgs a) {
   asm volatile("" ::"v"(kf[0]), "v"(kf[1]), "v"(kf[2]), "v"(kf[3]), "v"(vf[0]), "v"(vf[1]),
                "v"(vf[2]), "v"(vf[3]));
   const float sc = uniform(a.scale * kLog2e);
-  int poff[4], toff[2][2];
-  operand_offsets(lane, poff, toff);
+  const OperandLanes lanes(lane);
   const bool wave_active = u.tile * BM + wave * 32 < N;
 
   f32x16 dk_acc[2] = {zero16(), zero16()}, dv_acc[2] = {zero16(), zero16()};
   for (int t = 0; t < n_tiles; ++t) {
     const char* Qst = stream.acquire(t, n_tiles);
-    const char* Gst = Qst + kTileBytes;
     const float* lse_row = reinterpret_cast<const float*>(Qst + kStage);
     const float* delta_row = lse_row + BN;
     if (!wave_active) continue;
-    dkv_tile(Qst, Gst, lse_row, delta_row, kf, vf, poff, toff, sc, hl, CodeMask(code + t * BN, hl, me.code, me.limit), dk_acc, dv_acc);
+    dkv_tile(lds_addr(Qst), lse_row, delta_row, kf, vf, lanes, sc, hl, CodeMask(code + t * BN, hl, me.code, me.limit), dk_acc, dv_acc);
   }
   __syncthreads();
   const bool live = me.in_range && me.code != kPadCode;  // pad positions: zeros

@@ -50,6 +50,15 @@ constexpr int kStride = kD + 4;
 constexpr int kTileFloats = kRows * kStride;
 constexpr int kTokAt = kD, kDeltaAt = kD + 1;
 
+// A lane's window of the tile's rows.  (Compared per pair: the matrix pipe bounds these kernels, and their registers are
+// full.)
+struct SlotWindow {
+  int d0, len;  // the tile's first slot + 4 hl - the window's, and its length
+  __device__ __forceinline__ bool in(int c) const { return (unsigned)(d0 + 8 * (c >> 2) + (c & 3)) < (unsigned)len; }
+  // tile row `row`, whichever lane half holds its score
+  __device__ __forceinline__ bool meets(int row, int hl) const { return (unsigned)(d0 - 4 * hl + row) < (unsigned)len; }
+};
+
 // A tile on its way from global memory: lane l holds piece l % 16 of rows l / 16 + 4 i.
 struct TileRegs {
   f32x4 v[8];
@@ -111,7 +120,7 @@ __device__ __forceinline__ void accumulate(f32x16 (&acc)[2], const float* tile, 
 // not all finite when its loop ends does its tiles again this way, without a prefetch.  (Looking for such values
 // in every tile instead of in the results: 88.8 us a training step for 85.6.)
 __device__ __forceinline__ void accumulate_special(f32x16 (&acc)[2], float* tile, int m, int hl, f32x16& p,
-                                                   const WindowMask& mask) {
+                                                   const SlotWindow& mask) {
   const int lane = 32 * hl + m;
 #pragma unroll 1
   for (int row = 0; row < kRows; ++row) {
@@ -209,10 +218,10 @@ struct Rows {
     t = min(t, n - 1);
     return t < nG ? gidx[min(kRows * t + m, G - 1)] : list[min(s_lo + kRows * (t - nG) + m, s_hi - 1)];
   }
-  __device__ __forceinline__ WindowMask mask(int t, int hl) const {
+  __device__ __forceinline__ SlotWindow mask(int t, int hl) const {
     const bool part0 = t < nG;
     const int base = part0 ? kRows * t : s_lo + kRows * (t - nG);
-    return WindowMask(base, hl, part0 ? 0 : lo, part0 ? G : hi, 0, 0, 0, 0);
+    return {base + 4 * hl - (part0 ? 0 : lo), part0 ? G : hi - lo};
   }
 };
 
@@ -296,9 +305,9 @@ __global__ __launch_bounds__(kThreads, 3) void fwd_f32_kernel(AttnArgs a) {
   f32x16 o[2] = {zero16(), zero16()};
   float m_run = -INFINITY, l_run = 0.f;
   // S^T -> P^T of a tile, O and the row sum rescaled
-  auto probs = [&](f32x16& s, const WindowMask& mask) {
+  auto probs = [&](f32x16& s, const SlotWindow& mask) {
 #pragma unroll
-    for (int c = 0; c < 16; ++c) s[c] = mask.in(0, c) ? s[c] : -INFINITY;
+    for (int c = 0; c < 16; ++c) s[c] = mask.in(c) ? s[c] : -INFINITY;
     float mx = s[0];
 #pragma unroll
     for (int c = 1; c < 16; ++c) mx = fmaxf(mx, s[c]);
@@ -339,7 +348,7 @@ __global__ __launch_bounds__(kThreads, 3) void fwd_f32_kernel(AttnArgs a) {
       f32x16 s = contract(tile, own, m, hl, zero16());
       val.load(V, tok, lane);
       val.put(tile, lane);
-      const WindowMask mask = r.mask(t, hl);
+      const SlotWindow mask = r.mask(t, hl);
       probs(s, mask);
       accumulate_special(o, tile, m, hl, s, mask);
     }
@@ -418,10 +427,10 @@ __global__ __launch_bounds__(kThreads, 3) void bwd_dq_f32_kernel(AttnArgs a) {
   float* tile = lds + wave * kTileFloats;
 
   f32x16 dq[2] = {zero16(), zero16()};
-  auto dscores = [&](f32x16& s, const f32x16& dp, const WindowMask& mask) {  // S^T -> dS^T
+  auto dscores = [&](f32x16& s, const f32x16& dp, const SlotWindow& mask) {  // S^T -> dS^T
 #pragma unroll
     for (int c = 0; c < 16; ++c)
-      s[c] = mask.in(0, c) ? __builtin_amdgcn_exp2f(fmaf(s[c], sc, -lse2)) * (dp[c] - delta) : 0.f;
+      s[c] = mask.in(c) ? __builtin_amdgcn_exp2f(fmaf(s[c], sc, -lse2)) * (dp[c] - delta) : 0.f;
   };
   for (int t = t0; t < r.n; t += kWaves) {
     const int tok_after = r.token(t + 2 * kWaves, m);
@@ -450,7 +459,7 @@ __global__ __launch_bounds__(kThreads, 3) void bwd_dq_f32_kernel(AttnArgs a) {
       key.put(tile, lane);
       keep_order();
       f32x16 s = contract(tile, own_q, m, hl, zero16());
-      const WindowMask mask = r.mask(t, hl);
+      const SlotWindow mask = r.mask(t, hl);
       dscores(s, dp, mask);
       accumulate_special(dq, tile, m, hl, s, mask);
     }
@@ -505,13 +514,13 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dkv_f32_kernel(AttnArgs a) {
   f32x16 dk[2] = {zero16(), zero16()}, dv[2] = {zero16(), zero16()};
   // S -> P, dP -> dS.  (A pair outside the pattern has P = 0 and so dS = 0, unless a value is not finite: then dS is
   // masked as well, in the second pass.)
-  auto dscores = [&](f32x16& s, f32x16& dp, const WindowMask& mask, bool mask_ds) {
+  auto dscores = [&](f32x16& s, f32x16& dp, const SlotWindow& mask, bool mask_ds) {
 #pragma unroll
     for (int c = 0; c < 16; ++c) {
       const float l = __shfl(row_lse, c_row(c, hl), 64), d = __shfl(row_delta, c_row(c, hl), 64);
-      s[c] = mask.in(0, c) ? __builtin_amdgcn_exp2f(fmaf(s[c], sc, -l * kLog2e)) : 0.f;
+      s[c] = mask.in(c) ? __builtin_amdgcn_exp2f(fmaf(s[c], sc, -l * kLog2e)) : 0.f;
       dp[c] = s[c] * (dp[c] - d);
-      if (mask_ds) dp[c] = mask.in(0, c) ? dp[c] : 0.f;
+      if (mask_ds) dp[c] = mask.in(c) ? dp[c] : 0.f;
     }
   };
   for (int t = t0; t < r.n; t += kWaves) {
@@ -543,7 +552,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dkv_f32_kernel(AttnArgs a) {
       grad.put(tile_g, lane);
       f32x16 s = contract(tile_q, own_k, m, hl, zero16());
       f32x16 dp = contract(tile_g, v_own, m, hl, zero16());
-      const WindowMask mask = r.mask(t, hl);
+      const SlotWindow mask = r.mask(t, hl);
       dscores(s, dp, mask, true);
       accumulate_special(dv, tile_g, m, hl, s, mask);
       accumulate_special(dk, tile_q, m, hl, dp, mask);

@@ -155,20 +155,18 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
   // *all* outstanding loads, prefetches included, at the first use).
   asm volatile("" ::"v"(qf[0]), "v"(qf[1]), "v"(qf[2]), "v"(qf[3]));
 
-  int koff[4], voff[2][2];
-  operand_offsets(lane, koff, voff);
+  const OperandLanes lanes(lane);
 
   for (int t = tb; t < te; ++t) {
-    const char* Kst = stream.acquire(t);
-    const char* Vst = Kst + kTileBytes;
+    const unsigned tile = lds_addr(stream.acquire(t));
 
     // visible slot window for this tile: question keys [0,G), else this lane's segment range
     const bool part0 = t < u.n_t0;
     const int base = part0 ? t * BN : u.s_lo + (t - u.n_t0) * BN;
     if (me.wave_active) {
-      WindowMask mask(base, hl, part0 ? 0 : me.lo, part0 ? u.G : me.hi, split.first(base, part0 ? 0 : me.w_lo),
+      WindowMask mask(base, hl, part0, u.G, me.lo, me.hi, split.first(base, part0 ? 0 : me.w_lo),
                       split.end(base, part0 ? u.G : me.w_hi), part0 ? 0 : me.a_lo, part0 ? u.G : me.a_hi);
-      fwd_tile(Kst, Vst, qf, koff, voff, sc, mask, o_acc, m_run, l_run, ref);
+      fwd_tile(tile, qf, lanes, sc, mask, o_acc, m_run, l_run, ref);
     }
   }
   __syncthreads();  // all wavefronts are done reading the stages; reuse them for the epilogue

@@ -49,7 +49,7 @@ __device__ inline LoadLane make_load_lane(int wave, int lane) {
 // its waits stricter, since loads retire in issue order.
 // (The low half of the generic address of LDS is the LDS offset; a cast to the LDS address space would add
 // a comparison with the null pointer to every load.)
-__device__ inline unsigned lds_addr(const void* p) { return __builtin_amdgcn_readfirstlane((unsigned)(size_t)p); }
+__device__ __forceinline__ unsigned lds_addr(const void* p) { return __builtin_amdgcn_readfirstlane((unsigned)(size_t)p); }
 // Address form: 64-bit base in scalar registers (wave-uniform) plus a 32-bit byte offset per
 // lane, so the per-lane address arithmetic is one shift-add.
 __device__ inline void load_to_lds_16(const void* base /* wave-uniform */, unsigned byte_off,
@@ -137,6 +137,43 @@ __device__ inline bf16x8 read_transposed(const char* tile, int off_lo, int off_h
   u.h[1] = b;
   return u.v;
 }
+
+// The same two reads from an LDS address (the low half of a generic address).  Tiles begin at multiples of 128 bytes, so
+// all of a lane's addresses in a tile follow from three by exclusive or: one addition and one exclusive or each where
+// address = tile + offset takes an addition and a register per offset.
+typedef const __attribute__((address_space(3))) bf16x8* LdsOperand;
+typedef __attribute__((address_space(3))) s16x4* LdsQuad;
+__device__ inline bf16x8 read_plain(unsigned addr) { return *(LdsOperand)addr; }
+__device__ inline bf16x8 read_transposed(unsigned addr_lo, unsigned addr_hi) {
+  union { s16x4 h[2]; bf16x8 v; } u;
+  u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsQuad)addr_lo);
+  u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsQuad)addr_hi);
+  return u.v;
+}
+// A lane's part of the addresses: plain_off(0), tr_off(0, 0), tr_off(0, 1).
+struct OperandLanes {
+  unsigned plain, tr_lo, tr_hi;
+  __device__ explicit OperandLanes(int lane)
+      : plain(plain_off(lane & 31, lane >> 5, 0)), tr_lo(tr_off(lane, 0, 0)), tr_hi(tr_off(lane, 0, 1)) {}
+};
+// Addresses of the operands in the tile at LDS address `tile` (wave-uniform).
+struct PlainAddr {
+  unsigned a[4];  // per 16-wide k slice
+  __device__ PlainAddr(const OperandLanes& o, unsigned tile) {
+    a[0] = tile + o.plain;
+#pragma unroll
+    for (int ks = 1; ks < 4; ++ks) a[ks] = a[0] ^ (ks << 5);
+  }
+};
+struct TransposedAddr {
+  unsigned lo[2], hi[2];  // per 32-wide dim block
+  __device__ TransposedAddr(const OperandLanes& o, unsigned tile) {
+    lo[0] = tile + o.tr_lo;
+    hi[0] = tile + o.tr_hi;
+    lo[1] = lo[0] ^ 64;
+    hi[1] = hi[0] ^ 64;
+  }
+};
 
 // Tile row (0..31 inside a 32-row block) held in C register c of a lane in half hl when the A
 // operand rows are fed unpermuted.

@@ -39,31 +39,31 @@ __device__ __forceinline__ void operand_offsets(int lane, int (&poff)[4], int (&
 // a bitwise select: no compare, whose result would travel through a scalar register pair (with the wait
 // that takes between two vector instructions).  Add, compare and select per pair before: see fwd_tile.
 struct WindowMask {
-  const int d0;        // base + 4 hl - lo
-  const int len;       // hi - lo
+  const int base, hl;   // the tile's first slot (wave-uniform), the lane's half
+  const bool all;       // wave-uniform: every row's window is [0, end) (the question-token part of a stream)
+  const int lo, hi;     // else this lane's
+  const int end;
   const int u_lo, u_hi, a_lo, a_hi;  // wave-uniform, relative to base: union and intersection of the rows' windows
   int one = 1;         // width of the extract; its value is hidden from the compiler, which would turn extract
                        // and select into test, compare and conditional move
   unsigned bits = 0;   // bit 8 (c >> 2) + (c & 3): register c of the loaded block is inside
   // [u0, u1) = union, [a0, a1) = intersection of the windows of the wavefront's rows, in the same slot
-  // numbering as base
-  __device__ __forceinline__ WindowMask(int base, int hl, int lo, int hi, int u0, int u1, int a0, int a1)
-      : d0(base + 4 * hl - lo), len(hi - lo), u_lo(u0 - base), u_hi(u1 - base), a_lo(a0 - base), a_hi(a1 - base) {
+  // numbering as base.  (What a lane needs is computed where a block is masked: most blocks are not.)
+  __device__ __forceinline__ WindowMask(int base_, int hl_, bool all_, int end_, int lo_, int hi_, int u0, int u1, int a0, int a1)
+      : base(base_), hl(hl_), all(all_), lo(lo_), hi(hi_), end(end_), u_lo(u0 - base_), u_hi(u1 - base_), a_lo(a0 - base_),
+        a_hi(a1 - base_) {
     asm("" : "+s"(one));
   }
+  // base + 4 hl - lo, and the window's length
+  __device__ __forceinline__ int d0() const { return base + 4 * hl - (all ? 0 : lo); }
+  __device__ __forceinline__ int len() const { return all ? end : hi - lo; }
   __device__ __forceinline__ bool full(int blk) const { return 32 * blk >= a_lo && 32 * blk + 32 <= a_hi; }
   __device__ __forceinline__ bool skip(int blk) const { return 32 * blk >= u_hi || 32 * blk + 32 <= u_lo; }
   __device__ __forceinline__ void load(int blk) {
     // (31 of 32 bits are enough: the highest one asked for is 27)
-    const int first = min(max(-d0 - 32 * blk, 0), 31), end = min(max(len - d0 - 32 * blk, 0), 31);
-    bits = ((1u << end) - 1u) & ~((1u << first) - 1u);
+    const int d = d0(), first = min(max(-d - 32 * blk, 0), 31), last = min(max(len() - d - 32 * blk, 0), 31);
+    bits = ((1u << last) - 1u) & ~((1u << first) - 1u);
   }
-  // (the fp32 kernels, which the matrix pipe bounds and whose registers are full, compare)
-  __device__ __forceinline__ bool in(int blk, int c) const {
-    return (unsigned)(d0 + blk * 32 + 8 * (c >> 2) + (c & 3)) < (unsigned)len;
-  }
-  // tile row `row` of block 0, whichever lane half holds its score
-  __device__ __forceinline__ bool meets(int row, int hl) const { return (unsigned)(d0 - 4 * hl + row) < (unsigned)len; }
   __device__ __forceinline__ float keep(int c, float x, float other) const {
     const unsigned in = (unsigned)__builtin_amdgcn_sbfe((int)bits, 8 * (c >> 2) + (c & 3), one);
     return __uint_as_float((__float_as_uint(x) & in) | (__float_as_uint(other) & ~in));
@@ -100,13 +100,12 @@ typedef unsigned Probs[2][2][4];
 // S^T = K Q^T of kBlocks 32-key blocks from block blk0 on: rows = keys, columns = this wave's queries; -inf
 // outside the pattern.
 template <int kBlocks, class Mask>
-__device__ __forceinline__ void fwd_scores(int blk0, const char* Kst, const bf16x8 (&qf)[4], const int (&koff)[4],
-                                           Mask& mask, f32x16 (&s)[kBlocks]) {
+__device__ __forceinline__ void fwd_scores(int blk0, const PlainAddr& k, const bf16x8 (&qf)[4], Mask& mask, f32x16 (&s)[kBlocks]) {
 #pragma unroll
   for (int jb = 0; jb < kBlocks; ++jb) {
     s[jb] = zero16();
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) s[jb] = mfma(read_plain(Kst + jb * 32 * 128, koff[ks]), qf[ks], s[jb]);
+    for (int ks = 0; ks < 4; ++ks) s[jb] = mfma(read_plain(k.a[ks] + jb * 32 * 128), qf[ks], s[jb]);
   }
   if constexpr (kBlocks == 2) {  // six of the eight operands ahead: all eight do not fit the registers
     __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
@@ -143,11 +142,10 @@ __device__ __forceinline__ float fwd_probs(f32x16 (&s)[kBlocks], float sc, float
   return kBlocks == 2 ? l[0] + l[kBlocks - 1] : l[0];
 }
 template <int kBlocks, class Mask>
-__device__ __forceinline__ float fwd_probs_new_max(int blk0, const char* Kst, const bf16x8 (&qf)[4],
-                                                   const int (&koff)[4], Mask& mask, float sc, float& m_run,
-                                                   Probs& pb) {
+__device__ __forceinline__ float fwd_probs_new_max(int blk0, const PlainAddr& k, const bf16x8 (&qf)[4], Mask& mask, float sc,
+                                                   float& m_run, Probs& pb) {
   f32x16 s[kBlocks];
-  fwd_scores<kBlocks>(blk0, Kst, qf, koff, mask, s);
+  fwd_scores<kBlocks>(blk0, k, qf, mask, s);
   float mx = s[0][0];
 #pragma unroll
   for (int jb = 0; jb < kBlocks; ++jb)
@@ -156,32 +154,28 @@ __device__ __forceinline__ float fwd_probs_new_max(int blk0, const char* Kst, co
   m_run = fmaxf(m_run, half_max(mx));
   return fwd_probs<kBlocks>(s, sc, (m_run == -INFINITY ? 0.f : m_run) * sc, pb);
 }
+// `tile`: LDS address of the K tile; the V tile follows.
 template <class Mask>
-__device__ __forceinline__ void fwd_tile(const char* Kst, const char* Vst, const bf16x8 (&qf)[4],
-                                         const int (&koff_)[4], const int (&voff_)[2][2], float sc, Mask&& mask,
+__device__ __forceinline__ void fwd_tile(unsigned tile, const bf16x8 (&qf)[4], const OperandLanes& lanes, float sc, Mask&& mask,
                                          f32x16 (&o_acc)[2], float& m_run, float& l_run, Reference& ref) {
-  if (mask.skip(0) && mask.skip(1)) return;
-  const bool both = !mask.skip(0) && !mask.skip(1);
-  const int blk0 = mask.skip(0) ? 1 : 0;
-  Kst += blk0 * 32 * 128;
-  Vst += blk0 * 32 * 128;
-  // (the other offsets are computed from these per tile: kept, they would be spilled)
-  int koff[4] = {koff_[0]}, voff[2][2] = {{voff_[0][0], voff_[0][1]}};
-  asm volatile("" : "+v"(koff[0]), "+v"(voff[0][0]), "+v"(voff[0][1]));
-  voff[1][0] = voff[0][0] ^ 64;
-  voff[1][1] = voff[0][1] ^ 64;
-#pragma unroll
-  for (int ks = 1; ks < 4; ++ks) koff[ks] = koff[0] ^ (ks << 5);
+  const bool skip0 = mask.skip(0), skip1 = mask.skip(1);
+  if (skip0 && skip1) return;
+  // (a word: a condition that lives across the branches below would go through a vector register)
+  const int both = __builtin_amdgcn_readfirstlane(!skip0 && !skip1);
+  const int blk0 = skip0 ? 1 : 0;
+  tile += blk0 * 32 * 128;
+  const PlainAddr k(lanes, tile);
   // O^T += V^T P^T
   auto add = [&](const Probs& pb, float l_tile) {
     l_run += l_tile;
+    const TransposedAddr v(lanes, tile + kTileBytes);
     auto block = [&](int jb) {
 #pragma unroll
       for (int tt = 0; tt < 2; ++tt) {
-        const char* vt = Vst + (jb * 32 + tt * 16) * 128;
+        const int at = (jb * 32 + tt * 16) * 128;
         const bf16x8 p = as_bf16x8(make_uint4(pb[jb][tt][0], pb[jb][tt][1], pb[jb][tt][2], pb[jb][tt][3]));
 #pragma unroll
-        for (int db = 0; db < 2; ++db) o_acc[db] = mfma(read_transposed(vt, voff[db][0], voff[db][1]), p, o_acc[db]);
+        for (int db = 0; db < 2; ++db) o_acc[db] = mfma(read_transposed(v.lo[db] + at, v.hi[db] + at), p, o_acc[db]);
       }
     };
     block(0);
@@ -192,11 +186,11 @@ __device__ __forceinline__ void fwd_tile(const char* Kst, const char* Vst, const
     float l_tile;
     if (both) {
       f32x16 s[2];
-      fwd_scores<2>(0, Kst, qf, koff, mask, s);
+      fwd_scores<2>(0, k, qf, mask, s);
       l_tile = fwd_probs<2>(s, sc, m_run * sc, pb);
     } else {
       f32x16 s[1];
-      fwd_scores<1>(blk0, Kst, qf, koff, mask, s);
+      fwd_scores<1>(blk0, k, qf, mask, s);
       l_tile = fwd_probs<1>(s, sc, m_run * sc, pb);
     }
     if (__all(l_tile <= kMaxTileSum)) return add(pb, l_tile);
@@ -204,8 +198,8 @@ __device__ __forceinline__ void fwd_tile(const char* Kst, const char* Vst, const
   }
   Probs pb;
   const float m_old = m_run;
-  const float l_tile = both ? fwd_probs_new_max<2>(0, Kst, qf, koff, mask, sc, m_run, pb)
-                            : fwd_probs_new_max<1>(blk0, Kst, qf, koff, mask, sc, m_run, pb);
+  const float l_tile = both ? fwd_probs_new_max<2>(0, k, qf, mask, sc, m_run, pb)
+                            : fwd_probs_new_max<1>(blk0, k, qf, mask, sc, m_run, pb);
   const float alpha = m_run == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m_old - m_run) * sc);
   l_run *= alpha;
 #pragma unroll
@@ -219,18 +213,18 @@ __device__ __forceinline__ void fwd_tile(const char* Kst, const char* Vst, const
 // dQ: P = exp2(S sc - lse2), dP^T = V dO^T, dS = P (dP - delta), dQ^T += K^T dS^T; one 32-key block
 // at a time, so only one block's scores are live.
 template <class Mask>
-__device__ __forceinline__ void dq_tile(const char* Kst, const char* Vst, const bf16x8 (&qf)[4],
-                                        const bf16x8 (&gf)[4], const int (&koff)[4],
-                                        const int (&toff)[2][2], float sc, float lse2, float delta,
-                                        Mask&& mask, f32x16 (&dq_acc)[2]) {
+__device__ __forceinline__ void dq_tile(unsigned tile, const bf16x8 (&qf)[4], const bf16x8 (&gf)[4], const OperandLanes& lanes,
+                                        float sc, float lse2, float delta, Mask&& mask, f32x16 (&dq_acc)[2]) {
+  const PlainAddr p(lanes, tile);  // K; V follows it
+  const TransposedAddr kt(lanes, tile);
 #pragma unroll
   for (int jb = 0; jb < 2; ++jb) {
     if (mask.skip(jb)) continue;
     f32x16 s = zero16(), dp = zero16();
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      s = mfma(read_plain(Kst + jb * 32 * 128, koff[ks]), qf[ks], s);     // S^T  = K Q^T
-      dp = mfma(read_plain(Vst + jb * 32 * 128, koff[ks]), gf[ks], dp);   // dP^T = V dO^T
+      s = mfma(read_plain(p.a[ks] + jb * 32 * 128), qf[ks], s);                 // S^T  = K Q^T
+      dp = mfma(read_plain(p.a[ks] + kTileBytes + jb * 32 * 128), gf[ks], dp);  // dP^T = V dO^T
     }
 #pragma unroll
     for (int c = 0; c < 16; ++c)
@@ -243,10 +237,9 @@ __device__ __forceinline__ void dq_tile(const char* Kst, const char* Vst, const 
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {
       const bf16x8 ds8 = pack8(s, 8 * tt);
-      const char* kt = Kst + (jb * 32 + tt * 16) * 128;
+      const int at = (jb * 32 + tt * 16) * 128;
 #pragma unroll
-      for (int db = 0; db < 2; ++db)
-        dq_acc[db] = mfma(read_transposed(kt, toff[db][0], toff[db][1]), ds8, dq_acc[db]);
+      for (int db = 0; db < 2; ++db) dq_acc[db] = mfma(read_transposed(kt.lo[db] + at, kt.hi[db] + at), ds8, dq_acc[db]);
     }
   }
 }
@@ -256,11 +249,11 @@ __device__ __forceinline__ void dq_tile(const char* Kst, const char* Vst, const 
 // contractions deliver S - lse / scale and dP - delta directly: P = exp2(that sc), dS = P (dP - delta);
 // dV^T += dO^T P, dK^T += Q^T dS.
 template <class Mask>
-__device__ __forceinline__ void dkv_tile(const char* Qst, const char* Gst, const float* lse_row,
-                                         const float* delta_row, const bf16x8 (&kf)[4],
-                                         const bf16x8 (&vf)[4], const int (&poff)[4],
-                                         const int (&toff)[2][2], float sc, int hl, Mask&& mask,
+__device__ __forceinline__ void dkv_tile(unsigned tile, const float* lse_row, const float* delta_row, const bf16x8 (&kf)[4],
+                                         const bf16x8 (&vf)[4], const OperandLanes& lanes, float sc, int hl, Mask&& mask,
                                          f32x16 (&dk_acc)[2], f32x16 (&dv_acc)[2]) {
+  const PlainAddr p(lanes, tile);  // Q; dO follows it
+  const TransposedAddr t(lanes, tile);
 #pragma unroll
   for (int ib = 0; ib < 2; ++ib) {
     if (mask.skip(ib)) continue;
@@ -275,8 +268,8 @@ __device__ __forceinline__ void dkv_tile(const char* Qst, const char* Gst, const
     }
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      s = mfma(read_plain(Qst + ib * 32 * 128, poff[ks]), kf[ks], s);     // S  = Q K^T
-      dp = mfma(read_plain(Gst + ib * 32 * 128, poff[ks]), vf[ks], dp);   // dP = dO V^T
+      s = mfma(read_plain(p.a[ks] + ib * 32 * 128), kf[ks], s);                 // S  = Q K^T
+      dp = mfma(read_plain(p.a[ks] + kTileBytes + ib * 32 * 128), vf[ks], dp);  // dP = dO V^T
     }
 #pragma unroll
     for (int c = 0; c < 16; ++c) {
@@ -294,12 +287,11 @@ __device__ __forceinline__ void dkv_tile(const char* Qst, const char* Gst, const
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {
       const bf16x8 p8 = pack8(s, 8 * tt), ds8 = pack8(dp, 8 * tt);
-      const char* gt = Gst + (ib * 32 + tt * 16) * 128;
-      const char* qt = Qst + (ib * 32 + tt * 16) * 128;
+      const int q_at = (ib * 32 + tt * 16) * 128, g_at = q_at + kTileBytes;
 #pragma unroll
       for (int db = 0; db < 2; ++db) {
-        dv_acc[db] = mfma(read_transposed(gt, toff[db][0], toff[db][1]), p8, dv_acc[db]);   // dV^T += dO^T P
-        dk_acc[db] = mfma(read_transposed(qt, toff[db][0], toff[db][1]), ds8, dk_acc[db]);  // dK^T += Q^T dS
+        dv_acc[db] = mfma(read_transposed(t.lo[db] + g_at, t.hi[db] + g_at), p8, dv_acc[db]);   // dV^T += dO^T P
+        dk_acc[db] = mfma(read_transposed(t.lo[db] + q_at, t.hi[db] + q_at), ds8, dk_acc[db]);  // dK^T += Q^T dS
       }
     }
   }
