@@ -1,27 +1,30 @@
-// fp32 MATE attention on the matrix cores (v_mfma_f32_32x32x2_f32: exact fp32 products, fp32
-// accumulation): the path for dtype f32, forward and backward.
+// fp32 MATE attention on the matrix cores: the path for dtype f32, forward and backward.
 //
-// Same pattern, tables and work units as the bf16 kernels (stream_plan.h), other proportions: the
-// fp32 matrix instruction does 1/16 of the bf16 one's work per cycle (150 TFLOP/s measured), so a
-// 32 x 32 block of scores costs 2048 cycles of matrix pipe per contraction and everything else --
-// loads, softmax, masks -- hides behind it.  So no shared tiles and no barriers in the loop: a
-// workgroup owns 32 rows (a quarter of a unit), its four wavefronts take every fourth 32-row tile of
-// the other side, each through LDS of its own, and their results are added in LDS at the end.
+// Products are formed from splits: x = x1 + x2 + x3 with bf16 parts of 8 significant bits each, which together hold all 24
+// bits of an fp32 value, and x y = x1 y1 + (x1 y2 + x2 y1) + (x1 y3 + x2 y2 + x3 y1).  What is left out is below
+// 2^-25 |x y|, an eighth of an fp32 rounding of the sums it goes into.  Six v_mfma_f32_32x32x16_bf16 (32 cycles, 16 of the contraction)
+// take the place of eight v_mfma_f32_32x32x2_f32 (64 cycles, 2 of it): 192 cycles for 512.
+// Sums are fp32 as before, and fewer of them are rounded (a matrix instruction adds sixteen products at once).
+// (A value above the largest bf16, 3.39e38, has no such split, nor has an infinity or a NaN: see accumulate_special.  The parts
+// of a value below 2^-108 lose bits.)
+//
+// Same pattern, tables and work units as the bf16 kernels (stream_plan.h), other proportions: no shared tiles and no
+// barriers in the loop.  A workgroup owns 32 rows (a quarter of a unit), its four wavefronts take every fourth
+// 32-row tile of the other side, each through LDS of its own, and their results are added in LDS at the end.
 // Small units also mean that a batch of short sequences fills the chip.
 //
-// A tile is loaded in whole rows (16 lanes x 16 bytes), one tile ahead, into registers and passes
-// through LDS into operand order.  Operands loaded straight from global memory (16 bytes of 64
-// different rows per instruction) touched four times as many cache lines per instruction, and the
-// first tiles of a launch took 10 us to arrive.
+// A tile is loaded in whole rows (16 lanes x 16 bytes) into registers, is split there, and passes through LDS into
+// operand order: three planes of 32 rows x 128 bytes, laid out and read like the tiles of the bf16 kernels (d2l.h).
 //
-// Measured (training step of 4 sequences of 512 tokens, 12 heads: tables, forward, dQ, dK/dV):
-// 90 us, 1390 us with one wavefront per query and dot products on the vector ALU.  Kernels 23, 28 and
-// 34 us: question-token owners (four tiles per wavefront) end last, the rest is over after 20 us.
+// Measured (4 sequences of 512 tokens, 12 heads), with the fp32 instruction and with splits: forward 22.8 -> 17.5 us, backward
+// 62.4 -> 45.6, a training step 91.3 -> 69; one sequence of 128, 4 heads 7.4 both ways.  Errors against 64 bits (relative, 2-norm):
+// O 2.6e-7 -> 1.4e-7, LSE 4.7e-8 -> 4.6e-8, dQ 3.9e-7 -> 3.0e-7, dK 4.0e-7 -> 3.1e-7, dV 3.8e-7 -> 3.0e-7.
+// What bounds it: a tile is 440 to 510 vector instructions (224 of them the splits of two tensors, 56 those of P or dS) beside
+// 1536 (forward) to 3072 cycles of matrix pipe; question-token owners have four tiles per wavefront and end last, and 74 KB of LDS
+// leave room for two workgroups on a CU.  (The splits interleaved with the matrix instructions of the tile before: 17.5 ->
+// 19.9 and 46 -> 64, most wavefronts have one or two tiles and would split one that nobody meets.)
 //
-// Operand layout of the instruction: lane l = 32 hl + m holds row (A) or column (B) m at k = hl; the
-// C tile is that of the bf16 instruction.  The order of a contraction is free:
-//   over dims      lane half hl takes dims 8 j + 4 hl + e: 16-byte loads, 32 contiguous bytes per row
-//   over tile rows step c pairs rows c_row(c, 0) and c_row(c, 1): the B operand is C register c itself
+// Operand layouts are those of the bf16 kernels; the second contraction's operand of P or dS is C registers 8 tt .. 8 tt + 7.
 #include <hip/hip_runtime.h>
 
 #include "d2l.h"
@@ -42,13 +45,42 @@ __device__ __forceinline__ f32x16 mfma1(float a, float b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-// LDS tiles: 32 rows of 64 floats and a pad of 4, which spreads row accesses (16 bytes of 16 rows at
+// The three planes of a tile, and a wavefront's piece of LDS.
+constexpr int kPlane = kRows * 128;
+constexpr int kPlanes = 3 * kPlane;
+
+// Tiles of whole fp32 values (accumulate_special, and results on their way out): 32 rows of 64 floats and a pad of 4, which spreads row accesses (16 bytes of 16 rows at
 // once) over the 64 banks; column reads (rows r and r + 4 at once) overlap in a quarter of them, which
-// the matrix pipe hides.  The pad of an owned tile keeps the row's token and its delta.  (An XOR
-// swizzle needs no pad, but its addresses are not base + constant: 30 registers more, and spills.)
+// the matrix pipe hides.
 constexpr int kStride = kD + 4;
-constexpr int kTileFloats = kRows * kStride;
-constexpr int kTokAt = kD, kDeltaAt = kD + 1;
+static_assert(kRows * kStride * 4 <= kPlanes, "a wavefront's piece holds either form");
+
+// Two values as three words of bf16 parts (rounded to nearest, so that what is left has a sign of its own).  A dot product with
+// (-1, 0) or (0, -1) takes a part off its value in one instruction, exactly.
+__device__ __forceinline__ void split2(float x, float y, unsigned (&w)[3]) {
+  // (-1, 0) and (0, -1), in scalar registers: written as constants, one becomes the instruction's inline -1.0, which the
+  // hardware reads as 32 bits, that is as the other
+  unsigned one = 0x0000bf80u, other = 0xbf800000u;
+  asm("" : "+s"(one), "+s"(other));
+  const bf16x2 minus_x = __builtin_bit_cast(bf16x2, one), minus_y = __builtin_bit_cast(bf16x2, other);
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    w[p] = pack2(x, y);
+    if (p == 2) break;
+    const bf16x2 part = __builtin_bit_cast(bf16x2, w[p]);
+    x = __builtin_amdgcn_fdot2_f32_bf16(part, minus_x, x, false);
+    y = __builtin_amdgcn_fdot2_f32_bf16(part, minus_y, y, false);
+  }
+}
+// 16 bytes of a row to the planes at `tile`: piece = dims 4 piece .. + 3 of row `row`.
+__device__ __forceinline__ void put_split(char* tile, int row, int piece, const f32x4& v) {
+  unsigned a[3], b[3];
+  split2(v.x, v.y, a);
+  split2(v.z, v.w, b);
+  char* at = tile + row * 128 + (((piece >> 1) ^ swz(row & 15)) << 4) + 8 * (piece & 1);
+#pragma unroll
+  for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2*>(at + p * kPlane) = make_uint2(a[p], b[p]);
+}
 
 // A lane's window of the tile's rows.  (Compared per pair: the matrix pipe bounds these kernels, and their registers are
 // full.)
@@ -59,42 +91,96 @@ struct SlotWindow {
   __device__ __forceinline__ bool meets(int row, int hl) const { return (unsigned)(d0 - 4 * hl + row) < (unsigned)len; }
 };
 
+// Piece l % 16 of a row; X is wave-uniform and the offset in it below 2^32 bytes, which is the form of a load that takes
+// no 64-bit arithmetic.
+__device__ __forceinline__ f32x4 load_piece(const float* X, int tok, int lane) {
+  return *reinterpret_cast<const f32x4*>(reinterpret_cast<const char*>(X) + ((unsigned)tok * (kD * 4u) + (unsigned)(lane & 15) * 16u));
+}
+
 // A tile on its way from global memory: lane l holds piece l % 16 of rows l / 16 + 4 i.
 struct TileRegs {
   f32x4 v[8];
   // `tok`: lanes m and m + 32 hold the token of tile row m
   __device__ __forceinline__ void load(const float* X, int tok, int lane) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      v[i] = *reinterpret_cast<const f32x4*>(X + (unsigned)__shfl(tok, (lane >> 4) + 4 * i, 64) * kD + 4 * (lane & 15));
+    for (int i = 0; i < 8; ++i) v[i] = load_piece(X, __shfl(tok, (lane >> 4) + 4 * i, 64), lane);
+  }
+  __device__ __forceinline__ void split(char* tile, int lane) const {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) put_split(tile, (lane >> 4) + 4 * i, lane & 15, v[i]);
   }
   __device__ __forceinline__ void put(float* tile, int lane) const {
 #pragma unroll
     for (int i = 0; i < 8; ++i) *reinterpret_cast<f32x4*>(tile + ((lane >> 4) + 4 * i) * kStride + 4 * (lane & 15)) = v[i];
   }
 };
-// The owned rows of a tensor into an LDS tile: every wavefront brings eight of them.
-__device__ __forceinline__ void put_owned(float* tile, const float* X, int pos, int wave, int lane) {
+// The owned rows of a tensor into planes: every wavefront brings eight of them.
+struct OwnedRows {
+  f32x4 v[2];
+  __device__ __forceinline__ void load(const float* X, int pos, int wave, int lane) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int row = 8 * wave + 4 * i + (lane >> 4);
-    *reinterpret_cast<f32x4*>(tile + row * kStride + 4 * (lane & 15)) =
-        *reinterpret_cast<const f32x4*>(X + (unsigned)__shfl(pos, row, 64) * kD + 4 * (lane & 15));
+    for (int i = 0; i < 2; ++i) v[i] = load_piece(X, __shfl(pos, 8 * wave + 4 * i + (lane >> 4), 64), lane);
+  }
+  __device__ __forceinline__ void split(char* tile, int wave, int lane) const {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) put_split(tile, 8 * wave + 4 * i + (lane >> 4), lane & 15, v[i]);
+  }
+};
+
+// Over dims: rows of the tile against rows of an owned one, both in planes.  (The small products have a sum of their own, which
+// rounds them against each other and not against the large ones.)  kOwned: which of the workgroup's owned tiles.
+template <int kOwned = 0>
+__device__ __forceinline__ f32x16 contract(const PlainAddr& a, const PlainAddr& b) {
+  f32x16 sum = zero16(), small = zero16();
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    bf16x8 x[3], y[3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      x[p] = read_plain(a.a[ks] + p * kPlane);
+      y[p] = read_plain(b.a[ks] + kOwned * kPlanes + p * kPlane);
+    }
+    small = mfma(x[2], y[0], small);
+    sum = mfma(x[0], y[0], sum);
+    small = mfma(x[0], y[2], small);
+    small = mfma(x[1], y[1], small);
+    small = mfma(x[1], y[0], small);
+    small = mfma(x[0], y[1], small);
+  }
+#pragma unroll
+  for (int c = 0; c < 16; ++c) sum[c] += small[c];
+  return sum;
+}
+// Over tile rows: the tile's columns against C registers.
+__device__ __forceinline__ void accumulate(f32x16 (&acc)[2], const TransposedAddr& t, const f32x16& p) {
+#pragma unroll
+  for (int tt = 0; tt < 2; ++tt) {
+    unsigned w[4][3];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) split2(p[8 * tt + 2 * e], p[8 * tt + 2 * e + 1], w[e]);
+    bf16x8 y[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) y[i] = as_bf16x8(make_uint4(w[0][i], w[1][i], w[2][i], w[3][i]));
+    bf16x8 x[2][3];
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+      for (int i = 0; i < 3; ++i) x[db][i] = read_transposed(t.lo[db] + i * kPlane + tt * 2048, t.hi[db] + i * kPlane + tt * 2048);
+    constexpr int kX[6] = {2, 0, 1, 1, 0, 0}, kY[6] = {0, 2, 1, 0, 1, 0};  // smallest products first
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+#pragma unroll
+      for (int db = 0; db < 2; ++db) acc[db] = mfma(x[db][kX[i]], y[kY[i]], acc[db]);
   }
 }
 
-// Over dims: row m of the wavefront's tile and of an owned one.
-__device__ __forceinline__ f32x16 contract(const float* a_tile, const float* b_tile, int m, int hl, f32x16 c) {
+// The same with whole fp32 values.  Over dims: row m of the tile, and an owned row in registers (dims 8 j + 4 hl + e).
+__device__ __forceinline__ void load_row(f32x4 (&b)[8], const float* X, int pos, int hl) {
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const f32x4 a = *reinterpret_cast<const f32x4*>(a_tile + m * kStride + 8 * j + 4 * hl);
-    const f32x4 b = *reinterpret_cast<const f32x4*>(b_tile + m * kStride + 8 * j + 4 * hl);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) c = mfma1(a[e], b[e], c);
-  }
-  return c;
+  for (int j = 0; j < 8; ++j) b[j] = *reinterpret_cast<const f32x4*>(X + (unsigned)pos * kD + 8 * j + 4 * hl);
 }
-__device__ __forceinline__ f32x16 contract(const float* a_tile, const f32x4 (&b)[8], int m, int hl, f32x16 c) {
+__device__ __forceinline__ f32x16 contract(const float* a_tile, const f32x4 (&b)[8], int m, int hl) {
+  f32x16 c = zero16();
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const f32x4 a = *reinterpret_cast<const f32x4*>(a_tile + m * kStride + 8 * j + 4 * hl);
@@ -113,11 +199,11 @@ __device__ __forceinline__ void accumulate(f32x16 (&acc)[2], const float* tile, 
   }
 }
 
-// The same for a tile that may hold an infinity or a NaN.  The matrix instruction multiplies every weight with
+// For a tile that may hold an infinity or a NaN, or a value that has no split.  The matrix instruction multiplies every weight with
 // every row, and 0 x Inf is NaN: such a row would reach the owned rows that do not meet it.  So these rows
 // go through the vector ALU, owned rows that meet them only, and are cleared for the matrix instruction.
-// In the main loops this would take 30 to 40 registers that are not there; a wavefront whose results are
-// not all finite when its loop ends does its tiles again this way, without a prefetch.  (Looking for such values
+// A wavefront whose results are not all finite when its loop ends does its tiles again this way, without splits or a
+// prefetch.  (Looking for such values
 // in every tile instead of in the results: 88.8 us a training step for 85.6.)
 __device__ __forceinline__ void accumulate_special(f32x16 (&acc)[2], float* tile, int m, int hl, f32x16& p,
                                                    const SlotWindow& mask) {
@@ -226,10 +312,11 @@ struct Rows {
 };
 
 // Sum of the four wavefronts' accumulators, stored as whole rows: lane m's column is owned row m.
-// `lds` = the wavefronts' tiles, `own` = the owned tile that keeps the rows' tokens.
-__device__ __forceinline__ void store_sum(const f32x16 (&acc)[2], float mul, float* lds, const float* own, float* out,
+// `lds` = the wavefronts' pieces, `row_tok` = the owned rows' tokens.
+__device__ __forceinline__ float* piece_of(char* lds, int wave) { return reinterpret_cast<float*>(lds + wave * kPlanes); }
+__device__ __forceinline__ void store_sum(const f32x16 (&acc)[2], float mul, char* lds, const int* row_tok, float* out,
                                           int wave, int m, int hl) {
-  float* mine = lds + wave * kTileFloats;
+  float* mine = piece_of(lds, wave);
 #pragma unroll
   for (int db = 0; db < 2; ++db)
 #pragma unroll
@@ -240,10 +327,10 @@ __device__ __forceinline__ void store_sum(const f32x16 (&acc)[2], float mul, flo
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const int row = (threadIdx.x >> 4) + 16 * i, piece = threadIdx.x & 15, tok = __float_as_int(own[row * kStride + kTokAt]);
-    f32x4 s = *reinterpret_cast<const f32x4*>(lds + row * kStride + 4 * piece);
+    const int row = (threadIdx.x >> 4) + 16 * i, piece = threadIdx.x & 15, tok = row_tok[row];
+    f32x4 s = *reinterpret_cast<const f32x4*>(piece_of(lds, 0) + row * kStride + 4 * piece);
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) s += *reinterpret_cast<const f32x4*>(lds + w * kTileFloats + row * kStride + 4 * piece);
+    for (int w = 1; w < kWaves; ++w) s += *reinterpret_cast<const f32x4*>(piece_of(lds, w) + row * kStride + 4 * piece);
     if (tok >= 0) *reinterpret_cast<f32x4*>(out + (size_t)tok * kD + 4 * piece) = s;
   }
 }
@@ -272,9 +359,11 @@ __device__ __forceinline__ void zero_pads(const Quarter& q, float* const (&out)[
 // ======================================================================================
 // forward
 // ======================================================================================
-__global__ __launch_bounds__(kThreads, 3) void fwd_f32_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) float lds[kWaves * kTileFloats], own[kTileFloats];
+__global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) char lds[kWaves * kPlanes];
+  __shared__ __attribute__((aligned(1024))) char own[kPlanes];
   __shared__ float2 stat[kWaves][kRows];
+  __shared__ int row_tok[kRows];
   Quarter q;
   if (!take_quarter(a, q)) return;
   const int tid = threadIdx.x, lane = tid & 63, m = lane & 31, hl = lane >> 5;
@@ -290,16 +379,21 @@ __global__ __launch_bounds__(kThreads, 3) void fwd_f32_kernel(AttnArgs a) {
     return;
   }
   const Rows r(a, q, m);
-  if (tid < kRows) own[tid * kStride + kTokAt] = __int_as_float(r.valid ? r.pos : -1);
+  if (tid < kRows) row_tok[tid] = r.valid ? r.pos : -1;
   const int t0 = (wave + q.turn) & (kWaves - 1);
   int tok = r.token(t0, m), tok_next = r.token(t0 + kWaves, m);
   TileRegs key, val;
+  OwnedRows q_rows;
+  q_rows.load(Q, r.pos, wave, lane);
   key.load(K, tok, lane);
-  put_owned(own, Q, r.pos, wave, lane);
   val.load(V, tok, lane);
   keep_order();
+  q_rows.split(own, wave, lane);
   __syncthreads();
-  float* tile = lds + wave * kTileFloats;
+  char* const tile = lds + wave * kPlanes;
+  const OperandLanes lanes(lane);
+  const PlainAddr tile_rows(lanes, lds_addr(tile)), own_rows(lanes, lds_addr(own));
+  const TransposedAddr tile_cols(lanes, lds_addr(tile));
 
   const float sc = a.scale * kLog2e;  // scores are kept raw; exp2(s sc - m sc)
   f32x16 o[2] = {zero16(), zero16()};
@@ -326,31 +420,40 @@ __global__ __launch_bounds__(kThreads, 3) void fwd_f32_kernel(AttnArgs a) {
   };
   for (int t = t0; t < r.n; t += kWaves) {
     const int tok_after = r.token(t + 2 * kWaves, m);
-    key.put(tile, lane);
+    key.split(tile, lane);
     key.load(K, tok_next, lane);                          // the next tile's keys land during this one
     keep_order();
-    f32x16 s = contract(tile, own, m, hl, zero16());      // S^T = K Q^T
-    val.put(tile, lane);                                  // (the keys have been read)
+    f32x16 s = contract(tile_rows, own_rows);             // S^T = K Q^T
+    keep_order();
+    val.split(tile, lane);                                // (the keys have been read)
     val.load(V, tok_next, lane);
     keep_order();
     probs(s, r.mask(t, hl));
-    accumulate(o, tile, m, hl, s);                        // O^T += V^T P^T
+    accumulate(o, tile_cols, s);                          // O^T += V^T P^T
+    keep_order();
     tok_next = tok_after;
   }
   if (__builtin_expect(any_special(o), 0)) {
     o[0] = o[1] = zero16();
     m_run = -INFINITY;
     l_run = 0.f;
+    float* const x = piece_of(lds, wave);
+    f32x4 q_own[8];
+    load_row(q_own, Q, r.pos, hl);
     for (int t = t0; t < r.n; t += kWaves) {
       tok = r.token(t, m);
       key.load(K, tok, lane);
-      key.put(tile, lane);
-      f32x16 s = contract(tile, own, m, hl, zero16());
+      key.put(x, lane);
+      keep_order();
+      f32x16 s = contract(x, q_own, m, hl);
+      keep_order();
       val.load(V, tok, lane);
-      val.put(tile, lane);
+      val.put(x, lane);
+      keep_order();
       const SlotWindow mask = r.mask(t, hl);
       probs(s, mask);
-      accumulate_special(o, tile, m, hl, s, mask);
+      accumulate_special(o, x, m, hl, s, mask);
+      keep_order();
     }
   }
   // the wavefronts' maxima and sums, then their sum of O scaled to the common maximum
@@ -369,14 +472,17 @@ __global__ __launch_bounds__(kThreads, 3) void fwd_f32_kernel(AttnArgs a) {
   }
   if (wave == 0 && hl == 0 && r.valid) a.lse[bh + r.pos] = (m_all * sc + __builtin_amdgcn_logf(l_all)) * kLn2;
   const float mul = weight(m_run, m_all) / l_all;
-  store_sum(o, mul, lds, own, O, wave, m, hl);
+  store_sum(o, mul, lds, row_tok, O, wave, m, hl);
 }
 
 // ======================================================================================
 // dQ, and delta = rowsum(dO * O) for the dK/dV kernel
 // ======================================================================================
-__global__ __launch_bounds__(kThreads, 3) void bwd_dq_f32_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) float lds[kWaves * kTileFloats], own_q[kTileFloats], own_g[kTileFloats];
+__global__ __launch_bounds__(kThreads, 2) void bwd_dq_f32_kernel(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) char lds[kWaves * kPlanes];
+  __shared__ __attribute__((aligned(1024))) char own[2 * kPlanes];  // Q, dO
+  __shared__ int row_tok[kRows];
+  __shared__ float row_delta[kRows];
   Quarter q;
   if (!take_quarter(a, q)) return;
   const int tid = threadIdx.x, lane = tid & 63, m = lane & 31, hl = lane >> 5;
@@ -394,37 +500,37 @@ __global__ __launch_bounds__(kThreads, 3) void bwd_dq_f32_kernel(AttnArgs a) {
     return;
   }
   const Rows r(a, q, m);
-  if (tid < kRows) own_q[tid * kStride + kTokAt] = __int_as_float(r.valid ? r.pos : -1);
+  if (tid < kRows) row_tok[tid] = r.valid ? r.pos : -1;
   const int t0 = (wave + q.turn) & (kWaves - 1);
   int tok = r.token(t0, m), tok_next = r.token(t0 + kWaves, m);
   const float lse2 = a.lse[bh + r.pos] * kLog2e, sc = a.scale * kLog2e;
   TileRegs key, val;
-  val.load(V, tok, lane);
   {  // owned Q and dO rows to LDS; delta of the eight rows this wavefront brings, 16 lanes per row
-    f32x4 g[2], o[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const unsigned off = (unsigned)__shfl(r.pos, 8 * wave + 4 * i + (lane >> 4), 64) * kD + 4 * (lane & 15);
-      g[i] = *reinterpret_cast<const f32x4*>(dO + off);
-      o[i] = *reinterpret_cast<const f32x4*>(O + off);
-    }
-    put_owned(own_q, Q, r.pos, wave, lane);
+    OwnedRows g, o, qr;
+    g.load(dO, r.pos, wave, lane);
+    o.load(O, r.pos, wave, lane);
+    qr.load(Q, r.pos, wave, lane);
+    val.load(V, tok, lane);
     key.load(K, tok, lane);
     keep_order();
+    g.split(own + kPlanes, wave, lane);
+    qr.split(own, wave, lane);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int row = 8 * wave + 4 * i + (lane >> 4);
-      *reinterpret_cast<f32x4*>(own_g + row * kStride + 4 * (lane & 15)) = g[i];
-      float d = g[i].x * o[i].x + g[i].y * o[i].y + g[i].z * o[i].z + g[i].w * o[i].w;
+      const f32x4 &x = g.v[i], &y = o.v[i];
+      float d = x.x * y.x + x.y * y.y + x.z * y.z + x.w * y.w;
 #pragma unroll
-      for (int x = 8; x >= 1; x >>= 1) d += __shfl_xor(d, x, 64);
-      if ((lane & 15) == 0) own_g[row * kStride + kDeltaAt] = d;
+      for (int e = 8; e >= 1; e >>= 1) d += __shfl_xor(d, e, 64);
+      if ((lane & 15) == 0) row_delta[8 * wave + 4 * i + (lane >> 4)] = d;
     }
   }
   __syncthreads();
-  const float delta = own_g[m * kStride + kDeltaAt];
+  const float delta = row_delta[m];
   if (wave == 0 && hl == 0 && r.valid) a.delta[bh + r.pos] = delta;
-  float* tile = lds + wave * kTileFloats;
+  char* const tile = lds + wave * kPlanes;
+  const OperandLanes lanes(lane);
+  const PlainAddr tile_rows(lanes, lds_addr(tile)), own_rows(lanes, lds_addr(own));
+  const TransposedAddr tile_cols(lanes, lds_addr(tile));
 
   f32x16 dq[2] = {zero16(), zero16()};
   auto dscores = [&](f32x16& s, const f32x16& dp, const SlotWindow& mask) {  // S^T -> dS^T
@@ -434,38 +540,45 @@ __global__ __launch_bounds__(kThreads, 3) void bwd_dq_f32_kernel(AttnArgs a) {
   };
   for (int t = t0; t < r.n; t += kWaves) {
     const int tok_after = r.token(t + 2 * kWaves, m);
-    val.put(tile, lane);
+    val.split(tile, lane);
     val.load(V, tok_next, lane);
     keep_order();
-    const f32x16 dp = contract(tile, own_g, m, hl, zero16());  // dP^T = V dO^T
-    key.put(tile, lane);
+    const f32x16 dp = contract<1>(tile_rows, own_rows);  // dP^T = V dO^T
+    keep_order();
+    key.split(tile, lane);
     key.load(K, tok_next, lane);
     keep_order();
-    f32x16 s = contract(tile, own_q, m, hl, zero16());         // S^T  = K Q^T
+    f32x16 s = contract<0>(tile_rows, own_rows);         // S^T  = K Q^T
     dscores(s, dp, r.mask(t, hl));
-    accumulate(dq, tile, m, hl, s);                            // dQ^T += K^T dS^T
+    accumulate(dq, tile_cols, s);                   // dQ^T += K^T dS^T
+    keep_order();
     tok_next = tok_after;
   }
   if (__builtin_expect(any_special(dq), 0)) {
     dq[0] = dq[1] = zero16();
+    float* const x = piece_of(lds, wave);
     for (int t = t0; t < r.n; t += kWaves) {
       tok = r.token(t, m);
+      f32x4 own[8];
+      load_row(own, dO, r.pos, hl);
       val.load(V, tok, lane);
-      val.put(tile, lane);
+      val.put(x, lane);
       keep_order();
-      const f32x16 dp = contract(tile, own_g, m, hl, zero16());
+      const f32x16 dp = contract(x, own, m, hl);
       keep_order();
+      load_row(own, Q, r.pos, hl);
       key.load(K, tok, lane);
-      key.put(tile, lane);
+      key.put(x, lane);
       keep_order();
-      f32x16 s = contract(tile, own_q, m, hl, zero16());
+      f32x16 s = contract(x, own, m, hl);
       const SlotWindow mask = r.mask(t, hl);
       dscores(s, dp, mask);
-      accumulate_special(dq, tile, m, hl, s, mask);
+      accumulate_special(dq, x, m, hl, s, mask);
+      keep_order();
     }
   }
   __syncthreads();
-  store_sum(dq, a.scale, lds, own_q, dQ, wave, m, hl);
+  store_sum(dq, a.scale, lds, row_tok, dQ, wave, m, hl);
 }
 
 // ======================================================================================
@@ -473,8 +586,10 @@ __global__ __launch_bounds__(kThreads, 3) void bwd_dq_f32_kernel(AttnArgs a) {
 // windows as in the forward, read the other way round)
 // ======================================================================================
 __global__ __launch_bounds__(kThreads, 2) void bwd_dkv_f32_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) float lds[2 * kWaves * kTileFloats];
-  __shared__ __attribute__((aligned(16))) float own_k[kTileFloats];
+  __shared__ __attribute__((aligned(1024))) char lds[kWaves * kPlanes];
+  __shared__ __attribute__((aligned(1024))) char own[2 * kPlanes];  // K, V
+  __shared__ __attribute__((aligned(16))) float stat[kWaves][2][kRows];  // of the wavefront's tile: lse in base 2, delta
+  __shared__ int row_tok[kRows];
   Quarter q;
   if (!take_quarter(a, q)) return;
   const int tid = threadIdx.x, lane = tid & 63, m = lane & 31, hl = lane >> 5;
@@ -492,75 +607,111 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dkv_f32_kernel(AttnArgs a) {
     return;
   }
   const Rows r(a, q, m);
-  if (tid < kRows) own_k[tid * kStride + kTokAt] = __int_as_float(r.valid ? r.pos : -1);
+  if (tid < kRows) row_tok[tid] = r.valid ? r.pos : -1;
   const int t0 = (wave + q.turn) & (kWaves - 1);
   int tok = r.token(t0, m), tok_next = r.token(t0 + kWaves, m);
   const float *lse = a.lse + bh, *delta = a.delta + bh;
   float row_lse = lse[tok], row_delta = delta[tok];  // of tile row m
-  float *tile_q = lds + wave * kTileFloats, *tile_g = tile_q + kWaves * kTileFloats;
   TileRegs qry, grad;
-  qry.load(Q, tok, lane);
-  put_owned(own_k, K, r.pos, wave, lane);
-  put_owned(lds, V, r.pos, wave, lane);  // passes through the first tile into registers: there is no room for both
-  grad.load(dO, tok, lane);
-  keep_order();
+  {
+    OwnedRows k_rows, v_rows;
+    k_rows.load(K, r.pos, wave, lane);
+    v_rows.load(V, r.pos, wave, lane);
+    grad.load(dO, tok, lane);
+    qry.load(Q, tok, lane);
+    keep_order();
+    k_rows.split(own, wave, lane);
+    v_rows.split(own + kPlanes, wave, lane);
+  }
   __syncthreads();
-  f32x4 v_own[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) v_own[j] = *reinterpret_cast<const f32x4*>(lds + m * kStride + 8 * j + 4 * hl);
-  __syncthreads();
+  char* const tile = lds + wave * kPlanes;
+  const OperandLanes lanes(lane);
+  const PlainAddr tile_rows(lanes, lds_addr(tile)), own_rows(lanes, lds_addr(own));
+  const TransposedAddr tile_cols(lanes, lds_addr(tile));
   const float sc = a.scale * kLog2e;
 
   f32x16 dk[2] = {zero16(), zero16()}, dv[2] = {zero16(), zero16()};
+  float* const my_stat = &stat[wave][0][0];
+  auto put_stat = [&]() {
+    if (hl == 0) {
+      my_stat[m] = row_lse * kLog2e;
+      my_stat[kRows + m] = row_delta;
+    }
+  };
   // S -> P, dP -> dS.  (A pair outside the pattern has P = 0 and so dS = 0, unless a value is not finite: then dS is
   // masked as well, in the second pass.)
   auto dscores = [&](f32x16& s, f32x16& dp, const SlotWindow& mask, bool mask_ds) {
 #pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      const float l = __shfl(row_lse, c_row(c, hl), 64), d = __shfl(row_delta, c_row(c, hl), 64);
-      s[c] = mask.in(c) ? __builtin_amdgcn_exp2f(fmaf(s[c], sc, -l * kLog2e)) : 0.f;
-      dp[c] = s[c] * (dp[c] - d);
-      if (mask_ds) dp[c] = mask.in(c) ? dp[c] : 0.f;
+    for (int g = 0; g < 4; ++g) {
+      const f32x4 l = *reinterpret_cast<const f32x4*>(my_stat + 8 * g + 4 * hl);
+      const f32x4 d = *reinterpret_cast<const f32x4*>(my_stat + kRows + 8 * g + 4 * hl);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int c = 4 * g + e;
+        s[c] = mask.in(c) ? __builtin_amdgcn_exp2f(fmaf(s[c], sc, -l[e])) : 0.f;
+        dp[c] = s[c] * (dp[c] - d[e]);
+        if (mask_ds) dp[c] = mask.in(c) ? dp[c] : 0.f;
+      }
     }
   };
   for (int t = t0; t < r.n; t += kWaves) {
     const int tok_after = r.token(t + 2 * kWaves, m);
-    qry.put(tile_q, lane);
-    qry.load(Q, tok_next, lane);
-    grad.put(tile_g, lane);
-    grad.load(dO, tok_next, lane);
+    // (One tile of planes at a time, so that two workgroups fit a CU; the gradients are split twice for it.)
+    grad.split(tile, lane);
+    put_stat();
     keep_order();
-    f32x16 s = contract(tile_q, own_k, m, hl, zero16());   // S  = Q K^T
-    f32x16 dp = contract(tile_g, v_own, m, hl, zero16());  // dP = dO V^T
+    f32x16 dp = contract<1>(tile_rows, own_rows);  // dP = dO V^T
+    keep_order();
+    qry.split(tile, lane);
+    qry.load(Q, tok_next, lane);
+    keep_order();
+    f32x16 s = contract<0>(tile_rows, own_rows);   // S  = Q K^T
     dscores(s, dp, r.mask(t, hl), false);
     row_lse = lse[tok_next];
     row_delta = delta[tok_next];
+    accumulate(dk, tile_cols, dp);            // dK^T += Q^T dS
     keep_order();
-    accumulate(dv, tile_g, m, hl, s);                      // dV^T += dO^T P
-    accumulate(dk, tile_q, m, hl, dp);                     // dK^T += Q^T dS
+    grad.split(tile, lane);
+    grad.load(dO, tok_next, lane);
+    keep_order();
+    accumulate(dv, tile_cols, s);             // dV^T += dO^T P
+    keep_order();
     tok_next = tok_after;
   }
   if (__builtin_expect(any_special(dk) || any_special(dv), 0)) {
     dk[0] = dk[1] = dv[0] = dv[1] = zero16();
+    float* const x = piece_of(lds, wave);
     for (int t = t0; t < r.n; t += kWaves) {
       tok = r.token(t, m);
       row_lse = lse[tok];
       row_delta = delta[tok];
-      qry.load(Q, tok, lane);
-      qry.put(tile_q, lane);
+      f32x4 own[8];
+      load_row(own, V, r.pos, hl);
       grad.load(dO, tok, lane);
-      grad.put(tile_g, lane);
-      f32x16 s = contract(tile_q, own_k, m, hl, zero16());
-      f32x16 dp = contract(tile_g, v_own, m, hl, zero16());
+      grad.put(x, lane);
+      put_stat();
+      keep_order();
+      f32x16 dp = contract(x, own, m, hl);
+      keep_order();
+      load_row(own, K, r.pos, hl);
+      qry.load(Q, tok, lane);
+      qry.put(x, lane);
+      keep_order();
+      f32x16 s = contract(x, own, m, hl);
       const SlotWindow mask = r.mask(t, hl);
       dscores(s, dp, mask, true);
-      accumulate_special(dv, tile_g, m, hl, s, mask);
-      accumulate_special(dk, tile_q, m, hl, dp, mask);
+      accumulate_special(dk, x, m, hl, dp, mask);
+      keep_order();
+      grad.put(x, lane);
+      keep_order();
+      accumulate_special(dv, x, m, hl, s, mask);
+      keep_order();
     }
   }
   __syncthreads();
-  store_sum(dk, a.scale, lds, own_k, dK, wave, m, hl);
-  store_sum(dv, 1.f, lds + kWaves * kTileFloats, own_k, dV, wave, m, hl);
+  store_sum(dk, a.scale, lds, row_tok, dK, wave, m, hl);
+  __syncthreads();
+  store_sum(dv, 1.f, lds, row_tok, dV, wave, m, hl);
 }
 
 }  // namespace
