@@ -156,7 +156,9 @@ __global__ __launch_bounds__(kThreads) void fwd_dense_kernel(DenseArgs a) {
   unsigned short* O = static_cast<unsigned short*>(a.out) + bh * kD;
 
   DenseStream stream{K, V, nullptr, nullptr, lds, kStage, N, wave, lane, make_load_lane(wave, lane)};
-  // everything in one round trip: the owned rows, the first two tiles, the codes
+  // everything in one round trip: the owned rows, the first two tiles, the codes.  (Whole owned rows, which the backward
+  // loads, have to pass through the place of the second tile first: 8.5 -> 8.2 us for 32 x 128, 12 heads, but 16.8 -> 17.4 for
+  // 64 x 128, 16 heads, and 4.8 -> 5.1 for one sequence of 64.)
   const int n_tiles = (N + BN - 1) / BN;
   const int pos = min(u.tile * BM + wave * 32 + m, N - 1);
   bf16x8 qf[4];
@@ -340,7 +342,7 @@ __global__ __launch_bounds__(kThreads) void bwd_dkv_dense_kernel(DenseArgs a) {
 // and dP are computed once for all three gradients (the two kernels above compute them twice, and of
 // their 13 us each at B = 32, H = 12, N = 128 five are the launch): dK and dV accumulate in registers, the
 // bf16 dS^T of up to 128 queries goes through LDS, and dQ^T = K^T dS^T with both operands read transposed
-// (both permute the keys of a slice the same way).  17.4 to 18.6 us in place of 25.6; reading five tensors and
+// (both permute the keys of a slice the same way).  15.3 us in place of 25.6; reading five tensors and
 // writing three once takes 10 at the rate of a large copy.
 template <int NW>
 struct SmallShape {
@@ -350,17 +352,18 @@ struct SmallShape {
   static constexpr int kKeyBytes = kKeys * 128, kQryBytes = kQueries * 128;
   static constexpr int kDsBytes = kKeys * kQueries * 2;
   static constexpr bool kOverlay = kDsBytes <= 2 * kQryBytes;  // dS^T over the Q and dO tiles
-  // K tiles | Q tiles | dO tiles | dS^T; dQ rows are staged over the Q tiles, dK and dV rows over the K tiles
-  static constexpr int kLds = kKeyBytes + 2 * kQryBytes + (kOverlay ? 0 : kDsBytes);
+  // K tiles | Q tiles | dO tiles | V tiles, dS^T (if it is not over Q and dO); dQ rows are staged over the Q tiles, dK
+  // and dV rows over the K tiles
+  static constexpr int kLds = kKeyBytes + 2 * kQryBytes + (kOverlay || kKeyBytes > kDsBytes ? kKeyBytes : kDsBytes);
 };
 template <int NW>
-__global__ __launch_bounds__(64 * NW, 2) void bwd_dense_small_kernel(DenseArgs a) {
+__global__ __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) void bwd_dense_small_kernel(DenseArgs a) {
   using S = SmallShape<NW>;
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   __shared__ __attribute__((aligned(16))) unsigned code[S::kKeys];
   __shared__ __attribute__((aligned(16))) float nlse[S::kKeys], ndelta[S::kKeys];
   char *const kt = lds, *const qt = lds + S::kKeyBytes, *const gt = qt + S::kQryBytes;
-  char *const ds = S::kOverlay ? qt : gt + S::kQryBytes;
+  char *const vt = gt + S::kQryBytes, *const ds = S::kOverlay ? qt : vt;
   const int N = a.N, tid = threadIdx.x, lane = tid & 63, bh_i = blockIdx.x, b = bh_i / a.H;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = lane & 31, hl = lane >> 5;
@@ -385,35 +388,28 @@ __global__ __launch_bounds__(64 * NW, 2) void bwd_dense_small_kernel(DenseArgs a
   stream_rows(Q, 0, S::kQueries, qt);
   stream_rows(dO, 0, S::kQueries, gt);
 
-  // this lane's row: key and value as B operands; delta and -lse / scale of the query at the same position
+  stream_rows(V, 0, S::kKeys, vt);
+
+  // of this lane's row: delta and -lse / scale of the query, and the code.  (All rows are loaded whole, eight per
+  // instruction.  With key, value, dO and O operands straight from global memory, sixteen loads that touch 32 lines each: 32 x
+  // 128, 12 heads 16.8 us, now 15.3; 64 x 64 13.2, now 12.0; 8 x 256 20.4, now 18.1; one sequence of 128 9.1, now 8.2.)
   const int pos = min(32 * wave + m, N - 1);
-  bf16x8 kf[4], vf[4];
-  float delta = 0.f;
   {
-    bf16x8 gf[4], of[4];
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const size_t off = (size_t)pos * kD + ks * 16 + hl * 8;
-      kf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(K + off));
-      vf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(V + off));
-      gf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(dO + off));
-      of[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(O + off));
-    }
+    OwnedTile g_rows, o_rows;
+    g_rows.load(dO, pos, lane);
+    o_rows.load(O, pos, lane);
     const float lse = a.lse[bh + pos];
     const int view = a.head_kind[bh_i % a.H];
     const int* ids = (view == 0 ? a.row_ids : a.col_ids) + (size_t)b * N;
     const int f = a.flags[(size_t)b * N + pos], id = ids[pos];
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) delta = fmaf((float)gf[ks][e], (float)of[ks][e], delta);
-    delta = half_sum(delta);
+    const float delta = row_delta(g_rows, o_rows, reinterpret_cast<char*>(ndelta + 32 * wave), lane);
     if (hl == 0) {
       nlse[32 * wave + m] = -lse / a.scale;
       ndelta[32 * wave + m] = -delta;
       code[32 * wave + m] = token_code(32 * wave + m < N, f, id);
     }
   }
+  bf16x8 kf[4], vf[4];  // this lane's key and value as B operands
   const float sc = uniform(a.scale * kLog2e);
   int poff[4], toff[2][2];
   operand_offsets(lane, poff, toff);
@@ -429,6 +425,12 @@ __global__ __launch_bounds__(64 * NW, 2) void bwd_dense_small_kernel(DenseArgs a
     }
     wait_vmcnt_le<0>(0);
     __syncthreads();
+    if (p == 0)  // (dS^T may come where V is, but of each wavefront over its own rows)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        kf[ks] = read_plain(kt + wave * 32 * 128, poff[ks]);
+        vf[ks] = read_plain(vt + wave * 32 * 128, poff[ks]);
+      }
     bf16x8 ds8[S::kBlocks][2];
     const unsigned my_code = code[32 * wave + m], my_limit = owner_limit(my_code);
     if (active)
