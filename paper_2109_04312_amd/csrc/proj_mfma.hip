@@ -457,14 +457,20 @@ hipError_t launch_proj(ProjArgs a, int kernel_id, hipStream_t stream) {
 // Which shape.  A compute unit that gets n tiles of a shape needs about (k / 64) (c2 for every two tiles, c1 for
 // an odd last one) + e n us, so the shape with the smallest such sum wins, n being the rounds of the busiest XCD:
 // large tiles once they fill the chip, smaller ones where they fit its units better.  The constants were fitted
-// to the times of all six shapes for 912 products (64 to 40000 tokens, widths 128 to 4096, 2 to 32 heads, no
+// to the times of the other six shapes for 912 products (64 to 40000 tokens, widths 128 to 4096, 2 to 32 heads, no
 // padding): the shape that they choose takes 0.2 % more than the fastest one on average and 22 % at most, against
 // 2.4 % and 74 % with constants measured on widths of 768 and 1024 alone and n = ceil(tiles / 256).  For
 // instance, us, 256 x 256, 192 x 128, 128 x 128, with two groups, 128 x 64, with two groups: 2048 -> 6144 at 900
 // tokens 47, 39, 34, 40, 55, 61, at 8 x 512 98, 116, 111, 132, 216, 225; 1024 -> 3072 at 512 tokens 27, 17, 15, 12, 11, 11.
+// 192 x 128 with two groups came later, fitted to 186 products (128 to 16384 tokens, widths 128 to 2048): it is for
+// the few sizes whose tiles fill most of one round and no more, where a unit that has the same tile to itself waits
+// at every stage.  us, before and with it: 768 -> 2304 at 1999 tokens 15.4 and 14.6, 1024 -> 3072 at 1500 19.0 and
+// 17.2, 1536 -> 4608 at 1000 28.2 and 24.0, 768 -> 768 at 8192 15.6 and 14.4; in a second round it loses (768 -> 2304
+// at 2300 tokens 16.2 and 25.4), which its constant for two tiles says.
 //                        features x tokens, wavefronts, stages, workgroups per CU, groups
 using Proj256 = Shape<4, 4, 2, 4, 2, 1>;      // 256 x 256
 using Proj192 = Shape<3, 2, 2, 2, 2, 2>;      // 192 x 128  (plain weights; its wavefronts' 96 features are not whole tiles)
+using Proj192x2 = Shape<3, 2, 2, 2, 2, 1, 2>; // (all 160 KB of a compute unit's LDS)
 using Proj128 = Shape<2, 2, 2, 2, 2, 2>;      // 128 x 128
 using Proj128x2 = Shape<2, 2, 2, 2, 2, 1, 2>;
 using Proj64 = Shape<2, 1, 2, 2, 3, 2>;       // 128 x  64
@@ -489,7 +495,10 @@ hipError_t launch_proj_any(const ProjArgs& a, int kernel_id, hipStream_t stream)
   offer(proj_cost<Proj256>(a, 1.37, 3.14, 5.33), launch_proj<Proj256, kHeadTok, kTransposedW>);
   if constexpr (!kTransposedW)
     // (beyond 4608 features it takes up to 23 % more than its constants say)
-    if (a.F % Proj192::kRowsA == 0 && a.F <= 4608) offer(proj_cost<Proj192>(a, 1.17, 1.52, 0.86), launch_proj<Proj192, kHeadTok, kTransposedW>);
+    if (a.F % Proj192::kRowsA == 0 && a.F <= 4608) {
+      offer(proj_cost<Proj192>(a, 1.17, 1.52, 0.86), launch_proj<Proj192, kHeadTok, kTransposedW>);
+      offer(proj_cost<Proj192x2>(a, 0.8, 1.5, 4.6), launch_proj<Proj192x2, kHeadTok, kTransposedW>);
+    }
   offer(proj_cost<Proj128>(a, 0.62, 1.09, 1.1), launch_proj<Proj128, kHeadTok, kTransposedW>);
   offer(proj_cost<Proj128x2>(a, 0.47, 1.2, 1.86), launch_proj<Proj128x2, kHeadTok, kTransposedW>);
   offer(proj_cost<Proj64>(a, 0.46, 0.74, 0.53), launch_proj<Proj64, kHeadTok, kTransposedW>);

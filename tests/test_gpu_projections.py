@@ -282,3 +282,10 @@ def test_shared_contractions(B, N, H, E):
 def test_tiles_dealt_by_feature(B, N, H, E):
     check(N, B, N, H, E, pad_tail=N // 4)
     check_bwd(N, B, N, H, E, pad_tail=N // 4)
+
+
+# tiles of 192 x 128 that two groups of wavefronts share: 16 token tiles of two sequences with one row in the last
+# (QKV), and 49 token tiles of one sequence (output)
+@pytest.mark.parametrize("B,N,H,E", [(2, 897, 12, 768), (1, 6145, 12, 768)])
+def test_one_round_of_shared_tiles(B, N, H, E):
+    check(N, B, N, H, E, pad_tail=N // 5)
