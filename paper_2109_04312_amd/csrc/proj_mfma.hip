@@ -128,9 +128,11 @@ __device__ __forceinline__ bf16x8 read_frag(const char* tiles, const FragOffsets
 
 // One stage (64 of k): two slices of 32.
 // kHalves: `next_landed` is called where this wavefront's share of the next stage must have landed.
-template <class S, bool kTA, bool kTB, bool kHalves, class PerSlice, class Next>
+// kAlternate: `reading` is called while the fragments travel and the other group multiplies.
+template <class S, bool kTA, bool kTB, bool kHalves, class PerSlice, class Next, class Reading>
 __device__ __forceinline__ void contract_stage(const char* stage, const FragOffsets& fa, const FragOffsets& fb, int wa,
-                                               int wb, f32x4 (&acc)[S::kFA][S::kFB], PerSlice&& per_slice, Next&& next_landed) {
+                                               int wb, f32x4 (&acc)[S::kFA][S::kFB], PerSlice&& per_slice, Next&& next_landed,
+                                               Reading&& reading) {
   const char* ta = stage + (kTA ? 0 : wa * S::kFA * 16 * 128);
   const char* tb = stage + S::kA * kTileBytes + (kTB ? 0 : wb * S::kFB * 16 * 128);
   bf16x8 a[2][S::kFA], b[2][S::kFB];
@@ -165,6 +167,7 @@ __device__ __forceinline__ void contract_stage(const char* stage, const FragOffs
   read_slice(0);
   if constexpr (S::kAlternate) {
     read_slice(1);
+    reading();
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
     barrier_no_fence();  // from here on the other group reads
@@ -266,7 +269,7 @@ struct ProjArgs {
   int F, K;                      // features, contraction length
   int tok_tiles_per_seq;         // ceil(N / tile tokens)
   int feat_tiles;                // ceil(F / tile features)
-  int by_feature;                // which way tiles are dealt to the XCDs, see proj_kernel
+  int by_feature;                // which way tiles are dealt to the XCDs, see product_tile
   int tile_blocks;               // workgroups of the product; those behind them add `ranges`
   RangeSums ranges;
 };
@@ -274,8 +277,7 @@ struct ProjArgs {
 // kHeadTok: the token operand comes from head-layout tensors and the output is flat; else the reverse.
 // kTransposedW: the weight operand is read transposed.
 template <class S, bool kHeadTok, bool kTransposedW>
-__global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void proj_kernel(ProjArgs a) {
-  extern __shared__ __attribute__((aligned(1024))) char lds[];
+__device__ __forceinline__ void product_tile(ProjArgs a, char* lds, int block) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int group = wave_id / S::kWaves, wave = wave_id - group * S::kWaves;
@@ -283,16 +285,12 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
   const int r = lane & 15, quarter = lane >> 4;
   char* const ring = lds + group * S::kRingBytes;
 
-  if ((int)blockIdx.x >= a.tile_blocks) {  // behind the tiles: partial sums of a weight gradient
-    add_ranges(a.ranges, blockIdx.x - a.tile_blocks, S::kThreads);
-    return;
-  }
   // Workgroup -> (token tile, feature tile).  XCD q walks the feature tiles fastest, so the token rows it
   // streams stay in its L2 while the weights cycle, and takes one of every eight consecutive token
   // tiles, another one each time, so that the padding at the end of the sequences is spread over all XCDs.
   // With few token tiles that leaves XCDs idle or uneven (one of 64 tokens and 6144 x 2048 weights: 48 tiles on
   // the 32 CUs of one XCD, 29 us); then the feature tiles are dealt instead, and every weight is read by one XCD.
-  const int q = blockIdx.x & 7, jx = blockIdx.x >> 3;
+  const int q = block & 7, jx = block >> 3;
   const int per = a.by_feature ? a.B * a.tok_tiles_per_seq : a.feat_tiles, jk = jx / per, rest = jx - jk * per;
   const int tt = a.by_feature ? rest : 8 * jk + ((q + 3 * jk) & 7), f0 = (a.by_feature ? 8 * jk + q : rest) * S::kRowsA;
   if (f0 >= a.F) return;
@@ -384,7 +382,7 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
       barrier_no_fence();  // ... for every wavefront, and everyone is done with stage ks - 1
       if (ks + S::kStages - 1 < nk) issue_stage(ks + S::kStages - 1);
       contract_stage<S, kTransposedW, false, kHalves>(ring + (ks % S::kStages) * S::kStageBytes, fa, fb, wa, wb, acc,
-                                                      [](const bf16x8 (&)[S::kFB]) {}, []() { wait_vmcnt_le<0>(0); });
+                                                      [](const bf16x8 (&)[S::kFB]) {}, []() { wait_vmcnt_le<0>(0); }, []() {});
     }
     if (apart && !second) barrier_no_fence();
   }
@@ -428,6 +426,13 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
   }
 }
 
+template <class S, bool kHeadTok, bool kTransposedW>
+__global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void proj_kernel(ProjArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  if ((int)blockIdx.x < a.tile_blocks) product_tile<S, kHeadTok, kTransposedW>(a, lds, blockIdx.x);
+  else add_ranges(a.ranges, blockIdx.x - a.tile_blocks, S::kThreads);  // behind the tiles: partial sums of a weight gradient
+}
+
 // Tiles of the busiest XCD, dealt by token or by feature tile, and how many its 32 CUs take one after the other.
 // (By feature where that is fewer: 1024 -> 3072 at 600 tokens, 10 tiles of 64: 17.6 -> 9.3 us; 2048 -> 6144 at 64:
 // 29.4 -> 13.4.  In equal rounds by token: the weights are then read once per token tile from an L2 that keeps them.)
@@ -438,13 +443,18 @@ long tiles_per_xcd(const ProjArgs& a, bool by_feature) {
 }
 long rounds(long tiles) { return (tiles + 31) / 32; }
 
-template <class S, bool kHeadTok, bool kTransposedW>
-hipError_t launch_proj(ProjArgs a, int kernel_id, hipStream_t stream) {
+template <class S>
+void deal_tiles(ProjArgs& a) {
   a.tok_tiles_per_seq = (a.N + S::kRowsB - 1) / S::kRowsB;
   a.feat_tiles = (a.F + S::kRowsA - 1) / S::kRowsA;
   const long by_token = tiles_per_xcd<S>(a, false), by_feature = tiles_per_xcd<S>(a, true);
   a.by_feature = rounds(by_feature) < rounds(by_token);
   a.tile_blocks = 8 * (int)(a.by_feature ? by_feature : by_token);
+}
+
+template <class S, bool kHeadTok, bool kTransposedW>
+hipError_t launch_proj(ProjArgs a, int kernel_id, hipStream_t stream) {
+  deal_tiles<S>(a);
   if (a.ranges.splits) a.ranges.blocks = (int)std::max<size_t>(1, std::min<size_t>(1024 * 256 / S::kThreads, a.ranges.n / 4 / S::kThreads));
   const hipError_t e = allow_lds<&proj_kernel<S, kHeadTok, kTransposedW>>(S::kLds);
   if (e != hipSuccess) return e;
@@ -481,16 +491,16 @@ double proj_cost(const ProjArgs& a, double c1, double c2, double e) {
   return (a.K / 64) * ((n / 2) * c2 + (n % 2) * c1) + e * n;
 }
 
+typedef hipError_t (*ProjLaunch)(ProjArgs, int, hipStream_t);
+struct ProjChoice {
+  double cost;
+  ProjLaunch launch;
+};
 template <bool kHeadTok, bool kTransposedW>
-hipError_t launch_proj_any(const ProjArgs& a, int kernel_id, hipStream_t stream) {
-  typedef hipError_t (*Launch)(ProjArgs, int, hipStream_t);
-  double best = 1e30;
-  Launch launch = nullptr;
-  auto offer = [&](double cost, Launch l) {
-    if (cost < best) {
-      best = cost;
-      launch = l;
-    }
+ProjChoice choose_proj(const ProjArgs& a) {
+  ProjChoice best = {1e30, nullptr};
+  auto offer = [&](double cost, ProjLaunch launch) {
+    if (cost < best.cost) best = {cost, launch};
   };
   offer(proj_cost<Proj256>(a, 1.37, 3.14, 5.33), launch_proj<Proj256, kHeadTok, kTransposedW>);
   if constexpr (!kTransposedW)
@@ -503,7 +513,7 @@ hipError_t launch_proj_any(const ProjArgs& a, int kernel_id, hipStream_t stream)
   offer(proj_cost<Proj128x2>(a, 0.47, 1.2, 1.86), launch_proj<Proj128x2, kHeadTok, kTransposedW>);
   offer(proj_cost<Proj64>(a, 0.46, 0.74, 0.53), launch_proj<Proj64, kHeadTok, kTransposedW>);
   offer(proj_cost<Proj64x2>(a, 0.39, 0.8, 0.71), launch_proj<Proj64x2, kHeadTok, kTransposedW>);
-  return launch(a, kernel_id, stream);
+  return best;
 }
 
 // ======================================================================================
@@ -560,42 +570,43 @@ __device__ __forceinline__ unsigned long long pad_mask(const unsigned char* flag
   return n < 64 ? bits | ~0ull << n : bits;
 }
 
-template <class S>
-__global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void proj_wgrad_kernel(WgradArgs a) {
-  extern __shared__ __attribute__((aligned(1024))) char lds[];
+// kList: token blocks of one range at most.  kChain > 0: a group's accumulators go into a second set after every
+// kChain blocks, so that a long range is no less exact than the sum of short ones.
+template <class S, int kList, int kChain>
+__device__ __forceinline__ void wgrad_tile(WgradArgs a, char* lds, int block) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int group = wave_id / S::kWaves, wave = wave_id - group * S::kWaves;
   char* const ring = lds + group * S::kRingBytes;
   const int e_tiles = (a.E + S::kRowsA - 1) / S::kRowsA, tiles = ((a.F + S::kRowsB - 1) / S::kRowsB) * e_tiles;
-  // Workgroup -> (token range, tile): XCD q = blockIdx % 8 takes a contiguous piece of the list
+  // Workgroup -> (token range, tile): XCD q = block % 8 takes a contiguous piece of the list
   // ordered by token range first, so the workgroups that stream the same tokens share an L2
   // (dealt round-robin, every XCD would fetch all of G from memory: 8 x the traffic).
   const int total = tiles * a.splits, per_xcd = (total + 7) >> 3;
-  const int q = blockIdx.x & 7, jx = blockIdx.x >> 3, idx = q * per_xcd + jx;
+  const int q = block & 7, jx = block >> 3, idx = q * per_xcd + jx;
   if (jx >= per_xcd || idx >= total) return;
   const int split = idx / tiles, tile = idx - split * tiles;
   const int ft = tile / e_tiles, et = tile - ft * e_tiles;
   const int f0 = ft * S::kRowsB, e0 = et * S::kRowsA;
   const int wa = wave / S::kWB, wb = wave - wa * S::kWB;
   const int total_blocks = a.B * a.blocks_per_seq;
-  // Up to kMaxRange token blocks: every workgroup lists all of them and takes its share of the live ones
+  // Up to kList token blocks: every workgroup lists all of them and takes its share of the live ones
   // (with ranges of equal length the padding at the end of the sequences left some ranges half empty:
   // 52 live blocks in the longest of five where 41 would do).  More: ranges of equal length.
-  const bool share = total_blocks <= kMaxRange;
+  const bool share = total_blocks <= kList;
   const int s_begin = share ? 0 : split * a.per_split, s_end = share ? total_blocks : min(total_blocks, s_begin + a.per_split);
 
   // ---- the blocks with a non-pad row, in order, and their pad masks, listed in LDS before the
   // loop (looked up one by one inside it, every step waited for dependent loads: 3 us a step where the
   // contractions need 0.9) ----
-  __shared__ unsigned long long live_mask[kMaxRange];
-  __shared__ uint2 live_at[kMaxRange];  // where the block begins in X and G, in units of 128 bytes
+  __shared__ unsigned long long live_mask[kList];
+  __shared__ uint2 live_at[kList];  // where the block begins in X and G, in units of 128 bytes
   __shared__ int wave_live[S::kAllWaves], first_tail;
   int n_live = 0;
   const unsigned x_stride = a.x.heads ? kD * 2 : (unsigned)a.x.ld * 2, g_stride = a.g.heads ? kD * 2 : (unsigned)a.g.ld * 2;
   const unsigned x_seq = (unsigned)((a.x.heads ? (size_t)a.H * a.N * kD * 2 : (size_t)a.N * x_stride) / 128);
   const unsigned g_seq = (unsigned)((a.g.heads ? (size_t)a.H * a.N * kD * 2 : (size_t)a.N * g_stride) / 128);
-  if (tid == 0) first_tail = kMaxRange;  // (the loop's first barrier comes before anyone else's turn)
+  if (tid == 0) first_tail = kList;  // (the loop's first barrier comes before anyone else's turn)
   for (int s0 = s_begin; s0 < s_end; s0 += S::kThreads) {  // one block per thread, its 64 flags at once
     const int s = s0 + tid, b = s / a.blocks_per_seq;
     const unsigned long long mask = s < s_end ? pad_mask(a.flags, (size_t)a.B * a.N, (size_t)b * a.N, (s - b * a.blocks_per_seq) * 64, a.N) : ~0ull;
@@ -668,6 +679,12 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
   for (int i = 0; i < S::kFA; ++i)
 #pragma unroll
     for (int j = 0; j < S::kFB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 chains[S::kFA][S::kFB];
+  if constexpr (kChain > 0)
+#pragma unroll
+    for (int i = 0; i < S::kFA; ++i)
+#pragma unroll
+      for (int j = 0; j < S::kFB; ++j) chains[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   float bias_acc[S::kFB];
 #pragma unroll
   for (int j = 0; j < S::kFB; ++j) bias_acc[j] = 0.f;
@@ -712,9 +729,25 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
                                       for (int j = 0; j < S::kFB; ++j) bias_acc[j] = sum8(g[j], bias_acc[j]);
                                     }
                                   },
-                                  []() {});
+                                  []() {},
+                                  [&]() {
+                                    if constexpr (kChain > 0)
+                                      if (it % kChain == 0 && it)
+#pragma unroll
+                                        for (int y = 0; y < S::kFA; ++y)
+#pragma unroll
+                                          for (int j = 0; j < S::kFB; ++j) {
+                                            chains[y][j] += acc[y][j];
+                                            acc[y][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                                          }
+                                  });
   }
   if (S::kAlternate && group == 0) barrier_no_fence();
+  if constexpr (kChain > 0)
+#pragma unroll
+    for (int i = 0; i < S::kFA; ++i)
+#pragma unroll
+      for (int j = 0; j < S::kFB; ++j) acc[i][j] += chains[i][j];
   f32x4 sum[S::kFA][S::kOutB];
   add_groups<S>(acc, sum, lds, group, wave, lane);
 
@@ -754,6 +787,12 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void pro
   }
 }
 
+template <class S>
+__global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void proj_wgrad_kernel(WgradArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  wgrad_tile<S, kMaxRange, 0>(a, lds, blockIdx.x);
+}
+
 // For a weight gradient that no product follows.
 __global__ __launch_bounds__(256) void add_ranges_kernel(RangeSums s) { add_ranges(s, blockIdx.x, 256); }
 
@@ -764,6 +803,7 @@ using Wgrad128 = Shape<2, 2, 2, 2, 2, 1, 2>;   // 128 x 128, two groups
 size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
 struct WgradPlan {
   int blocks_per_seq, splits, per_split, tile;
+  double cost;
   size_t bias_off, total;
 };
 // F x E = shape of the weight gradient.
@@ -777,7 +817,6 @@ WgradPlan plan_wgrad(int B, int N, int F, int E) {
   // 128 x 128 with two groups, 1 per 5.2 MB of partial sums.  (3072 x 1024 at 4096 tokens: 50 against 47,
   // at 8192 70 against 85, at 1024 37 against 19.)
   constexpr int kSlots = 256;
-  double best = 0;
   for (int tile : {256, 128}) {
     const int tiles = ((F + tile - 1) / tile) * ((E + tile - 1) / tile);
     // enough workgroups for the chip, but ranges of at least eight token blocks
@@ -785,8 +824,8 @@ WgradPlan plan_wgrad(int B, int N, int F, int E) {
     const int per = (total_blocks + want - 1) / want, splits = (total_blocks + per - 1) / per;
     const double rounds = (double)((tiles * splits + kSlots - 1) / kSlots);
     const double cost = rounds * per * (tile == 256 ? 1.9 : 0.7) + (splits > 1 ? splits * 8.0 * F * E / 5.2e6 : 0.0);
-    if (tile == 256 || cost < best) {
-      best = cost;
+    if (tile == 256 || cost < p.cost) {
+      p.cost = cost;
       p.tile = tile;
       p.per_split = per;
       p.splits = splits;
@@ -808,8 +847,7 @@ hipError_t launch_wgrad(const WgradArgs& a, int kernel_id, hipStream_t stream) {
 }
 
 // Leaves in `sums` what is still to be added up.
-hipError_t run_wgrad(WgradArgs a, char* ws, int kernel_id, RangeSums& sums, hipStream_t stream) {
-  const WgradPlan p = plan_wgrad(a.B, a.N, a.F, a.E);
+hipError_t run_wgrad(WgradArgs a, const WgradPlan& p, char* ws, int kernel_id, RangeSums& sums, hipStream_t stream) {
   a.blocks_per_seq = p.blocks_per_seq;
   a.splits = p.splits;
   a.per_split = p.per_split;
@@ -824,6 +862,87 @@ hipError_t add_ranges_alone(RangeSums s, hipStream_t stream) {
   s.blocks = (int)std::max<size_t>(1, std::min<size_t>(1024, s.n / 4 / 256));
   hipLaunchKernelGGL(add_ranges_kernel, dim3(s.blocks), dim3(256), 0, stream, s);
   return hipGetLastError();
+}
+
+// ---- both gradients of a projection in one launch ------------------------------------------------------------
+// A small layer's gradients are two launches of workgroups that leave compute units idle (dW 2304 x 768 has 108
+// tiles; token ranges that fill the chip leave partial sums to be written, read and added).  Here the tiles of dW, each
+// over all token blocks, go first and those of the other gradient take the units that are left: no ranges, no
+// partial sums, one launch.
+constexpr int kWholeBlocks = 128;  // token blocks, at most
+// The shortest ranges of two launches give each group four blocks; with chains of that length the error of dW (rms
+// against 64 bits, of its own rms) is 0.7e-7 to 1.1e-7 where it was up to 2.1e-7, and would be up to 3.4e-7 without.
+// Adding them up after the multiplication cost 8 % of a long range, while the next fragments travel half of that.
+constexpr int kWholeChain = 4;
+template <class S, bool kHeadTok>
+__global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4) void proj_bwd_kernel(WgradArgs w, ProjArgs a, int w_blocks) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  static_assert(S::kThreads == Wgrad128::kThreads, "one workgroup size for both");
+  if ((int)blockIdx.x < w_blocks) wgrad_tile<Wgrad128, kWholeBlocks, kWholeChain>(w, lds, blockIdx.x);
+  else product_tile<S, kHeadTok, true>(a, lds, blockIdx.x - w_blocks);
+}
+
+int wgrad_tiles128(const WgradArgs& w) { return (w.F + 127) / 128 * ((w.E + 127) / 128); }
+
+// When the last of `first` workgroups of t1 us and then `second` ones of t2 us ends, one at a time on each unit.
+double end_of_both(int first, double t1, long second, double t2) {
+  constexpr int kUnits = 256;
+  const int late = first % kUnits, early = kUnits - late;   // units that end the first kind a round later, or not
+  double early_at = first / kUnits * t1, late_at = early_at + t1, end = late ? late_at : early_at;
+  while (second > 0) {
+    const bool use_early = !late || early_at <= late_at;
+    double& at = use_early ? early_at : late_at;
+    at += t2;
+    second -= use_early ? early : late;
+    end = std::max(end, at);
+  }
+  return end;
+}
+
+template <class S, bool kHeadTok>
+hipError_t launch_bwd(WgradArgs w, ProjArgs a, int wgrad_id, int proj_id, hipStream_t stream) {
+  deal_tiles<S>(a);
+  w.blocks_per_seq = (w.N + 63) / 64;
+  w.splits = 1;
+  w.per_split = w.B * w.blocks_per_seq;
+  const int w_blocks = (wgrad_tiles128(w) + 7) / 8 * 8;  // (whole rounds of XCDs, so the products' tiles are dealt as ever)
+  constexpr int kLds = std::max(S::kLds, Wgrad128::kLds);
+  const hipError_t e = allow_lds<&proj_bwd_kernel<S, kHeadTok>>(kLds);
+  if (e != hipSuccess) return e;
+  ProfileScope prof(wgrad_id, stream, proj_id);
+  hipLaunchKernelGGL((proj_bwd_kernel<S, kHeadTok>), dim3(w_blocks + a.tile_blocks), dim3(S::kThreads), kLds, stream, w, a, w_blocks);
+  return hipGetLastError();
+}
+
+// us that the launch takes, for the rule below.
+template <class S>
+double bwd_cost(const WgradArgs& w, ProjArgs a, double per_step, double rest) {
+  deal_tiles<S>(a);
+  const int tiles = (wgrad_tiles128(w) + 7) / 8 * 8, blocks = w.B * ((w.N + 63) / 64);
+  return 2.7 + end_of_both(tiles, (0.43 + 0.25 * tiles / 256) * blocks + 5.7, a.tile_blocks, per_step * (a.K / 64) + rest);
+}
+
+// dW (unless w.out is null) and the other gradient (unless a.out[0] is).  One launch if that is at least 6 % faster
+// by these costs, fitted to 150 pairs of gradients (64 to 16384 tokens, 256 to 2048 wide) in all three forms; over them
+// it gains 12 % on average.  us, as two launches and as one, gradients of QKV and of the output projection, 768 wide:
+// 512 tokens 27.3 -> 17.2 and 18.3 -> 11.6, 2048 tokens 33.7 -> 24.6 and 23.2 -> 22.4, 8 x 512 43.0 -> 39.5 and 26.5
+// as two (33.8 as one); 1024 wide, 1024 tokens 37.2 -> 25.1 and 23.7 -> 15.5, 4 x 1024 63 either way.
+template <bool kHeadTok>
+hipError_t run_bwd(const WgradArgs& w, ProjArgs a, char* ws, int wgrad_id, int proj_id, hipStream_t stream) {
+  const bool want_w = w.out, want_a = a.out[0];
+  const ProjChoice product = choose_proj<kHeadTok, true>(a);
+  if (want_w) {
+    const WgradPlan plan = plan_wgrad(w.B, w.N, w.F, w.E);
+    if (want_a && wgrad_tiles128(w) <= 256 && w.B * plan.blocks_per_seq <= kWholeBlocks) {
+      const double x128 = bwd_cost<Proj128x2>(w, a, 0.43, 2.2), x64 = bwd_cost<Proj64x2>(w, a, 0.37, 2.0);
+      if (1.06 * std::min(x128, x64) < 12.3 + 0.64 * plan.cost + product.cost)
+        return x128 <= x64 ? launch_bwd<Proj128x2, kHeadTok>(w, a, wgrad_id, proj_id, stream)
+                           : launch_bwd<Proj64x2, kHeadTok>(w, a, wgrad_id, proj_id, stream);
+    }
+    const hipError_t e = run_wgrad(w, plan, ws, wgrad_id, a.ranges, stream);
+    if (e != hipSuccess) return e;
+  }
+  return want_a ? product.launch(a, proj_id, stream) : add_ranges_alone(a.ranges, stream);
 }
 
 }  // namespace
@@ -842,7 +961,7 @@ hipError_t launch_qkv_project(const void* x, const void* w_qkv, const float* bia
   a.B = B; a.N = N; a.H = H;
   a.F = 3 * H * kD;
   a.K = E;
-  return launch_proj_any<false, false>(a, 8, stream);
+  return choose_proj<false, false>(a).launch(a, 8, stream);
 }
 
 hipError_t launch_out_project(const void* o, const void* w_o, const float* bias,
@@ -857,7 +976,7 @@ hipError_t launch_out_project(const void* o, const void* w_o, const float* bias,
   a.B = B; a.N = N; a.H = H;
   a.F = E;
   a.K = H * kD;
-  return launch_proj_any<true, false>(a, 9, stream);
+  return choose_proj<true, false>(a).launch(a, 9, stream);
 }
 
 size_t qkv_project_bwd_workspace(int B, int N, int H, int E) { return plan_wgrad(B, N, 3 * H * kD, E).total; }
@@ -868,25 +987,19 @@ hipError_t launch_qkv_project_bwd(const void* x, const void* w_qkv, const unsign
                                   int E, void* dx, float* dw, float* dbias, void* workspace,
                                   hipStream_t stream) {
   const int F = 3 * H * kD;
-  RangeSums sums = {};
-  if (dw) {
-    WgradArgs g = {};
-    g.g.p[0] = static_cast<const unsigned short*>(dq);
-    g.g.p[1] = static_cast<const unsigned short*>(dk);
-    g.g.p[2] = static_cast<const unsigned short*>(dv);
-    g.g.heads = 1;
-    g.x.p[0] = static_cast<const unsigned short*>(x);
-    g.x.heads = 0;
-    g.x.ld = E;
-    g.flags = flags;
-    g.out = dw;
-    g.out_bias = dbias;
-    g.want_bias = dbias != nullptr;
-    g.B = B; g.N = N; g.H = H; g.F = F; g.E = E;
-    const hipError_t e = run_wgrad(g, static_cast<char*>(workspace), 11, sums, stream);
-    if (e != hipSuccess) return e;
-  }
-  if (!dx) return add_ranges_alone(sums, stream);
+  WgradArgs g = {};
+  g.g.p[0] = static_cast<const unsigned short*>(dq);
+  g.g.p[1] = static_cast<const unsigned short*>(dk);
+  g.g.p[2] = static_cast<const unsigned short*>(dv);
+  g.g.heads = 1;
+  g.x.p[0] = static_cast<const unsigned short*>(x);
+  g.x.heads = 0;
+  g.x.ld = E;
+  g.flags = flags;
+  g.out = dw;
+  g.out_bias = dbias;
+  g.want_bias = dbias != nullptr;
+  g.B = B; g.N = N; g.H = H; g.F = F; g.E = E;
   // dx[tok, :] = sum over the 3 H heads of dq, dk, dv [tok, head] . w_qkv[head rows, :]
   ProjArgs a = {};
   a.w = static_cast<const unsigned short*>(w_qkv);  // [F][E], contracted over its rows
@@ -898,31 +1011,24 @@ hipError_t launch_qkv_project_bwd(const void* x, const void* w_qkv, const unsign
   a.B = B; a.N = N; a.H = H;
   a.F = E;
   a.K = F;
-  a.ranges = sums;
-  return launch_proj_any<true, true>(a, 10, stream);
+  return run_bwd<true>(g, a, static_cast<char*>(workspace), 11, 10, stream);
 }
 
 hipError_t launch_out_project_bwd(const void* o, const void* w_o, const unsigned char* flags,
                                   const void* dy, int B, int N, int H, int E, void* d_o, float* dw,
                                   float* dbias, void* workspace, hipStream_t stream) {
   const int J = H * kD;
-  RangeSums sums = {};
-  if (dw) {
-    WgradArgs g = {};
-    g.g.p[0] = static_cast<const unsigned short*>(dy);
-    g.g.heads = 0;
-    g.g.ld = E;
-    g.x.p[0] = static_cast<const unsigned short*>(o);
-    g.x.heads = 1;
-    g.flags = flags;
-    g.out = dw;
-    g.out_bias = dbias;
-    g.want_bias = dbias != nullptr;
-    g.B = B; g.N = N; g.H = H; g.F = E; g.E = J;
-    const hipError_t e = run_wgrad(g, static_cast<char*>(workspace), 13, sums, stream);
-    if (e != hipSuccess) return e;
-  }
-  if (!d_o) return add_ranges_alone(sums, stream);
+  WgradArgs g = {};
+  g.g.p[0] = static_cast<const unsigned short*>(dy);
+  g.g.heads = 0;
+  g.g.ld = E;
+  g.x.p[0] = static_cast<const unsigned short*>(o);
+  g.x.heads = 1;
+  g.flags = flags;
+  g.out = dw;
+  g.out_bias = dbias;
+  g.want_bias = dbias != nullptr;
+  g.B = B; g.N = N; g.H = H; g.F = E; g.E = J;
   // d_o[tok, head i] = dy[tok, :] . w_o[:, head i columns], written head by head
   ProjArgs a = {};
   a.w = static_cast<const unsigned short*>(w_o);  // [E][H*64], contracted over its rows
@@ -932,8 +1038,7 @@ hipError_t launch_out_project_bwd(const void* o, const void* w_o, const unsigned
   a.B = B; a.N = N; a.H = H;
   a.F = J;
   a.K = E;
-  a.ranges = sums;
-  return launch_proj_any<false, true>(a, 12, stream);
+  return run_bwd<false>(g, a, static_cast<char*>(workspace), 13, 12, stream);
 }
 
 }  // namespace mate

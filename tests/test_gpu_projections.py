@@ -289,3 +289,10 @@ def test_tiles_dealt_by_feature(B, N, H, E):
 @pytest.mark.parametrize("B,N,H,E", [(2, 897, 12, 768), (1, 6145, 12, 768)])
 def test_one_round_of_shared_tiles(B, N, H, E):
     check(N, B, N, H, E, pad_tail=N // 5)
+
+
+# both gradients in one launch: one token, several sequences with a shorter last block, all of one sequence's tail
+# padding, the two tile shapes of the product, more dW tiles than products' tiles and fewer
+@pytest.mark.parametrize("B,N,H,E", [(1, 1, 2, 128), (3, 65, 12, 768), (1, 1024, 16, 1024), (2, 130, 4, 1152), (9, 100, 24, 128)])
+def test_both_gradients_in_one_launch(B, N, H, E):
+    check_bwd(N, B, N, H, E, pad_tail=N // 2)
