@@ -282,7 +282,7 @@ mate_status mate_qkv_project_bwd(const void* x, const void* w_qkv, const uint8_t
   if (dbias && !dw_qkv) return MATE_ERR_NULL;  // the bias gradient rides on the weight gradient
   if (!workspace || workspace_bytes < qkv_project_bwd_workspace(B, N, H, E)) return MATE_ERR_WORKSPACE;
   hipError_t e = launch_qkv_project_bwd(x, w_qkv, flags, dq, dk, dv, B, N, H, E, dx, dw_qkv, dbias,
-                                        workspace, static_cast<hipStream_t>(stream));
+                                        workspace, next_ticket(), static_cast<hipStream_t>(stream));
   return e == hipSuccess ? MATE_OK : MATE_ERR_HIP;
 }
 
@@ -296,7 +296,7 @@ mate_status mate_out_project_bwd(const void* o, const void* w_o, const uint8_t* 
   if (dbias && !dw_o) return MATE_ERR_NULL;
   if (!workspace || workspace_bytes < out_project_bwd_workspace(B, N, H, E)) return MATE_ERR_WORKSPACE;
   hipError_t e = launch_out_project_bwd(o, w_o, flags, dy, B, N, H, E, d_o, dw_o, dbias, workspace,
-                                        static_cast<hipStream_t>(stream));
+                                        next_ticket(), static_cast<hipStream_t>(stream));
   return e == hipSuccess ? MATE_OK : MATE_ERR_HIP;
 }
 

@@ -27,28 +27,6 @@ namespace {
 
 constexpr int kStageBytes = 2 * kTileBytes;   // K tile, V tile
 
-// Who merges.  The workspace is uninitialised, so there is no counter to add to: every chunk has a
-// word of its own and sets it to the call's ticket, a 64-bit number no earlier call has used; a
-// workgroup that then finds every word of its group set is the one (or one of several, which write
-// the same values: each sets its word before it reads the others', so at least one sees all).
-// The words are cleared again afterwards, so that a captured launch, which is replayed with its
-// old ticket, finds none of its own.
-__device__ __forceinline__ bool completes_group(unsigned long long* words, int mine, int n_chunks,
-                                                unsigned long long ticket, int* flag) {
-  publish_partials();
-  if (threadIdx.x < 64) {
-    if (threadIdx.x == 0) __hip_atomic_store(words + mine, ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    bool all = true;
-    for (int j = threadIdx.x; j < n_chunks; j += 64)
-      all &= __hip_atomic_load(words + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == ticket;
-    const bool every = __all(all);
-    if (threadIdx.x == 0) *flag = every;
-  }
-  __syncthreads();
-  return *flag != 0;
-}
-
 // O = sum_c 2^(m_c - m) O_c / sum_c 2^(m_c - m) l_c over the chunks of one owner tile of question
 // tokens; slot0 = the tile's first partial slot.  Items are dealt to the four wavefronts.
 __device__ __forceinline__ void merge_chunks(const AttnArgs& a, const UnitPlan& u, size_t slot0, unsigned short* O,

@@ -26,6 +26,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "arrival.h"
 #include "d2l.h"
 #include "launch.h"
 #include "mfma_common.h"
@@ -495,24 +496,25 @@ typedef hipError_t (*ProjLaunch)(ProjArgs, int, hipStream_t);
 struct ProjChoice {
   double cost;
   ProjLaunch launch;
+  int groups;   // shapes with as many groups add up a product's stages in the same order: the same bits
 };
 template <bool kHeadTok, bool kTransposedW>
 ProjChoice choose_proj(const ProjArgs& a) {
-  ProjChoice best = {1e30, nullptr};
-  auto offer = [&](double cost, ProjLaunch launch) {
-    if (cost < best.cost) best = {cost, launch};
+  ProjChoice best = {1e30, nullptr, 0};
+  auto offer = [&](double cost, ProjLaunch launch, int groups) {
+    if (cost < best.cost) best = {cost, launch, groups};
   };
-  offer(proj_cost<Proj256>(a, 1.37, 3.14, 5.33), launch_proj<Proj256, kHeadTok, kTransposedW>);
+  offer(proj_cost<Proj256>(a, 1.37, 3.14, 5.33), launch_proj<Proj256, kHeadTok, kTransposedW>, 1);
   if constexpr (!kTransposedW)
     // (beyond 4608 features it takes up to 23 % more than its constants say)
     if (a.F % Proj192::kRowsA == 0 && a.F <= 4608) {
-      offer(proj_cost<Proj192>(a, 1.17, 1.52, 0.86), launch_proj<Proj192, kHeadTok, kTransposedW>);
-      offer(proj_cost<Proj192x2>(a, 0.8, 1.5, 4.6), launch_proj<Proj192x2, kHeadTok, kTransposedW>);
+      offer(proj_cost<Proj192>(a, 1.17, 1.52, 0.86), launch_proj<Proj192, kHeadTok, kTransposedW>, 1);
+      offer(proj_cost<Proj192x2>(a, 0.8, 1.5, 4.6), launch_proj<Proj192x2, kHeadTok, kTransposedW>, 2);
     }
-  offer(proj_cost<Proj128>(a, 0.62, 1.09, 1.1), launch_proj<Proj128, kHeadTok, kTransposedW>);
-  offer(proj_cost<Proj128x2>(a, 0.47, 1.2, 1.86), launch_proj<Proj128x2, kHeadTok, kTransposedW>);
-  offer(proj_cost<Proj64>(a, 0.46, 0.74, 0.53), launch_proj<Proj64, kHeadTok, kTransposedW>);
-  offer(proj_cost<Proj64x2>(a, 0.39, 0.8, 0.71), launch_proj<Proj64x2, kHeadTok, kTransposedW>);
+  offer(proj_cost<Proj128>(a, 0.62, 1.09, 1.1), launch_proj<Proj128, kHeadTok, kTransposedW>, 1);
+  offer(proj_cost<Proj128x2>(a, 0.47, 1.2, 1.86), launch_proj<Proj128x2, kHeadTok, kTransposedW>, 2);
+  offer(proj_cost<Proj64>(a, 0.46, 0.74, 0.53), launch_proj<Proj64, kHeadTok, kTransposedW>, 1);
+  offer(proj_cost<Proj64x2>(a, 0.39, 0.8, 0.71), launch_proj<Proj64x2, kHeadTok, kTransposedW>, 2);
   return best;
 }
 
@@ -539,6 +541,8 @@ struct WgradArgs {
   float* out_bias;                // [F] or null
   float* part;                    // [splits][F][E] partial sums (splits > 1)
   float* part_bias;               // [splits][F]
+  unsigned long long* arrived;    // [tiles][kMaxRanges], where the ranges are added in the launch
+  unsigned long long ticket;
   int B, N, H;
   int F, E;                       // rows and columns of dW
   int blocks_per_seq;             // ceil(N / 64)
@@ -546,6 +550,7 @@ struct WgradArgs {
   int want_bias;
 };
 constexpr int kMaxRange = 1024;   // token blocks of one range
+constexpr int kMaxRanges = 8;     // of a launch that adds them itself
 
 // Which of the 64 tokens from position n0 of the sequence at flags[seq] on are padding (or past its end):
 // one bit each.  `total` = bytes of the flags array, which is read 64 bytes at a time.
@@ -572,7 +577,8 @@ __device__ __forceinline__ unsigned long long pad_mask(const unsigned char* flag
 
 // kList: token blocks of one range at most.  kChain > 0: a group's accumulators go into a second set after every
 // kChain blocks, so that a long range is no less exact than the sum of short ones.
-template <class S, int kList, int kChain>
+// kMerge: the range of a tile that is done last adds them all (otherwise another launch does).
+template <class S, int kList, int kChain, bool kMerge>
 __device__ __forceinline__ void wgrad_tile(WgradArgs a, char* lds, int block) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -751,9 +757,80 @@ __device__ __forceinline__ void wgrad_tile(WgradArgs a, char* lds, int block) {
   f32x4 sum[S::kFA][S::kOutB];
   add_groups<S>(acc, sum, lds, group, wave, lane);
 
-  // a lane holds columns 16 i + 4 quarter .. + 3 of row 16 j + r
   const int r = lane & 15, quarter = lane >> 4;
-  float* dst = (a.splits > 1 ? a.part + (size_t)split * a.F * a.E : a.out);
+  float bias_sum[S::kFB];   // of row 16 j + r, in group 0's wavefronts of the first columns
+  if (a.want_bias && et == 0) {
+    if (S::kGroups > 1) {  // the other group's column sums
+      float* x = reinterpret_cast<float*>(lds);
+      __syncthreads();
+      if (do_bias && group)
+#pragma unroll
+        for (int j = 0; j < S::kFB; ++j) x[(wb * S::kFB + j) * 64 + lane] = bias_acc[j];
+      __syncthreads();
+      if (do_bias && !group)
+#pragma unroll
+        for (int j = 0; j < S::kFB; ++j) bias_acc[j] += x[(wb * S::kFB + j) * 64 + lane];
+    }
+#pragma unroll
+    for (int j = 0; j < S::kFB; ++j) {
+      bias_sum[j] = bias_acc[j] + __shfl_xor(bias_acc[j], 16, 64);
+      bias_sum[j] += __shfl_xor(bias_sum[j], 32, 64);
+    }
+  }
+  const bool has_bias = do_bias && !group;
+  if constexpr (kMerge) {
+    if (a.splits > 1) {
+      // Ranges are added in pairs, pairs of pairs and so on: of two, the one that comes first leaves its registers
+      // as they are ([wavefront][block][half][lane] pairs, in the place of its lowest range) and ends, the other adds
+      // them to its own.  (One workgroup that adds all of them waits for 64 KB of far memory per range.)
+      constexpr int kTile = S::kRowsA * S::kRowsB, kBlocks = S::kFA * S::kOutB;
+      static_assert(kTile == S::kAllWaves * kBlocks * 256, "the registers are the tile");
+      __shared__ int second;
+      for (int level = 0; (1 << level) < a.splits; ++level) {
+        const int node = split >> level, other = (node ^ 1) << level;
+        if (other >= a.splits) continue;
+        unsigned long long* const word = a.arrived + (size_t)tile * kMaxRanges + (kMaxRanges - (kMaxRanges >> level)) + (node >> 1);
+        auto place = [&](int range) { return a.part + ((size_t)range * tiles + tile) * kTile + wave_id * kBlocks * 256 + lane * 2; };
+        auto bias_place = [&](int range) { return a.part_bias + (size_t)range * a.F + f0 + wb * S::kFB * 16 + r; };
+        if (tid == 0) second = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.ticket;
+        __syncthreads();
+        if (!second) {
+          float* const mine = place(node << level);
+#pragma unroll
+          for (int y = 0; y < kBlocks; ++y)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+              put_pair<true>(mine + y * 256 + h * 128, sum[y / S::kOutB][y % S::kOutB][2 * h], sum[y / S::kOutB][y % S::kOutB][2 * h + 1]);
+          if (has_bias && quarter == 0)
+#pragma unroll
+            for (int j = 0; j < S::kFB; ++j)
+              __hip_atomic_store(bias_place(node << level) + j * 16, bias_sum[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          publish_partials();
+          if (tid == 0) second = __hip_atomic_exchange(word, a.ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.ticket;
+          __syncthreads();
+          if (!second) return;
+        }
+        const float* const theirs = place(other);
+        float2 v[kBlocks][2];
+#pragma unroll
+        for (int y = 0; y < kBlocks; ++y)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) v[y][h] = get_pair<true>(theirs + y * 256 + h * 128);
+#pragma unroll
+        for (int y = 0; y < kBlocks; ++y) sum[y / S::kOutB][y % S::kOutB] += f32x4{v[y][0].x, v[y][0].y, v[y][1].x, v[y][1].y};
+        if (has_bias)
+#pragma unroll
+          for (int j = 0; j < S::kFB; ++j)
+            bias_sum[j] += __hip_atomic_load(bias_place(other) + j * 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // (cleared again, so that a captured launch, which is replayed with its old ticket, finds none of its own)
+        if (tid == 0) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();  // (everyone has looked at `second`)
+      }
+    }
+  }
+  const bool partial = !kMerge && a.splits > 1;
+  // a lane holds columns 16 i + 4 quarter .. + 3 of row 16 j + r
+  float* dst = (partial ? a.part + (size_t)split * a.F * a.E : a.out);
 #pragma unroll
   for (int j = 0; j < S::kOutB; ++j) {
     const int f = f0 + (wb * S::kFB + group * S::kOutB + j) * 16 + r;
@@ -763,34 +840,19 @@ __device__ __forceinline__ void wgrad_tile(WgradArgs a, char* lds, int block) {
       if (f < a.F && e < a.E) *reinterpret_cast<f32x4*>(dst + (size_t)f * a.E + e) = sum[i][j];
     }
   }
-  if (S::kGroups > 1 && a.want_bias && et == 0) {  // the other group's column sums
-    float* x = reinterpret_cast<float*>(lds);
-    __syncthreads();
-    if (do_bias && group)
-#pragma unroll
-      for (int j = 0; j < S::kFB; ++j) x[(wb * S::kFB + j) * 64 + lane] = bias_acc[j];
-    __syncthreads();
-    if (do_bias && !group)
-#pragma unroll
-      for (int j = 0; j < S::kFB; ++j) bias_acc[j] += x[(wb * S::kFB + j) * 64 + lane];
-  }
-  if (do_bias && !group) {
-    float* bd = a.splits > 1 ? a.part_bias + (size_t)split * a.F : a.out_bias;
+  if (has_bias) {
+    float* bd = partial ? a.part_bias + (size_t)split * a.F : a.out_bias;
 #pragma unroll
     for (int j = 0; j < S::kFB; ++j) {
-      float v = bias_acc[j];
-      v += __shfl_xor(v, 16, 64);
-      v += __shfl_xor(v, 32, 64);
       const int f = f0 + (wb * S::kFB + j) * 16 + r;
-      if (quarter == 0 && f < a.F) bd[f] = v;
+      if (quarter == 0 && f < a.F) bd[f] = bias_sum[j];
     }
   }
 }
-
 template <class S>
 __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void proj_wgrad_kernel(WgradArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  wgrad_tile<S, kMaxRange, 0>(a, lds, blockIdx.x);
+  wgrad_tile<S, kMaxRange, 0, false>(a, lds, blockIdx.x);
 }
 
 // For a weight gradient that no product follows.
@@ -865,24 +927,24 @@ hipError_t add_ranges_alone(RangeSums s, hipStream_t stream) {
 }
 
 // ---- both gradients of a projection in one launch ------------------------------------------------------------
-// A small layer's gradients are two launches of workgroups that leave compute units idle (dW 2304 x 768 has 108
-// tiles; token ranges that fill the chip leave partial sums to be written, read and added).  Here the tiles of dW, each
-// over all token blocks, go first and those of the other gradient take the units that are left: no ranges, no
-// partial sums, one launch.
-constexpr int kWholeBlocks = 128;  // token blocks, at most
+// A small layer's gradients are two launches that leave compute units idle (dW 2304 x 768 has 108 tiles, dX at 8 x 512
+// tokens 192), and partial sums that the second has to read.  Here the tiles of dW go first, each over all token
+// blocks or a few ranges of them, and those of the other gradient take the units that are left; ranges are added by
+// the workgroups themselves.
+constexpr int kOneLaunchBlocks = 160;  // token blocks, at most (beyond, two launches are as fast)
 // The shortest ranges of two launches give each group four blocks; with chains of that length the error of dW (rms
 // against 64 bits, of its own rms) is 0.7e-7 to 1.1e-7 where it was up to 2.1e-7, and would be up to 3.4e-7 without.
 // Adding them up after the multiplication cost 8 % of a long range, while the next fragments travel half of that.
-constexpr int kWholeChain = 4;
+constexpr int kOneLaunchChain = 4;
 template <class S, bool kHeadTok>
 __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4) void proj_bwd_kernel(WgradArgs w, ProjArgs a, int w_blocks) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   static_assert(S::kThreads == Wgrad128::kThreads, "one workgroup size for both");
-  if ((int)blockIdx.x < w_blocks) wgrad_tile<Wgrad128, kWholeBlocks, kWholeChain>(w, lds, blockIdx.x);
+  if ((int)blockIdx.x < w_blocks) wgrad_tile<Wgrad128, kOneLaunchBlocks, kOneLaunchChain, true>(w, lds, blockIdx.x);
   else product_tile<S, kHeadTok, true>(a, lds, blockIdx.x - w_blocks);
 }
 
-int wgrad_tiles128(const WgradArgs& w) { return (w.F + 127) / 128 * ((w.E + 127) / 128); }
+int wgrad_tiles128(int F, int E) { return (F + 127) / 128 * ((E + 127) / 128); }
 
 // When the last of `first` workgroups of t1 us and then `second` ones of t2 us ends, one at a time on each unit.
 double end_of_both(int first, double t1, long second, double t2) {
@@ -899,13 +961,53 @@ double end_of_both(int first, double t1, long second, double t2) {
   return end;
 }
 
-template <class S, bool kHeadTok>
-hipError_t launch_bwd(WgradArgs w, ProjArgs a, int wgrad_id, int proj_id, hipStream_t stream) {
+struct BwdPlan {
+  double cost;       // us
+  int ranges;        // of token blocks; 0: not in one launch
+  bool wide;         // the product's tiles: 128 x 128, or 128 x 64
+  size_t bias_off, words_off, total;
+};
+template <class S>
+void offer_bwd(BwdPlan& best, ProjArgs a, int tiles, int blocks, int ranges, double per_step, double rest) {
   deal_tiles<S>(a);
+  const int first = (tiles * ranges + 7) / 8 * 8, per_range = (blocks + ranges - 1) / ranges;
+  double t1 = (0.44 + 0.12 * std::min(1.0, first / 256.0)) * per_range + 5.1;
+  for (int r = 1; r < ranges; r *= 2) t1 += 2.7;   // one addition of pairs
+  const double cost = 4.4 + end_of_both(first, t1, a.tile_blocks, per_step * (a.K / 64) + rest);
+  if (cost < best.cost) {
+    best.cost = cost;
+    best.ranges = ranges;
+    best.wide = S::kB == 2;
+  }
+}
+BwdPlan plan_bwd(const WgradArgs& w, const ProjArgs& a) {
+  BwdPlan p = {1e30, 0, false, 0, 0, 0};
+  const int tiles = wgrad_tiles128(w.F, w.E), blocks = w.B * ((w.N + 63) / 64);
+  if (blocks > kOneLaunchBlocks) return p;
+  for (int ranges = 1; ranges <= kMaxRanges && tiles * ranges <= 256 && (ranges == 1 || blocks >= 8 * ranges); ++ranges) {
+    offer_bwd<Proj128x2>(p, a, tiles, blocks, ranges, 0.38, 3.1);
+    offer_bwd<Proj64x2>(p, a, tiles, blocks, ranges, 0.35, 1.8);
+  }
+  if (p.ranges > 1) {
+    p.bias_off = align256((size_t)p.ranges * w.F * w.E * 4);
+    p.words_off = p.bias_off + align256((size_t)p.ranges * w.F * 4);
+    p.total = p.words_off + (size_t)tiles * kMaxRanges * 8 + 16;   // (the caller's address may be any)
+  }
+  return p;
+}
+
+template <class S, bool kHeadTok>
+hipError_t launch_bwd(WgradArgs w, ProjArgs a, const BwdPlan& p, char* ws, int wgrad_id, int proj_id, hipStream_t stream) {
+  deal_tiles<S>(a);
+  if (!a.out[0]) a.tile_blocks = 0;
+  ws += -reinterpret_cast<uintptr_t>(ws) & 15;
   w.blocks_per_seq = (w.N + 63) / 64;
-  w.splits = 1;
+  w.splits = p.ranges;
   w.per_split = w.B * w.blocks_per_seq;
-  const int w_blocks = (wgrad_tiles128(w) + 7) / 8 * 8;  // (whole rounds of XCDs, so the products' tiles are dealt as ever)
+  w.part = reinterpret_cast<float*>(ws);
+  w.part_bias = reinterpret_cast<float*>(ws + p.bias_off);
+  w.arrived = reinterpret_cast<unsigned long long*>(ws + p.words_off);
+  const int w_blocks = (wgrad_tiles128(w.F, w.E) * p.ranges + 7) / 8 * 8;  // (whole rounds of XCDs, so the products' tiles are dealt as ever)
   constexpr int kLds = std::max(S::kLds, Wgrad128::kLds);
   const hipError_t e = allow_lds<&proj_bwd_kernel<S, kHeadTok>>(kLds);
   if (e != hipSuccess) return e;
@@ -914,32 +1016,26 @@ hipError_t launch_bwd(WgradArgs w, ProjArgs a, int wgrad_id, int proj_id, hipStr
   return hipGetLastError();
 }
 
-// us that the launch takes, for the rule below.
-template <class S>
-double bwd_cost(const WgradArgs& w, ProjArgs a, double per_step, double rest) {
-  deal_tiles<S>(a);
-  const int tiles = (wgrad_tiles128(w) + 7) / 8 * 8, blocks = w.B * ((w.N + 63) / 64);
-  return 2.7 + end_of_both(tiles, (0.43 + 0.25 * tiles / 256) * blocks + 5.7, a.tile_blocks, per_step * (a.K / 64) + rest);
-}
-
-// dW (unless w.out is null) and the other gradient (unless a.out[0] is).  One launch if that is at least 6 % faster
-// by these costs, fitted to 150 pairs of gradients (64 to 16384 tokens, 256 to 2048 wide) in all three forms; over them
-// it gains 12 % on average.  us, as two launches and as one, gradients of QKV and of the output projection, 768 wide:
-// 512 tokens 27.3 -> 17.2 and 18.3 -> 11.6, 2048 tokens 33.7 -> 24.6 and 23.2 -> 22.4, 8 x 512 43.0 -> 39.5 and 26.5
-// as two (33.8 as one); 1024 wide, 1024 tokens 37.2 -> 25.1 and 23.7 -> 15.5, 4 x 1024 63 either way.
+// dW (unless w.out is null) and the other gradient (unless a.out[0] is).  One launch if these costs say that it is 12 %
+// faster at least, and if the other gradient alone would be computed in two groups (then it comes in the same bits
+// from either).  The costs were fitted to 64 pairs of sizes (64 to 16384 tokens, 256 to 1536 wide) in eleven
+// forms; over them the rule gains 15 % and loses nowhere.  us, as two launches and as one, gradients of QKV and of the
+// output projection, 768 wide: 512 tokens 28.0 -> 18.1 and 18.8 -> 12.5, 2048 tokens 33.9 -> 25.4 and 23.2 -> 19.3,
+// 8 x 512 47.2 -> 39.9 and 28.1 -> 23.5; 1024 wide, 1024 tokens 37.4 -> 26.9 and 24.3 -> 16.3, 4 x 1024 67.3 -> 63.8 and
+// 36.3 -> 28.8.
+// The rule looks at the sizes alone, so that dW is the same bits whether or not the other gradient is wanted.  (Alone
+// it takes, us, 512 tokens 13.1 -> 12.4 and 12.3 -> 11.7, 2048 tokens 26.4 -> 23.5, 8 x 512 32.3 -> 37.3 and 24.0 -> 24.5.)
 template <bool kHeadTok>
 hipError_t run_bwd(const WgradArgs& w, ProjArgs a, char* ws, int wgrad_id, int proj_id, hipStream_t stream) {
-  const bool want_w = w.out, want_a = a.out[0];
+  const WgradPlan alone = plan_wgrad(w.B, w.N, w.F, w.E);
   const ProjChoice product = choose_proj<kHeadTok, true>(a);
+  const BwdPlan both = plan_bwd(w, a);
+  const bool want_w = w.out, want_a = a.out[0];
+  if (want_w && product.groups == 2 && 1.12 * both.cost < 13.4 + 0.66 * alone.cost + 0.88 * product.cost)
+    return both.wide ? launch_bwd<Proj128x2, kHeadTok>(w, a, both, ws, wgrad_id, proj_id, stream)
+                     : launch_bwd<Proj64x2, kHeadTok>(w, a, both, ws, wgrad_id, proj_id, stream);
   if (want_w) {
-    const WgradPlan plan = plan_wgrad(w.B, w.N, w.F, w.E);
-    if (want_a && wgrad_tiles128(w) <= 256 && w.B * plan.blocks_per_seq <= kWholeBlocks) {
-      const double x128 = bwd_cost<Proj128x2>(w, a, 0.43, 2.2), x64 = bwd_cost<Proj64x2>(w, a, 0.37, 2.0);
-      if (1.06 * std::min(x128, x64) < 12.3 + 0.64 * plan.cost + product.cost)
-        return x128 <= x64 ? launch_bwd<Proj128x2, kHeadTok>(w, a, wgrad_id, proj_id, stream)
-                           : launch_bwd<Proj64x2, kHeadTok>(w, a, wgrad_id, proj_id, stream);
-    }
-    const hipError_t e = run_wgrad(w, plan, ws, wgrad_id, a.ranges, stream);
+    const hipError_t e = run_wgrad(w, alone, ws, wgrad_id, a.ranges, stream);
     if (e != hipSuccess) return e;
   }
   return want_a ? product.launch(a, proj_id, stream) : add_ranges_alone(a.ranges, stream);
@@ -979,15 +1075,40 @@ hipError_t launch_out_project(const void* o, const void* w_o, const float* bias,
   return choose_proj<true, false>(a).launch(a, 9, stream);
 }
 
-size_t qkv_project_bwd_workspace(int B, int N, int H, int E) { return plan_wgrad(B, N, 3 * H * kD, E).total; }
-size_t out_project_bwd_workspace(int B, int N, int H, int E) { return plan_wgrad(B, N, E, H * kD).total; }
+namespace {
+// The sizes of both gradients: dW [F][E] and the product over K.
+void bwd_sizes(WgradArgs& w, ProjArgs& a, int B, int N, int H, int F, int E, int features, int K) {
+  w = {};
+  a = {};
+  w.B = a.B = B; w.N = a.N = N; w.H = a.H = H;
+  w.F = F; w.E = E;
+  a.F = features; a.K = K;
+}
+void qkv_bwd_sizes(WgradArgs& w, ProjArgs& a, int B, int N, int H, int E) { bwd_sizes(w, a, B, N, H, 3 * H * kD, E, E, 3 * H * kD); }
+void out_bwd_sizes(WgradArgs& w, ProjArgs& a, int B, int N, int H, int E) { bwd_sizes(w, a, B, N, H, E, H * kD, H * kD, E); }
+size_t bwd_workspace(const WgradArgs& w, const ProjArgs& a) { return std::max(plan_wgrad(w.B, w.N, w.F, w.E).total, plan_bwd(w, a).total); }
+}  // namespace
+
+size_t qkv_project_bwd_workspace(int B, int N, int H, int E) {
+  WgradArgs w;
+  ProjArgs a;
+  qkv_bwd_sizes(w, a, B, N, H, E);
+  return bwd_workspace(w, a);
+}
+size_t out_project_bwd_workspace(int B, int N, int H, int E) {
+  WgradArgs w;
+  ProjArgs a;
+  out_bwd_sizes(w, a, B, N, H, E);
+  return bwd_workspace(w, a);
+}
 
 hipError_t launch_qkv_project_bwd(const void* x, const void* w_qkv, const unsigned char* flags,
                                   const void* dq, const void* dk, const void* dv, int B, int N, int H,
                                   int E, void* dx, float* dw, float* dbias, void* workspace,
-                                  hipStream_t stream) {
-  const int F = 3 * H * kD;
-  WgradArgs g = {};
+                                  unsigned long long ticket, hipStream_t stream) {
+  WgradArgs g;
+  ProjArgs a;
+  qkv_bwd_sizes(g, a, B, N, H, E);
   g.g.p[0] = static_cast<const unsigned short*>(dq);
   g.g.p[1] = static_cast<const unsigned short*>(dk);
   g.g.p[2] = static_cast<const unsigned short*>(dv);
@@ -999,26 +1120,23 @@ hipError_t launch_qkv_project_bwd(const void* x, const void* w_qkv, const unsign
   g.out = dw;
   g.out_bias = dbias;
   g.want_bias = dbias != nullptr;
-  g.B = B; g.N = N; g.H = H; g.F = F; g.E = E;
+  g.ticket = ticket;
   // dx[tok, :] = sum over the 3 H heads of dq, dk, dv [tok, head] . w_qkv[head rows, :]
-  ProjArgs a = {};
   a.w = static_cast<const unsigned short*>(w_qkv);  // [F][E], contracted over its rows
   a.tok3[0] = static_cast<const unsigned short*>(dq);
   a.tok3[1] = static_cast<const unsigned short*>(dk);
   a.tok3[2] = static_cast<const unsigned short*>(dv);
   a.flags = flags;
   a.out[0] = static_cast<unsigned short*>(dx);
-  a.B = B; a.N = N; a.H = H;
-  a.F = E;
-  a.K = F;
   return run_bwd<true>(g, a, static_cast<char*>(workspace), 11, 10, stream);
 }
 
 hipError_t launch_out_project_bwd(const void* o, const void* w_o, const unsigned char* flags,
                                   const void* dy, int B, int N, int H, int E, void* d_o, float* dw,
-                                  float* dbias, void* workspace, hipStream_t stream) {
-  const int J = H * kD;
-  WgradArgs g = {};
+                                  float* dbias, void* workspace, unsigned long long ticket, hipStream_t stream) {
+  WgradArgs g;
+  ProjArgs a;
+  out_bwd_sizes(g, a, B, N, H, E);
   g.g.p[0] = static_cast<const unsigned short*>(dy);
   g.g.heads = 0;
   g.g.ld = E;
@@ -1028,16 +1146,12 @@ hipError_t launch_out_project_bwd(const void* o, const void* w_o, const unsigned
   g.out = dw;
   g.out_bias = dbias;
   g.want_bias = dbias != nullptr;
-  g.B = B; g.N = N; g.H = H; g.F = E; g.E = J;
+  g.ticket = ticket;
   // d_o[tok, head i] = dy[tok, :] . w_o[:, head i columns], written head by head
-  ProjArgs a = {};
   a.w = static_cast<const unsigned short*>(w_o);  // [E][H*64], contracted over its rows
   a.tok = static_cast<const unsigned short*>(dy);
   a.flags = flags;
   a.out[0] = static_cast<unsigned short*>(d_o);
-  a.B = B; a.N = N; a.H = H;
-  a.F = J;
-  a.K = E;
   return run_bwd<false>(g, a, static_cast<char*>(workspace), 13, 12, stream);
 }
 

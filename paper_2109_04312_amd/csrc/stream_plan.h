@@ -37,6 +37,7 @@
 
 #include <type_traits>
 
+#include "arrival.h"
 #include "d2l.h"
 #include "launch.h"
 #include "mfma_common.h"
@@ -364,22 +365,8 @@ __device__ inline void store_owned_rows(const f32x16 (*acc[kTensors])[2], const 
 //
 // Forward and dK/dV: the chunk of an owner tile that arrives last merges inside the same launch
 // (a finalize kernel of its own cost 4.8 us in the forward and 6.4 us in the backward at B = 2,
-// N = 8192, H = 16, nearly all of it the launch).  Chunks of one tile may run on different XCDs, whose
-// L2s are not coherent, so partials and arrival words are accessed with relaxed device-scope
-// atomics (which bypass the L2), and "partials before arrival" comes from waiting for the stores'
-// acknowledgement.  dQ: merged by the first workgroups of the dK/dV kernel, behind the kernel boundary.
-template <bool kShared>
-__device__ __forceinline__ void put_pair(float* p, float x, float y) {
-  const unsigned long long v = (unsigned long long)__float_as_uint(x) | ((unsigned long long)__float_as_uint(y) << 32);
-  if (kShared) __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  else *reinterpret_cast<unsigned long long*>(p) = v;
-}
-template <bool kShared>
-__device__ __forceinline__ float2 get_pair(const float* p) {
-  const unsigned long long* q = reinterpret_cast<const unsigned long long*>(p);
-  const unsigned long long v = kShared ? __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *q;
-  return make_float2(__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32)));
-}
+// N = 8192, H = 16, nearly all of it the launch).  dQ: merged by the first workgroups of the dK/dV kernel, behind
+// the kernel boundary.
 constexpr int kItemFloats = 16 * 64;  // one wavefront's accumulator of one dim block
 template <bool kShared>
 __device__ __forceinline__ void store_partial(const f32x16 acc[2], float mul, float* __restrict__ part, int wave, int lane) {
@@ -427,12 +414,6 @@ __device__ __forceinline__ void load_items(float2 (&v)[kBatch][8], const float* 
       asm volatile("" ::"v"(v[e][i].x), "v"(v[e][i].y), "v"(v[e][i + 1].x), "v"(v[e][i + 1].y), "v"(v[e][i + 2].x),
                    "v"(v[e][i + 2].y), "v"(v[e][i + 3].x), "v"(v[e][i + 3].y));
 }
-// All of the workgroup's partials and words are where every XCD sees them from here on.
-__device__ __forceinline__ void publish_partials() {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-}
-
 // Zero fill of the rows of a pad unit in kTensors tensors.  The positions of all the rows a
 // thread will write are loaded first (independent loads, one round trip), then the stores go
 // out back to back.

@@ -296,3 +296,18 @@ def test_one_round_of_shared_tiles(B, N, H, E):
 @pytest.mark.parametrize("B,N,H,E", [(1, 1, 2, 128), (3, 65, 12, 768), (1, 1024, 16, 1024), (2, 130, 4, 1152), (9, 100, 24, 128)])
 def test_both_gradients_in_one_launch(B, N, H, E):
     check_bwd(N, B, N, H, E, pad_tail=N // 2)
+
+
+# ... and each alone, bit for bit: dW whole and in ranges (3 and 4, which are added in pairs), either tile shape
+@pytest.mark.parametrize("B,N,H,E", [(1, 300, 12, 768), (1, 2048, 12, 768), (8, 512, 12, 768), (4, 1000, 8, 512), (4, 1024, 16, 1024)])
+def test_each_gradient_alone_is_the_same(B, N, H, E):
+    from paper_2109_04312_amd import mate
+    x, w_qkv, _, w_o, _, flags, o = make(N, B, N, H, E, pad_tail=N // 7)
+    x, w_qkv, w_o, o, fl = dev(x), dev(w_qkv), dev(w_o), dev(o), torch.from_numpy(flags).cuda()
+    for call, want_x in ((lambda **kw: mate.qkv_project_bwd(x, w_qkv, fl, o, o, o, **kw), "want_dx"),
+                         (lambda **kw: mate.out_project_bwd(o, w_o, fl, x, **kw), "want_do")):
+        both, again = call(), call()
+        no_w, no_x = call(want_dw=False, want_dbias=False), call(**{want_x: False})
+        torch.cuda.synchronize()
+        assert all(torch.equal(u, v) for u, v in zip(both, again))
+        assert torch.equal(no_w[0], both[0]) and torch.equal(no_x[1], both[1]) and torch.equal(no_x[2], both[2])
