@@ -496,7 +496,7 @@ typedef hipError_t (*ProjLaunch)(ProjArgs, int, hipStream_t);
 struct ProjChoice {
   double cost;
   ProjLaunch launch;
-  int groups;   // shapes with as many groups add up a product's stages in the same order: the same bits
+  int groups;   // shapes with as many groups add up a product's stages in the same order
 };
 template <bool kHeadTok, bool kTransposedW>
 ProjChoice choose_proj(const ProjArgs& a) {
@@ -944,6 +944,13 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4) void proj_bwd_kernel
   else product_tile<S, kHeadTok, true>(a, lds, blockIdx.x - w_blocks);
 }
 
+// The product's tiles there, eight wavefronts each.  Those of one group and those of two add up a product's stages in
+// different orders; which of them, is as for the product alone, so that it comes in the same bits from either.
+using Both256 = Proj256;
+using Both128 = Shape<4, 2, 4, 2, 2, 1>;   // 256 x 128
+using Both128x2 = Proj128x2;
+using Both64x2 = Proj64x2;
+
 int wgrad_tiles128(int F, int E) { return (F + 127) / 128 * ((E + 127) / 128); }
 
 // When the last of `first` workgroups of t1 us and then `second` ones of t2 us ends, one at a time on each unit.
@@ -964,29 +971,36 @@ double end_of_both(int first, double t1, long second, double t2) {
 struct BwdPlan {
   double cost;       // us
   int ranges;        // of token blocks; 0: not in one launch
-  bool wide;         // the product's tiles: 128 x 128, or 128 x 64
+  bool large;        // the larger or the smaller tiles of the product
   size_t bias_off, words_off, total;
 };
 template <class S>
-void offer_bwd(BwdPlan& best, ProjArgs a, int tiles, int blocks, int ranges, double per_step, double rest) {
+void offer_bwd(BwdPlan& best, ProjArgs a, bool large, int tiles, int blocks, int ranges, double per_step, double rest) {
   deal_tiles<S>(a);
   const int first = (tiles * ranges + 7) / 8 * 8, per_range = (blocks + ranges - 1) / ranges;
   double t1 = (0.44 + 0.12 * std::min(1.0, first / 256.0)) * per_range + 5.1;
   for (int r = 1; r < ranges; r *= 2) t1 += 2.7;   // one addition of pairs
-  const double cost = 4.4 + end_of_both(first, t1, a.tile_blocks, per_step * (a.K / 64) + rest);
+  // (padding, which this leaves out, shortens long ranges most: several must be worth 16 %)
+  const double cost = (ranges > 1 ? 1.16 : 1.0) * (4.4 + end_of_both(first, t1, a.tile_blocks, per_step * (a.K / 64) + rest));
   if (cost < best.cost) {
     best.cost = cost;
     best.ranges = ranges;
-    best.wide = S::kB == 2;
+    best.large = large;
   }
 }
-BwdPlan plan_bwd(const WgradArgs& w, const ProjArgs& a) {
+// `groups`: of the product's shape if it were alone.
+BwdPlan plan_bwd(const WgradArgs& w, const ProjArgs& a, int groups) {
   BwdPlan p = {1e30, 0, false, 0, 0, 0};
   const int tiles = wgrad_tiles128(w.F, w.E), blocks = w.B * ((w.N + 63) / 64);
   if (blocks > kOneLaunchBlocks) return p;
   for (int ranges = 1; ranges <= kMaxRanges && tiles * ranges <= 256 && (ranges == 1 || blocks >= 8 * ranges); ++ranges) {
-    offer_bwd<Proj128x2>(p, a, tiles, blocks, ranges, 0.38, 3.1);
-    offer_bwd<Proj64x2>(p, a, tiles, blocks, ranges, 0.35, 1.8);
+    if (groups == 2) {
+      offer_bwd<Both128x2>(p, a, true, tiles, blocks, ranges, 0.38, 3.1);
+      offer_bwd<Both64x2>(p, a, false, tiles, blocks, ranges, 0.35, 1.8);
+    } else {
+      offer_bwd<Both256>(p, a, true, tiles, blocks, ranges, 1.3, 5.3);
+      offer_bwd<Both128>(p, a, false, tiles, blocks, ranges, 0.75, 5.0);
+    }
   }
   if (p.ranges > 1) {
     p.bias_off = align256((size_t)p.ranges * w.F * w.E * 4);
@@ -1016,24 +1030,26 @@ hipError_t launch_bwd(WgradArgs w, ProjArgs a, const BwdPlan& p, char* ws, int w
   return hipGetLastError();
 }
 
-// dW (unless w.out is null) and the other gradient (unless a.out[0] is).  One launch if these costs say that it is 12 %
-// faster at least, and if the other gradient alone would be computed in two groups (then it comes in the same bits
-// from either).  The costs were fitted to 64 pairs of sizes (64 to 16384 tokens, 256 to 1536 wide) in eleven
-// forms; over them the rule gains 15 % and loses nowhere.  us, as two launches and as one, gradients of QKV and of the
-// output projection, 768 wide: 512 tokens 28.0 -> 18.1 and 18.8 -> 12.5, 2048 tokens 33.9 -> 25.4 and 23.2 -> 19.3,
-// 8 x 512 47.2 -> 39.9 and 28.1 -> 23.5; 1024 wide, 1024 tokens 37.4 -> 26.9 and 24.3 -> 16.3, 4 x 1024 67.3 -> 63.8 and
-// 36.3 -> 28.8.
+// dW (unless w.out is null) and the other gradient (unless a.out[0] is).  One launch if these costs say that it is
+// faster.  They were fitted to 130 pairs of gradients (64 to 16384 tokens, 256 to 1536 wide) in up to fifteen forms;
+// over them the rule gains 16 %, loses 5 % at most and is 1.5 % behind the best form of each.  us, as two launches and
+// as one, gradients of QKV and of the output projection, 768 wide: 512 tokens 28.0 -> 18.1 and 18.8 -> 12.5, 2048 tokens
+// 33.9 -> 25.4 and 23.2 -> 19.3, 8 x 512 47.6 -> 41.2 and 27.8 -> 23.6, 3 x 1999 70.2 -> 56.4 and 33.6 -> 28.2;
+// 1024 wide, 1024 tokens 37.4 -> 26.9 and 24.3 -> 16.3, 4 x 1024 67.3 -> 63.8 and 36.3 -> 28.8.
 // The rule looks at the sizes alone, so that dW is the same bits whether or not the other gradient is wanted.  (Alone
-// it takes, us, 512 tokens 13.1 -> 12.4 and 12.3 -> 11.7, 2048 tokens 26.4 -> 23.5, 8 x 512 32.3 -> 37.3 and 24.0 -> 24.5.)
+// it takes, us, 512 tokens 13.1 -> 12.0 and 12.5 -> 11.4, 2048 tokens 26.0 -> 23.1 and 19.8 -> 20.9, 8 x 512 32.2 -> 36.8
+// and 23.7 -> 23.8, 16 x 512 49.5 -> 65.0 and 26.5 -> 29.8; 1024 wide, 4 x 1024 44.4 -> 34.9 and 24.9 -> 26.2.)
 template <bool kHeadTok>
 hipError_t run_bwd(const WgradArgs& w, ProjArgs a, char* ws, int wgrad_id, int proj_id, hipStream_t stream) {
   const WgradPlan alone = plan_wgrad(w.B, w.N, w.F, w.E);
   const ProjChoice product = choose_proj<kHeadTok, true>(a);
-  const BwdPlan both = plan_bwd(w, a);
+  const BwdPlan both = plan_bwd(w, a, product.groups);
   const bool want_w = w.out, want_a = a.out[0];
-  if (want_w && product.groups == 2 && 1.12 * both.cost < 13.4 + 0.66 * alone.cost + 0.88 * product.cost)
-    return both.wide ? launch_bwd<Proj128x2, kHeadTok>(w, a, both, ws, wgrad_id, proj_id, stream)
-                     : launch_bwd<Proj64x2, kHeadTok>(w, a, both, ws, wgrad_id, proj_id, stream);
+  if (want_w && both.cost < 13.4 + 0.66 * alone.cost + 0.88 * product.cost) {
+    const auto launch = product.groups == 2 ? (both.large ? launch_bwd<Both128x2, kHeadTok> : launch_bwd<Both64x2, kHeadTok>)
+                                            : (both.large ? launch_bwd<Both256, kHeadTok> : launch_bwd<Both128, kHeadTok>);
+    return launch(w, a, both, ws, wgrad_id, proj_id, stream);
+  }
   if (want_w) {
     const hipError_t e = run_wgrad(w, alone, ws, wgrad_id, a.ranges, stream);
     if (e != hipSuccess) return e;
@@ -1086,7 +1102,7 @@ void bwd_sizes(WgradArgs& w, ProjArgs& a, int B, int N, int H, int F, int E, int
 }
 void qkv_bwd_sizes(WgradArgs& w, ProjArgs& a, int B, int N, int H, int E) { bwd_sizes(w, a, B, N, H, 3 * H * kD, E, E, 3 * H * kD); }
 void out_bwd_sizes(WgradArgs& w, ProjArgs& a, int B, int N, int H, int E) { bwd_sizes(w, a, B, N, H, E, H * kD, H * kD, E); }
-size_t bwd_workspace(const WgradArgs& w, const ProjArgs& a) { return std::max(plan_wgrad(w.B, w.N, w.F, w.E).total, plan_bwd(w, a).total); }
+size_t bwd_workspace(const WgradArgs& w, const ProjArgs& a) { return std::max(plan_wgrad(w.B, w.N, w.F, w.E).total, plan_bwd(w, a, choose_proj<true, true>(a).groups).total); }
 }  // namespace
 
 size_t qkv_project_bwd_workspace(int B, int N, int H, int E) {

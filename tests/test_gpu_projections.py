@@ -298,7 +298,8 @@ def test_both_gradients_in_one_launch(B, N, H, E):
     check_bwd(N, B, N, H, E, pad_tail=N // 2)
 
 
-# ... and each alone, bit for bit: dW whole and in ranges (3 and 4, which are added in pairs), either tile shape
+# ... and each alone, bit for bit, and both replayed from a graph (the words that ranges announce themselves with must be
+# as good as new each time): dW whole and in ranges that are added in pairs, either tile shape
 @pytest.mark.parametrize("B,N,H,E", [(1, 300, 12, 768), (1, 2048, 12, 768), (8, 512, 12, 768), (4, 1000, 8, 512), (4, 1024, 16, 1024)])
 def test_each_gradient_alone_is_the_same(B, N, H, E):
     from paper_2109_04312_amd import mate
@@ -311,3 +312,14 @@ def test_each_gradient_alone_is_the_same(B, N, H, E):
         torch.cuda.synchronize()
         assert all(torch.equal(u, v) for u, v in zip(both, again))
         assert torch.equal(no_w[0], both[0]) and torch.equal(no_x[1], both[1]) and torch.equal(no_x[2], both[2])
+        ws = torch.full((mate.mate_project_bwd_workspace_bytes(B, N, H, E) // 4 + 1,), float("nan"), device="cuda").view(torch.uint8)
+        side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            captured = call(ws=ws)
+        for replay in range(3):
+            for y in captured:
+                y.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert all(torch.equal(u, v) for u, v in zip(both, captured)), replay
+            call(ws=ws)                                 # eager work on the same words
