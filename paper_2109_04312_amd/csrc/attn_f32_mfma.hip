@@ -17,7 +17,7 @@
 // operand order: three planes of 32 rows x 128 bytes, laid out and read like the tiles of the bf16 kernels (d2l.h).
 //
 // Measured (4 sequences of 512 tokens, 12 heads), with the fp32 instruction and with splits: forward 22.8 -> 17.5 us, backward
-// 62.4 -> 45.6, a training step 91.3 -> 69; one sequence of 128, 4 heads 7.4 both ways.  Errors against 64 bits (relative, 2-norm):
+// (dQ and dK/dV in two launches) 62.4 -> 45.6, a training step 91.3 -> 69; one sequence of 128, 4 heads 7.4 both ways.  Errors against 64 bits (relative, 2-norm):
 // O 2.6e-7 -> 1.4e-7, LSE 4.7e-8 -> 4.6e-8, dQ 3.9e-7 -> 3.0e-7, dK 4.0e-7 -> 3.1e-7, dV 3.8e-7 -> 3.0e-7.
 // What bounds it: a tile is 440 to 510 vector instructions (224 of them the splits of two tensors, 56 those of P or dS) beside
 // 1536 (forward) to 3072 cycles of matrix pipe; question-token owners have four tiles per wavefront and end last, and 74 KB of LDS
@@ -258,10 +258,10 @@ struct Quarter {
   int turn;  // which wavefront takes the first tile: the ones that get a tile more than the others
              // should not all sit on the same SIMD
 };
-__device__ inline bool take_quarter(const AttnArgs& a, Quarter& q) {
-  q.sub = ((blockIdx.x >> 3) + (blockIdx.x >> 5)) & 3;
-  q.turn = blockIdx.x >> 5;
-  if (!take_unit<false, false>(a, ((blockIdx.x >> 5) << 3) | (blockIdx.x & 7), q.w)) return false;
+__device__ inline bool take_quarter(const AttnArgs& a, unsigned block, Quarter& q) {
+  q.sub = ((block >> 3) + (block >> 5)) & 3;
+  q.turn = block >> 5;
+  if (!take_unit<false, false>(a, ((block >> 5) << 3) | (block & 7), q.w)) return false;
   const UnitPlan& u = q.w.u;
   if (u.kind == UNIT_PAD) return true;
   // (a chunked question-token owner: its first unit streams everything, there are no partials here)
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
   __shared__ float2 stat[kWaves][kRows];
   __shared__ int row_tok[kRows];
   Quarter q;
-  if (!take_quarter(a, q)) return;
+  if (!take_quarter(a, blockIdx.x, q)) return;
   const int tid = threadIdx.x, lane = tid & 63, m = lane & 31, hl = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const size_t bh = (size_t)q.w.bh * a.N;
@@ -476,22 +476,25 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
 }
 
 // ======================================================================================
-// dQ, and delta = rowsum(dO * O) for the dK/dV kernel
+// dQ
 // ======================================================================================
-__global__ __launch_bounds__(kThreads, 2) void bwd_dq_f32_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(1024))) char lds[kWaves * kPlanes];
-  __shared__ __attribute__((aligned(1024))) char own[2 * kPlanes];  // Q, dO
-  __shared__ int row_tok[kRows];
-  __shared__ float row_delta[kRows];
-  Quarter q;
-  if (!take_quarter(a, q)) return;
+// LDS of a backward workgroup.
+struct BwdLds {
+  char tiles[kWaves * kPlanes];
+  char own[2 * kPlanes];        // Q, dO; or K, V
+  float stat[kWaves][2][kRows]; // dK/dV, of the wavefront's tile: lse in base 2, delta
+  int row_tok[kRows];
+};
+
+__device__ __forceinline__ void dq_quarter(const AttnArgs& a, const Quarter& q, BwdLds& shared) {
+  char *const lds = shared.tiles, *const own = shared.own;
+  int* const row_tok = shared.row_tok;
   const int tid = threadIdx.x, lane = tid & 63, m = lane & 31, hl = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const size_t bh = (size_t)q.w.bh * a.N;
   const float* Q = static_cast<const float*>(a.q) + bh * kD;
   const float* K = static_cast<const float*>(a.k) + bh * kD;
   const float* V = static_cast<const float*>(a.v) + bh * kD;
-  const float* O = static_cast<const float*>(a.o) + bh * kD;
   const float* dO = static_cast<const float*>(a.dout) + bh * kD;
   float* dQ = static_cast<float*>(a.dq) + bh * kD;
   if (q.w.u.kind == UNIT_PAD) {
@@ -503,30 +506,19 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_f32_kernel(AttnArgs a) {
   if (tid < kRows) row_tok[tid] = r.valid ? r.pos : -1;
   const int t0 = (wave + q.turn) & (kWaves - 1);
   int tok = r.token(t0, m), tok_next = r.token(t0 + kWaves, m);
-  const float lse2 = a.lse[bh + r.pos] * kLog2e, sc = a.scale * kLog2e;
+  const float lse2 = a.lse[bh + r.pos] * kLog2e, sc = a.scale * kLog2e, delta = a.delta[bh + r.pos];
   TileRegs key, val;
-  {  // owned Q and dO rows to LDS; delta of the eight rows this wavefront brings, 16 lanes per row
-    OwnedRows g, o, qr;
+  {  // owned Q and dO rows to LDS
+    OwnedRows g, qr;
     g.load(dO, r.pos, wave, lane);
-    o.load(O, r.pos, wave, lane);
     qr.load(Q, r.pos, wave, lane);
     val.load(V, tok, lane);
     key.load(K, tok, lane);
     keep_order();
     g.split(own + kPlanes, wave, lane);
     qr.split(own, wave, lane);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const f32x4 &x = g.v[i], &y = o.v[i];
-      float d = x.x * y.x + x.y * y.y + x.z * y.z + x.w * y.w;
-#pragma unroll
-      for (int e = 8; e >= 1; e >>= 1) d += __shfl_xor(d, e, 64);
-      if ((lane & 15) == 0) row_delta[8 * wave + 4 * i + (lane >> 4)] = d;
-    }
   }
   __syncthreads();
-  const float delta = row_delta[m];
-  if (wave == 0 && hl == 0 && r.valid) a.delta[bh + r.pos] = delta;
   char* const tile = lds + wave * kPlanes;
   const OperandLanes lanes(lane);
   const PlainAddr tile_rows(lanes, lds_addr(tile)), own_rows(lanes, lds_addr(own));
@@ -585,13 +577,9 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_f32_kernel(AttnArgs a) {
 // dK, dV: the owned rows are keys, the streamed ones the queries that see them (the same lists and
 // windows as in the forward, read the other way round)
 // ======================================================================================
-__global__ __launch_bounds__(kThreads, 2) void bwd_dkv_f32_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(1024))) char lds[kWaves * kPlanes];
-  __shared__ __attribute__((aligned(1024))) char own[2 * kPlanes];  // K, V
-  __shared__ __attribute__((aligned(16))) float stat[kWaves][2][kRows];  // of the wavefront's tile: lse in base 2, delta
-  __shared__ int row_tok[kRows];
-  Quarter q;
-  if (!take_quarter(a, q)) return;
+__device__ __forceinline__ void dkv_quarter(const AttnArgs& a, const Quarter& q, BwdLds& shared) {
+  char *const lds = shared.tiles, *const own = shared.own;
+  int* const row_tok = shared.row_tok;
   const int tid = threadIdx.x, lane = tid & 63, m = lane & 31, hl = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const size_t bh = (size_t)q.w.bh * a.N;
@@ -631,7 +619,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dkv_f32_kernel(AttnArgs a) {
   const float sc = a.scale * kLog2e;
 
   f32x16 dk[2] = {zero16(), zero16()}, dv[2] = {zero16(), zero16()};
-  float* const my_stat = &stat[wave][0][0];
+  float* const my_stat = &shared.stat[wave][0][0];
   auto put_stat = [&]() {
     if (hl == 0) {
       my_stat[m] = row_lse * kLog2e;
@@ -714,6 +702,43 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dkv_f32_kernel(AttnArgs a) {
   store_sum(dv, 1.f, lds, row_tok, dV, wave, m, hl);
 }
 
+// ======================================================================================
+// The backward: delta = rowsum(dO * O), then both of the above
+// ======================================================================================
+// One after the other, dQ and dK/dV each ended with a last round of workgroups that left most of the chip idle (two fit on
+// a CU, 4 sequences of 512 tokens with 12 heads are 1.6 rounds) or were one round of latency.  In one launch, a unit's dK/dV beside its dQ, they
+// fill each other's; delta, which both need, comes from a launch of its own and is not computed by dQ.  us, backward as
+// dQ and dK/dV and now: one sequence of 128, 4 heads 22.7 -> 15.3; 12 heads, one of 512 37.7 -> 25.6, of 1024 66.8 -> 42.7,
+// 4 x 512 48.4 -> 46.0, 8 x 512 82.2 -> 78.0, 16 x 1024 331 -> 328.  (All of dK/dV first: 16.5, 25.9, 43.7, 46.8, 79.7, 330.)
+constexpr int kDeltaRows = 64;   // of a workgroup, 16 lanes of four dims each
+__global__ __launch_bounds__(kThreads) void delta_f32_kernel(AttnArgs a) {
+  const size_t rows = (size_t)a.B * a.H * a.N, first = (size_t)blockIdx.x * kDeltaRows + (threadIdx.x >> 4);
+  const int piece = threadIdx.x & 15;
+  f32x4 g[4], o[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const size_t at = min(first + 16 * i, rows - 1) * kD + 4 * piece;
+    g[i] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(a.dout) + at);
+    o[i] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(a.o) + at);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float d = g[i].x * o[i].x + g[i].y * o[i].y + g[i].z * o[i].z + g[i].w * o[i].w;
+#pragma unroll
+    for (int e = 8; e >= 1; e >>= 1) d += __shfl_xor(d, e, 64);
+    if (piece == 0 && first + 16 * i < rows) a.delta[first + 16 * i] = d;
+  }
+}
+__global__ __launch_bounds__(kThreads, 2) void bwd_f32_kernel(AttnArgs a, unsigned first) {
+  __shared__ __attribute__((aligned(1024))) BwdLds lds;
+  const unsigned block = first + blockIdx.x;
+  Quarter q;
+  // (32 workgroups are the quarters of eight units, one on each XCD)
+  if (!take_quarter(a, ((block >> 6) << 5) | (block & 31), q)) return;
+  if (block & 32) dq_quarter(a, q, lds);
+  else dkv_quarter(a, q, lds);
+}
+
 }  // namespace
 
 hipError_t launch_fwd_f32(const AttnArgs& a, hipStream_t stream) {
@@ -722,12 +747,15 @@ hipError_t launch_fwd_f32(const AttnArgs& a, hipStream_t stream) {
 }
 
 hipError_t launch_bwd_f32(const AttnArgs& a, hipStream_t stream) {
-  const dim3 grid(4 * unit_grid(a.B, a.H, a.N, a.n_col));
-  hipLaunchKernelGGL(bwd_dq_f32_kernel, grid, dim3(kThreads), 0, stream, a);
+  const size_t rows = (size_t)a.B * a.H * a.N;
+  hipLaunchKernelGGL(delta_f32_kernel, dim3((unsigned)((rows + kDeltaRows - 1) / kDeltaRows)), dim3(kThreads), 0, stream, a);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(bwd_dkv_f32_kernel, grid, dim3(kThreads), 0, stream, a);
-  return hipGetLastError();
+  const unsigned blocks = 2 * 4 * (unsigned)unit_grid(a.B, a.H, a.N, a.n_col), most = 1u << 23;  // (a launch has less than 2^32 threads)
+  for (unsigned first = 0; first < blocks && e == hipSuccess; first += most) {
+    hipLaunchKernelGGL(bwd_f32_kernel, dim3(min(most, blocks - first)), dim3(kThreads), 0, stream, a, first);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 }  // namespace mate
