@@ -14,6 +14,7 @@
 // Question-token owners stream the whole sequence, so their stream is cut into chunks run by
 // separate workgroups, which leave fp32 partials that are added in chunk order: dQ's by the first
 // workgroups of the dkv kernel, dK's and dV's by the chunk that arrives last.
+// Small launches run the units of both kernels in one (see the end).
 // Pairs (table query, table key) are therefore recomputed once in each of the first two.
 #include <hip/hip_runtime.h>
 
@@ -64,11 +65,9 @@ __device__ __forceinline__ void merge_chunks(const float* const (&part)[kTensors
 constexpr int kDqStage = 2 * kTileBytes;          // K tile, V tile
 constexpr int kDkvStage = 2 * kTileBytes + 512;   // Q tile, dO tile, -lse/scale[64], -delta[64]
 
-__device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
-  __shared__ __attribute__((aligned(1024))) char lds[kStages * kDqStage];
-  __shared__ int idx_ring[kIdxSlots][BN];
-  __shared__ int q_tok[BM];
-
+// kOne: delta and -LSE / scale are there already, and chunks are merged here.
+template <bool kOne>
+__device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w, char* lds, int (*idx_ring)[BN], int* q_tok, int* group_done) {
   const int b = w.b;
   const int N = a.N, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction
@@ -101,18 +100,19 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
   asm volatile("" ::"v"(me.pos), "v"(me.lo), "v"(me.hi), "v"(me.stage_tok));  // the owned rows are known from here on
   if (tid < BM) q_tok[tid] = me.stage_tok;
   // the dkv kernel counts the chunks of an owner tile in the word of its first one
-  if (tid == 0 && u.part >= 0) a.arrived[(size_t)w.bh * owner_slots(N) + u.part] = 0;
+  if (!kOne && tid == 0 && u.part >= 0) a.arrived[(size_t)w.bh * owner_slots(N) + u.part] = 0;
   stream.prime();
 
   // this lane's query row and dO row as B operands (column m, k = dims), and delta
   OwnedTile q_rows, g_rows, o_rows;
   g_rows.load(dO, me.pos, lane);
-  o_rows.load(O, me.pos, lane);
+  if (!kOne) o_rows.load(O, me.pos, lane);
   q_rows.load(Q, me.pos, lane);
   const float lse = a.lse[bh + me.pos];
+  const float kept = kOne ? a.delta[bh + me.pos] : 0.f;
   bf16x8 qf[4], gf[4];
   g_rows.operands(gf, stream.room(), lane);
-  const float delta = row_delta(g_rows, o_rows, stream.room(), lane);
+  const float delta = kOne ? -kept : row_delta(g_rows, o_rows, stream.room(), lane);
   q_rows.operands(qf, stream.room(), lane);
   // Everything loaded into registers so far is pinned as complete here, so that no load with a
   // register destination is pending inside the loop.
@@ -120,7 +120,7 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
                "v"(gf[2]), "v"(gf[3]), "v"(delta), "v"(lse));
   // every chunk of a question-token owner computes the same delta; the first one stores it
   // (stored negated, with -lse / scale beside it: the dK/dV kernel starts its accumulators there)
-  if (hl == 0 && me.valid && u.t_begin == 0 && split.writes(wave)) {
+  if (!kOne && hl == 0 && me.valid && u.t_begin == 0 && split.writes(wave)) {
     a.delta[bh + me.pos] = -delta;
     a.nlse[bh + me.pos] = -lse / a.scale;
   }
@@ -151,7 +151,21 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
   }
   if (u.part >= 0) {
     const size_t slot = (size_t)w.bh * owner_slots(N) + u.part;
-    if (me.wave_active && split.writes(wave)) store_partial<false>(dq_acc, a.scale, a.part[0] + slot * BM * kD, wave, ln);
+    if (me.wave_active && split.writes(wave)) store_partial<kOne>(dq_acc, a.scale, a.part[0] + slot * BM * kD, wave, ln);
+    if constexpr (kOne) {
+      const size_t slot0 = slot - u.part % u.n_chunks;
+      publish_partials();
+      if (tid == 0)  // (the word of the second chunk; the first one's is dK/dV's)
+        *group_done = __hip_atomic_fetch_add(a.arrived + slot0 + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                      (unsigned long long)(u.n_chunks - 1);
+      __syncthreads();
+      if (*group_done) {
+        const float* const parts[1] = {a.part[0] + slot0 * BM * kD};
+        unsigned short* const grads[1] = {dQ};
+        merge_chunks<1, true>(parts, grads, u.own_count - u.t0, u.n_chunks, lds, q_tok, wave, ln);
+        if (tid == 0) __hip_atomic_store(a.arrived + slot0 + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
     return;
   }
   const f32x16 (*accs[1])[2] = {&dq_acc};
@@ -164,18 +178,18 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w) {
 // fit at once and the stragglers double the kernel's critical path)
 template <bool kJoin>
 __global__ __launch_bounds__(kThreads, 4) void bwd_dq_mfma_kernel(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) char lds[kStages * kDqStage];
+  __shared__ int idx_ring[kIdxSlots][BN];
+  __shared__ int row_tok[BM];
   Work w;
   if (!take_unit<true, kJoin>(a, blockIdx.x, w)) return;
-  bwd_dq_unit(a, w);
+  bwd_dq_unit<false>(a, w, lds, idx_ring, row_tok, nullptr);
 }
 
 // ======================================================================================
 // dK, dV
 // ======================================================================================
-__device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, char* lds, int* k_tok) {
-  __shared__ int idx_ring[kIdxSlots][BN];
-  __shared__ int group_done;
-
+__device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, char* lds, int (*idx_ring)[BN], int* k_tok, int* group_done) {
   const int b = w.b;
   const int N = a.N, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction
@@ -261,10 +275,10 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
     }
     publish_partials();
     if (tid == 0)
-      group_done = __hip_atomic_fetch_add(a.arrived + slot0, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+      *group_done = __hip_atomic_fetch_add(a.arrived + slot0, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
                    (unsigned long long)(u.n_chunks - 1);
     __syncthreads();
-    if (group_done) {
+    if (*group_done) {
       const float* const parts[2] = {a.part[1] + slot0 * BM * kD, a.part[2] + slot0 * BM * kD};
       unsigned short* const grads[2] = {dK, dV};
       merge_chunks<2, true>(parts, grads, u.own_count - u.t0, u.n_chunks, lds, k_tok, wave, lane);
@@ -306,14 +320,62 @@ __device__ __forceinline__ void merge_dq(const AttnArgs& a, int bh_i, char* stag
 template <bool kJoin>
 __global__ __launch_bounds__(kThreads) void bwd_dkv_mfma_kernel(AttnArgs a, int n_merge) {
   __shared__ __attribute__((aligned(1024))) char lds[kStages * kDkvStage];
+  __shared__ int idx_ring[kIdxSlots][BN];
   __shared__ int row_tok[BM];
+  __shared__ int group_done;
   if ((int)blockIdx.x < n_merge) {
     if ((int)blockIdx.x < a.B * a.H) merge_dq<kJoin>(a, blockIdx.x, lds, row_tok);
     return;
   }
   Work w;
   if (!take_unit<true, kJoin>(a, blockIdx.x - n_merge, w)) return;
-  bwd_dkv_unit(a, w, lds, row_tok);
+  bwd_dkv_unit(a, w, lds, idx_ring, row_tok, &group_done);
+}
+
+// ======================================================================================
+// Small launches: both in one, and delta before it
+// ======================================================================================
+// A launch that does not fill the chip is as long as its longest unit, twice over; with dK/dV's units and dQ's in one
+// launch the second time goes.  What dQ did for dK/dV (-delta, -LSE / scale, the cleared words) is a launch of its own
+// then, and dQ's chunks are merged by the one that arrives last, counted in the word of the group's second chunk.
+// us, backward as dQ and dK/dV and as delta and both: 12 heads, one sequence of 300 19.0 -> 13.8, 512 22.8 -> 16.1, 1024
+// 24.4 -> 17.1, 4096 56.8 -> 43.3, 8 x 512 30.3 -> 24.9, 16 x 512 44.2 -> 42.8.
+constexpr int kDeltaRows = 128;   // of a workgroup, eight lanes of eight dims each
+__global__ __launch_bounds__(kThreads) void bwd_delta_kernel(AttnArgs a) {
+  const size_t rows = (size_t)a.B * a.H * a.N, first = (size_t)blockIdx.x * kDeltaRows + (threadIdx.x >> 3);
+  const int piece = threadIdx.x & 7;
+  bf16x8 g[4], o[4];
+  float lse[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const size_t row = min(first + 32 * i, rows - 1), at = row * kD + 8 * piece;
+    g[i] = *reinterpret_cast<const bf16x8*>(static_cast<const unsigned short*>(a.dout) + at);
+    o[i] = *reinterpret_cast<const bf16x8*>(static_cast<const unsigned short*>(a.o) + at);
+    lse[i] = a.lse[row];
+  }
+  const size_t words = (size_t)a.B * a.H * owner_slots(a.N);
+  for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < words; i += (size_t)gridDim.x * kThreads) a.arrived[i] = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float d = row_dot8(g[i], o[i]);
+    if (piece == 0 && first + 32 * i < rows) {
+      a.delta[first + 32 * i] = -d;
+      a.nlse[first + 32 * i] = -lse[i] / a.scale;
+    }
+  }
+}
+template <bool kJoin>
+__global__ __launch_bounds__(kThreads) void bwd_both_mfma_kernel(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) char lds[kStages * kDkvStage];
+  __shared__ int idx_ring[kIdxSlots][BN];
+  __shared__ int row_tok[BM];
+  __shared__ int group_done;
+  const unsigned half = gridDim.x / 2;
+  const bool dkv = blockIdx.x < half;
+  Work w;
+  if (!take_unit<true, kJoin>(a, dkv ? blockIdx.x : blockIdx.x - half, w)) return;
+  if (dkv) bwd_dkv_unit(a, w, lds, idx_ring, row_tok, &group_done);
+  else bwd_dq_unit<true>(a, w, lds, idx_ring, row_tok, &group_done);
 }
 
 }  // namespace
@@ -322,6 +384,18 @@ template <bool kJoin>
 static hipError_t launch_bwd(const AttnArgs& a, hipStream_t stream) {
   const dim3 grid(unit_grid(a.B, a.H, a.N, a.n_col)), block(kThreads);
   hipError_t e;
+  // Up to three units of 128 rows a compute unit.  (78 sizes; one launch is so many times as fast: at 768 units 0.98 to
+  // 1.09, at 1024 0.98 to 1.10, at 1152 0.96 to 1.17, at 1536 0.92 to 1.05, 16 ragged sequences of 4096 0.93.  dQ has four
+  // workgroups on a compute unit where the registers of dK/dV leave room for three.)
+  if ((long)a.B * a.H * owner_slots(a.N) <= 3 * 256) {
+    const size_t rows = (size_t)a.B * a.H * a.N;
+    hipLaunchKernelGGL(bwd_delta_kernel, dim3((unsigned)((rows + kDeltaRows - 1) / kDeltaRows)), block, 0, stream, a);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    ProfileScope prof(4, stream, 3);
+    hipLaunchKernelGGL(bwd_both_mfma_kernel<kJoin>, dim3(2 * grid.x), block, 0, stream, a);
+    return hipGetLastError();
+  }
   {
     ProfileScope prof(3, stream);
     hipLaunchKernelGGL(bwd_dq_mfma_kernel<kJoin>, grid, block, 0, stream, a);

@@ -297,17 +297,21 @@ __device__ __forceinline__ float row_sum8(float x) {
   add(std::integral_constant<int, 0x141>{});  // mirrored within eight lanes: the other four
   return x;
 }
+// x . y of a row, eight lanes of eight dims each.
+__device__ __forceinline__ float row_dot8(const bf16x8& x, const bf16x8& y) {
+  float d = 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; e += 2) {
+    const bf16x2 u = {x[e], x[e + 1]}, v = {y[e], y[e + 1]};
+    d = __builtin_amdgcn_fdot2_f32_bf16(u, v, d, false);
+  }
+  return row_sum8(d);
+}
 // delta = dO . O of the rows of two OwnedTiles: every lane gets its row m's.  `room` as above (128 bytes of it).
 __device__ __forceinline__ float row_delta(const OwnedTile& g, const OwnedTile& o, char* room, int lane) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    float d = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-      const bf16x2 x = {g.v[i][e], g.v[i][e + 1]}, y = {o.v[i][e], o.v[i][e + 1]};
-      d = __builtin_amdgcn_fdot2_f32_bf16(x, y, d, false);
-    }
-    d = row_sum8(d);
+    const float d = row_dot8(g.v[i], o.v[i]);
     if ((lane & 7) == 0) reinterpret_cast<float*>(room)[(lane >> 3) + 8 * i] = d;
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

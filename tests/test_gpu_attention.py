@@ -551,3 +551,21 @@ def test_f32_special_values_reach_only_the_tokens_that_meet_them(tensor, value, 
             print(tensor, value, h, name, "finite", int(fine.sum()), "of", fine.size, flush=True)
             assert np.array_equal(np.isfinite(g), fine), (name, h)
             assert np.abs(g[fine] - r[fine]).max(initial=0.0) <= 1e-4, (name, h)
+
+
+@pytest.mark.parametrize("B,N,H,n_global", [(2, 5000, 16, 140), (22, 300, 12, 40)])
+def test_backward_of_a_batch_in_parts(B, N, H, n_global):
+    """A large launch runs dQ and dK/dV one after the other, a small one both at once (B H ceil(N / 128) of 1280 and 640,
+    792 and 396 units, with chunks of question-token owners and without): the same bits."""
+    from paper_2109_04312_amd import mate
+    w = chunked_workload(N, B, N, H, n_global)
+    r, c, f = hp.dev_structure(w.structure)
+    q, k, v, do = (hp.to_dev(x, "bf16") for x in (w.q, w.k, w.v, w.do))
+    out, lse = mate.attn_fwd(q, k, v, mate.build_segments(r, c, f), w.head_kind, w.scale)
+    whole = mate.attn_bwd(q, k, v, out, lse, do, mate.build_segments(r, c, f), w.head_kind, w.scale)
+    for part in (slice(0, B // 2), slice(B // 2, B)):
+        seg = mate.build_segments(*(x[part].contiguous() for x in (r, c, f)))
+        some = mate.attn_bwd(*(x[part].contiguous() for x in (q, k, v, out, lse, do)), seg, w.head_kind, w.scale)
+        torch.cuda.synchronize()
+        for name, x, y in zip(("dq", "dk", "dv"), some, whole):
+            assert torch.equal(x, y[part]), (part, name)
