@@ -569,3 +569,36 @@ def test_backward_of_a_batch_in_parts(B, N, H, n_global):
         torch.cuda.synchronize()
         for name, x, y in zip(("dq", "dk", "dv"), some, whole):
             assert torch.equal(x, y[part]), (part, name)
+
+
+@pytest.mark.parametrize("values", ["ordinary", "wide", "no split"])
+def test_f32_products_from_splits(values):
+    """fp32 products are formed from three bf16 parts: as good as fp32 over 120 binary orders of magnitude, and for a value
+    above the largest bf16, which has no such parts.  Bounds: a product and its share of an fp32 sum are within a few
+    2^-24 of their size, P within 2^-24 times the exponents of a score of a few units, of its own."""
+    from paper_2109_04312_amd import mate
+    n_global, rows, cols, cell, N = 33, 9, 5, 4, 230
+    st = synth._stack([synth.flatten_table(N, n_global, rows, cols, np.full(rows * cols, cell))])
+    rng = np.random.default_rng(4)
+    q, k, v, do = synth.draw_tensors(rng, 1, 2, N, 64, "f32", 4)
+    at = n_global + rows * cols * cell - 1
+    if values == "wide":
+        v, do = (x * np.exp2(rng.integers(-60, 61, (1, 2, N, 1))).astype(np.float32) for x in (v, do))
+    elif values == "no split":
+        v[0, :, at], do = np.float32(3.4e38), do * np.float32(2.0 ** -40)
+    w = synth.Workload("splits", "f32", st, np.array([ROW, COL], np.uint8), q, k, v, do, 0.125)
+    ref = pairwise_reference(w, (q, k, v, do))
+    dev = [hp.to_dev(x, "f32") for x in (q, k, v, do)]
+    seg = mate.build_segments(*hp.dev_structure(st))
+    out, lse = mate.attn_fwd(*dev[:3], seg, w.head_kind, w.scale)
+    got = dict(zip(("o", "dq", "dk", "dv"), (out, *mate.attn_bwd(*dev[:3], out, lse, dev[3], seg, w.head_kind, w.scale))))
+    for (b, h), d in ref.items():
+        Q, K, V, G = (x[b, h].astype(np.float64) for x in (q, k, v, do))
+        meets = orc.attention_mask(st.row_ids[b], st.col_ids[b], st.flags[b], int(w.head_kind[h])).astype(bool)
+        p = np.where(meets, np.exp(w.scale * (Q @ K.T) - d["lse"][:, None]), 0.0)
+        ds = p * (np.abs(G) @ np.abs(V).T + (np.abs(G) * np.abs(d["o"])).sum(1)[:, None])
+        size = {"o": p @ np.abs(V), "dv": p.T @ np.abs(G), "dq": w.scale * ds @ np.abs(K), "dk": w.scale * ds.T @ np.abs(Q)}
+        for name, s in size.items():
+            ratio = np.abs(got[name][b, h].double().cpu().numpy() - d[name]) / np.maximum(s, 1e-300)
+            print(values, h, name, "max error %.1e of its size" % ratio.max(), flush=True)
+            assert ratio.max() <= 32 * 2.0 ** -24, (name, h)
