@@ -328,7 +328,7 @@ mate_status mate_out_project(const void* o, const void* w_o, const float* bias,
  *   workspace   mate_project_bwd_workspace_bytes(B, N, H, E) bytes (partial sums of the weight
  *               gradient)
  *   t, H, E     as for the forward calls
- * Asynchronous on `stream`; deterministic (partial sums are added in a fixed order, no atomics).
+ * Asynchronous on `stream`; deterministic (partial sums are added in a fixed order, no floating-point atomics).
  */
 size_t mate_project_bwd_workspace_bytes(int B, int N, int H, int E);
 mate_status mate_qkv_project_bwd(const void* x, const void* w_qkv, const uint8_t* flags,
@@ -347,10 +347,11 @@ mate_status mate_out_project_bwd(const void* o, const void* w_o, const uint8_t* 
  * bracketed by hipEventRecord(start_event) and hipEventRecord(stop_event) on the stream of that
  * call; the hook disarms itself once used.  The events are hipEvent_t handles passed as void*,
  * created with timing enabled and owned by the caller.  kernel = MATE_KERNEL_NONE disarms.
- * Up to 256 positions the backward of the dense-mask variant is one launch; both of its names mean
- * that one.  The kernels of MATE_F32 have no name.
+ * Up to 256 positions the backward of the dense-mask variant is one launch, and so are the bf16 backward (behind
+ * a short one) up to B * H * ceil(N / 128) = 768 and both gradients of a projection of a small layer; both names mean
+ * that one then.  The kernels of MATE_F32 have no name.
  * The hook is per host thread.  The library keeps no other state that a caller can see: besides it a
- * counter that numbers the forward calls of the process, the static array of
+ * counter that numbers the forward and projection backward calls of the process, the static array of
  * mate_attn_bwd_dense_static, and launch settings per device.
  */
 enum { MATE_KERNEL_NONE = 0, MATE_KERNEL_BUILD = 1, MATE_KERNEL_FWD = 2, MATE_KERNEL_BWD_DQ = 3,

@@ -988,12 +988,20 @@ void offer_bwd(BwdPlan& best, ProjArgs a, bool large, int tiles, int blocks, int
     best.large = large;
   }
 }
-// `groups`: of the product's shape if it were alone.
-BwdPlan plan_bwd(const WgradArgs& w, const ProjArgs& a, int groups) {
+// Where the partial sums of dW's ranges lie in the workspace.
+void lay_out(BwdPlan& p, const WgradArgs& w, int ranges) {
+  p.bias_off = align256((size_t)ranges * w.F * w.E * 4);
+  p.words_off = p.bias_off + align256((size_t)ranges * w.F * 4);
+  p.total = p.words_off + (size_t)wgrad_tiles128(w.F, w.E) * kMaxRanges * 8 + 16;   // (the caller's address may be any)
+}
+// `groups`: of the product's shape if it were alone; `room`: bytes of the workspace, which are those that two launches need.
+BwdPlan plan_bwd(const WgradArgs& w, const ProjArgs& a, int groups, size_t room) {
   BwdPlan p = {1e30, 0, false, 0, 0, 0};
   const int tiles = wgrad_tiles128(w.F, w.E), blocks = w.B * ((w.N + 63) / 64);
   if (blocks > kOneLaunchBlocks) return p;
   for (int ranges = 1; ranges <= kMaxRanges && tiles * ranges <= 256 && (ranges == 1 || blocks >= 8 * ranges); ++ranges) {
+    lay_out(p, w, ranges);
+    if (ranges > 1 && p.total > room) break;
     if (groups == 2) {
       offer_bwd<Both128x2>(p, a, true, tiles, blocks, ranges, 0.38, 3.1);
       offer_bwd<Both64x2>(p, a, false, tiles, blocks, ranges, 0.35, 1.8);
@@ -1002,11 +1010,7 @@ BwdPlan plan_bwd(const WgradArgs& w, const ProjArgs& a, int groups) {
       offer_bwd<Both128>(p, a, false, tiles, blocks, ranges, 0.75, 5.0);
     }
   }
-  if (p.ranges > 1) {
-    p.bias_off = align256((size_t)p.ranges * w.F * w.E * 4);
-    p.words_off = p.bias_off + align256((size_t)p.ranges * w.F * 4);
-    p.total = p.words_off + (size_t)tiles * kMaxRanges * 8 + 16;   // (the caller's address may be any)
-  }
+  lay_out(p, w, p.ranges);
   return p;
 }
 
@@ -1043,7 +1047,7 @@ template <bool kHeadTok>
 hipError_t run_bwd(const WgradArgs& w, ProjArgs a, char* ws, int wgrad_id, int proj_id, hipStream_t stream) {
   const WgradPlan alone = plan_wgrad(w.B, w.N, w.F, w.E);
   const ProjChoice product = choose_proj<kHeadTok, true>(a);
-  const BwdPlan both = plan_bwd(w, a, product.groups);
+  const BwdPlan both = plan_bwd(w, a, product.groups, alone.total);
   const bool want_w = w.out, want_a = a.out[0];
   if (want_w && both.cost < 13.4 + 0.66 * alone.cost + 0.88 * product.cost) {
     const auto launch = product.groups == 2 ? (both.large ? launch_bwd<Both128x2, kHeadTok> : launch_bwd<Both64x2, kHeadTok>)
@@ -1102,21 +1106,10 @@ void bwd_sizes(WgradArgs& w, ProjArgs& a, int B, int N, int H, int F, int E, int
 }
 void qkv_bwd_sizes(WgradArgs& w, ProjArgs& a, int B, int N, int H, int E) { bwd_sizes(w, a, B, N, H, 3 * H * kD, E, E, 3 * H * kD); }
 void out_bwd_sizes(WgradArgs& w, ProjArgs& a, int B, int N, int H, int E) { bwd_sizes(w, a, B, N, H, E, H * kD, H * kD, E); }
-size_t bwd_workspace(const WgradArgs& w, const ProjArgs& a) { return std::max(plan_wgrad(w.B, w.N, w.F, w.E).total, plan_bwd(w, a, choose_proj<true, true>(a).groups).total); }
 }  // namespace
 
-size_t qkv_project_bwd_workspace(int B, int N, int H, int E) {
-  WgradArgs w;
-  ProjArgs a;
-  qkv_bwd_sizes(w, a, B, N, H, E);
-  return bwd_workspace(w, a);
-}
-size_t out_project_bwd_workspace(int B, int N, int H, int E) {
-  WgradArgs w;
-  ProjArgs a;
-  out_bwd_sizes(w, a, B, N, H, E);
-  return bwd_workspace(w, a);
-}
+size_t qkv_project_bwd_workspace(int B, int N, int H, int E) { return plan_wgrad(B, N, 3 * H * kD, E).total; }
+size_t out_project_bwd_workspace(int B, int N, int H, int E) { return plan_wgrad(B, N, E, H * kD).total; }
 
 hipError_t launch_qkv_project_bwd(const void* x, const void* w_qkv, const unsigned char* flags,
                                   const void* dq, const void* dk, const void* dv, int B, int N, int H,
