@@ -95,7 +95,7 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w, ch
   // transposed (dQ^T += K^T dS^T), V plain (dP^T = V dO^T).
   TileStream<kDqStage> stream(u, global_idx, lds, idx_ring, K, V, nullptr, 0, wave, lane);
   stream.begin();
-  const OwnerSplit split(u, wave);
+  const OwnerSplit<1> split(u, wave);
   const OwnedRow me = owned_row(u, a, b, view, split.block, m);
   asm volatile("" ::"v"(me.pos), "v"(me.lo), "v"(me.hi), "v"(me.stage_tok));  // the owned rows are known from here on
   if (tid < BM) q_tok[tid] = me.stage_tok;
@@ -221,7 +221,7 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
                                2 * kTileBytes + 256 * wave, wave, lane);
   stream.begin();
   // `me` is this lane's key; its window is the set of query slots that see it
-  const OwnerSplit split(u, wave);
+  const OwnerSplit<1> split(u, wave);
   const OwnedRow me = owned_row(u, a, b, view, split.block, m);
   asm volatile("" ::"v"(me.pos), "v"(me.lo), "v"(me.hi), "v"(me.stage_tok));  // the owned rows are known from here on
   if (tid < BM) k_tok[tid] = me.stage_tok;

@@ -70,12 +70,20 @@ __device__ __forceinline__ void merge_chunks(const AttnArgs& a, const UnitPlan& 
   flush_rows(O, stage, row_tok, wave, lane);
 }
 
-__device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
-  __shared__ __attribute__((aligned(1024))) char lds[kStages * kStageBytes];
-  __shared__ int idx_ring[kIdxSlots][BN];  // [tile & 7][row] token positions
-  __shared__ int q_tok[BM];
-  __shared__ int group_done;
+template <int kTiles>
+struct FwdLds {
+  __attribute__((aligned(1024))) char stages[kStages * kTiles * kStageBytes];
+  int idx_ring[kIdxSlots][BN];  // [tile & 7][row] token positions
+  int q_tok[BM];
+  int group_done;
+};
 
+template <int kTiles>
+__device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w, FwdLds<kTiles>& s) {
+  char* const lds = s.stages;
+  int (&idx_ring)[kIdxSlots][BN] = s.idx_ring;
+  int (&q_tok)[BM] = s.q_tok;
+  int& group_done = s.group_done;
   const int b = w.b;
   const int N = a.N, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction
@@ -109,9 +117,9 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
   // First round trip: which rows this workgroup owns, and the token indices of the first tiles.
   // Second: the owned query rows (registers) and the first K / V tiles (LDS), all in flight
   // together.
-  TileStream<kStageBytes> stream(u, global_idx, lds, idx_ring, K, V, nullptr, 0, wave, lane);
+  TileStream<kStageBytes, kTiles> stream(u, global_idx, lds, idx_ring, K, V, nullptr, 0, wave, lane);
   stream.begin();
-  const OwnerSplit split(u, wave);
+  const OwnerSplit<kTiles> split(u, wave);
   const OwnedRow me = owned_row(u, a, b, view, split.block, m);
   asm volatile("" ::"v"(me.pos), "v"(me.lo), "v"(me.hi), "v"(me.stage_tok));  // the owned rows are known from here on
   if (tid < BM) q_tok[tid] = me.stage_tok;
@@ -135,16 +143,20 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
 
   const OperandLanes lanes(lane);
 
-  for (int t = tb; t < te; ++t) {
-    const unsigned tile = lds_addr(stream.acquire(t));
-
-    // visible slot window for this tile: question keys [0,G), else this lane's segment range
-    const bool part0 = t < u.n_t0;
-    const int base = part0 ? t * BN : u.s_lo + (t - u.n_t0) * BN;
-    if (me.wave_active) {
-      WindowMask mask(base, hl, part0, u.G, me.lo, me.hi, split.first(base, part0 ? 0 : me.w_lo),
-                      split.end(base, part0 ? u.G : me.w_hi), part0 ? 0 : me.a_lo, part0 ? u.G : me.a_hi);
-      fwd_tile(tile, qf, lanes, sc, mask, o_acc, m_run, l_run, ref);
+  for (int t0 = tb; t0 < te; t0 += kTiles) {
+    const unsigned stage = lds_addr(stream.acquire(t0));
+#pragma unroll 1
+    for (int j = 0; j < kTiles; ++j) {
+      const int t = t0 + j;
+      if (kTiles > 1 && (t >= te || !split.meets(j))) continue;
+      // visible slot window for this tile: question keys [0,G), else this lane's segment range
+      const bool part0 = t < u.n_t0;
+      const int base = part0 ? t * BN : u.s_lo + (t - u.n_t0) * BN;
+      if (me.wave_active) {
+        WindowMask mask(base, hl, part0, u.G, me.lo, me.hi, split.first(base, part0 ? 0 : me.w_lo),
+                        split.end(base, part0 ? u.G : me.w_hi), part0 ? 0 : me.a_lo, part0 ? u.G : me.a_hi);
+        fwd_tile(stage + j * kStageBytes, qf, lanes, sc, mask, o_acc, m_run, l_run, ref);
+      }
     }
   }
   __syncthreads();  // all wavefronts are done reading the stages; reuse them for the epilogue
@@ -156,19 +168,26 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
     // (beyond the 16 KB the epilogue stages rows in; the statistics where the token indices were)
     char* const mine = lds + BM * 128 + (wave & 1) * (kItemFloats * 2 * 4);
     float* const stat = reinterpret_cast<float*>(&idx_ring[2 * (wave & 1)][0]);
-    if (wave >= 2) {
-      put_items<2>(mine, o_acc, ln);
-      stat[ln] = m_run;
-      stat[64 + ln] = l_run;
-    }
-    __syncthreads();
-    if (wave < 2) {
-      const float m2 = stat[ln], m_new = fmaxf(m_run, m2);
+    auto put = [&](char* items, float* st) {
+      put_items<2>(items, o_acc, ln);
+      st[ln] = m_run;
+      st[64 + ln] = l_run;
+    };
+    auto add = [&](const char* items, const float* st) {
+      const float m2 = st[ln], m_new = fmaxf(m_run, m2);
       const float own = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run - m_new) * sc);
       const float other = m2 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m2 - m_new) * sc);
-      l_run = l_run * own + stat[64 + ln] * other;
+      l_run = l_run * own + st[64 + ln] * other;
       m_run = m_new;
-      add_items<2>(mine, o_acc, own, other, ln);
+      add_items<2>(items, o_acc, own, other, ln);
+    };
+    if (wave >= 2) put(mine, stat);
+    __syncthreads();
+    if (wave < 2) add(mine, stat);
+    if (kTiles == 2 && split.four) {  // and the other tiles
+      if (wave == 1) put(mine, stat);
+      __syncthreads();
+      if (wave == 0) add(lds + BM * 128 + kItemFloats * 2 * 4, reinterpret_cast<const float*>(&idx_ring[2][0]));
     }
   }
   const bool writes = me.wave_active && split.writes(wave);
@@ -199,17 +218,35 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w) {
 
 template <bool kChunksFirst, bool kJoin>
 __global__ __launch_bounds__(kThreads, 4) void fwd_mfma_kernel(AttnArgs a) {
+  __shared__ FwdLds<1> s;
   Work w;
   if (!take_unit<kChunksFirst, kJoin>(a, blockIdx.x, w)) return;
-  fwd_unit(a, w);
+  fwd_unit<1>(a, w, s);
+}
+template <bool kChunksFirst>
+__global__ __launch_bounds__(kThreads, 2) void fwd_small_kernel(AttnArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char dynamic_lds[];
+  Work w;
+  if (!take_unit<kChunksFirst, false>(a, blockIdx.x, w)) return;
+  if (OwnerSplit<2>(w.u, 0).four) fwd_unit<2>(a, w, *reinterpret_cast<FwdLds<2>*>(dynamic_lds));
+  else fwd_unit<1>(a, w, *reinterpret_cast<FwdLds<1>*>(dynamic_lds));
 }
 
 }  // namespace
 
-hipError_t launch_fwd_mfma(const AttnArgs& a, hipStream_t stream) {
+template <bool kChunksFirst>
+static hipError_t launch_small(const AttnArgs& a, dim3 grid, hipStream_t stream) {
+  const hipError_t e = allow_lds<&fwd_small_kernel<kChunksFirst>>(sizeof(FwdLds<2>));
+  if (e != hipSuccess) return e;
   ProfileScope prof(2, stream);
+  hipLaunchKernelGGL(fwd_small_kernel<kChunksFirst>, grid, dim3(kThreads), sizeof(FwdLds<2>), stream, a);
+  return hipGetLastError();
+}
+hipError_t launch_fwd_mfma(const AttnArgs& a, hipStream_t stream) {
   const dim3 grid(unit_grid(a.B, a.H, a.N, a.n_col)), block(kThreads);
   const bool first = fwd_chunks_first(a.B, a.H, a.N), join = joins_chunks(a.B, a.H, a.N);
+  if (small_forward(a.B, a.H, a.N)) return small_owners_first(a.B, a.H, a.N) ? launch_small<true>(a, grid, stream) : launch_small<false>(a, grid, stream);
+  ProfileScope prof(2, stream);
   if (first && join) hipLaunchKernelGGL((fwd_mfma_kernel<true, true>), grid, block, 0, stream, a);
   else if (join) hipLaunchKernelGGL((fwd_mfma_kernel<false, true>), grid, block, 0, stream, a);
   else if (first) hipLaunchKernelGGL((fwd_mfma_kernel<true, false>), grid, block, 0, stream, a);

@@ -82,6 +82,17 @@ inline bool joins_chunks(int B, int H, int N) {
 }
 __host__ __device__ inline int joined(int n_chunks) { return (n_chunks + 1) >> 1; }
 
+// Small launches of the forward: a question-token owner of at most 32 rows is met by all four wavefronts, two tiles at a
+// time (OwnerSplit).  That takes the LDS of two workgroups, so a launch must fit the chip twice over: at most two units a
+// compute unit, with all the chunks that its sequences could have.  us, forward with 32 question tokens or fewer, one tile
+// and two at a time: one sequence, 12 heads, 450 tokens 9.4 -> 8.5, 512 10.0 -> 8.7, 700 11.1 -> 9.5, 2048 12.1 -> 11.3, 4 x
+// 512 10.3 -> 9.6, 8 x 512 12.5 -> 11.4; with more of them 0 to +2 %.
+inline int forward_units(int B, int H, int N) { return B * H * (owner_slots(N) + (may_chunk(B, N) ? owner_slots(N) : 1)); }
+inline bool small_forward(int B, int H, int N) { return (long)B * H * owner_slots(N) <= 512 && forward_units(B, H, N) <= 512; }
+// Question-token units before column-head units there: where some compute units get two.  (8 x 512 with 60 question
+// tokens 12.9 -> 11.6, with 77 15.3 -> 13.5; 4 x 512 10.4 -> 10.9.)
+inline bool small_owners_first(int B, int H, int N) { return forward_units(B, H, N) > 256; }
+
 // Entry i of the head order.  A byte indexed by a run-time value would be fetched with a vector
 // load (a memory round trip at the start of every workgroup); the containing 32-bit word comes
 // through the scalar cache with the other kernel arguments.
@@ -207,13 +218,21 @@ __device__ inline void tile_source(const UnitPlan& u, const int* global_idx, int
 // two results are added (through LDS) before anything is stored.  Most question-token owners are such units,
 // and they are the longest chain of tiles of a small launch.  (One or two tiles are not worth the addition: forward /
 // backward of one sequence of 64 with 12 heads 6.2/14.7 us split, 5.6/13.1 whole; from three on split is faster.)
+//
+// With kTiles = 2 tiles in a stage, a unit of at most 32 rows has work for all four: wavefronts 2 h + j meet half h of
+// tile j of every stage.
+template <int kTiles>
 struct OwnerSplit {
   bool on;
+  bool four;  // all four own the same 32 rows
   int block;  // the wavefront's 32-row block of owned rows
   int half;   // and of streamed rows
+  int tile;   // and, if four, of the tiles
   __device__ inline OwnerSplit(const UnitPlan& u, int wave)
-      : on(u.own_count - u.t0 <= BM / 2 && u.t_end - u.t_begin >= 3), block(on ? wave & 1 : wave), half(wave >> 1) {}
-  __device__ inline bool writes(int wave) const { return !on || wave < 2; }
+      : on(u.own_count - u.t0 <= BM / 2 && u.t_end - u.t_begin >= 3), four(kTiles == 2 && on && u.own_count - u.t0 <= BM / 4),
+        block(four ? 0 : on ? wave & 1 : wave), half(wave >> 1), tile(wave & 1) {}
+  __device__ inline bool meets(int j) const { return kTiles == 1 || !four || j == tile; }
+  __device__ inline bool writes(int wave) const { return !on || wave < (kTiles == 2 && four ? 1 : 2); }
   // [first, end): the part of the slots [lo, hi) met in the tile that begins at slot `base`
   __device__ inline int first(int base, int lo) const { return on ? max(lo, base + 32 * half) : lo; }
   __device__ inline int end(int base, int hi) const { return on ? min(hi, base + 32 * half + 32) : hi; }

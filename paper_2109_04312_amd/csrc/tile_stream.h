@@ -18,10 +18,13 @@
 namespace mate {
 
 constexpr int kStages = 2;
-constexpr int kIdxSlots = 8;  // tiles of indices in the ring (at least three are live at once; a power of two)
+constexpr int kIdxSlots = 8;  // tiles of indices in the ring (three stages' are live at once; a power of two)
 
-template <int kStageBytes>
+// kTiles = 2 (small launches, see small_forward in stream_plan.h): a stage holds two consecutive tiles, which the
+// wavefronts meet one after the other or share, and every function below is for both.
+template <int kTileStage, int kTiles = 1>
 struct TileStream {
+  static constexpr int kStageBytes = kTiles * kTileStage;
   const UnitPlan& u;
   const int* global_idx;
   char* stages;               // kStages * kStageBytes of LDS
@@ -39,7 +42,8 @@ struct TileStream {
       : u(u_), global_idx(gidx), stages(st), ring(rg), X0(x0), X1(x1), row_src(rs), row_off(row_off_), wave(wave_),
         lane(lane_), ll(make_load_lane(wave_, lane_)) {}
 
-  __device__ char* stage(int t) { return stages + ((unsigned)(t - u.t_begin) % kStages) * kStageBytes; }
+  // (tile t of a stage that begins with tile t - j)
+  __device__ char* stage(int t) { return stages + ((unsigned)(t - u.t_begin) / kTiles % kStages) * kStageBytes; }
   // 4 KB of the stage that stays empty until the first acquire(), one piece per wavefront
   __device__ char* room() { return stages + kStageBytes + wave * 4096; }
   __device__ void issue_idx(int t) {
@@ -48,10 +52,10 @@ struct TileStream {
     tile_source(u, global_idx, t, list, base, last);
     issue_row_words(list, min(base + lane, last), &ring[t & (kIdxSlots - 1)][0]);
   }
-  __device__ void issue_data(int t) {
+  __device__ void issue_data(int t, int j = 0) {
     const int* r = ring[t & (kIdxSlots - 1)];
     const int x0 = r[ll.row0], x1 = r[ll.row0 + 8];
-    char* st = stage(t);
+    char* st = stage(t) + j * kTileStage;
     issue_tile(X0, x0, x1, ll, st, wave);
     issue_tile(X1, x0, x1, ll, st + kTileBytes, wave);
     if (row_src) issue_row_words(row_src, r[lane], st + row_off);
@@ -62,21 +66,27 @@ struct TileStream {
   // data of the first.
   __device__ void begin() {
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
+    for (int s = 0; s < 2 * kTiles; ++s)
       if (u.t_begin + s < u.t_end) issue_idx(u.t_begin + s);
   }
   __device__ void prime() {
     wait_vmcnt_le(0);
     barrier_no_fence();  // every wavefront's share of the first indices is in the ring
-    if (u.t_begin < u.t_end) issue_data(u.t_begin);
+#pragma unroll
+    for (int j = 0; j < kTiles; ++j)
+      if (u.t_begin + j < u.t_end) issue_data(u.t_begin + j, j);
   }
-  // Top of iteration t: tile t is complete in LDS for every wavefront, tile t - 1's stage is
+  // Top of an iteration: tile t (and t + 1) is complete in LDS for every wavefront, the stage before is
   // free; keep the pipeline full.  Returns the stage holding tile t.
   __device__ const char* acquire(int t) {
     wait_vmcnt_le<0>(0);      // my share of tile t has landed
     barrier_no_fence();       // ... everyone's has, and everyone is done with tile t - 1
-    if (t + 2 < u.t_end) issue_idx(t + 2);
-    if (t + 1 < u.t_end) issue_data(t + 1);
+#pragma unroll
+    for (int j = 0; j < kTiles; ++j)
+      if (t + 2 * kTiles + j < u.t_end) issue_idx(t + 2 * kTiles + j);
+#pragma unroll
+    for (int j = 0; j < kTiles; ++j)
+      if (t + kTiles + j < u.t_end) issue_data(t + kTiles + j, j);
     return stage(t);
   }
 };

@@ -602,3 +602,12 @@ def test_f32_products_from_splits(values):
             ratio = np.abs(got[name][b, h].double().cpu().numpy() - d[name]) / np.maximum(s, 1e-300)
             print(values, h, name, "max error %.1e of its size" % ratio.max(), flush=True)
             assert ratio.max() <= 32 * 2.0 ** -24, (name, h)
+
+
+@pytest.mark.parametrize("n_global,N", [(1, 130), (32, 160), (32, 200), (31, 321), (33, 321), (32, 700), (7, 1500)])
+def test_owners_that_all_wavefronts_meet_two_tiles_at_a_time(n_global, N):
+    """Small launches, question-token owners of at most 32 rows: three, an odd and an even number of tiles, a last tile of
+    one row or of all, chunks, and one row more than 32."""
+    w = chunked_workload(N + n_global, 1, N, 2, n_global)
+    got, _ = hp.run_hip(w, True)
+    print(hp.report(hp.compare(got, hp.run_oracle(w, True, [(0, 0), (0, 1)]), w, w.name)), flush=True)
