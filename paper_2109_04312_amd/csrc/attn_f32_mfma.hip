@@ -1,12 +1,14 @@
 // fp32 MATE attention on the matrix cores: the path for dtype f32, forward and backward.
 //
-// Products are formed from splits: x = x1 + x2 + x3 with bf16 parts of 8 significant bits each, which together hold all 24
-// bits of an fp32 value, and x y = x1 y1 + (x1 y2 + x2 y1) + (x1 y3 + x2 y2 + x3 y1).  What is left out is below
-// 2^-25 |x y|, an eighth of an fp32 rounding of the sums it goes into.  Six v_mfma_f32_32x32x16_bf16 (32 cycles, 16 of the contraction)
+// Products are formed from splits (the published three-part bfloat16 scheme of Henry, Tang and Heinecke, 2019, "Leveraging
+// the bfloat16 artificial intelligence datatype for higher-precision computations"): x = x1 + x2 + x3 with bf16 parts of 8
+// significant bits each, which together hold all 24 bits of an fp32 value, and
+// x y = x1 y1 + (x1 y2 + x2 y1) + (x1 y3 + x2 y2 + x3 y1).  What is left out is below 2^-25 |x y|, less than an fp32
+// rounding of the sums it goes into.  Six v_mfma_f32_32x32x16_bf16 (32 cycles, 16 of the contraction)
 // take the place of eight v_mfma_f32_32x32x2_f32 (64 cycles, 2 of it): 192 cycles for 512.
 // Sums are fp32 as before, and fewer of them are rounded (a matrix instruction adds sixteen products at once).
-// (A value above the largest bf16, 3.39e38, has no such split, nor has an infinity or a NaN: see accumulate_special.  The parts
-// of a value below 2^-108 lose bits.)
+// (A value above the largest bf16, 3.39e38, has no such split, nor has an infinity or a NaN: see accumulate_special.  For
+// values below 2^-103 see kLeast.)
 //
 // Same pattern, tables and work units as the bf16 kernels (stream_plan.h), other proportions: no shared tiles and no
 // barriers in the loop.  A workgroup owns 32 rows (a quarter of a unit), its four wavefronts take every fourth
@@ -16,9 +18,12 @@
 // A tile is loaded in whole rows (16 lanes x 16 bytes) into registers, is split there, and passes through LDS into
 // operand order: three planes of 32 rows x 128 bytes, laid out and read like the tiles of the bf16 kernels (d2l.h).
 //
-// Measured (4 sequences of 512 tokens, 12 heads), with the fp32 instruction and with splits: forward 22.8 -> 17.5 us, backward
-// (dQ and dK/dV in two launches) 62.4 -> 45.6, a training step 91.3 -> 69; one sequence of 128, 4 heads 7.4 both ways.  Errors against 64 bits (relative, 2-norm):
-// O 2.6e-7 -> 1.4e-7, LSE 4.7e-8 -> 4.6e-8, dQ 3.9e-7 -> 3.0e-7, dK 4.0e-7 -> 3.1e-7, dV 3.8e-7 -> 3.0e-7.
+// Measured (4 sequences of 512 tokens, 12 heads), with the fp32 instruction and with splits: forward 22.8 -> 18.3 us, backward
+// 62.4 -> 46.5 (3 of it from one launch), a training step 91.3 -> 69; one sequence of 128, 4 heads 7.4 -> 7.5.  Errors against
+// 64 bits (relative 2-norm, and the largest in units of the rms; means of 12 seeds at that shape): O 2.6e-7 -> 1.4e-7 and
+// 5.2e-6 -> 2.7e-6, LSE 4.7e-8 -> 4.5e-8 and 2.0e-7 -> 1.8e-7, dQ 3.9e-7 -> 3.0e-7 and 7.4e-6 -> 5.5e-6, dK 4.1e-7 -> 3.2e-7
+// and 1.09e-5 -> 0.81e-5, dV 3.9e-7 -> 3.1e-7 and 9.3e-6 -> 7.3e-6; smaller at seven other shapes of 64 to 1024 tokens and with
+// Q and K three times as large, too.
 // What bounds it: a tile is 440 to 510 vector instructions (224 of them the splits of two tensors, 56 those of P or dS) beside
 // 1536 (forward) to 3072 cycles of matrix pipe; question-token owners have four tiles per wavefront and end last, and 74 KB of LDS
 // leave room for two workgroups on a CU.  (The splits interleaved with the matrix instructions of the tile before: 17.5 ->
@@ -72,6 +77,33 @@ __device__ __forceinline__ void split2(float x, float y, unsigned (&w)[3]) {
     y = __builtin_amdgcn_fdot2_f32_bf16(part, minus_y, y, false);
   }
 }
+// ---- values whose parts would not all be normal numbers -----------------------------------------------------------
+// A value of kLeast or more has its last bit at 2^-126 or above, so its parts are zeros or normal numbers.  Smaller ones
+// would lose up to kLost of themselves.  Results in which that could show are computed with whole values, in the second
+// pass that infinities have too.  No streamed value is looked at for it (that took 3 % of a backward and 5 % of a forward,
+// this takes 2 %):
+//  * P and dS are small by themselves (a score 87 below the largest is 2^-126): they are split times kLift.
+//  * A sum of weights times rows of V, K or Q is off by at most kLost times the sum of the weights, which is known (the
+//    forward's row sum) or bounded by the largest (dS).  Only where a result is less than 2^25 times that are the
+//    rows looked at.  (Zeros in a result, from a column of zeros, cost that look; small values the second pass.)
+//  * A score matters as it is, not against its size: from exact owned rows of at most kLarge it is off by less than 2^-54
+//    before the scale.  Owned rows that hold small or large values have the second pass, and so have large scales.
+//  * dP matters against delta, which shows what small values of V could cost; those of dO: see delta_f32_kernel.
+constexpr float kLeast = 0x1p-103f, kLost = 0x1p-125f, kLarge = 0x1p64f, kLargeScale = 0x1p20f, kLift = 0x1p24f;
+constexpr float kVisible = kLost * 0x1p25f;        // times the sum of weights: a result above it has lost nothing
+constexpr float kMostRows = 16384;                 // MATE_MAX_N
+// Is x small and not zero?
+__device__ __forceinline__ bool is_small(float x) { return __float_as_uint(fabsf(x)) - 1u < __float_as_uint(kLeast) - 1u; }
+template <int kCount>
+__device__ __forceinline__ bool any_small(const f32x4 (&v)[kCount]) {
+  bool small = false;
+#pragma unroll
+  for (int i = 0; i < kCount; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) small |= is_small(v[i][e]);
+  return __any(small);
+}
+
 // 16 bytes of a row to the planes at `tile`: piece = dims 4 piece .. + 3 of row `row`.
 __device__ __forceinline__ void put_split(char* tile, int row, int piece, const f32x4& v) {
   unsigned a[3], b[3];
@@ -124,6 +156,26 @@ struct OwnedRows {
   __device__ __forceinline__ void split(char* tile, int wave, int lane) const {
 #pragma unroll
     for (int i = 0; i < 2; ++i) put_split(tile, 8 * wave + 4 * i + (lane >> 4), lane & 15, v[i]);
+  }
+  // Is there a value that is zero, small or large?
+  __device__ __forceinline__ bool suspect() const {
+    float least = kLeast, most = kLarge;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; e += 2) {
+        least = fminf(fminf(least, fabsf(v[i][e])), fabsf(v[i][e + 1]));
+        most = fmaxf(fmaxf(most, fabsf(v[i][e])), fabsf(v[i][e + 1]));
+      }
+    return least < kLeast || most > kLarge;
+  }
+  __device__ __forceinline__ bool inexact() const {
+    bool large = false;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) large |= fabsf(v[i][e]) > kLarge;
+    return any_small(v) || __any(large);
   }
 };
 
@@ -245,6 +297,25 @@ __device__ __forceinline__ bool any_special(const f32x16 (&acc)[2]) {
   return __any(__float_as_uint(x) >= 0x7f800000u);
 }
 
+// Is any value's size below the lane's bound?
+__device__ __forceinline__ bool any_below(const f32x16 (&acc)[2], float bound) {
+  float least = fabsf(acc[0][0]);
+#pragma unroll
+  for (int i = 1; i < 31; i += 2) least = fminf(fminf(least, fabsf(acc[i >> 4][i & 15])), fabsf(acc[(i + 1) >> 4][(i + 1) & 15]));
+  return __any(fminf(least, fabsf(acc[1][15])) < bound);
+}
+__device__ __forceinline__ void most_of(float& most, const f32x16& x) {
+#pragma unroll
+  for (int c = 0; c < 16; c += 2) most = fmaxf(fmaxf(most, fabsf(x[c])), fabsf(x[c + 1]));
+}
+// What the four wavefronts found in the owned rows that they loaded.
+__device__ __forceinline__ int any_of(const int (&flags)[kWaves]) {
+  int any = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) any |= flags[w];
+  return any;
+}
+
 // Loads and stores stay on their side of this (the compiler sinks a prefetch to its first use otherwise).
 __device__ __forceinline__ void keep_order() { asm volatile("" ::: "memory"); }
 
@@ -311,6 +382,18 @@ struct Rows {
   }
 };
 
+// Has X a small value in this wavefront's tiles?
+__device__ __forceinline__ bool any_small_row(const float* X, const Rows& r, int t0, int m, int lane) {
+  bool small = false;
+#pragma unroll 1
+  for (int t = t0; t < r.n && !small; t += kWaves) {
+    TileRegs x;
+    x.load(X, r.token(t, m), lane);
+    small = any_small(x.v);
+  }
+  return small;
+}
+
 // Sum of the four wavefronts' accumulators, stored as whole rows: lane m's column is owned row m.
 // `lds` = the wavefronts' pieces, `row_tok` = the owned rows' tokens.
 __device__ __forceinline__ float* piece_of(char* lds, int wave) { return reinterpret_cast<float*>(lds + wave * kPlanes); }
@@ -363,7 +446,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds[kWaves * kPlanes];
   __shared__ __attribute__((aligned(1024))) char own[kPlanes];
   __shared__ float2 stat[kWaves][kRows];
-  __shared__ int row_tok[kRows];
+  __shared__ int row_tok[kRows], inexact[kWaves];
   Quarter q;
   if (!take_quarter(a, blockIdx.x, q)) return;
   const int tid = threadIdx.x, lane = tid & 63, m = lane & 31, hl = lane >> 5;
@@ -389,7 +472,10 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
   val.load(V, tok, lane);
   keep_order();
   q_rows.split(own, wave, lane);
+  inexact[wave] = __any(q_rows.suspect()) && q_rows.inexact();
   __syncthreads();
+  const int own_inexact = any_of(inexact);
+  keep_order();
   char* const tile = lds + wave * kPlanes;
   const OperandLanes lanes(lane);
   const PlainAddr tile_rows(lanes, lds_addr(tile)), own_rows(lanes, lds_addr(own));
@@ -399,7 +485,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
   f32x16 o[2] = {zero16(), zero16()};
   float m_run = -INFINITY, l_run = 0.f;
   // S^T -> P^T of a tile, O and the row sum rescaled
-  auto probs = [&](f32x16& s, const SlotWindow& mask) {
+  auto probs = [&](f32x16& s, const SlotWindow& mask, float lift) {
 #pragma unroll
     for (int c = 0; c < 16; ++c) s[c] = mask.in(c) ? s[c] : -INFINITY;
     float mx = s[0];
@@ -416,6 +502,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
       o[1][c] *= alpha;
       s[c] = __builtin_amdgcn_exp2f(fmaf(s[c], sc, -msc));
       l_run += s[c];
+      s[c] *= lift;
     }
   };
   for (int t = t0; t < r.n; t += kWaves) {
@@ -428,12 +515,15 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
     val.split(tile, lane);                                // (the keys have been read)
     val.load(V, tok_next, lane);
     keep_order();
-    probs(s, r.mask(t, hl));
+    probs(s, r.mask(t, hl), kLift);
     accumulate(o, tile_cols, s);                          // O^T += V^T P^T
     keep_order();
     tok_next = tok_after;
   }
-  if (__builtin_expect(any_special(o), 0)) {
+  float l_tot = half_sum(l_run);
+  bool whole = any_special(o) || __builtin_amdgcn_readfirstlane(own_inexact) || a.scale > kLargeScale;
+  if (__builtin_expect(any_below(o, l_tot * (kLift * kVisible)), 0)) whole |= any_small_row(V, r, t0, m, lane);
+  if (__builtin_expect(whole, 0)) {
     o[0] = o[1] = zero16();
     m_run = -INFINITY;
     l_run = 0.f;
@@ -451,13 +541,13 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
       val.put(x, lane);
       keep_order();
       const SlotWindow mask = r.mask(t, hl);
-      probs(s, mask);
+      probs(s, mask, 1.f);
       accumulate_special(o, x, m, hl, s, mask);
       keep_order();
     }
+    l_tot = half_sum(l_run);
   }
   // the wavefronts' maxima and sums, then their sum of O scaled to the common maximum
-  const float l_tot = half_sum(l_run);
   if (hl == 0) stat[wave][m] = make_float2(m_run, l_tot);
   __syncthreads();
   // (a wavefront without a maximum has a sum of zero, or of NaN if it met scores of NaN only)
@@ -471,7 +561,17 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
     l_all += ml.y * weight(ml.x, m_all);
   }
   if (wave == 0 && hl == 0 && r.valid) a.lse[bh + r.pos] = (m_all * sc + __builtin_amdgcn_logf(l_all)) * kLn2;
-  const float mul = weight(m_run, m_all) / l_all;
+  float mul = weight(m_run, m_all) / l_all;
+  if (!whole) {  // (where the product of both would be too small, one after the other)
+    if (__builtin_expect(__any(mul < kLeast), 0))
+#pragma unroll
+      for (int c = 0; c < 16; ++c) {
+        o[0][c] *= 1.f / kLift;
+        o[1][c] *= 1.f / kLift;
+      }
+    else
+      mul *= 1.f / kLift;
+  }
   store_sum(o, mul, lds, row_tok, O, wave, m, hl);
 }
 
@@ -484,7 +584,21 @@ struct BwdLds {
   char own[2 * kPlanes];        // Q, dO; or K, V
   float stat[kWaves][2][kRows]; // dK/dV, of the wavefront's tile: lse in base 2, delta
   int row_tok[kRows];
+  int inexact[kWaves];          // Q; or K
 };
+
+// delta = rowsum(dO * O) of the token of row m, in the second pass: lanes m and m + 32 have half of the dims each.
+__device__ __forceinline__ float row_delta(const float* dO, const float* O, int tok, int hl) {
+  f32x4 g[8], o[8];
+  load_row(g, dO, tok, hl);
+  load_row(o, O, tok, hl);
+  float d = 0.f;
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) d = fmaf(g[j][e], o[j][e], d);
+  return half_sum(d);
+}
 
 __device__ __forceinline__ void dq_quarter(const AttnArgs& a, const Quarter& q, BwdLds& shared) {
   char *const lds = shared.tiles, *const own = shared.own;
@@ -495,7 +609,7 @@ __device__ __forceinline__ void dq_quarter(const AttnArgs& a, const Quarter& q, 
   const float* Q = static_cast<const float*>(a.q) + bh * kD;
   const float* K = static_cast<const float*>(a.k) + bh * kD;
   const float* V = static_cast<const float*>(a.v) + bh * kD;
-  const float* dO = static_cast<const float*>(a.dout) + bh * kD;
+  const float *dO = static_cast<const float*>(a.dout) + bh * kD, *O = static_cast<const float*>(a.o) + bh * kD;
   float* dQ = static_cast<float*>(a.dq) + bh * kD;
   if (q.w.u.kind == UNIT_PAD) {
     float* const outs[1] = {dQ};
@@ -506,7 +620,8 @@ __device__ __forceinline__ void dq_quarter(const AttnArgs& a, const Quarter& q, 
   if (tid < kRows) row_tok[tid] = r.valid ? r.pos : -1;
   const int t0 = (wave + q.turn) & (kWaves - 1);
   int tok = r.token(t0, m), tok_next = r.token(t0 + kWaves, m);
-  const float lse2 = a.lse[bh + r.pos] * kLog2e, sc = a.scale * kLog2e, delta = a.delta[bh + r.pos];
+  const float lse2 = a.lse[bh + r.pos] * kLog2e, sc = a.scale * kLog2e;
+  float delta = a.delta[bh + r.pos];
   TileRegs key, val;
   {  // owned Q and dO rows to LDS
     OwnedRows g, qr;
@@ -517,6 +632,7 @@ __device__ __forceinline__ void dq_quarter(const AttnArgs& a, const Quarter& q, 
     keep_order();
     g.split(own + kPlanes, wave, lane);
     qr.split(own, wave, lane);
+    shared.inexact[wave] = __any(qr.suspect()) && qr.inexact();
   }
   __syncthreads();
   char* const tile = lds + wave * kPlanes;
@@ -525,11 +641,12 @@ __device__ __forceinline__ void dq_quarter(const AttnArgs& a, const Quarter& q, 
   const TransposedAddr tile_cols(lanes, lds_addr(tile));
 
   f32x16 dq[2] = {zero16(), zero16()};
-  auto dscores = [&](f32x16& s, const f32x16& dp, const SlotWindow& mask) {  // S^T -> dS^T
+  auto dscores = [&](f32x16& s, const f32x16& dp, const SlotWindow& mask, float lift) {  // S^T -> dS^T
 #pragma unroll
     for (int c = 0; c < 16; ++c)
-      s[c] = mask.in(c) ? __builtin_amdgcn_exp2f(fmaf(s[c], sc, -lse2)) * (dp[c] - delta) : 0.f;
+      s[c] = mask.in(c) ? __builtin_amdgcn_exp2f(fmaf(s[c], sc, -lse2)) * fmaf(dp[c], lift, -delta * lift) : 0.f;
   };
+  float most = 0.f;  // of |dS|
   for (int t = t0; t < r.n; t += kWaves) {
     const int tok_after = r.token(t + 2 * kWaves, m);
     val.split(tile, lane);
@@ -541,13 +658,19 @@ __device__ __forceinline__ void dq_quarter(const AttnArgs& a, const Quarter& q, 
     key.load(K, tok_next, lane);
     keep_order();
     f32x16 s = contract<0>(tile_rows, own_rows);         // S^T  = K Q^T
-    dscores(s, dp, r.mask(t, hl));
+    dscores(s, dp, r.mask(t, hl), kLift);
+    most_of(most, s);
     accumulate(dq, tile_cols, s);                   // dQ^T += K^T dS^T
     keep_order();
     tok_next = tok_after;
   }
-  if (__builtin_expect(any_special(dq), 0)) {
+  float mul = a.scale * (1.f / kLift);
+  bool whole = any_special(dq) || __builtin_amdgcn_readfirstlane(any_of(shared.inexact)) || mul < kLeast || a.scale > kLargeScale;
+  if (__builtin_expect(any_below(dq, half_max(most) * (kMostRows * kVisible)), 0)) whole |= any_small_row(K, r, t0, m, lane);
+  if (__builtin_expect(whole, 0)) {
     dq[0] = dq[1] = zero16();
+    mul = a.scale;
+    delta = row_delta(dO, O, r.pos, hl);
     float* const x = piece_of(lds, wave);
     for (int t = t0; t < r.n; t += kWaves) {
       tok = r.token(t, m);
@@ -564,13 +687,13 @@ __device__ __forceinline__ void dq_quarter(const AttnArgs& a, const Quarter& q, 
       keep_order();
       f32x16 s = contract(x, own, m, hl);
       const SlotWindow mask = r.mask(t, hl);
-      dscores(s, dp, mask);
+      dscores(s, dp, mask, 1.f);
       accumulate_special(dq, x, m, hl, s, mask);
       keep_order();
     }
   }
   __syncthreads();
-  store_sum(dq, a.scale, lds, row_tok, dQ, wave, m, hl);
+  store_sum(dq, mul, lds, row_tok, dQ, wave, m, hl);
 }
 
 // ======================================================================================
@@ -586,7 +709,7 @@ __device__ __forceinline__ void dkv_quarter(const AttnArgs& a, const Quarter& q,
   const float* Q = static_cast<const float*>(a.q) + bh * kD;
   const float* K = static_cast<const float*>(a.k) + bh * kD;
   const float* V = static_cast<const float*>(a.v) + bh * kD;
-  const float* dO = static_cast<const float*>(a.dout) + bh * kD;
+  const float *dO = static_cast<const float*>(a.dout) + bh * kD, *O = static_cast<const float*>(a.o) + bh * kD;
   float* dK = static_cast<float*>(a.dk) + bh * kD;
   float* dV = static_cast<float*>(a.dv) + bh * kD;
   if (q.w.u.kind == UNIT_PAD) {
@@ -599,7 +722,7 @@ __device__ __forceinline__ void dkv_quarter(const AttnArgs& a, const Quarter& q,
   const int t0 = (wave + q.turn) & (kWaves - 1);
   int tok = r.token(t0, m), tok_next = r.token(t0 + kWaves, m);
   const float *lse = a.lse + bh, *delta = a.delta + bh;
-  float row_lse = lse[tok], row_delta = delta[tok];  // of tile row m
+  float row_lse = lse[tok], row_d = delta[tok];  // of tile row m
   TileRegs qry, grad;
   {
     OwnedRows k_rows, v_rows;
@@ -610,6 +733,7 @@ __device__ __forceinline__ void dkv_quarter(const AttnArgs& a, const Quarter& q,
     keep_order();
     k_rows.split(own, wave, lane);
     v_rows.split(own + kPlanes, wave, lane);
+    shared.inexact[wave] = __any(k_rows.suspect()) && k_rows.inexact();
   }
   __syncthreads();
   char* const tile = lds + wave * kPlanes;
@@ -623,12 +747,12 @@ __device__ __forceinline__ void dkv_quarter(const AttnArgs& a, const Quarter& q,
   auto put_stat = [&]() {
     if (hl == 0) {
       my_stat[m] = row_lse * kLog2e;
-      my_stat[kRows + m] = row_delta;
+      my_stat[kRows + m] = row_d;
     }
   };
   // S -> P, dP -> dS.  (A pair outside the pattern has P = 0 and so dS = 0, unless a value is not finite: then dS is
   // masked as well, in the second pass.)
-  auto dscores = [&](f32x16& s, f32x16& dp, const SlotWindow& mask, bool mask_ds) {
+  auto dscores = [&](f32x16& s, f32x16& dp, const SlotWindow& mask, float lift, bool mask_ds) {
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const f32x4 l = *reinterpret_cast<const f32x4*>(my_stat + 8 * g + 4 * hl);
@@ -636,12 +760,13 @@ __device__ __forceinline__ void dkv_quarter(const AttnArgs& a, const Quarter& q,
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int c = 4 * g + e;
-        s[c] = mask.in(c) ? __builtin_amdgcn_exp2f(fmaf(s[c], sc, -l[e])) : 0.f;
+        s[c] = mask.in(c) ? __builtin_amdgcn_exp2f(fmaf(s[c], sc, -l[e])) * lift : 0.f;
         dp[c] = s[c] * (dp[c] - d[e]);
         if (mask_ds) dp[c] = mask.in(c) ? dp[c] : 0.f;
       }
     }
   };
+  float most = 0.f;  // of |dS|
   for (int t = t0; t < r.n; t += kWaves) {
     const int tok_after = r.token(t + 2 * kWaves, m);
     // (One tile of planes at a time, so that two workgroups fit a CU; the gradients are split twice for it.)
@@ -654,9 +779,10 @@ __device__ __forceinline__ void dkv_quarter(const AttnArgs& a, const Quarter& q,
     qry.load(Q, tok_next, lane);
     keep_order();
     f32x16 s = contract<0>(tile_rows, own_rows);   // S  = Q K^T
-    dscores(s, dp, r.mask(t, hl), false);
+    dscores(s, dp, r.mask(t, hl), kLift, false);
+    most_of(most, dp);
     row_lse = lse[tok_next];
-    row_delta = delta[tok_next];
+    row_d = delta[tok_next];
     accumulate(dk, tile_cols, dp);            // dK^T += Q^T dS
     keep_order();
     grad.split(tile, lane);
@@ -666,13 +792,19 @@ __device__ __forceinline__ void dkv_quarter(const AttnArgs& a, const Quarter& q,
     keep_order();
     tok_next = tok_after;
   }
-  if (__builtin_expect(any_special(dk) || any_special(dv), 0)) {
+  float mul_k = a.scale * (1.f / kLift), mul_v = 1.f / kLift;
+  bool whole = any_special(dk) || any_special(dv) || __builtin_amdgcn_readfirstlane(any_of(shared.inexact)) || mul_k < kLeast ||
+               a.scale > kLargeScale;
+  if (__builtin_expect(any_below(dk, half_max(most) * (kMostRows * kVisible)), 0)) whole |= any_small_row(Q, r, t0, m, lane);
+  if (__builtin_expect(whole, 0)) {
+    mul_k = a.scale;
+    mul_v = 1.f;
     dk[0] = dk[1] = dv[0] = dv[1] = zero16();
     float* const x = piece_of(lds, wave);
     for (int t = t0; t < r.n; t += kWaves) {
       tok = r.token(t, m);
       row_lse = lse[tok];
-      row_delta = delta[tok];
+      row_d = row_delta(dO, O, tok, hl);
       f32x4 own[8];
       load_row(own, V, r.pos, hl);
       grad.load(dO, tok, lane);
@@ -687,7 +819,7 @@ __device__ __forceinline__ void dkv_quarter(const AttnArgs& a, const Quarter& q,
       keep_order();
       f32x16 s = contract(x, own, m, hl);
       const SlotWindow mask = r.mask(t, hl);
-      dscores(s, dp, mask, true);
+      dscores(s, dp, mask, 1.f, true);
       accumulate_special(dk, x, m, hl, dp, mask);
       keep_order();
       grad.put(x, lane);
@@ -697,9 +829,9 @@ __device__ __forceinline__ void dkv_quarter(const AttnArgs& a, const Quarter& q,
     }
   }
   __syncthreads();
-  store_sum(dk, a.scale, lds, row_tok, dK, wave, m, hl);
+  store_sum(dk, mul_k, lds, row_tok, dK, wave, m, hl);
   __syncthreads();
-  store_sum(dv, 1.f, lds, row_tok, dV, wave, m, hl);
+  store_sum(dv, mul_v, lds, row_tok, dV, wave, m, hl);
 }
 
 // ======================================================================================
@@ -710,7 +842,19 @@ __device__ __forceinline__ void dkv_quarter(const AttnArgs& a, const Quarter& q,
 // fill each other's; delta, which both need, comes from a launch of its own and is not computed by dQ.  us, backward as
 // dQ and dK/dV and now: one sequence of 128, 4 heads 22.7 -> 15.3; 12 heads, one of 512 37.7 -> 25.6, of 1024 66.8 -> 42.7,
 // 4 x 512 48.4 -> 46.0, 8 x 512 82.2 -> 78.0, 16 x 1024 331 -> 328.  (All of dK/dV first: 16.5, 25.9, 43.7, 46.8, 79.7, 330.)
+//
+// delta is NaN, which sends those that meet the row into their second pass (they compute it themselves there), where dO has
+// a small value, and where it is so small against dO that dP - delta could show what dP loses with small values of V:
+// at most kLost times the sum of |dO|, so 2^-35 of delta where delta is at least 2^-84 times the largest |dO|.
 constexpr int kDeltaRows = 64;   // of a workgroup, 16 lanes of four dims each
+template <int kDpp>
+__device__ __forceinline__ void row_reduce(float& sum, float& most) {
+  auto other = [](float x) {
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), kDpp, 0xf, 0xf, true));
+  };
+  sum += other(sum);
+  most = fmaxf(most, other(most));
+}
 __global__ __launch_bounds__(kThreads) void delta_f32_kernel(AttnArgs a) {
   const size_t rows = (size_t)a.B * a.H * a.N, first = (size_t)blockIdx.x * kDeltaRows + (threadIdx.x >> 4);
   const int piece = threadIdx.x & 15;
@@ -723,10 +867,15 @@ __global__ __launch_bounds__(kThreads) void delta_f32_kernel(AttnArgs a) {
   }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    float d = g[i].x * o[i].x + g[i].y * o[i].y + g[i].z * o[i].z + g[i].w * o[i].w;
+    float d = g[i].x * o[i].x + g[i].y * o[i].y + g[i].z * o[i].z + g[i].w * o[i].w, most = 0.f;
 #pragma unroll
-    for (int e = 8; e >= 1; e >>= 1) d += __shfl_xor(d, e, 64);
-    if (piece == 0 && first + 16 * i < rows) a.delta[first + 16 * i] = d;
+    for (int e = 0; e < 4; ++e) most = is_small(g[i][e]) ? INFINITY : fmaxf(most, fabsf(g[i][e]));
+    row_reduce<0xb1>(d, most);   // lanes ^ 1, ^ 2, and the other half of eight and of sixteen
+    row_reduce<0x4e>(d, most);
+    row_reduce<0x141>(d, most);
+    row_reduce<0x140>(d, most);
+    const unsigned bits = fabsf(d) < most * 0x1p-84f ? 0x7fc00000u : __float_as_uint(d);
+    if (piece == 0 && first + 16 * i < rows) reinterpret_cast<unsigned*>(a.delta)[first + 16 * i] = bits;
   }
 }
 __global__ __launch_bounds__(kThreads, 2) void bwd_f32_kernel(AttnArgs a, unsigned first) {

@@ -571,11 +571,14 @@ def test_backward_of_a_batch_in_parts(B, N, H, n_global):
             assert torch.equal(x, y[part]), (part, name)
 
 
-@pytest.mark.parametrize("values", ["ordinary", "wide", "no split"])
+@pytest.mark.parametrize("values", ["ordinary", "wide", "no split", "small q", "small k", "small v", "small do",
+                                    "small products", "small probabilities", "zeros"])
 def test_f32_products_from_splits(values):
-    """fp32 products are formed from three bf16 parts: as good as fp32 over 120 binary orders of magnitude, and for a value
-    above the largest bf16, which has no such parts.  Bounds: a product and its share of an fp32 sum are within a few
-    2^-24 of their size, P within 2^-24 times the exponents of a score of a few units, of its own."""
+    """fp32 products are formed from three bf16 parts: as good as fp32 over 120 binary orders of magnitude, for a value
+    above the largest bf16, which has no such parts, and for values whose parts would not be normal numbers (an input, or
+    P and dS, of 2^-120 keeps 14 bits in parts of bf16, none below 2^-126).  Bounds: a product and its share of an fp32 sum
+    are within a few 2^-24 of their size, P within 2^-24 times the exponents of a score of a few units, of its own; where
+    scores spread by 82 (118 in base 2), a score and the log-sum-exp are within a few 2^-18, and with them P."""
     from paper_2109_04312_amd import mate
     n_global, rows, cols, cell, N = 33, 9, 5, 4, 230
     st = synth._stack([synth.flatten_table(N, n_global, rows, cols, np.full(rows * cols, cell))])
@@ -586,6 +589,21 @@ def test_f32_products_from_splits(values):
         v, do = (x * np.exp2(rng.integers(-60, 61, (1, 2, N, 1))).astype(np.float32) for x in (v, do))
     elif values == "no split":
         v[0, :, at], do = np.float32(3.4e38), do * np.float32(2.0 ** -40)
+    elif values in ("small q", "small k"):       # (scores are as ever)
+        sign = -1 if values == "small q" else 1
+        q, k = q * np.float32(2.0 ** (120 * sign)), k * np.float32(2.0 ** (-120 * sign))
+    elif values == "small v":
+        v = v * np.float32(2.0 ** -120)
+    elif values == "small do":
+        do = do * np.float32(2.0 ** -120)
+    elif values == "small products":             # dP and dS
+        v, do = v * np.float32(2.0 ** -60), do * np.float32(2.0 ** -60)
+    elif values == "small probabilities":        # some keys take it all and have nothing to give
+        q, k = q * np.float32(0.3), k * np.float32(0.3)
+        q[..., 0], k[..., 0] = 32, 0
+        k[:, :, ::5, 0], v[:, :, ::5] = 20.5, 0
+    elif values == "zeros":
+        v[..., ::3], do[:, :, ::2], k[:, :, 40:80], q[..., 5] = 0, 0, 0, 0
     w = synth.Workload("splits", "f32", st, np.array([ROW, COL], np.uint8), q, k, v, do, 0.125)
     ref = pairwise_reference(w, (q, k, v, do))
     dev = [hp.to_dev(x, "f32") for x in (q, k, v, do)]
@@ -601,7 +619,7 @@ def test_f32_products_from_splits(values):
         for name, s in size.items():
             ratio = np.abs(got[name][b, h].double().cpu().numpy() - d[name]) / np.maximum(s, 1e-300)
             print(values, h, name, "max error %.1e of its size" % ratio.max(), flush=True)
-            assert ratio.max() <= 32 * 2.0 ** -24, (name, h)
+            assert ratio.max() <= (512 if values == "small probabilities" else 32) * 2.0 ** -24, (name, h)
 
 
 @pytest.mark.parametrize("n_global,N", [(1, 130), (32, 160), (32, 200), (31, 321), (33, 321), (32, 700), (7, 1500)])
