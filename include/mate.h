@@ -330,7 +330,8 @@ mate_status mate_out_project(const void* o, const void* w_o, const float* bias,
  *   workspace   mate_project_bwd_workspace_bytes(B, N, H, E) bytes (partial sums of the weight
  *               gradient)
  *   t, H, E     as for the forward calls
- * Asynchronous on `stream`; deterministic (partial sums are added in a fixed order, no floating-point atomics).
+ * Asynchronous on `stream`; deterministic (partial sums are added in a fixed order, no floating-point atomics).  dw and
+ * dbias are the same bits with and without dx / d_o up to B * ceil(N / 64) = 64; beyond, the order of their sums may differ.
  */
 size_t mate_project_bwd_workspace_bytes(int B, int N, int H, int E);
 mate_status mate_qkv_project_bwd(const void* x, const void* w_qkv, const uint8_t* flags,

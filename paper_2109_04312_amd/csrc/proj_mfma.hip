@@ -685,12 +685,7 @@ __device__ __forceinline__ void wgrad_tile(WgradArgs a, char* lds, int block) {
   for (int i = 0; i < S::kFA; ++i)
 #pragma unroll
     for (int j = 0; j < S::kFB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  f32x4 chains[S::kFA][S::kFB];
-  if constexpr (kChain > 0)
-#pragma unroll
-    for (int i = 0; i < S::kFA; ++i)
-#pragma unroll
-      for (int j = 0; j < S::kFB; ++j) chains[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 chains[S::kFA][S::kFB];  // (the first chain sets it: zeroing it took short ranges 0.3 us)
   float bias_acc[S::kFB];
 #pragma unroll
   for (int j = 0; j < S::kFB; ++j) bias_acc[j] = 0.f;
@@ -743,17 +738,18 @@ __device__ __forceinline__ void wgrad_tile(WgradArgs a, char* lds, int block) {
                                         for (int y = 0; y < S::kFA; ++y)
 #pragma unroll
                                           for (int j = 0; j < S::kFB; ++j) {
-                                            chains[y][j] += acc[y][j];
+                                            chains[y][j] = it == kChain ? acc[y][j] : chains[y][j] + acc[y][j];
                                             acc[y][j] = f32x4{0.f, 0.f, 0.f, 0.f};
                                           }
                                   });
   }
   if (S::kAlternate && group == 0) barrier_no_fence();
   if constexpr (kChain > 0)
+    if (i_end - i_begin > kChain * S::kGroups)
 #pragma unroll
-    for (int i = 0; i < S::kFA; ++i)
+      for (int i = 0; i < S::kFA; ++i)
 #pragma unroll
-      for (int j = 0; j < S::kFB; ++j) acc[i][j] += chains[i][j];
+        for (int j = 0; j < S::kFB; ++j) acc[i][j] += chains[i][j];
   f32x4 sum[S::kFA][S::kOutB];
   add_groups<S>(acc, sum, lds, group, wave, lane);
 
@@ -970,6 +966,7 @@ double end_of_both(int first, double t1, long second, double t2) {
 
 struct BwdPlan {
   double cost;       // us
+  double wgrad;      // of that, until dW is there
   int ranges;        // of token blocks; 0: not in one launch
   bool large;        // the larger or the smaller tiles of the product
   size_t bias_off, words_off, total;
@@ -984,23 +981,33 @@ void offer_bwd(BwdPlan& best, ProjArgs a, bool large, int tiles, int blocks, int
   const double cost = (ranges > 1 ? 1.16 : 1.0) * (4.4 + end_of_both(first, t1, a.tile_blocks, per_step * (a.K / 64) + rest));
   if (cost < best.cost) {
     best.cost = cost;
+    best.wgrad = t1;
     best.ranges = ranges;
     best.large = large;
   }
 }
-// Where the partial sums of dW's ranges lie in the workspace.
-void lay_out(BwdPlan& p, const WgradArgs& w, int ranges) {
+// Where the partial sums of dW's ranges lie in the workspace, for `tiles` tiles of dW.
+void lay_out(BwdPlan& p, const WgradArgs& w, int ranges, int tiles) {
   p.bias_off = align256((size_t)ranges * w.F * w.E * 4);
   p.words_off = p.bias_off + align256((size_t)ranges * w.F * 4);
-  p.total = p.words_off + (size_t)wgrad_tiles128(w.F, w.E) * kMaxRanges * 8 + 16;   // (the caller's address may be any)
+  p.total = p.words_off + (size_t)tiles * kMaxRanges * 8 + 16;   // (the caller's address may be any)
+}
+void place_ranges(WgradArgs& w, const BwdPlan& p, char* ws) {
+  ws += -reinterpret_cast<uintptr_t>(ws) & 15;
+  w.blocks_per_seq = (w.N + 63) / 64;
+  w.splits = p.ranges;
+  w.per_split = w.B * w.blocks_per_seq;
+  w.part = reinterpret_cast<float*>(ws);
+  w.part_bias = reinterpret_cast<float*>(ws + p.bias_off);
+  w.arrived = reinterpret_cast<unsigned long long*>(ws + p.words_off);
 }
 // `groups`: of the product's shape if it were alone; `room`: bytes of the workspace, which are those that two launches need.
 BwdPlan plan_bwd(const WgradArgs& w, const ProjArgs& a, int groups, size_t room) {
-  BwdPlan p = {1e30, 0, false, 0, 0, 0};
+  BwdPlan p = {1e30, 0, 0, false, 0, 0, 0};
   const int tiles = wgrad_tiles128(w.F, w.E), blocks = w.B * ((w.N + 63) / 64);
   if (blocks > kOneLaunchBlocks) return p;
   for (int ranges = 1; ranges <= kMaxRanges && tiles * ranges <= 256 && (ranges == 1 || blocks >= 8 * ranges); ++ranges) {
-    lay_out(p, w, ranges);
+    lay_out(p, w, ranges, tiles);
     if (ranges > 1 && p.total > room) break;
     if (groups == 2) {
       offer_bwd<Both128x2>(p, a, true, tiles, blocks, ranges, 0.38, 3.1);
@@ -1010,21 +1017,14 @@ BwdPlan plan_bwd(const WgradArgs& w, const ProjArgs& a, int groups, size_t room)
       offer_bwd<Both128>(p, a, false, tiles, blocks, ranges, 0.75, 5.0);
     }
   }
-  lay_out(p, w, p.ranges);
+  lay_out(p, w, p.ranges, tiles);
   return p;
 }
 
 template <class S, bool kHeadTok>
 hipError_t launch_bwd(WgradArgs w, ProjArgs a, const BwdPlan& p, char* ws, int wgrad_id, int proj_id, hipStream_t stream) {
   deal_tiles<S>(a);
-  if (!a.out[0]) a.tile_blocks = 0;
-  ws += -reinterpret_cast<uintptr_t>(ws) & 15;
-  w.blocks_per_seq = (w.N + 63) / 64;
-  w.splits = p.ranges;
-  w.per_split = w.B * w.blocks_per_seq;
-  w.part = reinterpret_cast<float*>(ws);
-  w.part_bias = reinterpret_cast<float*>(ws + p.bias_off);
-  w.arrived = reinterpret_cast<unsigned long long*>(ws + p.words_off);
+  place_ranges(w, p, ws);
   const int w_blocks = (wgrad_tiles128(w.F, w.E) * p.ranges + 7) / 8 * 8;  // (whole rounds of XCDs, so the products' tiles are dealt as ever)
   constexpr int kLds = std::max(S::kLds, Wgrad128::kLds);
   const hipError_t e = allow_lds<&proj_bwd_kernel<S, kHeadTok>>(kLds);
@@ -1034,22 +1034,61 @@ hipError_t launch_bwd(WgradArgs w, ProjArgs a, const BwdPlan& p, char* ws, int w
   return hipGetLastError();
 }
 
+// dW alone, in the same bits: the same ranges, groups and chains for each element, in tiles small enough that
+// they spread over the chip, which no product fills.  The smallest tile whose workgroups are one round; us for 128 x 128 (as
+// beside a product), 128 x 64 and 64 x 64: 512 wide, 512 tokens 11.1, 8.6, 8.1, 2048 tokens in two ranges 19.8, 15.6,
+// 15.6; 768 wide, 512 tokens 11.6, 9.5, 10.4, 8 x 512 36.4, 29.1, 30.1; with more than 128 workgroups of 128 x 128, 16 to
+// 64 blocks each, 23.2, 34.0, 36.2.
+using Wgrad64 = Shape<2, 1, 2, 2, 2, 1, 2>;
+using Wgrad64x64 = Shape<1, 1, 2, 2, 2, 1, 2>;
+template <class S>
+__global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void proj_wgrad_alone_kernel(WgradArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  wgrad_tile<S, kOneLaunchBlocks, kOneLaunchChain, true>(a, lds, blockIdx.x);
+}
+template <class S>
+hipError_t launch_wgrad_alone(WgradArgs w, const BwdPlan& p, char* ws, int kernel_id, hipStream_t stream) {
+  place_ranges(w, p, ws);
+  const hipError_t e = allow_lds<&proj_wgrad_alone_kernel<S>>(S::kLds);
+  if (e != hipSuccess) return e;
+  const int tiles = ((w.F + S::kRowsB - 1) / S::kRowsB) * ((w.E + S::kRowsA - 1) / S::kRowsA);
+  ProfileScope prof(kernel_id, stream);
+  hipLaunchKernelGGL(proj_wgrad_alone_kernel<S>, dim3((tiles * p.ranges + 7) / 8 * 8), dim3(S::kThreads), S::kLds, stream, w);
+  return hipGetLastError();
+}
+hipError_t run_wgrad_alone(const WgradArgs& w, BwdPlan p, char* ws, size_t room, int kernel_id, hipStream_t stream) {
+  const int tiles = wgrad_tiles128(w.F, w.E);
+  int cut = 4;   // tiles made of one
+  for (;; cut /= 2) {
+    lay_out(p, w, p.ranges, tiles * cut);
+    if (cut == 1 || (tiles * p.ranges * cut <= 256 && (p.ranges == 1 || p.total <= room))) break;
+  }
+  const auto launch = cut == 4 ? launch_wgrad_alone<Wgrad64x64> : cut == 2 ? launch_wgrad_alone<Wgrad64> : launch_wgrad_alone<Wgrad128>;
+  return launch(w, p, ws, kernel_id, stream);
+}
+
 // dW (unless w.out is null) and the other gradient (unless a.out[0] is).  One launch if these costs say that it is
 // faster.  They were fitted to 130 pairs of gradients (64 to 16384 tokens, 256 to 1536 wide) in up to fifteen forms;
 // over them the rule gains 16 %, loses 5 % at most and is 1.5 % behind the best form of each.  us, as two launches and
-// as one, gradients of QKV and of the output projection, 768 wide: 512 tokens 28.0 -> 18.1 and 18.8 -> 12.5, 2048 tokens
-// 33.9 -> 25.4 and 23.2 -> 19.3, 8 x 512 47.6 -> 41.2 and 27.8 -> 23.6, 3 x 1999 70.2 -> 56.4 and 33.6 -> 28.2;
-// 1024 wide, 1024 tokens 37.4 -> 26.9 and 24.3 -> 16.3, 4 x 1024 67.3 -> 63.8 and 36.3 -> 28.8.
-// The rule looks at the sizes alone, so that dW is the same bits whether or not the other gradient is wanted.  (Alone
-// it takes, us, 512 tokens 13.1 -> 12.0 and 12.5 -> 11.4, 2048 tokens 26.0 -> 23.1 and 19.8 -> 20.9, 8 x 512 32.2 -> 36.8
-// and 23.7 -> 23.8, 16 x 512 49.5 -> 65.0 and 26.5 -> 29.8; 1024 wide, 4 x 1024 44.4 -> 34.9 and 24.9 -> 26.2.)
+// as one, gradients of QKV and of the output projection, 768 wide: 512 tokens 27.1 -> 16.8 and 17.8 -> 11.1, 2048 tokens
+// 32.5 -> 23.5 and 22.4 -> 18.7, 8 x 512 44 -> 39.5 and 26.4 -> 23.0, 3 x 1999 64 -> 53.5 and 32 -> 27;
+// 1024 wide, 1024 tokens 35.8 -> 25 and 22.9 -> 15.3, 8 x 512 61 -> 60.5 and 35 -> 27.5.
+// dW alone follows the same rule up to kSameBits token blocks, so that it is the same bits whether or not the other gradient
+// is wanted (us, as two launches and as one: 512 tokens 11.1 -> 9.5 and 10.6 -> 7.8, 2048 tokens 23.0 -> 18.2 and 18.3 ->
+// 14.9, 8 x 512 27 -> 29.1 and 22.3 -> 18.8; at worst, 1024 wide at 2500 tokens, 25.5 -> 27.2).  Beyond, the form that is
+// faster beside a product can take 1.2 times as long without one (768 wide, 15 x 512 39 -> 48.3), and dW alone has two
+// unless its tiles of 128 x 128 nearly fill the chip (1024 wide, 3 x 1999 58.2 -> 53.6).
+constexpr int kSameBits = 64;
 template <bool kHeadTok>
 hipError_t run_bwd(const WgradArgs& w, ProjArgs a, char* ws, int wgrad_id, int proj_id, hipStream_t stream) {
   const WgradPlan alone = plan_wgrad(w.B, w.N, w.F, w.E);
   const ProjChoice product = choose_proj<kHeadTok, true>(a);
   const BwdPlan both = plan_bwd(w, a, product.groups, alone.total);
   const bool want_w = w.out, want_a = a.out[0];
-  if (want_w && both.cost < 13.4 + 0.66 * alone.cost + 0.88 * product.cost) {
+  const bool same = want_a || w.B * ((w.N + 63) / 64) <= kSameBits ||
+                    (wgrad_tiles128(w.F, w.E) * both.ranges > 128 && both.wgrad + 3 < alone.cost);
+  if (want_w && same && both.cost < 13.4 + 0.66 * alone.cost + 0.88 * product.cost) {
+    if (!want_a) return run_wgrad_alone(w, both, ws, alone.total, wgrad_id, stream);
     const auto launch = product.groups == 2 ? (both.large ? launch_bwd<Both128x2, kHeadTok> : launch_bwd<Both64x2, kHeadTok>)
                                             : (both.large ? launch_bwd<Both256, kHeadTok> : launch_bwd<Both128, kHeadTok>);
     return launch(w, a, both, ws, wgrad_id, proj_id, stream);

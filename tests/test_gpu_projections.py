@@ -323,3 +323,38 @@ def test_each_gradient_alone_is_the_same(B, N, H, E):
             torch.cuda.synchronize()
             assert all(torch.equal(u, v) for u, v in zip(both, captured)), replay
             call(ws=ws)                                 # eager work on the same words
+
+
+# dW without the other gradient: one token, tiles of 64 x 64 (one range, and several), 128 x 64 (the same) and 128 x 128, and
+# more token blocks than the form shared with the product is for
+@pytest.mark.parametrize("B,N,H,E", [(1, 1, 2, 128), (1, 2048, 4, 256), (3, 65, 12, 768), (2, 2047, 8, 512), (2, 200, 16, 1024),
+                                     (9, 541, 6, 384)])
+def test_weight_gradient_alone(B, N, H, E):
+    from paper_2109_04312_amd import mate
+    x, w_qkv, _, w_o, _, flags, o = make(N, B, N, H, E, pad_tail=N // 6)
+    rng = np.random.default_rng(N)
+    dq, dk, dv = (bf16(rng.standard_normal((B, H, N, 64))) for _ in range(3))
+    dy = bf16(rng.standard_normal((B, N, E)))
+    fl, n_tok = torch.from_numpy(flags).cuda(), max(1, int((flags != P).sum()))
+    _, rw, rb = orc.project_qkv_backward(x, w_qkv, flags, dq, dk, dv, H)
+    _, rwo, rbo = orc.project_out_backward(o, w_o, flags, dy)
+    ws = torch.full((mate.mate_project_bwd_workspace_bytes(B, N, H, E) // 4 + 1,), float("nan"), device="cuda").view(torch.uint8)
+    x, w_qkv, w_o, o, dq, dk, dv, dy = (dev(y) for y in (x, w_qkv, w_o, o, dq, dk, dv, dy))
+    for call, want_x, want_w, want_b in ((lambda **kw: mate.qkv_project_bwd(x, w_qkv, fl, dq, dk, dv, ws=ws, **kw), "want_dx", rw, rb),
+                                         (lambda **kw: mate.out_project_bwd(o, w_o, fl, dy, ws=ws, **kw), "want_do", rwo, rbo)):
+        _, dw, db = call(**{want_x: False})
+        both = call()
+        torch.cuda.synchronize()
+        close_f32(dw, want_w, "dw", n_tok)
+        close_f32(db, want_b, "dbias", n_tok)
+        if B * -(-N // 64) <= 64:
+            assert torch.equal(dw, both[1]) and torch.equal(db, both[2])
+        side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            _, dw2, db2 = call(**{want_x: False})
+        for replay in range(3):
+            dw2.fill_(float("nan")), db2.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(dw, dw2) and torch.equal(db, db2), replay
+            call()                                      # eager work on the same words
