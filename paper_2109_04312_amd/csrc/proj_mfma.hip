@@ -577,7 +577,8 @@ __device__ __forceinline__ unsigned long long pad_mask(const unsigned char* flag
 
 // kList: token blocks of one range at most.  kChain > 0: a group's accumulators go into a second set after every
 // kChain blocks, so that a long range is no less exact than the sum of short ones.
-// kMerge: the range of a tile that is done last adds them all (otherwise another launch does).
+// kMerge: the range of a tile that is done last adds them all (otherwise another launch does).  Partial sums of a range are
+// then whole tiles, one after the other, so F and E must be whole tiles as well.
 template <class S, int kList, int kChain, bool kMerge>
 __device__ __forceinline__ void wgrad_tile(WgradArgs a, char* lds, int block) {
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1005,7 +1006,9 @@ void place_ranges(WgradArgs& w, const BwdPlan& p, char* ws) {
 BwdPlan plan_bwd(const WgradArgs& w, const ProjArgs& a, int groups, size_t room) {
   BwdPlan p = {1e30, 0, 0, false, 0, 0, 0};
   const int tiles = wgrad_tiles128(w.F, w.E), blocks = w.B * ((w.N + 63) / 64);
-  if (blocks > kOneLaunchBlocks) return p;
+  // (Ranges that are added in the launch leave whole tiles and whole tiles' bias rows in space for F x E and F values: see
+  // wgrad_tile.  The callers allow no other sizes today.)
+  if (blocks > kOneLaunchBlocks || w.F % Wgrad128::kRowsB || w.E % Wgrad128::kRowsA) return p;
   for (int ranges = 1; ranges <= kMaxRanges && tiles * ranges <= 256 && (ranges == 1 || blocks >= 8 * ranges); ++ranges) {
     lay_out(p, w, ranges, tiles);
     if (ranges > 1 && p.total > room) break;
