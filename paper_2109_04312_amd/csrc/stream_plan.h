@@ -84,14 +84,29 @@ __host__ __device__ inline int joined(int n_chunks) { return (n_chunks + 1) >> 1
 
 // Small launches of the forward: a question-token owner of at most 32 rows is met by all four wavefronts, two tiles at a
 // time (OwnerSplit).  That takes the LDS of two workgroups, so a launch must fit the chip twice over: at most two units a
-// compute unit, with all the chunks that its sequences could have.  us, forward with 32 question tokens or fewer, one tile
-// and two at a time: one sequence, 12 heads, 450 tokens 9.4 -> 8.5, 512 10.0 -> 8.7, 700 11.1 -> 9.5, 2048 12.1 -> 11.3, 4 x
-// 512 10.3 -> 9.6, 8 x 512 12.5 -> 11.4; with more of them 0 to +2 %.
+// compute unit, with all the chunks that its sequences could have.  us, forward with 16 or 32 question tokens, one tile and
+// two at a time: 12 heads, one sequence of 450 9.8 -> 8.5, of 2048 12.7 -> 11.7, 4 x 512 10.1 -> 9.5, 8 x 512 12.9 -> 11.3, 9 x 384
+// 11.4 -> 10.7, 13 x 250 11.0 -> 10.8.  With more of them, which the host cannot know, two workgroups a compute unit cost 0 to
+// 2 % (2 x 1000 with 64 11.3 -> 11.6) except where the order below gains.  Where owners stream three or four tiles (N up to 256)
+// there is nothing to gain at fewer units (10 x 256 with 96 10.5 -> 10.75), and sequences of one tile of owners have pad
+// owners as well, a unit in three: 20 x 128 8.1 -> 10.0, where 13 to 16 gain from the order (8.1 -> 7.8).
 inline int forward_units(int B, int H, int N) { return B * H * (owner_slots(N) + (may_chunk(B, N) ? owner_slots(N) : 1)); }
-inline bool small_forward(int B, int H, int N) { return (long)B * H * owner_slots(N) <= 512 && forward_units(B, H, N) <= 512; }
-// Question-token units before column-head units there: where some compute units get two.  (8 x 512 with 60 question
-// tokens 12.9 -> 11.6, with 77 15.3 -> 13.5; 4 x 512 10.4 -> 10.9.)
-inline bool small_owners_first(int B, int H, int N) { return forward_units(B, H, N) > 256; }
+inline bool small_forward(int B, int H, int N) {
+  const long most = (long)B * H * owner_slots(N);
+  if (most > 512) return false;
+  const int units = forward_units(B, H, N);
+  if (owner_slots(N) == 1) return units > 256 && units <= 384;
+  if (owner_slots(N) == 2) return units > 416 && units <= 512;
+  return units <= 512;
+}
+// Question-token units before column-head units there: where whole owners make some compute units get two (8 x 512 with 64
+// question tokens 12.5 -> 11.4, with 96 14.8 -> 13.2, 10 x 384 with 96 12.9 -> 11.9; at 400 units and fewer 5 x 512 with 64 10.3 ->
+// 10.65, 8 x 300 with 96 10.0 -> 11.0; with two tiles of owners 12 x 250 with 16 9.8 -> 10.4), and where chunks do (one sequence of 1500, 160 question tokens 16.6 -> 14.6, 2 x 900 14.4 -> 13.7; with up to
+// 64 of them 1 to 4 % slower).
+inline bool small_owners_first(int B, int H, int N) {
+  if (owner_slots(N) == 1) return true;
+  return owner_slots(N) > 2 && forward_units(B, H, N) > (may_chunk(B, N) ? 256 : 416);
+}
 
 // Entry i of the head order.  A byte indexed by a run-time value would be fetched with a vector
 // load (a memory round trip at the start of every workgroup); the containing 32-bit word comes

@@ -629,3 +629,14 @@ def test_owners_that_all_wavefronts_meet_two_tiles_at_a_time(n_global, N):
     w = chunked_workload(N + n_global, 1, N, 2, n_global)
     got, _ = hp.run_hip(w, True)
     print(hp.report(hp.compare(got, hp.run_oracle(w, True, [(0, 0), (0, 1)]), w, w.name)), flush=True)
+
+
+@pytest.mark.parametrize("n_global,B,N,H", [(1, 72, 130, 2), (32, 70, 160, 2), (33, 70, 200, 2), (16, 65, 128, 2), (7, 50, 300, 2),
+                                            (32, 54, 300, 2), (8, 42, 500, 2), (60, 42, 500, 2)])
+def test_forward_of_launches_that_fill_half_of_the_chip(n_global, B, N, H):
+    """Such owners where a launch has one, two, three or four tiles of owners a sequence and about two units a compute unit,
+    in either order of its units."""
+    w = chunked_workload(N + n_global, B, N, H, n_global)
+    got, _ = hp.run_hip(w, False)
+    pairs = [(b, h) for b in (0, B // 2, B - 1) for h in range(H)]
+    print(hp.report(hp.compare(got, hp.run_oracle(w, False, pairs), w, w.name)), flush=True)
