@@ -351,7 +351,7 @@ mate_status mate_out_project_bwd(const void* o, const void* w_o, const uint8_t* 
  * call; the hook disarms itself once used.  The events are hipEvent_t handles passed as void*,
  * created with timing enabled and owned by the caller.  kernel = MATE_KERNEL_NONE disarms.
  * Up to 256 positions the backward of the dense-mask variant is one launch, and so are the bf16 backward (behind
- * a short one) up to B * H * ceil(N / 128) = 768 and both gradients of a projection of a small layer; both names mean
+ * a short one) where B * H * ceil(N / 128) is small (at most 768) and both gradients of a projection of a small layer; both names mean
  * that one then.  The kernels of MATE_F32 have no name.
  * The hook is per host thread.  The library keeps no other state that a caller can see: besides it a
  * counter that numbers the forward and projection backward calls of the process, the static array of

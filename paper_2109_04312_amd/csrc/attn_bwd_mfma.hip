@@ -380,14 +380,24 @@ __global__ __launch_bounds__(kThreads) void bwd_both_mfma_kernel(AttnArgs a) {
 
 }  // namespace
 
+// Does a launch leave so much of the chip idle that dQ and dK/dV run at once?  dQ has four workgroups on a compute unit
+// where the registers of dK/dV leave room for three, so two launches of one full round each are as fast as one of two.
+// Measured over 500 launches of 64 to 8192 tokens, full sequences and such with a third of padding, 12 and 16 heads.  By units of
+// 128 owners (a sequence's tiles and, per head, one for its question tokens) one launch is so many times as fast, mean and worst:
+// up to two tiles a sequence 1.05 and 1.00 at 1000 units, 1.04 and 0.99 at 1080, 1.00 and 0.94 beyond; three to six tiles 1.11 and
+// 0.99 at 640, 1.03 and 0.94 (12 x 512) at 760, 1.00 and 0.93 at 840, 0.98 and 0.92 at 1000; more tiles, where one long chain is
+// most of a launch, 1.09 and 1.04 at 760, 1.05 and 0.97 at 860 (768 tiles), 1.0 at 1500.
+static bool both_at_once(int B, int H, int N) {
+  const int T = owner_slots(N);
+  const long tiles = (long)B * H * T, units = tiles + (long)B * H;
+  return T > 6 ? tiles <= 768 : units <= (T > 2 ? 760 : 1080);
+}
+
 template <bool kJoin>
 static hipError_t launch_bwd(const AttnArgs& a, hipStream_t stream) {
   const dim3 grid(unit_grid(a.B, a.H, a.N, a.n_col)), block(kThreads);
   hipError_t e;
-  // Up to three units of 128 rows a compute unit.  (78 sizes; one launch is so many times as fast: at 768 units 0.98 to
-  // 1.09, at 1024 0.98 to 1.10, at 1152 0.96 to 1.17, at 1536 0.92 to 1.05, 16 ragged sequences of 4096 0.93.  dQ has four
-  // workgroups on a compute unit where the registers of dK/dV leave room for three.)
-  if ((long)a.B * a.H * owner_slots(a.N) <= 3 * 256) {
+  if (both_at_once(a.B, a.H, a.N)) {
     const size_t rows = (size_t)a.B * a.H * a.N;
     hipLaunchKernelGGL(bwd_delta_kernel, dim3((unsigned)((rows + kDeltaRows - 1) / kDeltaRows)), block, 0, stream, a);
     e = hipGetLastError();
