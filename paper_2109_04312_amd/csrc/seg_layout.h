@@ -67,7 +67,8 @@ struct GlobalSplit {
 };
 // Tiles per chunk of a stream of n_st tiles, about.  In a launch that fills the chip a chunk is as long as the
 // column-head units beside it, and more chunks only mean more partial results.  In a small one the
-// question-token owners are the longest chain of tiles (about 0.75 us each) and shorter chunks shorten it; the
+// question-token owners are the longest chain of tiles (about 0.75 us each; small forwards have since met owners of at
+// most 32 rows two tiles at a time, fwd_small_kernel, which these figures do not know) and shorter chunks shorten it; the
 // merge loads four chunks at a time and takes a microsecond and a half for every further four, so four chunks it
 // is, and short streams stay whole.  Forward / training step in us, chunks of 16, of 6 up to 24 tiles and 8 above,
 // and four: one sequence of 1024 (17 tiles), 16 heads 14.4/50, 12.3/43, the same; of 2048 (24), 12 heads 18.8/68,

@@ -294,9 +294,9 @@ __device__ inline OwnedRow owned_row(const UnitPlan& u, const AttnArgs& a, int b
 // instruction (lane l holds 16-byte piece l & 7 of row (l >> 3) + 8 i), and pass through 4 KB of LDS of the wavefront's
 // own.  Operands loaded straight from global memory (lane m: 16 bytes of row m) touch 32 lines per instruction and
 // each line four times, and at the start of a launch every wavefront of a CU wants its 4 (forward), 8 (dK/dV) or 12
-// (dQ) such loads at once.  delta comes from the rows as they are loaded.  Training steps: 2 x 8192, 16 heads 199.9 -> 196.8
-// us, bucketed 145.2 -> 141.1, 32 x 512, 12 heads 114.0 -> 112.2, 16 ragged sequences of 4096 507.7 -> 500.7; single
-// sequences the same.
+// (dQ) such loads at once.  delta comes from the rows as they are loaded.  Training steps, us, four runs of each in turn: 2 x 8192,
+// 16 heads 196.9 -> 195.7 (runs of one side differ by 0.7 %), bucketed 138.5 -> 136.1, 8 x 2048 with long cells 169.9 -> 168.0,
+// 16 ragged sequences of 4096 554 -> 545, 32 x 512, 12 heads 106.9 -> 106.6; single sequences the same.
 struct OwnedTile {
   bf16x8 v[4];  // (an array of HIP's uint4 class ends up in scratch memory)
   // `pos`: lane m and m + 32 hold the token of row m; X wave-uniform
