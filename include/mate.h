@@ -183,8 +183,8 @@ mate_status mate_segments_export_windows(const void* segments, int B, int N, int
  *
  *   q, k, v     [B, H, N, D] of dtype t (bf16: accumulate and softmax in fp32, probabilities
  *               rounded to bf16 before multiplying V; f32: fp32 throughout, products from three bf16
- *               parts per value that hold its 24 bits: within 2^-25 of the product, and no input,
- *               probability or sum is rounded below fp32, whatever its size)
+ *               parts per value that hold its 24 bits: within 2^-24 of the product, 2^-27 rms, and
+ *               no input, probability or sum is rounded below fp32, whatever its size)
  *   segments    tables from mate_build_segments for the same (B, N)
  *   head_kind   HOST [H] uint8, MATE_HEAD_*
  *   scale       softmax scale, positive and finite (the appendix listing uses 1/sqrt(D));

@@ -3,9 +3,10 @@
 // Products are formed from splits (the published three-part bfloat16 scheme of Henry, Tang and Heinecke, 2019, "Leveraging
 // the bfloat16 artificial intelligence datatype for higher-precision computations"): x = x1 + x2 + x3 with bf16 parts of 8
 // significant bits each, which together hold all 24 bits of an fp32 value, and
-// x y = x1 y1 + (x1 y2 + x2 y1) + (x1 y3 + x2 y2 + x3 y1).  What is left out is below 2^-25 |x y|, less than an fp32
-// rounding of the sums it goes into.  Six v_mfma_f32_32x32x16_bf16 (32 cycles, 16 of the contraction)
-// take the place of eight v_mfma_f32_32x32x2_f32 (64 cycles, 2 of it): 192 cycles for 512.
+// x y = x1 y1 + (x1 y2 + x2 y1) + (x1 y3 + x2 y2 + x3 y1).  What is left out, x2 y3 + x3 y2 + x3 y3, is at most
+// (2^-24 + 2^-34) |x y| (x2 of 2^-8 and x3 of 2^-17 of the power of two below x, the most that rounding to nearest leaves) and
+// 2^-27.5 |x y| rms, where an fp32 rounding of the sum that it goes into is up to 2^-24 of that sum.
+// Six v_mfma_f32_32x32x16_bf16 (32 cycles, 16 of the contraction) take the place of eight v_mfma_f32_32x32x2_f32 (64 cycles, 2 of it): 192 cycles for 512.
 // Sums are fp32 as before, and fewer of them are rounded (a matrix instruction adds sixteen products at once).
 // (A value above the largest bf16, 3.39e38, has no such split, nor has an infinity or a NaN: see accumulate_special.  For
 // values below 2^-103 see kLeast.)

@@ -11,7 +11,7 @@
 //   pad     ceil(P / 1024) pad owners (zero fill)
 //   global  question-token owners.  Their streamed side is the whole sequence, so it is cut into
 //           chunks that run as separate units and leave partial results; the chunk that arrives
-//           last merges them (the dQ kernel's chunks are merged by the next kernel).
+//           last merges them (where dQ has a launch of its own, its chunks are merged by the next kernel).
 // Workgroup -> unit is arithmetic on the workgroup index plus one record read: no counters, no
 // atomics, no dependent loads.  Workgroup i serves queue i mod 8 (consecutive workgroups go to
 // consecutive XCDs, so a queue stays on one XCD and the units of one (sequence, head) pair
@@ -101,8 +101,9 @@ inline bool small_forward(int B, int H, int N) {
 }
 // Question-token units before column-head units there: where whole owners make some compute units get two (8 x 512 with 64
 // question tokens 12.5 -> 11.4, with 96 14.8 -> 13.2, 10 x 384 with 96 12.9 -> 11.9; at 400 units and fewer 5 x 512 with 64 10.3 ->
-// 10.65, 8 x 300 with 96 10.0 -> 11.0; with two tiles of owners 12 x 250 with 16 9.8 -> 10.4), and where chunks do (one sequence of 1500, 160 question tokens 16.6 -> 14.6, 2 x 900 14.4 -> 13.7; with up to
-// 64 of them 1 to 4 % slower).
+// 10.65, 8 x 300 with 96 10.0 -> 11.0; with two tiles of owners 12 x 250 with 16 9.8 -> 10.4), and
+// where chunks do (one sequence of 1500, 160 question tokens 16.6 -> 14.6, 2 x 900 14.4 -> 13.7; with up to 64 of them 1 to
+// 4 % slower).
 inline bool small_owners_first(int B, int H, int N) {
   if (owner_slots(N) == 1) return true;
   return owner_slots(N) > 2 && forward_units(B, H, N) > (may_chunk(B, N) ? 256 : 416);
@@ -403,8 +404,8 @@ __device__ inline void store_owned_rows(const f32x16 (*acc[kTensors])[2], const 
 //
 // Forward and dK/dV: the chunk of an owner tile that arrives last merges inside the same launch
 // (a finalize kernel of its own cost 4.8 us in the forward and 6.4 us in the backward at B = 2,
-// N = 8192, H = 16, nearly all of it the launch).  dQ: merged by the first workgroups of the dK/dV kernel, behind
-// the kernel boundary.
+// N = 8192, H = 16, nearly all of it the launch), and so does dQ's where all three gradients are one launch.  Where dQ has
+// one of its own: merged by the first workgroups of the dK/dV kernel, behind the kernel boundary.
 constexpr int kItemFloats = 16 * 64;  // one wavefront's accumulator of one dim block
 template <bool kShared>
 __device__ __forceinline__ void store_partial(const f32x16 acc[2], float mul, float* __restrict__ part, int wave, int lane) {

@@ -408,6 +408,29 @@ def test_chunks_in_pairs_where_many_heads_fill_the_chip(n_global, table, N, H):
             assert np.array_equal(x[0, h], x[0, first[int(hk[h])]]), (name, h)
 
 
+# a joined stream; two owner tiles of question tokens; a stream so long that its chunks are not joined
+@pytest.mark.parametrize("n_global,table,N,few,many", [(60, 950, 1024, 96, 128), (130, 1370, 1500, 64, 80), (64, 2500, 2600, 36, 40)])
+def test_chunks_in_pairs_with_gradients_at_once_and_one_after_the_other(n_global, table, N, few, many):
+    """Up to 768 units (heads times ceil(N / 128); `few` heads have 768 or 756, `many` 1024, 960 and 840) dQ and dK/dV are one
+    launch and dQ's chunks are merged by the last to arrive, beyond by the first workgroups of dK/dV's launch: the same bits.
+    Heads of a kind have the same inputs."""
+    cols, cell = 5, 10
+    cells = table // cell
+    st = synth._stack([synth.flatten_table(N, n_global, cells // cols, cols, np.full(cells // cols * cols, cell))])
+    pair = synth.draw_tensors(np.random.default_rng(N), 1, 2, N, 64, "bf16", 4)
+    first = {}
+    for H in (few, many):
+        hk = synth.half_row_half_col(H)
+        w = synth.Workload(f"pairs {N} {H}", "bf16", st, hk, *(np.ascontiguousarray(x[:, hk]) for x in pair), 0.125)
+        got, _ = hp.run_hip(w, True)
+        at = {int(kind): int(np.argmax(hk == kind)) for kind in (ROW, COL)}
+        first = first or {(name, kind): x[0, h] for name, x in got.items() for kind, h in at.items()}
+        for name, x in got.items():
+            for h in range(H):
+                assert np.array_equal(x[0, h], first[name, int(hk[h])]), (name, H, h)
+    print(hp.report(hp.compare(got, hp.run_oracle(w, True, [(0, h) for h in at.values()]), w, w.name)), flush=True)
+
+
 def chunked_workload(seed, B, N, H, n_global=80):
     """Sequences filled to the last position, whose question-token owners' streams are cut into several chunks."""
     rng = np.random.default_rng(seed)
@@ -423,8 +446,14 @@ def arrival_words(ws, B, H, N):
     return ws.view(torch.int64)[-B * H * ((N + 127) // 128):].view(B * H, -1)
 
 
-# chunks of 16 tiles (B N > 4096), short ones, short ones in pairs, and two owner tiles of question tokens
-CHUNKED = [(2, 2100, 4, 80), (1, 2100, 4, 80), (1, 1500, 64, 40), (1, 2000, 2, 200)]
+# Chunks of 16 tiles (B N > 4096), short ones, short ones in pairs, and two owner tiles of question tokens.  Units (B H
+# ceil(N / 128)) 136, 68, 768 and 32: dQ and dK/dV in one launch; the forward is fwd_small_kernel up to 512 (with question-token
+# owners of more than 32 rows, one tile at a time), fwd_mfma_kernel<., true> at 768.  Then, in this order: owners of at most
+# 32 rows, two tiles at a time (48 units); short chunks on fwd_mfma_kernel<true, false>, still one backward launch (576); chunks
+# of 16 tiles there, with dQ and dK/dV one after the other, dQ's chunks merged by dK/dV's first workgroups (1280); short
+# ones in pairs and one after the other (960).
+CHUNKED = [(2, 2100, 4, 80), (1, 2100, 4, 80), (1, 1500, 64, 40), (1, 2000, 2, 200),
+           (1, 1500, 4, 20), (1, 2000, 36, 60), (2, 5000, 16, 140), (1, 1500, 80, 40)]
 
 
 @pytest.mark.parametrize("B,N,H,n_global", CHUNKED)
