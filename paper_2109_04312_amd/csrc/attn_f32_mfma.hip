@@ -330,10 +330,11 @@ struct Quarter {
   int turn;  // which wavefront takes the first tile: the ones that get a tile more than the others
              // should not all sit on the same SIMD
 };
+template <bool kOwnersFirst>
 __device__ inline bool take_quarter(const AttnArgs& a, unsigned block, Quarter& q) {
   q.sub = ((block >> 3) + (block >> 5)) & 3;
   q.turn = block >> 5;
-  if (!take_unit<false, false>(a, ((block >> 5) << 3) | (block & 7), q.w)) return false;
+  if (!take_unit<kOwnersFirst, false>(a, ((block >> 5) << 3) | (block & 7), q.w)) return false;
   const UnitPlan& u = q.w.u;
   if (u.kind == UNIT_PAD) return true;
   // (a chunked question-token owner: its first unit streams everything, there are no partials here)
@@ -443,13 +444,14 @@ __device__ __forceinline__ void zero_pads(const Quarter& q, float* const (&out)[
 // ======================================================================================
 // forward
 // ======================================================================================
+template <bool kOwnersFirst>
 __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds[kWaves * kPlanes];
   __shared__ __attribute__((aligned(1024))) char own[kPlanes];
   __shared__ float2 stat[kWaves][kRows];
   __shared__ int row_tok[kRows], inexact[kWaves];
   Quarter q;
-  if (!take_quarter(a, blockIdx.x, q)) return;
+  if (!take_quarter<kOwnersFirst>(a, blockIdx.x, q)) return;
   const int tid = threadIdx.x, lane = tid & 63, m = lane & 31, hl = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const size_t bh = (size_t)q.w.bh * a.N;
@@ -884,15 +886,25 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_f32_kernel(AttnArgs a, unsign
   const unsigned block = first + blockIdx.x;
   Quarter q;
   // (32 workgroups are the quarters of eight units, one on each XCD)
-  if (!take_quarter(a, ((block >> 6) << 5) | (block & 31), q)) return;
+  if (!take_quarter<false>(a, ((block >> 6) << 5) | (block & 31), q)) return;
   if (block & 32) dq_quarter(a, q, lds);
   else dkv_quarter(a, q, lds);
 }
 
 }  // namespace
 
+// Question-token owners before column-head units in the forward: where quarters of units are more than the 512 that fit the
+// chip at once.  An owner streams the whole sequence alone, and one that starts in the second round ends long after
+// everything else.  us, after and before the columns: 12 heads, 8 x 512 31.4 -> 30.7 and (14 columns) 27.3 -> 25.3, 4 x 1024
+// 47.2 -> 43.5 and 40.3 -> 31.4, one sequence of 2048 53.8 -> 44.1, 2 x 1500 48.7 -> 36.0, 16 x 1024 132.6 -> 132.9; 8 heads, 2 x 2100
+// 77.1 -> 52.2 (66.6 with the fp32 instruction), one of 8192 301 -> 207.  Launches that fit: one of 512 14.6 -> 15.0, 2 x 512
+// 15.9 -> 16.1, one of 1024, 4 heads 24.9 -> 24.7.
+static bool owners_first(int B, int H, int N) { return 4l * B * H * (owner_slots(N) + 1) > 512; }
+
 hipError_t launch_fwd_f32(const AttnArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL(fwd_f32_kernel, dim3(4 * unit_grid(a.B, a.H, a.N, a.n_col)), dim3(kThreads), 0, stream, a);
+  const dim3 grid(4 * unit_grid(a.B, a.H, a.N, a.n_col)), block(kThreads);
+  if (owners_first(a.B, a.H, a.N)) hipLaunchKernelGGL(fwd_f32_kernel<true>, grid, block, 0, stream, a);
+  else hipLaunchKernelGGL(fwd_f32_kernel<false>, grid, block, 0, stream, a);
   return hipGetLastError();
 }
 

@@ -354,6 +354,15 @@ def test_f32_tile_edges(n_global, rows, cols, cell, N):
     check_workload(synth.Workload(f"f32 edges {N}", "f32", st, np.array([ROW, COL], np.uint8), q, k, v, do, 0.125), True)
 
 
+@pytest.mark.parametrize("B,N,H,n_global", [(16, 300, 2, 40), (17, 300, 2, 40), (33, 120, 2, 3), (4, 2100, 2, 140)])
+def test_f32_forward_in_either_order_of_units(B, N, H, n_global):
+    """A launch of more than 128 units (B H (ceil(N / 128) + 1): 128, 136, 132 and 144) starts its question-token owners before
+    the columns', a smaller one after them."""
+    w = chunked_workload(N, B, N, H, n_global, "f32")
+    got, _ = hp.run_hip(w, False)
+    print(hp.report(hp.compare(got, hp.run_oracle(w, False, [(b, h) for b in (0, B - 1) for h in range(H)]), w, w.name)), flush=True)
+
+
 @pytest.mark.parametrize("rise", [0, 12])
 @pytest.mark.parametrize("n_global,rows,cols,cell,N", [(1, 1, 1, 1, 2), (31, 3, 1, 32, 127), (32, 5, 2, 13, 170),
                                                        (33, 4, 3, 33, 440), (64, 2, 2, 65, 330), (65, 31, 2, 3, 260),
@@ -431,14 +440,14 @@ def test_chunks_in_pairs_with_gradients_at_once_and_one_after_the_other(n_global
     print(hp.report(hp.compare(got, hp.run_oracle(w, True, [(0, h) for h in at.values()]), w, w.name)), flush=True)
 
 
-def chunked_workload(seed, B, N, H, n_global=80):
+def chunked_workload(seed, B, N, H, n_global=80, dtype="bf16"):
     """Sequences filled to the last position, whose question-token owners' streams are cut into several chunks."""
     rng = np.random.default_rng(seed)
     cols, cell = 6, 5
     rows = -(-N // (cols * cell))
     st = synth._stack([synth.flatten_table(N, n_global, rows, cols, np.full(rows * cols, cell)) for _ in range(B)])
     hk = synth.half_row_half_col(H)
-    return synth.Workload(f"chunks{seed}", "bf16", st, hk, *synth.draw_tensors(rng, B, H, N, 64, "bf16", 4), 0.125)
+    return synth.Workload(f"chunks{seed}", dtype, st, hk, *synth.draw_tensors(rng, B, H, N, 64, dtype, 4), 0.125)
 
 
 def arrival_words(ws, B, H, N):
