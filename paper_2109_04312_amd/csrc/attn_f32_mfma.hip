@@ -341,7 +341,7 @@ __device__ inline bool take_quarter(const AttnArgs& a, unsigned block, Quarter& 
   if (u.part >= 0 && u.t_begin != 0) return false;
   if (u.t0 + kRows * q.sub >= u.own_count) return false;
   // Question-token owners stream the whole sequence and end last: they go first on a shared SIMD
-  // (their tiles took 7.8 us each beside two other wavefronts, 2.6 us of it their own).
+  // (with the fp32 instruction, beside two other wavefronts, their tiles took 7.8 us each, 2.6 us of it their own).
   if (u.kind == UNIT_GLOBAL) __builtin_amdgcn_s_setprio(3);
   return true;
 }
