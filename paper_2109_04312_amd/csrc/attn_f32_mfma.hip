@@ -893,13 +893,18 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_f32_kernel(AttnArgs a, unsign
 
 }  // namespace
 
-// Question-token owners before column-head units in the forward: where quarters of units are more than the 512 that fit the
-// chip at once.  An owner streams the whole sequence alone, and one that starts in the second round ends long after
-// everything else.  us, after and before the columns: 12 heads, 8 x 512 31.4 -> 30.7 and (14 columns) 27.3 -> 25.3, 4 x 1024
-// 47.2 -> 43.5 and 40.3 -> 31.4, one sequence of 2048 53.8 -> 44.1, 2 x 1500 48.7 -> 36.0, 16 x 1024 132.6 -> 132.9; 8 heads, 2 x 2100
-// 77.1 -> 52.2 (66.6 with the fp32 instruction), one of 8192 301 -> 207.  Launches that fit: one of 512 14.6 -> 15.0, 2 x 512
-// 15.9 -> 16.1, one of 1024, 4 heads 24.9 -> 24.7.
-static bool owners_first(int B, int H, int N) { return 4l * B * H * (owner_slots(N) + 1) > 512; }
+// Question-token owners before column-head units in the forward: where the quarters of table-token units are more than the 512
+// that fit the chip at once.  An owner streams the whole sequence alone, and one that starts in the second round ends long
+// after everything else.  us, after and before the columns: 12 heads, 4 x 1024 47.2 -> 43.5 and (14 columns) 40.3 -> 31.4, 8 x 512
+// 31.4 -> 30.7 and 27.3 -> 25.3, one sequence of 2048 53.8 -> 44.1, 2 x 1500 48.7 -> 36.0, 16 x 1024 132.6 -> 132.9; 8 heads, 2 x
+// 2100 77.1 -> 52.2 (66.6 with the fp32 instruction), one of 8192 301 -> 207.  Launches that fit: one of 512 14.6 -> 15.0, 2 x
+// 512 15.9 -> 16.1, one of 1000 24.6 -> 24.5.  With two or three tiles of owners a sequence the chain is short and most
+// of the workgroups in front are empty: from 1024 on (8 x 300 23.5 -> 23.1, 16 x 250 30.5 -> 29.7, but 6 x 232 12.0 -> 13.1, 4 x
+// 300 14.2 -> 15.1, 5 x 300 17.2 -> 17.7; one tile: 11 x 100 14.5 -> 14.2, 16 x 128 19.2 -> 19.0).
+static bool owners_first(int B, int H, int N) {
+  const int T = owner_slots(N);
+  return 4l * B * H * T > (T == 2 || T == 3 ? 1024 : 512);
+}
 
 hipError_t launch_fwd_f32(const AttnArgs& a, hipStream_t stream) {
   const dim3 grid(4 * unit_grid(a.B, a.H, a.N, a.n_col)), block(kThreads);

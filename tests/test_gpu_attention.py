@@ -354,10 +354,10 @@ def test_f32_tile_edges(n_global, rows, cols, cell, N):
     check_workload(synth.Workload(f"f32 edges {N}", "f32", st, np.array([ROW, COL], np.uint8), q, k, v, do, 0.125), True)
 
 
-@pytest.mark.parametrize("B,N,H,n_global", [(16, 300, 2, 40), (17, 300, 2, 40), (33, 120, 2, 3), (4, 2100, 2, 140)])
+@pytest.mark.parametrize("B,N,H,n_global", [(42, 300, 2, 40), (43, 300, 2, 40), (65, 120, 2, 3), (16, 500, 2, 33), (17, 500, 2, 33), (4, 2100, 2, 140)])
 def test_f32_forward_in_either_order_of_units(B, N, H, n_global):
-    """A launch of more than 128 units (B H (ceil(N / 128) + 1): 128, 136, 132 and 144) starts its question-token owners before
-    the columns', a smaller one after them."""
+    """A launch of more than 128 tiles of owners (B H ceil(N / 128): 130, 128, 136 and 136 in the last four) starts its question-token
+    owners before the columns', with two or three tiles a sequence one of more than 256 (252 and 258); a smaller one after them."""
     w = chunked_workload(N, B, N, H, n_global, "f32")
     got, _ = hp.run_hip(w, False)
     print(hp.report(hp.compare(got, hp.run_oracle(w, False, [(b, h) for b in (0, B - 1) for h in range(H)]), w, w.name)), flush=True)
