@@ -610,7 +610,7 @@ def test_backward_of_a_batch_in_parts(B, N, H, n_global):
 
 
 @pytest.mark.parametrize("values", ["ordinary", "wide", "no split", "small q", "small k", "small v", "small do",
-                                    "small products", "small probabilities", "zeros"])
+                                    "small products", "small probabilities", "zeros", "zero v", "small v that cancels"])
 def test_f32_products_from_splits(values):
     """fp32 products are formed from three bf16 parts: as good as fp32 over 120 binary orders of magnitude, for a value
     above the largest bf16, which has no such parts, and for values whose parts would not be normal numbers (an input, or
@@ -642,6 +642,13 @@ def test_f32_products_from_splits(values):
         k[:, :, ::5, 0], v[:, :, ::5] = 20.5, 0
     elif values == "zeros":
         v[..., ::3], do[:, :, ::2], k[:, :, 40:80], q[..., 5] = 0, 0, 0, 0
+    elif values == "zero v":
+        v[:] = 0
+    elif values == "small v that cancels":       # out of O and delta, not out of dP and dK: 16 bits, the last at 2^-135
+        k[:] = 0
+        v[:] = (2.0 ** -120 * (1 + 2.0 ** -15) * (1 - 2 * (np.arange(N) % 2)))[:, None]
+        v[:, :, n_global - 2] *= 2
+        do = do * np.float32(2.0 ** 60)
     w = synth.Workload("splits", "f32", st, np.array([ROW, COL], np.uint8), q, k, v, do, 0.125)
     ref = pairwise_reference(w, (q, k, v, do))
     dev = [hp.to_dev(x, "f32") for x in (q, k, v, do)]
