@@ -14,9 +14,10 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmate.so")
 NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["api.hip", "segments.hip", "positions.hip", "probe.hip", "proj_mfma.hip", "attn_f32_mfma.hip", "attn_fwd_mfma.hip", "attn_bwd_mfma.hip", "attn_dense_mfma.hip"]
-# packed-fp32 instructions are switched off on purpose (device code only).
+# packed-fp32 instructions are switched off on purpose (device code only).  Kernel arguments that are plain values arrive in
+# registers with the wavefront instead of by its first load (builder and cell positions: 0.2 us a launch).
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature",
-         "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-mfma-vgpr-form", "-fno-honor-nans", "-Wall", "-Wno-unused-function", "-Wno-inline-asm"]
+         "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-amdgpu-kernarg-preload-count=14", "-fno-honor-nans", "-Wall", "-Wno-unused-function", "-Wno-inline-asm"]
 
 
 def _compile(src: str) -> str:

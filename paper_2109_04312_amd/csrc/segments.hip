@@ -30,7 +30,10 @@
 // (six dependent shuffles were 2 us of the kernel), ids and segments are counted in one scan, and the
 // classification, which the instruction issue bounds, takes four elements per lane.  us per launch in a row of
 // them, against the version without these: one sequence of 128 positions 8.6 -> 5.0, of 512 9.3 -> 5.6, of 1999
-// 10.3 -> 7.0, two of 8192 14.3 -> 11.0.
+// 10.3 -> 7.0, two of 8192 14.3 -> 11.0.  Since then a lane's inputs are one load each and leave before anything else is
+// worked out (sequence_loads.h), all arguments arrive in registers, a slot's window is written by the token that takes the
+// slot (it knows its segment; a binary search per slot before), and the unit list finds its segments in three rounds
+// of reads instead of nine: 5.1 -> 5.0, 5.6 -> 5.2, 7.1 -> 6.1, 11.0 -> 9.5, one sequence of 16384 16.9 -> 14.2.
 //
 // Bucketed mode (the approximation of Section 3.1: a global part of at most G tokens, the rest
 // of the head's order in buckets of R, a bucket meeting itself and its two neighbours): the
@@ -43,6 +46,7 @@
 
 #include "launch.h"
 #include "seg_layout.h"
+#include "sequence_loads.h"
 
 namespace mate {
 
@@ -143,7 +147,7 @@ template <int P2, int kSegWaves>
 __global__ __launch_bounds__(64 * kSegWaves) void build_segments_kernel(
     const int* __restrict__ row_ids, const int* __restrict__ col_ids,
     const unsigned char* __restrict__ flags, int B, int N, int max_global, int radius,
-    int* __restrict__ seg) {
+    int* __restrict__ seg, int K) {
   constexpr int kSegThreads = 64 * kSegWaves;
   constexpr int CHUNK = P2 / kSegWaves;  // consecutive elements owned by one wavefront
   constexpr int NB = CHUNK / 64;         // 64-element batches per wavefront
@@ -159,7 +163,7 @@ __global__ __launch_bounds__(64 * kSegWaves) void build_segments_kernel(
   __shared__ int s_or, s_bad;
   // counting-sort path: how often every id is seen, anywhere and (<< 16) before this workgroup's
   // chunk (it lives in an order buffer, which only the general path uses, and later); first slot
-  // and segment index of every id; scratch for the work-unit list
+  // (and << 16 one past the last) and segment index of every id; scratch for the work-unit list
   unsigned* const id_count = reinterpret_cast<unsigned*>(buf_b);
   __shared__ int start_v[kBins];
   __shared__ int seg_i[kBins];
@@ -169,9 +173,31 @@ __global__ __launch_bounds__(64 * kSegWaves) void build_segments_kernel(
   const int b = blockIdx.x, view = blockIdx.y, tid = threadIdx.x;
   // Several workgroups per (sequence, view): K of them take a chunk of the positions each, one
   // more (k == K, no chunk) lists the work units.
-  const int k = blockIdx.z, K = (int)gridDim.z - 1;
+  const int k = blockIdx.z;
   const int chunk = (((N + K - 1) / K) + 63) & ~63, c0 = k < K ? k * chunk : 0, c1 = min(N, c0 + chunk);
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int* id_src = (view == 0 ? row_ids : col_ids) + (size_t)b * N;
+  const unsigned char* fl = flags + (size_t)b * N;
+  // Element order everywhere below: a wavefront owns CHUNK consecutive elements and walks them in
+  // batches of 64, lane = consecutive element, so that LDS and global accesses are unit-stride
+  // and ranks inside a batch come from ballots.  Only the classification, which every workgroup
+  // does for the whole sequence and which the instruction issue bounds, takes VE consecutive
+  // elements per lane.
+  const int w0 = wave * CHUNK;
+
+  // All of this wavefront's inputs first, in one go: the loads travel together instead of one
+  // dependent round trip per batch.
+  typedef typename Ids<VE>::type idv;
+  unsigned in_word[NV];
+  idv in_id[NV];
+#pragma unroll
+  for (int e = 0; e < NV; ++e) {
+    const int i0 = w0 + (e * 64 + lane) * VE;
+    in_word[e] = load_flags<VE>(fl, i0, N);
+    in_id[e] = load_ids<VE>(id_src, i0, N);
+  }
+  asm volatile("" ::: "memory");  // (where the tables lie is worked out while they travel)
+
   const SegLayout lay(B, N);
   int* counts = seg + lay.counts + (size_t)b * kCountWords;
   int* global_idx = seg + lay.global_idx + (size_t)b * N;
@@ -183,38 +209,9 @@ __global__ __launch_bounds__(64 * kSegWaves) void build_segments_kernel(
   int2* slot_rng = reinterpret_cast<int2*>(vbase + lay.slot_rng) + (size_t)b * N;
   int4* unit = reinterpret_cast<int4*>(vbase + lay.unit) + (size_t)b * lay.units * 2;
   int4* gunit = reinterpret_cast<int4*>(seg + lay.gunit) + (size_t)b * lay.tiles * 2;
-  const int* id_src = (view == 0 ? row_ids : col_ids) + (size_t)b * N;
-  const unsigned char* fl = flags + (size_t)b * N;
 
   if (b == 0 && view == 0 && k == 0 && tid < kHdrWords)
     seg[tid] = tid == 0 ? kMagic : tid == 1 ? B : tid == 2 ? N : tid == 4 ? max_global : tid == 5 ? radius : 0;
-  // Element order everywhere below: a wavefront owns CHUNK consecutive elements and walks them in
-  // batches of 64, lane = consecutive element, so that LDS and global accesses are unit-stride
-  // and ranks inside a batch come from ballots.  Only the classification, which every workgroup
-  // does for the whole sequence and which the instruction issue bounds, takes VE consecutive
-  // elements per lane.
-  const int w0 = wave * CHUNK;
-
-  // All of this wavefront's inputs first, in one go: the loads travel together instead of one
-  // dependent round trip per batch.
-  typedef int idv __attribute__((ext_vector_type(VE)));
-  unsigned char in_flag[NV][VE];
-  int in_id[NV][VE];
-#pragma unroll
-  for (int e = 0; e < NV; ++e) {
-    const int i0 = w0 + (e * 64 + lane) * VE;
-    if (i0 + VE <= N) {   // (any alignment: a sequence of odd length shifts the next one)
-      __builtin_memcpy(in_flag[e], fl + i0, VE);
-      __builtin_memcpy(in_id[e], id_src + i0, VE * sizeof(int));
-    } else {
-#pragma unroll
-      for (int j = 0; j < VE; ++j) {
-        const int i = min(i0 + j, N - 1);
-        in_flag[e][j] = fl[i];
-        in_id[e][j] = id_src[i];
-      }
-    }
-  }
 
   // (while they travel) clear the counters
   if (tid == 0) { s_or = 0; s_bad = 0; }
@@ -222,6 +219,18 @@ __global__ __launch_bounds__(64 * kSegWaves) void build_segments_kernel(
   for (int i = tid; i < kSegWaves * (int)kBins / 8; i += kSegThreads)
     reinterpret_cast<uint4*>(&hist[0][0])[i] = make_uint4(0, 0, 0, 0);
   lds_barrier();
+
+  unsigned char in_flag[NV][VE];
+#pragma unroll
+  for (int e = 0; e < NV; ++e) {
+    const int i0 = w0 + (e * 64 + lane) * VE;
+    if (w0 + CHUNK > N) {  // uniform
+      in_word[e] = align_flags<VE>(in_word[e], i0, N);
+      in_id[e] = align_ids<VE>(in_id[e], i0, N);
+    }
+#pragma unroll
+    for (int j = 0; j < VE; ++j) in_flag[e][j] = (unsigned char)(in_word[e] >> (8 * j));
+  }
 
   // ---- bucketed mode: question tokens past the first max_global join the table tokens ----------
   int q_at = 0;   // question tokens before this wavefront's block
@@ -321,24 +330,17 @@ __global__ __launch_bounds__(64 * kSegWaves) void build_segments_kernel(
     const int at = block_exclusive_scan<kSegWaves>(c_id | (c_id > 0 ? 1 << 16 : 0), scan_tmp[1], tot);
     const int first_slot = at & 0xffff, seg_index = at >> 16, S = tot >> 16;
     if (tid < (int)kBins) {
-      start_v[tid] = first_slot;
+      start_v[tid] = first_slot | (first_slot + c_id) << 16;
       seg_i[tid] = seg_index;
       if (c_id > 0) seg_tmp[0][seg_index] = first_slot;   // first slot of every segment, compact
     }
     if (tid == 0) seg_tmp[0][S] = L;
     lds_barrier();
     const int* sstart = seg_tmp[0];
-    // window of slot s: its segment (binary search over the first slots), in bucketed mode cut to
-    // the neighbouring buckets.  Slots are below 2^14, so the bucket index comes exactly from one
-    // float multiply: (s + 0.5) / radius is at least 0.5 / radius away from an integer and the
-    // rounding error is below 2e-7 s / radius.
-    auto window = [&](int s) {
-      int lo_i = 0, hi_i = S;   // sstart[lo_i] <= s < sstart[hi_i]
-      while (hi_i - lo_i > 1) {
-        const int mid = (lo_i + hi_i) >> 1;
-        if (sstart[mid] > s) hi_i = mid; else lo_i = mid;
-      }
-      int lo = sstart[lo_i], hi = sstart[hi_i];
+    // A slot's window: its segment [lo, hi), in bucketed mode cut to the neighbouring buckets.  Slots are below 2^14, so the
+    // bucket index comes exactly from one float multiply: (s + 0.5) / radius is at least 0.5 / radius away from an
+    // integer and the rounding error is below 2e-7 s / radius.
+    auto bounded = [&](int s, int lo, int hi) {
       if (radius > 0) {
         const int first = (int)(((float)s + 0.5f) * inv_radius) * radius;  // first slot of s's bucket
         lo = max(lo, first - radius);
@@ -393,19 +395,20 @@ __global__ __launch_bounds__(64 * kSegWaves) void build_segments_kernel(
       for (int j = 0; j < NBC; ++j) {
         const int p = c0 + (wave * NBC + j) * 64 + lane;
         if (p < c1) {
+          const int g_at = g_at_c + g_rank[j], p_at = p_at_c + p_rank[j];
           if (code[j] >= 0) {
-            const int slot = start_v[code[j]] + hist[wave][code[j]] + rank_w[j];
+            const int range = start_v[code[j]], lo = range & 0xffff, slot = lo + hist[wave][code[j]] + rank_w[j];
             perm[slot] = p;
+            slot_rng[slot] = bounded(slot, lo, range >> 16);
             seg_of_tok[p] = seg_i[code[j]];
           } else {
+            slot_rng[L + g_at + p_at] = make_int2(0, 0);  // (behind the last slot, one for every other token)
             seg_of_tok[p] = -1;
             if (view == 0) {
-              if (code[j] == -1) global_idx[g_at_c + g_rank[j]] = p;
-              else pad_idx[p_at_c + p_rank[j]] = p;
+              if (code[j] == -1) global_idx[g_at] = p;
+              else pad_idx[p_at] = p;
             }
           }
-          // the same index range, read as sorted slots: their windows
-          slot_rng[p] = p < L ? window(p) : make_int2(0, 0);
         }
       }
     }
@@ -466,7 +469,28 @@ __global__ __launch_bounds__(64 * kSegWaves) void build_segments_kernel(
     if (tid < n_units) {
       const int t0 = min((int)head_pos[tid], L - 1);
       const int end = min(max(tid + 1 < n_units ? (int)head_pos[tid + 1] : L, t0 + 1), min(L, t0 + kTileSlots));
-      const int lo = window(t0).x, hi = window(end - 1).y;
+      // their segments: the last that begin at or before them (S is at most 512; three rounds of seven reads at a
+      // time, where a binary search is up to nine rounds, of 50 ns each)
+      int first_seg = 0, last_seg = 0;
+      static_assert(kBins == 8 * 8 * 8, "three digits");
+#pragma unroll
+      for (int step = 64; step > 0; step /= 8) {
+        int f[7], l[7];
+#pragma unroll
+        for (int j = 0; j < 7; ++j) {   // (sstart[S] = L is beyond every slot)
+          f[j] = sstart[min(first_seg + (j + 1) * step, S)];
+          l[j] = sstart[min(last_seg + (j + 1) * step, S)];
+        }
+        int f_n = 0, l_n = 0;
+#pragma unroll
+        for (int j = 0; j < 7; ++j) {
+          f_n += f[j] <= t0;
+          l_n += l[j] < end;
+        }
+        first_seg += f_n * step;
+        last_seg += l_n * step;
+      }
+      const int lo = bounded(t0, sstart[first_seg], L).x, hi = bounded(end - 1, 0, sstart[last_seg + 1]).y;
       r0 = make_int4(UNIT_LOCAL, t0, lo, hi);
       r1.y = n_t0 + (hi - lo + BN - 1) / BN;
       r1.w = end;
@@ -763,17 +787,18 @@ hipError_t launch_build_segments(const int* row_ids, const int* col_ids,
   const int chunks = std::min(8, (N + kSegChunk - 1) / kSegChunk);
   dim3 grid(B, 2, chunks + 1);
   ProfileScope prof(1, stream);
-#define MATE_SEG_CASE(P2, WAVES)                                                                     \
-  if (N <= P2) {                                                                                      \
+#define MATE_SEG_CASE(MAX, P2, WAVES)                                                                     \
+  if (N <= MAX) {                                                                                     \
     hipLaunchKernelGGL((build_segments_kernel<P2, WAVES>), grid, dim3(64 * WAVES), 0, stream, row_ids, \
-                       col_ids, flags, B, N, max_global, radius, seg);                                \
+                       col_ids, flags, B, N, max_global, radius, seg, chunks);                             \
     return hipGetLastError();                                                                         \
   }
-  MATE_SEG_CASE(1024, 8)
-  MATE_SEG_CASE(2048, 8)
-  MATE_SEG_CASE(4096, 16)
-  MATE_SEG_CASE(8192, 16)
-  MATE_SEG_CASE(16384, 16)
+  MATE_SEG_CASE(1, 1024, 16)   // (one position a lane)
+  MATE_SEG_CASE(1024, 1024, 8)
+  MATE_SEG_CASE(2048, 2048, 8)
+  MATE_SEG_CASE(4096, 4096, 16)
+  MATE_SEG_CASE(8192, 8192, 16)
+  MATE_SEG_CASE(16384, 16384, 16)
 #undef MATE_SEG_CASE
   return hipErrorInvalidValue;
 }

@@ -123,7 +123,7 @@ def _positions(st):
     assert np.array_equal(out.cpu().numpy(), orc.cell_positions(st.row_ids, st.col_ids, st.flags))
 
 
-@pytest.mark.parametrize("N", [1, 2, 63, 64, 65, 1000, 1024, 1025, 4097, 8192, 9000, 16384])
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 5, 63, 64, 65, 255, 257, 1000, 1024, 1025, 4095, 4097, 8192, 9000, 16384])
 def test_cell_positions_sizes(N):
     """Positional index restarting per cell, bit-exact: cells of 1..40 tokens crossing batch
     and wavefront boundaries, in table order and with positions shuffled."""
@@ -148,3 +148,28 @@ def test_cell_positions_one_long_cell_and_all_kinds():
     col = np.zeros((4, N), np.int32)
     row[3] = np.arange(N)                    # every token its own cell
     _positions(synth.Structure(row, col, flags))   # sequence 0: one cell of 5000 tokens
+
+
+@pytest.mark.parametrize("start", [0, 4030, 4031, 4032, 4033, 4095, 4096, 4097])
+def test_cell_positions_cell_across_workgroups(start):
+    """One cell from `start` to past the second boundary of 4096 positions: found by the first look back, by the
+    longer one, or inside; and the same with a question token or a pad before the boundary."""
+    N = 9001
+    L, G, P = synth.TOK_LOCAL, synth.TOK_GLOBAL, synth.TOK_PAD
+    flags = np.full((3, N), L, np.uint8)
+    flags[1, 4095], flags[2, 4090:4096] = G, P
+    row = np.zeros((3, N), np.int32)
+    row[:, :start] = np.arange(start) // 3 + 1
+    row[:, 8500:] = 7
+    _positions(synth.Structure(row, np.zeros_like(row), flags))
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 5, 127, 129, 511, 1023, 1024, 1025, 1027, 2047, 2049])
+def test_builder_odd_lengths(N):
+    """Lanes load several positions at once and shift what they loaded where a sequence ends; sequences of odd length
+    begin anywhere."""
+    from paper_2109_04312_amd import mate
+    rng = np.random.default_rng(N)
+    st = synth.random_structure(rng, 5, N, max_rows=max(1, min(40, N // 3)), max_cols=7, max_global=min(N, 20),
+                                max_cell=9, scatter=True)
+    hp.compare_segments(mate.build_segments(*hp.dev_structure(st)), st)
