@@ -68,11 +68,9 @@ constexpr int kDkvStage = 2 * kTileBytes + 512;   // Q tile, dO tile, -lse/scale
 // kOne: delta and -LSE / scale are there already, and chunks are merged here.
 template <bool kOne>
 __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w, char* lds, int (*idx_ring)[BN], int* q_tok, int* group_done) {
-  const int b = w.b;
   const int N = a.N, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction
   const int m = lane & 31, hl = lane >> 5;
-  const int view = w.view;
   const UnitPlan& u = w.u;
 
   const size_t bh = (size_t)w.bh * N;
@@ -82,7 +80,6 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w, ch
   const unsigned short* O = static_cast<const unsigned short*>(a.o) + bh * kD;
   const unsigned short* dO = static_cast<const unsigned short*>(a.dout) + bh * kD;
   unsigned short* dQ = static_cast<unsigned short*>(a.dq) + bh * kD;
-  const int* global_idx = a.seg.global_idx + (size_t)b * N;
 
   if (u.kind == UNIT_PAD) {
     unsigned short* const outs[1] = {dQ};
@@ -93,10 +90,10 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w, ch
   // Second: the owned rows (registers) and the first K / V tiles (LDS), all in flight together.
   // K and V tiles stream through the LDS ring; K is read both plain (S^T = K Q^T) and
   // transposed (dQ^T += K^T dS^T), V plain (dP^T = V dO^T).
-  TileStream<kDqStage> stream(u, global_idx, lds, idx_ring, K, V, nullptr, 0, wave, lane);
+  TileStream<kDqStage> stream(u, w.global_idx, lds, idx_ring, K, V, nullptr, 0, wave, lane);
   stream.begin();
   const OwnerSplit<1> split(u, wave);
-  const OwnedRow me = owned_row(u, a, b, view, split.block, m);
+  const OwnedRow me = owned_row(w, split.block, m);
   asm volatile("" ::"v"(me.pos), "v"(me.lo), "v"(me.hi), "v"(me.stage_tok));  // the owned rows are known from here on
   if (tid < BM) q_tok[tid] = me.stage_tok;
   // the dkv kernel counts the chunks of an owner tile in the word of its first one
@@ -177,12 +174,12 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w, ch
 // (four workgroups per CU: with three, the column-head units of the benchmark shape do not all
 // fit at once and the stragglers double the kernel's critical path)
 template <bool kJoin>
-__global__ __launch_bounds__(kThreads, 4) void bwd_dq_mfma_kernel(AttnArgs a) {
+__global__ __launch_bounds__(kThreads, 4) void bwd_dq_mfma_kernel(MATE_UNIT_LISTS, AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds[kStages * kDqStage];
   __shared__ int idx_ring[kIdxSlots][BN];
   __shared__ int row_tok[BM];
   Work w;
-  if (!take_unit<true, kJoin>(a, blockIdx.x, w)) return;
+  if (!take_unit<true, kJoin>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x, w)) return;
   bwd_dq_unit<false>(a, w, lds, idx_ring, row_tok, nullptr);
 }
 
@@ -190,11 +187,9 @@ __global__ __launch_bounds__(kThreads, 4) void bwd_dq_mfma_kernel(AttnArgs a) {
 // dK, dV
 // ======================================================================================
 __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, char* lds, int (*idx_ring)[BN], int* k_tok, int* group_done) {
-  const int b = w.b;
   const int N = a.N, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction
   const int m = lane & 31, hl = lane >> 5;
-  const int view = w.view;
   const UnitPlan& u = w.u;
 
   const size_t bh = (size_t)w.bh * N;
@@ -204,7 +199,6 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
   const unsigned short* dO = static_cast<const unsigned short*>(a.dout) + bh * kD;
   unsigned short* dK = static_cast<unsigned short*>(a.dk) + bh * kD;
   unsigned short* dV = static_cast<unsigned short*>(a.dv) + bh * kD;
-  const int* global_idx = a.seg.global_idx + (size_t)b * N;
 
   if (u.kind == UNIT_PAD) {
     unsigned short* const outs[2] = {dK, dV};
@@ -217,12 +211,12 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
   // First round trip: the owned rows' positions and the first tiles' token indices; second:
   // the owned K / V rows (registers) and the first tiles (LDS).
   const float* row_src = wave == 0 ? a.nlse + bh : wave == 1 ? a.delta + bh : nullptr;
-  TileStream<kDkvStage> stream(u, global_idx, lds, idx_ring, Q, dO, row_src,
+  TileStream<kDkvStage> stream(u, w.global_idx, lds, idx_ring, Q, dO, row_src,
                                2 * kTileBytes + 256 * wave, wave, lane);
   stream.begin();
   // `me` is this lane's key; its window is the set of query slots that see it
   const OwnerSplit<1> split(u, wave);
-  const OwnedRow me = owned_row(u, a, b, view, split.block, m);
+  const OwnedRow me = owned_row(w, split.block, m);
   asm volatile("" ::"v"(me.pos), "v"(me.lo), "v"(me.hi), "v"(me.stage_tok));  // the owned rows are known from here on
   if (tid < BM) k_tok[tid] = me.stage_tok;
   stream.prime();
@@ -318,7 +312,7 @@ __device__ __forceinline__ void merge_dq(const AttnArgs& a, int bh_i, char* stag
 // The first `n_merge` workgroups (a multiple of eight, so that the unit queues keep their XCDs) merge
 // dQ partials: a few microseconds each, out of the way before the kernel's own tail.
 template <bool kJoin>
-__global__ __launch_bounds__(kThreads) void bwd_dkv_mfma_kernel(AttnArgs a, int n_merge) {
+__global__ __launch_bounds__(kThreads) void bwd_dkv_mfma_kernel(MATE_UNIT_LISTS, AttnArgs a, int n_merge) {
   __shared__ __attribute__((aligned(1024))) char lds[kStages * kDkvStage];
   __shared__ int idx_ring[kIdxSlots][BN];
   __shared__ int row_tok[BM];
@@ -328,7 +322,7 @@ __global__ __launch_bounds__(kThreads) void bwd_dkv_mfma_kernel(AttnArgs a, int 
     return;
   }
   Work w;
-  if (!take_unit<true, kJoin>(a, blockIdx.x - n_merge, w)) return;
+  if (!take_unit<true, kJoin>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x - n_merge, w)) return;
   bwd_dkv_unit(a, w, lds, idx_ring, row_tok, &group_done);
 }
 
@@ -365,7 +359,7 @@ __global__ __launch_bounds__(kThreads) void bwd_delta_kernel(AttnArgs a) {
   }
 }
 template <bool kJoin>
-__global__ __launch_bounds__(kThreads) void bwd_both_mfma_kernel(AttnArgs a) {
+__global__ __launch_bounds__(kThreads) void bwd_both_mfma_kernel(MATE_UNIT_LISTS, AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds[kStages * kDkvStage];
   __shared__ int idx_ring[kIdxSlots][BN];
   __shared__ int row_tok[BM];
@@ -373,7 +367,7 @@ __global__ __launch_bounds__(kThreads) void bwd_both_mfma_kernel(AttnArgs a) {
   const unsigned half = gridDim.x / 2;
   const bool dkv = blockIdx.x < half;
   Work w;
-  if (!take_unit<true, kJoin>(a, dkv ? blockIdx.x : blockIdx.x - half, w)) return;
+  if (!take_unit<true, kJoin>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, dkv ? blockIdx.x : blockIdx.x - half, w)) return;
   if (dkv) bwd_dkv_unit(a, w, lds, idx_ring, row_tok, &group_done);
   else bwd_dq_unit<true>(a, w, lds, idx_ring, row_tok, &group_done);
 }
@@ -403,18 +397,18 @@ static hipError_t launch_bwd(const AttnArgs& a, hipStream_t stream) {
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     ProfileScope prof(4, stream, 3);
-    hipLaunchKernelGGL(bwd_both_mfma_kernel<kJoin>, dim3(2 * grid.x), block, 0, stream, a);
+    hipLaunchKernelGGL(bwd_both_mfma_kernel<kJoin>, dim3(2 * grid.x), block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
     return hipGetLastError();
   }
   {
     ProfileScope prof(3, stream);
-    hipLaunchKernelGGL(bwd_dq_mfma_kernel<kJoin>, grid, block, 0, stream, a);
+    hipLaunchKernelGGL(bwd_dq_mfma_kernel<kJoin>, grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   ProfileScope prof(4, stream);
   const int n_merge = may_chunk(a.B, a.N) ? 8 * ((a.B * a.H + 7) / 8) : 0;
-  hipLaunchKernelGGL(bwd_dkv_mfma_kernel<kJoin>, dim3(grid.x + n_merge), block, 0, stream, a, n_merge);
+  hipLaunchKernelGGL(bwd_dkv_mfma_kernel<kJoin>, dim3(grid.x + n_merge), block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a, n_merge);
   return hipGetLastError();
 }
 hipError_t launch_bwd_mfma(const AttnArgs& a, hipStream_t stream) {

@@ -331,10 +331,10 @@ struct Quarter {
              // should not all sit on the same SIMD
 };
 template <bool kOwnersFirst>
-__device__ inline bool take_quarter(const AttnArgs& a, unsigned block, Quarter& q) {
+__device__ inline bool take_quarter(const UnitLists& l, const AttnArgs& a, unsigned block, Quarter& q) {
   q.sub = ((block >> 3) + (block >> 5)) & 3;
   q.turn = block >> 5;
-  if (!take_unit<kOwnersFirst, false>(a, ((block >> 5) << 3) | (block & 7), q.w)) return false;
+  if (!take_unit<kOwnersFirst, false>(l, a, ((block >> 5) << 3) | (block & 7), q.w)) return false;
   const UnitPlan& u = q.w.u;
   if (u.kind == UNIT_PAD) return true;
   // (a chunked question-token owner: its first unit streams everything, there are no partials here)
@@ -352,19 +352,19 @@ struct Rows {
   bool valid;
   const int *gidx, *list;  // question tokens [0, G), then slots [s_lo, s_hi) of list
   int G, s_lo, s_hi, nG, n;
-  __device__ __forceinline__ Rows(const AttnArgs& a, const Quarter& q, int m) {
+  __device__ __forceinline__ Rows(const Quarter& q, int m) {
     const UnitPlan& u = q.w.u;
-    const int b = q.w.b, first = u.t0 + kRows * q.sub, slot = min(first + m, u.own_count - 1);
+    const int first = u.t0 + kRows * q.sub, slot = min(first + m, u.own_count - 1);
     valid = first + m < u.own_count;
     pos = u.own_list[slot];
     lo = 0;
     hi = u.L;
     if (u.kind == UNIT_LOCAL) {
-      const int2 g = a.seg.slot_rng[q.w.view][(size_t)b * a.N + slot];
+      const int2 g = q.w.slot_rng[slot];
       lo = g.x;
       hi = g.y;
     }
-    gidx = a.seg.global_idx + (size_t)b * a.N;
+    gidx = q.w.global_idx;
     list = u.str_list;
     G = u.G;
     s_lo = __builtin_amdgcn_readlane(lo, 0);  // windows are monotone in the slot
@@ -445,13 +445,13 @@ __device__ __forceinline__ void zero_pads(const Quarter& q, float* const (&out)[
 // forward
 // ======================================================================================
 template <bool kOwnersFirst>
-__global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
+__global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(MATE_UNIT_LISTS, AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds[kWaves * kPlanes];
   __shared__ __attribute__((aligned(1024))) char own[kPlanes];
   __shared__ float2 stat[kWaves][kRows];
   __shared__ int row_tok[kRows], inexact[kWaves];
   Quarter q;
-  if (!take_quarter<kOwnersFirst>(a, blockIdx.x, q)) return;
+  if (!take_quarter<kOwnersFirst>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x, q)) return;
   const int tid = threadIdx.x, lane = tid & 63, m = lane & 31, hl = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const size_t bh = (size_t)q.w.bh * a.N;
@@ -464,7 +464,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
     zero_pads<1>(q, outs, a.lse + bh);
     return;
   }
-  const Rows r(a, q, m);
+  const Rows r(q, m);
   if (tid < kRows) row_tok[tid] = r.valid ? r.pos : -1;
   const int t0 = (wave + q.turn) & (kWaves - 1);
   int tok = r.token(t0, m), tok_next = r.token(t0 + kWaves, m);
@@ -622,7 +622,7 @@ __device__ __forceinline__ void dq_quarter(const AttnArgs& a, const Quarter& q, 
     zero_pads<1>(q, outs, nullptr);
     return;
   }
-  const Rows r(a, q, m);
+  const Rows r(q, m);
   if (tid < kRows) row_tok[tid] = r.valid ? r.pos : -1;
   const int t0 = (wave + q.turn) & (kWaves - 1);
   int tok = r.token(t0, m), tok_next = r.token(t0 + kWaves, m);
@@ -724,7 +724,7 @@ __device__ __forceinline__ void dkv_quarter(const AttnArgs& a, const Quarter& q,
     zero_pads<2>(q, outs, nullptr);
     return;
   }
-  const Rows r(a, q, m);
+  const Rows r(q, m);
   if (tid < kRows) row_tok[tid] = r.valid ? r.pos : -1;
   const int t0 = (wave + q.turn) & (kWaves - 1);
   int tok = r.token(t0, m), tok_next = r.token(t0 + kWaves, m);
@@ -895,12 +895,12 @@ __global__ __launch_bounds__(kThreads) void delta_f32_kernel(AttnArgs a) {
     if (piece == 0 && first + 16 * i < rows) reinterpret_cast<unsigned*>(a.delta)[first + 16 * i] = bits;
   }
 }
-__global__ __launch_bounds__(kThreads, 2) void bwd_f32_kernel(AttnArgs a, unsigned first) {
+__global__ __launch_bounds__(kThreads, 2) void bwd_f32_kernel(MATE_UNIT_LISTS, AttnArgs a, unsigned first) {
   __shared__ __attribute__((aligned(1024))) BwdLds lds;
   const unsigned block = first + blockIdx.x;
   Quarter q;
   // (32 workgroups are the quarters of eight units, one on each XCD)
-  if (!take_quarter<false>(a, ((block >> 6) << 5) | (block & 31), q)) return;
+  if (!take_quarter<false>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, ((block >> 6) << 5) | (block & 31), q)) return;
   if (block & 32) dq_quarter(a, q, lds);
   else dkv_quarter(a, q, lds);
 }
@@ -922,8 +922,8 @@ static bool owners_first(int B, int H, int N) {
 
 hipError_t launch_fwd_f32(const AttnArgs& a, hipStream_t stream) {
   const dim3 grid(4 * unit_grid(a.B, a.H, a.N, a.n_col)), block(kThreads);
-  if (owners_first(a.B, a.H, a.N)) hipLaunchKernelGGL(fwd_f32_kernel<true>, grid, block, 0, stream, a);
-  else hipLaunchKernelGGL(fwd_f32_kernel<false>, grid, block, 0, stream, a);
+  if (owners_first(a.B, a.H, a.N)) hipLaunchKernelGGL(fwd_f32_kernel<true>, grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
+  else hipLaunchKernelGGL(fwd_f32_kernel<false>, grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
   return hipGetLastError();
 }
 
@@ -933,7 +933,7 @@ hipError_t launch_bwd_f32(const AttnArgs& a, hipStream_t stream) {
   hipError_t e = hipGetLastError();
   const unsigned blocks = 2 * 4 * (unsigned)unit_grid(a.B, a.H, a.N, a.n_col), most = 1u << 23;  // (a launch has less than 2^32 threads)
   for (unsigned first = 0; first < blocks && e == hipSuccess; first += most) {
-    hipLaunchKernelGGL(bwd_f32_kernel, dim3(min(most, blocks - first)), dim3(kThreads), 0, stream, a, first);
+    hipLaunchKernelGGL(bwd_f32_kernel, dim3(min(most, blocks - first)), dim3(kThreads), 0, stream, MATE_UNIT_LISTS_VALUES(a), a, first);
     e = hipGetLastError();
   }
   return e;

@@ -84,11 +84,9 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w, FwdLd
   int (&idx_ring)[kIdxSlots][BN] = s.idx_ring;
   int (&q_tok)[BM] = s.q_tok;
   int& group_done = s.group_done;
-  const int b = w.b;
   const int N = a.N, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction
   const int m = lane & 31, hl = lane >> 5;
-  const int view = w.view;
   const UnitPlan& u = w.u;
 
   const size_t bh = (size_t)w.bh * N;
@@ -97,7 +95,6 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w, FwdLd
   const unsigned short* V = static_cast<const unsigned short*>(a.v) + bh * kD;
   unsigned short* O = static_cast<unsigned short*>(a.out) + bh * kD;
   float* LSE = a.lse + bh;
-  const int* global_idx = a.seg.global_idx + (size_t)b * N;
 
   if (u.kind == UNIT_PAD) {  // pad positions: O = 0, LSE = 0
     unsigned short* const outs[1] = {O};
@@ -117,10 +114,10 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w, FwdLd
   // First round trip: which rows this workgroup owns, and the token indices of the first tiles.
   // Second: the owned query rows (registers) and the first K / V tiles (LDS), all in flight
   // together.
-  TileStream<kStageBytes, kTiles> stream(u, global_idx, lds, idx_ring, K, V, nullptr, 0, wave, lane);
+  TileStream<kStageBytes, kTiles> stream(u, w.global_idx, lds, idx_ring, K, V, nullptr, 0, wave, lane);
   stream.begin();
   const OwnerSplit<kTiles> split(u, wave);
-  const OwnedRow me = owned_row(u, a, b, view, split.block, m);
+  const OwnedRow me = owned_row(w, split.block, m);
   asm volatile("" ::"v"(me.pos), "v"(me.lo), "v"(me.hi), "v"(me.stage_tok));  // the owned rows are known from here on
   if (tid < BM) q_tok[tid] = me.stage_tok;
   stream.prime();
@@ -217,17 +214,17 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w, FwdLd
 }
 
 template <bool kChunksFirst, bool kJoin>
-__global__ __launch_bounds__(kThreads, 4) void fwd_mfma_kernel(AttnArgs a) {
+__global__ __launch_bounds__(kThreads, 4) void fwd_mfma_kernel(MATE_UNIT_LISTS, AttnArgs a) {
   __shared__ FwdLds<1> s;
   Work w;
-  if (!take_unit<kChunksFirst, kJoin>(a, blockIdx.x, w)) return;
+  if (!take_unit<kChunksFirst, kJoin>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x, w)) return;
   fwd_unit<1>(a, w, s);
 }
 template <bool kChunksFirst>
-__global__ __launch_bounds__(kThreads, 2) void fwd_small_kernel(AttnArgs a) {
+__global__ __launch_bounds__(kThreads, 2) void fwd_small_kernel(MATE_UNIT_LISTS, AttnArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char dynamic_lds[];
   Work w;
-  if (!take_unit<kChunksFirst, false>(a, blockIdx.x, w)) return;
+  if (!take_unit<kChunksFirst, false>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x, w)) return;
   if (OwnerSplit<2>(w.u, 0).four) fwd_unit<2>(a, w, *reinterpret_cast<FwdLds<2>*>(dynamic_lds));
   else fwd_unit<1>(a, w, *reinterpret_cast<FwdLds<1>*>(dynamic_lds));
 }
@@ -239,7 +236,7 @@ static hipError_t launch_small(const AttnArgs& a, dim3 grid, hipStream_t stream)
   const hipError_t e = allow_lds<&fwd_small_kernel<kChunksFirst>>(sizeof(FwdLds<2>));
   if (e != hipSuccess) return e;
   ProfileScope prof(2, stream);
-  hipLaunchKernelGGL(fwd_small_kernel<kChunksFirst>, grid, dim3(kThreads), sizeof(FwdLds<2>), stream, a);
+  hipLaunchKernelGGL(fwd_small_kernel<kChunksFirst>, grid, dim3(kThreads), sizeof(FwdLds<2>), stream, MATE_UNIT_LISTS_VALUES(a), a);
   return hipGetLastError();
 }
 hipError_t launch_fwd_mfma(const AttnArgs& a, hipStream_t stream) {
@@ -247,10 +244,10 @@ hipError_t launch_fwd_mfma(const AttnArgs& a, hipStream_t stream) {
   const bool first = fwd_chunks_first(a.B, a.H, a.N), join = joins_chunks(a.B, a.H, a.N);
   if (small_forward(a.B, a.H, a.N)) return small_owners_first(a.B, a.H, a.N) ? launch_small<true>(a, grid, stream) : launch_small<false>(a, grid, stream);
   ProfileScope prof(2, stream);
-  if (first && join) hipLaunchKernelGGL((fwd_mfma_kernel<true, true>), grid, block, 0, stream, a);
-  else if (join) hipLaunchKernelGGL((fwd_mfma_kernel<false, true>), grid, block, 0, stream, a);
-  else if (first) hipLaunchKernelGGL((fwd_mfma_kernel<true, false>), grid, block, 0, stream, a);
-  else hipLaunchKernelGGL((fwd_mfma_kernel<false, false>), grid, block, 0, stream, a);
+  if (first && join) hipLaunchKernelGGL((fwd_mfma_kernel<true, true>), grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
+  else if (join) hipLaunchKernelGGL((fwd_mfma_kernel<false, true>), grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
+  else if (first) hipLaunchKernelGGL((fwd_mfma_kernel<true, false>), grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
+  else hipLaunchKernelGGL((fwd_mfma_kernel<false, false>), grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
   return hipGetLastError();
 }
 

@@ -63,8 +63,20 @@ struct UnitPlan {
 // ---- workgroup -> unit ---------------------------------------------------------------------
 struct Work {
   int b, bh, view;
+  const int* global_idx;  // of the sequence
+  const int2* slot_rng;   // of the sequence and view
   UnitPlan u;
 };
+
+// Where the unit lists are, and the sizes that map a workgroup to one of them.  These are kernel arguments of their own, the
+// first ones: plain values arrive in registers with the wavefront, a structure is loaded.
+struct UnitLists {
+  const int* hdr;   // the tables' header; the counts follow it
+  const int4 *gunit, *unit_row, *unit_col;
+  int B, H, N, n_col;
+};
+#define MATE_UNIT_LISTS const int *hdr, const int4 *gunit, const int4 *unit_row, const int4 *unit_col, int B, int H, int N, int n_col
+#define MATE_UNIT_LISTS_VALUES(a) (a).seg.hdr, (a).seg.gunit, (a).seg.unit[0], (a).seg.unit[1], (a).B, (a).H, (a).N, (a).n_col
 
 inline int unit_grid(int B, int H, int N, int n_col) {
   const int T = owner_slots(N), U = view_units(N), nc = (B * n_col + 7) / 8, nr = (B * (H - n_col) + 7) / 8;
@@ -109,107 +121,133 @@ inline bool small_owners_first(int B, int H, int N) {
   return owner_slots(N) > 2 && forward_units(B, H, N) > (may_chunk(B, N) ? 256 : 416);
 }
 
-// Entry i of the head order.  A byte indexed by a run-time value would be fetched with a vector
-// load (a memory round trip at the start of every workgroup); the containing 32-bit word comes
-// through the scalar cache with the other kernel arguments.
-__device__ inline int head_at(const AttnArgs& a, int i) {
-  const unsigned word = reinterpret_cast<const unsigned*>(a.head_order)[i >> 2];
-  return (word >> (8 * (i & 3))) & 0xffu;
-}
-
-// x / d and the remainder, both wave-uniform and not negative: one float product and its correction, half the
-// instructions of an integer division (scalar instructions wait for each other, and a workgroup's first
+// x / d and the remainder, both wave-uniform and not negative, for a quotient below 2^20: one float product and its
+// correction, half the instructions of an integer division (scalar instructions wait for each other, and a workgroup's first
 // microsecond is little else).
 __device__ inline int uniform_div(int x, int d, int& rest) {
   int k = __builtin_amdgcn_readfirstlane((int)((float)x * __builtin_amdgcn_rcpf((float)d)));
   rest = x - k * d;
-  while (rest < 0) { rest += d; --k; }   // (at most once below 2^22)
-  while (rest >= d) { rest -= d; ++k; }
+  const int below = rest >> 31;
+  k += below;
+  rest += below & d;
+  const int above = rest >= d;
+  k += above;
+  rest -= above ? d : 0;
   return k;
 }
 
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+// c ? x : y of values (of two variables the operator yields a variable, which the compiler then looks for in memory)
+template <class T>
+__device__ __forceinline__ T pick(bool c, T x, T y) { return c ? x : y; }
+
 // Returns false if this workgroup has nothing to do.  Everything here is wave-uniform and
 // stays in scalar registers.
+//
+// One round trip to memory: the place of the record is arithmetic on arguments that are in registers, and
+// the record, the header and the counts are loaded together, the pointers that a unit's beginning needs during the
+// arithmetic.  (Left to the compiler, every one of these was loaded where it is first used, behind the test of the one before:
+// nine scalar round trips, three of them to memory, before the first index load.  us, before and now: f32 forward of one sequence of
+// 128, 4 heads 12.7 -> 12.0, serving one of 512, 12 heads 16.4 -> 15.8, training at 2 x 8192, 16 heads 198.2 -> 197.3 and
+// bucketed 142.4 -> 141.7, 8 x 2048 177.8 -> 175.3.)
 template <bool kChunksFirst, bool kJoin>
-__device__ inline bool take_unit(const AttnArgs& a, int block, Work& w) {
-  const int T = a.seg.tiles, U = a.seg.units, N = a.N, n_col = a.n_col, n_row = a.H - n_col;
+__device__ __forceinline__ bool take_unit(UnitLists l, const AttnArgs& a, int block, Work& w) {
+  const int *gidx = a.seg.global_idx, *pads = a.seg.pad_idx, *perm_row = a.seg.perm[0], *perm_col = a.seg.perm[1];
+  const int2 *rng_row = a.seg.slot_rng[0], *rng_col = a.seg.slot_rng[1];
+  const void *xq = a.q, *xk = a.k, *xv = a.v, *xo = a.o, *xg = a.dout, *out = a.out;
+  const float* lse = a.lse;
+  __builtin_amdgcn_sched_barrier(0);   // these loads are under way during the arithmetic
+  const int N = l.N, T = owner_slots(N), U = view_units(N), n_col = l.n_col, n_row = l.H - n_col;
   const int q = block & 7;
   // row-head pairs are dealt to the queues starting where the column-head pairs stopped, so that
   // a handful of pairs still spreads over as many XCDs as possible
-  const int qr = (q - a.B * n_col) & 7;
-  const int nc = (a.B * n_col - q + 7) >> 3, nr = (a.B * n_row - qr + 7) >> 3;  // pairs of this queue
+  const int qr = (q - l.B * n_col) & 7;
+  const int nc = (l.B * n_col - q + 7) >> 3, nr = (l.B * n_row - qr + 7) >> 3;  // pairs of this queue
   // Records are listed longest first and the empty ones last, and how many are real is only
   // known on the device: a workgroup that finds an empty record leaves at once, but it still
   // took a slot for a microsecond, and a thousand of them ahead of real units delay those by
   // several.  So the early part of each list (where the real records are unless a sequence is
   // filled to the last position, resp. has more than 128 question tokens) comes first for all
   // three kinds of unit, the remainders after them.
-  const int E = min(U, T), T1 = min(T, (T >> 3) + 2);
-  int t = block >> 3;
-  // region -> (first pair, pairs, first record, records per pair)
-  const int n_all = nc + nr;
+  const int T1 = min(T, (T >> 3) + 2), n_all = nc + nr;
   // the first two regions: column heads then question-token owners (early parts), or the reverse
-  const int len_a = kChunksFirst ? n_all * T1 : nc * E, len_b = kChunksFirst ? nc * E : n_all * T1;
+  const int len_a = kChunksFirst ? n_all * T1 : nc * T, len_b = kChunksFirst ? nc * T : n_all * T1;
+  int t = block >> 3, k0 = 0, first = 0;
   bool glob = kChunksFirst;
-  int first = 0, pairs = glob ? n_all : nc, k0 = 0, per = glob ? T1 : E;
-  if (t >= len_a) {
-    t -= len_a; glob = !kChunksFirst; pairs = glob ? n_all : nc; per = glob ? T1 : E;
-    if (t >= len_b) {                      // row heads, early part
-      t -= len_b; first = nc; pairs = nr; k0 = 0; per = E; glob = false;
-      if (t >= nr * E) {                   // column heads, rest
-        t -= nr * E; first = 0; pairs = nc; k0 = E; per = U - E;
-        if (t >= nc * (U - E)) {           // row heads, rest
-          t -= nc * (U - E); first = nc; pairs = nr;
-          if (t >= nr * (U - E)) {         // question-token owners, rest
-            t -= nr * (U - E); first = 0; pairs = n_all; k0 = T1; per = T - T1; glob = true;
-          }
-        }
+  if (t >= len_a) { t -= len_a; glob = !kChunksFirst; }
+  const bool rows = t >= len_b && glob != kChunksFirst;  // row heads, early part
+  t -= rows ? len_b : 0;
+  glob &= !rows;
+  first = rows ? nc : 0;
+  int pairs = rows ? nr : glob ? n_all : nc, per = glob ? T1 : T;
+  if (__builtin_expect(rows && t >= nr * T, 0)) {  // the rest of the three lists
+    t -= nr * T; first = 0; pairs = nc; k0 = T; per = U - T;          // column heads
+    if (t >= nc * (U - T)) {
+      t -= nc * (U - T); first = nc; pairs = nr;                      // row heads
+      if (t >= nr * (U - T)) {
+        t -= nr * (U - T); first = 0; pairs = n_all; k0 = T1; per = T - T1; glob = true;  // question-token owners
       }
     }
   }
-  if (pairs <= 0) return false;
+  // (the pointers have arrived here)
+  asm("" : "+s"(t) : "s"(gidx), "s"(pads), "s"(perm_row), "s"(perm_col), "s"(rng_row), "s"(rng_col), "s"(xq), "s"(xk), "s"(xv),
+      "s"(xo), "s"(xg), "s"(out), "s"(lse));
   // The hardware hands consecutive workgroups of an XCD to its shader engines in rotation and
   // stalls when the engine whose turn it is has no room, so each engine must see the same mix
   // of units: the pair order rotates from sweep to sweep.
-  int at, i;
-  const int kk = uniform_div(t, pairs, at), k = k0 + kk;
-  if (kk >= per) return false;
-  uniform_div(at + kk, pairs, at);
-  const int j = first + at;
+  int turn;
+  const int kk = uniform_div(t, max(pairs, 1), turn);
+  uniform_div(turn + kk, max(pairs, 1), turn);
+  const bool real = pairs > 0 && kk < per;
+  const int k = real ? k0 + kk : 0, j = real ? first + turn : 0;
   w.view = j < nc ? 1 : 0;
-  const int b = w.view ? uniform_div(q + 8 * j, n_col, i) : uniform_div(qr + 8 * (j - nc), n_row, i);
-  const int h = head_at(a, w.view ? i : n_col + i);
+  const int pair = pick(j < nc, q + 8 * j, qr + 8 * (j - nc)), heads = max(pick(j < nc, n_col, n_row), 1);
+  int b, i;
+  if (__builtin_expect(l.B < 1 << 20, 1)) {
+    b = uniform_div(pair, heads, i);
+  } else {
+    b = (int)((unsigned)pair / (unsigned)heads);
+    i = pair - b * heads;
+  }
+  b = real ? b : 0;
+  i = real ? i : 0;
+  const int order = i + (real && j >= nc ? n_col : 0);
   w.b = b;
-  w.bh = b * a.H + h;
-  const int4* rec = glob ? a.seg.gunit + ((size_t)b * T + k) * 2
-                         : a.seg.unit[w.view] + ((size_t)b * U + k) * 2;
-  // The header is fetched together with the record (one scalar round trip for both): tables
+  const int4* list = pick<const int4*>(glob, l.gunit, pick<const int4*>(j < nc, l.unit_col, l.unit_row));
+  // (A byte of the head order, indexed by a run-time value, would be fetched with a vector load; the
+  // containing 32-bit word comes with the other kernel arguments.)
+  unsigned heads4 = reinterpret_cast<const unsigned*>(a.head_order)[order >> 2];
+  // The header is fetched together with the record: tables
   // built for another (B, N), or never built, make every workgroup leave before it uses a word
   // of them.  All of these reads stay inside the mate_segments_bytes(B, N) bytes the caller
   // must provide.
-  const int h_magic = a.seg.hdr[0], h_B = a.seg.hdr[1], h_N = a.seg.hdr[2];
-  const int4 r0 = rec[0], r1 = rec[1];
-  const int* cnt = a.seg.counts + (size_t)b * kCountWords;
+  i32x8 r = *reinterpret_cast<const i32x8*>(list + ((size_t)b * pick(glob, T, U) + k) * 2);
+  i32x4 h = *reinterpret_cast<const i32x4*>(l.hdr);
+  i32x4 cnt = *reinterpret_cast<const i32x4*>(l.hdr + kHdrWords + (size_t)b * kCountWords);
+  asm("" : "+s"(h), "+s"(heads4) : "s"(r), "s"(cnt));
+  w.bh = b * l.H + (int)((heads4 >> (8 * (order & 3))) & 0xffu);
   UnitPlan& u = w.u;
-  u.kind = r0.x;
-  if (h_magic != kMagic || h_B != a.B || h_N != a.N) return false;
-  if (u.kind == UNIT_NONE) return false;
-  u.t0 = r0.y;
-  u.s_lo = r0.z;
-  u.s_hi = r0.w;
-  u.t_begin = r1.x;
-  u.t_end = r1.y;
-  u.part = r1.z;
-  u.n_chunks = r1.w;
+  u.kind = r[0];
+  if (!real || h[0] != kMagic || h[1] != l.B || h[2] != N || u.kind == UNIT_NONE) return false;
+  u.t0 = r[1];
+  u.s_lo = r[2];
+  u.s_hi = r[3];
+  u.t_begin = r[4];
+  u.t_end = r[5];
+  u.part = r[6];
+  u.n_chunks = r[7];
   u.G = cnt[C_G];
   u.L = cnt[C_L];
   u.P = cnt[C_P];
   u.n_t0 = (u.G + BN - 1) / BN;
-  const int* perm_v = a.seg.perm[w.view] + (size_t)b * N;
-  u.str_list = glob ? a.seg.perm[0] + (size_t)b * N : perm_v;  // row order: the contiguous one
-  u.own_list = glob ? a.seg.global_idx + (size_t)b * N
-                    : u.kind == UNIT_LOCAL ? perm_v : a.seg.pad_idx + (size_t)b * N;
-  u.own_count = glob ? u.G : u.kind == UNIT_LOCAL ? r1.w : u.P;
+  const size_t seq = (size_t)b * N;
+  w.global_idx = gidx + seq;
+  w.slot_rng = pick(j < nc, rng_col, rng_row) + seq;
+  const int* perm_v = pick(j < nc, perm_col, perm_row) + seq;
+  u.str_list = pick<const int*>(glob, perm_row + seq, perm_v);  // row order: the contiguous one
+  u.own_list = pick<const int*>(glob, gidx + seq, pick<const int*>(r[0] == UNIT_LOCAL, perm_v, pads + seq));
+  u.own_count = glob ? cnt[C_G] : r[0] == UNIT_LOCAL ? r[7] : cnt[C_P];
   if (kJoin && glob && u.part >= 0) {
     const int n_st = u.n_t0 + (u.L + BN - 1) / BN, gt = u.t0 / BM, c = u.part - gt * u.n_chunks;
     if (n_st <= kLongStream) {
@@ -265,8 +303,8 @@ struct OwnedRow {
   int a_lo, a_hi;     // intersection over the wavefront's rows
   bool wave_active;   // the wavefront owns at least one valid row
 };
-__device__ inline OwnedRow owned_row(const UnitPlan& u, const AttnArgs& a, int b, int view,
-                                     int wave, int m) {
+__device__ inline OwnedRow owned_row(const Work& w, int wave, int m) {
+  const UnitPlan& u = w.u;
   OwnedRow r;
   const int slot_raw = u.t0 + wave * 32 + m;
   const int slot = min(slot_raw, u.own_count - 1);
@@ -280,7 +318,7 @@ __device__ inline OwnedRow owned_row(const UnitPlan& u, const AttnArgs& a, int b
   r.lo = 0;
   r.hi = u.L;
   if (u.kind == UNIT_LOCAL) {
-    const int2 g = a.seg.slot_rng[view][(size_t)b * a.N + slot];
+    const int2 g = w.slot_rng[slot];
     r.lo = g.x;
     r.hi = g.y;
   }
