@@ -258,27 +258,53 @@ __device__ __forceinline__ void add_ranges(const RangeSums& s, int block, int th
 // ======================================================================================
 // Products with the weights: forward, dX, d_o
 // ======================================================================================
-struct ProjArgs {
+// Workgroup -> tile.  A grid row is eight token tiles times all feature tiles: XCD x % 8 takes one of the token tiles, so
+// the token rows that it streams stay in its L2 while the weights cycle, another one in each grid row, so that the
+// padding at the end of the sequences is spread over all XCDs.  The tiles of the last token tiles, fewer than eight, are
+// dealt one by one: no XCD has more than one tile more than another, where 21 whole token tiles with 12 feature tiles were 36
+// tiles on some XCDs' 32 CUs, two rounds where one does (1024 -> 3072 at 5376 tokens 38 -> 32 us, at 10752 74 -> 61, gradients
+// of the output projection at 7 x 577 tokens, 768 wide 31.2 -> 25.2, at 9 x 1000 40 -> 33; where it saves no round, 1024 ->
+// 3072 at 25 x 273, 71 -> 72.5).  (Halves and quarters of a token tile's features to an XCD: 0 to 4 % slower.)
+constexpr int kMostGridY = 32768;  // (a grid's second dimension is at most 65536: the third continues it)
+struct TileDeal {
+  int tokens, features;  // tiles
+  int rows;              // grid rows that are dealt as whole token tiles (or feature tiles)
+  int by_feature;        // the same with the two exchanged
+  __device__ __host__ int grid_x() const { return 8 * (by_feature ? tokens : features); }
+  __device__ __host__ int grid_y() const { return rows + ((by_feature ? features : tokens) > 8 * rows ? 1 : 0); }
+};
+__device__ __forceinline__ bool dealt_tile(const TileDeal& d, int x, int y, int& token_tile, int& feature_tile) {
+  int major = 8 * y + ((x + 3 * y) & 7), minor = x >> 3;
+  const int majors = d.by_feature ? d.features : d.tokens;
+  if (y >= d.rows) major = 8 * y + uniform_div(x, d.by_feature ? d.tokens : d.features, minor);
+  token_tile = d.by_feature ? minor : major;
+  feature_tile = d.by_feature ? major : minor;
+  return major < majors;
+}
+
+// What a tile's first loads need: kernel arguments of their own, the first ones, because plain values arrive in registers with
+// the wavefront.
+struct ProjStart {
   const unsigned short* w;       // plain: [F][K] row-major; transposed: [K][F]
   const unsigned short* tok;     // flat tokens: [B*N][K] row-major (x, or dy in the backward)
+  const unsigned char* flags;    // [B][N]
+  int N;
+  int F, K;                      // features, contraction length
+  TileDeal deal;
+};
+struct ProjArgs : ProjStart {
   const unsigned short* tok3[3]; // head tokens: [B][H][N][64] tensors whose heads are the k steps, one
                                  // after the other (o; or dq, dk, dv in the backward)
   const float* bias;             // [F] or null
-  const unsigned char* flags;    // [B][N]
   unsigned short* out[3];        // head layout: q, k, v (or d_o) [B][H][N][64];  flat: [B][N][F] in out[0]
-  int B, N, H;
-  int F, K;                      // features, contraction length
-  int tok_tiles_per_seq;         // ceil(N / tile tokens)
-  int feat_tiles;                // ceil(F / tile features)
-  int by_feature;                // which way tiles are dealt to the XCDs, see product_tile
-  int tile_blocks;               // workgroups of the product; those behind them add `ranges`
+  int B, H;
   RangeSums ranges;
 };
 
 // kHeadTok: the token operand comes from head-layout tensors and the output is flat; else the reverse.
 // kTransposedW: the weight operand is read transposed.
 template <class S, bool kHeadTok, bool kTransposedW>
-__device__ __forceinline__ void product_tile(ProjArgs a, char* lds, int block) {
+__device__ __forceinline__ void product_tile(const ProjStart& p, const ProjArgs& a, char* lds, int b, int n0, int f0) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int group = wave_id / S::kWaves, wave = wave_id - group * S::kWaves;
@@ -286,19 +312,7 @@ __device__ __forceinline__ void product_tile(ProjArgs a, char* lds, int block) {
   const int r = lane & 15, quarter = lane >> 4;
   char* const ring = lds + group * S::kRingBytes;
 
-  // Workgroup -> (token tile, feature tile).  XCD q walks the feature tiles fastest, so the token rows it
-  // streams stay in its L2 while the weights cycle, and takes one of every eight consecutive token
-  // tiles, another one each time, so that the padding at the end of the sequences is spread over all XCDs.
-  // With few token tiles that leaves XCDs idle or uneven (one of 64 tokens and 6144 x 2048 weights: 48 tiles on
-  // the 32 CUs of one XCD, 29 us); then the feature tiles are dealt instead, and every weight is read by one XCD.
-  const int q = block & 7, jx = block >> 3;
-  const int per = a.by_feature ? a.B * a.tok_tiles_per_seq : a.feat_tiles, jk = jx / per, rest = jx - jk * per;
-  const int tt = a.by_feature ? rest : 8 * jk + ((q + 3 * jk) & 7), f0 = (a.by_feature ? 8 * jk + q : rest) * S::kRowsA;
-  if (f0 >= a.F) return;
-  const int b = tt / a.tok_tiles_per_seq, tile = tt - b * a.tok_tiles_per_seq;
-  if (b >= a.B) return;
-  const int n0 = tile * S::kRowsB;
-  const int rows = min(S::kRowsB, a.N - n0), feats = min(S::kRowsA, a.F - f0);
+  const int rows = min(S::kRowsB, p.N - n0), feats = min(S::kRowsA, p.F - f0);
 
   // ---- operand streams: per load a wave-uniform base and a 32-bit lane offset -----------------------
   unsigned off[S::kLoads];
@@ -306,19 +320,20 @@ __device__ __forceinline__ void product_tile(ProjArgs a, char* lds, int block) {
   for (int i = 0; i < S::kLoadsA; ++i) {
     const LoadUnit l = load_unit<S::kWaves>(wave, lane, i);
     // (features past F repeat the last 64-column block or the last row, and are not stored)
-    off[i] = kTransposedW ? (unsigned)l.row * (unsigned)a.F * 2 + (unsigned)min(64 * l.tile, feats - 64) * 2 + l.chunk * 16
-                          : (unsigned)min(64 * l.tile + l.row, feats - 1) * (unsigned)a.K * 2 + l.chunk * 16;
+    off[i] = kTransposedW ? (unsigned)l.row * (unsigned)p.F * 2 + (unsigned)min(64 * l.tile, feats - 64) * 2 + l.chunk * 16
+                          : (unsigned)min(64 * l.tile + l.row, feats - 1) * (unsigned)p.K * 2 + l.chunk * 16;
   }
 #pragma unroll
   for (int i = 0; i < S::kLoadsB; ++i) {  // (tokens past the end repeat the last one)
     const LoadUnit l = load_unit<S::kWaves>(wave, lane, i);
-    off[S::kLoadsA + i] = (unsigned)min(64 * l.tile + l.row, rows - 1) * (kHeadTok ? kD * 2u : (unsigned)a.K * 2) + l.chunk * 16;
+    off[S::kLoadsA + i] = (unsigned)min(64 * l.tile + l.row, rows - 1) * (kHeadTok ? kD * 2u : (unsigned)p.K * 2) + l.chunk * 16;
   }
-  const size_t w_step = kTransposedW ? (size_t)64 * a.F * 2 : 128;
-  const char* w_ptr = reinterpret_cast<const char*>(kTransposedW ? a.w + f0 : a.w + (size_t)f0 * a.K) + group * w_step;  // of the next stage
-  const size_t head0 = (((size_t)b * a.H) * a.N + n0) * kD * 2, t_step = kHeadTok ? (size_t)a.N * kD * 2 : 128;
+  const unsigned short *tok3_1 = a.tok3[1], *tok3_2 = a.tok3[2];
+  const size_t w_step = kTransposedW ? (size_t)64 * p.F * 2 : 128;
+  const char* w_ptr = reinterpret_cast<const char*>(kTransposedW ? p.w + f0 : p.w + (size_t)f0 * p.K) + group * w_step;  // of the next stage
+  const size_t head0 = (((size_t)b * a.H) * p.N + n0) * kD * 2, t_step = kHeadTok ? (size_t)p.N * kD * 2 : 128;
   const char* t_ptr = kHeadTok ? reinterpret_cast<const char*>(a.tok3[0]) + head0
-                               : reinterpret_cast<const char*>(a.tok + ((size_t)b * a.N + n0) * a.K);
+                               : reinterpret_cast<const char*>(p.tok + ((size_t)b * p.N + n0) * p.K);
   t_ptr += group * t_step;
   int head = group, tensor = 0;
   auto issue_stage = [&](int g) {
@@ -334,18 +349,18 @@ __device__ __forceinline__ void product_tile(ProjArgs a, char* lds, int block) {
     if (kHeadTok && (head += S::kGroups) >= a.H) {  // the next tensor's heads (H is even)
       head -= a.H;
       ++tensor;
-      t_ptr = reinterpret_cast<const char*>(tensor == 1 ? a.tok3[1] : a.tok3[2]) + head0 + head * t_step;
+      t_ptr = reinterpret_cast<const char*>(pick(tensor == 1, tok3_1, tok3_2)) + head0 + head * t_step;
     }
   };
   constexpr bool kHalves = S::kGroups == 1 && S::kWaves == 8 && S::kStages == 2;
-  const int nk = a.K / 64 / S::kGroups;  // this group's stages (K is a multiple of 128)
+  const int nk = p.K / 64 / S::kGroups;  // this group's stages (K is a multiple of 128)
 #pragma unroll
   for (int s = 0; s < S::kStages - 1; ++s)
     if (s < nk) issue_stage(s);
 
   // While the first stages travel: is any token of the tile not padding (every wavefront looks at all of
   // them), which of this lane's are, and the bias of this lane's features.
-  const unsigned char* fl = a.flags + (size_t)b * a.N + n0;
+  const unsigned char* fl = p.flags + (size_t)b * p.N + n0;
   bool any = false;
 #pragma unroll
   for (int i = 0; i < S::kB; ++i) any |= fl[min(64 * i + lane, rows - 1)] < 2;
@@ -359,10 +374,10 @@ __device__ __forceinline__ void product_tile(ProjArgs a, char* lds, int block) {
   }
   f32x4 bias[S::kFA];
 #pragma unroll
-  for (int i = 0; i < S::kFA; ++i) {
-    bias[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (a.bias) bias[i] = *reinterpret_cast<const f32x4*>(a.bias + f0 + min((wa * S::kFA + i) * 16, feats - 16) + 4 * quarter);
-  }
+  for (int i = 0; i < S::kFA; ++i) bias[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (a.bias)   // (one branch around all loads: a branch each had a wait each)
+#pragma unroll
+    for (int i = 0; i < S::kFA; ++i) bias[i] = *reinterpret_cast<const f32x4*>(a.bias + f0 + min((wa * S::kFA + i) * 16, feats - 16) + 4 * quarter);
 
   f32x4 acc[S::kFA][S::kFB];
 #pragma unroll
@@ -390,6 +405,7 @@ __device__ __forceinline__ void product_tile(ProjArgs a, char* lds, int block) {
   f32x4 sum[S::kFA][S::kOutB];
   add_groups<S>(acc, sum, lds, group, wave, lane);
 
+  unsigned short *const out_0 = a.out[0], *const out_1 = a.out[1], *const out_2 = a.out[2];
   // ---- epilogue: + bias, round to bf16.  A lane holds features 16 i + 4 quarter .. + 3 of token 16 j + r;
   // after exchanging quarters between neighbouring blocks it holds eight consecutive ones and stores
   // 16 bytes, 64 of a token's bytes per instruction. ------------------------------------------------
@@ -400,12 +416,12 @@ __device__ __forceinline__ void product_tile(ProjArgs a, char* lds, int block) {
     unsigned short* dst;
     size_t dst_stride;  // elements between consecutive tokens
     if (kHeadTok) {
-      dst = a.out[0] + ((size_t)b * a.N + n0) * a.F + f0 + fw;
-      dst_stride = a.F;
+      dst = a.out[0] + ((size_t)b * p.N + n0) * p.F + f0 + fw;
+      dst_stride = p.F;
     } else {
       const int head_slot = (f0 + fw) >> 6, x = head_slot / a.H, h = head_slot - x * a.H;
-      unsigned short* out = x == 0 ? a.out[0] : x == 1 ? a.out[1] : a.out[2];
-      dst = out + (((size_t)b * a.H + h) * a.N + n0) * kD + (fw & 63);
+      unsigned short* out = pick(x == 0, out_0, pick(x == 1, out_1, out_2));
+      dst = out + (((size_t)b * a.H + h) * p.N + n0) * kD + (fw & 63);
       dst_stride = kD;
     }
     dst += (quarter & 1) * 16 + (quarter >> 1) * 8;
@@ -428,45 +444,63 @@ __device__ __forceinline__ void product_tile(ProjArgs a, char* lds, int block) {
 }
 
 template <class S, bool kHeadTok, bool kTransposedW>
-__global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void proj_kernel(ProjArgs a) {
-  extern __shared__ __attribute__((aligned(1024))) char lds[];
-  if ((int)blockIdx.x < a.tile_blocks) product_tile<S, kHeadTok, kTransposedW>(a, lds, blockIdx.x);
-  else add_ranges(a.ranges, blockIdx.x - a.tile_blocks, S::kThreads);  // behind the tiles: partial sums of a weight gradient
+__device__ __forceinline__ void dealt_product(const ProjStart& p, const ProjArgs& a, char* lds, int x, int y) {
+  int token_tile, feature_tile, tile;
+  if (!dealt_tile(p.deal, x, y, token_tile, feature_tile)) return;
+  const int b = uniform_div(token_tile, (p.N + S::kRowsB - 1) / S::kRowsB, tile);
+  product_tile<S, kHeadTok, kTransposedW>(p, a, lds, b, tile * S::kRowsB, feature_tile * S::kRowsA);
 }
 
-// Tiles of the busiest XCD, dealt by token or by feature tile, and how many its 32 CUs take one after the other.
-// (By feature where that is fewer: 1024 -> 3072 at 600 tokens, 10 tiles of 64: 17.6 -> 9.3 us; 2048 -> 6144 at 64:
-// 29.4 -> 13.4.  In equal rounds by token: the weights are then read once per token tile from an L2 that keeps them.)
-template <class S>
-long tiles_per_xcd(const ProjArgs& a, bool by_feature) {
-  const long tok = (long)a.B * ((a.N + S::kRowsB - 1) / S::kRowsB), feat = (a.F + S::kRowsA - 1) / S::kRowsA;
-  return by_feature ? (feat + 7) / 8 * tok : (tok + 7) / 8 * feat;
+template <class S, bool kHeadTok, bool kTransposedW>
+__global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void proj_kernel(
+    const unsigned short* w, const unsigned short* tok, const unsigned char* flags, int N, int F, int K, int token_tiles, int feature_tiles,
+    int whole_rows, int by_feature, ProjArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const ProjStart p = {w, tok, flags, N, F, K, {token_tiles, feature_tiles, whole_rows, by_feature}};
+  const int x = blockIdx.x, y = blockIdx.y + kMostGridY * blockIdx.z, behind = y - p.deal.grid_y();
+  if (behind < 0) dealt_product<S, kHeadTok, kTransposedW>(p, a, lds, x, y);
+  else if (behind * p.deal.grid_x() < a.ranges.blocks) add_ranges(a.ranges, behind * p.deal.grid_x() + x, S::kThreads);  // behind the tiles: partial sums of a weight gradient
 }
-long rounds(long tiles) { return (tiles + 31) / 32; }
+
+// Tiles of a product, and how many a CU takes one after the other.
+template <class S>
+long tiles_of(const ProjArgs& a) {
+  return (long)a.B * ((a.N + S::kRowsB - 1) / S::kRowsB) * ((a.F + S::kRowsA - 1) / S::kRowsA);
+}
+long rounds(long tiles) { return (tiles + 255) / 256; }
 
 template <class S>
 void deal_tiles(ProjArgs& a) {
-  a.tok_tiles_per_seq = (a.N + S::kRowsB - 1) / S::kRowsB;
-  a.feat_tiles = (a.F + S::kRowsA - 1) / S::kRowsA;
-  const long by_token = tiles_per_xcd<S>(a, false), by_feature = tiles_per_xcd<S>(a, true);
-  a.by_feature = rounds(by_feature) < rounds(by_token);
-  a.tile_blocks = 8 * (int)(a.by_feature ? by_feature : by_token);
+  TileDeal& d = a.deal;
+  d.tokens = a.B * ((a.N + S::kRowsB - 1) / S::kRowsB);
+  d.features = (a.F + S::kRowsA - 1) / S::kRowsA;
+  // every XCD reads all of the other operand: the smaller one (us by token tiles and by feature tiles: 1024 -> 3072 at 600
+  // tokens 12.1 and 9.8, at 1200 13.8 and 12.5, at 1700 16.8 and 16.5; 2048 -> 6144 at 1000 33.5 and 32.0)
+  d.by_feature = a.F > (long)a.B * a.N;
+  d.rows = (d.by_feature ? d.features : d.tokens) / 8;
 }
 
 template <class S, bool kHeadTok, bool kTransposedW>
 hipError_t launch_proj(ProjArgs a, int kernel_id, hipStream_t stream) {
   deal_tiles<S>(a);
-  if (a.ranges.splits) a.ranges.blocks = (int)std::max<size_t>(1, std::min<size_t>(1024 * 256 / S::kThreads, a.ranges.n / 4 / S::kThreads));
+  const int x = a.deal.grid_x();
+  int range_rows = 0;
+  if (a.ranges.splits) {
+    range_rows = (int)(std::max<size_t>(1, std::min<size_t>(1024 * 256 / S::kThreads, a.ranges.n / 4 / S::kThreads)) + x - 1) / x;
+    a.ranges.blocks = range_rows * x;
+  }
+  const int y = a.deal.grid_y() + range_rows;
+  const dim3 grid(x, std::min(y, kMostGridY), (y + kMostGridY - 1) / kMostGridY);
   const hipError_t e = allow_lds<&proj_kernel<S, kHeadTok, kTransposedW>>(S::kLds);
   if (e != hipSuccess) return e;
   ProfileScope prof(kernel_id, stream);
-  hipLaunchKernelGGL((proj_kernel<S, kHeadTok, kTransposedW>), dim3(a.tile_blocks + a.ranges.blocks), dim3(S::kThreads),
-                     S::kLds, stream, a);
+  hipLaunchKernelGGL((proj_kernel<S, kHeadTok, kTransposedW>), grid, dim3(S::kThreads),
+                     S::kLds, stream, a.w, a.tok, a.flags, a.N, a.F, a.K, a.deal.tokens, a.deal.features, a.deal.rows, a.deal.by_feature, a);
   return hipGetLastError();
 }
 
 // Which shape.  A compute unit that gets n tiles of a shape needs about (k / 64) (c2 for every two tiles, c1 for
-// an odd last one) + e n us, so the shape with the smallest such sum wins, n being the rounds of the busiest XCD:
+// an odd last one) + e n us, so the shape with the smallest such sum wins, n being the rounds of tiles:
 // large tiles once they fill the chip, smaller ones where they fit its units better.  The constants were fitted
 // to the times of the other six shapes for 912 products (64 to 40000 tokens, widths 128 to 4096, 2 to 32 heads, no
 // padding): the shape that they choose takes 0.2 % more than the fastest one on average and 22 % at most, against
@@ -488,7 +522,7 @@ using Proj64 = Shape<2, 1, 2, 2, 3, 2>;       // 128 x  64
 using Proj64x2 = Shape<2, 1, 2, 2, 3, 1, 2>;
 template <class S>
 double proj_cost(const ProjArgs& a, double c1, double c2, double e) {
-  const long n = std::min(rounds(tiles_per_xcd<S>(a, false)), rounds(tiles_per_xcd<S>(a, true)));
+  const long n = rounds(tiles_of<S>(a));
   return (a.K / 64) * ((n / 2) * c2 + (n % 2) * c1) + e * n;
 }
 
@@ -938,7 +972,11 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4) void proj_bwd_kernel
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   static_assert(S::kThreads == Wgrad128::kThreads, "one workgroup size for both");
   if ((int)blockIdx.x < w_blocks) wgrad_tile<Wgrad128, kOneLaunchBlocks, kOneLaunchChain, true>(w, lds, blockIdx.x);
-  else product_tile<S, kHeadTok, true>(a, lds, blockIdx.x - w_blocks);
+  else {
+    int x;
+    const int y = uniform_div(blockIdx.x - w_blocks, a.deal.grid_x(), x);
+    dealt_product<S, kHeadTok, true>(a, a, lds, x, y);
+  }
 }
 
 // The product's tiles there, eight wavefronts each.  Those of one group and those of two add up a product's stages in
@@ -979,7 +1017,7 @@ void offer_bwd(BwdPlan& best, ProjArgs a, bool large, int tiles, int blocks, int
   double t1 = (0.44 + 0.12 * std::min(1.0, first / 256.0)) * per_range + 5.1;
   for (int r = 1; r < ranges; r *= 2) t1 += 2.7;   // one addition of pairs
   // (padding, which this leaves out, shortens long ranges most: several must be worth 16 %)
-  const double cost = (ranges > 1 ? 1.16 : 1.0) * (4.4 + end_of_both(first, t1, a.tile_blocks, per_step * (a.K / 64) + rest));
+  const double cost = (ranges > 1 ? 1.16 : 1.0) * (4.4 + end_of_both(first, t1, a.deal.tokens * a.deal.features, per_step * (a.K / 64) + rest));
   if (cost < best.cost) {
     best.cost = cost;
     best.wgrad = t1;
@@ -1033,7 +1071,7 @@ hipError_t launch_bwd(WgradArgs w, ProjArgs a, const BwdPlan& p, char* ws, int w
   const hipError_t e = allow_lds<&proj_bwd_kernel<S, kHeadTok>>(kLds);
   if (e != hipSuccess) return e;
   ProfileScope prof(wgrad_id, stream, proj_id);
-  hipLaunchKernelGGL((proj_bwd_kernel<S, kHeadTok>), dim3(w_blocks + a.tile_blocks), dim3(S::kThreads), kLds, stream, w, a, w_blocks);
+  hipLaunchKernelGGL((proj_bwd_kernel<S, kHeadTok>), dim3(w_blocks + a.deal.grid_x() * a.deal.grid_y()), dim3(S::kThreads), kLds, stream, w, a, w_blocks);
   return hipGetLastError();
 }
 

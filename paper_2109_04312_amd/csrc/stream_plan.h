@@ -121,26 +121,8 @@ inline bool small_owners_first(int B, int H, int N) {
   return owner_slots(N) > 2 && forward_units(B, H, N) > (may_chunk(B, N) ? 256 : 416);
 }
 
-// x / d and the remainder, both wave-uniform and not negative, for a quotient below 2^20: one float product and its
-// correction, half the instructions of an integer division (scalar instructions wait for each other, and a workgroup's first
-// microsecond is little else).
-__device__ inline int uniform_div(int x, int d, int& rest) {
-  int k = __builtin_amdgcn_readfirstlane((int)((float)x * __builtin_amdgcn_rcpf((float)d)));
-  rest = x - k * d;
-  const int below = rest >> 31;
-  k += below;
-  rest += below & d;
-  const int above = rest >= d;
-  k += above;
-  rest -= above ? d : 0;
-  return k;
-}
-
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
-// c ? x : y of values (of two variables the operator yields a variable, which the compiler then looks for in memory)
-template <class T>
-__device__ __forceinline__ T pick(bool c, T x, T y) { return c ? x : y; }
 
 // Returns false if this workgroup has nothing to do.  Everything here is wave-uniform and
 // stays in scalar registers.

@@ -284,6 +284,13 @@ def test_tiles_dealt_by_feature(B, N, H, E):
     check_bwd(N, B, N, H, E, pad_tail=N // 4)
 
 
+@pytest.mark.parametrize("B,N,H,E", [(1, 2690, 2, 128), (13, 100, 6, 384), (3, 1111, 4, 128)])
+def test_last_token_tiles_dealt_one_by_one(B, N, H, E):
+    """Token tiles that are no multiple of eight, of one sequence and of several: the last ones go to all XCDs."""
+    check(N, B, N, H, E, pad_tail=N // 9)
+    check_bwd(N, B, N, H, E, pad_tail=N // 9)
+
+
 # tiles of 192 x 128 that two groups of wavefronts share: 16 token tiles of two sequences with one row in the last
 # (QKV), and 49 token tiles of one sequence (output)
 @pytest.mark.parametrize("B,N,H,E", [(2, 897, 12, 768), (1, 6145, 12, 768)])
