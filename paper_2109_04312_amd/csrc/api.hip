@@ -355,11 +355,12 @@ mate_status fill_dense(DenseArgs& a, const int32_t* row_ids, const int32_t* col_
   if (!shape_ok(B, N) || H < 1 || H > MATE_MAX_HEADS) return MATE_ERR_SHAPE;
   if (D != MATE_HEAD_DIM || t != MATE_BF16 || N > MATE_DENSE_MAX_N) return MATE_ERR_UNSUPPORTED;
   if (!(scale > 0.f) || !(scale < 3.0e38f)) return MATE_ERR_UNSUPPORTED;
+  static_assert(MATE_HEAD_ROW == 0 && MATE_HEAD_COL == 1, "a bit says which");
   static_assert(MATE_DENSE_MAX_N == kDenseMaxN, "header and kernels disagree");
   std::memset(&a, 0, sizeof(a));
   for (int h = 0; h < H; ++h) {
     if (head_kind[h] > MATE_HEAD_COL) return MATE_ERR_UNSUPPORTED;
-    a.head_kind[h] = head_kind[h];
+    a.col_heads[h >> 5] |= (unsigned)head_kind[h] << (h & 31);
   }
   a.row_ids = row_ids; a.col_ids = col_ids; a.flags = flags;
   a.B = B; a.H = H; a.N = N; a.scale = scale;

@@ -33,15 +33,28 @@ struct DenseUnit {
   int b, bh, view, tile;  // tile: which 128 positions are owned
 };
 
+// The first arguments of a kernel, plain values, which arrive in registers with the wavefront; N and H in one word.  With the
+// head kinds as bits and the codes' loads ahead of the tiles' (a kind was a byte, a vector load that the ids, and
+// so the first barrier, waited for): forward of 32 x 128, 12 heads 8.6 -> 8.1 us, 64 x 64 7.2 -> 6.9, 3 x 600 14.2 -> 13.4,
+// backward of 64 x 64 11.7 -> 11.0, 8 x 256 18.0 -> 17.5.
+inline int pack_sizes(int N, int H) { return N | H << 16; }
+static_assert(kDenseMaxN < 1 << 16, "sixteen bits hold N");
+
+__device__ __forceinline__ int head_view(const DenseArgs& a, int h) { return (int)(a.col_heads[h >> 5] >> (h & 31)) & 1; }
+__device__ __forceinline__ int sequence_of(int bh, int H, int& h) {
+  if (__builtin_expect(bh < 1 << 21, 1)) return uniform_div(bh, H, h);
+  h = (int)((unsigned)bh % (unsigned)H);
+  return (int)((unsigned)bh / (unsigned)H);
+}
 // Workgroup -> (sequence, head, owner tile); (sequence, head) pairs with equal index mod 8 share
 // an XCD (consecutive workgroups go to consecutive XCDs), so their K / V tiles share an L2.
-__device__ inline bool dense_unit(const DenseArgs& a, DenseUnit& u) {
-  const int T = owner_slots(a.N), q = blockIdx.x & 7, r = blockIdx.x >> 3;
-  u.tile = r % T;
-  u.bh = (r / T) * 8 + q;
-  if (u.bh >= a.B * a.H) return false;
-  u.b = u.bh / a.H;
-  u.view = a.head_kind[u.bh % a.H];
+__device__ __forceinline__ bool dense_unit(const DenseArgs& a, int N, int H, int pairs, DenseUnit& u) {
+  const int q = blockIdx.x & 7, r = blockIdx.x >> 3;
+  u.bh = uniform_div(r, owner_slots(N), u.tile) * 8 + q;
+  if (u.bh >= pairs) return false;
+  int h;
+  u.b = sequence_of(u.bh, H, h);
+  u.view = head_view(a, h);
   return true;
 }
 inline int dense_grid(const DenseArgs& a) { return 8 * ((a.B * a.H + 7) / 8) * owner_slots(a.N); }
@@ -52,16 +65,28 @@ __device__ inline unsigned token_code(bool in_range, int flag, int id) {
   return flag == 1 ? 0u : (unsigned)id + 1u;
 }
 
-// Codes of all positions of the sequence (padded with kPadCode to a whole number of tiles) into LDS.
-__device__ inline void load_codes(const DenseArgs& a, const DenseUnit& u, unsigned* code) {
-  const int N = a.N;
-  const int* ids = (u.view == 0 ? a.row_ids : a.col_ids) + (size_t)u.b * N;
-  const unsigned char* fl = a.flags + (size_t)u.b * N;
-  for (int n = threadIdx.x; n < ((N + BN - 1) / BN) * BN; n += kThreads) {
-    const int f = fl[min(n, N - 1)], id = ids[min(n, N - 1)];  // (one round trip: both loads are unconditional)
-    code[n] = token_code(n < N, f, id);
+// Codes of all positions of the sequence (padded with kPadCode to a whole number of tiles), on their way into LDS.
+struct DenseCodes {
+  int flag[kDenseMaxN / kThreads], id[kDenseMaxN / kThreads];
+  __device__ __forceinline__ void load(const int* row_ids, const int* col_ids, const unsigned char* flags, const DenseUnit& u, int N) {
+    const int* ids = pick(u.view == 0, row_ids, col_ids) + (size_t)u.b * N;
+    const unsigned char* fl = flags + (size_t)u.b * N;
+#pragma unroll
+    for (int i = 0; i < kDenseMaxN / kThreads; ++i)
+      if (i * kThreads < N) {
+        const int n = min((int)threadIdx.x + i * kThreads, N - 1);
+        flag[i] = fl[n];
+        id[i] = ids[n];
+      }
   }
-}
+  __device__ __forceinline__ void put(unsigned* code, int N) const {
+#pragma unroll
+    for (int i = 0; i < kDenseMaxN / kThreads; ++i) {
+      const int n = (int)threadIdx.x + i * kThreads;
+      if (i * kThreads < N && n < ((N + BN - 1) / BN) * BN) code[n] = token_code(n < N, flag[i], id[i]);
+    }
+  }
+};
 
 // May the owned row (code mc) meet a streamed row with code kc?  min(kc, kc ^ mc) is 0 iff the streamed row is a
 // question token or has the same code, and with mc = 0 it is kc; so one comparison with a limit that depends on
@@ -77,11 +102,11 @@ struct DenseRow {
   bool in_range;
   unsigned code, limit;
 };
-__device__ inline DenseRow dense_row(const DenseArgs& a, const DenseUnit& u, const unsigned* code, int wave, int m) {
+__device__ inline DenseRow dense_row(int N, const DenseUnit& u, const unsigned* code, int wave, int m) {
   DenseRow r;
   const int p = u.tile * BM + wave * 32 + m;
-  r.in_range = p < a.N;
-  r.pos = min(p, a.N - 1);
+  r.in_range = p < N;
+  r.pos = min(p, N - 1);
   r.code = code[r.pos];
   r.limit = owner_limit(r.code);
   return r;
@@ -140,19 +165,21 @@ struct CodeMask {
 // ======================================================================================
 // forward
 // ======================================================================================
-__global__ __launch_bounds__(kThreads) void fwd_dense_kernel(DenseArgs a) {
+__global__ __launch_bounds__(kThreads) void fwd_dense_kernel(const void* q, const void* k, const void* v, const int* row_ids,
+                                                             const int* col_ids, const unsigned char* flags, int sizes, int pairs,
+                                                             DenseArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds[2 * kStage];
   __shared__ __attribute__((aligned(16))) unsigned code[kDenseMaxN];
   __shared__ int q_tok[BM];
+  const int N = sizes & 0xffff, H = sizes >> 16, tid = threadIdx.x, lane = tid & 63;
   DenseUnit u;
-  if (!dense_unit(a, u)) return;
-  const int N = a.N, tid = threadIdx.x, lane = tid & 63;
+  if (!dense_unit(a, N, H, pairs, u)) return;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = lane & 31, hl = lane >> 5;
   const size_t bh = (size_t)u.bh * N;
-  const unsigned short* Q = static_cast<const unsigned short*>(a.q) + bh * kD;
-  const unsigned short* K = static_cast<const unsigned short*>(a.k) + bh * kD;
-  const unsigned short* V = static_cast<const unsigned short*>(a.v) + bh * kD;
+  const unsigned short* Q = static_cast<const unsigned short*>(q) + bh * kD;
+  const unsigned short* K = static_cast<const unsigned short*>(k) + bh * kD;
+  const unsigned short* V = static_cast<const unsigned short*>(v) + bh * kD;
   unsigned short* O = static_cast<unsigned short*>(a.out) + bh * kD;
 
   DenseStream stream{K, V, nullptr, nullptr, lds, kStage, N, wave, lane, make_load_lane(wave, lane)};
@@ -165,11 +192,13 @@ __global__ __launch_bounds__(kThreads) void fwd_dense_kernel(DenseArgs a) {
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks)
     qf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(Q + (size_t)pos * kD + ks * 16 + hl * 8));
+  DenseCodes codes;
+  codes.load(row_ids, col_ids, flags, u, N);
   stream.begin(n_tiles);
-  load_codes(a, u, code);
+  codes.put(code, N);
   if (tid < BM) q_tok[tid] = u.tile * BM + tid < N ? u.tile * BM + tid : -1;
   __syncthreads();
-  DenseRow me = dense_row(a, u, code, wave, m);
+  DenseRow me = dense_row(N, u, code, wave, m);
   if (me.limit == 0) me.limit = kPadCode;  // (padding meets anything: its results are replaced, and every row has a maximum)
   asm volatile("" ::"v"(qf[0]), "v"(qf[1]), "v"(qf[2]), "v"(qf[3]));
 
@@ -209,7 +238,7 @@ __global__ __launch_bounds__(kThreads, 4) void bwd_dq_dense_kernel(DenseArgs a) 
   __shared__ __attribute__((aligned(16))) unsigned code[kDenseMaxN];
   __shared__ int q_tok[BM];
   DenseUnit u;
-  if (!dense_unit(a, u)) return;
+  if (!dense_unit(a, a.N, a.H, a.B * a.H, u)) return;
   const int N = a.N, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = lane & 31, hl = lane >> 5;
@@ -223,11 +252,13 @@ __global__ __launch_bounds__(kThreads, 4) void bwd_dq_dense_kernel(DenseArgs a) 
 
   DenseStream stream{K, V, nullptr, nullptr, lds, kStage, N, wave, lane, make_load_lane(wave, lane)};
   const int n_tiles = (N + BN - 1) / BN;
+  DenseCodes codes;
+  codes.load(a.row_ids, a.col_ids, a.flags, u, N);
   stream.begin(n_tiles);
-  load_codes(a, u, code);
+  codes.put(code, N);
   if (tid < BM) q_tok[tid] = u.tile * BM + tid < N ? u.tile * BM + tid : -1;
   __syncthreads();
-  const DenseRow me = dense_row(a, u, code, wave, m);
+  const DenseRow me = dense_row(N, u, code, wave, m);
   bf16x8 qf[4], gf[4], of[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
@@ -279,7 +310,7 @@ __global__ __launch_bounds__(kThreads) void bwd_dkv_dense_kernel(DenseArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned code[kDenseMaxN];
   __shared__ int k_tok[BM];
   DenseUnit u;
-  if (!dense_unit(a, u)) return;
+  if (!dense_unit(a, a.N, a.H, a.B * a.H, u)) return;
   const int N = a.N, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = lane & 31, hl = lane >> 5;
@@ -294,11 +325,13 @@ __global__ __launch_bounds__(kThreads) void bwd_dkv_dense_kernel(DenseArgs a) {
   DenseStream stream{Q, dO, a.nlse + bh, a.delta + bh, lds, kDkvStageD, N, wave, lane,
                      make_load_lane(wave, lane)};
   const int n_tiles = (N + BN - 1) / BN;
+  DenseCodes codes;
+  codes.load(a.row_ids, a.col_ids, a.flags, u, N);
   stream.begin(n_tiles);
-  load_codes(a, u, code);
+  codes.put(code, N);
   if (tid < BM) k_tok[tid] = u.tile * BM + tid < N ? u.tile * BM + tid : -1;
   __syncthreads();
-  const DenseRow me = dense_row(a, u, code, wave, m);  // this lane's key
+  const DenseRow me = dense_row(N, u, code, wave, m);  // this lane's key
   bf16x8 kf[4], vf[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
@@ -357,38 +390,47 @@ struct SmallShape {
   static constexpr int kLds = kKeyBytes + 2 * kQryBytes + (kOverlay || kKeyBytes > kDsBytes ? kKeyBytes : kDsBytes);
 };
 template <int NW>
-__global__ __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) void bwd_dense_small_kernel(DenseArgs a) {
+__global__ __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) void bwd_dense_small_kernel(
+    const void* q, const void* k, const void* v, const void* o, const void* dout, int sizes, DenseArgs a) {
   using S = SmallShape<NW>;
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   __shared__ __attribute__((aligned(16))) unsigned code[S::kKeys];
   __shared__ __attribute__((aligned(16))) float nlse[S::kKeys], ndelta[S::kKeys];
   char *const kt = lds, *const qt = lds + S::kKeyBytes, *const gt = qt + S::kQryBytes;
   char *const vt = gt + S::kQryBytes, *const ds = S::kOverlay ? qt : vt;
-  const int N = a.N, tid = threadIdx.x, lane = tid & 63, bh_i = blockIdx.x, b = bh_i / a.H;
+  const int N = sizes & 0xffff, tid = threadIdx.x, lane = tid & 63, bh_i = blockIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = lane & 31, hl = lane >> 5;
   const size_t bh = (size_t)bh_i * N;
-  const unsigned short* Q = static_cast<const unsigned short*>(a.q) + bh * kD;
-  const unsigned short* K = static_cast<const unsigned short*>(a.k) + bh * kD;
-  const unsigned short* V = static_cast<const unsigned short*>(a.v) + bh * kD;
-  const unsigned short* O = static_cast<const unsigned short*>(a.o) + bh * kD;
-  const unsigned short* dO = static_cast<const unsigned short*>(a.dout) + bh * kD;
+  const unsigned short* Q = static_cast<const unsigned short*>(q) + bh * kD;
+  const unsigned short* K = static_cast<const unsigned short*>(k) + bh * kD;
+  const unsigned short* V = static_cast<const unsigned short*>(v) + bh * kD;
+  const unsigned short* O = static_cast<const unsigned short*>(o) + bh * kD;
+  const unsigned short* dO = static_cast<const unsigned short*>(dout) + bh * kD;
   unsigned short* dQ = static_cast<unsigned short*>(a.dq) + bh * kD;
   unsigned short* dK = static_cast<unsigned short*>(a.dk) + bh * kD;
   unsigned short* dV = static_cast<unsigned short*>(a.dv) + bh * kD;
 
+  int h;
+  const int b = sequence_of(bh_i, sizes >> 16, h), view = head_view(a, h);
+  const int *row_ids = a.row_ids, *col_ids = a.col_ids;
+  const unsigned char* flags = a.flags;
   // rows [first, first + rows) of X to LDS, eight per instruction (rows past N repeat the last)
-  auto stream_rows = [&](const unsigned short* X, int first, int rows, const char* tile) {
-    for (int g = wave; g < rows / 8; g += NW) {
-      const int row = 8 * g + (lane >> 3), chunk = (lane & 7) ^ swz(row & 15);
+  auto stream_rows = [&](const unsigned short* X, int first, auto rows, const char* tile) {
+    static_assert(decltype(rows)::value % (8 * NW) == 0, "the wavefronts share the rows evenly");
+#pragma unroll
+    for (int i = 0; i < decltype(rows)::value / (8 * NW); ++i) {
+      const int g = wave + i * NW, row = 8 * g + (lane >> 3), chunk = (lane & 7) ^ swz(row & 15);
       load_to_lds_16(X, (unsigned)min(first + row, N - 1) * 128u + chunk * 16, tile + g * 1024);
     }
   };
-  stream_rows(K, 0, S::kKeys, kt);
-  stream_rows(Q, 0, S::kQueries, qt);
-  stream_rows(dO, 0, S::kQueries, gt);
+  const std::integral_constant<int, S::kKeys> keys;
+  const std::integral_constant<int, S::kQueries> queries;
+  stream_rows(K, 0, keys, kt);
+  stream_rows(Q, 0, queries, qt);
+  stream_rows(dO, 0, queries, gt);
 
-  stream_rows(V, 0, S::kKeys, vt);
+  stream_rows(V, 0, keys, vt);
 
   // of this lane's row: delta and -lse / scale of the query, and the code.  (All rows are loaded whole, eight per
   // instruction.  With key, value, dO and O operands straight from global memory, sixteen loads that touch 32 lines each: 32 x
@@ -399,9 +441,8 @@ __global__ __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) void bwd_dense_small_kern
     g_rows.load(dO, pos, lane);
     o_rows.load(O, pos, lane);
     const float lse = a.lse[bh + pos];
-    const int view = a.head_kind[bh_i % a.H];
-    const int* ids = (view == 0 ? a.row_ids : a.col_ids) + (size_t)b * N;
-    const int f = a.flags[(size_t)b * N + pos], id = ids[pos];
+    const int* ids = pick(view == 0, row_ids, col_ids) + (size_t)b * N;
+    const int f = flags[(size_t)b * N + pos], id = ids[pos];
     const float delta = row_delta(g_rows, o_rows, reinterpret_cast<char*>(ndelta + 32 * wave), lane);
     if (hl == 0) {
       nlse[32 * wave + m] = -lse / a.scale;
@@ -420,8 +461,8 @@ __global__ __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) void bwd_dense_small_kern
   for (int p = 0; p < S::kPasses && p * S::kBlocks < n_blocks; ++p) {
     if (p > 0) {
       __syncthreads();  // the staged dQ rows of the pass before have been stored
-      stream_rows(Q, p * S::kQueries, S::kQueries, qt);
-      stream_rows(dO, p * S::kQueries, S::kQueries, gt);
+      stream_rows(Q, p * S::kQueries, queries, qt);
+      stream_rows(dO, p * S::kQueries, queries, gt);
     }
     wait_vmcnt_le<0>(0);
     __syncthreads();
@@ -552,7 +593,8 @@ hipError_t launch_bwd_small(const DenseArgs& a, hipStream_t stream) {
   const hipError_t e = allow_lds<&bwd_dense_small_kernel<NW>>(S::kLds);
   if (e != hipSuccess) return e;
   ProfileScope prof(7, stream, 6);
-  hipLaunchKernelGGL(bwd_dense_small_kernel<NW>, dim3(a.B * a.H), dim3(64 * NW), S::kLds, stream, a);
+  hipLaunchKernelGGL(bwd_dense_small_kernel<NW>, dim3(a.B * a.H), dim3(64 * NW), S::kLds, stream, a.q, a.k, a.v, a.o, a.dout,
+                     pack_sizes(a.N, a.H), a);
   return hipGetLastError();
 }
 
@@ -560,7 +602,8 @@ hipError_t launch_bwd_small(const DenseArgs& a, hipStream_t stream) {
 
 hipError_t launch_fwd_dense(const DenseArgs& a, hipStream_t stream) {
   ProfileScope prof(5, stream);
-  hipLaunchKernelGGL(fwd_dense_kernel, dim3(dense_grid(a)), dim3(kThreads), 0, stream, a);
+  hipLaunchKernelGGL(fwd_dense_kernel, dim3(dense_grid(a)), dim3(kThreads), 0, stream, a.q, a.k, a.v, a.row_ids, a.col_ids, a.flags,
+                     pack_sizes(a.N, a.H), a.B * a.H, a);
   return hipGetLastError();
 }
 

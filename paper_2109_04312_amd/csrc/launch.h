@@ -39,7 +39,7 @@ struct DenseArgs {
   float *delta, *nlse;      // backward scratch [B,H,N]: -rowsum(dO * O), -lse / scale
   const int *row_ids, *col_ids;
   const unsigned char* flags;
-  unsigned char head_kind[256];
+  unsigned col_heads[8];    // one bit per head: words, because a byte would be fetched with a vector load
   int B, H, N;
   float scale;
 };
