@@ -311,8 +311,9 @@ __device__ __forceinline__ void merge_dq(const AttnArgs& a, int bh_i, char* stag
 
 // The first `n_merge` workgroups (a multiple of eight, so that the unit queues keep their XCDs) merge
 // dQ partials: a few microseconds each, out of the way before the kernel's own tail.
+// (168 registers: three workgroups per CU; with two the kernel takes 15 to 20 % longer)
 template <bool kJoin>
-__global__ __launch_bounds__(kThreads) void bwd_dkv_mfma_kernel(MATE_UNIT_LISTS, AttnArgs a, int n_merge) {
+__global__ __launch_bounds__(kThreads, 3) void bwd_dkv_mfma_kernel(MATE_UNIT_LISTS, AttnArgs a, int n_merge) {
   __shared__ __attribute__((aligned(1024))) char lds[kStages * kDkvStage];
   __shared__ int idx_ring[kIdxSlots][BN];
   __shared__ int row_tok[BM];
@@ -359,7 +360,7 @@ __global__ __launch_bounds__(kThreads) void bwd_delta_kernel(AttnArgs a) {
   }
 }
 template <bool kJoin>
-__global__ __launch_bounds__(kThreads) void bwd_both_mfma_kernel(MATE_UNIT_LISTS, AttnArgs a) {
+__global__ __launch_bounds__(kThreads, 3) void bwd_both_mfma_kernel(MATE_UNIT_LISTS, AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds[kStages * kDkvStage];
   __shared__ int idx_ring[kIdxSlots][BN];
   __shared__ int row_tok[BM];

@@ -144,6 +144,7 @@ struct DenseStream {
 // The dense-mask rule as a Mask of tile_bodies.h: the pair is kept iff the two tokens' codes say
 // so.  `codes` points at the tile's 64 codes in LDS, offset by this lane half's 4 hl.
 struct CodeMask {
+  static constexpr bool kPairs = false;
   const unsigned* codes;
   unsigned my_code, limit;
   unsigned k[16];

@@ -8,11 +8,15 @@
 //   mask.load(blk)     fetch what keep() needs for the 32-row block blk of the tile
 //   mask.keep(c, x, o) x if the pair (this lane's owned row, streamed row c_row(c) of the loaded
 //                      block) belongs to the pattern, else o.  c = accumulator register 0..15
+//   Mask::kPairs       the mask also has load_pairs(blk) and pair_mask(i): ones where registers 2 i (low half of the
+//                      word) and 2 i + 1 belong to the pattern, for words of two bf16 values
 //
 // Layout everywhere: C tiles have rows = streamed rows, columns = the wavefront's 32 owned rows
 // (lane m = owned row, lane half hl), so per-owned-row quantities are per-lane scalars.
 #pragma once
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "d2l.h"
 #include "mfma_common.h"
@@ -44,6 +48,7 @@ struct WindowMask {
   const int lo, hi;     // else this lane's
   const int end;
   const int u_lo, u_hi, a_lo, a_hi;  // wave-uniform, relative to base: union and intersection of the rows' windows
+  static constexpr bool kPairs = true;
   int one = 1;         // width of the extract; its value is hidden from the compiler, which would turn extract
                        // and select into test, compare and conditional move
   unsigned bits = 0;   // bit 8 (c >> 2) + (c & 3): register c of the loaded block is inside
@@ -63,6 +68,20 @@ struct WindowMask {
     // (31 of 32 bits are enough: the highest one asked for is 27)
     const int d = d0(), first = min(max(-d - 32 * blk, 0), 31), last = min(max(len() - d - 32 * blk, 0), 31);
     bits = ((1u << last) - 1u) & ~((1u << first) - 1u);
+  }
+  // Two values rounded to bf16 share a word, and so do the two halves of its mask: the signs of a word's two
+  // halves, spread over them by one byte permutation, from a register that has every pair's bits 16 apart.  For P and dS four
+  // instructions per pair of each where masking them one by one takes six (dK/dV of 8 x 2048 with long cells 77.0 -> 75.0 us, of
+  // 2 x 8192 82.0 -> 79.7, of 16 ragged sequences of 4096 228 -> 222); for dS or P alone three where it takes four,
+  // which gained nothing.
+  unsigned pairs[2];   // of registers 0..7 and 8..15: bit 8 g + 2 i and that + 16: pair i of group g
+  __device__ __forceinline__ void load_pairs(int blk) {
+    load(blk);
+    pairs[0] = (bits & 0xffffu) | ((bits << 15) & 0xffff0000u);
+    pairs[1] = (bits >> 16) | ((bits >> 1) & 0xffff0000u);
+  }
+  __device__ __forceinline__ unsigned pair_mask(int i) const {
+    return __builtin_amdgcn_perm(0u, pairs[i >> 2] << (15 - 8 * ((i >> 1) & 1) - 2 * (i & 1)), 0x09090808u);
   }
   __device__ __forceinline__ float keep(int c, float x, float other) const {
     const unsigned in = (unsigned)__builtin_amdgcn_sbfe((int)bits, 8 * (c >> 2) + (c & 3), one);
@@ -200,12 +219,14 @@ __device__ __forceinline__ void fwd_tile(unsigned tile, const bf16x8 (&qf)[4], c
   const float m_old = m_run;
   const float l_tile = both ? fwd_probs_new_max<2>(0, k, qf, mask, sc, m_run, pb)
                             : fwd_probs_new_max<1>(blk0, k, qf, mask, sc, m_run, pb);
-  const float alpha = m_run == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m_old - m_run) * sc);
-  l_run *= alpha;
+  if (__any(m_old != -INFINITY)) {  // (not for a wavefront's first tile: there is nothing to scale)
+    const float alpha = m_run == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m_old - m_run) * sc);
+    l_run *= alpha;
 #pragma unroll
-  for (int db = 0; db < 2; ++db)
+    for (int db = 0; db < 2; ++db)
 #pragma unroll
-    for (int c = 0; c < 16; ++c) o_acc[db][c] *= alpha;
+      for (int c = 0; c < 16; ++c) o_acc[db][c] *= alpha;
+  }
   if (ref == kMissing && !__any(m_run == -INFINITY)) ref = kFixed;
   add(pb, l_tile);
 }
@@ -276,7 +297,9 @@ __device__ __forceinline__ void dkv_tile(unsigned tile, const float* lse_row, co
       s[c] = __builtin_amdgcn_exp2f(s[c] * sc);  // P
       dp[c] *= s[c];                             // dS
     }
-    if (!mask.full(ib)) {  // wave-uniform: zero the pairs outside the pattern
+    // wave-uniform: zero the pairs outside the pattern
+    constexpr bool kPairs = std::remove_reference<Mask>::type::kPairs;
+    if (!kPairs && !mask.full(ib)) {
       mask.load(ib);
 #pragma unroll
       for (int c = 0; c < 16; ++c) {
@@ -284,9 +307,26 @@ __device__ __forceinline__ void dkv_tile(unsigned tile, const float* lse_row, co
         dp[c] = mask.keep(c, dp[c], 0.f);
       }
     }
+    unsigned pw[8], dw[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      pw[i] = pack2(s[2 * i], s[2 * i + 1]);
+      dw[i] = pack2(dp[2 * i], dp[2 * i + 1]);
+    }
+    if constexpr (kPairs)
+      if (!mask.full(ib)) {
+        mask.load_pairs(ib);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const unsigned in = mask.pair_mask(i);
+          pw[i] &= in;
+          dw[i] &= in;
+        }
+      }
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {
-      const bf16x8 p8 = pack8(s, 8 * tt), ds8 = pack8(dp, 8 * tt);
+      const bf16x8 p8 = as_bf16x8(make_uint4(pw[4 * tt], pw[4 * tt + 1], pw[4 * tt + 2], pw[4 * tt + 3]));
+      const bf16x8 ds8 = as_bf16x8(make_uint4(dw[4 * tt], dw[4 * tt + 1], dw[4 * tt + 2], dw[4 * tt + 3]));
       const int q_at = (ib * 32 + tt * 16) * 128, g_at = q_at + kTileBytes;
 #pragma unroll
       for (int db = 0; db < 2; ++db) {
