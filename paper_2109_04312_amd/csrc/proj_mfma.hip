@@ -512,8 +512,14 @@ hipError_t launch_proj(ProjArgs a, int kernel_id, hipStream_t stream) {
 // at every stage.  us, before and with it: 768 -> 2304 at 1999 tokens 15.4 and 14.6, 1024 -> 3072 at 1500 19.0 and
 // 17.2, 1536 -> 4608 at 1000 28.2 and 24.0, 768 -> 768 at 8192 15.6 and 14.4; in a second round it loses (768 -> 2304
 // at 2300 tokens 16.2 and 25.4), which its constant for two tiles says.
+// 192 x 256 and 256 x 192, eight wavefronts, read 0.9 of what a CU loads for as many products in 192 x 128 and have a third more
+// tiles than 256 x 256: for sizes whose tiles are one round.  us, before and with them: 768 -> 2304 at 8 x 512 23.1 -> 22.1, at
+// 5 x 929 22.7 -> 21.3, 1024 -> 3072 at 4000 28.1 -> 25.3, 1024 -> 1024 at 2 x 4344 28.0 -> 23.5, at 10752 29.4 -> 26.4, d_o
+// there with dW 55.5 -> 52.2.
 //                        features x tokens, wavefronts, stages, workgroups per CU, groups
 using Proj256 = Shape<4, 4, 2, 4, 2, 1>;      // 256 x 256
+using Proj192x256 = Shape<3, 4, 2, 4, 2, 1>;  // 192 x 256  (plain weights, as below)
+using Proj256x192 = Shape<4, 3, 4, 2, 2, 1>;  // 256 x 192
 using Proj192 = Shape<3, 2, 2, 2, 2, 2>;      // 192 x 128  (plain weights; its wavefronts' 96 features are not whole tiles)
 using Proj192x2 = Shape<3, 2, 2, 2, 2, 1, 2>; // (all 160 KB of a compute unit's LDS)
 using Proj128 = Shape<2, 2, 2, 2, 2, 2>;      // 128 x 128
@@ -539,6 +545,12 @@ ProjChoice choose_proj(const ProjArgs& a) {
     if (cost < best.cost) best = {cost, launch, groups};
   };
   offer(proj_cost<Proj256>(a, 1.37, 3.14, 5.33), launch_proj<Proj256, kHeadTok, kTransposedW>, 1);
+  // In one round only: in a second one, where sequences end in padding, 256 x 256 has skipped enough tiles to need none (1024 ->
+  // 3072 at 12000 tokens, a fifth of them padding, 65.7 and 71.4 us).  dX, whose weights are four times as long, gains nothing.
+  if constexpr (!kTransposedW)
+    if (tiles_of<Proj192x256>(a) <= 256) offer(proj_cost<Proj192x256>(a, 1.0, 0, 6.8), launch_proj<Proj192x256, kHeadTok, kTransposedW>, 1);
+  if constexpr (!kTransposedW || !kHeadTok)
+    if (tiles_of<Proj256x192>(a) <= 256) offer(proj_cost<Proj256x192>(a, 1.0, 0, 6.8), launch_proj<Proj256x192, kHeadTok, kTransposedW>, 1);
   if constexpr (!kTransposedW)
     // (beyond 4608 features it takes up to 23 % more than its constants say)
     if (a.F % Proj192::kRowsA == 0 && a.F <= 4608) {

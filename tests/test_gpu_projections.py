@@ -284,6 +284,13 @@ def test_tiles_dealt_by_feature(B, N, H, E):
     check_bwd(N, B, N, H, E, pad_tail=N // 4)
 
 
+@pytest.mark.parametrize("B,N,H,E", [(5, 901, 12, 768), (1, 3999, 16, 1024), (2, 4225, 16, 1024)])
+def test_one_round_of_eight_wavefronts(B, N, H, E):
+    """Tiles of 192 x 256 (QKV; the last a token or a feature block) and of 256 x 192 (output, d_o) in one round."""
+    check(N, B, N, H, E, pad_tail=N // 7)
+    check_bwd(N, B, N, H, E, pad_tail=N // 7)
+
+
 @pytest.mark.parametrize("B,N,H,E", [(1, 2690, 2, 128), (13, 100, 6, 384), (3, 1111, 4, 128)])
 def test_last_token_tiles_dealt_one_by_one(B, N, H, E):
     """Token tiles that are no multiple of eight, of one sequence and of several: the last ones go to all XCDs."""
