@@ -33,7 +33,7 @@
 // 10.3 -> 7.0, two of 8192 14.3 -> 11.0.  Since then a lane's inputs are one load each and leave before anything else is
 // worked out (sequence_loads.h), all arguments arrive in registers, a slot's window is written by the token that takes the
 // slot (it knows its segment; a binary search per slot before), and the unit list finds its segments in three rounds
-// of reads instead of nine: 5.1 -> 5.0, 5.6 -> 5.2, 7.1 -> 6.1, 11.0 -> 9.5, one sequence of 16384 16.9 -> 14.2.
+// of reads instead of nine, in one wavefront without a barrier where it is short: 5.1 -> 4.3, 5.6 -> 4.4, 7.1 -> 5.4, 11.0 -> 9.1, one sequence of 16384 16.9 -> 13.7.
 //
 // Bucketed mode (the approximation of Section 3.1: a global part of at most G tokens, the rest
 // of the head's order in buckets of R, a bucket meeting itself and its two neighbours): the
@@ -43,6 +43,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "launch.h"
 #include "seg_layout.h"
@@ -424,10 +425,10 @@ __global__ __launch_bounds__(64 * kSegWaves) void build_segments_kernel(
     }
     if (k != K) return;
     // ---- work units of the attention kernels (the workgroup without a chunk) ---------------------
-    // question-token owners (the same for both views), if possible by wavefronts that list no units
-    constexpr int kFirst = kSegThreads > (int)kBins ? (int)kBins : 0;
-    static_assert(kMaxTiles <= kSegThreads - kFirst, "a thread per record");
-    if (view == 0 && tid >= kFirst && tid - kFirst < lay.tiles) {
+    // question-token owners (the same for both views), by the last wavefronts, which seldom list units
+    constexpr int kFirst = kSegThreads - kMaxTiles;
+    auto list_question_owners = [&]() {
+      if (view != 0 || tid < kFirst || tid - kFirst >= lay.tiles) return;
       const int rec = tid - kFirst;
       const GlobalSplit gs = global_split(G, L, B, N);
       int4 q0 = make_int4(UNIT_NONE, 0, 0, 0), q1 = make_int4(0, 0, -1, 0);
@@ -441,9 +442,106 @@ __global__ __launch_bounds__(64 * kSegWaves) void build_segments_kernel(
       }
       gunit[2 * rec] = q0;
       gunit[2 * rec + 1] = q1;
-    }
+    };
+    // The record of the unit that owns slots [t0, end), without its place in the list.  Its first and last segments are the
+    // last ones that begin at or before t0 and end - 1: rounds of seven reads at a time (three for up to 512 segments),
+    // where a binary search is up to nine rounds, of 50 ns each.
+    auto local_unit = [&](int t0, int end, auto first_step, int4& r0, int4& r1) {
+      int first_seg = 0, last_seg = 0;
+#pragma unroll
+      for (int step = decltype(first_step)::value; step > 0; step /= 8) {
+        int f[7], l[7];
+#pragma unroll
+        for (int j = 0; j < 7; ++j) {   // (sstart[S] = L is beyond every slot)
+          f[j] = sstart[min(first_seg + (j + 1) * step, S)];
+          l[j] = sstart[min(last_seg + (j + 1) * step, S)];
+        }
+        int f_n = 0, l_n = 0;
+#pragma unroll
+        for (int j = 0; j < 7; ++j) {
+          f_n += f[j] <= t0;
+          l_n += l[j] < end;
+        }
+        first_seg += f_n * step;
+        last_seg += l_n * step;
+      }
+      const int lo = bounded(t0, sstart[first_seg], L).x, hi = bounded(end - 1, 0, sstart[last_seg + 1]).y;
+      r0 = make_int4(UNIT_LOCAL, t0, lo, hi);
+      r1.y = n_t0 + (hi - lo + BN - 1) / BN;
+      r1.w = end;
+    };
     // A run is a segment of at least kBigSegment slots, or the shorter segments between two such
     // segments; units are 128-slot pieces of runs (see the general path below for why).
+    // Up to 64 records (5248 positions) and 128 segments: one wavefront lists them, without a barrier, kEach consecutive segments and one record to
+    // a lane.  (us with the workgroup's scans below and with this: one sequence of 128 4.9 and 4.3, of 512 5.2 and 4.4, of 1999
+    // with 100 rows 6.0 and 5.4, 8 of 2048 6.6 and 5.7; with eight segments to a lane, for up to 512, the scans are faster: 5.7 and 5.9.)
+    auto list_units = [&](auto each) {
+      constexpr int kEach = decltype(each)::value;
+      int start[kEach + 1];
+#pragma unroll
+      for (int e = 0; e <= kEach; ++e) start[e] = sstart[min(kEach * lane + e, S)];
+      const int before = sstart[max(min(kEach * lane, S) - 1, 0)];
+      unsigned cuts = 0;
+      int first_start = L;   // of the lane's first run
+#pragma unroll
+      for (int e = kEach - 1; e >= 0; --e) {
+        const int i = kEach * lane + e, last = e ? start[e - 1] : before;
+        if (i < S && (i == 0 || start[e + 1] - start[e] >= kBigSegment || start[e] - last >= kBigSegment)) {
+          cuts |= 1u << e;
+          first_start = start[e];
+        }
+      }
+      const unsigned long long lanes = __ballot(cuts != 0), later = lane < 63 ? lanes >> (lane + 1) : 0;
+      const int next_start = __shfl(first_start, later ? lane + __ffsll((long long)later) : lane, 64);
+      int run_end = later ? next_start : L, units_of[kEach], mine = 0;
+#pragma unroll
+      for (int e = kEach - 1; e >= 0; --e) {
+        const bool cut = (cuts >> e) & 1u;
+        units_of[e] = cut ? (run_end - start[e] + kTileSlots - 1) / kTileSlots : 0;
+        run_end = cut ? start[e] : run_end;
+        mine += units_of[e];
+      }
+      const int upto = wave_scan(mine);
+      int n_units = __builtin_amdgcn_readlane(upto, 63);
+      if (n_units + n_pt <= lay.units) {
+        int at = upto - mine;
+#pragma unroll
+        for (int e = 0; e < kEach; ++e)
+          for (int i = 0; i < units_of[e]; ++i) head_pos[at++] = (unsigned short)(start[e] + i * kTileSlots);
+      } else {  // more records than the buffer has: every 128 slots regardless of segments
+        n_units = (L + kTileSlots - 1) / kTileSlots;
+        if (lane < n_units) head_pos[lane] = (unsigned short)(lane * kTileSlots);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      int4 r0 = make_int4(UNIT_NONE, 0, 0, 0), r1 = make_int4(0, 0, -1, 0);
+      if (lane < n_units) {
+        const int t0 = min((int)head_pos[lane], L - 1);
+        const int end = min(max(lane + 1 < n_units ? (int)head_pos[lane + 1] : L, t0 + 1), min(L, t0 + kTileSlots));
+        local_unit(t0, end, std::integral_constant<int, kEach == 1 ? 8 : 64>(), r0, r1);
+      } else if (lane < n_units + n_pt) {
+        r0 = make_int4(UNIT_PAD, (lane - n_units) * kPadSlots, 0, 0);
+      }
+      int place = lane;
+      if (lane < n_units) {   // longest streamed side first, ties in slot order
+        place = 0;
+        for (int j = 0; j < n_units; ++j) {
+          const int other = __builtin_amdgcn_readlane(r1.y, j);
+          place += other > r1.y || (other == r1.y && j < lane);
+        }
+      }
+      if (lane < lay.units) {
+        unit[2 * place] = r0;
+        unit[2 * place + 1] = r1;
+      }
+    };
+    if (lay.units <= 64 && S <= 128) {
+      if (wave != 0) list_question_owners();
+      else if (S <= 64) list_units(std::integral_constant<int, 1>());
+      else list_units(std::integral_constant<int, 2>());
+      return;
+    }
+    // More: the workgroup, a segment and a record to a thread.
     int* run_start = seg_tmp[1];
     bool cut = false;
     if (tid < S) {
@@ -469,31 +567,8 @@ __global__ __launch_bounds__(64 * kSegWaves) void build_segments_kernel(
     if (tid < n_units) {
       const int t0 = min((int)head_pos[tid], L - 1);
       const int end = min(max(tid + 1 < n_units ? (int)head_pos[tid + 1] : L, t0 + 1), min(L, t0 + kTileSlots));
-      // their segments: the last that begin at or before them (S is at most 512; three rounds of seven reads at a
-      // time, where a binary search is up to nine rounds, of 50 ns each)
-      int first_seg = 0, last_seg = 0;
       static_assert(kBins == 8 * 8 * 8, "three digits");
-#pragma unroll
-      for (int step = 64; step > 0; step /= 8) {
-        int f[7], l[7];
-#pragma unroll
-        for (int j = 0; j < 7; ++j) {   // (sstart[S] = L is beyond every slot)
-          f[j] = sstart[min(first_seg + (j + 1) * step, S)];
-          l[j] = sstart[min(last_seg + (j + 1) * step, S)];
-        }
-        int f_n = 0, l_n = 0;
-#pragma unroll
-        for (int j = 0; j < 7; ++j) {
-          f_n += f[j] <= t0;
-          l_n += l[j] < end;
-        }
-        first_seg += f_n * step;
-        last_seg += l_n * step;
-      }
-      const int lo = bounded(t0, sstart[first_seg], L).x, hi = bounded(end - 1, 0, sstart[last_seg + 1]).y;
-      r0 = make_int4(UNIT_LOCAL, t0, lo, hi);
-      r1.y = n_t0 + (hi - lo + BN - 1) / BN;
-      r1.w = end;
+      local_unit(t0, end, std::integral_constant<int, 64>(), r0, r1);
       unit_len[tid] = (unsigned short)r1.y;
     }
     lds_barrier();
@@ -513,6 +588,7 @@ __global__ __launch_bounds__(64 * kSegWaves) void build_segments_kernel(
       unit[2 * place] = r0;
       unit[2 * place + 1] = r1;
     }
+    list_question_owners();
     return;
   }
   if (k != 0) return;   // ids of 512 and more: the first workgroup sorts alone

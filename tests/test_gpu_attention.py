@@ -205,6 +205,21 @@ def test_more_unit_cuts_than_records(id_step):
     check_workload(w, backward=True)
 
 
+@pytest.mark.parametrize("segments,N", [(63, 500), (64, 500), (65, 700), (128, 700), (129, 700), (128, 2000)])
+def test_units_of_as_many_segments_as_lanes(segments, N):
+    """Work units listed by one wavefront (a segment or two to a lane) and by all: segment counts beside 64 and 128, with a
+    long segment among short ones in each view."""
+    rng = np.random.default_rng(segments + N)
+    ids = np.sort(np.concatenate([np.arange(segments), rng.integers(0, segments, N - segments)]))
+    row = np.stack([np.where(rng.random(N) < 0.4, segments // 2, ids), rng.permutation(ids)]).astype(np.int32)
+    col = np.stack([rng.permutation(ids), np.where(rng.random(N) < 0.3, 0, ids)]).astype(np.int32)
+    flags = (rng.random((2, N)) < 0.05).astype(np.uint8)
+    flags[1, N - 40:] = synth.TOK_PAD
+    q, k, v, do = synth.draw_tensors(rng, 2, 2, N, 64, "bf16", 4)
+    w = synth.Workload(f"lanes{segments}", "bf16", synth.Structure(row, col, flags), np.array([ROW, COL], np.uint8), q, k, v, do, 0.125)
+    check_workload(w, backward=True)
+
+
 def test_head_kind_mix_and_order():
     # any assignment of kinds to heads, not only "first half rows"
     w = small_workload(8, "bf16", B=1, N=260, H=5, max_rows=10, max_cols=5, max_global=9)
