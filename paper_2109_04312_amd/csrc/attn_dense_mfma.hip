@@ -574,8 +574,8 @@ __global__ __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) void bwd_dense_small_kern
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
       const int row = it * 8 + (lane >> 3), piece = lane & 7, k = 32 * wave + row;
-      const uint4 v = *reinterpret_cast<const uint4*>(st + row * 128 + ((piece ^ (row & 7)) << 4));
-      if (k < N) *reinterpret_cast<uint4*>(out + (size_t)k * kD + piece * 8) = v;
+      const u32x4 v = *reinterpret_cast<const u32x4*>(st + row * 128 + ((piece ^ (row & 7)) << 4));
+      if (k < N) ResultRows<>(out).store((unsigned)k * (kD * 2) + piece * 16, v);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     __builtin_amdgcn_wave_barrier();

@@ -29,6 +29,7 @@ constexpr int kStageBytes = 2 * kTileBytes;   // K tile, V tile
 
 // O = sum_c 2^(m_c - m) O_c / sum_c 2^(m_c - m) l_c over the chunks of one owner tile of question
 // tokens; slot0 = the tile's first partial slot.  Items are dealt to the four wavefronts.
+template <bool kThrough>
 __device__ __forceinline__ void merge_chunks(const AttnArgs& a, const UnitPlan& u, size_t slot0, unsigned short* O,
                                              float* LSE, char* stage, const int* row_tok, int wave, int lane) {
   const int m = lane & 31, hl = lane >> 5;
@@ -67,7 +68,7 @@ __device__ __forceinline__ void merge_chunks(const AttnArgs& a, const UnitPlan& 
     if ((item & 1) == 0 && hl == 0 && row_tok[row] >= 0) LSE[row_tok[row]] = (mx + __builtin_amdgcn_logf(l)) * kLn2;
   }
   __syncthreads();
-  flush_rows(O, stage, row_tok, wave, lane);
+  flush_rows<kThrough>(O, stage, row_tok, wave, lane);
 }
 
 template <int kTiles>
@@ -78,7 +79,8 @@ struct FwdLds {
   int group_done;
 };
 
-template <int kTiles>
+// kThrough: see ResultRows (small launches, whose rows fit a few L2 lines, do not: one sequence of 512, 12 heads, with its tables 14.93 us, and 14.98 through).
+template <int kTiles, bool kThrough>
 __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w, FwdLds<kTiles>& s) {
   char* const lds = s.stages;
   int (&idx_ring)[kIdxSlots][BN] = s.idx_ring;
@@ -200,7 +202,7 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w, FwdLd
     }
     unsigned long long* words = a.arrived + (slot - mine);
     if (completes_group(words, mine, u.n_chunks, a.ticket, &group_done)) {
-      merge_chunks(a, u, slot - mine, O, LSE, lds, q_tok, wave, ln);
+      merge_chunks<kThrough>(a, u, slot - mine, O, LSE, lds, q_tok, wave, ln);
       const int c = wave * 64 + ln;
       if (c < u.n_chunks) __hip_atomic_store(words + c, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -210,7 +212,7 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w, FwdLd
   const f32x16 (*accs[1])[2] = {&o_acc};
   const float muls[1] = {1.f / l_tot};
   unsigned short* const outs[1] = {O};
-  store_owned_rows<1>(accs, muls, outs, lds, q_tok, wave, ln);
+  store_owned_rows<1, kThrough>(accs, muls, outs, lds, q_tok, wave, ln);
 }
 
 template <bool kChunksFirst, bool kJoin>
@@ -218,15 +220,15 @@ __global__ __launch_bounds__(kThreads, 4) void fwd_mfma_kernel(MATE_UNIT_LISTS, 
   __shared__ FwdLds<1> s;
   Work w;
   if (!take_unit<kChunksFirst, kJoin>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x, w)) return;
-  fwd_unit<1>(a, w, s);
+  fwd_unit<1, true>(a, w, s);
 }
 template <bool kChunksFirst>
 __global__ __launch_bounds__(kThreads, 2) void fwd_small_kernel(MATE_UNIT_LISTS, AttnArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char dynamic_lds[];
   Work w;
   if (!take_unit<kChunksFirst, false>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x, w)) return;
-  if (OwnerSplit<2>(w.u, 0).four) fwd_unit<2>(a, w, *reinterpret_cast<FwdLds<2>*>(dynamic_lds));
-  else fwd_unit<1>(a, w, *reinterpret_cast<FwdLds<1>*>(dynamic_lds));
+  if (OwnerSplit<2>(w.u, 0).four) fwd_unit<2, false>(a, w, *reinterpret_cast<FwdLds<2>*>(dynamic_lds));
+  else fwd_unit<1, false>(a, w, *reinterpret_cast<FwdLds<1>*>(dynamic_lds));
 }
 
 }  // namespace

@@ -298,13 +298,14 @@ struct ProjArgs : ProjStart {
   const float* bias;             // [F] or null
   unsigned short* out[3];        // head layout: q, k, v (or d_o) [B][H][N][64];  flat: [B][N][F] in out[0]
   int B, H;
+  int lazy_tiles;                // the tiles before this one leave their results in the L2
   RangeSums ranges;
 };
 
 // kHeadTok: the token operand comes from head-layout tensors and the output is flat; else the reverse.
 // kTransposedW: the weight operand is read transposed.
 template <class S, bool kHeadTok, bool kTransposedW>
-__device__ __forceinline__ void product_tile(const ProjStart& p, const ProjArgs& a, char* lds, int b, int n0, int f0) {
+__device__ __forceinline__ void product_tile(const ProjStart& p, const ProjArgs& a, char* lds, int b, int n0, int f0, bool through) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int group = wave_id / S::kWaves, wave = wave_id - group * S::kWaves;
@@ -409,38 +410,38 @@ __device__ __forceinline__ void product_tile(const ProjStart& p, const ProjArgs&
   // ---- epilogue: + bias, round to bf16.  A lane holds features 16 i + 4 quarter .. + 3 of token 16 j + r;
   // after exchanging quarters between neighbouring blocks it holds eight consecutive ones and stores
   // 16 bytes, 64 of a token's bytes per instruction. ------------------------------------------------
+  auto store = [&](auto through) {
 #pragma unroll
-  for (int i = 0; i < S::kFA; i += 2) {
-    const int fw = (wa * S::kFA + i) * 16;       // first feature of the block pair in the tile
-    if (fw >= feats) break;                      // (F is a multiple of 64: a pair is inside or outside)
-    unsigned short* dst;
-    size_t dst_stride;  // elements between consecutive tokens
-    if (kHeadTok) {
-      dst = a.out[0] + ((size_t)b * p.N + n0) * p.F + f0 + fw;
-      dst_stride = p.F;
-    } else {
-      const int head_slot = (f0 + fw) >> 6, x = head_slot / a.H, h = head_slot - x * a.H;
-      unsigned short* out = pick(x == 0, out_0, pick(x == 1, out_1, out_2));
-      dst = out + (((size_t)b * a.H + h) * p.N + n0) * kD + (fw & 63);
-      dst_stride = kD;
-    }
-    dst += (quarter & 1) * 16 + (quarter >> 1) * 8;
-#pragma unroll
-    for (int j = 0; j < S::kOutB; ++j) {
-      unsigned u[2][2];
-#pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        const f32x4 c = sum[i + p][j] + bias[i + p];
-        u[p][0] = pack2(c[0], c[1]);
-        u[p][1] = pack2(c[2], c[3]);
+    for (int i = 0; i < S::kFA; i += 2) {
+      const int fw = (wa * S::kFA + i) * 16;       // first feature of the block pair in the tile
+      if (fw >= feats) break;                      // (F is a multiple of 64: a pair is inside or outside)
+      unsigned short* dst;
+      if (kHeadTok) dst = out_0 + ((size_t)b * p.N + n0) * p.F + f0 + fw;
+      else {
+        const int head_slot = (f0 + fw) >> 6, x = head_slot / a.H, h = head_slot - x * a.H;
+        dst = pick(x == 0, out_0, pick(x == 1, out_1, out_2)) + (((size_t)b * a.H + h) * p.N + n0) * kD + (fw & 63);
       }
-      const auto lo = __builtin_amdgcn_permlane16_swap(u[0][0], u[1][0], false, false);
-      const auto hi = __builtin_amdgcn_permlane16_swap(u[0][1], u[1][1], false, false);
-      uint4 v = make_uint4(lo[0], hi[0], lo[1], hi[1]);
-      if ((pad_bits >> j) & 1u) v = make_uint4(0, 0, 0, 0);
-      if ((j0 + j) * 16 + r < rows) *reinterpret_cast<uint4*>(dst + (size_t)row[j] * dst_stride) = v;
+      const ResultRows<decltype(through)::value> result(dst);
+      const unsigned token_bytes = (kHeadTok ? (unsigned)p.F : (unsigned)kD) * 2;   // between consecutive tokens
+#pragma unroll
+      for (int j = 0; j < S::kOutB; ++j) {
+        unsigned u[2][2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          const f32x4 c = sum[i + p][j] + bias[i + p];
+          u[p][0] = pack2(c[0], c[1]);
+          u[p][1] = pack2(c[2], c[3]);
+        }
+        const auto lo = __builtin_amdgcn_permlane16_swap(u[0][0], u[1][0], false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(u[0][1], u[1][1], false, false);
+        u32x4 v = {lo[0], hi[0], lo[1], hi[1]};
+        if ((pad_bits >> j) & 1u) v = u32x4{0, 0, 0, 0};
+        if ((j0 + j) * 16 + r < rows) result.store((unsigned)row[j] * token_bytes + ((quarter & 1) * 16 + (quarter >> 1) * 8) * 2, v);
+      }
     }
-  }
+  };
+  if (through) store(std::true_type());
+  else store(std::false_type());
 }
 
 template <class S, bool kHeadTok, bool kTransposedW>
@@ -448,7 +449,7 @@ __device__ __forceinline__ void dealt_product(const ProjStart& p, const ProjArgs
   int token_tile, feature_tile, tile;
   if (!dealt_tile(p.deal, x, y, token_tile, feature_tile)) return;
   const int b = uniform_div(token_tile, (p.N + S::kRowsB - 1) / S::kRowsB, tile);
-  product_tile<S, kHeadTok, kTransposedW>(p, a, lds, b, tile * S::kRowsB, feature_tile * S::kRowsA);
+  product_tile<S, kHeadTok, kTransposedW>(p, a, lds, b, tile * S::kRowsB, feature_tile * S::kRowsA, y * p.deal.grid_x() + x >= a.lazy_tiles);
 }
 
 template <class S, bool kHeadTok, bool kTransposedW>
@@ -480,9 +481,22 @@ void deal_tiles(ProjArgs& a) {
   d.rows = (d.by_feature ? d.features : d.tokens) / 8;
 }
 
+// How many tiles, the first ones, leave their part of the result in the L2 (see ResultRows): all that do not fit it at the end anyway.
+// us, 30 % padding, left, through, and through for the last 64 MB: 768 -> 2304 at 8 x 2048 tokens (75 MB) 52.4, 51.2, 51.0, at 16 x
+// 4096 (302 MB) 227, 238, 225.5; 768 -> 768 at 8 x 2048 (25 MB) 19.9 and 18.1, at 4 x 10584 (65 MB) 46.4 and 45.5.  The gradients
+// behind a weight gradient lose by the last 64 MB of a long result what they gain by a short one: dX (and dW) at 2 x 8192, 1024 wide (34
+// MB) 140 and 138, at 4 x 10584 217 and 222, at 16 x 4096 (101 MB) 334 and 343, d_o there 138 and 143.
+template <class S, bool kTransposedW>
+int lazy_tiles(const ProjArgs& a) {
+  const size_t tiles = (size_t)a.deal.tokens * a.deal.features, bytes = tiles * (S::kRowsA * S::kRowsB * 2);
+  if (kTransposedW) return bytes <= (48u << 20) ? 0 : (int)tiles;
+  return (int)(tiles - std::min(tiles, (size_t)(64u << 20) / (S::kRowsA * S::kRowsB * 2)));
+}
+
 template <class S, bool kHeadTok, bool kTransposedW>
 hipError_t launch_proj(ProjArgs a, int kernel_id, hipStream_t stream) {
   deal_tiles<S>(a);
+  a.lazy_tiles = lazy_tiles<S, kTransposedW>(a);
   const int x = a.deal.grid_x();
   int range_rows = 0;
   if (a.ranges.splits) {
@@ -873,14 +887,16 @@ __device__ __forceinline__ void wgrad_tile(WgradArgs a, char* lds, int block) {
   }
   const bool partial = !kMerge && a.splits > 1;
   // a lane holds columns 16 i + 4 quarter .. + 3 of row 16 j + r
-  float* dst = (partial ? a.part + (size_t)split * a.F * a.E : a.out);
+  // (kMerge: at the end of a launch, through the L2.  Otherwise another launch of the same tiles follows: through, 8 x 2048 tokens,
+  // 768 wide gain 1.5 %, 4 x 10584 and 16 x 4096 lose 1.5 %)
+  const ResultRows<kMerge> rows((partial ? a.part + (size_t)split * a.F * a.E : a.out) + (size_t)f0 * a.E);
 #pragma unroll
   for (int j = 0; j < S::kOutB; ++j) {
-    const int f = f0 + (wb * S::kFB + group * S::kOutB + j) * 16 + r;
+    const int f = (wb * S::kFB + group * S::kOutB + j) * 16 + r;
 #pragma unroll
     for (int i = 0; i < S::kFA; ++i) {
       const int e = e0 + (wa * S::kFA + i) * 16 + 4 * quarter;
-      if (f < a.F && e < a.E) *reinterpret_cast<f32x4*>(dst + (size_t)f * a.E + e) = sum[i][j];
+      if (f < a.F - f0 && e < a.E) rows.store(((unsigned)f * a.E + e) * 4, __builtin_bit_cast(u32x4, sum[i][j]));
     }
   }
   if (has_bias) {
@@ -1077,6 +1093,7 @@ BwdPlan plan_bwd(const WgradArgs& w, const ProjArgs& a, int groups, size_t room)
 template <class S, bool kHeadTok>
 hipError_t launch_bwd(WgradArgs w, ProjArgs a, const BwdPlan& p, char* ws, int wgrad_id, int proj_id, hipStream_t stream) {
   deal_tiles<S>(a);
+  a.lazy_tiles = lazy_tiles<S, true>(a);
   place_ranges(w, p, ws);
   const int w_blocks = (wgrad_tiles128(w.F, w.E) * p.ranges + 7) / 8 * 8;  // (whole rounds of XCDs, so the products' tiles are dealt as ever)
   constexpr int kLds = std::max(S::kLds, Wgrad128::kLds);

@@ -392,17 +392,18 @@ __device__ __forceinline__ void stage_rows(const f32x16& a, float mul, char* sta
     *reinterpret_cast<uint2*>(stage + wrow * 128 + (((4 * db + g) ^ (wrow & 7)) << 4) + 8 * hl) = w;
   }
 }
+template <bool kThrough = true>
 __device__ __forceinline__ void flush_rows(unsigned short* out, const char* stage, const int* row_tok, int wave, int lane) {
+  const ResultRows<kThrough> rows(out);
 #pragma unroll
   for (int it = 0; it < 4; ++it) {
     const int row = wave * 32 + it * 8 + (lane >> 3), piece = lane & 7;
     const int tok = row_tok[row];
     if (tok >= 0)
-      *reinterpret_cast<uint4*>(out + (size_t)tok * kD + piece * 8) =
-          *reinterpret_cast<const uint4*>(stage + row * 128 + ((piece ^ (row & 7)) << 4));
+      rows.store((unsigned)tok * (kD * 2) + piece * 16, *reinterpret_cast<const u32x4*>(stage + row * 128 + ((piece ^ (row & 7)) << 4)));
   }
 }
-template <int kTensors>
+template <int kTensors, bool kThrough = true>
 __device__ inline void store_owned_rows(const f32x16 (*acc[kTensors])[2], const float (&mul)[kTensors],
                                         unsigned short* const (&out)[kTensors], char* stage,
                                         const int* row_tok, int wave, int lane) {
@@ -413,7 +414,7 @@ __device__ inline void store_owned_rows(const f32x16 (*acc[kTensors])[2], const 
       stage_rows((*acc[x])[db], mul[x], stage + x * (BM * 128), wave * 32 + (lane & 31), db, lane >> 5);
   __syncthreads();
 #pragma unroll
-  for (int x = 0; x < kTensors; ++x) flush_rows(out[x], stage + x * (BM * 128), row_tok, wave, lane);
+  for (int x = 0; x < kTensors; ++x) flush_rows<kThrough>(out[x], stage + x * (BM * 128), row_tok, wave, lane);
 }
 
 // ---- partial results of chunked question-token owners ------------------------------------------
@@ -491,7 +492,7 @@ __device__ inline void zero_pad_rows(unsigned short* const (&out)[kTensors], con
 #pragma unroll
     for (int i = 0; i < kRounds; ++i)
       if (tok[i] >= 0)
-        *reinterpret_cast<uint4*>(out[x] + (size_t)tok[i] * kD + piece * 8) = make_uint4(0, 0, 0, 0);
+        ResultRows<>(out[x]).store((unsigned)tok[i] * (kD * 2) + piece * 16, u32x4{0, 0, 0, 0});
 }
 
 // Workspace carving (float words).  Partial buffers are per (b,h): [UG][BM][64].

@@ -291,6 +291,12 @@ def test_one_round_of_eight_wavefronts(B, N, H, E):
     check_bwd(N, B, N, H, E, pad_tail=N // 7)
 
 
+def test_results_larger_than_the_caches():
+    """QKV: the first tiles' results stay in the L2, the last 64 MB are written through it; dX and d_o: all stay (63 MB)."""
+    check(7, 5, 16383, 6, 384, pad_tail=2000)
+    check_bwd(7, 5, 16383, 6, 384, pad_tail=2000)
+
+
 @pytest.mark.parametrize("B,N,H,E", [(1, 2690, 2, 128), (13, 100, 6, 384), (3, 1111, 4, 128)])
 def test_last_token_tiles_dealt_one_by_one(B, N, H, E):
     """Token tiles that are no multiple of eight, of one sequence and of several: the last ones go to all XCDs."""
