@@ -166,6 +166,7 @@ struct CodeMask {
 // ======================================================================================
 // forward
 // ======================================================================================
+template <bool kThrough>
 __global__ __launch_bounds__(kThreads) void fwd_dense_kernel(const void* q, const void* k, const void* v, const int* row_ids,
                                                              const int* col_ids, const unsigned char* flags, int sizes, int pairs,
                                                              DenseArgs a) {
@@ -228,7 +229,7 @@ __global__ __launch_bounds__(kThreads) void fwd_dense_kernel(const void* q, cons
   const f32x16 (*accs[1])[2] = {&o_acc};
   const float muls[1] = {1.f};
   unsigned short* const outs[1] = {O};
-  store_owned_rows<1>(accs, muls, outs, lds, q_tok, wave, lane);
+  store_owned_rows<1, kThrough>(accs, muls, outs, lds, q_tok, wave, lane);
 }
 
 // ======================================================================================
@@ -390,7 +391,7 @@ struct SmallShape {
   // and dV rows over the K tiles
   static constexpr int kLds = kKeyBytes + 2 * kQryBytes + (kOverlay || kKeyBytes > kDsBytes ? kKeyBytes : kDsBytes);
 };
-template <int NW>
+template <int NW, bool kThrough>
 __global__ __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) void bwd_dense_small_kernel(
     const void* q, const void* k, const void* v, const void* o, const void* dout, int sizes, DenseArgs a) {
   using S = SmallShape<NW>;
@@ -575,7 +576,7 @@ __global__ __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) void bwd_dense_small_kern
     for (int it = 0; it < 4; ++it) {
       const int row = it * 8 + (lane >> 3), piece = lane & 7, k = 32 * wave + row;
       const u32x4 v = *reinterpret_cast<const u32x4*>(st + row * 128 + ((piece ^ (row & 7)) << 4));
-      if (k < N) ResultRows<>(out).store((unsigned)k * (kD * 2) + piece * 16, v);
+      if (k < N) ResultRows<kThrough>(out).store((unsigned)k * (kD * 2) + piece * 16, v);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -588,13 +589,13 @@ __global__ __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) void bwd_dense_small_kern
   flush(dV);
 }
 
-template <int NW>
+template <int NW, bool kThrough>
 hipError_t launch_bwd_small(const DenseArgs& a, hipStream_t stream) {
   using S = SmallShape<NW>;
-  const hipError_t e = allow_lds<&bwd_dense_small_kernel<NW>>(S::kLds);
+  const hipError_t e = allow_lds<&bwd_dense_small_kernel<NW, kThrough>>(S::kLds);
   if (e != hipSuccess) return e;
   ProfileScope prof(7, stream, 6);
-  hipLaunchKernelGGL(bwd_dense_small_kernel<NW>, dim3(a.B * a.H), dim3(64 * NW), S::kLds, stream, a.q, a.k, a.v, a.o, a.dout,
+  hipLaunchKernelGGL((bwd_dense_small_kernel<NW, kThrough>), dim3(a.B * a.H), dim3(64 * NW), S::kLds, stream, a.q, a.k, a.v, a.o, a.dout,
                      pack_sizes(a.N, a.H), a);
   return hipGetLastError();
 }
@@ -603,16 +604,18 @@ hipError_t launch_bwd_small(const DenseArgs& a, hipStream_t stream) {
 
 hipError_t launch_fwd_dense(const DenseArgs& a, hipStream_t stream) {
   ProfileScope prof(5, stream);
-  hipLaunchKernelGGL(fwd_dense_kernel, dim3(dense_grid(a)), dim3(kThreads), 0, stream, a.q, a.k, a.v, a.row_ids, a.col_ids, a.flags,
+  const auto kernel = result_through(a.B, a.H, a.N, 2) ? fwd_dense_kernel<true> : fwd_dense_kernel<false>;
+  hipLaunchKernelGGL(kernel, dim3(dense_grid(a)), dim3(kThreads), 0, stream, a.q, a.k, a.v, a.row_ids, a.col_ids, a.flags,
                      pack_sizes(a.N, a.H), a.B * a.H, a);
   return hipGetLastError();
 }
 
 hipError_t launch_bwd_dense(const DenseArgs& a, hipStream_t stream) {
   // one workgroup per (sequence, head) as long as its dS^T and K fit the LDS
-  if (a.N <= 64) return launch_bwd_small<2>(a, stream);
-  if (a.N <= 128) return launch_bwd_small<4>(a, stream);
-  if (a.N <= 256) return launch_bwd_small<8>(a, stream);
+  const bool through = result_through(a.B, a.H, a.N, 3 * 2);
+  if (a.N <= 64) return through ? launch_bwd_small<2, true>(a, stream) : launch_bwd_small<2, false>(a, stream);
+  if (a.N <= 128) return through ? launch_bwd_small<4, true>(a, stream) : launch_bwd_small<4, false>(a, stream);
+  if (a.N <= 256) return through ? launch_bwd_small<8, true>(a, stream) : launch_bwd_small<8, false>(a, stream);
   {
     ProfileScope prof(6, stream);
     hipLaunchKernelGGL(bwd_dq_dense_kernel, dim3(dense_grid(a)), dim3(kThreads), 0, stream, a);

@@ -398,7 +398,7 @@ __device__ __forceinline__ bool any_small_row(const float* X, const Rows& r, int
 
 // Sum of the four wavefronts' accumulators, stored as whole rows: lane m's column is owned row m.
 // `lds` = the wavefronts' pieces, `row_tok` = the owned rows' tokens.
-// kThrough: see ResultRows (the backward, with the forward 66.0 us for 4 x 512, 12 heads, and 65.2 through; the forward of 6 x 106, 4 heads 11.77 and 11.9).
+// kThrough: see ResultRows (the backward: with the forward 66.0 us for 4 x 512, 12 heads, and 65.2 through) and result_through.
 __device__ __forceinline__ float* piece_of(char* lds, int wave) { return reinterpret_cast<float*>(lds + wave * kPlanes); }
 template <bool kThrough>
 __device__ __forceinline__ void store_sum(const f32x16 (&acc)[2], float mul, char* lds, const int* row_tok, float* out,
@@ -446,7 +446,7 @@ __device__ __forceinline__ void zero_pads(const Quarter& q, float* const (&out)[
 // ======================================================================================
 // forward
 // ======================================================================================
-template <bool kOwnersFirst>
+template <bool kOwnersFirst, bool kThrough>
 __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(MATE_UNIT_LISTS, AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds[kWaves * kPlanes];
   __shared__ __attribute__((aligned(1024))) char own[kPlanes];
@@ -577,7 +577,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(MATE_UNIT_LISTS, A
     else
       mul *= 1.f / kLift;
   }
-  store_sum<false>(o, mul, lds, row_tok, O, wave, m, hl);
+  store_sum<kThrough>(o, mul, lds, row_tok, O, wave, m, hl);
 }
 
 // ======================================================================================
@@ -924,8 +924,10 @@ static bool owners_first(int B, int H, int N) {
 
 hipError_t launch_fwd_f32(const AttnArgs& a, hipStream_t stream) {
   const dim3 grid(4 * unit_grid(a.B, a.H, a.N, a.n_col)), block(kThreads);
-  if (owners_first(a.B, a.H, a.N)) hipLaunchKernelGGL(fwd_f32_kernel<true>, grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
-  else hipLaunchKernelGGL(fwd_f32_kernel<false>, grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
+  const bool owners = owners_first(a.B, a.H, a.N);
+  const auto kernel = result_through(a.B, a.H, a.N, 4) ? (owners ? fwd_f32_kernel<true, true> : fwd_f32_kernel<false, true>)
+                                                       : (owners ? fwd_f32_kernel<true, false> : fwd_f32_kernel<false, false>);
+  hipLaunchKernelGGL(kernel, grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
   return hipGetLastError();
 }
 

@@ -79,7 +79,7 @@ struct FwdLds {
   int group_done;
 };
 
-// kThrough: see ResultRows (small launches, whose rows fit a few L2 lines, do not: one sequence of 512, 12 heads, with its tables 14.93 us, and 14.98 through).
+// kThrough: see result_through.
 template <int kTiles, bool kThrough>
 __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w, FwdLds<kTiles>& s) {
   char* const lds = s.stages;
@@ -222,29 +222,33 @@ __global__ __launch_bounds__(kThreads, 4) void fwd_mfma_kernel(MATE_UNIT_LISTS, 
   if (!take_unit<kChunksFirst, kJoin>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x, w)) return;
   fwd_unit<1, true>(a, w, s);
 }
-template <bool kChunksFirst>
+template <bool kChunksFirst, bool kThrough>
 __global__ __launch_bounds__(kThreads, 2) void fwd_small_kernel(MATE_UNIT_LISTS, AttnArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char dynamic_lds[];
   Work w;
   if (!take_unit<kChunksFirst, false>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x, w)) return;
-  if (OwnerSplit<2>(w.u, 0).four) fwd_unit<2, false>(a, w, *reinterpret_cast<FwdLds<2>*>(dynamic_lds));
-  else fwd_unit<1, false>(a, w, *reinterpret_cast<FwdLds<1>*>(dynamic_lds));
+  if (OwnerSplit<2>(w.u, 0).four) fwd_unit<2, kThrough>(a, w, *reinterpret_cast<FwdLds<2>*>(dynamic_lds));
+  else fwd_unit<1, kThrough>(a, w, *reinterpret_cast<FwdLds<1>*>(dynamic_lds));
 }
 
 }  // namespace
 
-template <bool kChunksFirst>
+template <bool kChunksFirst, bool kThrough>
 static hipError_t launch_small(const AttnArgs& a, dim3 grid, hipStream_t stream) {
-  const hipError_t e = allow_lds<&fwd_small_kernel<kChunksFirst>>(sizeof(FwdLds<2>));
+  const hipError_t e = allow_lds<&fwd_small_kernel<kChunksFirst, kThrough>>(sizeof(FwdLds<2>));
   if (e != hipSuccess) return e;
   ProfileScope prof(2, stream);
-  hipLaunchKernelGGL(fwd_small_kernel<kChunksFirst>, grid, dim3(kThreads), sizeof(FwdLds<2>), stream, MATE_UNIT_LISTS_VALUES(a), a);
+  hipLaunchKernelGGL((fwd_small_kernel<kChunksFirst, kThrough>), grid, dim3(kThreads), sizeof(FwdLds<2>), stream, MATE_UNIT_LISTS_VALUES(a), a);
   return hipGetLastError();
 }
 hipError_t launch_fwd_mfma(const AttnArgs& a, hipStream_t stream) {
   const dim3 grid(unit_grid(a.B, a.H, a.N, a.n_col)), block(kThreads);
   const bool first = fwd_chunks_first(a.B, a.H, a.N), join = joins_chunks(a.B, a.H, a.N);
-  if (small_forward(a.B, a.H, a.N)) return small_owners_first(a.B, a.H, a.N) ? launch_small<true>(a, grid, stream) : launch_small<false>(a, grid, stream);
+  if (small_forward(a.B, a.H, a.N)) {
+    const bool owners = small_owners_first(a.B, a.H, a.N);
+    if (result_through(a.B, a.H, a.N, 2)) return owners ? launch_small<true, true>(a, grid, stream) : launch_small<false, true>(a, grid, stream);
+    return owners ? launch_small<true, false>(a, grid, stream) : launch_small<false, false>(a, grid, stream);
+  }
   ProfileScope prof(2, stream);
   if (first && join) hipLaunchKernelGGL((fwd_mfma_kernel<true, true>), grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
   else if (join) hipLaunchKernelGGL((fwd_mfma_kernel<false, true>), grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);

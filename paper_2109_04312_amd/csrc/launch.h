@@ -8,6 +8,16 @@
 
 namespace mate {
 
+// Do the rows that an attention launch stores, `bytes_each` for an element of Q, pass through the L2 (see ResultRows)?  Where it is small there is nothing to overlap, and the launch waits for
+// memory instead of the L2.  us, left and through: dense forward of 4 x 60, 12 heads (0.4 MB) 4.34 and 4.55, 4 x 128 (0.8 MB) 5.46
+// and 5.65, 8 x 128 (1.6 MB) 5.57 and 5.67, 16 x 128 (3.1 MB) 5.86 and 5.80, 24 x 128 (4.7 MB) 7.50 and 7.17; segments, 12 heads, one
+// sequence of 512 with its tables 14.93 and 14.98, 3 x 512 (2.4 MB) 8.27 and 8.22, 2 x 1000 10.03 and 9.78, 8 x 512 (6.3 MB) 11.27 and
+// 10.69; f32, 6 x 106 with 4 heads and its tables 11.77 and 11.9, 4 x 512 (6.3 MB) 13.81 and 13.66; dense backward of 1 x 64, 4 heads (0.1
+// MB) 5.79 and 5.95, 4 x 60, 12 heads (1.1 MB) 6.01 and 6.10, 4 x 128 (2.4 MB) 8.02 and 8.06, 8 x 128 (4.7 MB) 8.31 and 8.14.  The other
+// backward kernels and the products gain nothing by the L2 at any size.  (Zeros of pad rows
+// always do: their workgroups end long before the launch.)
+inline bool result_through(int B, int H, int N, int bytes_each) { return (size_t)B * H * N * 64 * bytes_each > (2u << 20); }
+
 struct AttnArgs {
   const void *q, *k, *v;    // [B,H,N,64]
   const void *o, *dout;     // backward only

@@ -45,7 +45,7 @@ __device__ inline bf16x8 pack8(const f32x16& x, int c0) {
 // cache either way.  us, left and through: dense forward and backward of 32 x 128, 12 heads 22.5 and 20.8, forward and backward of
 // 32 x 512, 12 heads 111 and 103.3, layer training of 8 x 512 138 and 133, of 2 x 8192 580 and 574.  (Non-temporal stores, which pass that
 // cache as well, gain another 3 % where nothing reads the result, and cost a layer 1 to 3 %.)  Where a launch writes a few hundred
-// kilobytes there is nothing to overlap, and it waits for memory instead of the L2: see the callers.
+// kilobytes there is nothing to overlap, and it waits for memory instead of the L2: see result_through and the other callers.
 // Offsets from `base` are below 4 GB: a (sequence, head)'s rows, or a tile's.
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 template <bool kThrough = true>

@@ -220,6 +220,12 @@ def test_units_of_as_many_segments_as_lanes(segments, N):
     check_workload(w, backward=True)
 
 
+@pytest.mark.parametrize("dtype,B,N", [("bf16", 4, 341), ("bf16", 4, 342), ("f32", 2, 341), ("f32", 2, 342)])
+def test_results_on_either_side_of_two_megabytes(dtype, B, N):
+    """A small forward's result stays in the L2 or passes through it (12 heads: 341 positions are the last below 2 MB)."""
+    check_workload(small_workload(N, dtype, B=B, N=N, H=12, bwd=False, max_rows=30, max_cols=6, max_global=20), backward=False)
+
+
 def test_head_kind_mix_and_order():
     # any assignment of kinds to heads, not only "first half rows"
     w = small_workload(8, "bf16", B=1, N=260, H=5, max_rows=10, max_cols=5, max_global=9)

@@ -116,3 +116,9 @@ def test_dense_backward_answers_to_both_profile_names(N, kernel):
     torch.cuda.synchronize()
     assert stop.elapsed_time(mark) >= 0                                     # and not again
     assert mate.mate_profile_kernel(mate.MATE_KERNEL_NONE, None, None) == mate.MATE_OK
+
+
+@pytest.mark.parametrize("B,N,H", [(32, 128, 4), (32, 129, 4), (31, 44, 4), (32, 43, 4), (11, 124, 4), (11, 125, 4), (7, 195, 4), (7, 196, 4)])
+def test_dense_results_on_either_side_of_two_megabytes(B, N, H):
+    """Results stay in the L2 or pass through it: the forward's 128 bytes a row (two cases) and the one-launch backward's 384."""
+    check_dense(small_workload(N, "bf16", B=B, N=N, H=H, max_rows=min(12, N // 4), max_cols=5, max_global=12, max_cell=4))
