@@ -173,13 +173,14 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w, ch
 
 // (four workgroups per CU: with three, the column-head units of the benchmark shape do not all
 // fit at once and the stragglers double the kernel's critical path)
-template <bool kJoin>
+template <bool kJoin, bool kMany>
 __global__ __launch_bounds__(kThreads, 4) void bwd_dq_mfma_kernel(MATE_UNIT_LISTS, AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds[kStages * kDqStage];
   __shared__ int idx_ring[kIdxSlots][BN];
   __shared__ int row_tok[BM];
   Work w;
-  if (!take_unit<true, kJoin>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x, w)) return;
+  if (kMany ? !take_unit_of_many<true, kJoin>(a, blockIdx.x, w)
+            : !take_unit<true, kJoin>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x, w)) return;
   bwd_dq_unit<false>(a, w, lds, idx_ring, row_tok, nullptr);
 }
 
@@ -312,7 +313,7 @@ __device__ __forceinline__ void merge_dq(const AttnArgs& a, int bh_i, char* stag
 // The first `n_merge` workgroups (a multiple of eight, so that the unit queues keep their XCDs) merge
 // dQ partials: a few microseconds each, out of the way before the kernel's own tail.
 // (168 registers: three workgroups per CU; with two the kernel takes 15 to 20 % longer)
-template <bool kJoin>
+template <bool kJoin, bool kMany>
 __global__ __launch_bounds__(kThreads, 3) void bwd_dkv_mfma_kernel(MATE_UNIT_LISTS, AttnArgs a, int n_merge) {
   __shared__ __attribute__((aligned(1024))) char lds[kStages * kDkvStage];
   __shared__ int idx_ring[kIdxSlots][BN];
@@ -323,7 +324,8 @@ __global__ __launch_bounds__(kThreads, 3) void bwd_dkv_mfma_kernel(MATE_UNIT_LIS
     return;
   }
   Work w;
-  if (!take_unit<true, kJoin>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x - n_merge, w)) return;
+  if (kMany ? !take_unit_of_many<true, kJoin>(a, blockIdx.x - n_merge, w)
+            : !take_unit<true, kJoin>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x - n_merge, w)) return;
   bwd_dkv_unit(a, w, lds, idx_ring, row_tok, &group_done);
 }
 
@@ -391,6 +393,7 @@ static bool both_at_once(int B, int H, int N) {
 template <bool kJoin>
 static hipError_t launch_bwd(const AttnArgs& a, hipStream_t stream) {
   const dim3 grid(unit_grid(a.B, a.H, a.N, a.n_col)), block(kThreads);
+  const bool many = (int)grid.x > kManyRecords;
   hipError_t e;
   if (both_at_once(a.B, a.H, a.N)) {
     const size_t rows = (size_t)a.B * a.H * a.N;
@@ -403,13 +406,15 @@ static hipError_t launch_bwd(const AttnArgs& a, hipStream_t stream) {
   }
   {
     ProfileScope prof(3, stream);
-    hipLaunchKernelGGL(bwd_dq_mfma_kernel<kJoin>, grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
+    const auto kernel = many ? bwd_dq_mfma_kernel<kJoin, true> : bwd_dq_mfma_kernel<kJoin, false>;
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   ProfileScope prof(4, stream);
   const int n_merge = may_chunk(a.B, a.N) ? 8 * ((a.B * a.H + 7) / 8) : 0;
-  hipLaunchKernelGGL(bwd_dkv_mfma_kernel<kJoin>, dim3(grid.x + n_merge), block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a, n_merge);
+  const auto kernel = many ? bwd_dkv_mfma_kernel<kJoin, true> : bwd_dkv_mfma_kernel<kJoin, false>;
+  hipLaunchKernelGGL(kernel, dim3(grid.x + n_merge), block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a, n_merge);
   return hipGetLastError();
 }
 hipError_t launch_bwd_mfma(const AttnArgs& a, hipStream_t stream) {

@@ -215,11 +215,12 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w, FwdLd
   store_owned_rows<1, kThrough>(accs, muls, outs, lds, q_tok, wave, ln);
 }
 
-template <bool kChunksFirst, bool kJoin>
+template <bool kChunksFirst, bool kJoin, bool kMany>
 __global__ __launch_bounds__(kThreads, 4) void fwd_mfma_kernel(MATE_UNIT_LISTS, AttnArgs a) {
   __shared__ FwdLds<1> s;
   Work w;
-  if (!take_unit<kChunksFirst, kJoin>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x, w)) return;
+  if (kMany ? !take_unit_of_many<kChunksFirst, kJoin>(a, blockIdx.x, w)
+            : !take_unit<kChunksFirst, kJoin>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x, w)) return;
   fwd_unit<1, true>(a, w, s);
 }
 template <bool kChunksFirst, bool kThrough>
@@ -250,10 +251,12 @@ hipError_t launch_fwd_mfma(const AttnArgs& a, hipStream_t stream) {
     return owners ? launch_small<true, false>(a, grid, stream) : launch_small<false, false>(a, grid, stream);
   }
   ProfileScope prof(2, stream);
-  if (first && join) hipLaunchKernelGGL((fwd_mfma_kernel<true, true>), grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
-  else if (join) hipLaunchKernelGGL((fwd_mfma_kernel<false, true>), grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
-  else if (first) hipLaunchKernelGGL((fwd_mfma_kernel<true, false>), grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
-  else hipLaunchKernelGGL((fwd_mfma_kernel<false, false>), grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
+  const bool many = (int)grid.x > kManyRecords;
+  const auto kernel = first ? (join ? (many ? fwd_mfma_kernel<true, true, true> : fwd_mfma_kernel<true, true, false>)
+                                    : (many ? fwd_mfma_kernel<true, false, true> : fwd_mfma_kernel<true, false, false>))
+                            : (join ? (many ? fwd_mfma_kernel<false, true, true> : fwd_mfma_kernel<false, true, false>)
+                                    : (many ? fwd_mfma_kernel<false, false, true> : fwd_mfma_kernel<false, false, false>));
+  hipLaunchKernelGGL(kernel, grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
   return hipGetLastError();
 }
 
