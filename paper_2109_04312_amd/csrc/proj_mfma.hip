@@ -482,15 +482,17 @@ void deal_tiles(ProjArgs& a) {
 }
 
 // How many tiles, the first ones, leave their part of the result in the L2 (see ResultRows): all that do not fit it at the end anyway.
-// us, 30 % padding, left, through, and through for the last 64 MB: 768 -> 2304 at 8 x 2048 tokens (75 MB) 52.4, 51.2, 51.0, at 16 x
-// 4096 (302 MB) 227, 238, 225.5; 768 -> 768 at 8 x 2048 (25 MB) 19.9 and 18.1, at 4 x 10584 (65 MB) 46.4 and 45.5.  The gradients
+// The last 32 MB are what the L2s hold.  us, left, through for the last 64 MB, and for the last 32: 768 -> 2304 at 6 x 8447 tokens, 30 %
+// padding (233 MB) 169.8, 175.8, 171.9, 1024 -> 3072 at 8 x 4096 (201 MB) 190.6, 191.9, 187.2, at 14566 (89 MB) 89.4, 86.9, 86.7, 768 ->
+// 2304 at 2 x 11434 (105 MB) 77.6, 76.3, 75.8, 1024 -> 1024 at 8 x 4096 (67 MB) 61.5, 60.4, 59.6; 768 -> 768 at 8 x 2048 (25 MB) 19.9 and,
+// through, 18.1.  The gradients
 // behind a weight gradient lose by the last 64 MB of a long result what they gain by a short one: dX (and dW) at 2 x 8192, 1024 wide (34
 // MB) 140 and 138, at 4 x 10584 217 and 222, at 16 x 4096 (101 MB) 334 and 343, d_o there 138 and 143.
 template <class S, bool kTransposedW>
 int lazy_tiles(const ProjArgs& a) {
   const size_t tiles = (size_t)a.deal.tokens * a.deal.features, bytes = tiles * (S::kRowsA * S::kRowsB * 2);
   if (kTransposedW) return bytes <= (48u << 20) ? 0 : (int)tiles;
-  return (int)(tiles - std::min(tiles, (size_t)(64u << 20) / (S::kRowsA * S::kRowsB * 2)));
+  return (int)(tiles - std::min(tiles, (size_t)(32u << 20) / (S::kRowsA * S::kRowsB * 2)));
 }
 
 template <class S, bool kHeadTok, bool kTransposedW>

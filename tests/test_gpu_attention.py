@@ -220,6 +220,13 @@ def test_units_of_as_many_segments_as_lanes(segments, N):
     check_workload(w, backward=True)
 
 
+@pytest.mark.parametrize("B,N,H", [(187, 60, 16), (188, 60, 16), (2, 1999, 256), (20, 700, 40)])
+def test_launches_on_either_side_of_many_records(B, N, H):
+    """12000 records: a unit is found in one round trip below, step by step above (chunks joined: 2 x 1999 with 256 heads)."""
+    w = small_workload(N, "bf16", B=B, N=N, H=H, max_rows=30, max_cols=6, max_global=min(N // 4, 40))
+    check_workload(w, backward=True, pairs=[(0, 0), (0, H - 1), (B // 2, 1), (B - 1, H - 2), (B - 1, H - 1)])
+
+
 @pytest.mark.parametrize("dtype,B,N", [("bf16", 4, 341), ("bf16", 4, 342), ("f32", 2, 341), ("f32", 2, 342)])
 def test_results_on_either_side_of_two_megabytes(dtype, B, N):
     """A small forward's result stays in the L2 or passes through it (12 heads: 341 positions are the last below 2 MB)."""

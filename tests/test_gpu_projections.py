@@ -292,7 +292,7 @@ def test_one_round_of_eight_wavefronts(B, N, H, E):
 
 
 def test_results_larger_than_the_caches():
-    """QKV: the first tiles' results stay in the L2, the last 64 MB are written through it; dX and d_o: all stay (63 MB)."""
+    """QKV: the first tiles' results stay in the L2, the last 32 MB are written through it; dX and d_o: all stay (63 MB)."""
     check(7, 5, 16383, 6, 384, pad_tail=2000)
     check_bwd(7, 5, 16383, 6, 384, pad_tail=2000)
 
