@@ -41,11 +41,6 @@ inline int pack_sizes(int N, int H) { return N | H << 16; }
 static_assert(kDenseMaxN < 1 << 16, "sixteen bits hold N");
 
 __device__ __forceinline__ int head_view(const DenseArgs& a, int h) { return (int)(a.col_heads[h >> 5] >> (h & 31)) & 1; }
-__device__ __forceinline__ int sequence_of(int bh, int H, int& h) {
-  if (__builtin_expect(bh < 1 << 21, 1)) return uniform_div(bh, H, h);
-  h = (int)((unsigned)bh % (unsigned)H);
-  return (int)((unsigned)bh / (unsigned)H);
-}
 // Workgroup -> (sequence, head, owner tile); (sequence, head) pairs with equal index mod 8 share
 // an XCD (consecutive workgroups go to consecutive XCDs), so their K / V tiles share an L2.
 __device__ __forceinline__ bool dense_unit(const DenseArgs& a, int N, int H, int pairs, DenseUnit& u) {
@@ -53,7 +48,7 @@ __device__ __forceinline__ bool dense_unit(const DenseArgs& a, int N, int H, int
   u.bh = uniform_div(r, owner_slots(N), u.tile) * 8 + q;
   if (u.bh >= pairs) return false;
   int h;
-  u.b = sequence_of(u.bh, H, h);
+  u.b = uniform_div_any(u.bh, H, h);
   u.view = head_view(a, h);
   return true;
 }
@@ -414,7 +409,7 @@ __global__ __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) void bwd_dense_small_kern
   unsigned short* dV = static_cast<unsigned short*>(a.dv) + bh * kD;
 
   int h;
-  const int b = sequence_of(bh_i, sizes >> 16, h), view = head_view(a, h);
+  const int b = uniform_div_any(bh_i, sizes >> 16, h), view = head_view(a, h);
   const int *row_ids = a.row_ids, *col_ids = a.col_ids;
   const unsigned char* flags = a.flags;
   // rows [first, first + rows) of X to LDS, eight per instruction (rows past N repeat the last)

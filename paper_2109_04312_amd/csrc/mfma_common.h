@@ -10,6 +10,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "division.h"
+
 namespace mate {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -57,21 +59,6 @@ struct ResultRows {
 
 // A value that is the same in all lanes, in a scalar register.
 __device__ inline float uniform(float x) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x))); }
-
-// x / d and the remainder, both wave-uniform and not negative, for a quotient below 2^21: one float product and its
-// correction, half the instructions of an integer division (scalar instructions wait for each other, and a workgroup's first
-// microsecond is little else).
-__device__ inline int uniform_div(int x, int d, int& rest) {
-  int k = __builtin_amdgcn_readfirstlane((int)((float)x * __builtin_amdgcn_rcpf((float)d)));
-  rest = x - k * d;
-  const int below = rest >> 31;
-  k += below;
-  rest += below & d;
-  const int above = rest >= d;
-  k += above;
-  rest -= above ? d : 0;
-  return k;
-}
 
 // c ? x : y of values (of two variables the operator yields a variable, which the compiler then looks for in memory)
 template <class T>

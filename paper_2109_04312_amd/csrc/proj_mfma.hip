@@ -30,6 +30,7 @@
 #include "d2l.h"
 #include "launch.h"
 #include "mfma_common.h"
+#include "tile_deal.h"
 
 namespace mate {
 namespace {
@@ -258,30 +259,6 @@ __device__ __forceinline__ void add_ranges(const RangeSums& s, int block, int th
 // ======================================================================================
 // Products with the weights: forward, dX, d_o
 // ======================================================================================
-// Workgroup -> tile.  A grid row is eight token tiles times all feature tiles: XCD x % 8 takes one of the token tiles, so
-// the token rows that it streams stay in its L2 while the weights cycle, another one in each grid row, so that the
-// padding at the end of the sequences is spread over all XCDs.  The tiles of the last token tiles, fewer than eight, are
-// dealt one by one: no XCD has more than one tile more than another, where 21 whole token tiles with 12 feature tiles were 36
-// tiles on some XCDs' 32 CUs, two rounds where one does (1024 -> 3072 at 5376 tokens 38 -> 32 us, at 10752 74 -> 61, gradients
-// of the output projection at 7 x 577 tokens, 768 wide 31.2 -> 25.2, at 9 x 1000 40 -> 33; where it saves no round, 1024 ->
-// 3072 at 25 x 273, 71 -> 72.5).  (Halves and quarters of a token tile's features to an XCD: 0 to 4 % slower.)
-constexpr int kMostGridY = 32768;  // (a grid's second dimension is at most 65536: the third continues it)
-struct TileDeal {
-  int tokens, features;  // tiles
-  int rows;              // grid rows that are dealt as whole token tiles (or feature tiles)
-  int by_feature;        // the same with the two exchanged
-  __device__ __host__ int grid_x() const { return 8 * (by_feature ? tokens : features); }
-  __device__ __host__ int grid_y() const { return rows + ((by_feature ? features : tokens) > 8 * rows ? 1 : 0); }
-};
-__device__ __forceinline__ bool dealt_tile(const TileDeal& d, int x, int y, int& token_tile, int& feature_tile) {
-  int major = 8 * y + ((x + 3 * y) & 7), minor = x >> 3;
-  const int majors = d.by_feature ? d.features : d.tokens;
-  if (y >= d.rows) major = 8 * y + uniform_div(x, d.by_feature ? d.tokens : d.features, minor);
-  token_tile = d.by_feature ? minor : major;
-  feature_tile = d.by_feature ? major : minor;
-  return major < majors;
-}
-
 // What a tile's first loads need: kernel arguments of their own, the first ones, because plain values arrive in registers with
 // the wavefront.
 struct ProjStart {
@@ -448,7 +425,7 @@ template <class S, bool kHeadTok, bool kTransposedW>
 __device__ __forceinline__ void dealt_product(const ProjStart& p, const ProjArgs& a, char* lds, int x, int y) {
   int token_tile, feature_tile, tile;
   if (!dealt_tile(p.deal, x, y, token_tile, feature_tile)) return;
-  const int b = uniform_div(token_tile, (p.N + S::kRowsB - 1) / S::kRowsB, tile);
+  const int b = sequence_of(token_tile, (p.N + S::kRowsB - 1) / S::kRowsB, tile);
   product_tile<S, kHeadTok, kTransposedW>(p, a, lds, b, tile * S::kRowsB, feature_tile * S::kRowsA, y * p.deal.grid_x() + x >= a.lazy_tiles);
 }
 

@@ -304,6 +304,33 @@ def test_last_token_tiles_dealt_one_by_one(B, N, H, E):
     check_bwd(N, B, N, H, E, pad_tail=N // 9)
 
 
+@pytest.mark.parametrize("B", [300_001, (1 << 21) + 3])
+def test_very_many_sequences(B):
+    """One token each: token tiles beyond what a grid's second dimension holds, and beyond 2^21, from where on a tile's sequence
+    is found by whole division.  Products of 128 terms against fp32 ones of the same bf16 values."""
+    from paper_2109_04312_amd import mate
+    H, E = 2, 128
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    normal = lambda *shape, scale=1.0: (torch.randn(shape, device="cuda", generator=gen) * scale).to(torch.bfloat16)
+    x, o = normal(B, 1, E), normal(B, H, 1, 64)
+    w_qkv, w_o = normal(3 * H * 64, E, scale=E ** -0.5), normal(E, H * 64, scale=(H * 64) ** -0.5)
+    flags = torch.randint(0, 3, (B, 1), device="cuda", generator=gen, dtype=torch.uint8)
+    live = (flags != P).float()
+
+    def product_close(got, tokens, w, what):
+        want = tokens.reshape(B, -1).float() @ w.float() * live
+        err = (got.reshape(B, -1).float() - want).abs()
+        print(f"   {what}: max-abs {float(err.max()):.2e}", flush=True)
+        assert bool((err <= 2e-2 + 2.0 ** -8 * want.abs()).all()), what
+
+    for name, got, i in zip("qkv", mate.qkv_project(x, w_qkv, None, flags, H), range(3)):
+        product_close(got, x, w_qkv[128 * i:128 * (i + 1)].t(), name)
+    product_close(mate.out_project(o, w_o, None, flags), o, w_o.t(), "y")
+    product_close(mate.out_project_bwd(o, w_o, flags, x, want_dw=False, want_dbias=False)[0], x, w_o, "d_o")
+    dx = mate.qkv_project_bwd(x, w_qkv, flags, o, o, o, want_dw=False, want_dbias=False)[0]
+    product_close(dx, o.reshape(B, -1).repeat(1, 3), w_qkv, "dx")
+
+
 # tiles of 192 x 128 that two groups of wavefronts share: 16 token tiles of two sequences with one row in the last
 # (QKV), and 49 token tiles of one sequence (output)
 @pytest.mark.parametrize("B,N,H,E", [(2, 897, 12, 768), (1, 6145, 12, 768)])
