@@ -453,8 +453,10 @@ void deal_tiles(ProjArgs& a) {
   d.tokens = a.B * ((a.N + S::kRowsB - 1) / S::kRowsB);
   d.features = (a.F + S::kRowsA - 1) / S::kRowsA;
   // every XCD reads all of the other operand: the smaller one (us by token tiles and by feature tiles: 1024 -> 3072 at 600
-  // tokens 12.1 and 9.8, at 1200 13.8 and 12.5, at 1700 16.8 and 16.5; 2048 -> 6144 at 1000 33.5 and 32.0)
-  d.by_feature = a.F > (long)a.B * a.N;
+  // tokens 12.1 and 9.8, at 1200 13.8 and 12.5, at 1700 16.8 and 16.5; 2048 -> 6144 at 1000 33.5 and 32.0).  Fewer than eight
+  // feature tiles would all be dealt one by one, and each be read by every XCD: dX 640 wide (five) at 3 x 173 tokens 12.9 and 13.5,
+  // 768 wide (six) at 295 15.1 and 15.5, where 1024 wide (eight) at 512 takes 20.5 and 18.9; QKV and output of five and six gain 0 to 1 %.
+  d.by_feature = a.F > (long)a.B * a.N && d.features >= 8;
   d.rows = (d.by_feature ? d.features : d.tokens) / 8;
 }
 
