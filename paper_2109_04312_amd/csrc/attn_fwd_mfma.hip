@@ -251,11 +251,10 @@ hipError_t launch_fwd_mfma(const AttnArgs& a, hipStream_t stream) {
     return owners ? launch_small<true, false>(a, grid, stream) : launch_small<false, false>(a, grid, stream);
   }
   ProfileScope prof(2, stream);
-  const bool many = (int)grid.x > kManyRecords;
-  const auto kernel = first ? (join ? (many ? fwd_mfma_kernel<true, true, true> : fwd_mfma_kernel<true, true, false>)
-                                    : (many ? fwd_mfma_kernel<true, false, true> : fwd_mfma_kernel<true, false, false>))
-                            : (join ? (many ? fwd_mfma_kernel<false, true, true> : fwd_mfma_kernel<false, true, false>)
-                                    : (many ? fwd_mfma_kernel<false, false, true> : fwd_mfma_kernel<false, false, false>));
+  const bool many = !first && (int)grid.x > kManyRecords;   // (chunks first: never that many)
+  const auto kernel = first  ? (join ? fwd_mfma_kernel<true, true, false> : fwd_mfma_kernel<true, false, false>)
+                      : many ? (join ? fwd_mfma_kernel<false, true, true> : fwd_mfma_kernel<false, false, true>)
+                             : (join ? fwd_mfma_kernel<false, true, false> : fwd_mfma_kernel<false, false, false>);
   hipLaunchKernelGGL(kernel, grid, block, 0, stream, MATE_UNIT_LISTS_VALUES(a), a);
   return hipGetLastError();
 }

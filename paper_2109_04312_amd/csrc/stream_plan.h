@@ -247,9 +247,14 @@ __device__ __forceinline__ bool take_unit(UnitLists l, const AttnArgs& a, int bl
   return join_chunks<kJoin>(u, glob);
 }
 
-// The same for launches of many records (kManyRecords), most of them empty where sequences differ in length: every step is loaded where
-// it is first needed and an empty record asks for nothing more.  us, forward of 13 sequences of up to 6512 with 16 heads (27000 records)
-// 79.5 with the form above and 74.4 with this one, of 11 of up to 6576, bucketed, 77.5 and 73.3; 2 x 8192 (5200) 50.2 and 51.3.
+// The same for launches of many records: every step is loaded where it is first needed and an empty record asks for nothing more,
+// which gains where most are empty, as they are where sequences differ in length.  us, the form above and this one.  Above the line, lengths
+// that differ: forward of 13 sequences of up to 6512, 16 heads (26832 records) 97.4 and 94.5, 16 of 4096 (20992) 73.7 and 72.1, 32 of 2048, 12
+// heads (16128) 55.8 and 54.9, backward there 240 and 235, 230 and 227, 170 and 168; full sequences: forward of 32 x 2048 118.8 and
+// 117.7, 48 x 1024 (16896) 114.4 and 113.7, 8 x 8192 (20736) 209.8 and 209.2, 64 x 512 (12288) 74.2 and 74.2, backward the same within 0.5 %.
+// Below it: forward and backward of 2 x 8192 (5184) 52.4 and 52.8, 147.1 and 148.8, forward of 4 x 8192 (10368) 103.5 and 103.4, of lengths
+// that differ 36.9 and 37.5, of 16 x 2048 (8064) 29.4 and 29.7.  (A forward with its chunks first, may_chunk and B H T <= 3072, has
+// 11880 records at most.)
 constexpr int kManyRecords = 12000;
 template <bool kChunksFirst, bool kJoin>
 __device__ inline bool take_unit_of_many(const AttnArgs& a, int block, Work& w) {
