@@ -542,10 +542,14 @@ ProjChoice choose_proj(const ProjArgs& a) {
   offer(proj_cost<Proj256>(a, 1.37, 3.14, 5.33), launch_proj<Proj256, kHeadTok, kTransposedW>, 1);
   // In one round only: in a second one, where sequences end in padding, 256 x 256 has skipped enough tiles to need none (1024 ->
   // 3072 at 12000 tokens, a fifth of them padding, 65.7 and 71.4 us).  dX, whose weights are four times as long, gains nothing.
+  // And where 128 x 128 needs more than the two tiles that a CU takes at once: long products in those take less than their
+  // constants say (us, 128 x 128 and these: 4096 -> 6144 at 8 x 76 tokens 55.0 and 74.7, 3456 -> 3840 at 1988 52.2 and 64.5, 4096 -> 2304 at 2 x
+  // 1769 65.9 and 80.1, d_o of 1536 from 3584 at 11 x 248 46.4 and 60.2; shorter ones are told apart by the costs).
+  const bool large = tiles_of<Proj128>(a) > 512;
   if constexpr (!kTransposedW)
-    if (tiles_of<Proj192x256>(a) <= 256) offer(proj_cost<Proj192x256>(a, 1.0, 0, 6.8), launch_proj<Proj192x256, kHeadTok, kTransposedW>, 1);
+    if (large && tiles_of<Proj192x256>(a) <= 256) offer(proj_cost<Proj192x256>(a, 1.0, 0, 6.8), launch_proj<Proj192x256, kHeadTok, kTransposedW>, 1);
   if constexpr (!kTransposedW || !kHeadTok)
-    if (tiles_of<Proj256x192>(a) <= 256) offer(proj_cost<Proj256x192>(a, 1.0, 0, 6.8), launch_proj<Proj256x192, kHeadTok, kTransposedW>, 1);
+    if (large && tiles_of<Proj256x192>(a) <= 256) offer(proj_cost<Proj256x192>(a, 1.0, 0, 6.8), launch_proj<Proj256x192, kHeadTok, kTransposedW>, 1);
   if constexpr (!kTransposedW)
     // (beyond 4608 features it takes up to 23 % more than its constants say)
     if (a.F % Proj192::kRowsA == 0 && a.F <= 4608) {

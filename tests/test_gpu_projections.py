@@ -291,6 +291,12 @@ def test_one_round_of_eight_wavefronts(B, N, H, E):
     check_bwd(N, B, N, H, E, pad_tail=N // 7)
 
 
+@pytest.mark.parametrize("B,N,H,E", [(8, 76, 32, 4096), (1, 1285, 20, 3456)])
+def test_long_contractions(B, N, H, E):
+    """More than 3271 terms and two 128 x 128 tiles a compute unit at most: QKV stays in those."""
+    check(N, B, N, H, E, pad_tail=N // 8)
+
+
 def test_results_larger_than_the_caches():
     """QKV: the first tiles' results stay in the L2, the last 32 MB are written through it; dX and d_o: all stay (63 MB)."""
     check(7, 5, 16383, 6, 384, pad_tail=2000)
