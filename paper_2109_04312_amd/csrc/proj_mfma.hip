@@ -281,7 +281,7 @@ struct ProjArgs : ProjStart {
 
 // kHeadTok: the token operand comes from head-layout tensors and the output is flat; else the reverse.
 // kTransposedW: the weight operand is read transposed.
-template <class S, bool kHeadTok, bool kTransposedW>
+template <class S, bool kHeadTok, bool kTransposedW, bool kBeside>
 __device__ __forceinline__ void product_tile(const ProjStart& p, const ProjArgs& a, char* lds, int b, int n0, int f0, bool through) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -398,7 +398,8 @@ __device__ __forceinline__ void product_tile(const ProjStart& p, const ProjArgs&
         const int head_slot = (f0 + fw) >> 6, x = head_slot / a.H, h = head_slot - x * a.H;
         dst = pick(x == 0, out_0, pick(x == 1, out_1, out_2)) + (((size_t)b * a.H + h) * p.N + n0) * kD + (fw & 63);
       }
-      const ResultRows<decltype(through)::value> result(dst);
+      const ResultRows<true> past_l2(dst);
+      const ResultRows<false> in_l2(dst);
       const unsigned token_bytes = (kHeadTok ? (unsigned)p.F : (unsigned)kD) * 2;   // between consecutive tokens
 #pragma unroll
       for (int j = 0; j < S::kOutB; ++j) {
@@ -413,20 +414,28 @@ __device__ __forceinline__ void product_tile(const ProjStart& p, const ProjArgs&
         const auto hi = __builtin_amdgcn_permlane16_swap(u[0][1], u[1][1], false, false);
         u32x4 v = {lo[0], hi[0], lo[1], hi[1]};
         if ((pad_bits >> j) & 1u) v = u32x4{0, 0, 0, 0};
-        if ((j0 + j) * 16 + r < rows) result.store((unsigned)row[j] * token_bytes + ((quarter & 1) * 16 + (quarter >> 1) * 8) * 2, v);
+        if ((j0 + j) * 16 + r < rows) {
+          const unsigned at = (unsigned)row[j] * token_bytes + ((quarter & 1) * 16 + (quarter >> 1) * 8) * 2;
+          if (through) past_l2.store(at, v);
+          else in_l2.store(at, v);
+        }
       }
     }
   };
-  if (through) store(std::true_type());
+  // Two groups: one copy of this, with a branch at every store; one group, or beside a weight gradient: a copy for each.  us, with two copies and
+  // with one: d_o 256 x 256 at 33 tokens 4.88 and 4.43, output 768 x 768 at 7 x 97 7.37 and 7.14, QKV there 8.6 and 8.3, over 1000 products in two
+  // groups 2 to 5 % shorter in the mean; one group, d_o 128 x 128 at 40 tokens 3.50 and 3.91; both gradients of 512 x 512 at 51 12.4 and 12.8.
+  if constexpr (S::kGroups == 2 && !kBeside) store(through);
+  else if (through) store(std::true_type());
   else store(std::false_type());
 }
 
-template <class S, bool kHeadTok, bool kTransposedW>
+template <class S, bool kHeadTok, bool kTransposedW, bool kBeside = false>
 __device__ __forceinline__ void dealt_product(const ProjStart& p, const ProjArgs& a, char* lds, int x, int y) {
   int token_tile, feature_tile, tile;
   if (!dealt_tile(p.deal, x, y, token_tile, feature_tile)) return;
   const int b = sequence_of(token_tile, (p.N + S::kRowsB - 1) / S::kRowsB, tile);
-  product_tile<S, kHeadTok, kTransposedW>(p, a, lds, b, tile * S::kRowsB, feature_tile * S::kRowsA, y * p.deal.grid_x() + x >= a.lazy_tiles);
+  product_tile<S, kHeadTok, kTransposedW, kBeside>(p, a, lds, b, tile * S::kRowsB, feature_tile * S::kRowsA, y * p.deal.grid_x() + x >= a.lazy_tiles);
 }
 
 template <class S, bool kHeadTok, bool kTransposedW>
@@ -988,7 +997,7 @@ __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4) void proj_bwd_kernel
   else {
     int x;
     const int y = uniform_div(blockIdx.x - w_blocks, a.deal.grid_x(), x);
-    dealt_product<S, kHeadTok, true>(a, a, lds, x, y);
+    dealt_product<S, kHeadTok, true, true>(a, a, lds, x, y);
   }
 }
 
