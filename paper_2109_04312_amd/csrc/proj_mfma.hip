@@ -633,7 +633,9 @@ __device__ __forceinline__ unsigned long long pad_mask(const unsigned char* flag
 // kChain blocks, so that a long range is no less exact than the sum of short ones.
 // kMerge: the range of a tile that is done last adds them all (otherwise another launch does).  Partial sums of a range are
 // then whole tiles, one after the other, so F and E must be whole tiles as well.
-template <class S, int kList, int kChain, bool kMerge>
+// kThrough: see ResultRows; not where another launch of the same tiles follows (8 x 2048 tokens, 768 wide gain 1.5 %, 4 x 10584
+// and 16 x 4096 lose 1.5 %).
+template <class S, int kList, int kChain, bool kMerge, bool kThrough>
 __device__ __forceinline__ void wgrad_tile(WgradArgs a, char* lds, int block) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -881,9 +883,7 @@ __device__ __forceinline__ void wgrad_tile(WgradArgs a, char* lds, int block) {
   }
   const bool partial = !kMerge && a.splits > 1;
   // a lane holds columns 16 i + 4 quarter .. + 3 of row 16 j + r
-  // (kMerge: at the end of a launch, through the L2.  Otherwise another launch of the same tiles follows: through, 8 x 2048 tokens,
-  // 768 wide gain 1.5 %, 4 x 10584 and 16 x 4096 lose 1.5 %)
-  const ResultRows<kMerge> rows((partial ? a.part + (size_t)split * a.F * a.E : a.out) + (size_t)f0 * a.E);
+  const ResultRows<kThrough> rows((partial ? a.part + (size_t)split * a.F * a.E : a.out) + (size_t)f0 * a.E);
 #pragma unroll
   for (int j = 0; j < S::kOutB; ++j) {
     const int f = (wb * S::kFB + group * S::kOutB + j) * 16 + r;
@@ -905,7 +905,7 @@ __device__ __forceinline__ void wgrad_tile(WgradArgs a, char* lds, int block) {
 template <class S>
 __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void proj_wgrad_kernel(WgradArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  wgrad_tile<S, kMaxRange, 0, false>(a, lds, blockIdx.x);
+  wgrad_tile<S, kMaxRange, 0, false, false>(a, lds, blockIdx.x);
 }
 
 // For a weight gradient that no product follows.
@@ -993,7 +993,7 @@ template <class S, bool kHeadTok>
 __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4) void proj_bwd_kernel(WgradArgs w, ProjArgs a, int w_blocks) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   static_assert(S::kThreads == Wgrad128::kThreads, "one workgroup size for both");
-  if ((int)blockIdx.x < w_blocks) wgrad_tile<Wgrad128, kOneLaunchBlocks, kOneLaunchChain, true>(w, lds, blockIdx.x);
+  if ((int)blockIdx.x < w_blocks) wgrad_tile<Wgrad128, kOneLaunchBlocks, kOneLaunchChain, true, true>(w, lds, blockIdx.x);
   else {
     int x;
     const int y = uniform_div(blockIdx.x - w_blocks, a.deal.grid_x(), x);
@@ -1105,19 +1105,22 @@ hipError_t launch_bwd(WgradArgs w, ProjArgs a, const BwdPlan& p, char* ws, int w
 // 64 blocks each, 23.2, 34.0, 36.2.
 using Wgrad64 = Shape<2, 1, 2, 2, 2, 1, 2>;
 using Wgrad64x64 = Shape<1, 1, 2, 2, 2, 1, 2>;
-template <class S>
+template <class S, bool kThrough>
 __global__ __launch_bounds__(S::kThreads, S::kAllWaves / 4 * S::kPerCU) void proj_wgrad_alone_kernel(WgradArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  wgrad_tile<S, kOneLaunchBlocks, kOneLaunchChain, true>(a, lds, blockIdx.x);
+  wgrad_tile<S, kOneLaunchBlocks, kOneLaunchChain, true, kThrough>(a, lds, blockIdx.x);
 }
-template <class S>
+// kThrough: dW of more than 1 MB (us, left and through: 256 x 256 at 47 tokens 6.45 and 6.65, 512 x 512 at 2 x 101 6.5 and 6.65; of 240 sizes
+// up to 0.7 MB take 1.5 % longer through, 0.75 to 1 MB 1 %, 1.1 to 2 MB 0.3 % less, 2.2 to 3 MB 1.7 %, 4.5 to 9 MB 5 %; beside a product there
+// is no difference up to 1 MB).
+template <class S, bool kThrough>
 hipError_t launch_wgrad_alone(WgradArgs w, const BwdPlan& p, char* ws, int kernel_id, hipStream_t stream) {
   place_ranges(w, p, ws);
-  const hipError_t e = allow_lds<&proj_wgrad_alone_kernel<S>>(S::kLds);
+  const hipError_t e = allow_lds<&proj_wgrad_alone_kernel<S, kThrough>>(S::kLds);
   if (e != hipSuccess) return e;
   const int tiles = ((w.F + S::kRowsB - 1) / S::kRowsB) * ((w.E + S::kRowsA - 1) / S::kRowsA);
   ProfileScope prof(kernel_id, stream);
-  hipLaunchKernelGGL(proj_wgrad_alone_kernel<S>, dim3((tiles * p.ranges + 7) / 8 * 8), dim3(S::kThreads), S::kLds, stream, w);
+  hipLaunchKernelGGL((proj_wgrad_alone_kernel<S, kThrough>), dim3((tiles * p.ranges + 7) / 8 * 8), dim3(S::kThreads), S::kLds, stream, w);
   return hipGetLastError();
 }
 hipError_t run_wgrad_alone(const WgradArgs& w, BwdPlan p, char* ws, size_t room, int kernel_id, hipStream_t stream) {
@@ -1127,8 +1130,14 @@ hipError_t run_wgrad_alone(const WgradArgs& w, BwdPlan p, char* ws, size_t room,
     lay_out(p, w, p.ranges, tiles * cut);
     if (cut == 1 || (tiles * p.ranges * cut <= 256 && (p.ranges == 1 || p.total <= room))) break;
   }
-  const auto launch = cut == 4 ? launch_wgrad_alone<Wgrad64x64> : cut == 2 ? launch_wgrad_alone<Wgrad64> : launch_wgrad_alone<Wgrad128>;
-  return launch(w, p, ws, kernel_id, stream);
+  const auto run = [&](auto through) {
+    constexpr bool kThrough = decltype(through)::value;
+    const auto launch = cut == 4   ? launch_wgrad_alone<Wgrad64x64, kThrough>
+                        : cut == 2 ? launch_wgrad_alone<Wgrad64, kThrough>
+                                   : launch_wgrad_alone<Wgrad128, kThrough>;
+    return launch(w, p, ws, kernel_id, stream);
+  };
+  return (size_t)w.F * w.E > (256u << 10) ? run(std::true_type()) : run(std::false_type());
 }
 
 // dW (unless w.out is null) and the other gradient (unless a.out[0] is).  One launch if these costs say that it is
