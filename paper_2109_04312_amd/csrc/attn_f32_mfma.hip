@@ -330,11 +330,12 @@ struct Quarter {
   int turn;  // which wavefront takes the first tile: the ones that get a tile more than the others
              // should not all sit on the same SIMD
 };
-template <bool kOwnersFirst>
+template <bool kOwnersFirst, bool kMany>
 __device__ inline bool take_quarter(const UnitLists& l, const AttnArgs& a, unsigned block, Quarter& q) {
   q.sub = ((block >> 3) + (block >> 5)) & 3;
   q.turn = block >> 5;
-  if (!take_unit<kOwnersFirst, false>(l, a, ((block >> 5) << 3) | (block & 7), q.w)) return false;
+  const int unit = ((block >> 5) << 3) | (block & 7);
+  if (kMany ? !take_unit_of_many<kOwnersFirst, false>(a, unit, q.w) : !take_unit<kOwnersFirst, false>(l, a, unit, q.w)) return false;
   const UnitPlan& u = q.w.u;
   if (u.kind == UNIT_PAD) return true;
   // (a chunked question-token owner: its first unit streams everything, there are no partials here)
@@ -453,7 +454,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(MATE_UNIT_LISTS, A
   __shared__ float2 stat[kWaves][kRows];
   __shared__ int row_tok[kRows], inexact[kWaves];
   Quarter q;
-  if (!take_quarter<kOwnersFirst>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x, q)) return;
+  if (!take_quarter<kOwnersFirst, false>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x, q)) return;
   const int tid = threadIdx.x, lane = tid & 63, m = lane & 31, hl = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const size_t bh = (size_t)q.w.bh * a.N;
@@ -897,12 +898,13 @@ __global__ __launch_bounds__(kThreads) void delta_f32_kernel(AttnArgs a) {
     if (piece == 0 && first + 16 * i < rows) reinterpret_cast<unsigned*>(a.delta)[first + 16 * i] = bits;
   }
 }
+template <bool kMany>
 __global__ __launch_bounds__(kThreads, 2) void bwd_f32_kernel(MATE_UNIT_LISTS, AttnArgs a, unsigned first) {
   __shared__ __attribute__((aligned(1024))) BwdLds lds;
   const unsigned block = first + blockIdx.x;
   Quarter q;
   // (32 workgroups are the quarters of eight units, one on each XCD)
-  if (!take_quarter<false>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, ((block >> 6) << 5) | (block & 31), q)) return;
+  if (!take_quarter<false, kMany>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, ((block >> 6) << 5) | (block & 31), q)) return;
   if (block & 32) dq_quarter(a, q, lds);
   else dkv_quarter(a, q, lds);
 }
@@ -936,8 +938,13 @@ hipError_t launch_bwd_f32(const AttnArgs& a, hipStream_t stream) {
   hipLaunchKernelGGL(delta_f32_kernel, dim3((unsigned)((rows + kDeltaRows - 1) / kDeltaRows)), dim3(kThreads), 0, stream, a);
   hipError_t e = hipGetLastError();
   const unsigned blocks = 2 * 4 * (unsigned)unit_grid(a.B, a.H, a.N, a.n_col), most = 1u << 23;  // (a launch has less than 2^32 threads)
+  // Step by step (see kManyRecords) from 40 rounds of workgroups on.  us, in one round trip and so, 16 heads unless said, lengths that differ: 20 x
+  // 936 203.8 and 196.2, 15 x 653 131.5 and 128.6, 12 x 637 97.9 and 95.7, 18 x 846, 12 heads 142.7 and 137.9; full sequences: 29 x 315 225 and 223, 19 x
+  // 652, 12 heads 241 and 237.5, 9 x 1325 421 and 424.  With fewer, full ones are up to 3 % longer (3 x 1073, 12 heads 87.7 and 90.9).  (The forward
+  // gains by the round trip at any size, up to 5 %.)
+  const auto kernel = blocks > 20000 ? bwd_f32_kernel<true> : bwd_f32_kernel<false>;
   for (unsigned first = 0; first < blocks && e == hipSuccess; first += most) {
-    hipLaunchKernelGGL(bwd_f32_kernel, dim3(min(most, blocks - first)), dim3(kThreads), 0, stream, MATE_UNIT_LISTS_VALUES(a), a, first);
+    hipLaunchKernelGGL(kernel, dim3(min(most, blocks - first)), dim3(kThreads), 0, stream, MATE_UNIT_LISTS_VALUES(a), a, first);
     e = hipGetLastError();
   }
   return e;

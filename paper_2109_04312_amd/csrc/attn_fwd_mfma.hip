@@ -223,31 +223,36 @@ __global__ __launch_bounds__(kThreads, 4) void fwd_mfma_kernel(MATE_UNIT_LISTS, 
             : !take_unit<kChunksFirst, kJoin>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x, w)) return;
   fwd_unit<1, true>(a, w, s);
 }
-template <bool kChunksFirst, bool kThrough>
+template <bool kChunksFirst, bool kThrough, bool kMany>
 __global__ __launch_bounds__(kThreads, 2) void fwd_small_kernel(MATE_UNIT_LISTS, AttnArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char dynamic_lds[];
   Work w;
-  if (!take_unit<kChunksFirst, false>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x, w)) return;
+  if (kMany ? !take_unit_of_many<kChunksFirst, false>(a, blockIdx.x, w)
+            : !take_unit<kChunksFirst, false>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, blockIdx.x, w)) return;
   if (OwnerSplit<2>(w.u, 0).four) fwd_unit<2, kThrough>(a, w, *reinterpret_cast<FwdLds<2>*>(dynamic_lds));
   else fwd_unit<1, kThrough>(a, w, *reinterpret_cast<FwdLds<1>*>(dynamic_lds));
 }
 
 }  // namespace
 
-template <bool kChunksFirst, bool kThrough>
+template <bool kChunksFirst, bool kThrough, bool kMany = false>
 static hipError_t launch_small(const AttnArgs& a, dim3 grid, hipStream_t stream) {
-  const hipError_t e = allow_lds<&fwd_small_kernel<kChunksFirst, kThrough>>(sizeof(FwdLds<2>));
+  const hipError_t e = allow_lds<&fwd_small_kernel<kChunksFirst, kThrough, kMany>>(sizeof(FwdLds<2>));
   if (e != hipSuccess) return e;
   ProfileScope prof(2, stream);
-  hipLaunchKernelGGL((fwd_small_kernel<kChunksFirst, kThrough>), grid, dim3(kThreads), sizeof(FwdLds<2>), stream, MATE_UNIT_LISTS_VALUES(a), a);
+  hipLaunchKernelGGL((fwd_small_kernel<kChunksFirst, kThrough, kMany>), grid, dim3(kThreads), sizeof(FwdLds<2>), stream, MATE_UNIT_LISTS_VALUES(a), a);
   return hipGetLastError();
 }
 hipError_t launch_fwd_mfma(const AttnArgs& a, hipStream_t stream) {
   const dim3 grid(unit_grid(a.B, a.H, a.N, a.n_col)), block(kThreads);
   const bool first = fwd_chunks_first(a.B, a.H, a.N), join = joins_chunks(a.B, a.H, a.N);
   if (small_forward(a.B, a.H, a.N)) {
-    const bool owners = small_owners_first(a.B, a.H, a.N);
-    if (result_through(a.B, a.H, a.N, 2)) return owners ? launch_small<true, true>(a, grid, stream) : launch_small<false, true>(a, grid, stream);
+    const bool owners = small_owners_first(a.B, a.H, a.N), through = result_through(a.B, a.H, a.N, 2);
+    // Sequences of one tile whose records, half of them padding and empty ones, are more than the chip takes at once: step by step (see
+    // kManyRecords).  us, in one round trip and so: 24 x 33, 8 heads 7.35 and 6.85, 14 x 45, 12 heads 7.3 and 6.8; 9 x 68, 16 heads (576 records)
+    // 6.1 and 6.25, and longer sequences at as many records 0 to 2 % longer.
+    if (owner_slots(a.N) == 1 && grid.x >= 640) return through ? launch_small<true, true, true>(a, grid, stream) : launch_small<true, false, true>(a, grid, stream);
+    if (through) return owners ? launch_small<true, true>(a, grid, stream) : launch_small<false, true>(a, grid, stream);
     return owners ? launch_small<true, false>(a, grid, stream) : launch_small<false, false>(a, grid, stream);
   }
   ProfileScope prof(2, stream);

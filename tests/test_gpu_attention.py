@@ -227,6 +227,16 @@ def test_launches_on_either_side_of_many_records(B, N, H):
     check_workload(w, backward=True, pairs=[(0, 0), (0, H - 1), (B // 2, 1), (B - 1, H - 2), (B - 1, H - 1)])
 
 
+# small launches on either side of where units are found step by step: the backward of one or two tiles from 1152 workgroups on (8 and
+# 9 sequences of 60 with 16 heads, 5 and 6 of 200; three tiles never), the forward of one tile from 640 records on (9 and 10
+# of 60; 10 of 128 with a result beyond 2 MB), the f32 backward beyond 20000 workgroups
+@pytest.mark.parametrize("dtype,B,N,H", [("bf16", 8, 60, 16), ("bf16", 9, 60, 16), ("bf16", 10, 60, 16), ("bf16", 10, 128, 16), ("bf16", 5, 200, 16),
+                                         ("bf16", 6, 200, 16), ("bf16", 5, 300, 16), ("f32", 22, 130, 16), ("f32", 23, 130, 16)])
+def test_small_launches_on_either_side_of_many_records(dtype, B, N, H):
+    w = small_workload(N, dtype, B=B, N=N, H=H, max_rows=12, max_cols=6, max_global=min(N // 4, 40))
+    check_workload(w, backward=True, pairs=[(0, 0), (0, H - 1), (B // 2, 1), (B - 1, H - 2), (B - 1, H - 1)])
+
+
 @pytest.mark.parametrize("dtype,B,N", [("bf16", 4, 341), ("bf16", 4, 342), ("f32", 2, 341), ("f32", 2, 342)])
 def test_results_on_either_side_of_two_megabytes(dtype, B, N):
     """A small forward's result stays in the L2 or passes through it (12 heads: 341 positions are the last below 2 MB)."""
