@@ -180,13 +180,13 @@ def test_backward_is_bit_reproducible():
     assert torch.equal(out, out2) and torch.equal(lse, lse2)
 
 
-@pytest.mark.parametrize("id_step", [1, 1000])
-def test_more_unit_cuts_than_records(id_step):
+@pytest.mark.parametrize("id_step,N,rows,cols", [(1, 4096, 30, 15), (1000, 4096, 30, 15), (1, 8192, 62, 31)])
+def test_more_unit_cuts_than_records(id_step, N, rows, cols):
     """Every row is a segment of 129 slots and every column one of 258: cutting at each of them
-    would need about twice as many unit records as a view has, so the builder falls back to a cut
-    every 128 slots, and units straddle long segments again.  id_step = 1000 takes the ids past
-    the counting sort's range (general sorting path)."""
-    N, rows, cols = 4096, 30, 15
+    would need more unit records than a view has, so the builder falls back to a cut every 128 slots,
+    and units straddle long segments again.  Each way to list units: one wavefront (up to 64
+    records), the workgroup (8192 positions have 98), and id_step = 1000, which takes the ids past the
+    counting sort's range (general sorting path)."""
     L, G, P = synth.TOK_LOCAL, synth.TOK_GLOBAL, synth.TOK_PAD
     flags = np.full((1, N), P, np.uint8)
     row = np.zeros((1, N), np.int32)
@@ -201,14 +201,14 @@ def test_more_unit_cuts_than_records(id_step):
     st = synth.Structure(row, col, flags)
     rng = np.random.default_rng(129 + id_step)
     q, k, v, do = synth.draw_tensors(rng, 1, 2, N, 64, "bf16", 4)
-    w = synth.Workload(f"cuts_step{id_step}", "bf16", st, np.array([ROW, COL], np.uint8), q, k, v, do, 0.125)
+    w = synth.Workload(f"cuts_step{id_step}_{N}", "bf16", st, np.array([ROW, COL], np.uint8), q, k, v, do, 0.125)
     check_workload(w, backward=True)
 
 
-@pytest.mark.parametrize("segments,N", [(63, 500), (64, 500), (65, 700), (128, 700), (129, 700), (128, 2000)])
+@pytest.mark.parametrize("segments,N", [(63, 500), (64, 500), (65, 700), (128, 700), (129, 700), (128, 2000), (100, 5248), (100, 5249)])
 def test_units_of_as_many_segments_as_lanes(segments, N):
-    """Work units listed by one wavefront (a segment or two to a lane) and by all: segment counts beside 64 and 128, with a
-    long segment among short ones in each view."""
+    """Work units listed by one wavefront (a segment or two to a lane) and by all: segment counts beside 64 and 128, and 63
+    and 65 records (5248 and 5249 positions), with a long segment among short ones in each view."""
     rng = np.random.default_rng(segments + N)
     ids = np.sort(np.concatenate([np.arange(segments), rng.integers(0, segments, N - segments)]))
     row = np.stack([np.where(rng.random(N) < 0.4, segments // 2, ids), rng.permutation(ids)]).astype(np.int32)
