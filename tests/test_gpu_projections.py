@@ -286,7 +286,7 @@ def test_tiles_dealt_by_feature(B, N, H, E):
 
 @pytest.mark.parametrize("B,N,H,E", [(5, 901, 12, 768), (1, 3999, 16, 1024), (2, 4225, 16, 1024)])
 def test_one_round_of_eight_wavefronts(B, N, H, E):
-    """Tiles of 192 x 256 (QKV; the last a token or a feature block) and of 256 x 192 (output, d_o) in one round."""
+    """Tiles of 192 x 256 in one round: QKV of the first two sizes, the output of the last (its last feature tile a third)."""
     check(N, B, N, H, E, pad_tail=N // 7)
     check_bwd(N, B, N, H, E, pad_tail=N // 7)
 
@@ -295,6 +295,20 @@ def test_one_round_of_eight_wavefronts(B, N, H, E):
 def test_long_contractions(B, N, H, E):
     """More than 3271 terms and two 128 x 128 tiles a compute unit at most: QKV stays in those."""
     check(N, B, N, H, E, pad_tail=N // 8)
+
+
+@pytest.mark.parametrize("B,N,H,E", [(12, 300, 12, 768), (13, 383, 12, 768), (1, 11000, 16, 1024), (2, 4225, 16, 1024)])
+def test_one_round_of_256_by_192(B, N, H, E):
+    """Tiles of 256 x 192 in one round, where 192 x 256 would be two or are not offered: QKV of the first two sizes (the last
+    token tile 108 and 191 rows), the output of the third (56 rows), d_o of the last two (one row, by itself)."""
+    from paper_2109_04312_amd import mate
+    check(N, B, N, H, E, pad_tail=N // 7)
+    x, _, _, w_o, _, flags, o = make(N, B, N, H, E, pad_tail=N // 7)
+    dy = bf16(np.random.default_rng(N).standard_normal((B, N, E)))
+    want, _, _ = orc.project_out_backward(o, w_o, flags, dy)
+    args = (dev(o), dev(w_o), torch.from_numpy(flags).cuda(), dev(dy))
+    got = mate.out_project_bwd(*args, want_dw=False, want_dbias=False)[0]
+    close(got, want, "d_o")
 
 
 def test_results_larger_than_the_caches():
