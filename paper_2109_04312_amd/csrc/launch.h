@@ -14,8 +14,10 @@ namespace mate {
 // sequence of 512 with its tables 14.93 and 14.98, 3 x 512 (2.4 MB) 8.27 and 8.22, 2 x 1000 10.03 and 9.78, 8 x 512 (6.3 MB) 11.27 and
 // 10.69; f32, 6 x 106 with 4 heads and its tables 11.77 and 11.9, 4 x 512 (6.3 MB) 13.81 and 13.66; dense backward of 1 x 64, 4 heads (0.1
 // MB) 5.79 and 5.95, 4 x 60, 12 heads (1.1 MB) 6.01 and 6.10, 4 x 128 (2.4 MB) 8.02 and 8.06, 8 x 128 (4.7 MB) 8.31 and 8.14.  The other
-// backward kernels and the products gain nothing by the L2 at any size.  (Zeros of pad rows
-// always do: their workgroups end long before the launch.)
+// backward kernels and the products pass it at any size: backward by segments, 12 heads, of 1 x 128 10.31 and 10.27, 1 x 512 14.60 and
+// 14.31, 8 x 512 23.4 and 22.5, 1 x 2048 18.9 and 17.7, f32 of 1 x 128, 4 heads 11.66 and 11.77, 1 x 512, 12 heads 25.3 and 24.8; 768 wide, QKV
+// at 64 tokens 7.22 and 7.21, 512 8.22 and 7.96, 8 x 512 19.3 and 17.6, output 7.10 and 7.10, 7.55 and 7.52, 10.7 and 10.1, both gradients of QKV at
+// 300 16.4 and 15.8 (dW alone has a rule of its own).  (Zeros of pad rows always do: their workgroups end long before the launch.)
 inline bool result_through(int B, int H, int N, int bytes_each) { return (size_t)B * H * N * 64 * bytes_each > (2u << 20); }
 
 struct AttnArgs {

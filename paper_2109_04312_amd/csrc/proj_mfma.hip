@@ -506,9 +506,10 @@ hipError_t launch_proj(ProjArgs a, int kernel_id, hipStream_t stream) {
 // Which shape.  A compute unit that gets n tiles of a shape needs about (k / 64) (c2 for every two tiles, c1 for
 // an odd last one) + e n us, so the shape with the smallest such sum wins, n being the rounds of tiles:
 // large tiles once they fill the chip, smaller ones where they fit its units better.  The constants were fitted
-// to the times of the other six shapes for 912 products (64 to 40000 tokens, widths 128 to 4096, 2 to 32 heads, no
-// padding): the shape that they choose takes 0.2 % more than the fastest one on average and 22 % at most, against
-// 2.4 % and 74 % with constants measured on widths of 768 and 1024 alone and n = ceil(tiles / 256).  For
+// to the times of six shapes for 912 products when n was the rounds of the busiest of eight XCDs, which no deal of tiles evened out; with the
+// present deal, n and nine shapes, over 7148 products (64 to 40000 tokens, widths 128 to 4096, 2 to 32 heads, no padding), the shape that they
+// choose takes 0.5 % more than the fastest one on average, more than 5 % in one of 26 and 27 % at most (short contractions of 128 and 256
+// terms and many tokens, where larger tiles than the chosen ones would be faster).  For
 // instance, us, 256 x 256, 192 x 128, 128 x 128, with two groups, 128 x 64, with two groups: 2048 -> 6144 at 900
 // tokens 47, 39, 34, 40, 55, 61, at 8 x 512 98, 116, 111, 132, 216, 225; 1024 -> 3072 at 512 tokens 27, 17, 15, 12, 11, 11.
 // 192 x 128 with two groups came later, fitted to 186 products (128 to 16384 tokens, widths 128 to 2048): it is for
@@ -519,7 +520,9 @@ hipError_t launch_proj(ProjArgs a, int kernel_id, hipStream_t stream) {
 // 192 x 256 and 256 x 192, eight wavefronts, read 0.9 of what a CU loads for as many products in 192 x 128 and have a third more
 // tiles than 256 x 256: for sizes whose tiles are one round.  us, before and with them: 768 -> 2304 at 8 x 512 23.1 -> 22.1, at
 // 5 x 929 22.7 -> 21.3, 1024 -> 3072 at 4000 28.1 -> 25.3, 1024 -> 1024 at 2 x 4344 28.0 -> 23.5, at 10752 29.4 -> 26.4, d_o
-// there with dW 55.5 -> 52.2.
+// there with dW 55.5 -> 52.2.  Their constants (1.0 a stage, 6.8) were read off these times and are the same for both, so 192 x 256 is taken where
+// both are one round; of 128 such products 256 x 192 would be 1 % faster in the mean, between 5 % slower (768 -> 2304 at 9 x 458 19.3 and 20.2)
+// and 9 % faster (4096 -> 6144 at 8 x 76 74.7 and 68.6).
 //                        features x tokens, wavefronts, stages, workgroups per CU, groups
 using Proj256 = Shape<4, 4, 2, 4, 2, 1>;      // 256 x 256
 using Proj192x256 = Shape<3, 4, 2, 4, 2, 1>;  // 192 x 256  (plain weights, as below)
@@ -1142,13 +1145,16 @@ hipError_t run_wgrad_alone(const WgradArgs& w, BwdPlan p, char* ws, size_t room,
 
 // dW (unless w.out is null) and the other gradient (unless a.out[0] is).  One launch if these costs say that it is
 // faster.  They were fitted to 130 pairs of gradients (64 to 16384 tokens, 256 to 1536 wide) in up to fifteen forms;
-// over them the rule gains 16 %, loses 5 % at most and is 1.5 % behind the best form of each.  us, as two launches and
+// over them the rule gained 16 %, lost 5 % at most and was 1.5 % behind the best form of each.  Over 1800 pairs of up to 40000 tokens, with the
+// present deal of tiles, what it takes is 0.2 % behind the better of two launches and the best one launch in the mean, 16 % at most (1536 wide at
+// 2453 tokens 43.6 and 50.2).  us, as two launches and
 // as one, gradients of QKV and of the output projection, 768 wide: 512 tokens 27.1 -> 16.8 and 17.8 -> 11.1, 2048 tokens
 // 32.5 -> 23.5 and 22.4 -> 18.7, 8 x 512 44 -> 39.5 and 26.4 -> 23.0, 3 x 1999 64 -> 53.5 and 32 -> 27;
 // 1024 wide, 1024 tokens 35.8 -> 25 and 22.9 -> 15.3, 8 x 512 61 -> 60.5 and 35 -> 27.5.
 // dW alone follows the same rule up to kSameBits token blocks, so that it is the same bits whether or not the other gradient
 // is wanted (us, as two launches and as one: 512 tokens 11.1 -> 9.5 and 10.6 -> 7.8, 2048 tokens 23.0 -> 18.2 and 18.3 ->
-// 14.9, 8 x 512 27 -> 29.1 and 22.3 -> 18.8; at worst, 1024 wide at 2500 tokens, 25.5 -> 27.2).  Beyond, the form that is
+// 14.9, 8 x 512 27 -> 29.1 and 22.3 -> 18.8; at worst, 512 wide with 8 heads at 13 x 134, 18.8 -> 22.6, where both gradients are 24.3 ->
+// 22.1).  Beyond, the form that is
 // faster beside a product can take 1.2 times as long without one (768 wide, 15 x 512 39 -> 48.3), and dW alone has two
 // unless its tiles of 128 x 128 nearly fill the chip (1024 wide, 3 x 1999 58.2 -> 53.6).
 constexpr int kSameBits = 64;

@@ -11,8 +11,14 @@ namespace mate {
 // padding at the end of the sequences is spread over all XCDs.  The tiles of the last token tiles, fewer than eight, are
 // dealt one by one: no XCD has more than one tile more than another, where 21 whole token tiles with 12 feature tiles were 36
 // tiles on some XCDs' 32 CUs, two rounds where one does (1024 -> 3072 at 5376 tokens 38 -> 32 us, at 10752 74 -> 61, gradients
-// of the output projection at 7 x 577 tokens, 768 wide 31.2 -> 25.2, at 9 x 1000 40 -> 33; where it saves no round, 1024 ->
-// 3072 at 25 x 273, 71 -> 72.5).  (Halves and quarters of a token tile's features to an XCD: 0 to 4 % slower.)
+// of the output projection at 7 x 577 tokens, 768 wide 31.2 -> 25.2, at 9 x 1000 40 -> 33; over 280 products of 1000 tokens and more QKV
+// takes 0.91 of what it took before this deal, the tile shapes chosen for it and results through the L2, the output 0.92,
+// dX 0.97, d_o 0.94).  Which tiles are padding is not known here: where sequences end in it, the XCD with the most live tiles gets its share
+// of the last ones too, and one product in a hundred takes a round more by that (1024 -> 1024 at 6 x 5458 tokens, a tenth padding: one XCD has 64
+// live tiles for its 32 CUs and gets another, 71 -> 88; 1024 -> 3072 at 5 x 3378, a third, 91 -> 115; 1536 -> 4608 at 12 x 1189 170 -> 198).  (Tried:
+// whole token tiles wherever dealing the last ones one by one saves no round for full sequences.  These products are as before then, others
+// up to 13 % slower or faster, 0.0 % in the mean over 600, and both gradients in one launch up to 1.7 times as long.  Halves and
+// quarters of a token tile's features to an XCD: 0 to 4 % slower.)
 constexpr int kMostGridY = 32768;  // (a grid's second dimension is at most 65536: the third continues it)
 struct TileDeal {
   int tokens, features;  // tiles
