@@ -228,6 +228,133 @@ __global__ __launch_bounds__(kThreads) void fwd_dense_kernel(const void* q, cons
 }
 
 // ======================================================================================
+// forward of up to 128 positions
+// ======================================================================================
+// One workgroup per (sequence, head), whose keys and values are in LDS at once; wavefront w owns queries 16 w .. 16 w + 15.  All scores
+// of a query are there before the first is used, so there is one maximum and nothing to rescale, and one barrier.  Like the backward
+// below, such a launch is as long as a wavefront's own chain.
+// us, before (128 queries a workgroup, 32 a wavefront) and so: 64 x 64 positions, 16 heads 7.3 -> 5.6, 64 x 33 7.0 -> 5.1, 17 x 64 5.5 -> 4.5, one
+// sequence of 64, 4 heads 4.6 -> 4.2; 128 positions, 1 x, 4 heads 5.6 -> 5.1, 16 x, 16 heads 6.2 -> 5.6, 32 x, 12 heads 7.25 -> 6.85, 43 x 8.9 -> 8.1,
+// 64 x, 12 heads 11.05 -> 11.2, 16 heads 14.2 -> 13.9; 40 x 96, 16 heads 8.9 -> 7.05.
+template <int NW>
+struct ShortShape {
+  static constexpr int kRows = 16 * NW;                   // most positions
+  static constexpr int kBlocks = kRows / 32;              // 32-row blocks
+  static constexpr int kBytes = kRows * 128;              // of one tensor
+  // Backward: K tiles | Q tiles | dO tiles | V tiles; dS^T, 64 queries a tile, comes over the last three
+  static constexpr int kBwdLds = (1 + ((kBlocks + 1) / 2 > 3 ? (kBlocks + 1) / 2 : 3)) * kBytes;
+};
+// The rows of X to LDS, eight per instruction (rows past N repeat the last).
+template <int NW>
+__device__ __forceinline__ void stream_short(const unsigned short* X, const char* tile, int N, int wave, int lane) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int g = wave + i * NW, row = 8 * g + (lane >> 3), chunk = (lane & 7) ^ swz_quad(row);
+    load_to_lds_16(X, (unsigned)min(row, N - 1) * 128u + chunk * 16, tile + g * 1024);
+  }
+}
+// Sixteen result rows of a wavefront, scaled and rounded to bf16, through 2 KB of LDS that no other wavefront uses.  (Registers e
+// of lane 16 q + r: dims 16 d + 4 q + e of row r.)  Pad positions: zeros, whatever was computed for them.
+template <bool kThrough>
+__device__ __forceinline__ void store_short(const f32x4 (&acc)[4], float mul, bool live, char* st, unsigned short* out, int own, int N, int lane) {
+  const int r = lane & 15, q = lane >> 4;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    uint2 w = make_uint2(pack2(acc[d][0] * mul, acc[d][1] * mul), pack2(acc[d][2] * mul, acc[d][3] * mul));
+    if (!live) w = make_uint2(0, 0);
+    *reinterpret_cast<uint2*>(st + r * 128 + (((2 * d + (q >> 1)) ^ (r & 7)) << 4) + 8 * (q & 1)) = w;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // LDS keeps a wavefront's accesses in order
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int it = 0; it < 2; ++it) {
+    const int row = it * 8 + (lane >> 3), piece = lane & 7;
+    const u32x4 v = *reinterpret_cast<const u32x4*>(st + row * 128 + ((piece ^ (row & 7)) << 4));
+    if (own + row < N) ResultRows<kThrough>(out).store((unsigned)(own + row) * (kD * 2) + piece * 16, v);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+template <int NW, bool kThrough>
+__global__ __launch_bounds__(64 * NW, 4) void fwd_dense_short_kernel(const void* q, const void* k, const void* v, const int* row_ids,
+                                                                     const int* col_ids, const unsigned char* flags, int sizes, DenseArgs a) {
+  using S = ShortShape<NW>;
+  __shared__ __attribute__((aligned(1024))) char kt[S::kBytes], vt[S::kBytes];
+  __shared__ __attribute__((aligned(16))) char rows[NW * 2048];
+  __shared__ __attribute__((aligned(16))) unsigned code[S::kRows];
+  const int N = sizes & 0xffff, tid = threadIdx.x, lane = tid & 63, bh_i = blockIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, quarter = lane >> 4, own = 16 * wave, pos = min(own + r, N - 1);
+  const size_t bh = (size_t)bh_i * N;
+  int h;
+  const int b = uniform_div_any(bh_i, sizes >> 16, h), view = head_view(a, h);
+  const int f = flags[(size_t)b * N + pos], id = (pick(view == 0, row_ids, col_ids) + (size_t)b * N)[pos];
+  const unsigned short* Q = static_cast<const unsigned short*>(q) + bh * kD;
+  bf16x8 qf[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(Q + (unsigned)pos * kD + 32 * ks + 8 * quarter);
+  stream_short<NW>(static_cast<const unsigned short*>(k) + bh * kD, kt, N, wave, lane);
+  stream_short<NW>(static_cast<const unsigned short*>(v) + bh * kD, vt, N, wave, lane);
+  const unsigned my_code = token_code(true, f, id);
+  // (padding meets anything: its results are replaced, and every row has a maximum)
+  const unsigned my_limit = my_code == 0u || my_code == kPadCode ? kPadCode : 1u;
+  if (lane < 16) code[own + r] = own + r < N ? my_code : kPadCode;
+  wait_vmcnt_le<0>(0);
+  __syncthreads();
+  if (own >= N) return;
+  const float sc = uniform(a.scale * kLog2e);
+  const QuadLanes lanes(lane);
+  const unsigned k_at = lds_addr(kt), v_at = lds_addr(vt);
+  f32x4 s[S::kBlocks][2];  // S^T: keys 8 q + 4 h + e of the block, query r
+  float mx = -INFINITY;
+#pragma unroll
+  for (int ib = 0; ib < S::kBlocks; ++ib)
+#pragma unroll
+    for (int hb = 0; hb < 2; ++hb) {
+      if (ib * 32 >= N) continue;
+      f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) x = mfma16(read_quad(lanes, k_at + ib * kBlockBytes, hb, ks), qf[ks], x);
+      const uint4 c4 = *reinterpret_cast<const uint4*>(code + ib * 32 + 8 * quarter + 4 * hb);
+      const unsigned codes[4] = {c4.x, c4.y, c4.z, c4.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = allowed(codes[e], my_code, my_limit) ? x[e] : -INFINITY;
+      mx = fmaxf(fmaxf(mx, x[0]), x[1]);
+      mx = fmaxf(fmaxf(mx, x[2]), x[3]);
+      s[ib][hb] = x;
+    }
+  mx = quad_max(mx);
+  const float msc = mx * sc;
+  float l = 0.f;
+  f32x4 acc[4];
+#pragma unroll
+  for (int d = 0; d < 4; ++d) acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int ib = 0; ib < S::kBlocks; ++ib) {
+    if (ib * 32 >= N) continue;
+    unsigned w[4];
+#pragma unroll
+    for (int hb = 0; hb < 2; ++hb) {
+      f32x4& x = s[ib][hb];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = __builtin_amdgcn_exp2f(fmaf(x[e], sc, -msc));
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        w[2 * hb + i] = pack2(x[2 * i], x[2 * i + 1]);
+        l = sum2(w[2 * hb + i], l);
+      }
+    }
+    const bf16x8 p8 = as_bf16x8(make_uint4(w[0], w[1], w[2], w[3]));
+#pragma unroll
+    for (int d = 0; d < 4; ++d) acc[d] = mfma16(read_quad_transposed(lanes, v_at + ib * kBlockBytes, d), p8, acc[d]);   // O^T += V^T P^T
+  }
+  l = quad_sum(l);
+  const bool live = my_code != kPadCode;  // pad positions: O = 0, LSE = 0
+  if (lane < 16 && own + r < N) a.lse[bh + own + r] = live ? (msc + __builtin_amdgcn_logf(l)) * kLn2 : 0.f;
+  store_short<kThrough>(acc, 1.f / l, live, rows + wave * 2048, static_cast<unsigned short*>(a.out) + bh * kD, own, N, lane);
+}
+
+// ======================================================================================
 // dQ (and -delta, -lse / scale for the dK/dV kernel)
 // ======================================================================================
 __global__ __launch_bounds__(kThreads, 4) void bwd_dq_dense_kernel(DenseArgs a) {
@@ -368,33 +495,43 @@ __global__ __launch_bounds__(kThreads) void bwd_dkv_dense_kernel(DenseArgs a) {
 // ======================================================================================
 // Backward of up to 256 positions in one launch
 // ======================================================================================
-// One workgroup per (sequence, head); wavefront w owns keys 32 w .. 32 w + 31 and meets every query, so S
-// and dP are computed once for all three gradients (the two kernels above compute them twice, and of
-// their 13 us each at B = 32, H = 12, N = 128 five are the launch): dK and dV accumulate in registers, the
-// bf16 dS^T of up to 128 queries goes through LDS, and dQ^T = K^T dS^T with both operands read transposed
-// (both permute the keys of a slice the same way).  15.3 us in place of 25.6; reading five tensors and
-// writing three once takes 10 at the rate of a large copy.
-template <int NW>
+// One workgroup per (sequence, head) that meets every pair, so S and dP are computed once for all three gradients (the two
+// kernels above compute them twice, and of their 13 us each at B = 32, H = 12, N = 128 five are the launch): a wavefront's dK and dV
+// accumulate in registers, the bf16 dS^T goes through LDS, and dQ^T = K^T dS^T with both operands read transposed (both permute
+// the keys of a slice the same way).
+//
+// Here for 193 to 256 positions: wavefront w owns keys 32 w .. 32 w + 31, and queries come in two passes of 128.  (Shorter
+// sequences: bwd_dense_short_kernel.)
+//
+// Per-lane LDS offsets of the operand reads: plain 16-byte reads for the four 16-wide k slices,
+// transposing reads for the two 32-row blocks of the other operand (see d2l.h).
+__device__ __forceinline__ void operand_offsets(int lane, int (&poff)[4], int (&toff)[2][2]) {
+  const int m = lane & 31, hl = lane >> 5;
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) poff[ks] = plain_off(m, hl, ks);
+#pragma unroll
+  for (int db = 0; db < 2; ++db) {
+    toff[db][0] = tr_off(lane, db, 0);
+    toff[db][1] = tr_off(lane, db, 1);
+  }
+}
 struct SmallShape {
-  static constexpr int kKeys = 32 * NW;                  // most positions
-  static constexpr int kBlocks = NW < 4 ? NW : 4;        // 32-query blocks per pass
-  static constexpr int kQueries = 32 * kBlocks, kPasses = NW / kBlocks;
+  static constexpr int kWaves = 8, kKeys = 32 * kWaves;  // most positions
+  static constexpr int kBlocks = 4, kQueries = 32 * kBlocks, kPasses = 2;  // 32-query blocks of a pass
   static constexpr int kKeyBytes = kKeys * 128, kQryBytes = kQueries * 128;
-  static constexpr int kDsBytes = kKeys * kQueries * 2;
-  static constexpr bool kOverlay = kDsBytes <= 2 * kQryBytes;  // dS^T over the Q and dO tiles
-  // K tiles | Q tiles | dO tiles | V tiles, dS^T (if it is not over Q and dO); dQ rows are staged over the Q tiles, dK
-  // and dV rows over the K tiles
-  static constexpr int kLds = kKeyBytes + 2 * kQryBytes + (kOverlay || kKeyBytes > kDsBytes ? kKeyBytes : kDsBytes);
+  // K tiles | Q tiles | dO tiles | V tiles, then dS^T; dQ rows are staged over the Q tiles, dK and dV rows over the K tiles
+  static constexpr int kLds = kKeyBytes + 2 * kQryBytes + kKeys * kQueries * 2;
 };
-template <int NW, bool kThrough>
-__global__ __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) void bwd_dense_small_kernel(
+template <bool kThrough>
+__global__ __launch_bounds__(64 * SmallShape::kWaves, 2) void bwd_dense_small_kernel(
     const void* q, const void* k, const void* v, const void* o, const void* dout, int sizes, DenseArgs a) {
-  using S = SmallShape<NW>;
+  using S = SmallShape;
+  constexpr int NW = S::kWaves;
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   __shared__ __attribute__((aligned(16))) unsigned code[S::kKeys];
   __shared__ __attribute__((aligned(16))) float nlse[S::kKeys], ndelta[S::kKeys];
   char *const kt = lds, *const qt = lds + S::kKeyBytes, *const gt = qt + S::kQryBytes;
-  char *const vt = gt + S::kQryBytes, *const ds = S::kOverlay ? qt : vt;
+  char *const vt = gt + S::kQryBytes, *const ds = vt;
   const int N = sizes & 0xffff, tid = threadIdx.x, lane = tid & 63, bh_i = blockIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = lane & 31, hl = lane >> 5;
@@ -430,8 +567,8 @@ __global__ __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) void bwd_dense_small_kern
   stream_rows(V, 0, keys, vt);
 
   // of this lane's row: delta and -lse / scale of the query, and the code.  (All rows are loaded whole, eight per
-  // instruction.  With key, value, dO and O operands straight from global memory, sixteen loads that touch 32 lines each: 32 x
-  // 128, 12 heads 16.8 us, now 15.3; 64 x 64 13.2, now 12.0; 8 x 256 20.4, now 18.1; one sequence of 128 9.1, now 8.2.)
+  // instruction.  With key, value, dO and O operands straight from global memory, sixteen loads that touch 32 lines each: 8 x 256,
+  // 12 heads 20.4 us, now 18.1.)
   const int pos = min(32 * wave + m, N - 1);
   {
     OwnedTile g_rows, o_rows;
@@ -509,7 +646,6 @@ __global__ __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) void bwd_dense_small_kern
           }
         }
       }
-    if (S::kOverlay) __syncthreads();  // everyone is done with the Q and dO tiles
     // dS^T: row = key, 64 queries per 128-byte row and tile, swizzled like the other tiles
     if (active)
 #pragma unroll
@@ -524,32 +660,25 @@ __global__ __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) void bwd_dense_small_kern
                 x.h[g & 1];
           }
     __syncthreads();
-    // dQ of query block `wave` (both halves of the head dims; with eight wavefronts one half each)
-    constexpr int kHalves = NW / S::kBlocks == 2 ? 1 : 2;
-    const int qb = wave % S::kBlocks, db0 = kHalves == 1 ? wave / S::kBlocks : 0;
+    // dQ: 32 dims (block db) of query block qb
+    const int qb = wave % S::kBlocks, db = wave / S::kBlocks;
     const bool has_block = (p * S::kBlocks + qb) * 32 < N;
-    f32x16 dq_acc[kHalves];
-#pragma unroll
-    for (int i = 0; i < kHalves; ++i) dq_acc[i] = zero16();
+    f32x16 dq_acc = zero16();
     if (has_block) {
       const char* dst = ds + (qb >> 1) * S::kKeys * 128;
       const int q_lo = qb & 1 ? toff[1][0] : toff[0][0], q_hi = qb & 1 ? toff[1][1] : toff[0][1];
-      const int d_lo = db0 ? toff[1][0] : toff[0][0], d_hi = db0 ? toff[1][1] : toff[0][1];
+      const int d_lo = db ? toff[1][0] : toff[0][0], d_hi = db ? toff[1][1] : toff[0][1];
       for (int kb = 0; kb < n_blocks; ++kb)
 #pragma unroll
         for (int kk = 2 * kb; kk < 2 * kb + 2; ++kk) {
           const bf16x8 dsq = read_transposed(dst + kk * 16 * 128, q_lo, q_hi);
-          dq_acc[0] = mfma(read_transposed(kt + kk * 16 * 128, d_lo, d_hi), dsq, dq_acc[0]);
-          if (kHalves == 2)
-            dq_acc[kHalves - 1] = mfma(read_transposed(kt + kk * 16 * 128, toff[1][0], toff[1][1]), dsq, dq_acc[kHalves - 1]);
+          dq_acc = mfma(read_transposed(kt + kk * 16 * 128, d_lo, d_hi), dsq, dq_acc);
         }
     }
-    __syncthreads();  // dS^T has been read: its place (or the Q tiles) takes the dQ rows
     if (has_block) {
       const int q = (p * S::kBlocks + qb) * 32 + m;
       const bool live_q = code[q] != kPadCode;  // pad positions: zeros, whatever their rows held
-#pragma unroll
-      for (int i = 0; i < kHalves; ++i) stage_rows(live_q ? dq_acc[i] : zero16(), a.scale, qt, qb * 32 + m, db0 + i, hl);
+      stage_rows(live_q ? dq_acc : zero16(), a.scale, qt, qb * 32 + m, db, hl);
     }
     __syncthreads();
     for (int g = wave; g < S::kQueries / 8; g += NW) {
@@ -584,33 +713,209 @@ __global__ __launch_bounds__(64 * NW, NW == 2 ? 3 : 2) void bwd_dense_small_kern
   flush(dV);
 }
 
+// The same for up to 192 positions: sixteen keys a wavefront in place of 32, in 16 x 16 x 32 instructions, all queries in one pass, and no
+// barrier after dQ's.  Such a launch is one or two workgroups on a compute unit that load, compute and store at the same time, so it is
+// as long as a wavefront's own chain, which is half as long here.  Every wavefront reads all of Q and dO, plain and transposed, so LDS
+// reads double, and from 193 positions on those bound it (14 wavefronts: 1 x 224, 12 heads 15.4 -> 15.7, 32 x 224 35.5 -> 36.8).
+// us, 32 keys a wavefront and sixteen: 64 x 64 positions, 16 heads 13.3 -> 11.7, 48 x 64 9.4 -> 7.4, 17 x 64 7.4 -> 5.6, one sequence of 64,
+// 4 heads 6.1 -> 4.9; 128 positions, 1 x, 4 heads 7.8 -> 7.4, 16 x, 16 heads 8.9 -> 8.4, 32 x, 12 heads 12.2 -> 11.8, 33 x, 16 heads 19.4 -> 18.2,
+// 64 x 27.2 -> 26.6, 24 x, 12 heads 11.1 -> 11.0; 40 x 96, 16 heads 16.7 -> 14.4; 8 x 160, 12 heads 12.6 -> 10.1, 40 x 160, 16 heads 41.9 -> 35.9; 8 x 192, 12 heads 14.0 -> 12.1, 40 x 192, 16 heads
+// 47.8 -> 43.7.
 template <int NW, bool kThrough>
-hipError_t launch_bwd_small(const DenseArgs& a, hipStream_t stream) {
-  using S = SmallShape<NW>;
-  const hipError_t e = allow_lds<&bwd_dense_small_kernel<NW, kThrough>>(S::kLds);
+__global__ __launch_bounds__(64 * NW, 4) void bwd_dense_short_kernel(
+    const void* q, const void* k, const void* v, const void* o, const void* dout, int sizes, DenseArgs a) {
+  using S = ShortShape<NW>;
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  __shared__ __attribute__((aligned(16))) unsigned code[S::kRows];
+  __shared__ __attribute__((aligned(16))) float nlse[S::kRows], ndelta[S::kRows];
+  char *const kt = lds, *const qt = lds + S::kBytes, *const gt = qt + S::kBytes, *const vt = gt + S::kBytes, *const ds = qt;
+  const int N = sizes & 0xffff, tid = threadIdx.x, lane = tid & 63, bh_i = blockIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, quarter = lane >> 4, q8 = 8 * quarter;
+  const size_t bh = (size_t)bh_i * N;
+  const unsigned short* Q = static_cast<const unsigned short*>(q) + bh * kD;
+  const unsigned short* K = static_cast<const unsigned short*>(k) + bh * kD;
+  const unsigned short* V = static_cast<const unsigned short*>(v) + bh * kD;
+  const unsigned short* O = static_cast<const unsigned short*>(o) + bh * kD;
+  const unsigned short* dO = static_cast<const unsigned short*>(dout) + bh * kD;
+  unsigned short* dQ = static_cast<unsigned short*>(a.dq) + bh * kD;
+  unsigned short* dK = static_cast<unsigned short*>(a.dk) + bh * kD;
+  unsigned short* dV = static_cast<unsigned short*>(a.dv) + bh * kD;
+
+  int h;
+  const int b = uniform_div_any(bh_i, sizes >> 16, h), view = head_view(a, h);
+  const int *row_ids = a.row_ids, *col_ids = a.col_ids;
+  const unsigned char* flags = a.flags;
+  stream_short<NW>(K, kt, N, wave, lane);
+  stream_short<NW>(Q, qt, N, wave, lane);
+  stream_short<NW>(dO, gt, N, wave, lane);
+  stream_short<NW>(V, vt, N, wave, lane);
+
+  // of this wavefront's rows: delta and -lse / scale of the queries, and the codes
+  const int own = 16 * wave;
+  {
+    bf16x8 g[2], y[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const unsigned at = (unsigned)min(own + 8 * i + (lane >> 3), N - 1) * kD + 8 * (lane & 7);
+      g[i] = *reinterpret_cast<const bf16x8*>(dO + at);
+      y[i] = *reinterpret_cast<const bf16x8*>(O + at);
+    }
+    const int pos = min(own + r, N - 1);
+    const float lse = a.lse[bh + pos];
+    const int* ids = pick(view == 0, row_ids, col_ids) + (size_t)b * N;
+    const int f = flags[(size_t)b * N + pos], id = ids[pos];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float d = row_dot8(g[i], y[i]);
+      if ((lane & 7) == 0) ndelta[own + 8 * i + (lane >> 3)] = -d;
+    }
+    if (lane < 16) {
+      nlse[own + r] = -lse / a.scale;
+      code[own + r] = token_code(own + r < N, f, id);
+    }
+  }
+  bf16x8 kf[2], vf[2];  // this lane's key and value as B operands
+  const float sc = uniform(a.scale * kLog2e);
+  const QuadLanes lanes(lane);
+  const unsigned q_at = lds_addr(qt), g_at = lds_addr(gt), k_at = lds_addr(kt), ds_at = lds_addr(ds);
+  // the wavefront owns a key, or its rows of dS^T are met together with those of one that does
+  const bool active = (own & ~31) < N;
+  f32x4 dk_acc[4], dv_acc[4];
+#pragma unroll
+  for (int d = 0; d < 4; ++d) dk_acc[d] = dv_acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  wait_vmcnt_le<0>(0);
+  __syncthreads();
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const int row = own + r, at = row * 128 + (((4 * ks + quarter) ^ swz_quad(row)) << 4);
+    kf[ks] = read_plain(kt, at);
+    vf[ks] = read_plain(vt, at);
+  }
+  unsigned dw[S::kBlocks][4];   // dS of the block's queries 8 q .. 8 q + 7
+  const unsigned my_code = code[own + r], my_limit = owner_limit(my_code);
+  if (active)
+#pragma unroll
+    for (int ib = 0; ib < S::kBlocks; ++ib) {
+      const int q0 = ib * 32;
+      if (q0 >= N) continue;
+      unsigned pw[4];
+#pragma unroll
+      for (int hb = 0; hb < 2; ++hb) {
+        f32x4 s = *reinterpret_cast<const f32x4*>(nlse + q0 + q8 + 4 * hb), dp = *reinterpret_cast<const f32x4*>(ndelta + q0 + q8 + 4 * hb);
+        const uint4 c4 = *reinterpret_cast<const uint4*>(code + q0 + q8 + 4 * hb);
+        const unsigned codes[4] = {c4.x, c4.y, c4.z, c4.w};
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+          s = mfma16(read_quad(lanes, q_at + ib * kBlockBytes, hb, ks), kf[ks], s);     // S  = Q K^T
+          dp = mfma16(read_quad(lanes, g_at + ib * kBlockBytes, hb, ks), vf[ks], dp);   // dP = dO V^T
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool in = allowed(codes[e], my_code, my_limit);
+          s[e] = in ? __builtin_amdgcn_exp2f(s[e] * sc) : 0.f;   // P
+          dp[e] = in ? s[e] * dp[e] : 0.f;                       // dS
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          pw[2 * hb + i] = pack2(s[2 * i], s[2 * i + 1]);
+          dw[ib][2 * hb + i] = pack2(dp[2 * i], dp[2 * i + 1]);
+        }
+      }
+      const bf16x8 p8 = as_bf16x8(make_uint4(pw[0], pw[1], pw[2], pw[3]));
+      const bf16x8 ds8 = as_bf16x8(make_uint4(dw[ib][0], dw[ib][1], dw[ib][2], dw[ib][3]));
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        dv_acc[d] = mfma16(read_quad_transposed(lanes, g_at + ib * kBlockBytes, d), p8, dv_acc[d]);   // dV^T += dO^T P
+        dk_acc[d] = mfma16(read_quad_transposed(lanes, q_at + ib * kBlockBytes, d), ds8, dk_acc[d]);  // dK^T += Q^T dS
+      }
+    }
+  __syncthreads();  // everyone is done with the Q and dO tiles, and with its own rows of V
+  // dS^T: row = key, 64 queries per 128-byte row and tile, swizzled like the other tiles
+  if (active)
+#pragma unroll
+    for (int ib = 0; ib < S::kBlocks; ++ib)
+      if (ib * 32 < N) {
+        const int row = own + r, chunk = 4 * (ib & 1) + quarter;
+        *reinterpret_cast<uint4*>(ds + (ib >> 1) * S::kBytes + row * 128 + ((chunk ^ swz_quad(row)) << 4)) =
+            make_uint4(dw[ib][0], dw[ib][1], dw[ib][2], dw[ib][3]);
+      }
+  __syncthreads();
+  // dQ of this wavefront's queries
+  f32x4 dq_acc[4];
+#pragma unroll
+  for (int d = 0; d < 4; ++d) dq_acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (own < N)
+    for (int kb = 0; kb * 32 < N; ++kb) {
+      const bf16x8 dsq = read_quad_transposed(lanes, ds_at + (wave >> 2) * S::kBytes + kb * kBlockBytes, wave & 3);
+#pragma unroll
+      for (int d = 0; d < 4; ++d) dq_acc[d] = mfma16(read_quad_transposed(lanes, k_at + kb * kBlockBytes, d), dsq, dq_acc[d]);
+    }
+  __syncthreads();  // dS^T and the K tiles have been read
+  // Result rows of this wavefront, staged one tensor after the other over its own rows of the K tiles.
+  if (own >= N) return;
+  char* const st = kt + own * 128;
+  const bool live = code[own + r] != kPadCode;
+  store_short<kThrough>(dq_acc, a.scale, live, st, dQ, own, N, lane);
+  store_short<kThrough>(dk_acc, a.scale, live, st, dK, own, N, lane);
+  store_short<kThrough>(dv_acc, 1.f, live, st, dV, own, N, lane);
+}
+
+template <int NW, bool kThrough>
+hipError_t launch_fwd_short(const DenseArgs& a, hipStream_t stream) {
+  hipLaunchKernelGGL((fwd_dense_short_kernel<NW, kThrough>), dim3(a.B * a.H), dim3(64 * NW), 0, stream, a.q, a.k, a.v, a.row_ids, a.col_ids,
+                     a.flags, pack_sizes(a.N, a.H), a);
+  return hipGetLastError();
+}
+template <int NW, bool kThrough>
+hipError_t launch_bwd_short(const DenseArgs& a, hipStream_t stream) {
+  const hipError_t e = allow_lds<&bwd_dense_short_kernel<NW, kThrough>>(ShortShape<NW>::kBwdLds);
   if (e != hipSuccess) return e;
   ProfileScope prof(7, stream, 6);
-  hipLaunchKernelGGL((bwd_dense_small_kernel<NW, kThrough>), dim3(a.B * a.H), dim3(64 * NW), S::kLds, stream, a.q, a.k, a.v, a.o, a.dout,
-                     pack_sizes(a.N, a.H), a);
+  hipLaunchKernelGGL((bwd_dense_short_kernel<NW, kThrough>), dim3(a.B * a.H), dim3(64 * NW), ShortShape<NW>::kBwdLds, stream, a.q, a.k, a.v, a.o,
+                     a.dout, pack_sizes(a.N, a.H), a);
   return hipGetLastError();
+}
+template <bool kThrough>
+hipError_t launch_bwd_small(const DenseArgs& a, hipStream_t stream) {
+  const hipError_t e = allow_lds<&bwd_dense_small_kernel<kThrough>>(SmallShape::kLds);
+  if (e != hipSuccess) return e;
+  ProfileScope prof(7, stream, 6);
+  hipLaunchKernelGGL((bwd_dense_small_kernel<kThrough>), dim3(a.B * a.H), dim3(64 * SmallShape::kWaves), SmallShape::kLds, stream, a.q, a.k,
+                     a.v, a.o, a.dout, pack_sizes(a.N, a.H), a);
+  return hipGetLastError();
+}
+template <bool kThrough>
+hipError_t launch_bwd_one(const DenseArgs& a, hipStream_t stream) {
+  return a.N <= 64    ? launch_bwd_short<4, kThrough>(a, stream)
+         : a.N <= 128 ? launch_bwd_short<8, kThrough>(a, stream)
+         : a.N <= 160 ? launch_bwd_short<10, kThrough>(a, stream)
+         : a.N <= 192 ? launch_bwd_short<12, kThrough>(a, stream)
+                      : launch_bwd_small<kThrough>(a, stream);
 }
 
 }  // namespace
 
 hipError_t launch_fwd_dense(const DenseArgs& a, hipStream_t stream) {
   ProfileScope prof(5, stream);
-  const auto kernel = result_through(a.B, a.H, a.N, 2) ? fwd_dense_kernel<true> : fwd_dense_kernel<false>;
+  // The short form: up to 128 positions, and up to 192 where the general one has more workgroups than compute units and it has not (us,
+  // 16 heads: 16 x 160 8.65 -> 6.65, 16 x 192 8.7 -> 7.35; 8 x 192, 12 heads 6.6 -> 7.3, 24 x 192 10.9 -> 10.75, 40 x 192, 16 heads 17.2 -> 17.2).
+  const bool through = result_through(a.B, a.H, a.N, 2);
+  if (a.N <= 64) return through ? launch_fwd_short<4, true>(a, stream) : launch_fwd_short<4, false>(a, stream);
+  if (a.N <= 128) return through ? launch_fwd_short<8, true>(a, stream) : launch_fwd_short<8, false>(a, stream);
+  if (a.N <= 192 && a.B * a.H > 128 && a.B * a.H <= 256)
+    return through ? launch_fwd_short<12, true>(a, stream) : launch_fwd_short<12, false>(a, stream);
+  const auto kernel = through ? fwd_dense_kernel<true> : fwd_dense_kernel<false>;
   hipLaunchKernelGGL(kernel, dim3(dense_grid(a)), dim3(kThreads), 0, stream, a.q, a.k, a.v, a.row_ids, a.col_ids, a.flags,
                      pack_sizes(a.N, a.H), a.B * a.H, a);
   return hipGetLastError();
 }
 
 hipError_t launch_bwd_dense(const DenseArgs& a, hipStream_t stream) {
-  // one workgroup per (sequence, head) as long as its dS^T and K fit the LDS
+  // one workgroup per (sequence, head) as long as its dS^T and K fit the LDS; the length says which kernel: see there
   const bool through = result_through(a.B, a.H, a.N, 3 * 2);
-  if (a.N <= 64) return through ? launch_bwd_small<2, true>(a, stream) : launch_bwd_small<2, false>(a, stream);
-  if (a.N <= 128) return through ? launch_bwd_small<4, true>(a, stream) : launch_bwd_small<4, false>(a, stream);
-  if (a.N <= 256) return through ? launch_bwd_small<8, true>(a, stream) : launch_bwd_small<8, false>(a, stream);
+  if (a.N <= SmallShape::kKeys) return through ? launch_bwd_one<true>(a, stream) : launch_bwd_one<false>(a, stream);
   {
     ProfileScope prof(6, stream);
     hipLaunchKernelGGL(bwd_dq_dense_kernel, dim3(dense_grid(a)), dim3(kThreads), 0, stream, a);

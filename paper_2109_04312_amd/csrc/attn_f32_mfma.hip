@@ -45,8 +45,6 @@ namespace {
 constexpr int kRows = 32;                  // owned rows of a workgroup, rows of a streamed tile
 constexpr int kWaves = kThreads / 64;
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));  // (arrays of HIP's float4 class end up in scratch memory)
-
 __device__ __forceinline__ f32x16 mfma1(float a, float b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }

@@ -25,6 +25,9 @@ namespace mate {
 constexpr int kTileBytes = 64 * 128;  // one streamed tile in LDS
 
 __device__ inline int swz(int r) { return (((r >> 1) & 1) << 2) | ((r >> 2) & 3); }
+// The same for tiles that are read as QuadLanes says (below): rows 8 i + 4 h + j (i, j = 0 .. 3) at one chunk index, and
+// rows 8 i + 4 h + j of two i at two adjacent ones.  Bit 2 of a row (h) is not part of it.
+__device__ inline int swz_quad(int r) { return (((r >> 1) & 1) << 2) | (((r >> 3) & 1) << 1) | ((r >> 4) & 1); }
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
@@ -174,6 +177,29 @@ struct TransposedAddr {
     hi[1] = hi[0] ^ 64;
   }
 };
+
+// Operands of v_mfma_f32_16x16x32_bf16 from a tile, lane 16 q + r.  The 32 rows of a block are two blocks of 16, row
+// 8 i + 4 h + j being row 4 i + j of block h, so that in C tiles a lane holds rows 8 q .. 8 q + 7 of the 32: what the
+// second contraction's operand holds, and two transposing reads bring of the other one.
+struct QuadLanes {
+  unsigned plain;  // row r of block 0, dims 8 q .. + 7 (the other 32 dims: ^ 64; block 1: + 512; the next 32 rows: + 4096)
+  unsigned trans;  // rows 8 q .. + 3, columns 0 .. 15 (columns 16 d ..: ^ 32 d; rows 8 q + 4 .. + 7: + 512)
+  __device__ explicit QuadLanes(int lane) {
+    const int r = lane & 15, q = lane >> 4, row = 8 * (r >> 2) + (r & 3), row_t = 8 * q + (r >> 2);
+    plain = row * 128 + ((q ^ swz_quad(row)) << 4);
+    trans = row_t * 128 + ((((r & 3) >> 1) ^ swz_quad(row_t)) << 4) + ((r & 1) << 3);
+  }
+};
+constexpr int kBlockBytes = 32 * 128, kHalfBlock = 4 * 128;  // in LDS: 32 rows, and from block 0 to block 1 of them
+// Row r of block h of the 32 rows at LDS address `at`, dims 32 k + 8 q .. + 7.
+__device__ __forceinline__ bf16x8 read_quad(const QuadLanes& l, unsigned at, int h, int k) {
+  return read_plain(((at + l.plain) ^ (64 * k)) + h * kHalfBlock);
+}
+// Columns 16 d .. + 15 (operand rows) and rows 8 q .. + 7 (k) of the 32 rows at LDS address `at`.
+__device__ __forceinline__ bf16x8 read_quad_transposed(const QuadLanes& l, unsigned at, int d) {
+  const unsigned a = (at + l.trans) ^ (32 * d);
+  return read_transposed(a, a + kHalfBlock);
+}
 
 // Tile row (0..31 inside a 32-row block) held in C register c of a lane in half hl when the A
 // operand rows are fed unpermuted.

@@ -4,6 +4,10 @@
 //   A (32 x 16): lane holds row m,    k = 8*hl .. 8*hl+7   (8 bf16 = 16 bytes)
 //   B (16 x 32): lane holds column m, k = 8*hl .. 8*hl+7
 //   C (32 x 32): lane holds column m, register c = 4*g + r  <->  row 8*g + 4*hl + r
+// and, in the dense backward of up to 256 positions, v_mfma_f32_16x16x32_bf16, lane l = 16*q + r (r = l % 16):
+//   A (16 x 32): lane holds row r,    k = 8*q .. 8*q+7
+//   B (32 x 16): lane holds column r, k = 8*q .. 8*q+7
+//   C (16 x 16): lane holds column r, register e  <->  row 4*q + e
 // Every kernel here computes "transposed" score tiles (rows = keys or queries of the streamed
 // tile, columns = the rows the wavefront owns), so each lane owns one of the wavefront's rows
 // and per-row softmax statistics are per-lane scalars.
@@ -16,7 +20,7 @@ namespace mate {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kD = 64;             // head size
 constexpr float kLog2e = 1.4426950408889634f;
@@ -24,6 +28,10 @@ constexpr float kLn2 = 0.6931471805599453f;
 
 __device__ inline f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
 __device__ inline f32x16 zero16() {
@@ -76,6 +84,18 @@ __device__ inline float half_sum(float x) {
   const unsigned u = __float_as_uint(x);
   const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// The same across the four lane quarters of a 16 x 16 tile's column (lanes l, l ^ 16, l ^ 32, l ^ 48).
+__device__ inline float quad_max(float x) {
+  const unsigned u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return half_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ inline float quad_sum(float x) {
+  const unsigned u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return half_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 
 // Sum of the eight bf16 values of an operand, added to acc (v_dot2 against ones): the row sum

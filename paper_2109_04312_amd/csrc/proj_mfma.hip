@@ -35,11 +35,6 @@
 namespace mate {
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
 // A pointer the compiler can keep in scalar registers (the value is the same in every lane).
 __device__ inline const char* uniform_ptr(const void* p) {
   const unsigned long long v = reinterpret_cast<unsigned long long>(p);

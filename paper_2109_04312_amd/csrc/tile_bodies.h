@@ -23,19 +23,6 @@
 
 namespace mate {
 
-// Per-lane LDS offsets of the operand reads: plain 16-byte reads for the four 16-wide k slices,
-// transposing reads for the two 32-row blocks of the other operand (see d2l.h).
-__device__ __forceinline__ void operand_offsets(int lane, int (&poff)[4], int (&toff)[2][2]) {
-  const int m = lane & 31, hl = lane >> 5;
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) poff[ks] = plain_off(m, hl, ks);
-#pragma unroll
-  for (int db = 0; db < 2; ++db) {
-    toff[db][0] = tr_off(lane, db, 0);
-    toff[db][1] = tr_off(lane, db, 1);
-  }
-}
-
 // Segment path: the owned row meets the streamed sorted slots [lo, hi); the tile's first row is
 // slot `base`.  (For the question-token part of a stream lo = 0, hi = G.)
 //

@@ -91,6 +91,15 @@ def test_dense_edges_of_the_one_launch_backward(N):
     check_dense(small_workload(N, "bf16", N=N, max_rows=9, max_cols=5, max_global=9, scatter=N % 2 == 1))
 
 
+@pytest.mark.parametrize("B,N,H", [(2, 15, 4), (2, 16, 4), (2, 17, 4), (2, 47, 4), (2, 49, 4), (3, 80, 6), (2, 112, 4), (2, 113, 4),
+                                   (32, 129, 4), (33, 129, 4), (33, 160, 4), (33, 161, 4), (33, 176, 4), (33, 192, 4), (33, 193, 4),
+                                   (2, 191, 4), (2, 192, 4), (2, 193, 4), (2, 208, 4)])
+def test_dense_short_sequences(B, N, H):
+    """Sixteen rows a wavefront: edges of its 16- and 32-row blocks and of the workgroup sizes, and both forwards where the
+    number of (sequence, head) pairs decides (more than 128)."""
+    check_dense(small_workload(B + N, "bf16", B=B, N=N, H=H, max_rows=min(9, N // 4), max_cols=5, max_global=9, max_cell=4, scatter=N % 2 == 1))
+
+
 @pytest.mark.parametrize("N", [40, 128, 256, 300])
 @pytest.mark.parametrize("kernel", ["MATE_KERNEL_BWD_DQ_DENSE", "MATE_KERNEL_BWD_DKV_DENSE"])
 def test_dense_backward_answers_to_both_profile_names(N, kernel):
