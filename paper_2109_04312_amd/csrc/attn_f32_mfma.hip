@@ -896,13 +896,13 @@ __global__ __launch_bounds__(kThreads) void delta_f32_kernel(AttnArgs a) {
     if (piece == 0 && first + 16 * i < rows) reinterpret_cast<unsigned*>(a.delta)[first + 16 * i] = bits;
   }
 }
-template <bool kMany>
+template <bool kOwnersFirst, bool kMany>
 __global__ __launch_bounds__(kThreads, 2) void bwd_f32_kernel(MATE_UNIT_LISTS, AttnArgs a, unsigned first) {
   __shared__ __attribute__((aligned(1024))) BwdLds lds;
   const unsigned block = first + blockIdx.x;
   Quarter q;
   // (32 workgroups are the quarters of eight units, one on each XCD)
-  if (!take_quarter<false, kMany>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, ((block >> 6) << 5) | (block & 31), q)) return;
+  if (!take_quarter<kOwnersFirst, kMany>({hdr, gunit, unit_row, unit_col, B, H, N, n_col}, a, ((block >> 6) << 5) | (block & 31), q)) return;
   if (block & 32) dq_quarter(a, q, lds);
   else dkv_quarter(a, q, lds);
 }
@@ -920,6 +920,16 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_f32_kernel(MATE_UNIT_LISTS, A
 static bool owners_first(int B, int H, int N) {
   const int T = owner_slots(N);
   return 4l * B * H * T > (T == 2 || T == 3 ? 1024 : 512);
+}
+
+// The same in the backward, where an owner of dK and dV takes 22 us of 4 x 512's launch and owners began at 13: sequences of four tiles and
+// more whose quarters, two for each, are more than the 512 that fit at once.  us, columns first and owners first: 12 heads, 4 x 512 42.3 -> 38.7, 3 x
+// 512 40.3 -> 33.7, 2 x 478 31.5 -> 25.4, 2 x 847 65 -> 54.6, one of 847 48.6 -> 40.8, of 2048 86.9 -> 59.5, of 4096 190 -> 139, 16 x 512 137.2 -> 136.9, 16 x
+// 1024 291.6 -> 291.7; 8 heads, 3 x 858 68.2 -> 56.9, 8 x 512 49.2 -> 48.7, 10 x 550 86.2 -> 86.6.  Below: 2 x 400, 8 heads 21.8 -> 23.3, one of 701
+// 33.8 -> 34.1; three tiles: 2 x 377, 12 heads 22.5 -> 23.9, 10 x 301, 4 heads 22.8 -> 23.5.
+static bool bwd_owners_first(int B, int H, int N) {
+  const int T = owner_slots(N);
+  return T > 3 && 8l * B * H * T > 512;
 }
 
 hipError_t launch_fwd_f32(const AttnArgs& a, hipStream_t stream) {
@@ -940,7 +950,10 @@ hipError_t launch_bwd_f32(const AttnArgs& a, hipStream_t stream) {
   // 936 203.8 and 196.2, 15 x 653 131.5 and 128.6, 12 x 637 97.9 and 95.7, 18 x 846, 12 heads 142.7 and 137.9; full sequences: 29 x 315 225 and 223, 19 x
   // 652, 12 heads 241 and 237.5, 9 x 1325 421 and 424.  With fewer, full ones are up to 3 % longer (3 x 1073, 12 heads 87.7 and 90.9).  (The forward
   // gains by the round trip at any size, up to 5 %.)
-  const auto kernel = blocks > 20000 ? bwd_f32_kernel<true> : bwd_f32_kernel<false>;
+  // (There the order of owners and columns makes no difference.)
+  const auto kernel = blocks > 20000                      ? bwd_f32_kernel<false, true>
+                      : bwd_owners_first(a.B, a.H, a.N) ? bwd_f32_kernel<true, false>
+                                                        : bwd_f32_kernel<false, false>;
   for (unsigned first = 0; first < blocks && e == hipSuccess; first += most) {
     hipLaunchKernelGGL(kernel, dim3(min(most, blocks - first)), dim3(kThreads), 0, stream, MATE_UNIT_LISTS_VALUES(a), a, first);
     e = hipGetLastError();

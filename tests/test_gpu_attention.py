@@ -401,6 +401,14 @@ def test_f32_forward_in_either_order_of_units(B, N, H, n_global):
     print(hp.report(hp.compare(got, hp.run_oracle(w, False, [(b, h) for b in (0, B - 1) for h in range(H)]), w, w.name)), flush=True)
 
 
+@pytest.mark.parametrize("B,N,H,n_global", [(2, 384, 12, 40), (2, 385, 8, 40), (2, 385, 10, 40), (1, 700, 12, 130), (1, 1100, 12, 70)])
+def test_f32_backward_in_either_order_of_units(B, N, H, n_global):
+    """Owners of question tokens after the column heads' units and before them: three tiles of owners and four, 64 tiles
+    a launch and 80, and sequences with two tiles of question tokens."""
+    w = chunked_workload(N, B, N, H, n_global, "f32")
+    check_workload(w, True, pairs=[(0, 0), (0, H - 1), (B - 1, 1), (B - 1, H - 1)])
+
+
 @pytest.mark.parametrize("rise", [0, 12])
 @pytest.mark.parametrize("n_global,rows,cols,cell,N", [(1, 1, 1, 1, 2), (31, 3, 1, 32, 127), (32, 5, 2, 13, 170),
                                                        (33, 4, 3, 33, 440), (64, 2, 2, 65, 330), (65, 31, 2, 3, 260),
