@@ -124,14 +124,21 @@ __device__ __forceinline__ bf16x8 read_frag(const char* tiles, const FragOffsets
 }
 
 // One stage (64 of k): two slices of 32.
+// `issue` starts the loads of a later stage.  Where the stage's operands are plain it does so behind the operand
+// reads: its instructions (eight for 256 x 256, each with an address and m0) then cost the wavefront time in which its
+// reads travel, not time before them.  256 x 256 at 16384 x 3072 x 1024 2590 -> 2539 cycles a stage (2885 while the reads had bank
+// conflicts); whole products in 128 x 64 with two groups 5 to 9 % shorter, 128 x 128 with two groups 2 to 5, 192 x 128 1 to 2.
+// Transposing reads are twice as many instructions, and behind them the loads come too late: all gradients with `issue` behind
+// the reads take 3 to 6 % more in the mean.  And 128 x 128 with one group: 5 % less to 7 % more, none in the mean.
 // kHalves: `next_landed` is called where this wavefront's share of the next stage must have landed.
 // kAlternate: `reading` is called while the fragments travel and the other group multiplies.
-template <class S, bool kTA, bool kTB, bool kHalves, class PerSlice, class Next, class Reading>
+template <class S, bool kTA, bool kTB, bool kHalves, class Issue, class PerSlice, class Next, class Reading>
 __device__ __forceinline__ void contract_stage(const char* stage, const FragOffsets& fa, const FragOffsets& fb, int wa,
-                                               int wb, f32x4 (&acc)[S::kFA][S::kFB], PerSlice&& per_slice, Next&& next_landed,
-                                               Reading&& reading) {
+                                               int wb, f32x4 (&acc)[S::kFA][S::kFB], Issue&& issue, PerSlice&& per_slice,
+                                               Next&& next_landed, Reading&& reading) {
   const char* ta = stage + (kTA ? 0 : wa * S::kFA * 16 * 128);
   const char* tb = stage + S::kA * kTileBytes + (kTB ? 0 : wb * S::kFB * 16 * 128);
+  constexpr bool kIssueLate = !kTA && (S::kGroups > 1 || S::kFA * S::kFB != 16);
   bf16x8 a[2][S::kFA], b[2][S::kFB];
   auto read_slice = [&](int k) {
 #pragma unroll
@@ -139,12 +146,14 @@ __device__ __forceinline__ void contract_stage(const char* stage, const FragOffs
 #pragma unroll
     for (int j = 0; j < S::kFB; ++j) b[k][j] = read_frag<kTB>(tb, fb, (kTB ? wb * S::kFB : 0) + j, k);
   };
+  if (!kIssueLate) issue();
   if constexpr (kHalves) {
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       if (k) barrier_no_fence();
       __builtin_amdgcn_sched_barrier(0);
       read_slice(k);
+      if (kIssueLate && !k) issue();
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       if (k) next_landed();
       __builtin_amdgcn_sched_barrier(0);
@@ -164,6 +173,7 @@ __device__ __forceinline__ void contract_stage(const char* stage, const FragOffs
   read_slice(0);
   if constexpr (S::kAlternate) {
     read_slice(1);
+    if (kIssueLate) issue();
     reading();
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
@@ -173,7 +183,10 @@ __device__ __forceinline__ void contract_stage(const char* stage, const FragOffs
   }
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
-    if (k == 0 && !S::kAlternate) read_slice(1);  // the second slice travels while the first is contracted
+    if (k == 0 && !S::kAlternate) {
+      read_slice(1);  // the second slice travels while the first is contracted
+      if (kIssueLate) issue();
+    }
 #pragma unroll
     for (int i = 0; i < S::kFA; ++i)
 #pragma unroll
@@ -369,8 +382,8 @@ __device__ __forceinline__ void product_tile(const ProjStart& p, const ProjArgs&
       // stage ks has landed: everything but the younger stages' loads (fewer near the end)
       if (!kHalves) wait_vmcnt_le<S::kLoads * (S::kStages - 2)>(min(S::kStages - 2, nk - 1 - ks) * S::kLoads);
       barrier_no_fence();  // ... for every wavefront, and everyone is done with stage ks - 1
-      if (ks + S::kStages - 1 < nk) issue_stage(ks + S::kStages - 1);
       contract_stage<S, kTransposedW, false, kHalves>(ring + (ks % S::kStages) * S::kStageBytes, fa, fb, wa, wb, acc,
+                                                      [&]() { if (ks + S::kStages - 1 < nk) issue_stage(ks + S::kStages - 1); },
                                                       [](const bf16x8 (&)[S::kFB]) {}, []() { wait_vmcnt_le<0>(0); }, []() {});
     }
     if (apart && !second) barrier_no_fence();
@@ -777,8 +790,8 @@ __device__ __forceinline__ void wgrad_tile(WgradArgs a, char* lds, int block) {
     const uint2 next = live_at[min(ahead, i_end - 1)];
     land(i, it);
     barrier_no_fence();          // landed for everyone; and everyone is done with the block before it
-    if (ahead < i_end) issue_stage(ahead, next, (it + S::kStages - 1) % S::kStages);
     contract_stage<S, true, true, false>(ring + (it % S::kStages) * S::kStageBytes, fo, fo, wa, wb, acc,
+                                  [&]() { if (ahead < i_end) issue_stage(ahead, next, (it + S::kStages - 1) % S::kStages); },
                                   [&](const bf16x8 (&g)[S::kFB]) {
                                     if (do_bias) {
 #pragma unroll
