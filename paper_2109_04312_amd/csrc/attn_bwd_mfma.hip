@@ -52,7 +52,7 @@ __device__ __forceinline__ void merge_chunks(const float* const (&part)[kTensors
         }
       }
     }
-    stage_rows(acc, 1.f, stage + x * (BM * 128), (item >> 1) * 32 + (lane & 31), item & 1, lane >> 5);
+    stage_rows_quad(acc, 1.f, stage + x * (BM * 128), (item >> 1) * 32, item & 1, lane);
   }
   __syncthreads();
 #pragma unroll
@@ -90,7 +90,7 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w, ch
   // Second: the owned rows (registers) and the first K / V tiles (LDS), all in flight together.
   // K and V tiles stream through the LDS ring; K is read both plain (S^T = K Q^T) and
   // transposed (dQ^T += K^T dS^T), V plain (dP^T = V dO^T).
-  TileStream<kDqStage> stream(u, w.global_idx, lds, idx_ring, K, V, nullptr, 0, wave, lane);
+  TileStream<kDqStage, 1, true> stream(u, w.global_idx, lds, idx_ring, K, V, nullptr, 0, wave, lane);
   stream.begin();
   const OwnerSplit<1> split(u, wave);
   const OwnedRow me = owned_row(w, split.block, m);
@@ -100,44 +100,50 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w, ch
   if (!kOne && tid == 0 && u.part >= 0) a.arrived[(size_t)w.bh * owner_slots(N) + u.part] = 0;
   stream.prime();
 
-  // this lane's query row and dO row as B operands (column m, k = dims), and delta
+  // this lane's query rows and dO rows as B operands (columns r, k = dims), and delta
   OwnedTile q_rows, g_rows, o_rows;
   g_rows.load(dO, me.pos, lane);
   if (!kOne) o_rows.load(O, me.pos, lane);
   q_rows.load(Q, me.pos, lane);
   const float lse = a.lse[bh + me.pos];
   const float kept = kOne ? a.delta[bh + me.pos] : 0.f;
-  bf16x8 qf[4], gf[4];
+  bf16x8 qf[2][2], gf[2][2];
   g_rows.operands(gf, stream.room(), lane);
   const float delta = kOne ? -kept : row_delta(g_rows, o_rows, stream.room(), lane);
   q_rows.operands(qf, stream.room(), lane);
   // Everything loaded into registers so far is pinned as complete here, so that no load with a
   // register destination is pending inside the loop.
-  asm volatile("" ::"v"(qf[0]), "v"(qf[1]), "v"(qf[2]), "v"(qf[3]), "v"(gf[0]), "v"(gf[1]),
-               "v"(gf[2]), "v"(gf[3]), "v"(delta), "v"(lse));
+  asm volatile("" ::"v"(qf[0][0]), "v"(qf[0][1]), "v"(qf[1][0]), "v"(qf[1][1]), "v"(gf[0][0]), "v"(gf[0][1]),
+               "v"(gf[1][0]), "v"(gf[1][1]), "v"(delta), "v"(lse));
   // every chunk of a question-token owner computes the same delta; the first one stores it
   // (stored negated, with -lse / scale beside it: the dK/dV kernel starts its accumulators there)
   if (!kOne && hl == 0 && me.valid && u.t_begin == 0 && split.writes(wave)) {
     a.delta[bh + me.pos] = -delta;
     a.nlse[bh + me.pos] = -lse / a.scale;
   }
-  const float lse2 = lse * kLog2e;
+  const RowPair l = row_pair(__float_as_uint(lse * kLog2e)), nd = row_pair(__float_as_uint(-delta));
+  const float lse2[2] = {__uint_as_float(l.v[0]), __uint_as_float(l.v[1])};
+  f32x4 ndelta[2];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) ndelta[i >> 2][i & 3] = __uint_as_float(nd.v[i >> 2]);
+  const RowPair rng = row_pair(me.lo | me.hi << 16);
   const float sc = uniform(a.scale * kLog2e);
 
-  const OperandLanes lanes(lane);
+  const QuadLanes lanes(lane);
 
-  f32x16 dq_acc[2] = {zero16(), zero16()};
+  QuadAcc dq_q = {};
   for (int t = u.t_begin; t < u.t_end; ++t) {
     const unsigned tile = lds_addr(stream.acquire(t));
     const bool part0 = t < u.n_t0;
     const int base = part0 ? t * BN : u.s_lo + (t - u.n_t0) * BN;
     if (me.wave_active) {
-      WindowMask mask(base, hl, part0, u.G, me.lo, me.hi, split.first(base, part0 ? 0 : me.w_lo),
+      PairWindowMask mask(base, lane, part0, u.G, rng, split.first(base, part0 ? 0 : me.w_lo),
                       split.end(base, part0 ? u.G : me.w_hi), part0 ? 0 : me.a_lo, part0 ? u.G : me.a_hi);
-      dq_tile(tile, qf, gf, lanes, sc, lse2, delta, mask, dq_acc);
+      dq_tile(tile, qf, gf, lanes, sc, lse2, ndelta, mask, dq_q);
     }
   }
   __syncthreads();  // all wavefronts are done reading the stages; reuse them for the epilogue
+  f32x16 dq_acc[2] = {quad_item(dq_q, 0), quad_item(dq_q, 1)};
   int ln = lane;
   asm volatile("" : "+v"(ln));  // what follows is computed here, not kept in registers through the loop
   if (split.on) {  // add the other half of the streamed rows
@@ -168,7 +174,7 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w, ch
   const f32x16 (*accs[1])[2] = {&dq_acc};
   const float muls[1] = {a.scale};
   unsigned short* const outs[1] = {dQ};
-  store_owned_rows<1>(accs, muls, outs, lds, q_tok, wave, ln);
+  store_owned_rows<1, true, true>(accs, muls, outs, lds, q_tok, wave, ln);
 }
 
 // (four workgroups per CU: with three, the column-head units of the benchmark shape do not all
@@ -190,7 +196,7 @@ __global__ __launch_bounds__(kThreads, 4) void bwd_dq_mfma_kernel(MATE_UNIT_LIST
 __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, char* lds, int (*idx_ring)[BN], int* k_tok, int* group_done) {
   const int N = a.N, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction
-  const int m = lane & 31, hl = lane >> 5;
+  const int m = lane & 31;
   const UnitPlan& u = w.u;
 
   const size_t bh = (size_t)w.bh * N;
@@ -212,7 +218,7 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
   // First round trip: the owned rows' positions and the first tiles' token indices; second:
   // the owned K / V rows (registers) and the first tiles (LDS).
   const float* row_src = wave == 0 ? a.nlse + bh : wave == 1 ? a.delta + bh : nullptr;
-  TileStream<kDkvStage> stream(u, w.global_idx, lds, idx_ring, Q, dO, row_src,
+  TileStream<kDkvStage, 1, true> stream(u, w.global_idx, lds, idx_ring, Q, dO, row_src,
                                2 * kTileBytes + 256 * wave, wave, lane);
   stream.begin();
   // `me` is this lane's key; its window is the set of query slots that see it
@@ -225,16 +231,18 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
   OwnedTile k_rows, v_rows;
   k_rows.load(K, me.pos, lane);
   v_rows.load(V, me.pos, lane);
-  bf16x8 kf[4], vf[4];  // this lane's key and value rows as B operands
+  bf16x8 kf[2][2], vf[2][2];  // this lane's key and value rows as B operands
   k_rows.operands(kf, stream.room(), lane);
   v_rows.operands(vf, stream.room(), lane);
   const float sc = uniform(a.scale * kLog2e);
-  asm volatile("" ::"v"(kf[0]), "v"(kf[1]), "v"(kf[2]), "v"(kf[3]), "v"(vf[0]), "v"(vf[1]),
-               "v"(vf[2]), "v"(vf[3]));
+  asm volatile("" ::"v"(kf[0][0]), "v"(kf[0][1]), "v"(kf[1][0]), "v"(kf[1][1]), "v"(vf[0][0]), "v"(vf[0][1]),
+               "v"(vf[1][0]), "v"(vf[1][1]));
 
-  const OperandLanes lanes(lane);
+  const QuadLanes lanes(lane);
+  const int quarter = lane >> 4;
+  const RowPair rng = row_pair(me.lo | me.hi << 16);
 
-  f32x16 dk_acc[2] = {zero16(), zero16()}, dv_acc[2] = {zero16(), zero16()};
+  QuadAcc dk_q = {}, dv_q = {};
   for (int t = u.t_begin; t < u.t_end; ++t) {
     const char* Qst = stream.acquire(t);
     const float* lse_row = reinterpret_cast<const float*>(Qst + 2 * kTileBytes);
@@ -242,12 +250,13 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
     const bool part0 = t < u.n_t0;
     const int base = part0 ? t * BN : u.s_lo + (t - u.n_t0) * BN;
     if (me.wave_active) {
-      WindowMask mask(base, hl, part0, u.G, me.lo, me.hi, split.first(base, part0 ? 0 : me.w_lo),
+      PairWindowMask mask(base, lane, part0, u.G, rng, split.first(base, part0 ? 0 : me.w_lo),
                       split.end(base, part0 ? u.G : me.w_hi), part0 ? 0 : me.a_lo, part0 ? u.G : me.a_hi);
-      dkv_tile(lds_addr(Qst), lse_row, delta_row, kf, vf, lanes, sc, hl, mask, dk_acc, dv_acc);
+      dkv_tile(lds_addr(Qst), lse_row, delta_row, kf, vf, lanes, sc, quarter, mask, dk_q, dv_q);
     }
   }
   __syncthreads();  // all wavefronts are done reading the stages; reuse them for the epilogue
+  f32x16 dk_acc[2] = {quad_item(dk_q, 0), quad_item(dk_q, 1)}, dv_acc[2] = {quad_item(dv_q, 0), quad_item(dv_q, 1)};
   if (split.on) {  // add the other half of the streamed rows
     char* const mine = lds + (wave & 1) * (kItemFloats * 4 * 4);
     if (wave >= 2) {
@@ -283,7 +292,7 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
   const f32x16 (*accs[2])[2] = {&dk_acc, &dv_acc};
   const float muls[2] = {a.scale, 1.f};
   unsigned short* const outs[2] = {dK, dV};
-  store_owned_rows<2>(accs, muls, outs, lds, k_tok, wave, lane);
+  store_owned_rows<2, true, true>(accs, muls, outs, lds, k_tok, wave, lane);
 }
 
 // dQ rows of the question tokens of one (sequence, head) from the dq kernel's chunk partials.

@@ -139,7 +139,6 @@ struct DenseStream {
 // The dense-mask rule as a Mask of tile_bodies.h: the pair is kept iff the two tokens' codes say
 // so.  `codes` points at the tile's 64 codes in LDS, offset by this lane half's 4 hl.
 struct CodeMask {
-  static constexpr bool kPairs = false;
   const unsigned* codes;
   unsigned my_code, limit;
   unsigned k[16];
@@ -157,6 +156,42 @@ struct CodeMask {
   __device__ __forceinline__ bool in(int c) const { return allowed(k[c], my_code, limit); }
   __device__ __forceinline__ float keep(int c, float x, float other) const { return in(c) ? x : other; }
 };
+
+// The same in the backward: lane 16 q + r owns rows r and 16 + r, `codes` is offset by 8 q.
+struct PairCodeMask {
+  const unsigned* codes;
+  const RowPair &mine, &limit;
+  unsigned k[8];
+  __device__ __forceinline__ PairCodeMask(const unsigned* tile_codes, int q, const RowPair& mine_, const RowPair& limit_)
+      : codes(tile_codes + 8 * q), mine(mine_), limit(limit_) {}
+  __device__ __forceinline__ bool full(int) const { return false; }
+  __device__ __forceinline__ bool skip(int) const { return false; }
+  __device__ __forceinline__ void load_pairs(int blk) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint4 kc = *reinterpret_cast<const uint4*>(codes + blk * 32 + 4 * h);
+      k[4 * h] = kc.x; k[4 * h + 1] = kc.y; k[4 * h + 2] = kc.z; k[4 * h + 3] = kc.w;
+    }
+  }
+  __device__ __forceinline__ unsigned pair_mask(int cb, int i) const {
+    return (allowed(k[2 * i], mine.v[cb], limit.v[cb]) ? 0xffffu : 0u) | (allowed(k[2 * i + 1], mine.v[cb], limit.v[cb]) ? 0xffff0000u : 0u);
+  }
+};
+// Rows r and 16 + r of a wavefront's 32 owned positions from `first` on, as operands of 16 x 16 tiles.
+__device__ __forceinline__ void dense_operands(const unsigned short* X, int first, int N, int lane, bf16x8 (&f)[2][2]) {
+#pragma unroll
+  for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+      f[ks][cb] = *reinterpret_cast<const bf16x8*>(X + (unsigned)min(first + 16 * cb + (lane & 15), N - 1) * kD + 32 * ks + 8 * (lane >> 4));
+}
+// Results of pad positions, and of rows past the end, are zeros.
+__device__ __forceinline__ void live_rows(QuadAcc& acc, float mul, const RowPair& live) {
+#pragma unroll
+  for (int d = 0; d < 4; ++d)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[d][i >> 2][i & 3] = live.v[i >> 2] ? acc[d][i >> 2][i & 3] * mul : 0.f;
+}
 
 // ======================================================================================
 // forward
@@ -357,7 +392,7 @@ __global__ __launch_bounds__(64 * NW, 4) void fwd_dense_short_kernel(const void*
 // ======================================================================================
 // dQ (and -delta, -lse / scale for the dK/dV kernel)
 // ======================================================================================
-__global__ __launch_bounds__(kThreads, 4) void bwd_dq_dense_kernel(DenseArgs a) {
+__global__ __launch_bounds__(kThreads, 3) void bwd_dq_dense_kernel(DenseArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds[2 * kStage];
   __shared__ __attribute__((aligned(16))) unsigned code[kDenseMaxN];
   __shared__ int q_tok[BM];
@@ -365,7 +400,7 @@ __global__ __launch_bounds__(kThreads, 4) void bwd_dq_dense_kernel(DenseArgs a) 
   if (!dense_unit(a, a.N, a.H, a.B * a.H, u)) return;
   const int N = a.N, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int m = lane & 31, hl = lane >> 5;
+  const int m = lane & 31;
   const size_t bh = (size_t)u.bh * N;
   const unsigned short* Q = static_cast<const unsigned short*>(a.q) + bh * kD;
   const unsigned short* K = static_cast<const unsigned short*>(a.k) + bh * kD;
@@ -374,7 +409,7 @@ __global__ __launch_bounds__(kThreads, 4) void bwd_dq_dense_kernel(DenseArgs a) 
   const unsigned short* dO = static_cast<const unsigned short*>(a.dout) + bh * kD;
   unsigned short* dQ = static_cast<unsigned short*>(a.dq) + bh * kD;
 
-  DenseStream stream{K, V, nullptr, nullptr, lds, kStage, N, wave, lane, make_load_lane(wave, lane)};
+  DenseStream stream{K, V, nullptr, nullptr, lds, kStage, N, wave, lane, make_load_lane<true>(wave, lane)};
   const int n_tiles = (N + BN - 1) / BN;
   DenseCodes codes;
   codes.load(a.row_ids, a.col_ids, a.flags, u, N);
@@ -383,47 +418,47 @@ __global__ __launch_bounds__(kThreads, 4) void bwd_dq_dense_kernel(DenseArgs a) 
   if (tid < BM) q_tok[tid] = u.tile * BM + tid < N ? u.tile * BM + tid : -1;
   __syncthreads();
   const DenseRow me = dense_row(N, u, code, wave, m);
-  bf16x8 qf[4], gf[4], of[4];
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    const size_t off = (size_t)me.pos * kD + ks * 16 + hl * 8;
-    qf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(Q + off));
-    gf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(dO + off));
-    of[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(O + off));
-  }
+  const int first = u.tile * BM + wave * 32;
+  bf16x8 qf[2][2], gf[2][2], of[2][2];
+  dense_operands(Q, first, N, lane, qf);
+  dense_operands(dO, first, N, lane, gf);
+  dense_operands(O, first, N, lane, of);
   const float lse = a.lse[bh + me.pos];
-  asm volatile("" ::"v"(qf[0]), "v"(qf[1]), "v"(qf[2]), "v"(qf[3]), "v"(gf[0]), "v"(gf[1]),
-               "v"(gf[2]), "v"(gf[3]), "v"(of[0]), "v"(of[1]), "v"(of[2]), "v"(of[3]), "v"(lse));
-  float delta = 0.f;
+  asm volatile("" ::"v"(qf[0][0]), "v"(qf[0][1]), "v"(qf[1][0]), "v"(qf[1][1]), "v"(gf[0][0]), "v"(gf[0][1]), "v"(gf[1][0]),
+               "v"(gf[1][1]), "v"(of[0][0]), "v"(of[0][1]), "v"(of[1][0]), "v"(of[1][1]), "v"(lse));
+  f32x4 ndelta[2];
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks)
+  for (int cb = 0; cb < 2; ++cb) {
+    float d = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) delta = fmaf((float)gf[ks][e], (float)of[ks][e], delta);
-  delta = half_sum(delta);
-  if (hl == 0 && me.in_range) {
-    a.delta[bh + me.pos] = -delta;
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) d = fmaf((float)gf[ks][cb][e], (float)of[ks][cb][e], d);
+    d = -quad_sum(d);
+    ndelta[cb] = f32x4{d, d, d, d};
+  }
+  if (lane < 32 && me.in_range) {   // (lane m < 32: row m)
+    a.delta[bh + me.pos] = pick(lane < 16, ndelta[0][0], ndelta[1][0]);
     a.nlse[bh + me.pos] = -lse / a.scale;
   }
-  const float lse2 = lse * kLog2e, sc = a.scale * kLog2e;
-  const OperandLanes lanes(lane);
+  const RowPair l = row_pair(__float_as_uint(lse * kLog2e)), mine = row_pair(me.code), limit = row_pair(me.limit);
+  const float lse2[2] = {__uint_as_float(l.v[0]), __uint_as_float(l.v[1])}, sc = a.scale * kLog2e;
+  const QuadLanes lanes(lane);
   const bool wave_active = u.tile * BM + wave * 32 < N;
 
-  f32x16 dq_acc[2] = {zero16(), zero16()};
+  QuadAcc dq_quad = {};
   for (int t = 0; t < n_tiles; ++t) {
     const unsigned tile = lds_addr(stream.acquire(t, n_tiles));
     if (!wave_active) continue;
-    dq_tile(tile, qf, gf, lanes, sc, lse2, delta, CodeMask(code + t * BN, hl, me.code, me.limit), dq_acc);
+    dq_tile(tile, qf, gf, lanes, sc, lse2, ndelta, PairCodeMask(code + t * BN, lane >> 4, mine, limit), dq_quad);
   }
   __syncthreads();
-  const float mul = me.in_range && me.code != kPadCode ? a.scale : 0.f;  // pad positions: zeros
-#pragma unroll
-  for (int db = 0; db < 2; ++db)
-#pragma unroll
-    for (int c = 0; c < 16; ++c) dq_acc[db][c] = mul != 0.f ? dq_acc[db][c] * mul : 0.f;
+  live_rows(dq_quad, a.scale, row_pair(me.in_range && me.code != kPadCode));
+  const f32x16 dq_acc[2] = {quad_item(dq_quad, 0), quad_item(dq_quad, 1)};
   const f32x16 (*accs[1])[2] = {&dq_acc};
   const float muls[1] = {1.f};
   unsigned short* const outs[1] = {dQ};
-  store_owned_rows<1>(accs, muls, outs, lds, q_tok, wave, lane);
+  store_owned_rows<1, true, true>(accs, muls, outs, lds, q_tok, wave, lane);
 }
 
 // ======================================================================================
@@ -437,7 +472,7 @@ __global__ __launch_bounds__(kThreads) void bwd_dkv_dense_kernel(DenseArgs a) {
   if (!dense_unit(a, a.N, a.H, a.B * a.H, u)) return;
   const int N = a.N, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int m = lane & 31, hl = lane >> 5;
+  const int m = lane & 31;
   const size_t bh = (size_t)u.bh * N;
   const unsigned short* Q = static_cast<const unsigned short*>(a.q) + bh * kD;
   const unsigned short* K = static_cast<const unsigned short*>(a.k) + bh * kD;
@@ -447,7 +482,7 @@ __global__ __launch_bounds__(kThreads) void bwd_dkv_dense_kernel(DenseArgs a) {
   unsigned short* dV = static_cast<unsigned short*>(a.dv) + bh * kD;
 
   DenseStream stream{Q, dO, a.nlse + bh, a.delta + bh, lds, kDkvStageD, N, wave, lane,
-                     make_load_lane(wave, lane)};
+                     make_load_lane<true>(wave, lane)};
   const int n_tiles = (N + BN - 1) / BN;
   DenseCodes codes;
   codes.load(a.row_ids, a.col_ids, a.flags, u, N);
@@ -456,40 +491,33 @@ __global__ __launch_bounds__(kThreads) void bwd_dkv_dense_kernel(DenseArgs a) {
   if (tid < BM) k_tok[tid] = u.tile * BM + tid < N ? u.tile * BM + tid : -1;
   __syncthreads();
   const DenseRow me = dense_row(N, u, code, wave, m);  // this lane's key
-  bf16x8 kf[4], vf[4];
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    const size_t off = (size_t)me.pos * kD + ks * 16 + hl * 8;
-    kf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(K + off));
-    vf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(V + off));
-  }
-  asm volatile("" ::"v"(kf[0]), "v"(kf[1]), "v"(kf[2]), "v"(kf[3]), "v"(vf[0]), "v"(vf[1]),
-               "v"(vf[2]), "v"(vf[3]));
+  bf16x8 kf[2][2], vf[2][2];
+  dense_operands(K, u.tile * BM + wave * 32, N, lane, kf);
+  dense_operands(V, u.tile * BM + wave * 32, N, lane, vf);
+  asm volatile("" ::"v"(kf[0][0]), "v"(kf[0][1]), "v"(kf[1][0]), "v"(kf[1][1]), "v"(vf[0][0]), "v"(vf[0][1]), "v"(vf[1][0]),
+               "v"(vf[1][1]));
   const float sc = uniform(a.scale * kLog2e);
-  const OperandLanes lanes(lane);
+  const QuadLanes lanes(lane);
+  const RowPair mine = row_pair(me.code), limit = row_pair(me.limit);
   const bool wave_active = u.tile * BM + wave * 32 < N;
 
-  f32x16 dk_acc[2] = {zero16(), zero16()}, dv_acc[2] = {zero16(), zero16()};
+  QuadAcc dk_quad = {}, dv_quad = {};
   for (int t = 0; t < n_tiles; ++t) {
     const char* Qst = stream.acquire(t, n_tiles);
     const float* lse_row = reinterpret_cast<const float*>(Qst + kStage);
     const float* delta_row = lse_row + BN;
     if (!wave_active) continue;
-    dkv_tile(lds_addr(Qst), lse_row, delta_row, kf, vf, lanes, sc, hl, CodeMask(code + t * BN, hl, me.code, me.limit), dk_acc, dv_acc);
+    dkv_tile(lds_addr(Qst), lse_row, delta_row, kf, vf, lanes, sc, lane >> 4, PairCodeMask(code + t * BN, lane >> 4, mine, limit), dk_quad, dv_quad);
   }
   __syncthreads();
-  const bool live = me.in_range && me.code != kPadCode;  // pad positions: zeros
-#pragma unroll
-  for (int db = 0; db < 2; ++db)
-#pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      dk_acc[db][c] = live ? dk_acc[db][c] * a.scale : 0.f;
-      dv_acc[db][c] = live ? dv_acc[db][c] : 0.f;
-    }
+  const RowPair live = row_pair(me.in_range && me.code != kPadCode);
+  live_rows(dk_quad, a.scale, live);
+  live_rows(dv_quad, 1.f, live);
+  const f32x16 dk_acc[2] = {quad_item(dk_quad, 0), quad_item(dk_quad, 1)}, dv_acc[2] = {quad_item(dv_quad, 0), quad_item(dv_quad, 1)};
   const f32x16 (*accs[2])[2] = {&dk_acc, &dv_acc};
   const float muls[2] = {1.f, 1.f};
   unsigned short* const outs[2] = {dK, dV};
-  store_owned_rows<2>(accs, muls, outs, lds, k_tok, wave, lane);
+  store_owned_rows<2, true, true>(accs, muls, outs, lds, k_tok, wave, lane);
 }
 
 // ======================================================================================

@@ -42,10 +42,11 @@ struct LoadLane {
   int row0;    // this lane's row for instruction 0 (instruction 1: row0 + 8)
   int chunk0;  // global chunk this lane fetches for instruction 0 (instruction 1: chunk0 ^ 2)
 };
+template <bool kQuad = false>
 __device__ inline LoadLane make_load_lane(int wave, int lane) {
   LoadLane l;
   l.row0 = 16 * wave + (lane >> 3);
-  l.chunk0 = (lane & 7) ^ swz(l.row0 & 15);  // swz(row0 + 8) = swz(row0) ^ 2
+  l.chunk0 = (lane & 7) ^ (kQuad ? swz_quad(l.row0) : swz(l.row0 & 15));  // of row0 + 8: ^ 2
   return l;
 }
 

@@ -4,7 +4,7 @@
 //   A (32 x 16): lane holds row m,    k = 8*hl .. 8*hl+7   (8 bf16 = 16 bytes)
 //   B (16 x 32): lane holds column m, k = 8*hl .. 8*hl+7
 //   C (32 x 32): lane holds column m, register c = 4*g + r  <->  row 8*g + 4*hl + r
-// and, in the dense backward of up to 256 positions, v_mfma_f32_16x16x32_bf16, lane l = 16*q + r (r = l % 16):
+// and, in the backward and the dense forward of up to 128 positions, v_mfma_f32_16x16x32_bf16, lane l = 16*q + r (r = l % 16):
 //   A (16 x 32): lane holds row r,    k = 8*q .. 8*q+7
 //   B (32 x 16): lane holds column r, k = 8*q .. 8*q+7
 //   C (16 x 16): lane holds column r, register e  <->  row 4*q + e
@@ -96,6 +96,13 @@ __device__ inline float quad_sum(float x) {
   const unsigned u = __float_as_uint(x);
   const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
   return half_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+
+// Lanes m and m + 32 hold row m's value of 32 rows: those of rows r and 16 + r (r = lane % 16).
+struct RowPair { unsigned v[2]; };
+__device__ inline RowPair row_pair(unsigned x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  return {{r[0], r[1]}};
 }
 
 // Sum of the eight bf16 values of an operand, added to acc (v_dot2 against ones): the row sum

@@ -416,9 +416,26 @@ struct OwnedTile {
     for (int i = 0; i < 4; ++i)
       v[i] = *reinterpret_cast<const bf16x8*>(X + (unsigned)__shfl(pos, (lane >> 3) + 8 * i, 64) * kD + 8 * (lane & 7));
   }
-  // operand order: lane m, half hl holds dims 16 ks + 8 hl .. + 7 of row m.  `room`: 4 KB that no other wavefront uses;
-  // LDS keeps a wavefront's accesses in order.
+  // Operand order.  `room`: 4 KB that no other wavefront uses; LDS keeps a wavefront's accesses in order.
+  // 32 x 32 tiles: lane m, half hl holds dims 16 ks + 8 hl .. + 7 of row m.
   __device__ __forceinline__ void operands(bf16x8 (&f)[4], char* room, int lane) const {
+    through(room, lane, [&] {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) f[ks] = read_plain(room, plain_off(lane & 31, lane >> 5, ks));
+    });
+  }
+  // 16 x 16 tiles: lane 16 q + r holds dims 32 ks + 8 q .. + 7 of rows r and 16 + r, [ks][which].
+  __device__ __forceinline__ void operands(bf16x8 (&f)[2][2], char* room, int lane) const {
+    through(room, lane, [&] {
+      const int r = lane & 15;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) f[ks][cb] = read_plain(room, (16 * cb + r) * 128 + (((4 * ks + (lane >> 4)) ^ swz(r)) << 4));
+    });
+  }
+  template <class Read>
+  __device__ __forceinline__ void through(char* room, int lane, Read&& read) const {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int row = (lane >> 3) + 8 * i;
@@ -426,8 +443,7 @@ struct OwnedTile {
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) f[ks] = read_plain(room, plain_off(lane & 31, lane >> 5, ks));
+    read();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     __builtin_amdgcn_wave_barrier();
   }
@@ -482,6 +498,26 @@ __device__ __forceinline__ void stage_rows(const f32x16& a, float mul, char* sta
     *reinterpret_cast<uint2*>(stage + wrow * 128 + (((4 * db + g) ^ (wrow & 7)) << 4) + 8 * hl) = w;
   }
 }
+// The same of 16 x 16 tiles, [16 dims][16 owned rows]: register e of lane 16 q + r is dim 16 d + 4 q + e of row 16 cb + r.  As an item
+// (two of the four d) it is register 8 (d & 1) + 4 cb + e.
+typedef f32x4 QuadAcc[4][2];
+__device__ __forceinline__ f32x16 quad_item(const QuadAcc& a, int db) {
+  f32x16 x;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) x[i] = a[2 * db + (i >> 3)][(i >> 2) & 1][i & 3];
+  return x;
+}
+__device__ __forceinline__ void stage_rows_quad(const f32x16& a, float mul, char* stage, int row0, int db, int lane) {
+  const int r = lane & 15, q = lane >> 4;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = row0 + 16 * (i & 1) + r, d = 2 * db + (i >> 1);
+    uint2 w;
+    w.x = pack2(a[4 * i] * mul, a[4 * i + 1] * mul);
+    w.y = pack2(a[4 * i + 2] * mul, a[4 * i + 3] * mul);
+    *reinterpret_cast<uint2*>(stage + row * 128 + (((2 * d + (q >> 1)) ^ (r & 7)) << 4) + 8 * (q & 1)) = w;
+  }
+}
 template <bool kThrough = true>
 __device__ __forceinline__ void flush_rows(unsigned short* out, const char* stage, const int* row_tok, int wave, int lane) {
   const ResultRows<kThrough> rows(out);
@@ -493,15 +529,17 @@ __device__ __forceinline__ void flush_rows(unsigned short* out, const char* stag
       rows.store((unsigned)tok * (kD * 2) + piece * 16, *reinterpret_cast<const u32x4*>(stage + row * 128 + ((piece ^ (row & 7)) << 4)));
   }
 }
-template <int kTensors, bool kThrough = true>
+template <int kTensors, bool kThrough = true, bool kQuad = false>
 __device__ inline void store_owned_rows(const f32x16 (*acc[kTensors])[2], const float (&mul)[kTensors],
                                         unsigned short* const (&out)[kTensors], char* stage,
                                         const int* row_tok, int wave, int lane) {
 #pragma unroll
   for (int x = 0; x < kTensors; ++x)
 #pragma unroll
-    for (int db = 0; db < 2; ++db)
-      stage_rows((*acc[x])[db], mul[x], stage + x * (BM * 128), wave * 32 + (lane & 31), db, lane >> 5);
+    for (int db = 0; db < 2; ++db) {
+      if (kQuad) stage_rows_quad((*acc[x])[db], mul[x], stage + x * (BM * 128), wave * 32, db, lane);
+      else stage_rows((*acc[x])[db], mul[x], stage + x * (BM * 128), wave * 32 + (lane & 31), db, lane >> 5);
+    }
   __syncthreads();
 #pragma unroll
   for (int x = 0; x < kTensors; ++x) flush_rows<kThrough>(out[x], stage + x * (BM * 128), row_tok, wave, lane);

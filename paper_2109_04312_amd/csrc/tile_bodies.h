@@ -8,15 +8,16 @@
 //   mask.load(blk)     fetch what keep() needs for the 32-row block blk of the tile
 //   mask.keep(c, x, o) x if the pair (this lane's owned row, streamed row c_row(c) of the loaded
 //                      block) belongs to the pattern, else o.  c = accumulator register 0..15
-//   Mask::kPairs       the mask also has load_pairs(blk) and pair_mask(i): ones where registers 2 i (low half of the
-//                      word) and 2 i + 1 belong to the pattern, for words of two bf16 values
+// and in the backward, in place of the last two:
+//   mask.load_pairs(blk)
+//   mask.pair_mask(cb, i)  for words of two bf16 values: ones where the lane's streamed rows 2 i (low half) and 2 i + 1
+//                          belong to the pattern for its owned row of block cb
 //
-// Layout everywhere: C tiles have rows = streamed rows, columns = the wavefront's 32 owned rows
-// (lane m = owned row, lane half hl), so per-owned-row quantities are per-lane scalars.
+// Layout everywhere: C tiles have rows = streamed rows, columns = owned rows, so per-owned-row quantities are per-lane
+// scalars.  The forward has 32 x 32 tiles (lane m = owned row, lane half hl), the backward 16 x 16 ones (lane 16 q + r owns
+// rows r and 16 + r of the wavefront's 32, blocks cb = 0, 1, and holds streamed rows 8 q .. 8 q + 7 of 32: see QuadLanes).
 #pragma once
 #include <hip/hip_runtime.h>
-
-#include <type_traits>
 
 #include "d2l.h"
 #include "mfma_common.h"
@@ -35,7 +36,6 @@ struct WindowMask {
   const int lo, hi;     // else this lane's
   const int end;
   const int u_lo, u_hi, a_lo, a_hi;  // wave-uniform, relative to base: union and intersection of the rows' windows
-  static constexpr bool kPairs = true;
   int one = 1;         // width of the extract; its value is hidden from the compiler, which would turn extract
                        // and select into test, compare and conditional move
   unsigned bits = 0;   // bit 8 (c >> 2) + (c & 3): register c of the loaded block is inside
@@ -56,23 +56,43 @@ struct WindowMask {
     const int d = d0(), first = min(max(-d - 32 * blk, 0), 31), last = min(max(len() - d - 32 * blk, 0), 31);
     bits = ((1u << last) - 1u) & ~((1u << first) - 1u);
   }
-  // Two values rounded to bf16 share a word, and so do the two halves of its mask: the signs of a word's two
-  // halves, spread over them by one byte permutation, from a register that has every pair's bits 16 apart.  For P and dS four
-  // instructions per pair of each where masking them one by one takes six (dK/dV of 8 x 2048 with long cells 77.0 -> 75.0 us, of
-  // 2 x 8192 82.0 -> 79.7, of 16 ragged sequences of 4096 228 -> 222); for dS or P alone three where it takes four,
-  // which gained nothing.
-  unsigned pairs[2];   // of registers 0..7 and 8..15: bit 8 g + 2 i and that + 16: pair i of group g
-  __device__ __forceinline__ void load_pairs(int blk) {
-    load(blk);
-    pairs[0] = (bits & 0xffffu) | ((bits << 15) & 0xffff0000u);
-    pairs[1] = (bits >> 16) | ((bits >> 1) & 0xffff0000u);
-  }
-  __device__ __forceinline__ unsigned pair_mask(int i) const {
-    return __builtin_amdgcn_perm(0u, pairs[i >> 2] << (15 - 8 * ((i >> 1) & 1) - 2 * (i & 1)), 0x09090808u);
-  }
   __device__ __forceinline__ float keep(int c, float x, float other) const {
     const unsigned in = (unsigned)__builtin_amdgcn_sbfe((int)bits, 8 * (c >> 2) + (c & 3), one);
     return __uint_as_float((__float_as_uint(x) & in) | (__float_as_uint(other) & ~in));
+  }
+};
+
+// The same in the backward.  A masked value is already rounded to bf16, two in a word, and so are the two halves of its mask:
+// the signs of a word's two halves, spread over them by one byte permutation, from a register that has every pair's bits 16
+// apart.  For P and dS four instructions per pair of each where masking them one by one takes six (dK/dV of 8 x 2048 with
+// long cells 77.0 -> 75.0 us, of 16 ragged sequences of 4096 228 -> 222).
+struct PairWindowMask {
+  const int base, lane;
+  const bool all;
+  const RowPair& rng;   // of the lane's two rows: first slot | end << 16 (both are below 2^15)
+  const int end;
+  const int u_lo, u_hi, a_lo, a_hi;
+  unsigned pairs = 0;   // bit 8 cb + 2 i and that + 16: streamed rows 2 i and 2 i + 1 of the lane's eight
+  __device__ __forceinline__ PairWindowMask(int base_, int lane_, bool all_, int end_, const RowPair& rng_, int u0, int u1, int a0, int a1)
+      : base(base_), lane(lane_), all(all_), rng(rng_), end(end_), u_lo(u0 - base_), u_hi(u1 - base_), a_lo(a0 - base_),
+        a_hi(a1 - base_) {}
+  __device__ __forceinline__ bool full(int blk) const { return 32 * blk >= a_lo && 32 * blk + 32 <= a_hi; }
+  __device__ __forceinline__ bool skip(int blk) const { return 32 * blk >= u_hi || 32 * blk + 32 <= u_lo; }
+  __device__ __forceinline__ void load_pairs(int blk) {
+    int l = lane;
+    asm volatile("" : "+v"(l));  // (the lane's first row is worked out here, not kept in a register through the loop)
+    const int at = base + 32 * blk + 8 * (l >> 4);
+    unsigned bits = 0;
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) {
+      const unsigned r = all ? (unsigned)end << 16 : rng.v[cb];
+      const int first = min(max((int)(r & 0xffffu) - at, 0), 8), last = min(max((int)(r >> 16) - at, 0), 8);
+      bits |= (((1u << last) - 1u) & ~((1u << first) - 1u)) << (8 * cb);
+    }
+    pairs = bits | ((bits << 15) & 0xffff0000u);
+  }
+  __device__ __forceinline__ unsigned pair_mask(int cb, int i) const {
+    return __builtin_amdgcn_perm(0u, pairs << (15 - 8 * cb - 2 * i), 0x09090808u);
   }
 };
 
@@ -218,109 +238,149 @@ __device__ __forceinline__ void fwd_tile(unsigned tile, const bf16x8 (&qf)[4], c
   add(pb, l_tile);
 }
 
-// dQ: P = exp2(S sc - lse2), dP^T = V dO^T, dS = P (dP - delta), dQ^T += K^T dS^T; one 32-key block
+// The backward's tiles are 16 x 16 (16x16x32 instructions).  They move half as many accumulator bytes per operation; a lane's four registers of a
+// row block can all start at the same value, so dP - delta comes out of dQ's product too; and -lse / scale and -delta of a block are read once for both
+// blocks of owned rows.  Operand reads are told to go ahead of the products: left to itself the compiler reads one operand of the second
+// contraction, waits, multiplies and reads the next.  us, with 32 x 32 tiles and so: 2 x 8192, 16 heads dQ 58.9 -> 54.5 and dK/dV 73.5 ->
+// 68.7, 8 x 2048 with long cells 56.1 -> 53.1 and 70.4 -> 66.4, 16 ragged sequences of 4096 164.0 -> 160.2 and 215.3 -> 209.0, 32 x 512, 12
+// heads 32.0 -> 31.8 and 35.7 -> 35.1.  (The forward, whose vector part is larger, gains 2 % at 2 x 8192 and loses 1 to 3 %
+// elsewhere: half of its instructions are exponentials and their sums, and a short unit's beginning and end take longer.)
+//
+// dQ: P = exp2(S sc - lse2), dP^T - delta = V dO^T - delta, dS = P (dP - delta), dQ^T += K^T dS^T; one 32-key block
 // at a time, so only one block's scores are live.
 template <class Mask>
-__device__ __forceinline__ void dq_tile(unsigned tile, const bf16x8 (&qf)[4], const bf16x8 (&gf)[4], const OperandLanes& lanes,
-                                        float sc, float lse2, float delta, Mask&& mask, f32x16 (&dq_acc)[2]) {
-  const PlainAddr p(lanes, tile);  // K; V follows it
-  const TransposedAddr kt(lanes, tile);
+__device__ __forceinline__ void dq_tile(unsigned tile, const bf16x8 (&qf)[2][2], const bf16x8 (&gf)[2][2], const QuadLanes& lanes,
+                                             float sc, const float (&lse2)[2], const f32x4 (&ndelta)[2], Mask&& mask, f32x4 (&dq_acc)[4][2]) {
 #pragma unroll
   for (int jb = 0; jb < 2; ++jb) {
+    __builtin_amdgcn_sched_barrier(0);  // (where a mask brings no branches: blocks and their two contractions one after the other, or the registers do not do)
     if (mask.skip(jb)) continue;
-    f32x16 s = zero16(), dp = zero16();
+    const unsigned k_at = tile + jb * kBlockBytes, v_at = k_at + kTileBytes;
+    f32x4 s[2][2], dp[2][2];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      s = mfma(read_plain(p.a[ks] + jb * 32 * 128), qf[ks], s);                 // S^T  = K Q^T
-      dp = mfma(read_plain(p.a[ks] + kTileBytes + jb * 32 * 128), gf[ks], dp);  // dP^T = V dO^T
-    }
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int c = 0; c < 16; ++c)
-      s[c] = __builtin_amdgcn_exp2f(fmaf(s[c], sc, -lse2)) * (dp[c] - delta);
+      for (int ks = 0; ks < 2; ++ks) {
+        const bf16x8 k = read_quad(lanes, k_at, h, ks), v = read_quad(lanes, v_at, h, ks);
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+          s[h][cb] = mfma16(k, qf[ks][cb], ks ? s[h][cb] : f32x4{0.f, 0.f, 0.f, 0.f});  // S^T  = K Q^T
+          dp[h][cb] = mfma16(v, gf[ks][cb], ks ? dp[h][cb] : ndelta[cb]);               // dP^T = V dO^T
+        }
+      }
+    unsigned dw[2][4];
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[h][cb][e] = __builtin_amdgcn_exp2f(fmaf(s[h][cb][e], sc, -lse2[cb])) * dp[h][cb][e];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) dw[cb][2 * h + i] = pack2(s[h][cb][2 * i], s[h][cb][2 * i + 1]);
+      }
     if (!mask.full(jb)) {  // wave-uniform: zero the pairs outside the pattern
-      mask.load(jb);
+      mask.load_pairs(jb);
 #pragma unroll
-      for (int c = 0; c < 16; ++c) s[c] = mask.keep(c, s[c], 0.f);
+      for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dw[cb][i] &= mask.pair_mask(cb, i);
     }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
-      const bf16x8 ds8 = pack8(s, 8 * tt);
-      const int at = (jb * 32 + tt * 16) * 128;
+    for (int d = 0; d < 4; ++d) {
+      const bf16x8 k = read_quad_transposed(lanes, k_at, d);
 #pragma unroll
-      for (int db = 0; db < 2; ++db) dq_acc[db] = mfma(read_transposed(kt.lo[db] + at, kt.hi[db] + at), ds8, dq_acc[db]);
+      for (int cb = 0; cb < 2; ++cb)
+        dq_acc[d][cb] = mfma16(k, as_bf16x8(make_uint4(dw[cb][0], dw[cb][1], dw[cb][2], dw[cb][3])), dq_acc[d][cb]);
     }
+    __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
   }
 }
-
 // dK, dV: rows of the tile are the streamed queries.  The accumulators start at the rows'
-// -lse / scale and -delta (from LDS, four consecutive rows per group of four registers), so the
+// -lse / scale and -delta (from LDS, four consecutive rows per block h), so the
 // contractions deliver S - lse / scale and dP - delta directly: P = exp2(that sc), dS = P (dP - delta);
 // dV^T += dO^T P, dK^T += Q^T dS.
 template <class Mask>
-__device__ __forceinline__ void dkv_tile(unsigned tile, const float* lse_row, const float* delta_row, const bf16x8 (&kf)[4],
-                                         const bf16x8 (&vf)[4], const OperandLanes& lanes, float sc, int hl, Mask&& mask,
-                                         f32x16 (&dk_acc)[2], f32x16 (&dv_acc)[2]) {
-  const PlainAddr p(lanes, tile);  // Q; dO follows it
-  const TransposedAddr t(lanes, tile);
+__device__ __forceinline__ void dkv_tile(unsigned tile, const float* lse_row, const float* delta_row, const bf16x8 (&kf)[2][2],
+                                              const bf16x8 (&vf)[2][2], const QuadLanes& lanes, float sc, int q, Mask&& mask,
+                                              f32x4 (&dk_acc)[4][2], f32x4 (&dv_acc)[4][2]) {
 #pragma unroll
   for (int ib = 0; ib < 2; ++ib) {
+    __builtin_amdgcn_sched_barrier(0);
     if (mask.skip(ib)) continue;
-    f32x16 s, dp;
+    const unsigned q_at = tile + ib * kBlockBytes, g_at = q_at + kTileBytes;
+    f32x4 s[2][2], dp[2][2];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int row0 = ib * 32 + 8 * g + 4 * hl;
-      const float4 l4 = *reinterpret_cast<const float4*>(lse_row + row0);
-      const float4 d4 = *reinterpret_cast<const float4*>(delta_row + row0);
-      s[4 * g] = l4.x; s[4 * g + 1] = l4.y; s[4 * g + 2] = l4.z; s[4 * g + 3] = l4.w;
-      dp[4 * g] = d4.x; dp[4 * g + 1] = d4.y; dp[4 * g + 2] = d4.z; dp[4 * g + 3] = d4.w;
-    }
+    for (int h = 0; h < 2; ++h) {
+      const f32x4 l4 = *reinterpret_cast<const f32x4*>(lse_row + ib * 32 + 8 * q + 4 * h);
+      const f32x4 d4 = *reinterpret_cast<const f32x4*>(delta_row + ib * 32 + 8 * q + 4 * h);
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      s = mfma(read_plain(p.a[ks] + ib * 32 * 128), kf[ks], s);                 // S  = Q K^T
-      dp = mfma(read_plain(p.a[ks] + kTileBytes + ib * 32 * 128), vf[ks], dp);  // dP = dO V^T
-    }
+      for (int ks = 0; ks < 2; ++ks) {
+        const bf16x8 x = read_quad(lanes, q_at, h, ks), g = read_quad(lanes, g_at, h, ks);
 #pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      s[c] = __builtin_amdgcn_exp2f(s[c] * sc);  // P
-      dp[c] *= s[c];                             // dS
-    }
-    // wave-uniform: zero the pairs outside the pattern
-    constexpr bool kPairs = std::remove_reference<Mask>::type::kPairs;
-    if (!kPairs && !mask.full(ib)) {
-      mask.load(ib);
-#pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        s[c] = mask.keep(c, s[c], 0.f);
-        dp[c] = mask.keep(c, dp[c], 0.f);
-      }
-    }
-    unsigned pw[8], dw[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      pw[i] = pack2(s[2 * i], s[2 * i + 1]);
-      dw[i] = pack2(dp[2 * i], dp[2 * i + 1]);
-    }
-    if constexpr (kPairs)
-      if (!mask.full(ib)) {
-        mask.load_pairs(ib);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const unsigned in = mask.pair_mask(i);
-          pw[i] &= in;
-          dw[i] &= in;
+        for (int cb = 0; cb < 2; ++cb) {
+          s[h][cb] = mfma16(x, kf[ks][cb], ks ? s[h][cb] : l4);    // S  = Q K^T
+          dp[h][cb] = mfma16(g, vf[ks][cb], ks ? dp[h][cb] : d4);  // dP = dO V^T
         }
       }
+    }
+    __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
 #pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
-      const bf16x8 p8 = as_bf16x8(make_uint4(pw[4 * tt], pw[4 * tt + 1], pw[4 * tt + 2], pw[4 * tt + 3]));
-      const bf16x8 ds8 = as_bf16x8(make_uint4(dw[4 * tt], dw[4 * tt + 1], dw[4 * tt + 2], dw[4 * tt + 3]));
-      const int q_at = (ib * 32 + tt * 16) * 128, g_at = q_at + kTileBytes;
+    for (int i = 0; i < 4; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    unsigned pw[2][4], dw[2][4];
 #pragma unroll
-      for (int db = 0; db < 2; ++db) {
-        dv_acc[db] = mfma(read_transposed(t.lo[db] + g_at, t.hi[db] + g_at), p8, dv_acc[db]);   // dV^T += dO^T P
-        dk_acc[db] = mfma(read_transposed(t.lo[db] + q_at, t.hi[db] + q_at), ds8, dk_acc[db]);  // dK^T += Q^T dS
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          s[h][cb][e] = __builtin_amdgcn_exp2f(s[h][cb][e] * sc);  // P
+          dp[h][cb][e] *= s[h][cb][e];                             // dS
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          pw[cb][2 * h + i] = pack2(s[h][cb][2 * i], s[h][cb][2 * i + 1]);
+          dw[cb][2 * h + i] = pack2(dp[h][cb][2 * i], dp[h][cb][2 * i + 1]);
+        }
+      }
+    if (!mask.full(ib)) {  // wave-uniform: zero the pairs outside the pattern
+      mask.load_pairs(ib);
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const unsigned in = mask.pair_mask(cb, i);
+          pw[cb][i] &= in;
+          dw[cb][i] &= in;
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    bf16x8 p8[2], ds8[2];
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) {
+      p8[cb] = as_bf16x8(make_uint4(pw[cb][0], pw[cb][1], pw[cb][2], pw[cb][3]));
+      ds8[cb] = as_bf16x8(make_uint4(dw[cb][0], dw[cb][1], dw[cb][2], dw[cb][3]));
+    }
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      const bf16x8 g = read_quad_transposed(lanes, g_at, d), x = read_quad_transposed(lanes, q_at, d);
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) {
+        dv_acc[d][cb] = mfma16(g, p8[cb], dv_acc[d][cb]);   // dV^T += dO^T P
+        dk_acc[d][cb] = mfma16(x, ds8[cb], dk_acc[d][cb]);  // dK^T += Q^T dS
       }
     }
+    __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
   }
 }
 

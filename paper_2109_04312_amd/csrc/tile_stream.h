@@ -22,7 +22,8 @@ constexpr int kIdxSlots = 8;  // tiles of indices in the ring (three stages' are
 
 // kTiles = 2 (small launches, see small_forward in stream_plan.h): a stage holds two consecutive tiles, which the
 // wavefronts meet one after the other or share, and every function below is for both.
-template <int kTileStage, int kTiles = 1>
+// kQuad: tiles are read as QuadLanes says.
+template <int kTileStage, int kTiles = 1, bool kQuad = false>
 struct TileStream {
   static constexpr int kStageBytes = kTiles * kTileStage;
   const UnitPlan& u;
@@ -40,7 +41,7 @@ struct TileStream {
                         const unsigned short* x0, const unsigned short* x1, const float* rs,
                         int row_off_, int wave_, int lane_)
       : u(u_), global_idx(gidx), stages(st), ring(rg), X0(x0), X1(x1), row_src(rs), row_off(row_off_), wave(wave_),
-        lane(lane_), ll(make_load_lane(wave_, lane_)) {}
+        lane(lane_), ll(make_load_lane<kQuad>(wave_, lane_)) {}
 
   // (tile t of a stage that begins with tile t - j)
   __device__ char* stage(int t) { return stages + ((unsigned)(t - u.t_begin) / kTiles % kStages) * kStageBytes; }

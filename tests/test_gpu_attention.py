@@ -422,6 +422,14 @@ def test_bf16_tile_edges(n_global, rows, cols, cell, N, rise):
     check_workload(synth.Workload(f"bf16 edges {N}", "bf16", st, np.array([ROW, COL], np.uint8), q, k, v, do, 0.125), rise == 0)
 
 
+@pytest.mark.parametrize("n_global,columns,N", [(3, 40, 823), (37, 40, 900), (64, 23, 340)])
+def test_windows_of_every_length_at_every_offset(n_global, columns, N):
+    """Columns of 1, 2, 3, ... tokens: windows that begin and end at every place in the eight rows of a block that a lane masks."""
+    st = synth._stack([synth.flatten_table(N, n_global, 1, columns, np.arange(1, columns + 1))])
+    q, k, v, do = synth.draw_tensors(np.random.default_rng(N), 1, 2, N, 64, "bf16", 4)
+    check_workload(synth.Workload(f"columns of 1 to {columns}", "bf16", st, np.array([ROW, COL], np.uint8), q, k, v, do, 0.125), True)
+
+
 @pytest.mark.parametrize("bits", [12, 14, 50, 95, 110, 140])
 @pytest.mark.parametrize("n_global,rows,cols,cell,N", [(31, 3, 2, 40, 271), (70, 2, 3, 100, 670), (40, 90, 5, 4, 2100)])
 def test_bf16_scores_that_rise_in_steps(n_global, rows, cols, cell, N, bits):
