@@ -286,9 +286,17 @@ def test_tiles_dealt_by_feature(B, N, H, E):
 
 @pytest.mark.parametrize("B,N,H,E", [(5, 901, 12, 768), (1, 3999, 16, 1024), (2, 4225, 16, 1024)])
 def test_one_round_of_eight_wavefronts(B, N, H, E):
-    """Tiles of 192 x 256 in one round: QKV of the first two sizes, the output of the last (its last feature tile a third)."""
+    """192 x 256 and 256 x 192 both one round, the second with fewer tiles, which is taken: QKV of the first two sizes, the output
+    of the last."""
     check(N, B, N, H, E, pad_tail=N // 7)
     check_bwd(N, B, N, H, E, pad_tail=N // 7)
+
+
+@pytest.mark.parametrize("B,N,H,E", [(8, 442, 12, 768), (5, 700, 12, 768), (40, 250, 16, 1024)])
+def test_one_round_of_192_by_256(B, N, H, E):
+    """Tiles of 192 x 256 in one round, fewer than of 256 x 192 or as many (180): QKV of the first two sizes (the last token tile
+    186 and 188 rows), the output of the last (its last feature tile a third)."""
+    check(N, B, N, H, E, pad_tail=N // 7)
 
 
 @pytest.mark.parametrize("B,N,H,E", [(8, 76, 32, 4096), (1, 1988, 20, 3456)])
