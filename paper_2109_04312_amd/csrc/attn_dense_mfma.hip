@@ -347,9 +347,8 @@ __global__ __launch_bounds__(64 * NW, 4) void fwd_dense_short_kernel(const void*
 #pragma unroll
     for (int hb = 0; hb < 2; ++hb) {
       if (ib * 32 >= N) continue;
-      f32x4 x = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) x = mfma16(read_quad(lanes, k_at + ib * kBlockBytes, hb, ks), qf[ks], x);
+      f32x4 x = mfma16(read_quad(lanes, k_at + ib * kBlockBytes, hb, 0), qf[0], f32x4{0.f, 0.f, 0.f, 0.f});
+      x = mfma16_apart(read_quad(lanes, k_at + ib * kBlockBytes, hb, 1), qf[1], x);
       const uint4 c4 = *reinterpret_cast<const uint4*>(code + ib * 32 + 8 * quarter + 4 * hb);
       const unsigned codes[4] = {c4.x, c4.y, c4.z, c4.w};
 #pragma unroll

@@ -34,6 +34,16 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// The same for a start that the result does not simply replace (a start of two products, a chain outside a loop).  The compiler may give a
+// four-register result half of the registers of a start that nothing reads again; its assembler refuses that for longer results only.  Eight
+// such instructions agreed with the oracle wherever they ran, but a variant of the weight gradient that had one was wrong, and what made it wrong was
+// not found.  Here the start is kept until the result is there, so that the library has none (a test reads the built code).
+__device__ __forceinline__ f32x4 mfma16_apart(bf16x8 a, bf16x8 b, f32x4 start) {
+  f32x4 c = mfma16(a, b, start);
+  asm("" : "+v"(c) : "v"(start));
+  return c;
+}
+
 __device__ inline f32x16 zero16() {
   f32x16 z;
 #pragma unroll

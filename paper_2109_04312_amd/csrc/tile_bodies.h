@@ -320,8 +320,8 @@ __device__ __forceinline__ void dkv_tile(unsigned tile, const float* lse_row, co
         const bf16x8 x = read_quad(lanes, q_at, h, ks), g = read_quad(lanes, g_at, h, ks);
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) {
-          s[h][cb] = mfma16(x, kf[ks][cb], ks ? s[h][cb] : l4);    // S  = Q K^T
-          dp[h][cb] = mfma16(g, vf[ks][cb], ks ? dp[h][cb] : d4);  // dP = dO V^T
+          s[h][cb] = mfma16_apart(x, kf[ks][cb], ks ? s[h][cb] : l4);    // S  = Q K^T
+          dp[h][cb] = mfma16_apart(g, vf[ks][cb], ks ? dp[h][cb] : d4);  // dP = dO V^T
         }
       }
     }
