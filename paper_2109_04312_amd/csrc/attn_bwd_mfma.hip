@@ -38,7 +38,7 @@ __device__ __forceinline__ void merge_chunks(const float* const (&part)[kTensors
   for (int i = wave; i < items * kTensors; i += kThreads / 64) {
     const int x = i / items, item = i - x * items;
     const float* src = x == 0 ? part[0] : part[kTensors - 1];
-    f32x16 acc = zero16();
+    f32x4 acc[2][2] = {};  // register i of the item: [i / 8][i / 4 % 2][i % 4]
     for (int c0 = 0; c0 < n_chunks; c0 += kBatch) {
       float2 v[kBatch][8];
       load_items<kShared>(v, src, item, c0, n_chunks, lane);
@@ -47,12 +47,13 @@ __device__ __forceinline__ void merge_chunks(const float* const (&part)[kTensors
         const float w = c0 + e < n_chunks ? 1.f : 0.f;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-          acc[2 * k] += w * v[e][k].x;
-          acc[2 * k + 1] += w * v[e][k].y;
+          acc[k >> 2][(k >> 1) & 1][2 * (k & 1)] += w * v[e][k].x;
+          acc[k >> 2][(k >> 1) & 1][2 * (k & 1) + 1] += w * v[e][k].y;
         }
       }
     }
-    stage_rows_quad(acc, 1.f, stage + x * (BM * 128), (item >> 1) * 32, item & 1, lane);
+#pragma unroll
+    for (int d = 0; d < 2; ++d) stage_rows_quad(acc[d], 1.f, stage + x * (BM * 128), (item >> 1) * 32, 2 * (item & 1) + d, lane);
   }
   __syncthreads();
 #pragma unroll
@@ -131,7 +132,7 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w, ch
 
   const QuadLanes lanes(lane);
 
-  QuadAcc dq_q = {};
+  QuadAcc dq_acc = {};
   for (int t = u.t_begin; t < u.t_end; ++t) {
     const unsigned tile = lds_addr(stream.acquire(t));
     const bool part0 = t < u.n_t0;
@@ -139,18 +140,17 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w, ch
     if (me.wave_active) {
       PairWindowMask mask(base, lane, part0, u.G, rng, split.first(base, part0 ? 0 : me.w_lo),
                       split.end(base, part0 ? u.G : me.w_hi), part0 ? 0 : me.a_lo, part0 ? u.G : me.a_hi);
-      dq_tile(tile, qf, gf, lanes, sc, lse2, ndelta, mask, dq_q);
+      dq_tile(tile, qf, gf, lanes, sc, lse2, ndelta, mask, dq_acc);
     }
   }
   __syncthreads();  // all wavefronts are done reading the stages; reuse them for the epilogue
-  f32x16 dq_acc[2] = {quad_item(dq_q, 0), quad_item(dq_q, 1)};
   int ln = lane;
   asm volatile("" : "+v"(ln));  // what follows is computed here, not kept in registers through the loop
   if (split.on) {  // add the other half of the streamed rows
     char* const mine = lds + BM * 128 + (wave & 1) * (kItemFloats * 2 * 4);  // (rows are staged below that)
-    if (wave >= 2) put_items<2>(mine, dq_acc, ln);
+    if (wave >= 2) put_items(mine, dq_acc, ln);
     __syncthreads();
-    if (wave < 2) add_items<2>(mine, dq_acc, 1.f, 1.f, ln);
+    if (wave < 2) add_items(mine, dq_acc, 1.f, 1.f, ln);
   }
   if (u.part >= 0) {
     const size_t slot = (size_t)w.bh * owner_slots(N) + u.part;
@@ -171,10 +171,10 @@ __device__ __forceinline__ void bwd_dq_unit(const AttnArgs& a, const Work& w, ch
     }
     return;
   }
-  const f32x16 (*accs[1])[2] = {&dq_acc};
+  const QuadAcc* accs[1] = {&dq_acc};
   const float muls[1] = {a.scale};
   unsigned short* const outs[1] = {dQ};
-  store_owned_rows<1, true, true>(accs, muls, outs, lds, q_tok, wave, ln);
+  store_owned_rows<1>(accs, muls, outs, lds, q_tok, wave, ln);
 }
 
 // (four workgroups per CU: with three, the column-head units of the benchmark shape do not all
@@ -242,7 +242,7 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
   const int quarter = lane >> 4;
   const RowPair rng = row_pair(me.lo | me.hi << 16);
 
-  QuadAcc dk_q = {}, dv_q = {};
+  QuadAcc dk_acc = {}, dv_acc = {};
   for (int t = u.t_begin; t < u.t_end; ++t) {
     const char* Qst = stream.acquire(t);
     const float* lse_row = reinterpret_cast<const float*>(Qst + 2 * kTileBytes);
@@ -252,21 +252,20 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
     if (me.wave_active) {
       PairWindowMask mask(base, lane, part0, u.G, rng, split.first(base, part0 ? 0 : me.w_lo),
                       split.end(base, part0 ? u.G : me.w_hi), part0 ? 0 : me.a_lo, part0 ? u.G : me.a_hi);
-      dkv_tile(lds_addr(Qst), lse_row, delta_row, kf, vf, lanes, sc, quarter, mask, dk_q, dv_q);
+      dkv_tile(lds_addr(Qst), lse_row, delta_row, kf, vf, lanes, sc, quarter, mask, dk_acc, dv_acc);
     }
   }
   __syncthreads();  // all wavefronts are done reading the stages; reuse them for the epilogue
-  f32x16 dk_acc[2] = {quad_item(dk_q, 0), quad_item(dk_q, 1)}, dv_acc[2] = {quad_item(dv_q, 0), quad_item(dv_q, 1)};
   if (split.on) {  // add the other half of the streamed rows
     char* const mine = lds + (wave & 1) * (kItemFloats * 4 * 4);
     if (wave >= 2) {
-      put_items<2>(mine, dk_acc, lane);
-      put_items<2>(mine + kItemFloats * 2 * 4, dv_acc, lane);
+      put_items(mine, dk_acc, lane);
+      put_items(mine + kItemFloats * 2 * 4, dv_acc, lane);
     }
     __syncthreads();
     if (wave < 2) {
-      add_items<2>(mine, dk_acc, 1.f, 1.f, lane);
-      add_items<2>(mine + kItemFloats * 2 * 4, dv_acc, 1.f, 1.f, lane);
+      add_items(mine, dk_acc, 1.f, 1.f, lane);
+      add_items(mine + kItemFloats * 2 * 4, dv_acc, 1.f, 1.f, lane);
     }
     __syncthreads();
   }
@@ -289,10 +288,10 @@ __device__ __forceinline__ void bwd_dkv_unit(const AttnArgs& a, const Work& w, c
     }
     return;
   }
-  const f32x16 (*accs[2])[2] = {&dk_acc, &dv_acc};
+  const QuadAcc* accs[2] = {&dk_acc, &dv_acc};
   const float muls[2] = {a.scale, 1.f};
   unsigned short* const outs[2] = {dK, dV};
-  store_owned_rows<2, true, true>(accs, muls, outs, lds, k_tok, wave, lane);
+  store_owned_rows<2>(accs, muls, outs, lds, k_tok, wave, lane);
 }
 
 // dQ rows of the question tokens of one (sequence, head) from the dq kernel's chunk partials.
@@ -321,7 +320,7 @@ __device__ __forceinline__ void merge_dq(const AttnArgs& a, int bh_i, char* stag
 
 // The first `n_merge` workgroups (a multiple of eight, so that the unit queues keep their XCDs) merge
 // dQ partials: a few microseconds each, out of the way before the kernel's own tail.
-// (168 registers: three workgroups per CU; with two the kernel takes 15 to 20 % longer)
+// (162 registers: three workgroups per CU; with two the kernel takes 15 to 20 % longer)
 template <bool kJoin, bool kMany>
 __global__ __launch_bounds__(kThreads, 3) void bwd_dkv_mfma_kernel(MATE_UNIT_LISTS, AttnArgs a, int n_merge) {
   __shared__ __attribute__((aligned(1024))) char lds[kStages * kDkvStage];

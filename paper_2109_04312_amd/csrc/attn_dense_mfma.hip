@@ -338,7 +338,7 @@ __global__ __launch_bounds__(64 * NW, 4) void fwd_dense_short_kernel(const void*
   __syncthreads();
   if (own >= N) return;
   const float sc = uniform(a.scale * kLog2e);
-  const QuadLanes lanes(lane);
+  const QuadLanes lanes(lane);   // (an address for each block: one for all of a tensor takes up to 8 registers more here)
   const unsigned k_at = lds_addr(kt), v_at = lds_addr(vt);
   f32x4 s[S::kBlocks][2];  // S^T: keys 8 q + 4 h + e of the block, query r
   float mx = -INFINITY;
@@ -347,9 +347,9 @@ __global__ __launch_bounds__(64 * NW, 4) void fwd_dense_short_kernel(const void*
 #pragma unroll
     for (int hb = 0; hb < 2; ++hb) {
       if (ib * 32 >= N) continue;
-      f32x4 x = mfma16(read_quad(lanes, k_at + ib * kBlockBytes, hb, 0), qf[0], f32x4{0.f, 0.f, 0.f, 0.f});
+      f32x4 x = mfma16(read_quad(QuadAddr(lanes, k_at + ib * kBlockBytes), 0, hb, 0), qf[0], f32x4{0.f, 0.f, 0.f, 0.f});
       // (Four wavefronts have no such instruction by themselves, and with this take 2 % longer, one sequence of 64, 4 heads 3.02 and 3.09 us.)
-      const bf16x8 k1 = read_quad(lanes, k_at + ib * kBlockBytes, hb, 1);
+      const bf16x8 k1 = read_quad(QuadAddr(lanes, k_at + ib * kBlockBytes), 0, hb, 1);
       x = NW > 4 ? mfma16_apart(k1, qf[1], x) : mfma16(k1, qf[1], x);
       const uint4 c4 = *reinterpret_cast<const uint4*>(code + ib * 32 + 8 * quarter + 4 * hb);
       const unsigned codes[4] = {c4.x, c4.y, c4.z, c4.w};
@@ -382,7 +382,7 @@ __global__ __launch_bounds__(64 * NW, 4) void fwd_dense_short_kernel(const void*
     }
     const bf16x8 p8 = as_bf16x8(make_uint4(w[0], w[1], w[2], w[3]));
 #pragma unroll
-    for (int d = 0; d < 4; ++d) acc[d] = mfma16(read_quad_transposed(lanes, v_at + ib * kBlockBytes, d), p8, acc[d]);   // O^T += V^T P^T
+    for (int d = 0; d < 4; ++d) acc[d] = mfma16(read_quad_transposed(QuadAddr(lanes, v_at + ib * kBlockBytes), 0, d), p8, acc[d]);   // O^T += V^T P^T
   }
   l = quad_sum(l);
   const bool live = my_code != kPadCode;  // pad positions: O = 0, LSE = 0
@@ -447,25 +447,25 @@ __global__ __launch_bounds__(kThreads, 3) void bwd_dq_dense_kernel(DenseArgs a) 
   const QuadLanes lanes(lane);
   const bool wave_active = u.tile * BM + wave * 32 < N;
 
-  QuadAcc dq_quad = {};
+  QuadAcc dq_acc = {};
   for (int t = 0; t < n_tiles; ++t) {
     const unsigned tile = lds_addr(stream.acquire(t, n_tiles));
     if (!wave_active) continue;
-    dq_tile(tile, qf, gf, lanes, sc, lse2, ndelta, PairCodeMask(code + t * BN, lane >> 4, mine, limit), dq_quad);
+    dq_tile(tile, qf, gf, lanes, sc, lse2, ndelta, PairCodeMask(code + t * BN, lane >> 4, mine, limit), dq_acc);
   }
   __syncthreads();
-  live_rows(dq_quad, a.scale, row_pair(me.in_range && me.code != kPadCode));
-  const f32x16 dq_acc[2] = {quad_item(dq_quad, 0), quad_item(dq_quad, 1)};
-  const f32x16 (*accs[1])[2] = {&dq_acc};
+  live_rows(dq_acc, a.scale, row_pair(me.in_range && me.code != kPadCode));
+  const QuadAcc* accs[1] = {&dq_acc};
   const float muls[1] = {1.f};
   unsigned short* const outs[1] = {dQ};
-  store_owned_rows<1, true, true>(accs, muls, outs, lds, q_tok, wave, lane);
+  store_owned_rows<1>(accs, muls, outs, lds, q_tok, wave, lane);
 }
 
 // ======================================================================================
 // dK, dV
 // ======================================================================================
-__global__ __launch_bounds__(kThreads) void bwd_dkv_dense_kernel(DenseArgs a) {
+// (168 registers, three workgroups a compute unit; left to itself the compiler takes 182: 16 x 384, 16 heads, both kernels, 47.6 and 52.7 us)
+__global__ __launch_bounds__(kThreads, 3) void bwd_dkv_dense_kernel(DenseArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds[2 * kDkvStageD];
   __shared__ __attribute__((aligned(16))) unsigned code[kDenseMaxN];
   __shared__ int k_tok[BM];
@@ -502,23 +502,22 @@ __global__ __launch_bounds__(kThreads) void bwd_dkv_dense_kernel(DenseArgs a) {
   const RowPair mine = row_pair(me.code), limit = row_pair(me.limit);
   const bool wave_active = u.tile * BM + wave * 32 < N;
 
-  QuadAcc dk_quad = {}, dv_quad = {};
+  QuadAcc dk_acc = {}, dv_acc = {};
   for (int t = 0; t < n_tiles; ++t) {
     const char* Qst = stream.acquire(t, n_tiles);
     const float* lse_row = reinterpret_cast<const float*>(Qst + kStage);
     const float* delta_row = lse_row + BN;
     if (!wave_active) continue;
-    dkv_tile(lds_addr(Qst), lse_row, delta_row, kf, vf, lanes, sc, lane >> 4, PairCodeMask(code + t * BN, lane >> 4, mine, limit), dk_quad, dv_quad);
+    dkv_tile(lds_addr(Qst), lse_row, delta_row, kf, vf, lanes, sc, lane >> 4, PairCodeMask(code + t * BN, lane >> 4, mine, limit), dk_acc, dv_acc);
   }
   __syncthreads();
   const RowPair live = row_pair(me.in_range && me.code != kPadCode);
-  live_rows(dk_quad, a.scale, live);
-  live_rows(dv_quad, 1.f, live);
-  const f32x16 dk_acc[2] = {quad_item(dk_quad, 0), quad_item(dk_quad, 1)}, dv_acc[2] = {quad_item(dv_quad, 0), quad_item(dv_quad, 1)};
-  const f32x16 (*accs[2])[2] = {&dk_acc, &dv_acc};
+  live_rows(dk_acc, a.scale, live);
+  live_rows(dv_acc, 1.f, live);
+  const QuadAcc* accs[2] = {&dk_acc, &dv_acc};
   const float muls[2] = {1.f, 1.f};
   unsigned short* const outs[2] = {dK, dV};
-  store_owned_rows<2, true, true>(accs, muls, outs, lds, k_tok, wave, lane);
+  store_owned_rows<2>(accs, muls, outs, lds, k_tok, wave, lane);
 }
 
 // ======================================================================================
@@ -837,8 +836,8 @@ __global__ __launch_bounds__(64 * NW, 4) void bwd_dense_short_kernel(
         const unsigned codes[4] = {c4.x, c4.y, c4.z, c4.w};
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-          s = mfma16(read_quad(lanes, q_at + ib * kBlockBytes, hb, ks), kf[ks], s);     // S  = Q K^T
-          dp = mfma16(read_quad(lanes, g_at + ib * kBlockBytes, hb, ks), vf[ks], dp);   // dP = dO V^T
+          s = mfma16(read_quad(QuadAddr(lanes, q_at + ib * kBlockBytes), 0, hb, ks), kf[ks], s);     // S  = Q K^T
+          dp = mfma16(read_quad(QuadAddr(lanes, g_at + ib * kBlockBytes), 0, hb, ks), vf[ks], dp);   // dP = dO V^T
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -856,8 +855,8 @@ __global__ __launch_bounds__(64 * NW, 4) void bwd_dense_short_kernel(
       const bf16x8 ds8 = as_bf16x8(make_uint4(dw[ib][0], dw[ib][1], dw[ib][2], dw[ib][3]));
 #pragma unroll
       for (int d = 0; d < 4; ++d) {
-        dv_acc[d] = mfma16(read_quad_transposed(lanes, g_at + ib * kBlockBytes, d), p8, dv_acc[d]);   // dV^T += dO^T P
-        dk_acc[d] = mfma16(read_quad_transposed(lanes, q_at + ib * kBlockBytes, d), ds8, dk_acc[d]);  // dK^T += Q^T dS
+        dv_acc[d] = mfma16(read_quad_transposed(QuadAddr(lanes, g_at + ib * kBlockBytes), 0, d), p8, dv_acc[d]);   // dV^T += dO^T P
+        dk_acc[d] = mfma16(read_quad_transposed(QuadAddr(lanes, q_at + ib * kBlockBytes), 0, d), ds8, dk_acc[d]);  // dK^T += Q^T dS
       }
     }
   __syncthreads();  // everyone is done with the Q and dO tiles, and with its own rows of V
@@ -877,9 +876,9 @@ __global__ __launch_bounds__(64 * NW, 4) void bwd_dense_short_kernel(
   for (int d = 0; d < 4; ++d) dq_acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (own < N)
     for (int kb = 0; kb * 32 < N; ++kb) {
-      const bf16x8 dsq = read_quad_transposed(lanes, ds_at + (wave >> 2) * S::kBytes + kb * kBlockBytes, wave & 3);
+      const bf16x8 dsq = read_quad_transposed(QuadAddr(lanes, ds_at + (wave >> 2) * S::kBytes + kb * kBlockBytes), 0, wave & 3);
 #pragma unroll
-      for (int d = 0; d < 4; ++d) dq_acc[d] = mfma16(read_quad_transposed(lanes, k_at + kb * kBlockBytes, d), dsq, dq_acc[d]);
+      for (int d = 0; d < 4; ++d) dq_acc[d] = mfma16(read_quad_transposed(QuadAddr(lanes, k_at + kb * kBlockBytes), 0, d), dsq, dq_acc[d]);
     }
   __syncthreads();  // dS^T and the K tiles have been read
   // Result rows of this wavefront, staged one tensor after the other over its own rows of the K tiles.

@@ -168,7 +168,7 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w, FwdLd
     char* const mine = lds + BM * 128 + (wave & 1) * (kItemFloats * 2 * 4);
     float* const stat = reinterpret_cast<float*>(&idx_ring[2 * (wave & 1)][0]);
     auto put = [&](char* items, float* st) {
-      put_items<2>(items, o_acc, ln);
+      put_items(items, o_acc, ln);
       st[ln] = m_run;
       st[64 + ln] = l_run;
     };
@@ -178,7 +178,7 @@ __device__ __forceinline__ void fwd_unit(const AttnArgs& a, const Work& w, FwdLd
       const float other = m2 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m2 - m_new) * sc);
       l_run = l_run * own + st[64 + ln] * other;
       m_run = m_new;
-      add_items<2>(items, o_acc, own, other, ln);
+      add_items(items, o_acc, own, other, ln);
     };
     if (wave >= 2) put(mine, stat);
     __syncthreads();

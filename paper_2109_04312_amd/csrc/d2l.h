@@ -198,14 +198,22 @@ struct QuadLanes {
   }
 };
 constexpr int kBlockBytes = 32 * 128, kHalfBlock = 4 * 128;  // in LDS: 32 rows, and from block 0 to block 1 of them
-// Row r of block h of the 32 rows at LDS address `at`, dims 32 k + 8 q .. + 7.
-__device__ __forceinline__ bf16x8 read_quad(const QuadLanes& l, unsigned at, int h, int k) {
-  return read_plain(((at + l.plain) ^ (64 * k)) + h * kHalfBlock);
-}
-// Columns 16 d .. + 15 (operand rows) and rows 8 q .. + 7 (k) of the 32 rows at LDS address `at`.
-__device__ __forceinline__ bf16x8 read_quad_transposed(const QuadLanes& l, unsigned at, int d) {
-  const unsigned a = (at + l.trans) ^ (32 * d);
-  return read_transposed(a, a + kHalfBlock);
+// A lane's two addresses in the tiles from LDS address `tile` on.  Blocks of 32 rows, halves of them and tensors one tile after the other lie multiples
+// of 512 bytes apart, which the exclusive ors do not touch: immediate offsets (`at`).  us, backward, with an address of its own for each block and tensor and
+// results gathered before they are stored (see QuadAcc), and so: 5 x 487, 12 heads 16.75 -> 16.35, 5 x 348, 16 heads 16.5 -> 15.95, 6 x 289, 12 heads
+// 14.15 -> 13.95, 4 x 1024 25.5 -> 25.2, 2 x 8192, 16 heads 169.5 -> 164, dense 1 x 1024, 4 heads 54.15 -> 53.15, 8 x 300, 12 heads 32.0 -> 31.3.  (The first
+// of these are what a short unit's beginning and end cost; with 32 x 32 tiles they were 16.2, 15.8, 13.75, 26.0, 173.5, 53.9 and 32.2.)
+struct QuadAddr {
+  unsigned plain, trans;
+  __host__ __device__ __forceinline__ QuadAddr(const QuadLanes& l, unsigned tile) : plain(tile + l.plain), trans(tile + l.trans) {}
+  __host__ __device__ __forceinline__ unsigned plain_at(unsigned at, int h, int k) const { return (plain ^ (64 * k)) + (at + h * kHalfBlock); }
+  __host__ __device__ __forceinline__ unsigned trans_at(unsigned at, int d) const { return (trans ^ (32 * d)) + at; }
+};
+// Row r of block h of the 32 rows at `at`, dims 32 k + 8 q .. + 7.
+__device__ __forceinline__ bf16x8 read_quad(const QuadAddr& a, unsigned at, int h, int k) { return read_plain(a.plain_at(at, h, k)); }
+// Columns 16 d .. + 15 (operand rows) and rows 8 q .. + 7 (k) of the 32 rows at `at`.
+__device__ __forceinline__ bf16x8 read_quad_transposed(const QuadAddr& a, unsigned at, int d) {
+  return read_transposed(a.trans_at(at, d), a.trans_at(at + kHalfBlock, d));
 }
 
 // Tile row (0..31 inside a 32-row block) held in C register c of a lane in half hl when the A

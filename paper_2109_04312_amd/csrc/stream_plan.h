@@ -498,23 +498,18 @@ __device__ __forceinline__ void stage_rows(const f32x16& a, float mul, char* sta
     *reinterpret_cast<uint2*>(stage + wrow * 128 + (((4 * db + g) ^ (wrow & 7)) << 4) + 8 * hl) = w;
   }
 }
-// The same of 16 x 16 tiles, [16 dims][16 owned rows]: register e of lane 16 q + r is dim 16 d + 4 q + e of row 16 cb + r.  As an item
-// (two of the four d) it is register 8 (d & 1) + 4 cb + e.
+// The same of 16 x 16 tiles, [16 dims][16 owned rows]: register e of lane 16 q + r is dim 16 d + 4 q + e of row 16 cb + r.
+// They stay quads of registers from the loop to the stores: gathered into sixteen neighbours each, dK and dV took 158 moves at the end of
+// every unit (see QuadAddr for what the two cost together).
 typedef f32x4 QuadAcc[4][2];
-__device__ __forceinline__ f32x16 quad_item(const QuadAcc& a, int db) {
-  f32x16 x;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) x[i] = a[2 * db + (i >> 3)][(i >> 2) & 1][i & 3];
-  return x;
-}
-__device__ __forceinline__ void stage_rows_quad(const f32x16& a, float mul, char* stage, int row0, int db, int lane) {
+__device__ __forceinline__ void stage_rows_quad(const f32x4 (&a)[2], float mul, char* stage, int row0, int d, int lane) {
   const int r = lane & 15, q = lane >> 4;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = row0 + 16 * (i & 1) + r, d = 2 * db + (i >> 1);
+  for (int cb = 0; cb < 2; ++cb) {
+    const int row = row0 + 16 * cb + r;
     uint2 w;
-    w.x = pack2(a[4 * i] * mul, a[4 * i + 1] * mul);
-    w.y = pack2(a[4 * i + 2] * mul, a[4 * i + 3] * mul);
+    w.x = pack2(a[cb][0] * mul, a[cb][1] * mul);
+    w.y = pack2(a[cb][2] * mul, a[cb][3] * mul);
     *reinterpret_cast<uint2*>(stage + row * 128 + (((2 * d + (q >> 1)) ^ (r & 7)) << 4) + 8 * (q & 1)) = w;
   }
 }
@@ -529,20 +524,29 @@ __device__ __forceinline__ void flush_rows(unsigned short* out, const char* stag
       rows.store((unsigned)tok * (kD * 2) + piece * 16, *reinterpret_cast<const u32x4*>(stage + row * 128 + ((piece ^ (row & 7)) << 4)));
   }
 }
-template <int kTensors, bool kThrough = true, bool kQuad = false>
+template <int kTensors, bool kThrough = true>
 __device__ inline void store_owned_rows(const f32x16 (*acc[kTensors])[2], const float (&mul)[kTensors],
                                         unsigned short* const (&out)[kTensors], char* stage,
                                         const int* row_tok, int wave, int lane) {
 #pragma unroll
   for (int x = 0; x < kTensors; ++x)
 #pragma unroll
-    for (int db = 0; db < 2; ++db) {
-      if (kQuad) stage_rows_quad((*acc[x])[db], mul[x], stage + x * (BM * 128), wave * 32, db, lane);
-      else stage_rows((*acc[x])[db], mul[x], stage + x * (BM * 128), wave * 32 + (lane & 31), db, lane >> 5);
-    }
+    for (int db = 0; db < 2; ++db)
+      stage_rows((*acc[x])[db], mul[x], stage + x * (BM * 128), wave * 32 + (lane & 31), db, lane >> 5);
   __syncthreads();
 #pragma unroll
   for (int x = 0; x < kTensors; ++x) flush_rows<kThrough>(out[x], stage + x * (BM * 128), row_tok, wave, lane);
+}
+template <int kTensors>
+__device__ inline void store_owned_rows(const QuadAcc* (&acc)[kTensors], const float (&mul)[kTensors], unsigned short* const (&out)[kTensors],
+                                        char* stage, const int* row_tok, int wave, int lane) {
+#pragma unroll
+  for (int x = 0; x < kTensors; ++x)
+#pragma unroll
+    for (int d = 0; d < 4; ++d) stage_rows_quad((*acc[x])[d], mul[x], stage + x * (BM * 128), wave * 32, d, lane);
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < kTensors; ++x) flush_rows(out[x], stage + x * (BM * 128), row_tok, wave, lane);
 }
 
 // ---- partial results of chunked question-token owners ------------------------------------------
@@ -556,33 +560,39 @@ __device__ inline void store_owned_rows(const f32x16 (*acc[kTensors])[2], const 
 // N = 8192, H = 16, nearly all of it the launch), and so does dQ's where all three gradients are one launch.  Where dQ has
 // one of its own: merged by the first workgroups of the dK/dV kernel, behind the kernel boundary.
 constexpr int kItemFloats = 16 * 64;  // one wavefront's accumulator of one dim block
-template <bool kShared>
-__device__ __forceinline__ void store_partial(const f32x16 acc[2], float mul, float* __restrict__ part, int wave, int lane) {
+// (Of 16 x 16 tiles an item is two of the four d, its register 8 (d & 1) + 4 cb + e.)
+__device__ __forceinline__ float item_register(const f32x16 (&acc)[2], int item, int i) { return acc[item][i]; }
+__device__ __forceinline__ float item_register(const QuadAcc& acc, int item, int i) { return acc[2 * item + (i >> 3)][(i >> 2) & 1][i & 3]; }
+__device__ __forceinline__ void set_item_register(f32x16 (&acc)[2], int item, int i, float x) { acc[item][i] = x; }
+__device__ __forceinline__ void set_item_register(QuadAcc& acc, int item, int i, float x) { acc[2 * item + (i >> 3)][(i >> 2) & 1][i & 3] = x; }
+template <bool kShared, class Acc>
+__device__ __forceinline__ void store_partial(const Acc& acc, float mul, float* __restrict__ part, int wave, int lane) {
   asm volatile("" : "+v"(lane));  // keeps the address arithmetic out of the tile loop's registers
 #pragma unroll
   for (int db = 0; db < 2; ++db)
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      put_pair<kShared>(part + (2 * wave + db) * kItemFloats + (i * 64 + lane) * 2, acc[db][2 * i] * mul, acc[db][2 * i + 1] * mul);
+      put_pair<kShared>(part + (2 * wave + db) * kItemFloats + (i * 64 + lane) * 2, item_register(acc, db, 2 * i) * mul,
+                        item_register(acc, db, 2 * i + 1) * mul);
 }
-// The same registers through LDS (kItems blocks of kItemFloats floats at p): acc = own acc + other p.
-template <int kItems>
-__device__ __forceinline__ void put_items(char* p, const f32x16 (&acc)[kItems], int lane) {
+// The same registers through LDS (two blocks of kItemFloats floats at p): acc = own acc + other p.
+template <class Acc>
+__device__ __forceinline__ void put_items(char* p, const Acc& acc, int lane) {
 #pragma unroll
-  for (int x = 0; x < kItems; ++x)
+  for (int x = 0; x < 2; ++x)
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      *reinterpret_cast<float2*>(p + ((x * 8 + i) * 64 + lane) * 8) = make_float2(acc[x][2 * i], acc[x][2 * i + 1]);
+      *reinterpret_cast<float2*>(p + ((x * 8 + i) * 64 + lane) * 8) = make_float2(item_register(acc, x, 2 * i), item_register(acc, x, 2 * i + 1));
 }
-template <int kItems>
-__device__ __forceinline__ void add_items(const char* p, f32x16 (&acc)[kItems], float own, float other, int lane) {
+template <class Acc>
+__device__ __forceinline__ void add_items(const char* p, Acc& acc, float own, float other, int lane) {
 #pragma unroll
-  for (int x = 0; x < kItems; ++x)
+  for (int x = 0; x < 2; ++x)
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const float2 v = *reinterpret_cast<const float2*>(p + ((x * 8 + i) * 64 + lane) * 8);
-      acc[x][2 * i] = fmaf(v.x, other, acc[x][2 * i] * own);
-      acc[x][2 * i + 1] = fmaf(v.y, other, acc[x][2 * i + 1] * own);
+      set_item_register(acc, x, 2 * i, fmaf(v.x, other, item_register(acc, x, 2 * i) * own));
+      set_item_register(acc, x, 2 * i + 1, fmaf(v.y, other, item_register(acc, x, 2 * i + 1) * own));
     }
 }
 // kBatch chunks of one item with all loads issued before the first use (the pin: left alone, the

@@ -251,17 +251,18 @@ __device__ __forceinline__ void fwd_tile(unsigned tile, const bf16x8 (&qf)[4], c
 template <class Mask>
 __device__ __forceinline__ void dq_tile(unsigned tile, const bf16x8 (&qf)[2][2], const bf16x8 (&gf)[2][2], const QuadLanes& lanes,
                                              float sc, const float (&lse2)[2], const f32x4 (&ndelta)[2], Mask&& mask, f32x4 (&dq_acc)[4][2]) {
+  const QuadAddr at(lanes, tile);
 #pragma unroll
   for (int jb = 0; jb < 2; ++jb) {
     __builtin_amdgcn_sched_barrier(0);  // (where a mask brings no branches: blocks and their two contractions one after the other, or the registers do not do)
     if (mask.skip(jb)) continue;
-    const unsigned k_at = tile + jb * kBlockBytes, v_at = k_at + kTileBytes;
+    const unsigned k_at = jb * kBlockBytes, v_at = k_at + kTileBytes;
     f32x4 s[2][2], dp[2][2];
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        const bf16x8 k = read_quad(lanes, k_at, h, ks), v = read_quad(lanes, v_at, h, ks);
+        const bf16x8 k = read_quad(at, k_at, h, ks), v = read_quad(at, v_at, h, ks);
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) {
           s[h][cb] = mfma16(k, qf[ks][cb], ks ? s[h][cb] : f32x4{0.f, 0.f, 0.f, 0.f});  // S^T  = K Q^T
@@ -288,7 +289,7 @@ __device__ __forceinline__ void dq_tile(unsigned tile, const bf16x8 (&qf)[2][2],
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-      const bf16x8 k = read_quad_transposed(lanes, k_at, d);
+      const bf16x8 k = read_quad_transposed(at, k_at, d);
 #pragma unroll
       for (int cb = 0; cb < 2; ++cb)
         dq_acc[d][cb] = mfma16(k, as_bf16x8(make_uint4(dw[cb][0], dw[cb][1], dw[cb][2], dw[cb][3])), dq_acc[d][cb]);
@@ -305,11 +306,12 @@ template <class Mask>
 __device__ __forceinline__ void dkv_tile(unsigned tile, const float* lse_row, const float* delta_row, const bf16x8 (&kf)[2][2],
                                               const bf16x8 (&vf)[2][2], const QuadLanes& lanes, float sc, int q, Mask&& mask,
                                               f32x4 (&dk_acc)[4][2], f32x4 (&dv_acc)[4][2]) {
+  const QuadAddr at(lanes, tile);
 #pragma unroll
   for (int ib = 0; ib < 2; ++ib) {
     __builtin_amdgcn_sched_barrier(0);
     if (mask.skip(ib)) continue;
-    const unsigned q_at = tile + ib * kBlockBytes, g_at = q_at + kTileBytes;
+    const unsigned q_at = ib * kBlockBytes, g_at = q_at + kTileBytes;
     f32x4 s[2][2], dp[2][2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -317,7 +319,7 @@ __device__ __forceinline__ void dkv_tile(unsigned tile, const float* lse_row, co
       const f32x4 d4 = *reinterpret_cast<const f32x4*>(delta_row + ib * 32 + 8 * q + 4 * h);
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        const bf16x8 x = read_quad(lanes, q_at, h, ks), g = read_quad(lanes, g_at, h, ks);
+        const bf16x8 x = read_quad(at, q_at, h, ks), g = read_quad(at, g_at, h, ks);
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) {
           s[h][cb] = mfma16_apart(x, kf[ks][cb], ks ? s[h][cb] : l4);    // S  = Q K^T
@@ -367,7 +369,7 @@ __device__ __forceinline__ void dkv_tile(unsigned tile, const float* lse_row, co
     }
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-      const bf16x8 g = read_quad_transposed(lanes, g_at, d), x = read_quad_transposed(lanes, q_at, d);
+      const bf16x8 g = read_quad_transposed(at, g_at, d), x = read_quad_transposed(at, q_at, d);
 #pragma unroll
       for (int cb = 0; cb < 2; ++cb) {
         dv_acc[d][cb] = mfma16(g, p8[cb], dv_acc[d][cb]);   // dV^T += dO^T P

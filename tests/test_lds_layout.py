@@ -25,6 +25,12 @@ void tile_addresses(unsigned tile, int lane, unsigned* plain /* [4] */, unsigned
   for (int ks = 0; ks < 4; ++ks) plain[ks] = p.a[ks];
   for (int db = 0; db < 2; ++db) { trans[2 * db] = t.lo[db]; trans[2 * db + 1] = t.hi[db]; }
 }
+// of the 32 rows at `at` in the tiles: [2 halves of a block][2 k] and [4 d][2 halves]
+void quad_addresses(unsigned tile, unsigned at, int lane, unsigned* plain, unsigned* trans) {
+  const QuadAddr a(QuadLanes(lane), tile);
+  for (int h = 0; h < 2; ++h) for (int k = 0; k < 2; ++k) plain[2 * h + k] = a.plain_at(at, h, k);
+  for (int d = 0; d < 4; ++d) for (int h = 0; h < 2; ++h) trans[2 * d + h] = a.trans_at(at + h * kHalfBlock, d);
+}
 }
 """
 TILES = [0, 8192, 0x4200, 3 * 8192 + 128]
@@ -77,6 +83,23 @@ def test_operands_of_32_by_32_tiles(lib, tile):
             for half in range(2):
                 row, chunk = 4 * hl + (i >> 2) + 8 * half, 4 * db + 2 * (g & 1) + ((i & 3) >> 1)
                 assert trans[2 * db + half] == tile + place(lib, 0, row, chunk) + 8 * (i & 1)
+    assert all(no_bank_twice(s) for s in seen)
+
+
+@pytest.mark.parametrize("at", [0, 32 * 128, 64 * 128, 96 * 128])
+@pytest.mark.parametrize("tile", TILES)
+def test_operands_of_16_by_16_tiles(lib, tile, at):
+    plain, trans = (C.c_uint * 4)(), (C.c_uint * 8)()
+    seen = np.zeros((4, 64), np.int64)
+    for lane in range(64):
+        r, q = lane & 15, lane >> 4
+        lib.quad_addresses(tile, at, lane, plain, trans)
+        for h in range(2):
+            for k in range(2):
+                seen[2 * h + k, lane] = plain[2 * h + k]
+                assert plain[2 * h + k] == tile + at + place(lib, 1, 8 * (r >> 2) + 4 * h + (r & 3), 4 * k + q)
+            for d in range(4):
+                assert trans[2 * d + h] == tile + at + place(lib, 1, 8 * q + 4 * h + (r >> 2), 2 * d + ((r & 3) >> 1)) + 8 * (r & 1)
     assert all(no_bank_twice(s) for s in seen)
 
 
