@@ -529,9 +529,12 @@ hipError_t launch_proj(ProjArgs a, int kernel_id, hipStream_t stream) {
 // tiles than 256 x 256: for sizes whose tiles are one round.  us, before and with them: 768 -> 2304 at 8 x 512 23.1 -> 22.1, at
 // 5 x 929 22.7 -> 21.3, 1024 -> 3072 at 4000 28.1 -> 25.3, 1024 -> 1024 at 2 x 4344 28.0 -> 23.5, at 10752 29.4 -> 26.4, d_o
 // there with dW 55.5 -> 52.2.  Their constants (1.0 a stage, 6.8) were read off these times and are the same for both; where both are
-// one round, the one with fewer tiles is taken, which computes less past the last feature and the last token.  us, 192 x 256 and 256 x 192, where
-// the second has fewer: 1024 -> 1024 at 10656 tokens (252 and 224 tiles) 24.4 and 23.0, 1024 -> 3072 at 8 x 343 24.8 and 23.1, 2048 -> 6144 at 2 x
-// 769 51.1 and 44.5, 1536 -> 1536 at 7972 34.9 and 36.7; of 51 such products 3.4 % shorter in the mean, 13 % at best, 5 % longer at worst.  As many
+// one round, 256 x 192 is taken if it has fewer tiles, which compute less past the last feature and the last token, and 192 x 256 has more than 200.  With
+// fewer than that a fifth of the CUs is idle in either, and a tile of 256 tokens has more of them past the end of a short sequence, which cost it nothing.
+// us, 192 x 256 and 256 x 192: 2048 -> 6144 at 4 x 295 (256 and 192 tiles) 39.9 and 36.2, 1536 -> 1536 at 16 x 324 31.5 and 28.3, 768 -> 2304 at 4 x 1058
+// (240 and 216) 18.6 and 17.0, 1280 -> 3840 at 12 x 192 (240 and 180) 26.5 and 27.7; of 270 products with fewer tiles of 256 x 192 the 206 with more than
+// 200 of 192 x 256 are 1.9 % shorter in the mean, 11 % at best, 4 % longer at worst, the others 1.6 % longer, 6 % at worst (1024 -> 3072 at 12 x
+// 192, 192 and 144 tiles, 20.0 and 21.2, 1536 -> 4608 at 8 x 164 27.0 and 28.9).  As many
 // tiles: 22 products, equal in the mean (768 -> 2304 at 8 x 512, 192 and 216 tiles, 17.6 and 18.1, at 3 x 1511 19.1 and 21.2, 1536 -> 4608 at 3 x
 // 593 33.9 and 31.7); more tiles: 17, 0.5 % longer.
 //                        features x tokens, wavefronts, stages, workgroups per CU, groups
@@ -570,7 +573,8 @@ ProjChoice choose_proj(const ProjArgs& a) {
   // 1769 65.9 and 80.1, d_o of 1536 from 3584 at 11 x 248 46.4 and 60.2; shorter ones are told apart by the costs).
   const bool large = tiles_of<Proj128>(a) > 512;
   if constexpr (!kTransposedW)
-    if (large && tiles_of<Proj192x256>(a) <= std::min(256l, tiles_of<Proj256x192>(a))) offer(proj_cost<Proj192x256>(a, 1.0, 0, 6.8), launch_proj<Proj192x256, kHeadTok, kTransposedW>, 1);
+    if (large && tiles_of<Proj192x256>(a) <= std::min(256l, std::max(200l, tiles_of<Proj256x192>(a))))
+      offer(proj_cost<Proj192x256>(a, 1.0, 0, 6.8), launch_proj<Proj192x256, kHeadTok, kTransposedW>, 1);
   if constexpr (!kTransposedW || !kHeadTok)
     if (large && tiles_of<Proj256x192>(a) <= 256) offer(proj_cost<Proj256x192>(a, 1.0, 0, 6.8), launch_proj<Proj256x192, kHeadTok, kTransposedW>, 1);
   if constexpr (!kTransposedW)

@@ -292,10 +292,10 @@ def test_one_round_of_eight_wavefronts(B, N, H, E):
     check_bwd(N, B, N, H, E, pad_tail=N // 7)
 
 
-@pytest.mark.parametrize("B,N,H,E", [(8, 442, 12, 768), (5, 700, 12, 768), (40, 250, 16, 1024)])
+@pytest.mark.parametrize("B,N,H,E", [(8, 442, 12, 768), (5, 700, 12, 768), (40, 250, 16, 1024), (12, 161, 16, 1024)])
 def test_one_round_of_192_by_256(B, N, H, E):
     """Tiles of 192 x 256 in one round, fewer than of 256 x 192 or as many (180): QKV of the first two sizes (the last token tile
-    186 and 188 rows), the output of the last (its last feature tile a third)."""
+    186 and 188 rows), the output of the third (its last feature tile a third).  And 192 of them where 256 x 192 has 144: QKV of the last."""
     check(N, B, N, H, E, pad_tail=N // 7)
 
 
