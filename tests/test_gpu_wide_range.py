@@ -21,22 +21,28 @@ pytestmark = pytest.mark.gpu
 ROW, COL = synth.HEAD_ROW, synth.HEAD_COL
 
 
-def check(w, dense=False, bucketed=None, backward=True, pairs=None, label=""):
+def check(w, dense=False, bucketed=None, backward=True, pairs=None, label="", short=False):
     print(f"wide-range case {label or w.name} dtype={w.dtype} shape={w.shape} dense={dense} "
           f"bucketed={bucketed}", flush=True)
     got, seg = hp.run_hip(w, backward, dense=dense, bucketed=bucketed)
     if seg is not None:
         hp.compare_segments(seg, w.structure, bucketed=bucketed)
     ref = hp.run_oracle(w, backward, pairs, bucketed=bucketed)
-    slack = None
+    slack = mean_slack = None
     if backward and w.dtype == "bf16":
         # forward results are held to the usual bounds; gradients get twice what the bf16 format
         # itself costs on inputs of this magnitude (helpers.format_cost) on top of them
         cost = hp.format_cost(w, sorted(ref), bucketed=bucketed)
         slack = {bh: {n: 2.0 * c[n] for n in ("dq", "dk", "dv")} for bh, c in cost.items()}
+        if short:
+            # In a short sequence most queries have one key with nearly all the weight, so dS = P (dP - delta) is a difference that
+            # nearly cancels, and the rounding of O in delta is a larger share of it: the format alone has a mean-rel of up to 1.6e-2 in dQ
+            # on these inputs.  Its own mean-rel is allowed on top of 1e-2, once.
+            mean_slack = {bh: {n: c[n + "_mean"] for n in ("dq", "dk", "dv")} for bh, c in cost.items()}
+            print("   bf16 format mean-rel:", {n: f"{max(c[n + '_mean'] for c in cost.values()):.2e}" for n in ("dq", "dk", "dv")}, flush=True)
         print("   bf16 format cost (max |model - oracle|):",
               {n: f"{max(c[n] for c in cost.values()):.2e}" for n in ("o", "dq", "dk", "dv")}, flush=True)
-    print(hp.report(hp.compare(got, ref, w, label or w.name, slack=slack)), flush=True)
+    print(hp.report(hp.compare(got, ref, w, label or w.name, slack=slack, mean_slack=mean_slack)), flush=True)
 
 
 def test_segment_path_wide_scores():
@@ -88,6 +94,16 @@ def test_segment_path_wide_scores_long_segments_and_batch():
 def test_dense_path_wide_scores():
     w = wide_workload(5, "bf16", N=1024, n_global=70, rows=30, cols=5, mean_cell=5.0, B=2)
     check(w, dense=True)
+
+
+@pytest.mark.parametrize("N,B,H,dense_rows", [(64, 2, 2, 6), (128, 2, 2, 9), (160, 2, 2, 12), (192, 2, 2, 14), (160, 33, 4, 12), (192, 33, 4, 14),
+                                              (200, 2, 2, 15), (256, 2, 2, 20)])
+def test_short_dense_path_wide_scores(N, B, H, dense_rows):
+    """The forward that has all scores of a query at once (four, eight and, for more than 128 pairs, twelve wavefronts), the backward of sixteen
+    keys a wavefront (up to 192 positions) and that of 32 (beyond).  In the large batches four pairs go through the oracle."""
+    w = wide_workload(N + B, "bf16", N=N, n_global=max(4, N // 12), rows=dense_rows, cols=4, mean_cell=2.5, B=B, H=H)
+    pairs = [(0, 0), (1, H - 1), (B // 2, 0), (B - 1, H - 1)] if B > 2 else None
+    check(w, dense=True, pairs=pairs, label=f"wide dense {B} x {N}", short=True)
 
 
 @pytest.mark.parametrize("mode", [(116, 42), (40, 64)])
