@@ -620,7 +620,7 @@ __global__ __launch_bounds__(64 * SmallShape::kWaves, 2) void bwd_dense_small_ke
   const bool active = wave < n_blocks;
   f32x16 dk_acc[2] = {zero16(), zero16()}, dv_acc[2] = {zero16(), zero16()};
 
-  for (int p = 0; p < S::kPasses && p * S::kBlocks < n_blocks; ++p) {
+  for (int p = 0; p < S::kPasses; ++p) {
     if (p > 0) {
       __syncthreads();  // the staged dQ rows of the pass before have been stored
       stream_rows(Q, p * S::kQueries, queries, qt);
