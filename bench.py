@@ -628,9 +628,9 @@ def main():
         "roofline": {"bound": "mfma", "kernel": dom, "achieved": ach, "peak": PEAK_BF16_TFLOPS,
                      "unit": "TFLOP/s", "frac": ach / PEAK_BF16_TFLOPS, "traffic": traffic, "traffic_detail": traffic_detail,
                      "frac_of_measured_peak": ach / mfma_tflops,
-                     "limiter": "the kernel is a dense contraction, so it is priced against the matrix peak; what "
-                                "limits it today is SIMD issue time (vector ALU + matrix instructions taking turns) "
-                                "and per-unit latency, see profiles/" + w.name + "_sq_counters_pmc.txt",
+                     "limiter": "the kernel is a dense contraction, so it is priced against the matrix peak; most of its time "
+                                "today is SIMD issue (vector ALU and matrix instructions, which overlap only partly), and a quarter "
+                                "to a third is waiting and the start and end of units, see profiles/" + w.name + "_sq_counters_pmc.txt",
                      "algorithmic_flop_per_launch": cand[dom][0],
                      "avg_launch_us": cand[dom][1] * 1e6, "median_launch_us": kernel_median_s[{"fwd_mfma_kernel": "attn_fwd", "bwd_dq_mfma_kernel": "attn_bwd_dq", "bwd_dkv_mfma_kernel": "attn_bwd_dkv"}[dom]] * 1e6,
                      "hbm_view": {"algorithmic_bytes_per_launch": alg_bytes, "achieved": hbm_gbs,

@@ -4,15 +4,17 @@
 // plain attention under the mask of Section 3 -- and picks the faster per use case, because at
 // short lengths the cost of reordering outweighs the saved work.  Here the reordered path is
 // mate_build_segments + mate_attn_fwd / mate_attn_bwd; this file is the other one: no segment
-// tables, no sort, no gathers.  A workgroup owns 128 consecutive positions of one
-// (sequence, head) and streams every 64-position tile of the sequence; each (query, key) pair is
+// tables, no sort, no gathers.  A workgroup has a whole (sequence, head) in LDS, up to 128 positions
+// (192 for some numbers of pairs) in the forward and 256 in the backward; of longer sequences it owns 128
+// consecutive positions and streams every 64-position tile.  Each (query, key) pair is
 // scored and then kept or dropped by comparing the two tokens' codes
 //     code = row id + 1 (row heads) / column id + 1 (column heads) for a table token,
 //            0 for a question token, kPadCode for padding
 //     allowed = both are not padding, and they are equal or one is a question token
 // which is the attention pattern A^i_k of Section 3 written per pair.  The arithmetic (base-2
-// online softmax, bf16 P and dS, fp32 accumulation, accumulators of the dK/dV kernel started at
-// -lse / scale and -delta) is that of the segment kernels, so both paths meet the same oracle.
+// softmax, online where keys are streamed and with one maximum where all are there, bf16 P and dS, fp32
+// accumulation, accumulators of dK and dV started at -lse / scale and -delta) is that of the segment
+// kernels, so both paths meet the same oracle.
 #include <hip/hip_runtime.h>
 
 #include "d2l.h"
@@ -263,14 +265,14 @@ __global__ __launch_bounds__(kThreads) void fwd_dense_kernel(const void* q, cons
 }
 
 // ======================================================================================
-// forward of up to 128 positions
+// forward of up to 128 positions, and of up to 192 where launch_fwd_dense says so
 // ======================================================================================
 // One workgroup per (sequence, head), whose keys and values are in LDS at once; wavefront w owns queries 16 w .. 16 w + 15.  All scores
 // of a query are there before the first is used, so there is one maximum and nothing to rescale, and one barrier.  Like the backward
 // below, such a launch is as long as a wavefront's own chain.
-// us, before (128 queries a workgroup, 32 a wavefront) and so: 64 x 64 positions, 16 heads 7.3 -> 5.6, 64 x 33 7.0 -> 5.1, 17 x 64 5.5 -> 4.5, one
-// sequence of 64, 4 heads 4.6 -> 4.2; 128 positions, 1 x, 4 heads 5.6 -> 5.1, 16 x, 16 heads 6.2 -> 5.6, 32 x, 12 heads 7.25 -> 6.85, 43 x 8.9 -> 8.1,
-// 64 x, 12 heads 11.05 -> 11.2, 16 heads 14.2 -> 13.9; 40 x 96, 16 heads 8.9 -> 7.05.
+// us, before (128 queries a workgroup, 32 a wavefront) and so: 80 x 64 positions, 16 heads 9.1 -> 6.0, 24 x 33, 4 heads 4.1 -> 3.0, one sequence of 53
+// 4.05 -> 3.05; 128 positions, 1 x, 4 heads 5.2 -> 4.55, 32 x, 12 heads 7.6 -> 6.85, 48 x 9.3 -> 8.5, 64 x 10.8 -> 9.7, 86 x 16.0 -> 15.3, 64 x, 16
+// heads 14.4 -> 14.2, 128 x 24.65 -> 24.4; 64 x 100, 12 heads 9.6 -> 8.8.  With scores that rise late, where the form before starts tiles again, 32 x 128 8.7 -> 6.7.
 template <int NW>
 struct ShortShape {
   static constexpr int kRows = 16 * NW;                   // most positions
@@ -745,9 +747,10 @@ __global__ __launch_bounds__(64 * SmallShape::kWaves, 2) void bwd_dense_small_ke
 // barrier after dQ's.  Such a launch is one or two workgroups on a compute unit that load, compute and store at the same time, so it is
 // as long as a wavefront's own chain, which is half as long here.  Every wavefront reads all of Q and dO, plain and transposed, so LDS
 // reads double, and from 193 positions on those bound it (14 wavefronts: 1 x 224, 12 heads 15.4 -> 15.7, 32 x 224 35.5 -> 36.8).
-// us, 32 keys a wavefront and sixteen: 64 x 64 positions, 16 heads 13.3 -> 11.7, 48 x 64 9.4 -> 7.4, 17 x 64 7.4 -> 5.6, one sequence of 64,
-// 4 heads 6.1 -> 4.9; 128 positions, 1 x, 4 heads 7.8 -> 7.4, 16 x, 16 heads 8.9 -> 8.4, 32 x, 12 heads 12.2 -> 11.8, 33 x, 16 heads 19.4 -> 18.2,
-// 64 x 27.2 -> 26.6, 24 x, 12 heads 11.1 -> 11.0; 40 x 96, 16 heads 16.7 -> 14.4; 8 x 160, 12 heads 12.6 -> 10.1, 40 x 160, 16 heads 41.9 -> 35.9; 8 x 192, 12 heads 14.0 -> 12.1, 40 x 192, 16 heads
+// LDS banks: dS^T goes in by rows whose swizzle does not know bit 2, so those writes and the staged results meet in banks, 0.75 cycles per LDS instruction.
+// us, 32 keys a wavefront and sixteen: 80 x 64 positions, 16 heads 17.7 -> 14.6, 64 x 64 13.3 -> 11.7, 48 x 64 9.4 -> 7.4, 17 x 64 7.4 -> 5.6, one sequence of 64,
+// 4 heads 5.7 -> 4.25; 128 positions, 1 x, 4 heads 7.6 -> 7.0, 32 x, 12 heads 12.85 -> 11.75, 48 x 20.0 -> 18.6, 64 x, 16 heads
+// 27.7 -> 26.1, 128 x 49.0 -> 48.6; 40 x 96, 16 heads 16.7 -> 14.4; 8 x 160, 12 heads 12.6 -> 10.1, 40 x 160, 16 heads 41.9 -> 35.9; 8 x 192, 12 heads 14.0 -> 12.1, 40 x 192, 16 heads
 // 47.8 -> 43.7.
 template <int NW, bool kThrough>
 __global__ __launch_bounds__(64 * NW, 4) void bwd_dense_short_kernel(

@@ -4,7 +4,7 @@
 //   A (32 x 16): lane holds row m,    k = 8*hl .. 8*hl+7   (8 bf16 = 16 bytes)
 //   B (16 x 32): lane holds column m, k = 8*hl .. 8*hl+7
 //   C (32 x 32): lane holds column m, register c = 4*g + r  <->  row 8*g + 4*hl + r
-// and, in the backward and the dense forward of up to 128 positions, v_mfma_f32_16x16x32_bf16, lane l = 16*q + r (r = l % 16):
+// and, in the backward, the short dense forward and the projections, v_mfma_f32_16x16x32_bf16, lane l = 16*q + r (r = l % 16):
 //   A (16 x 32): lane holds row r,    k = 8*q .. 8*q+7
 //   B (32 x 16): lane holds column r, k = 8*q .. 8*q+7
 //   C (16 x 16): lane holds column r, register e  <->  row 4*q + e

@@ -1,5 +1,5 @@
 // Measurement aid, not part of the computation: a kernel that does nothing but issue independent
-// 32x32x16 bf16 MFMAs (the instruction the attention and projection kernels use), so that the
+// 32x32x16 bf16 MFMAs (the attention forward's instruction; the backward and the projections use 16x16x32), so that the
 // benchmark can time what the matrix cores of the box it runs on deliver under sustained load,
 // next to the nominal peak.
 #include <hip/hip_runtime.h>

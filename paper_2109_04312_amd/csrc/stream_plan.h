@@ -501,6 +501,7 @@ __device__ __forceinline__ void stage_rows(const f32x16& a, float mul, char* sta
 // The same of 16 x 16 tiles, [16 dims][16 owned rows]: register e of lane 16 q + r is dim 16 d + 4 q + e of row 16 cb + r.
 // They stay quads of registers from the loop to the stores: gathered into sixteen neighbours each, dK and dV took 158 moves at the end of
 // every unit (see QuadAddr for what the two cost together).
+// (Rows r and r + 8 of a write meet in one bank.)
 typedef f32x4 QuadAcc[4][2];
 __device__ __forceinline__ void stage_rows_quad(const f32x4 (&a)[2], float mul, char* stage, int row0, int d, int lane) {
   const int r = lane & 15, q = lane >> 4;

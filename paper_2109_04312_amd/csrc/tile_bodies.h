@@ -241,9 +241,13 @@ __device__ __forceinline__ void fwd_tile(unsigned tile, const bf16x8 (&qf)[4], c
 // The backward's tiles are 16 x 16 (16x16x32 instructions).  They move half as many accumulator bytes per operation; a lane's four registers of a
 // row block can all start at the same value, so dP - delta comes out of dQ's product too; and -lse / scale and -delta of a block are read once for both
 // blocks of owned rows.  Operand reads are told to go ahead of the products: left to itself the compiler reads one operand of the second
-// contraction, waits, multiplies and reads the next.  us, with 32 x 32 tiles and so: 2 x 8192, 16 heads dQ 58.9 -> 54.5 and dK/dV 73.5 ->
-// 68.7, 8 x 2048 with long cells 56.1 -> 53.1 and 70.4 -> 66.4, 16 ragged sequences of 4096 164.0 -> 160.2 and 215.3 -> 209.0, 32 x 512, 12
-// heads 32.0 -> 31.8 and 35.7 -> 35.1.  (The forward, whose vector part is larger, gains 2 % at 2 x 8192 and loses 1 to 3 %
+// contraction, waits, multiplies and reads the next.  us by the kernel trace, both in turn, with 32 x 32 tiles and so: 2 x 8192, 16 heads dQ 61.9 -> 58.4
+// and dK/dV 76.9 -> 73.9, 8 x 2048 with long cells 58.5 -> 55.1 and 73.0 -> 69.0, 16 ragged sequences of 4096 166.9 -> 160.3 and 220.7 -> 211.5, 32 x
+// 512, 12 heads 32.9 -> 32.6 and 37.0 -> 36.3.  By the counters of 2 x 8192 wavefronts wait less (41.1 to 33.1 million of dK/dV's cycle counts) with as many
+// vector instructions (11.6 million without the matrix ones); the kernels are 1 and 2 % shorter in cycles (109 and 137 thousand), and the rest is clock, which
+// matrix instructions that move fewer bytes leave higher.  220 launches of 257 to 9000 tokens a sequence: 2.2 % shorter in the mean, up to 4 % longer where dQ and
+// dK/dV are one launch (3 x 428, 12 heads, 57 question tokens 13.15 and 13.55, 5 x 381, 16 heads 14.7 and 15.1; run one after the other both kernels are
+// shorter there too, and single sequences are 4 to 5 % shorter in one launch).  (The forward, whose vector part is larger, gains 2 % at 2 x 8192 and loses 1 to 3 %
 // elsewhere: half of its instructions are exponentials and their sums, and a short unit's beginning and end take longer.)
 //
 // dQ: P = exp2(S sc - lse2), dP^T - delta = V dO^T - delta, dS = P (dP - delta), dQ^T += K^T dS^T; one 32-key block
